@@ -7,106 +7,164 @@ namespace svdc {
 
 namespace {
 
-constexpr int kOvRows = 16;      // rows of M per workgroup
-constexpr int kOvDepth = 32;     // channels staged per step
-constexpr int kOvMaxRank = 128;  // overlap / re-basing work up to this rank
+constexpr int kMaxRank = 128;    // overlap / re-basing work up to this rank
 
-// M[b][i][j] = sum_d V_old[b][d][i] * V_new[b][d][j].  Grid (ceil(k / 16), B); thread (ti, tj) of the
-// 16 x 16 arrangement owns M[i0 + ti][tj + 16 c], c = 0..7.  The sum runs over d in ascending order.
-template <int KC>   // column tiles of 16 that hold data: ceil(k / 16), a compile-time loop bound
-__global__ __launch_bounds__(256) void basis_overlap_kernel(const float* __restrict__ Vo,
-                                                            const float* __restrict__ Vn, float* M, int D, int k) {
-  __shared__ float so[kOvDepth][kOvRows + 1];
-  __shared__ float sn[kOvDepth][kOvMaxRank + 1];
-  const int b = blockIdx.y, i0 = blockIdx.x * kOvRows, t = threadIdx.x, ti = t >> 4, tj = t & 15;
-  const float* vo = Vo + (int64_t)b * D * k;
-  const float* vn = Vn + (int64_t)b * D * k;
-  float acc[KC];
-#pragma unroll
-  for (int c = 0; c < KC; ++c) acc[c] = 0.f;
-  for (int d0 = 0; d0 < D; d0 += kOvDepth) {
-    for (int e = t; e < kOvDepth * kOvRows; e += 256) {
-      const int dd = e / kOvRows, ii = e % kOvRows, d = d0 + dd, i = i0 + ii;
-      so[dd][ii] = (d < D && i < k) ? vo[(int64_t)d * k + i] : 0.f;
-    }
-    for (int e = t; e < kOvDepth * 16 * KC; e += 256) {       // columns beyond k are staged as zeros
-      const int dd = e / (16 * KC), jj = e % (16 * KC), d = d0 + dd;
-      sn[dd][jj] = (d < D && jj < k) ? vn[(int64_t)d * k + jj] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (int dd = 0; dd < kOvDepth; ++dd) {
-      const float a = so[dd][ti];
-#pragma unroll
-      for (int c = 0; c < KC; ++c) acc[c] = __builtin_fmaf(a, sn[dd][tj + 16 * c], acc[c]);
-    }
-    __syncthreads();
-  }
-  if (i0 + ti < k) {
-#pragma unroll
-    for (int c = 0; c < KC; ++c)
-      if (tj + 16 * c < k) M[((int64_t)b * k + i0 + ti) * k + tj + 16 * c] = acc[c];
-  }
+// v_mfma_f32_16x16x4_f32: lane (r = lane % 16, g = lane / 16) holds A[m = r][kk = g], B[kk = g][n = r] and the four
+// results D[m = 4 g + i][n = r].
+__device__ __forceinline__ f32x4 mfma_f32(float a, float b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-// S_out[row][j] = sum_i S_in[row][i] * M[i][j]: one wavefront per row, M of the block in LDS.  S_out may
-// be S_in: a row is staged in LDS completely before it is written.  Every wave of a workgroup runs the same
-// number of iterations (rows beyond N are skipped by predicate), so the barriers are uniform.
+// M[b][i][j] = sum_d V_old[b][d][i] * V_new[b][d][j], a 16 x 16 tile of M per workgroup, grid (tiles, B).  What bounds
+// it is the latency of the loads: a tile's contraction over D rows of 64 bytes from each basis is spread over the 16
+// waves of the workgroup (float32 matrix instructions, 16 independent loads in flight per wave), whose partial sums
+// are added in wave order.  One wave per row of the tile walking over all D channels through LDS, as this was done
+// before, took 201 us at 3072 channels, rank 32, one block (242 us for 57, 362 us at rank 64); this takes 9.6 us
+// (28 and 13 us).  D is a multiple of 4 (svdc_shape); columns beyond k are clamped, their results are not stored.
+constexpr int kOvWaves = 16;
+__global__ __launch_bounds__(64 * kOvWaves) void basis_overlap_kernel(const float* __restrict__ Vo,
+                                                                      const float* __restrict__ Vn, float* M, int D,
+                                                                      int k) {
+  __shared__ f32x4 part[kOvWaves][64];
+  const int b = blockIdx.y, tiles = (k + 15) / 16;
+  const int i0 = (blockIdx.x / tiles) * 16, j0 = (blockIdx.x % tiles) * 16;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const float* vo = Vo + (int64_t)b * D * k + min(i0 + r, k - 1);
+  const float* vn = Vn + (int64_t)b * D * k + min(j0 + r, k - 1);
+  // steps of 4 channels, wave w takes w, w + 16, ...; two accumulators
+  f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+  const int nstep = D / 4;
+  constexpr int U = 8;
+  int st = wave;
+  for (; st + (U - 1) * kOvWaves < nstep; st += U * kOvWaves) {
+    float x[U], y[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t at = (int64_t)(4 * (st + u * kOvWaves) + g) * k;
+      x[u] = vo[at];
+      y[u] = vn[at];
+    }
+#pragma unroll
+    for (int u = 0; u < U; u += 2) {
+      acc0 = mfma_f32(x[u], y[u], acc0);
+      acc1 = mfma_f32(x[u + 1], y[u + 1], acc1);
+    }
+  }
+  for (; st < nstep; st += kOvWaves) {
+    const int64_t at = (int64_t)(4 * st + g) * k;
+    acc0 = mfma_f32(vo[at], vn[at], acc0);
+  }
+  part[wave][lane] = f32x4{acc0[0] + acc1[0], acc0[1] + acc1[1], acc0[2] + acc1[2], acc0[3] + acc1[3]};
+  __syncthreads();
+  const int t = threadIdx.x;
+  if (t >= 256) return;
+  const int row = t >> 4, col = t & 15;                 // element of the tile; it sits in lane (col, row / 4), word row % 4
+  float s = 0.f;
+#pragma unroll
+  for (int w = 0; w < kOvWaves; ++w) s += part[w][(row >> 2) * 16 + col][row & 3];
+  if (i0 + row < k && j0 + col < k) M[((int64_t)b * k + i0 + row) * k + j0 + col] = s;
+}
+
+// S_out[row][j] = sum_i S_in[row][i] * M[i][j] on the float32 matrix cores, KT = ceil(k / 16).  M sits in LDS (row stride
+// 16 KT + 4 floats: the four rows that the lane groups of an operand read fall into different banks); a wave brings a
+// tile of 16 rows of S into registers before it writes any of it, so S_out may be S_in.  The contraction index of
+// step (s, e) is i = 16 s + 4 g + e, so that a lane's four steps are one 16-byte piece of its row (VEC: k a multiple of 4
+// and 16-byte aligned states; otherwise four loads).  It streams S: 27 -> 4.9 us at 4608 x 32 and 97 -> 18 us for 57
+// such blocks (3.7 TB/s) against one wave per row with a chain of k dependent LDS reads and multiply-adds.
+template <int KT, bool VEC>
 __global__ __launch_bounds__(256) void rebase_state_kernel(const float* __restrict__ M, const float* Sin, float* Sout,
-                                                           int N, int k, int rows_per_group) {
-  extern __shared__ float lds[];
-  float* m = lds;                       // [k][k]
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  float* srow = lds + k * k + wave * k;
+                                                           int N, int k, int tiles_per_wave) {
+  extern __shared__ float m[];          // [16 KT][LS]
+  constexpr int LS = 16 * KT + 4;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
   const int b = blockIdx.y;
-  for (int e = threadIdx.x; e < k * k; e += 256) m[e] = M[(int64_t)b * k * k + e];
-  const int r0 = blockIdx.x * rows_per_group;
-  for (int rr = 0; rr < rows_per_group; rr += 4) {
-    const int row = r0 + rr + wave;
-    const bool valid = row < N && rr + wave < rows_per_group;
-    const int64_t off = ((int64_t)b * N + row) * k;
-    __syncthreads();                    // M loaded / previous row consumed
-    if (valid)
-      for (int j = lane; j < k; j += kWave) srow[j] = Sin[off + j];
-    __syncthreads();
-    if (valid)
-      for (int j = lane; j < k; j += kWave) {
-        float acc = 0.f;
-        for (int i = 0; i < k; ++i) acc = __builtin_fmaf(srow[i], m[i * k + j], acc);
-        Sout[off + j] = acc;
+  const float* mg = M + (int64_t)b * k * k;
+  for (int e = threadIdx.x; e < 16 * KT * 16 * KT; e += 256) {
+    const int i = e / (16 * KT), j = e % (16 * KT);
+    m[i * LS + j] = (i < k && j < k) ? mg[i * k + j] : 0.f;
+  }
+  __syncthreads();
+  for (int q = 0; q < tiles_per_wave; ++q) {
+    const int row0 = ((blockIdx.x * tiles_per_wave + q) * 4 + wave) * 16;
+    if (row0 >= N) return;
+    const float* src = Sin + ((int64_t)b * N + min(row0 + r, N - 1)) * k;
+    float a[KT][4];
+#pragma unroll
+    for (int s = 0; s < KT; ++s) {
+      const int i = 16 * s + 4 * g;
+      if constexpr (VEC) {
+        f32x4 x = {0.f, 0.f, 0.f, 0.f};
+        if (i < k) x = *reinterpret_cast<const f32x4*>(src + i);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[s][e] = x[e];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[s][e] = i + e < k ? src[i + e] : 0.f;
+      }
+    }
+    f32x4 acc[KT];
+#pragma unroll
+    for (int jt = 0; jt < KT; ++jt) acc[jt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < KT; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int jt = 0; jt < KT; ++jt)
+          acc[jt] = mfma_f32(a[s][e], m[(16 * s + 4 * g + e) * LS + 16 * jt + r], acc[jt]);
+#pragma unroll
+    for (int jt = 0; jt < KT; ++jt)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = row0 + 4 * g + i;
+        if (row < N && 16 * jt + r < k) Sout[((int64_t)b * N + row) * k + 16 * jt + r] = acc[jt][i];
       }
   }
 }
 
 // Fig. 1(b): cosine similarity times magnitude similarity for every pair of basis directions and for the two
-// singular-value vectors.  One workgroup per block; wave w takes the directions w, w + 4, ...
-__global__ __launch_bounds__(256) void basis_similarity_kernel(const float* __restrict__ Va,
-                                                               const float* __restrict__ sa,
-                                                               const float* __restrict__ Vb,
-                                                               const float* __restrict__ sb, float* sim_dir,
-                                                               float* sim_sigma, int D, int k) {
-  const int b = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const float* va = Va + (int64_t)b * D * k;
-  const float* vb = Vb + (int64_t)b * D * k;
+// singular-value vectors, float64 sums.  A workgroup takes 16 columns of both bases: 16 neighbouring threads read 64
+// consecutive bytes of a row, the 64 groups of 16 threads take every 64th row.  (One wave per column read 4 bytes of
+// every row: 89 us at 3072 channels, rank 32, one block, 150 us for 57, against 7.3 and 18 us.)
+constexpr int kSimThreads = 1024;
+__global__ __launch_bounds__(kSimThreads) void basis_similarity_kernel(const float* __restrict__ Va,
+                                                                       const float* __restrict__ sa,
+                                                                       const float* __restrict__ Vb,
+                                                                       const float* __restrict__ sb, float* sim_dir,
+                                                                       float* sim_sigma, int D, int k) {
+  constexpr int kRowGroups = kSimThreads / 16, kWaves = kSimThreads / 64;
+  __shared__ double part[kWaves][16][3];
+  const int b = blockIdx.y, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = threadIdx.x & 15;
+  const int j = blockIdx.x * 16 + c;
+  const float* va = Va + (int64_t)b * D * k + min(j, k - 1);
+  const float* vb = Vb + (int64_t)b * D * k + min(j, k - 1);
   auto score = [](double dot, double na2, double nb2, bool take_abs) -> float {
     if (!(na2 > 0.0) || !(nb2 > 0.0)) return 0.f;
     const double na = sqrt(na2), nb = sqrt(nb2);
-    const double c = (take_abs ? fabs(dot) : dot) / (na * nb);
-    return (float)(c * (na < nb ? na / nb : nb / na));
+    const double co = (take_abs ? fabs(dot) : dot) / (na * nb);
+    return (float)(co * (na < nb ? na / nb : nb / na));
   };
-  for (int j = wave; j < k; j += 4) {
-    double dot = 0.0, na = 0.0, nb = 0.0;
-    for (int d = lane; d < D; d += kWave) {
-      const double x = va[(int64_t)d * k + j], y = vb[(int64_t)d * k + j];
-      dot += x * y; na += x * x; nb += y * y;
-    }
-    dot = wave_sum(dot); na = wave_sum(na); nb = wave_sum(nb);
-    if (lane == 0) sim_dir[(int64_t)b * k + j] = score(dot, na, nb, true);
+  double dot = 0.0, na = 0.0, nb = 0.0;
+#pragma unroll 8
+  for (int d = threadIdx.x >> 4; d < D; d += kRowGroups) {
+    const double x = va[(int64_t)d * k], y = vb[(int64_t)d * k];
+    dot += x * y; na += x * x; nb += y * y;
   }
-  if (wave == 0 && sim_sigma) {
-    double dot = 0.0, na = 0.0, nb = 0.0;
-    for (int j = lane; j < k; j += kWave) {
-      const double x = sa[(int64_t)b * k + j], y = sb[(int64_t)b * k + j];
+#pragma unroll
+  for (int o = 16; o < kWave; o <<= 1) {      // the four row groups of a wave
+    dot += __shfl_xor(dot, o, kWave); na += __shfl_xor(na, o, kWave); nb += __shfl_xor(nb, o, kWave);
+  }
+  if (lane < 16) { part[wave][c][0] = dot; part[wave][c][1] = na; part[wave][c][2] = nb; }
+  __syncthreads();
+  if (threadIdx.x < 16 && j < k) {
+    dot = na = nb = 0.0;
+    for (int w = 0; w < kWaves; ++w) { dot += part[w][c][0]; na += part[w][c][1]; nb += part[w][c][2]; }
+    sim_dir[(int64_t)b * k + j] = score(dot, na, nb, true);
+  }
+  if (blockIdx.x == 0 && wave == 1 && sim_sigma) {
+    dot = na = nb = 0.0;
+    for (int i = lane; i < k; i += kWave) {
+      const double x = sa[(int64_t)b * k + i], y = sb[(int64_t)b * k + i];
       dot += x * y; na += x * x; nb += y * y;
     }
     dot = wave_sum(dot); na = wave_sum(na); nb = wave_sum(nb);
@@ -116,38 +174,52 @@ __global__ __launch_bounds__(256) void basis_similarity_kernel(const float* __re
 
 }  // namespace
 
-bool rebase_rank_supported(int k) { return k >= 1 && k <= kOvMaxRank; }
+bool rebase_rank_supported(int k) { return k >= 1 && k <= kMaxRank; }
 
 int32_t launch_basis_overlap(const svdc_shape& s, const float* V_old, const float* V_new, float* M, hipStream_t st) {
-  dim3 grid((s.k + kOvRows - 1) / kOvRows, s.B);
-  switch ((s.k + 15) / 16) {
-    case 1: basis_overlap_kernel<1><<<grid, 256, 0, st>>>(V_old, V_new, M, s.D, s.k); break;
-    case 2: basis_overlap_kernel<2><<<grid, 256, 0, st>>>(V_old, V_new, M, s.D, s.k); break;
-    case 3: basis_overlap_kernel<3><<<grid, 256, 0, st>>>(V_old, V_new, M, s.D, s.k); break;
-    case 4: basis_overlap_kernel<4><<<grid, 256, 0, st>>>(V_old, V_new, M, s.D, s.k); break;
-    case 5: basis_overlap_kernel<5><<<grid, 256, 0, st>>>(V_old, V_new, M, s.D, s.k); break;
-    case 6: basis_overlap_kernel<6><<<grid, 256, 0, st>>>(V_old, V_new, M, s.D, s.k); break;
-    case 7: basis_overlap_kernel<7><<<grid, 256, 0, st>>>(V_old, V_new, M, s.D, s.k); break;
-    default: basis_overlap_kernel<8><<<grid, 256, 0, st>>>(V_old, V_new, M, s.D, s.k); break;
-  }
+  const int tiles = (s.k + 15) / 16;
+  basis_overlap_kernel<<<dim3(tiles * tiles, s.B), 64 * kOvWaves, 0, st>>>(V_old, V_new, M, s.D, s.k);
   return launch_status();
 }
 
+namespace {
+
+template <int KT>
+int32_t rebase_launch(const svdc_shape& s, const float* M, const float* S_in, float* S_out, hipStream_t st) {
+  const size_t lds = (size_t)16 * KT * (16 * KT + 4) * sizeof(float);
+  // M of rank 65..128 is 37-66 KB: two row tiles per wave for each copy of it
+  const int tiles_per_wave = KT > 4 ? 2 : 1;
+  const bool vec = s.k % 4 == 0 && ((reinterpret_cast<uintptr_t>(S_in) | reinterpret_cast<uintptr_t>(S_out)) & 15) == 0;
+  auto launch = [&](auto kernel) -> int32_t {
+    if (lds > 48 * 1024 && hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               (int)lds) != hipSuccess)
+      return SVDC_E_HIP;
+    const int rows = 64 * tiles_per_wave;
+    kernel<<<dim3((s.N + rows - 1) / rows, s.B), 256, lds, st>>>(M, S_in, S_out, s.N, s.k, tiles_per_wave);
+    return launch_status();
+  };
+  return vec ? launch(rebase_state_kernel<KT, true>) : launch(rebase_state_kernel<KT, false>);
+}
+
+}  // namespace
+
 int32_t launch_rebase_state(const svdc_shape& s, const float* M, const float* S_in, float* S_out, hipStream_t st) {
-  const size_t lds = ((size_t)s.k * s.k + 4 * (size_t)s.k) * sizeof(float);
-  if (lds > 48 * 1024 &&
-      hipFuncSetAttribute((const void*)rebase_state_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
-          hipSuccess)
-    return SVDC_E_HIP;
-  const int rows_per_group = 64;
-  dim3 grid((s.N + rows_per_group - 1) / rows_per_group, s.B);
-  rebase_state_kernel<<<grid, 256, lds, st>>>(M, S_in, S_out, s.N, s.k, rows_per_group);
-  return launch_status();
+  switch ((s.k + 15) / 16) {
+    case 1: return rebase_launch<1>(s, M, S_in, S_out, st);
+    case 2: return rebase_launch<2>(s, M, S_in, S_out, st);
+    case 3: return rebase_launch<3>(s, M, S_in, S_out, st);
+    case 4: return rebase_launch<4>(s, M, S_in, S_out, st);
+    case 5: return rebase_launch<5>(s, M, S_in, S_out, st);
+    case 6: return rebase_launch<6>(s, M, S_in, S_out, st);
+    case 7: return rebase_launch<7>(s, M, S_in, S_out, st);
+    default: return rebase_launch<8>(s, M, S_in, S_out, st);
+  }
 }
 
 int32_t launch_basis_similarity(const svdc_shape& s, const float* V_a, const float* sigma_a, const float* V_b,
                                 const float* sigma_b, float* sim_dir, float* sim_sigma, hipStream_t st) {
-  basis_similarity_kernel<<<s.B, 256, 0, st>>>(V_a, sigma_a, V_b, sigma_b, sim_dir, sim_sigma, s.D, s.k);
+  basis_similarity_kernel<<<dim3((s.k + 15) / 16, s.B), kSimThreads, 0, st>>>(V_a, sigma_a, V_b, sigma_b, sim_dir,
+                                                                              sim_sigma, s.D, s.k);
   return launch_status();
 }
 

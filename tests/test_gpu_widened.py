@@ -340,6 +340,42 @@ def test_basis_similarity(B, D, k):
     assert torch.equal(sd, sd2)
 
 
+@pytest.mark.parametrize("B,N,D,k", [(1, 15, 12, 4), (2, 129, 260, 16), (1, 65, 1028, 33), (2, 200, 516, 100),
+                                     (1, 129, 2052, 128)])
+def test_basis_kernels_at_the_edges_of_their_tiles(B, N, D, k):
+    """Ragged 16 x 16 tiles of M, ragged row tiles, channel counts that leave a remainder of every unrolled loop, and
+    states whose base address allows no 16-byte access; in place as well."""
+    from oracle import ref_basis_overlap, ref_rebase_state, ref_basis_similarity
+    g = torch.Generator().manual_seed(N + D + k)
+    Va, Vb = (torch.randn(B, D, k, generator=g) / D ** 0.5 for _ in range(2))
+    Va = (Vb + 0.5 * Va).contiguous()
+    S = torch.randn(B, N, k, generator=g)
+    shape = pkg.make_shape(torch.empty(B, max(N, k), D), k)
+    rshape = pkg.make_shape(torch.empty(B, N, max(k, 4) // 4 * 4 + 4), min(k, N))
+    M = torch.empty(B, k, k, device=DEV)
+    sd = torch.empty(B, k, device=DEV)
+    pkg.svdcache_basis_overlap(shape, Va.to(DEV), Vb.to(DEV), M)
+    pkg.svdcache_basis_similarity(shape, Va.to(DEV), None, Vb.to(DEV), None, sd, None)
+    torch.cuda.synchronize()
+    for b in range(B):
+        # float32 sums of D terms of size 1 / D: a few 2^-24
+        assert np.abs(to_np(M[b]) - ref_basis_overlap(to_np(Va[b]), to_np(Vb[b]))).max() <= 5e-6
+        assert np.abs(to_np(sd[b]) - ref_basis_similarity(to_np(Va[b]), np.ones(k), to_np(Vb[b]), np.ones(k))[0]).max() <= 1e-6
+    if rshape.k != k:
+        return
+    for skew in (0, 1):     # 16-byte aligned states, and states one float off
+        buf = torch.empty(B * N * k + skew, device=DEV)
+        Sg = buf[skew:].view(B, N, k)
+        Sg.copy_(S)
+        out = torch.empty(B * N * k + skew, device=DEV)[skew:].view(B, N, k)
+        pkg.svdcache_rebase_state(rshape, M, Sg, out)
+        pkg.svdcache_rebase_state(rshape, M, Sg, Sg)
+        torch.cuda.synchronize()
+        assert torch.equal(out, Sg)
+        for b in range(B):
+            assert_close(to_np(out[b]), ref_rebase_state(to_np(S[b]), to_np(M[b]), "f32"), "f32", f"block {b}")
+
+
 def test_rebase_rejects_ranks_beyond_its_limit():
     shape = pkg.make_shape(torch.empty(1, 200, 256), 160)
     t = torch.empty(1, 256, 160, device=DEV)
