@@ -1,173 +1,376 @@
-// General (any shape, any k <= 1024) kernels for the full-compute step and the
-// cached step.  Plain fp32 vector arithmetic, one wavefront per token row.
-// They are the fallback for shapes the matrix-core kernels do not cover (hidden sizes that are not one of the
-// instantiated multiples of 128, ranks above 128 or not a multiple of 4), for either storage type.
+// General (any shape, any k <= 1024) kernels for the full-compute step and the cached step, on the float32 matrix
+// cores (v_mfma_f32_16x16x4_f32: float32 operands as they are, float32 accumulation).  They serve the shapes that the
+// bf16 matrix-core kernels do not cover (hidden sizes that are not one of the instantiated multiples of 128, ranks above
+// 128 or not a multiple of 4) and calls without a packed basis, for either storage type.
+//
+// v_mfma_f32_16x16x4_f32: lane (r = lane % 16, g = lane / 16) holds A[m = r][kk = g], B[kk = g][n = r] and the four
+// results D[m = 4 g + i][n = r].  The contraction index is permuted so that loads are wide: a lane loads eight
+// consecutive channels 32 c + 8 g + e of its token row, and step e of eight contracts the channels {32 c + 8 g + e}.
+//
+// What bounds them: the matrix pipe (256 flop per clock and compute unit; 40-45 % of its rate is reached) behind the
+// latency of V, which has no packed form here and comes from L2 as it is.  A workgroup holds 16 token rows, so V is
+// read once per 16 rows and not once per row, and the operands of the next 32 channels are requested before the current
+// ones are multiplied.  Measured at 4 x 2173 x 1408 bf16, rank 50: full step 904 -> 67 us, cached step 290 -> 33 us; at
+// 22848 x 2136, rank 21: 1454 -> 108 and 490 -> 67 us, against one wave per token row on the vector units, which read
+// all of V for every row.  Tiles of 32 rows were no faster (half as many waves to hide the latency).
+#include <algorithm>
+#include <type_traits>
+
 #include "svdc_device.h"
 #include "svdc_internal.h"
 
 namespace svdc {
 
-constexpr int kRowsPerGroup = 4;   // one wave64 per row, 256 threads
-constexpr int kMaxRank = 1024;     // coefficients of one row staged in LDS
-constexpr int kChunk = 32;         // columns of V handled per projection pass
+namespace {
 
-// Full-compute step (Eq. 8-11): C = F V, R = F - C V^T, EMA update of S.
-// F and R may alias (in place): each element of a row is read before it is written.
+__device__ __forceinline__ f32x4 mfma_f32(float a, float b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// Eight consecutive channels d .. d + 7 of a token row; channels at or beyond D read as zero (D is a multiple of 8 for
+// bf16 and of 4 for float32, d of 8).
 template <typename T>
-__global__ __launch_bounds__(256) void full_step_general_kernel(const T* F, const float* __restrict__ V, T* R,
-                                                                const T* Rp, float alpha_r, float* S, float* C,
-                                                                int N, int D, int k, int64_t ldf, int64_t bstride,
-                                                                float alpha, int init) {
-  __shared__ float csh[kRowsPerGroup][kMaxRank];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int b = blockIdx.y;
-  const int64_t row = (int64_t)blockIdx.x * kRowsPerGroup + wave;
-  const bool valid = row < N;  // uniform within the wave
-  const T* f = F + (int64_t)b * bstride + (valid ? row : 0) * ldf;
-  T* r = R + (int64_t)b * bstride + (valid ? row : 0) * ldf;
-  const float* v = V + (int64_t)b * D * k;
-  const bool vec4 = (k & 3) == 0;
-
-  if (valid) {
-    // projection, kChunk columns of V at a time; each lane owns a stripe of d
-    for (int jc = 0; jc < k; jc += kChunk) {
-      const int jn = min(kChunk, k - jc);
-      float acc[kChunk];
+struct Piece;
+template <>
+struct Piece<bf16_t> {
+  u32x4 w;
+  __device__ __forceinline__ void load(const bf16_t* row, int d, int D) {
+    w = u32x4{0u, 0u, 0u, 0u};
+    if (d < D) w = *reinterpret_cast<const u32x4*>(row + d);
+  }
+  __device__ __forceinline__ float get(int e) const { return e & 1 ? bf16_hi(w[e >> 1]) : bf16_lo(w[e >> 1]); }
+  static __device__ __forceinline__ void store(bf16_t* row, int d, int D, const f32x4 (&x)[2]) {
+    if (d < D)
+      *reinterpret_cast<u32x4*>(row + d) = u32x4{pack_bf16(x[0][0], x[0][1]), pack_bf16(x[0][2], x[0][3]),
+                                                 pack_bf16(x[1][0], x[1][1]), pack_bf16(x[1][2], x[1][3])};
+  }
+};
+template <>
+struct Piece<float> {
+  f32x4 x[2];
+  __device__ __forceinline__ void load(const float* row, int d, int D) {
 #pragma unroll
-      for (int j = 0; j < kChunk; ++j) acc[j] = 0.f;
-      if (vec4) {
-        for (int d = lane; d < D; d += kWave) {
-          const float x = ld_elem(f, d);
-          const float4* vp = reinterpret_cast<const float4*>(v + (int64_t)d * k + jc);
-#pragma unroll
-          for (int g = 0; g < kChunk / 4; ++g) {
-            if (g * 4 < jn) {
-              const float4 w = vp[g];
-              acc[4 * g + 0] += x * w.x;
-              acc[4 * g + 1] += x * w.y;
-              acc[4 * g + 2] += x * w.z;
-              acc[4 * g + 3] += x * w.w;
-            }
-          }
-        }
-      } else {
-        for (int d = lane; d < D; d += kWave) {
-          const float x = ld_elem(f, d);
-          const float* vp = v + (int64_t)d * k + jc;
-#pragma unroll
-          for (int j = 0; j < kChunk; ++j)
-            if (j < jn) acc[j] += x * vp[j];
-        }
-      }
-      float mine = 0.f;
-#pragma unroll
-      for (int j = 0; j < kChunk; ++j) {
-        const float t = wave_sum(acc[j]);
-        if (lane == j) mine = t;
-      }
-      if (lane < jn) csh[wave][jc + lane] = mine;
+    for (int t = 0; t < 2; ++t) {
+      x[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (d + 4 * t < D) x[t] = *reinterpret_cast<const f32x4*>(row + d + 4 * t);
     }
   }
-  __syncthreads();
-  if (!valid) return;
+  __device__ __forceinline__ float get(int e) const { return x[e >> 2][e & 3]; }
+  static __device__ __forceinline__ void store(float* row, int d, int D, const f32x4 (&y)[2]) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+      if (d + 4 * t < D) *reinterpret_cast<f32x4*>(row + d + 4 * t) = y[t];
+  }
+};
 
-  // EMA update of the coefficient state (Eq. 11 with alpha = 1 - beta)
-  const int64_t srow = ((int64_t)b * N + row) * k;
-  for (int j = lane; j < k; j += kWave) {
-    const float c = csh[wave][j];
-    const float s = init ? c : (1.f - alpha) * S[srow + j] + alpha * c;
-    S[srow + j] = s;
-    if (C) C[srow + j] = c;
+// Coefficients of the workgroup's 16 rows in LDS: row stride 16 ceil(k / 16) + 4 floats (rows fall into different
+// banks for the 16-byte reads below), zeros beyond k.
+__host__ __device__ inline int coef_stride(int k) { return (k + 15) / 16 * 16 + 4; }
+
+// A piece of V, 32 channels from chunk c x KW = 16 KT coefficients from j0, on its way to the wave that uses it: loads
+// of whole row segments requested a piece ahead, then LDS, from where both phases read it in the lane layout that they
+// need.  (Loaded in that layout directly, an instruction touches 16 rows: twice the time.)  The LDS area belongs to one
+// wave, so no barrier is needed: the LDS executes a wave's accesses in order.  The loads are bounds-checked buffer
+// loads over the chunk's rows: rows beyond D and, with an offset past the end, columns beyond k read as zero.
+template <int KT>
+struct VPiece {
+  static constexpr int KW = 16 * KT, RPL = 64 / KW, NL = 32 / RPL, KS = KW + 4;
+  static constexpr int kFloats = 32 * KS;
+  float x[NL];
+  __device__ __forceinline__ void load(const float* v, int D, int k, int c, int j0) {
+    const int lane = threadIdx.x & 63, row = lane / KW, col = j0 + lane % KW;
+    const auto rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(v + (int64_t)32 * c * k), 0,
+                                                        min(32, D - 32 * c) * k * 4, 0x00027000);
+    const uint32_t off = col < k ? (uint32_t)(row * k + col) * 4u : 0x80000000u;
+#pragma unroll
+    for (int i = 0; i < NL; ++i)
+      x[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rows, off + (uint32_t)(RPL * i * k) * 4u, 0, 0));
+  }
+  __device__ __forceinline__ void to_lds(float* lds) const {
+    const int lane = threadIdx.x & 63, row = lane / KW, col = lane % KW;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+    for (int i = 0; i < NL; ++i) lds[(RPL * i + row) * KS + col] = x[i];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
+};
+
+// For the chunks c0, c0 + cstep, ... < nchunk of 32 channels: P = C V^T of the workgroup's 16 rows (C in LDS), handed to
+// `emit(c, P)` as the lane's eight channels 32 c + 8 g .. of row r; `fetch(c)` is called before the products so that the
+// caller can request what it combines P with.  Lane (r, g) takes, for the two halves t of the chunk,
+// V[32 c + 8 (r / 4) + 4 t + r % 4][j0 + 16 s + 4 g + e] as the operand of step (s, e): with its rows permuted like this
+// the result of half t is the lane's channels 32 c + 8 g + 4 t + i of token row r.
+template <int KT, typename Fetch, typename Emit>
+__device__ __forceinline__ void reconstruct(const float* v, const float* cs, float* vlds, int D, int k, int c0, int cstep,
+                                            int nchunk, Fetch fetch, Emit emit) {
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4, CS = coef_stride(k);
+  constexpr int KS = VPiece<KT>::KS;
+  if (c0 >= nchunk) return;
+  VPiece<KT> vp;
+  vp.load(v, D, k, c0, 0);
+  for (int c = c0; c < nchunk; c += cstep) {
+    fetch(c);
+    f32x4 acc[2][4];      // four accumulators per result tile: short chains of additions
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int h = 0; h < 4; ++h) acc[t][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j0 = 0; j0 < k; j0 += 16 * KT) {
+      vp.to_lds(vlds);
+      const bool more = j0 + 16 * KT < k;
+      const int cn = more ? c : c + cstep;
+      if (cn < nchunk) vp.load(v, D, k, cn, more ? j0 + 16 * KT : 0);
+#pragma unroll
+      for (int s = 0; s < KT; ++s) {
+        if (j0 + 16 * s >= k) break;
+        const f32x4 b = *reinterpret_cast<const f32x4*>(cs + r * CS + j0 + 16 * s + 4 * g);
+        f32x4 a[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          a[t] = *reinterpret_cast<const f32x4*>(vlds + (8 * (r >> 2) + 4 * t + (r & 3)) * KS + 16 * s + 4 * g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int t = 0; t < 2; ++t) acc[t][e] = mfma_f32(a[t][e], b[e], acc[t][e]);
+      }
+    }
+    f32x4 p[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) p[t][i] = (acc[t][0][i] + acc[t][1][i]) + (acc[t][2][i] + acc[t][3][i]);
+    emit(c, p);
+  }
+}
+
+// Full-compute step (Eq. 8-11): C = F V, R = F - C V^T, EMA update of S.  A workgroup takes 16 token rows; its eight
+// waves take every eighth chunk of 32 channels.  Phase 1 projects, 16 KT coefficients at a time: four accumulators per
+// result tile and eight waves keep the chains of additions short, float64 joins them (no less accurate than one chain per
+// lane and a tree over 64 lanes), and that leaves registers for two workgroups per compute unit; the waves' partial sums meet in LDS.
+// Phase 2 forms the residual chunk by chunk.  F and R may alias, R and Rp too: phase 1 has read all of the workgroup's
+// rows before the barrier, and phase 2 reads every element in the lane that overwrites it.
+constexpr int kStepWaves = 8;
+template <typename T, int KT>
+__global__ __launch_bounds__(64 * kStepWaves, 4) void full_step_general_kernel(const T* F, const float* __restrict__ V, T* R,
+                                                                            const T* Rp, float alpha_r, float* S,
+                                                                            float* C, int N, int D, int k,
+                                                                            int64_t ldf, int64_t bstride,
+                                                                            float alpha, int init) {
+  // per wave: its piece of V; between the phases its partial sums
+  __shared__ __align__(16) float vstage[kStepWaves][VPiece<KT>::kFloats];
+  static_assert(VPiece<KT>::kFloats >= KT * 256, "partial sums fit");
+  extern __shared__ __align__(16) float cs[];        // [16][coef_stride(k)]
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int b = blockIdx.y, row0 = blockIdx.x * 16, CS = coef_stride(k);
+  const int nchunk = (D + 31) / 32;
+  const float* v = V + (int64_t)b * D * k;
+  float* vlds = vstage[wave];
+  struct alignas(4 * KT) RowVec { float v[KT]; };
+  const int64_t roff = (int64_t)b * bstride + (int64_t)min(row0 + r, N - 1) * ldf;
+
+  for (int j0 = 0; j0 < k; j0 += 16 * KT) {
+    f32x4 acc[KT][4];
+#pragma unroll
+    for (int jt = 0; jt < KT; ++jt)
+#pragma unroll
+      for (int h = 0; h < 4; ++h) acc[jt][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+    Piece<T> fn;
+    VPiece<KT> vp;
+    if (wave < nchunk) {
+      fn.load(F + roff, 32 * wave + 8 * g, D);
+      vp.load(v, D, k, wave, j0);
+    }
+    for (int c = wave; c < nchunk; c += kStepWaves) {
+      const Piece<T> f = fn;
+      vp.to_lds(vlds);
+      if (c + kStepWaves < nchunk) {
+        fn.load(F + roff, 32 * (c + kStepWaves) + 8 * g, D);
+        vp.load(v, D, k, c + kStepWaves, j0);
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        // columns of the result tile jt: j0 + KT r + jt, so that one wide LDS read brings the operands of all tiles
+        const float x = f.get(e);
+        const RowVec vv = *reinterpret_cast<const RowVec*>(vlds + (8 * g + e) * VPiece<KT>::KS + KT * r);
+#pragma unroll
+        for (int jt = 0; jt < KT; ++jt) acc[jt][e & 3] = mfma_f32(x, vv.v[jt], acc[jt][e & 3]);
+      }
+    }
+    f32x4* part = reinterpret_cast<f32x4*>(vlds);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+    for (int jt = 0; jt < KT; ++jt) {
+      f32x4 s;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        s[i] = (float)(((double)acc[jt][0][i] + acc[jt][1][i]) + ((double)acc[jt][2][i] + acc[jt][3][i]));
+      part[jt * 64 + lane] = s;
+    }
+    __syncthreads();
+    // D[m = 4 g + i][n = r]: row 4 g + i, coefficient j0 + KT r + jt
+    if (wave < KT) {
+      const int j = j0 + KT * r + wave;
+      double c[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int w = 0; w < kStepWaves; ++w) {
+        const f32x4 p = reinterpret_cast<const f32x4*>(vstage[w])[wave * 64 + lane];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c[i] += (double)p[i];
+      }
+      if (j < CS - 4) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) cs[(4 * g + i) * CS + j] = j < k ? (float)c[i] : 0.f;
+      }
+    }
+    __syncthreads();
+  }
+
+  // EMA update of the coefficient state (Eq. 11 with alpha = 1 - beta); the rows of a tile are contiguous in S and C
+  const int nrow = min(16, N - row0);
+  const int64_t soff = ((int64_t)b * N + row0) * k;
+  for (int e = threadIdx.x; e < nrow * k; e += 64 * kStepWaves) {
+    const int row = e / k, j = e - row * k;
+    const float c = cs[row * CS + j];
+    const float s = init ? c : (1.f - alpha) * S[soff + e] + alpha * c;
+    S[soff + e] = s;
+    if (C) C[soff + e] = c;
   }
 
   // residual R = F - C V^T (Eq. 10)
-  const float* cw = csh[wave];
-  for (int d = lane; d < D; d += kWave) {
-    float acc = 0.f;
-    const float* vp = v + (int64_t)d * k;
-    if (vec4) {
-      for (int j = 0; j < k; j += 4) {
-        const float4 w = *reinterpret_cast<const float4*>(vp + j);
-        acc += cw[j] * w.x + cw[j + 1] * w.y + cw[j + 2] * w.z + cw[j + 3] * w.w;
+  Piece<T> f, rp;
+  auto fetch = [&](int c) {
+    f.load(F + roff, 32 * c + 8 * g, D);
+    if (Rp) rp.load(Rp + roff, 32 * c + 8 * g, D);
+  };
+  reconstruct<KT>(v, cs, vlds, D, k, wave, kStepWaves, nchunk, fetch, [&](int c, const f32x4 (&p)[2]) {
+    f32x4 x[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        x[t][i] = f.get(4 * t + i) - p[t][i];
+        // optional smoothing of the residual state (Rp: previous residual, may be the buffer R itself)
+        if (Rp) x[t][i] = (1.f - alpha_r) * rp.get(4 * t + i) + alpha_r * x[t][i];
       }
-    } else {
-      for (int j = 0; j < k; ++j) acc += cw[j] * vp[j];
-    }
-    float rnew = ld_elem(f, d) - acc;
-    // optional smoothing of the residual state (Rp: previous residual, may be the buffer R itself)
-    if (Rp) rnew = (1.f - alpha_r) * ld_elem(Rp + (int64_t)b * bstride + row * ldf, d) + alpha_r * rnew;
-    st_elem(r, d, rnew);
-  }
+    if (row0 + r < N) Piece<T>::store(R + roff, 32 * c + 8 * g, D, x);
+  });
 }
 
 // Cached step (Sec. 3.5): Fhat = C_hat V^T + R [+ X] with the coefficient forecast C_hat = sum_m w_m S_m
-// (one state with weight one is the paper's EMA forecast).  X is nullable; Fhat may alias R or X.
-template <typename T>
-__global__ __launch_bounds__(256) void forecast_general_kernel(const CoefStates cs, const float* __restrict__ V,
-                                                               const T* R, const T* X, T* Fh, int N, int D, int k,
-                                                               int64_t ldf, int64_t bstride) {
-  __shared__ float ssh[kRowsPerGroup][kMaxRank];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int b = blockIdx.y;
-  const int64_t row = (int64_t)blockIdx.x * kRowsPerGroup + wave;
-  const bool valid = row < N;
-  if (valid) {
-    const int64_t srow = ((int64_t)b * N + row) * k;
-    for (int j = lane; j < k; j += kWave) {
-      float c = cs.w[0] * cs.s[0][srow + j];
-      for (int m = 1; m < cs.m; ++m) c = __builtin_fmaf(cs.w[m], cs.s[m][srow + j], c);
-      ssh[wave][j] = c;
+// (one state with weight one is the paper's EMA forecast).  X is nullable; Fhat may alias R or X.  A workgroup of four
+// waves takes 16 rows and, of the chunks of 32 channels, the blockIdx.z-th of gridDim.z shares (small problems would
+// leave compute units idle otherwise).
+constexpr int kCachedWaves = 4;
+template <typename T, int KT>
+__global__ __launch_bounds__(64 * kCachedWaves, 4) void forecast_general_kernel(const CoefStates st,
+                                                                             const float* __restrict__ V, const T* R,
+                                                                             const T* X, T* Fh, int N, int D, int k,
+                                                                             int64_t ldf, int64_t bstride) {
+  __shared__ __align__(16) float vstage[kCachedWaves][VPiece<KT>::kFloats];
+  extern __shared__ __align__(16) float cs[];        // [16][coef_stride(k)]
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int b = blockIdx.y, row0 = blockIdx.x * 16, CS = coef_stride(k), kpad = CS - 4;
+  const int nchunk = (D + 31) / 32;
+  // the coefficients of the tile, zeros beyond N and k; 16 threads per row
+  const int64_t soff = ((int64_t)b * N + row0) * k;
+  {
+    const int row = threadIdx.x >> 4;
+    for (int j = threadIdx.x & 15; j < kpad; j += 16) {
+      float c = 0.f;
+      if (row0 + row < N && j < k) {
+        const int64_t at = soff + (int64_t)row * k + j;
+        c = st.w[0] * st.s[0][at];
+        for (int m = 1; m < st.m; ++m) c = __builtin_fmaf(st.w[m], st.s[m][at], c);
+      }
+      cs[row * CS + j] = c;
     }
   }
   __syncthreads();
-  if (!valid) return;
-  const T* r = R + (int64_t)b * bstride + row * ldf;
-  const T* x = X ? X + (int64_t)b * bstride + row * ldf : nullptr;
-  T* o = Fh + (int64_t)b * bstride + row * ldf;
-  const float* v = V + (int64_t)b * D * k;
-  const float* sw = ssh[wave];
-  const bool vec4 = (k & 3) == 0;
-  for (int d = lane; d < D; d += kWave) {
-    float acc = 0.f;
-    const float* vp = v + (int64_t)d * k;
-    if (vec4) {
-      for (int j = 0; j < k; j += 4) {
-        const float4 w = *reinterpret_cast<const float4*>(vp + j);
-        acc += sw[j] * w.x + sw[j + 1] * w.y + sw[j + 2] * w.z + sw[j + 3] * w.w;
+  const int64_t roff = (int64_t)b * bstride + (int64_t)min(row0 + r, N - 1) * ldf;
+  Piece<T> f, xp;
+  auto fetch = [&](int c) {
+    f.load(R + roff, 32 * c + 8 * g, D);
+    if (X) xp.load(X + roff, 32 * c + 8 * g, D);
+  };
+  reconstruct<KT>(V + (int64_t)b * D * k, cs, vstage[wave], D, k, blockIdx.z * kCachedWaves + wave,
+                  kCachedWaves * gridDim.z, nchunk, fetch, [&](int c, const f32x4 (&p)[2]) {
+    f32x4 x[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        x[t][i] = f.get(4 * t + i);
+        if (X) x[t][i] += xp.get(4 * t + i);
+        x[t][i] += p[t][i];
       }
-    } else {
-      for (int j = 0; j < k; ++j) acc += sw[j] * vp[j];
-    }
-    float base = ld_elem(r, d);
-    if (x) base += ld_elem(x, d);
-    st_elem(o, d, base + acc);
-  }
+    if (row0 + r < N) Piece<T>::store(Fh + roff, 32 * c + 8 * g, D, x);
+  });
 }
+
+// calls fn(KT) with the coefficient tiles that a piece of V holds, as a compile-time constant.  The full step stops at
+// two (32 coefficients at a time, ranks above 32 in several passes over the rows): with four its accumulators leave one
+// or, spilled, two workgroups per compute unit (93 against 67 us at rank 50).
+template <int kMaxTiles, typename Fn>
+int32_t general_dispatch(const svdc_shape& s, Fn fn) {
+  if (s.k <= 16) return fn(std::integral_constant<int, 1>{});
+  if constexpr (kMaxTiles > 2) {
+    if (s.k > 32) return fn(std::integral_constant<int, 4>{});
+  }
+  return fn(std::integral_constant<int, 2>{});
+}
+
+// the coefficients take up to 66 KB of LDS (rank 1024) beside the pieces of V
+template <typename K>
+int32_t allow_lds(K kernel, size_t bytes) {
+  if (bytes <= 8 * 1024) return SVDC_OK;
+  return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess
+             ? SVDC_OK : SVDC_E_HIP;
+}
+
+template <typename T>
+int32_t full_step_general_typed(const svdc_shape& s, const void* F, const float* V, void* R, float* S, float* C,
+                                float alpha, int init, ResidualEma re, hipStream_t st) {
+  return general_dispatch<2>(s, [&](auto kt) -> int32_t {
+    auto kernel = full_step_general_kernel<T, decltype(kt)::value>;
+    const size_t lds = (size_t)16 * coef_stride(s.k) * sizeof(float);
+    if (allow_lds(kernel, lds) != SVDC_OK) return SVDC_E_HIP;
+    kernel<<<dim3((s.N + 15) / 16, s.B), 64 * kStepWaves, lds, st>>>((const T*)F, V, (T*)R, (const T*)re.prev, re.alpha_r,
+                                                                     S, C, s.N, s.D, s.k, s.ldf, s.block_stride, alpha,
+                                                                     init);
+    return launch_status();
+  });
+}
+
+template <typename T>
+int32_t forecast_general_typed(const svdc_shape& s, const CoefStates& cs, const float* V, const void* R, const void* X,
+                               void* Out, hipStream_t st) {
+  return general_dispatch<4>(s, [&](auto kt) -> int32_t {
+    auto kernel = forecast_general_kernel<T, decltype(kt)::value>;
+    const size_t lds = (size_t)16 * coef_stride(s.k) * sizeof(float);
+    if (allow_lds(kernel, lds) != SVDC_OK) return SVDC_E_HIP;
+    const int64_t tiles = (s.N + 15) / 16;
+    // shares of the channels: until there are about four workgroups per compute unit, at least two chunks per wave
+    const int nchunk = (s.D + 31) / 32;
+    const int64_t want = (4 * 256 + tiles * s.B - 1) / (tiles * s.B);
+    const int shares = (int)std::max<int64_t>(1, std::min<int64_t>(want, nchunk / (2 * kCachedWaves)));
+    kernel<<<dim3((unsigned)tiles, s.B, shares), 64 * kCachedWaves, lds, st>>>(cs, V, (const T*)R, (const T*)X, (T*)Out,
+                                                                               s.N, s.D, s.k, s.ldf, s.block_stride);
+    return launch_status();
+  });
+}
+
+}  // namespace
 
 int32_t launch_full_step_general(const svdc_shape& s, const void* F, const float* V, void* R, float* S,
                                  float* C, float alpha, int init, ResidualEma re, hipStream_t st) {
-  dim3 grid((s.N + kRowsPerGroup - 1) / kRowsPerGroup, s.B), block(256);
-  if (s.dtype == SVDC_BF16)
-    full_step_general_kernel<bf16_t><<<grid, block, 0, st>>>((const bf16_t*)F, V, (bf16_t*)R, (const bf16_t*)re.prev,
-                                                           re.alpha_r, S, C, s.N, s.D, s.k, s.ldf, s.block_stride,
-                                                           alpha, init);
-  else
-    full_step_general_kernel<float><<<grid, block, 0, st>>>((const float*)F, V, (float*)R, (const float*)re.prev,
-                                                          re.alpha_r, S, C, s.N, s.D, s.k, s.ldf, s.block_stride,
-                                                          alpha, init);
-  return launch_status();
+  if (s.dtype == SVDC_BF16) return full_step_general_typed<bf16_t>(s, F, V, R, S, C, alpha, init, re, st);
+  return full_step_general_typed<float>(s, F, V, R, S, C, alpha, init, re, st);
 }
 
 int32_t launch_forecast_general(const svdc_shape& s, const CoefStates& cs, const float* V, const void* R,
                                 const void* X, void* Out, hipStream_t st) {
-  dim3 grid((s.N + kRowsPerGroup - 1) / kRowsPerGroup, s.B), block(256);
-  if (s.dtype == SVDC_BF16)
-    forecast_general_kernel<bf16_t><<<grid, block, 0, st>>>(cs, V, (const bf16_t*)R, (const bf16_t*)X, (bf16_t*)Out,
-                                                          s.N, s.D, s.k, s.ldf, s.block_stride);
-  else
-    forecast_general_kernel<float><<<grid, block, 0, st>>>(cs, V, (const float*)R, (const float*)X, (float*)Out, s.N,
-                                                         s.D, s.k, s.ldf, s.block_stride);
-  return launch_status();
+  if (s.dtype == SVDC_BF16) return forecast_general_typed<bf16_t>(s, cs, V, R, X, Out, st);
+  return forecast_general_typed<float>(s, cs, V, R, X, Out, st);
 }
 
 // ---------------------------------------------------------------------------

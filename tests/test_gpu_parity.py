@@ -58,6 +58,40 @@ def test_full_step_and_forecast_general_shapes(dtype, B, N, D, k):
             assert_close(to_np(Fh[b]), Fr, store, f"Fhat[{b}]", scale_of=to_np(Fbuf[b]), ulp_of=Rr)
 
 
+@pytest.mark.parametrize("B,N,D,k", [(1, 17, 24, 15), (2, 16, 40, 16), (1, 33, 1304, 33), (1, 70, 296, 65), (2, 131, 392, 129),
+                                     (1, 1030, 1040, 1024)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+def test_general_kernels_at_the_edges_of_their_tiles(dtype, B, N, D, k):
+    """Ragged 16-row tiles, 32-channel chunks and 16-, 32- and 64-coefficient groups, the largest rank; a row that holds
+    an infinity or a NaN stays the only one affected."""
+    store = "f32" if dtype == torch.float32 else "bf16"
+    if dtype == torch.float32:
+        D += 4                          # a chunk whose last piece of eight channels is half outside
+    Fbuf, V, S0 = _rand_problem(B, N, D, k, dtype, seed=N + k)
+    R, S, Cc, shape, pk = _run_full(Fbuf, D, V, S0, 0.3, False)
+    assert pk is None
+    Fh = torch.empty_like(R)
+    pkg.svdcache_forecast(shape, S, V.to(DEV), None, R, Fh)
+    torch.cuda.synchronize()
+    for b in range(B):
+        Rr, Sr, Cr = ref_full_step(to_np(Fbuf[b]), to_np(V[b]), to_np(S0[b]), 0.3, False, store)
+        assert_close(to_np(R[b]), Rr, store, f"R[{b}]", floor_of=to_np(Fbuf[b]))
+        assert_close(to_np(S[b]), Sr, "f32", f"S[{b}]")
+        assert_close(to_np(Cc[b]), Cr, "f32", f"C[{b}]")
+        Fr = ref_forecast(Sr, to_np(V[b]), Rr, store)
+        assert_close(to_np(Fh[b]), Fr, store, f"Fhat[{b}]", scale_of=to_np(Fbuf[b]), ulp_of=Rr)
+    bad = Fbuf.clone()
+    bad[0, 3, 1], bad[0, 5, D - 1] = float("inf"), float("nan")
+    R2, S2, C2, _, _ = _run_full(bad, D, V, S0, 0.3, False)
+    Fh2 = torch.empty_like(R)
+    pkg.svdcache_forecast(shape, S2, V.to(DEV), None, R2, Fh2)
+    torch.cuda.synchronize()
+    keep = torch.ones(N, dtype=torch.bool)
+    keep[[3, 5]] = False
+    for got, want in ((R2, R), (S2, S), (C2, Cc), (Fh2, Fh)):
+        assert torch.equal(got[0][keep], want[0][keep]) and not torch.isfinite(got[0][[3, 5]].float()).all(dim=1).any()
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
 def test_strided_rows_inplace_and_null_C(dtype):
     store = "f32" if dtype == torch.float32 else "bf16"
