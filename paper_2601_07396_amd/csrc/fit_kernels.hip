@@ -179,86 +179,138 @@ __device__ __forceinline__ void mfma64_accumulate(const double* As, const double
 // ---------------------------------------------------------------------------
 // Partial Gram matrices A^T A in float64, A float32 [rows x l]; rows split over grid.x, 64 x 64 tiles of the lower
 // block triangle (tile row >= tile column) over grid.y: the factorisation that follows never reads the rest.
-// 16 rows per step, staged in LDS as float64 (each value converted once); the next step's rows are fetched into
-// registers while the current ones are multiplied.
+// Four rows of A are one step of the matrix instruction, and a lane's operand A[row 4 k + lane / 16][column lane % 16] is
+// a coalesced load, so nothing is staged: each of the four waves takes every fourth group of four rows, requests the
+// next ones ahead, and multiplies the 16 x 16 tiles on or below the diagonal (10 of 16 in a diagonal tile); the waves'
+// sums meet in LDS.  27 us for 57 blocks of 3072 x 64 (the float64 matrix rate
+// allows 11), 8.2 us for one, against 40 and 14 us with all 16 tiles and the rows staged in LDS as float64, two barriers
+// per 16 rows.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void gram_f64_kernel(const float* __restrict__ A, double* G, int rows, int l,
+template <bool DIAGONAL>
+__device__ __forceinline__ void gram_tile(const float* a, double* g, f64x4 (*part)[DIAGONAL ? 10 : 16][64], int rows, int l, int ti, int tj,
+                                          int rbeg, int rend) {
+  constexpr int NI = 4, U = 4;         // column tiles per side; groups of four rows in flight
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, m = lane & 15, kq = lane >> 4;
+  int ci[NI], cj[NI];
+  bool ini[NI], inj[NI];
+#pragma unroll
+  for (int x = 0; x < NI; ++x) {
+    ini[x] = 64 * ti + 16 * x + m < l;
+    inj[x] = 64 * tj + 16 * x + m < l;
+    ci[x] = min(64 * ti + 16 * x + m, l - 1);
+    cj[x] = min(64 * tj + 16 * x + m, l - 1);
+  }
+  f64x4 acc[NI][NI];
+#pragma unroll
+  for (int x = 0; x < NI; ++x)
+#pragma unroll
+    for (int y = 0; y < NI; ++y) acc[x][y] = f64x4{0.0, 0.0, 0.0, 0.0};
+  // loaded from clamped addresses; what lies outside is made zero when it is used, so that no load is waited for early
+  float vi[U][NI], vj[U][NI];
+  auto fetch = [&](int u, int r0) {
+    const float* row = a + (int64_t)min(r0 + kq, rows - 1) * l;
+#pragma unroll
+    for (int x = 0; x < NI; ++x) {
+      vi[u][x] = row[ci[x]];
+      if constexpr (!DIAGONAL) vj[u][x] = row[cj[x]];
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < U; ++u) fetch(u, rbeg + 4 * wave + 16 * u);
+  for (int r0 = rbeg + 4 * wave; r0 < rend; r0 += 16 * U) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool in = r0 + 16 * u + kq < rend;
+      double di[NI], dj[NI];
+#pragma unroll
+      for (int x = 0; x < NI; ++x) {
+        di[x] = (double)(in && ini[x] ? vi[u][x] : 0.f);
+        if constexpr (!DIAGONAL) dj[x] = (double)(in && inj[x] ? vj[u][x] : 0.f);
+      }
+      fetch(u, r0 + 16 * (u + U));
+#pragma unroll
+      for (int x = 0; x < NI; ++x)
+#pragma unroll
+        for (int y = 0; y < NI; ++y) {
+          if (DIAGONAL && y > x) continue;
+          acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(di[x], DIAGONAL ? di[y] : dj[y], acc[x][y], 0, 0, 0);
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  // sum over the waves, two at a time (a wave's 16 tiles are 32 KB)
+  const auto tile = [](int x, int y) { return DIAGONAL ? x * (x + 1) / 2 + y : 4 * x + y; };
+#pragma unroll
+  for (int half = 2; half >= 1; half >>= 1) {
+    if (wave >= half && wave < 2 * half) {
+#pragma unroll
+      for (int x = 0; x < NI; ++x)
+#pragma unroll
+        for (int y = 0; y < NI; ++y)
+          if (!(DIAGONAL && y > x)) part[wave - half][tile(x, y)][lane] = acc[x][y];
+    }
+    __syncthreads();
+    if (wave < half) {
+#pragma unroll
+      for (int x = 0; x < NI; ++x)
+#pragma unroll
+        for (int y = 0; y < NI; ++y)
+          if (!(DIAGONAL && y > x)) acc[x][y] += part[wave][tile(x, y)][lane];
+    }
+    __syncthreads();
+  }
+  if (wave != 0) return;
+  // D[i = 4 v + lane / 16][j = lane % 16]; the tiles above the diagonal are the mirror images of those below
+#pragma unroll
+  for (int x = 0; x < NI; ++x)
+#pragma unroll
+    for (int y = 0; y < NI; ++y) {
+      if (DIAGONAL && y > x) continue;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int gi = 64 * ti + 16 * x + 4 * v + kq, gj = 64 * tj + 16 * y + m;
+        if (gi >= l || gj >= l) continue;
+        g[(int64_t)gi * l + gj] = acc[x][y][v];
+        if (DIAGONAL && y < x) g[(int64_t)gj * l + gi] = acc[x][y][v];
+      }
+    }
+}
+
+// ONE_TILE: l <= 64, a single tile on the diagonal (a kernel of its own: 150 instead of 330 registers)
+template <bool ONE_TILE>
+__global__ __launch_bounds__(256, ONE_TILE ? 3 : 1) void gram_f64_kernel(const float* __restrict__ A, double* G, int rows, int l,
                                                        int rows_per_slice) {
-  __shared__ double Ai[16 * kM64Stride];
-  __shared__ double Aj[16 * kM64Stride];
+  __shared__ f64x4 part[2 * (ONE_TILE ? 10 : 16) * 64];
   const int b = blockIdx.z;
   int ti = 0;
   while ((ti + 1) * (ti + 2) / 2 <= (int)blockIdx.y) ++ti;
   const int tj = blockIdx.y - ti * (ti + 1) / 2;
   const float* a = A + (int64_t)b * rows * l;
   double* g = G + ((int64_t)b * gridDim.x + blockIdx.x) * l * l;   // partial Gram matrix of this row slice
-  const int t = threadIdx.x;
   const int rbeg = blockIdx.x * rows_per_slice, rend = min(rows, rbeg + rows_per_slice);
-  const Quadrant q;
-  f64x4 acc[2][2];
-#pragma unroll
-  for (int x = 0; x < 2; ++x)
-#pragma unroll
-    for (int y = 0; y < 2; ++y) acc[x][y] = f64x4{0.0, 0.0, 0.0, 0.0};
-  const bool vec = (l & 3) == 0;
-  const int rr = t >> 4, c = (t & 15) * 4;
-  const int ci = ti * 64 + c, cj = tj * 64 + c;
-  float vi[4], vj[4];
-  auto fetch = [&](int r0) {
-    const int64_t r = r0 + rr;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { vi[e] = 0.f; vj[e] = 0.f; }
-    if (r < rend) {
-      if (vec) {
-        if (ci < l) *reinterpret_cast<float4*>(vi) = *reinterpret_cast<const float4*>(a + r * l + ci);
-        if (cj < l) *reinterpret_cast<float4*>(vj) = *reinterpret_cast<const float4*>(a + r * l + cj);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if (ci + e < l) vi[e] = a[r * l + ci + e];
-          if (cj + e < l) vj[e] = a[r * l + cj + e];
-        }
-      }
-    }
-  };
-  if (rbeg < rend) fetch(rbeg);
-  for (int r0 = rbeg; r0 < rend; r0 += 16) {
-    if (r0 > rbeg) __syncthreads();             // the previous step has been read by everybody
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      Ai[rr * kM64Stride + c + e] = (double)vi[e];
-      Aj[rr * kM64Stride + c + e] = (double)vj[e];
-    }
-    __syncthreads();
-    if (r0 + 16 < rend) fetch(r0 + 16);
-    mfma64_accumulate<4>(Ai, Aj, q, acc);
-  }
-#pragma unroll
-  for (int x = 0; x < 2; ++x)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int gi = ti * 64 + q.row(x, v);
-      if (gi >= l) continue;
-#pragma unroll
-      for (int y = 0; y < 2; ++y) {
-        const int gj = tj * 64 + q.col(y);
-        if (gj < l) g[(int64_t)gi * l + gj] = acc[x][y][v];
-      }
-    }
+  if (ONE_TILE || ti == tj) gram_tile<true>(a, g, reinterpret_cast<f64x4(*)[10][64]>(part), rows, l, ti, tj, rbeg, rend);
+  else if constexpr (!ONE_TILE) gram_tile<false>(a, g, reinterpret_cast<f64x4(*)[16][64]>(part), rows, l, ti, tj, rbeg, rend);
 }
 
-// G[b] = sum over the row slices of the partial Gram matrices, in slice order (no atomics: the same bits every run);
-// lower block triangle only, like the partial matrices
+// G[b] = sum over the row slices of the partial Gram matrices, in a fixed order (no atomics: the same bits every run);
+// lower block triangle only, like the partial matrices.  64 elements per workgroup, the slices in four shares with
+// several loads in flight each (one thread per element walking over 16 slices took 6.2 us at any size, this 3 us).
 __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restrict__ part, double* G, int nslice,
                                                           int l) {
-  const int b = blockIdx.y;
+  __shared__ double share[3][64];
+  const int b = blockIdx.y, lane = threadIdx.x & 63, q = threadIdx.x >> 6;
   const int64_t ll = (int64_t)l * l;
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= ll || (e % l) / 64 > (e / l) / 64) return;
-  const double* p = part + (int64_t)b * nslice * ll + e;
+  const int64_t e = (int64_t)blockIdx.x * 64 + lane;
+  const bool in = e < ll && (e % l) / 64 <= (e / l) / 64;
   double s = 0.0;
-  for (int i = 0; i < nslice; ++i) s += p[(int64_t)i * ll];
-  G[(int64_t)b * ll + e] = s;
+  if (in) {
+    const double* p = part + (int64_t)b * nslice * ll + e;
+#pragma unroll 6
+    for (int i = q; i < nslice; i += 4) s += p[(int64_t)i * ll];
+  }
+  if (q > 0) share[q - 1][lane] = s;
+  __syncthreads();
+  if (q == 0 && in) G[(int64_t)b * ll + e] = (s + share[0][lane]) + (share[1][lane] + share[2][lane]);
 }
 
 // A pivot of the Cholesky factorisation below kRankTol x the largest diagonal entry of the Gram matrix means that a
@@ -268,162 +320,290 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restri
 constexpr double kRankTol = 1e-12;
 
 // ---------------------------------------------------------------------------
-// Register-blocked Cholesky factor for l <= 64, factor only: thread (ti, tj) of a 16 x 16 grid owns the 4 x 4 block
-// (ti, tj) of the matrix in registers; a wave owns four block columns.  Right-looking by panels of 4 columns (one
-// block column), two barriers per panel:
-//   the thread on the diagonal factors its 4 x 4 block and publishes it,
-//   the threads below it in the block column (the same wave) solve their blocks against it, X = B L_d^-T, and publish
-//   the panel (64 rows x 4),
-//   every thread below or on the diagonal and right of the panel subtracts the rank-4 product of the panel rows of
-//   its block row and of its block column.
-// (One column at a time, with the column published through LDS and a barrier per column, took three times as long:
-// the per-column chain of barrier, pivot, reciprocal square root and rank-1 update is what costs, not the flops.)
-//   G      in/out  [l x l] at row stride ld, block b at G + b * bstride: lower triangle = L with
-//                  G + shift I = L L^T, upper triangle zeroed
-//   rdiag  out     (nullable) 1 / L[i][i], block b at rdiag + b * rd_bstride
-// The matrix may be a diagonal block of a larger one that is factored block by block (see chol_panel_kernel).
-// ChoShift tells every step which shift to use: the first computes it from the whole diagonal, diag_n >= l
-// entries, and stores it; the later ones, diag_n = 0, read it.  A later block is A_kk - L_k L_k^T with L_k the ku
-// finished columns of its rows, given transposed: Ut [ku x l] at row stride ldut.
+// Cholesky factor of a diagonal block of at most 64 columns, and its inverse, by one workgroup:
+//   A = G[c0 .. c0 + w, same] + shift I - sum_{c < c0} L[., c] L[., c]^T  =  L L^T,       Minv = L^-T
+// (the finished columns of its rows come transposed from the upper triangle of G: G[c][r] = L[r][c]).
+// Thread (ti, tj) of a 16 x 16 grid owns the 4 x 4 block (ti, tj) in registers.  The factorisation is right-looking by
+// panels of 4 columns, two barriers per panel: the thread on the diagonal factors its 4 x 4 block, the threads below it
+// solve theirs and publish the panel, every thread to the right subtracts a rank-4 product.  What bounds it is the chain
+// of dependent float64 operations on the diagonal, so the factor is kept as L' D L'^T with unit diagonal: a column then
+// costs a reciprocal (estimate and two Newton steps, two operations each) instead of a reciprocal square root, and the
+// square roots are taken side by side at the end.  The unit triangle is inverted without divisions: 4 x 4 blocks on the
+// way, then pairs of blocks of 4, 8, 16 and 32, U_21 = -U_22 (L'_21 U_11), from 16 on as matrix instructions.
+// L = L' D^(1/2), L^-1 = D^(-1/2) U.  Measured at 64 columns: 22 us with the inverse, against 18.6 us for the factor
+// alone with a square root per column and 26 us (57 us for 57 blocks of 3072 rows) for the substitution that the inverse
+// replaces in apply_factor_kernel.
+//   w <= 64; columns from w on are padded with the identity.  Lower triangle of the block of G = L, upper part zeroed.
+//   Minv   out  (want_inv) row-major [w x w] at row stride ldm, block b at Minv + b * m_bstride
+//   slot   the shift: computed from the diag_n diagonal entries of G and stored when c0 = 0, read otherwise (nullable when
+//          there is one block only)
 // ---------------------------------------------------------------------------
-struct ChoShift {
-  double* slot;        // per block (stride slot_bstride): the shift, written when diag_n > 0, read otherwise
-  int64_t slot_bstride;
-  int diag_n;          // diagonal entries of G (same ld) that define the shift
-};
-struct ChoUpdate {
-  const double* Ut;    // nullable
-  int64_t bstride;
-  int ldut, ku;
-};
+constexpr int kCholBlock = 64;
 
-template <int BS>
-__global__ __launch_bounds__(256) void chol_reg_kernel(double* G, int64_t bstride, int ld, double* rdiag,
-                                                       int64_t rd_bstride, int l, double rel_shift, int32_t* info,
-                                                       ChoShift sh, ChoUpdate up) {
-  static_assert(BS == 4, "4 x 4 blocks");
-  constexpr int LM = 16 * BS;          // padded matrix size
-  __shared__ double panel[LM][BS];     // the current block column of L, rows below its diagonal block
-  __shared__ double dblk[BS][BS];      // its diagonal block: strict lower part, reciprocals of the diagonal on the diagonal
+__global__ __launch_bounds__(256) void chol_inv_kernel(double* G, int l, int c0, int w, double* Minv, int64_t m_bstride,
+                                                       int ldm, int want_inv, double* slot, int64_t slot_bstride,
+                                                       double rel_shift, int32_t* info) {
+  constexpr int H = kCholBlock, LD = H + 1;
+  __shared__ double Lp[H * LD];        // L' (strictly lower 4 x 4 blocks); first the staging area of the update
+  __shared__ double U[H * LD];         // L'^-1; first the update itself
+  __shared__ double Tm[32 * 33];       // L'_21 U_11
+  __shared__ __align__(16) double py[4][H];   // panel: columns of L' D, rows contiguous
+  __shared__ double dl[2][6], dr[2][4];   // strict lower part and reciprocal pivots of the diagonal block, by panel parity
+  __shared__ double dv[H], sq[H], rs[H];  // pivots, their square roots and reciprocal square roots
   __shared__ double s_shift;
   const int b = blockIdx.x, t = threadIdx.x, tj = t >> 4, ti = t & 15;
-  double* g = G + (int64_t)b * bstride;
+  double* g = G + (int64_t)b * l * l;
+  double* gd = g + (int64_t)c0 * l + c0;
+  double a[4][4];
+#pragma unroll
+  for (int ii = 0; ii < 4; ++ii)
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) a[ii][jj] = gd[(int64_t)min(4 * ti + ii, w - 1) * l + min(4 * tj + jj, w - 1)];
   if (t < kWave) {
-    if (sh.diag_n > 0) {
+    if (c0 == 0) {
       double mx = 0.0;
-      for (int i = t; i < sh.diag_n; i += kWave) mx = fmax(mx, g[(int64_t)i * ld + i]);
+      for (int i = t; i < l; i += kWave) mx = fmax(mx, g[(int64_t)i * l + i]);
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, kWave));
       if (t == 0) {
         s_shift = mx * rel_shift;
-        if (sh.slot) sh.slot[(int64_t)b * sh.slot_bstride] = mx * rel_shift;
+        if (slot) slot[(int64_t)b * slot_bstride] = mx * rel_shift;
       }
     } else if (t == 0) {
-      s_shift = sh.slot[(int64_t)b * sh.slot_bstride];
+      s_shift = slot[(int64_t)b * slot_bstride];
+    }
+  }
+  if (c0 > 0) {   // sum_c L[i][c] L[j][c], 16 columns c per step, c0 a multiple of 64
+    const Quadrant q;
+    f64x4 acc[2][2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int y = 0; y < 2; ++y) acc[x][y] = f64x4{0.0, 0.0, 0.0, 0.0};
+    const int kr = t >> 4, col = 4 * (t & 15);
+    double v[4];
+    auto fetch = [&](int k0) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = g[(int64_t)(k0 + kr) * l + c0 + min(col + e, w - 1)];   // beyond w: not used
+    };
+    static_assert(16 * kM64Stride <= H * LD, "staging fits");
+    fetch(0);
+    for (int k0 = 0; k0 < c0; k0 += 16) {
+      if (k0 > 0) __syncthreads();
+#pragma unroll
+      for (int e = 0; e < 4; ++e) Lp[kr * kM64Stride + col + e] = v[e];
+      __syncthreads();
+      if (k0 + 16 < c0) fetch(k0 + 16);
+      mfma64_accumulate<4>(Lp, Lp, q, acc);
+    }
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int y = 0; y < 2; ++y)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) U[q.row(x, e) * LD + q.col(y)] = acc[x][y][e];
+    __syncthreads();
+#pragma unroll
+    for (int ii = 0; ii < 4; ++ii)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) a[ii][jj] -= U[(4 * ti + ii) * LD + 4 * tj + jj];
+  }
+  __syncthreads();
+  const double shift = s_shift;
+#pragma unroll
+  for (int ii = 0; ii < 4; ++ii)
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      const int i = 4 * ti + ii, j = 4 * tj + jj;
+      if (i >= w || j >= w) a[ii][jj] = i == j ? 1.0 : 0.0;   // identity padding
+      else if (i == j) a[ii][jj] += shift;
+    }
+
+  const double pivot_floor = shift * (kRankTol / rel_shift);
+  bool dependent = false;
+  for (int cb = 0; cb < H / 4; ++cb) {
+    const int par = cb & 1;
+    if (ti == cb && tj == cb) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        dependent |= (4 * cb + q < w) && a[q][q] < pivot_floor;
+        const double d = fmax(a[q][q], 1e-300);
+        double y[4], yy[4][4];
+#pragma unroll
+        for (int i = q + 1; i < 4; ++i) {
+          y[i] = a[i][q];
+#pragma unroll
+          for (int j = q + 1; j <= i; ++j) yy[i][j] = y[i] * a[j][q];
+        }
+        // 1 / d: the hardware's estimate (about 2^-23) and one step of third order
+        double x = __builtin_amdgcn_rcp(d);
+        const double e1 = fma(-d, x, 1.0);
+        x = fma(x, fma(e1, e1, e1), x);
+        dv[4 * cb + q] = d;
+        dr[par][q] = x;
+#pragma unroll
+        for (int j = q + 1; j < 4; ++j)
+#pragma unroll
+          for (int i = j; i < 4; ++i) a[i][j] = fma(-yy[i][j], x, a[i][j]);
+#pragma unroll
+        for (int i = q + 1; i < 4; ++i) a[i][q] = y[i] * x;
+      }
+      dl[par][0] = a[1][0]; dl[par][1] = a[2][0]; dl[par][2] = a[2][1];
+      dl[par][3] = a[3][0]; dl[par][4] = a[3][1]; dl[par][5] = a[3][2];
+    }
+    __syncthreads();
+    if (tj == cb && ti > cb) {    // rows of L' D: Y = B L'_d^-T, published; and of L', kept
+      const double l10 = dl[par][0], l20 = dl[par][1], l21 = dl[par][2], l30 = dl[par][3], l31 = dl[par][4], l32 = dl[par][5];
+      double y[4][4];
+#pragma unroll
+      for (int ii = 0; ii < 4; ++ii) {
+        y[0][ii] = a[ii][0];
+        y[1][ii] = a[ii][1] - y[0][ii] * l10;
+        y[2][ii] = a[ii][2] - y[0][ii] * l20 - y[1][ii] * l21;
+        y[3][ii] = a[ii][3] - y[0][ii] * l30 - y[1][ii] * l31 - y[2][ii] * l32;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int ii = 0; ii < 4; ii += 2)
+          *reinterpret_cast<double2*>(&py[q][4 * ti + ii]) = make_double2(y[q][ii], y[q][ii + 1]);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int ii = 0; ii < 4; ++ii) a[ii][q] = y[q][ii] * dr[par][q];
+    }
+    __syncthreads();
+    if (tj > cb && ti >= tj) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const double r = dr[par][q];
+        double x[4], y[4];
+#pragma unroll
+        for (int ii = 0; ii < 4; ii += 2) {
+          const double2 xv = *reinterpret_cast<const double2*>(&py[q][4 * ti + ii]);
+          const double2 yv = *reinterpret_cast<const double2*>(&py[q][4 * tj + ii]);
+          x[ii] = xv.x; x[ii + 1] = xv.y;
+          y[ii] = yv.x * r; y[ii + 1] = yv.y * r;
+        }
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+          for (int ii = 0; ii < 4; ++ii) a[ii][jj] -= x[ii] * y[jj];
+      }
+    }
+  }
+  // every thread on the diagonal has seen the pivots of its own block
+  if (info && dependent) atomicOr(info + b, SVDC_FIT_RANK_DEFICIENT);
+  if (t < H) {
+    const double d = dv[t];
+    double r = __builtin_amdgcn_rsq(d);
+    r = r * (1.5 - 0.5 * d * r * r);
+    r = r * (1.5 - 0.5 * d * r * r);
+    rs[t] = r;
+    sq[t] = d * r;
+  }
+  // L' to LDS; the diagonal 4 x 4 blocks and their inverses, zeros above
+  if (ti == tj) {
+    const double u10 = -a[1][0], u21 = -a[2][1], u32 = -a[3][2];
+    const double u20 = -(a[2][0] + a[2][1] * u10), u31 = -(a[3][1] + a[3][2] * u21);
+    const double u30 = -(a[3][0] + a[3][1] * u10 + a[3][2] * u20);
+    const double u[4][4] = {{1.0, 0.0, 0.0, 0.0}, {u10, 1.0, 0.0, 0.0}, {u20, u21, 1.0, 0.0}, {u30, u31, u32, 1.0}};
+#pragma unroll
+    for (int ii = 0; ii < 4; ++ii)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) {
+        U[(4 * ti + ii) * LD + 4 * tj + jj] = u[ii][jj];
+        Lp[(4 * ti + ii) * LD + 4 * tj + jj] = jj < ii ? a[ii][jj] : (ii == jj ? 1.0 : 0.0);
+      }
+  } else {
+#pragma unroll
+    for (int ii = 0; ii < 4; ++ii)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) {
+        if (ti > tj) Lp[(4 * ti + ii) * LD + 4 * tj + jj] = a[ii][jj];
+        else U[(4 * ti + ii) * LD + 4 * tj + jj] = 0.0;
+      }
+  }
+  __syncthreads();
+  if (want_inv) {
+    if (t < 128) {   // pairs of 4 x 4 blocks
+      const int p = t >> 4, i = (t >> 2) & 3, j = t & 3, rb = 8 * p + 4, cb = 8 * p;
+      double s = 0.0;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        double x = 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x += Lp[(rb + m) * LD + cb + k] * U[(cb + k) * LD + cb + j];
+        s += U[(rb + i) * LD + rb + m] * x;
+      }
+      U[(rb + i) * LD + cb + j] = -s;
+    }
+    __syncthreads();
+    {                // pairs of 8 x 8 blocks, one element per thread
+      const int p = t >> 6, i = (t >> 3) & 7, j = t & 7, rb = 16 * p + 8, cb = 16 * p;
+      double x = 0.0;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) x += Lp[(rb + i) * LD + cb + k] * U[(cb + k) * LD + cb + j];
+      Tm[64 * p + 8 * i + j] = x;
+      __syncthreads();
+      double s = 0.0;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) s += U[(rb + i) * LD + rb + k] * Tm[64 * p + 8 * k + j];
+      U[(rb + i) * LD + cb + j] = -s;
+    }
+    __syncthreads();
+    const int wave = t >> 6, lane = t & 63, m = lane & 15, kq = lane >> 4;
+    // 16 x 16 tile sum_k A[i][k] B[k][j] over K = 4 k4n
+    auto product = [&](const double* A, int lda, const double* Bm, int ldb, int k4n) {
+      f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+      for (int k4 = 0; k4 < k4n; ++k4)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[m * lda + 4 * k4 + kq], Bm[(4 * k4 + kq) * ldb + m], acc, 0, 0, 0);
+      return acc;
+    };
+    {                // pairs of 16 x 16 blocks: waves 0 and 1
+      const int rb = 32 * wave + 16, cb = 32 * wave;
+      double* tm = Tm + 272 * wave;
+      if (wave < 2) {
+        const f64x4 x = product(Lp + rb * LD + cb, LD, U + cb * LD + cb, LD, 4);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) tm[(4 * v + kq) * 17 + m] = x[v];
+      }
+      __syncthreads();
+      if (wave < 2) {
+        const f64x4 x = product(U + rb * LD + rb, LD, tm, 17, 4);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) U[(rb + 4 * v + kq) * LD + cb + m] = -x[v];
+      }
+    }
+    __syncthreads();
+    {                // the pair of 32 x 32 blocks: a 16 x 16 tile per wave
+      const int i0 = 16 * (wave >> 1), j0 = 16 * (wave & 1);
+      const f64x4 x = product(Lp + (32 + i0) * LD, LD, U + j0, LD, 8);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) Tm[(i0 + 4 * v + kq) * 33 + j0 + m] = x[v];
+      __syncthreads();
+      const f64x4 y = product(U + (32 + i0) * LD + 32, LD, Tm + j0, 33, 8);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) U[(32 + i0 + 4 * v + kq) * LD + j0 + m] = -y[v];
     }
   }
   __syncthreads();
-  double a[BS][BS];
+  double* mi = Minv + (int64_t)b * m_bstride;
+  const int j = t & 63;
+  const double sj = sq[j], rj = rs[j];
 #pragma unroll
-  for (int ii = 0; ii < BS; ++ii)
-#pragma unroll
-    for (int jj = 0; jj < BS; ++jj) {
-      const int i = BS * ti + ii, j = BS * tj + jj;
-      double v = (i < l && j < l) ? g[(int64_t)i * ld + j] : (i == j ? 1.0 : 0.0);   // identity padding
-      if (i == j && i < l) v += s_shift;
-      a[ii][jj] = v;
-    }
-  if (up.Ut && ti >= tj) {   // a -= L21 L21^T, from the transposed factor (rows of Ut are contiguous over i)
-    const double* ut = up.Ut + (int64_t)b * up.bstride;
-#pragma unroll 8
-    for (int kk = 0; kk < up.ku; ++kk) {   // ku is a multiple of 64; unrolled so that the loads of several steps are in flight
-      double ui[BS], uj[BS];
-#pragma unroll
-      for (int ii = 0; ii < BS; ++ii) ui[ii] = (BS * ti + ii < l) ? ut[(int64_t)kk * up.ldut + BS * ti + ii] : 0.0;
-#pragma unroll
-      for (int jj = 0; jj < BS; ++jj) uj[jj] = (BS * tj + jj < l) ? ut[(int64_t)kk * up.ldut + BS * tj + jj] : 0.0;
-#pragma unroll
-      for (int ii = 0; ii < BS; ++ii)
-#pragma unroll
-        for (int jj = 0; jj < BS; ++jj) a[ii][jj] -= ui[ii] * uj[jj];
+  for (int n = 0; n < H / 4; ++n) {
+    const int i = (t >> 6) + 4 * n;
+    const double lv = j <= i ? Lp[i * LD + j] * sj : 0.0, uv = j >= i ? U[j * LD + i] * rj : 0.0;
+    if (i < w && j < w) {
+      gd[(int64_t)i * l + j] = lv;
+      if (want_inv) mi[(int64_t)i * ldm + j] = uv;
     }
   }
-  const double pivot_floor = s_shift * (kRankTol / rel_shift);
-  bool dependent = false;
-  const int nbk = (l + BS - 1) / BS;
-  for (int cb = 0; cb < nbk; ++cb) {
-    if (ti == cb && tj == cb) {        // factor the diagonal block in place (lower part), publish it
-#pragma unroll
-      for (int q = 0; q < BS; ++q) {
-        dependent |= (BS * cb + q < l) && a[q][q] < pivot_floor;
-        const double piv2 = fmax(a[q][q], 1e-300);
-        // 1 / sqrt(piv2): hardware estimate refined by two Newton steps (an exact sqrt and a division per
-        // column would dominate this kernel)
-        double rs = __builtin_amdgcn_rsq(piv2);
-        rs = rs * (1.5 - 0.5 * piv2 * rs * rs);
-        rs = rs * (1.5 - 0.5 * piv2 * rs * rs);
-        a[q][q] = piv2 * rs;
-        dblk[q][q] = rs;
-#pragma unroll
-        for (int i = q + 1; i < BS; ++i) {
-          a[i][q] *= rs;
-          dblk[i][q] = a[i][q];
-        }
-#pragma unroll
-        for (int j = q + 1; j < BS; ++j)
-#pragma unroll
-          for (int i = j; i < BS; ++i) a[i][j] -= a[i][q] * a[j][q];
-      }
-    }
-    __syncthreads();
-    if (tj == cb && ti > cb) {         // X = B L_d^-T, row by row; publish the panel
-      const double r0 = dblk[0][0], r1 = dblk[1][1], r2 = dblk[2][2], r3 = dblk[3][3];
-      const double l10 = dblk[1][0], l20 = dblk[2][0], l21 = dblk[2][1], l30 = dblk[3][0], l31 = dblk[3][1],
-                   l32 = dblk[3][2];
-#pragma unroll
-      for (int ii = 0; ii < BS; ++ii) {
-        const double x0 = a[ii][0] * r0;
-        const double x1 = (a[ii][1] - x0 * l10) * r1;
-        const double x2 = (a[ii][2] - x0 * l20 - x1 * l21) * r2;
-        const double x3 = (a[ii][3] - x0 * l30 - x1 * l31 - x2 * l32) * r3;
-        a[ii][0] = x0; a[ii][1] = x1; a[ii][2] = x2; a[ii][3] = x3;
-        panel[BS * ti + ii][0] = x0; panel[BS * ti + ii][1] = x1;
-        panel[BS * ti + ii][2] = x2; panel[BS * ti + ii][3] = x3;
-      }
-    }
-    __syncthreads();
-    if (tj > cb && ti >= tj) {         // rank-4 update of the blocks right of the panel
-      double pi[BS][BS], pj[BS][BS];
-#pragma unroll
-      for (int ii = 0; ii < BS; ++ii)
-#pragma unroll
-        for (int q = 0; q < BS; ++q) {
-          pi[ii][q] = panel[BS * ti + ii][q];
-          pj[ii][q] = panel[BS * tj + ii][q];
-        }
-#pragma unroll
-      for (int ii = 0; ii < BS; ++ii)
-#pragma unroll
-        for (int jj = 0; jj < BS; ++jj)
-#pragma unroll
-          for (int q = 0; q < BS; ++q) a[ii][jj] -= pi[ii][q] * pj[jj][q];
-    }
-  }
-#pragma unroll
-  for (int ii = 0; ii < BS; ++ii)
-#pragma unroll
-    for (int jj = 0; jj < BS; ++jj) {
-      const int i = BS * ti + ii, j = BS * tj + jj;
-      const double v = (j <= i) ? a[ii][jj] : 0.0;
-      if (i < l && j < l) g[(int64_t)i * ld + j] = v;
-      if (rdiag && i == j && i < l) rdiag[(int64_t)b * rd_bstride + i] = 1.0 / v;
-    }
-  // every thread on the diagonal has seen the pivots of its own block
-  if (info && dependent) atomicOr(info + b, SVDC_FIT_RANK_DEFICIENT);
 }
 
 // ---------------------------------------------------------------------------
-// 64 x 64 tile of a product A[64 x K] (float32 rows) * Bm[K x 64] (float64), accumulated in float64 on the matrix
+// 64 x 64 tile of a product A[64 x K] (rows of type TA) * Bm[K x 64] (float64), accumulated in float64 on the matrix
 // cores by one workgroup of 256 threads (mfma64_accumulate).  The inner dimension is walked in chunks of 32 staged in
 // LDS as float64, A transposed to [k][r]; the next chunk's elements are fetched into registers before the current one
 // is multiplied, so their latency is hidden behind the arithmetic.
@@ -436,14 +616,14 @@ struct TileGemmLds {
   double As[kTileK * (kM64Stride + 1)];    // [k][r], odd stride: the transposing stores of a wave spread over the banks
 };
 
-template <typename LoadA, typename LoadB, typename Emit>
+template <typename TA, typename LoadA, typename LoadB, typename Emit>
 __device__ __forceinline__ void tile_gemm_64x64(int K, LoadA load_a, LoadB load_b, TileGemmLds& lds, Emit emit) {
   constexpr int LA = kM64Stride + 1;
   const int t = threadIdx.x;
   // staging role of this thread: 8 elements of each operand per chunk
   const int ar = t >> 5, ak = t & 31;          // A: rows ar + 8 e, column ak
   const int bk = t >> 6, bj = t & 63;          // B: rows bk + 4 e, column bj
-  float ra[8];
+  TA ra[8];
   double rb[8];
   auto fetch = [&](int k0) {
 #pragma unroll
@@ -499,7 +679,7 @@ __global__ __launch_bounds__(256) void rows_times_small_kernel(const float* __re
   const double* mm = M + (int64_t)b * l * ldm;
   float* out = Out + (int64_t)b * rows * m;
   const int r0 = blockIdx.x * 64, j0 = blockIdx.y * 64;
-  tile_gemm_64x64(
+  tile_gemm_64x64<float>(
       l, [&](int r, int k) { return (r0 + r < rows && k < l) ? in[(int64_t)(r0 + r) * l + k] : 0.f; },
       [&](int k, int j) { return (k < l && j0 + j < m) ? mm[(int64_t)k * ldm + j0 + j] : 0.0; }, lds,
       [&](int r, int j, double x) {
@@ -508,157 +688,214 @@ __global__ __launch_bounds__(256) void rows_times_small_kernel(const float* __re
 }
 
 // ---------------------------------------------------------------------------
-// Out = In * L^-T by forward substitution, one thread per row:
-//   q_j = (z_j - sum_{i<j} q_i L[j][i]) / L[j][j]
-// L (float64 Cholesky factor, lower) and the reciprocals of its diagonal are read
-// from LDS as broadcasts; the row lives in registers.  l <= LMAX <= 64: wider factors are applied block by block
-// (cholqr_apply).
-// The l columns may be a column range of wider rows (row stride ld_io, In and Out already offset to the range's
-// first column) and L a diagonal block of a larger factor (row stride ldl, block b at Lfac + b * l_bstride).  In may
-// be the same buffer as Out: a thread reads its whole row before it writes.
-// ---------------------------------------------------------------------------
-template <int LMAX>
-__global__ __launch_bounds__(256) void tri_solve_rows_kernel(const float* In, const double* __restrict__ Lfac,
-                                                             const double* __restrict__ rdiag, float* Out,
-                                                             int rows, int l, int ld_io, int ldl,
-                                                             int64_t l_bstride, int64_t rd_bstride) {
-  const int b = blockIdx.y, t = threadIdx.x;
-  // every thread reads the same element of L at the same time: the factor is staged in LDS and read as
-  // broadcasts (as scalar loads its 32 KB at l = 64 overflow the scalar cache)
-  __shared__ double Lf[LMAX * LMAX];
-  __shared__ double rd[LMAX];
-  // rows of L at a compile-time stride: every LDS offset below is then a constant and neighbouring elements of a
-  // row are fetched by one wide read
-  for (int e = t; e < l * l; e += 256) Lf[(e / l) * LMAX + e % l] = Lfac[(int64_t)b * l_bstride + (int64_t)(e / l) * ldl + e % l];
-  if (t < l) rd[t] = rdiag[(int64_t)b * rd_bstride + t];
-  __syncthreads();
-  const int64_t row = (int64_t)blockIdx.x * 256 + t;
-  if (row >= rows) return;
-  const float* in = In + ((int64_t)b * rows + row) * ld_io;
-  float* out = Out + ((int64_t)b * rows + row) * ld_io;
-  double q[LMAX];
-  const bool vec = ((l | ld_io) & 3) == 0;   // rows (and column ranges that start at a multiple of 4) are then 16-byte aligned
-  if (vec) {
-#pragma unroll
-    for (int j = 0; j < LMAX; j += 4) {
-      float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (j < l) x = *reinterpret_cast<const float4*>(in + j);
-      q[j] = x.x; q[j + 1] = x.y; q[j + 2] = x.z; q[j + 3] = x.w;
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < LMAX; ++j) q[j] = (j < l) ? (double)in[j] : 0.0;
-  }
-#pragma unroll
-  for (int j = 0; j < LMAX; ++j) {
-    if (j < l) {
-      double s = q[j];
-#pragma unroll
-      for (int i = 0; i < j; ++i) s -= q[i] * Lf[j * LMAX + i];
-      q[j] = s * rd[j];
-    }
-  }
-  if (vec) {
-#pragma unroll
-    for (int j = 0; j < LMAX; j += 4)
-      if (j < l) *reinterpret_cast<float4*>(out + j) = make_float4((float)q[j], (float)q[j + 1], (float)q[j + 2], (float)q[j + 3]);
-  } else {
-#pragma unroll
-    for (int j = 0; j < LMAX; ++j)
-      if (j < l) out[j] = (float)q[j];
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Blocked Cholesky factorisation for l > 64, left-looking over column blocks of 64: for block k at columns c0..c0+63
-//   L_kk = chol(A_kk - sum_{c < c0} L[k, c] L[k, c]^T)                     (chol_reg_kernel with its update)
-//   L_ik = (A_ik - sum_{c < c0} L[i, c] L[k, c]^T) L_kk^-T  for rows i below  (this kernel)
-// The finished columns are kept twice, as L in the lower triangle and as L^T in the upper one (G[c][r] = L[r][c]):
-// every product above then reads rows of the upper triangle, contiguous over the output index.
-// A workgroup takes 64 rows of the panel: all 256 threads form the 64 x 64 update (4 x 4 per thread, float64), then
-// 64 threads solve one row each against L_kk staged in LDS.
+//   L_kk = chol(A_kk - sum_{c < c0} L[k, c] L[k, c]^T), and L_kk^-T              (chol_inv_kernel)
+//   L_ik = (A_ik - sum_{c < c0} L[i, c] L[k, c]^T) L_kk^-T  for rows i below      (this kernel, 64 rows per workgroup)
+// The finished columns are kept twice, as L in the lower triangle and as L^T in the upper one (G[c][r] = L[r][c]).
+// Both products run on the float64 matrix cores: 21 -> 11 us at 128 columns against a substitution row by row.
 // ---------------------------------------------------------------------------
-constexpr int kCholBlock = 64;
+constexpr int kTileLd = kM64Stride + 1;   // row stride of a transposed 64 x 64 float64 tile in LDS
 
-__global__ __launch_bounds__(256) void chol_panel_kernel(double* G, const double* __restrict__ rdiag,
-                                                         int64_t rd_bstride, int l, int c0) {
-  constexpr int H = kCholBlock, LT = H + 1;
-  __shared__ double T[H * LT];     // [row][j]
-  __shared__ double Lk[H * H];     // [j][i]
-  __shared__ double rd[H];
-  const int b = blockIdx.y, t = threadIdx.x;
+__global__ __launch_bounds__(256) void chol_panel_kernel(double* G, const double* __restrict__ Minv, int64_t m_bstride,
+                                                         int l, int c0) {
+  constexpr int H = kCholBlock;
+  __shared__ TileGemmLds lds;
+  __shared__ double Tt[H * kTileLd];     // [column][row]
+  const int b = blockIdx.y;
   double* g = G + (int64_t)b * l * l;
+  const double* mi = Minv + (int64_t)b * m_bstride;
   const int r0 = c0 + H + blockIdx.x * H;          // first row of this workgroup
-  for (int e = t; e < H * H; e += 256) Lk[e] = g[(int64_t)(c0 + e / H) * l + c0 + e % H];
-  if (t < H) rd[t] = rdiag[(int64_t)b * rd_bstride + c0 + t];
-  const int ty = t >> 4, tx = t & 15;
-  double acc[4][4];
-#pragma unroll
-  for (int ii = 0; ii < 4; ++ii)
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) acc[ii][jj] = 0.0;
-  int ri[4];
-#pragma unroll
-  for (int ii = 0; ii < 4; ++ii) ri[ii] = min(r0 + 4 * ty + ii, l - 1);
-#pragma unroll 8
-  for (int c = 0; c < c0; ++c) {
-    const double* gc = g + (int64_t)c * l;
-    double av[4], bv[4];
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii) av[ii] = gc[ri[ii]];
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) bv[jj] = gc[c0 + tx + 16 * jj];
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii)
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) acc[ii][jj] += av[ii] * bv[jj];
+  if (c0 > 0) {
+    tile_gemm_64x64<double>(
+        c0, [&](int r, int k) { return r0 + r < l ? g[(int64_t)(r0 + r) * l + k] : 0.0; },
+        [&](int k, int j) { return g[(int64_t)k * l + c0 + j]; }, lds,
+        [&](int r, int j, double x) { Tt[j * kTileLd + r] = (r0 + r < l ? g[(int64_t)(r0 + r) * l + c0 + j] : 0.0) - x; });
+  } else {
+    for (int e = threadIdx.x; e < H * H; e += 256) {
+      const int r = e / H, j = e % H;
+      Tt[j * kTileLd + r] = r0 + r < l ? g[(int64_t)(r0 + r) * l + c0 + j] : 0.0;
+    }
   }
-#pragma unroll
-  for (int ii = 0; ii < 4; ++ii)
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj)
-      T[(4 * ty + ii) * LT + tx + 16 * jj] = g[(int64_t)ri[ii] * l + c0 + tx + 16 * jj] - acc[ii][jj];
   __syncthreads();
-  const int row = r0 + t;
-  if (t >= H || row >= l) return;
-  double q[H];
-#pragma unroll
-  for (int j = 0; j < H; ++j) q[j] = T[t * LT + j];
-#pragma unroll
-  for (int j = 0; j < H; ++j) {
-    double s = q[j];
-#pragma unroll
-    for (int i = 0; i < j; ++i) s -= q[i] * Lk[j * H + i];
-    q[j] = s * rd[j];
-  }
-#pragma unroll
-  for (int j = 0; j < H; ++j) {
-    g[(int64_t)row * l + c0 + j] = q[j];
-    g[(int64_t)(c0 + j) * l + row] = q[j];
-  }
+  tile_gemm_64x64<double>(
+      H, [&](int r, int k) { return Tt[k * kTileLd + r]; }, [&](int k, int j) { return mi[(int64_t)k * H + j]; }, lds,
+      [&](int r, int j, double x) {
+        if (r0 + r < l) {
+          g[(int64_t)(r0 + r) * l + c0 + j] = x;
+          g[(int64_t)(c0 + j) * l + r0 + r] = x;
+        }
+      });
 }
 
 // ---------------------------------------------------------------------------
-// Out[:, c0 + j] = In[:, c0 + j] - sum_{c < c0} Out[:, c] * L[c0 + j][c],  j < w: the update step of Out = In L^-T by
-// column blocks, between the triangular solves of the blocks (tri_solve_rows_kernel).  L^T is read from the upper
-// triangle of G.  A workgroup takes 64 rows x the block's columns (tile_gemm_64x64).
+// Out = In L^-T for 64 rows per workgroup, all columns: by column blocks of 64,
+//   Out_j = (In_j - sum_{i < j} Out_i L_ji^T) L_jj^-T
+// with the inverses of the diagonal blocks (chol_inv_kernel) and L^T from the upper triangle of G, every product on the
+// float64 matrix cores.  A wave has 16 rows to itself: its rows of In and the small matrices (which all workgroups
+// share, so they come from L2) are loaded in operand layout straight into registers, and of the 16 x 16 tiles of the
+// triangular L_jj^-T only the ten that are not zero are used.  The contraction index of step (s, e) is
+// 16 s + 4 (lane / 16) + e, so that a lane's four steps are one 16-byte piece of a float32 row.
+// The result leaves as float32 rows (out, nullable) and/or as the operand words of the projection (pq.p, nullable; see
+// pack_q_kernel), so that an iteration that goes on with the projection writes nothing else.  zero_in: the rows of In are
+// cleared once they have been read (the next back-projection accumulates into them).  Bound by the float64 matrix rate
+// (11 us for 57 blocks of 3072 x 64) and the latency of its loads: 38 us there and 8.4 us for one block, against 57 + 20 and 26 + 5 us for a
+// forward substitution per row followed by a packing kernel.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void rows_minus_product_kernel(const float* __restrict__ In, float* Out,
-                                                                 const double* __restrict__ G, int rows, int l,
-                                                                 int c0, int w) {
-  __shared__ TileGemmLds lds;
-  const int b = blockIdx.y;
-  const float* in = In + (int64_t)b * rows * l;
-  float* out = Out + (int64_t)b * rows * l;
+__device__ __forceinline__ void pack_rows(const float* ot, int ldo, int row0, int D, int b, int l, PackedQ pq);
+
+template <bool ONE_BLOCK>
+__global__ __launch_bounds__(256, ONE_BLOCK ? 3 : 1) void apply_factor_kernel(float* In, const double* __restrict__ G,
+                                                           const double* __restrict__ Minv, int64_t m_bstride, float* out,
+                                                           PackedQ pq, int rows, int l, int zero_in) {
+  constexpr int H = kCholBlock, LT = H + 2;
+  extern __shared__ __align__(16) char dyn[];
+  const int nb = ONE_BLOCK ? 1 : (l + H - 1) / H, ldo = nb * H + 4;
+  float* ot = reinterpret_cast<float*>(dyn);                                             // [64][ldo]
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, m = lane & 15, kq = lane >> 4;
+  // the wave's right-hand sides on their way from the result layout to the operand layout, [16][LT]
+  double* tt = reinterpret_cast<double*>(dyn + (size_t)H * ldo * sizeof(float)) + wave * 16 * LT;
+  const int b = blockIdx.y, r0 = blockIdx.x * H, rw = r0 + 16 * wave;
+  float* in = In + (int64_t)b * rows * l;
   const double* g = G + (int64_t)b * l * l;
-  const int r0 = blockIdx.x * 64;
-  tile_gemm_64x64(
-      c0, [&](int r, int k) { return (r0 + r < rows && k < c0) ? out[(int64_t)(r0 + r) * l + k] : 0.f; },
-      [&](int k, int j) { return (k < c0 && j < w) ? g[(int64_t)k * l + c0 + j] : 0.0; }, lds,
-      [&](int r, int j, double x) {
-        const int64_t at = (int64_t)(r0 + r) * l + c0 + j;
-        if (r0 + r < rows && j < w) out[at] = (float)((double)in[at] - x);
-      });
+  for (int j0 = 0; j0 < l; j0 += H) {
+    const int w = min(H, l - j0), ldm = l <= H ? l : H;
+    const double* mi = Minv + (int64_t)b * m_bstride + (int64_t)(j0 / H) * H * H;
+    double bm[4][4][4];                        // [s][e][y], y >= s: L_jj^-T[16 s + 4 kq + e][16 y + m]
+    auto load_b = [&](int s) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int y = s; y < 4; ++y) {
+          const int k = 16 * s + 4 * kq + e, j = 16 * y + m;
+          bm[s][e][y] = mi[min(k, w - 1) * ldm + min(j, w - 1)];     // columns beyond w are not used
+        }
+    };
+    load_b(0);
+    double a[4][4];
+    if (j0 == 0) {
+      const float* row = in + (int64_t)min(rw + m, rows - 1) * l;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const int k = 16 * s + 4 * kq;
+        if ((l & 3) == 0) {
+          float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (k < w) x = *reinterpret_cast<const float4*>(row + k);
+          a[s][0] = x.x; a[s][1] = x.y; a[s][2] = x.z; a[s][3] = x.w;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) a[s][e] = k + e < w ? (double)row[k + e] : 0.0;
+        }
+      }
+    } else if constexpr (!ONE_BLOCK) {
+      f64x4 up[4];
+      float rhs[4][4];
+#pragma unroll
+      for (int y = 0; y < 4; ++y) {
+        up[y] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = rw + 4 * v + kq, j = 16 * y + m;
+          rhs[y][v] = (r < rows && j < w) ? in[(int64_t)r * l + j0 + j] : 0.f;
+        }
+      }
+      double gb[4][4], gn[4][4];               // [e][y]: L^T[k0 + 4 kq + e][j0 + 16 y + m]
+      auto fetch = [&](int k0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int y = 0; y < 4; ++y) {
+            const int j = 16 * y + m;
+            gn[e][y] = j < w ? g[(int64_t)(k0 + 4 * kq + e) * l + j0 + j] : 0.0;
+          }
+      };
+      fetch(0);
+      for (int k0 = 0; k0 < j0; k0 += 16) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int y = 0; y < 4; ++y) gb[e][y] = gn[e][y];
+        if (k0 + 16 < j0) fetch(k0 + 16);
+        const float4 o = *reinterpret_cast<const float4*>(ot + (16 * wave + m) * ldo + k0 + 4 * kq);
+        const double oa[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int y = 0; y < 4; ++y) up[y] = __builtin_amdgcn_mfma_f64_16x16x4f64(oa[e], gb[e][y], up[y], 0, 0, 0);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+      for (int y = 0; y < 4; ++y)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) tt[(4 * v + kq) * LT + 16 * y + m] = (double)rhs[y][v] - up[y][v];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[s][e] = tt[m * LT + 16 * s + 4 * kq + e];
+    }
+    f64x4 acc[4];
+#pragma unroll
+    for (int y = 0; y < 4; ++y) acc[y] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      if (s < 3) load_b(s + 1);                // one step ahead
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int y = s; y < 4; ++y) {
+          const double bv = w < H && 16 * s + 4 * kq + e >= w ? 0.0 : bm[s][e][y];
+          acc[y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s][e], bv, acc[y], 0, 0, 0);
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+    for (int y = 0; y < 4; ++y)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) ot[(16 * wave + 4 * v + kq) * ldo + j0 + 16 * y + m] = (float)acc[y][v];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // a wave reads back only its own rows until here
+  }
+  __syncthreads();
+  const int nrow = min(H, rows - r0);
+  float* irow = in + (int64_t)r0 * l;
+  float* orow = out ? out + ((int64_t)b * rows + r0) * l : nullptr;
+  if (orow || zero_in) {
+    int r = threadIdx.x / l, j = threadIdx.x % l;        // element e = r l + j, advanced by 256 without divisions
+    const int dr = 256 / l, dj = 256 % l;
+    for (int e = threadIdx.x; e < nrow * l; e += 256) {
+      if (orow) orow[e] = ot[r * ldo + j];
+      if (zero_in) irow[e] = 0.f;
+      r += dr; j += dj;
+      if (j >= l) { j -= l; ++r; }
+    }
+  }
+  if (pq.p) pack_rows(ot, ldo, r0, rows, b, l, pq);
+}
+
+// The 64 rows of Q in `ot` as operand words of the projection: tile (cg, jt) of 64 lanes x 8 bf16, lane (r, g), e ->
+// Q[32 cg + 8 g + e][16 jt + r], high and low parts; sketches wider than 128 as two column ranges.
+__device__ __forceinline__ void pack_rows(const float* ot, int ldo, int row0, int D, int b, int l, PackedQ pq) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (h >= pq.ranges) break;
+    const int KT = pq.kt[h];
+    const int64_t per = (int64_t)D * KT * 16;                     // elements of one part of one block
+    u32x4* p = reinterpret_cast<u32x4*>(pq.p + pq.offset[h]) + (int64_t)b * 2 * (per / 8);
+    for (int q = wave; q < 2 * KT; q += 4) {
+      const int c = q / KT, jt = q % KT, cg = row0 / 32 + c;
+      if (32 * cg >= D) continue;
+      const int col = 128 * h + 16 * jt + r;
+      float x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = col < l ? ot[(32 * c + 8 * g + e) * ldo + col] : 0.f;
+      u32x4 hi, lo;
+      split_operand(x, &hi, &lo);
+      const int64_t at = ((int64_t)cg * KT + jt) * 64 + lane;
+      p[at] = hi;
+      p[per / 8 + at] = lo;
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1070,85 +1307,83 @@ void gemm_fty(const svdc_shape& s, int l, const T* F, const float* Y, float* Z, 
   fit_gemm_kernel<T, true><<<grid, 256, 0, st>>>(F, Y, Z, s.N, s.D, l, s.ldf, s.block_stride, split_len, nsplit);
 }
 
-void gram(const float* A, double* G, double* Gpart, int B, int rows, int l, hipStream_t st) {
-  const int ntile = (l + 63) / 64;
-  int rows_per_slice = ((rows + kGramSlices - 1) / kGramSlices + 15) / 16 * 16;
+// Scratch for partial Gram matrices: `doubles` float64 values.
+struct GramScratch { double* p; int64_t doubles; };
+
+// Row slices: as many as fit into one round of two workgroups per compute unit (three for l <= 64), of at least 64 rows
+// each and as the scratch holds.
+void gram(const float* A, double* G, GramScratch sc, int B, int rows, int l, hipStream_t st) {
+  const int ntile = (l + 63) / 64, tiles = ntile * (ntile + 1) / 2;
+  const int64_t ll = (int64_t)l * l;
+  int64_t want = std::max<int64_t>(1, (l <= 64 ? 768 : 512) / ((int64_t)tiles * B));
+  want = std::min<int64_t>(want, std::max<int64_t>(kGramSlices, sc.doubles / (ll * B)));
+  int rows_per_slice = (int)(((rows + want - 1) / want + 15) / 16 * 16);
   if (rows_per_slice < 64) rows_per_slice = 64;
   const int nslice = (rows + rows_per_slice - 1) / rows_per_slice;
-  dim3 grid(nslice, ntile * (ntile + 1) / 2, B);
-  gram_f64_kernel<<<grid, 256, 0, st>>>(A, Gpart, rows, l, rows_per_slice);
-  const int64_t ll = (int64_t)l * l;
-  gram_reduce_kernel<<<dim3((unsigned)((ll + 255) / 256), B), 256, 0, st>>>(Gpart, G, nslice, l);
+  const dim3 grid(nslice, tiles, B);
+  if (l <= 64) gram_f64_kernel<true><<<grid, 256, 0, st>>>(A, sc.p, rows, l, rows_per_slice);
+  else gram_f64_kernel<false><<<grid, 256, 0, st>>>(A, sc.p, rows, l, rows_per_slice);
+  gram_reduce_kernel<<<dim3((unsigned)((ll + 63) / 64), B), 256, 0, st>>>(sc.p, G, nslice, l);
 }
 
 // Cholesky factor of G + shift I in place, l <= 256: L in the lower triangle; for l > 64 the strict upper triangle
-// holds L^T outside the 64 x 64 diagonal blocks (whose upper halves are zeroed).  scratch (block stride l * l
-// doubles): receives the reciprocal diagonal in its first l entries per block when not null; REQUIRED for l > 64,
-// where entry [l] carries the diagonal shift from the first block's factorisation to the later ones.
-int32_t chol_factor(double* G, int B, int l, int32_t* info, hipStream_t st, double* scratch) {
+// holds L^T outside the 64 x 64 diagonal blocks (whose upper halves are zeroed).  M (block stride l * l doubles)
+// receives the transposed inverses of the diagonal blocks: row stride l for the only one of l <= 64, otherwise 64 and
+// 64 * 64 doubles apart; with l > 64 its last entry carries the shift from the first block to the later ones.
+// want_inv = false (the factor is all that is asked for): the inverse of the last block is not formed.
+void chol_factor(double* G, int B, int l, int32_t* info, hipStream_t st, double* M, bool want_inv) {
   const int64_t ll = (int64_t)l * l;
   constexpr int H = kCholBlock;
-  if (l <= H) {
-    chol_reg_kernel<4><<<B, 256, 0, st>>>(G, ll, l, scratch, ll, l, 1e-14, info, ChoShift{nullptr, 0, l},
-                                          ChoUpdate{nullptr, 0, 0, 0});
-    return SVDC_OK;
-  }
-  if (!scratch) return SVDC_E_NULL;
+  double* slot = l > H ? M + ll - 1 : nullptr;
   for (int c0 = 0; c0 < l; c0 += H) {
     const int w = std::min(H, l - c0);
-    chol_reg_kernel<4><<<B, 256, 0, st>>>(G + (int64_t)c0 * l + c0, ll, l, scratch + c0, ll, w, 1e-14, info,
-                                          ChoShift{scratch + l, ll, c0 == 0 ? l : 0},
-                                          ChoUpdate{c0 ? G + c0 : nullptr, ll, l, c0});
-    if (c0 + w < l) chol_panel_kernel<<<dim3((l - c0 - w + H - 1) / H, B), 256, 0, st>>>(G, scratch, ll, l, c0);
+    const bool last = c0 + w >= l;
+    chol_inv_kernel<<<B, 256, 0, st>>>(G, l, c0, w, M + (int64_t)(c0 / H) * H * H, ll, l <= H ? l : H,
+                                       (want_inv || !last) ? 1 : 0, slot, ll, 1e-14, info);
+    if (!last)
+      chol_panel_kernel<<<dim3((l - c0 - w + H - 1) / H, B), 256, 0, st>>>(G, M + (int64_t)(c0 / H) * H * H, ll, l, c0);
   }
-  return SVDC_OK;
 }
 
 // Out[rows x m] = In[rows x l] * M[l x m]
-int32_t rows_times_small(const float* In, const double* M, float* Out, int B, int rows, int l, int m, int ldm,
-                         hipStream_t st) {
+void rows_times_small(const float* In, const double* M, float* Out, int B, int rows, int l, int m, int ldm,
+                      hipStream_t st) {
   dim3 grid((rows + 63) / 64, (m + 63) / 64, B);
   rows_times_small_kernel<<<grid, 256, 0, st>>>(In, M, Out, rows, l, m, ldm);
-  return SVDC_OK;
 }
 
-// Orthonormalise the columns of Zin by CholeskyQR (Gram matrix and Cholesky factor in float64).
-// One pass leaves the result in Qout and is accurate to about eps32 * cond(Zin): enough to keep the
-// power iteration well conditioned.  two_pass repeats the step on the result (CholeskyQR2), giving
-// orthonormality at float32 round-off; the result is then back in Zin.
-// Out = In * L^-T with L the Cholesky factor of In^T In (left in G by chol_factor)
-int32_t cholqr_apply(const float* In, float* Out, double* G, double* M, int B, int rows, int l, int32_t* info,
-                     hipStream_t st) {
-  const int64_t ll = (int64_t)l * l;
-  // M receives the reciprocal diagonal of L (its first l entries per block)
-  if (chol_factor(G, B, l, info, st, M) != SVDC_OK) return SVDC_E_HIP;
-  // by column blocks of 64: Out_j = (In_j - sum_{i < j} Out_i L_ji^T) L_jj^-T
+// Out = In * L^-T with L and the inverses of its diagonal blocks in G and M (chol_factor)
+int32_t apply_factor(float* In, float* out, PackedQ pq, const double* G, const double* M, int B, int rows, int l,
+                     bool zero_in, hipStream_t st) {
   constexpr int H = kCholBlock;
-  const dim3 grid((rows + 255) / 256, B);
-  for (int c0 = 0; c0 < l; c0 += H) {
-    const int w = std::min(H, l - c0);
-    const float* src = In;
-    if (c0 > 0) {
-      rows_minus_product_kernel<<<dim3((rows + H - 1) / H, B), 256, 0, st>>>(In, Out, G, rows, l, c0, w);
-      src = Out;
-    }
-    const double* lkk = G + (int64_t)c0 * l + c0;
-    if (w <= 16) tri_solve_rows_kernel<16><<<grid, 256, 0, st>>>(src + c0, lkk, M + c0, Out + c0, rows, w, l, l, ll, ll);
-    else if (w <= 32) tri_solve_rows_kernel<32><<<grid, 256, 0, st>>>(src + c0, lkk, M + c0, Out + c0, rows, w, l, l, ll, ll);
-    else tri_solve_rows_kernel<64><<<grid, 256, 0, st>>>(src + c0, lkk, M + c0, Out + c0, rows, w, l, l, ll, ll);
-  }
-  return SVDC_OK;
+  const int nb = (l + H - 1) / H;
+  const size_t lds = (size_t)H * (nb * H + 4) * sizeof(float) + (nb > 1 ? (size_t)H * (H + 2) * sizeof(double) : 0);
+  const dim3 grid((rows + H - 1) / H, B);
+  auto launch = [&](auto kernel) -> int32_t {
+    if (set_dyn_lds((const void*)kernel, lds) != SVDC_OK) return SVDC_E_HIP;
+    kernel<<<grid, 256, lds, st>>>(In, G, M, (int64_t)l * l, out, pq, rows, l, zero_in ? 1 : 0);
+    return SVDC_OK;
+  };
+  return nb == 1 ? launch(apply_factor_kernel<true>) : launch(apply_factor_kernel<false>);
 }
 
-int32_t orth(float* Zin, float* Qout, double* G, double* Gpart, double* M, int B, int rows, int l, bool two_pass,
-             int32_t* info, hipStream_t st) {
-  gram(Zin, G, Gpart, B, rows, l, st);
-  if (cholqr_apply(Zin, Qout, G, M, B, rows, l, info, st) != SVDC_OK) return SVDC_E_HIP;
-  if (!two_pass) return SVDC_OK;
+// Orthonormalise the columns of Zin by CholeskyQR (Gram matrix, Cholesky factor and products with it in float64).
+// One pass is accurate to about eps32 * cond(Zin), enough to keep the power iteration well conditioned: the result leaves
+// as the projection's operand words where there is a packed form (pq.p), else as float32 rows in Qout.  two_pass repeats
+// the step on the result (CholeskyQR2), giving orthonormality at float32 round-off; the result is then back in Zin, as
+// float32 rows, and in the packed form.
+int32_t orth(float* Zin, float* Qout, double* G, GramScratch sc, double* M, int B, int rows, int l, bool two_pass,
+             PackedQ pq, bool zero_in, int32_t* info, hipStream_t st) {
+  gram(Zin, G, sc, B, rows, l, st);
+  chol_factor(G, B, l, info, st, M, true);
+  const PackedQ none{};
+  if (!two_pass) return apply_factor(Zin, pq.p ? nullptr : Qout, pq, G, M, B, rows, l, zero_in, st);
+  if (apply_factor(Zin, Qout, none, G, M, B, rows, l, false, st) != SVDC_OK) return SVDC_E_HIP;
   // the second pass factors a matrix that is already orthonormal to float32 round-off: only the first one can
   // meet a dependent column
-  gram(Qout, G, Gpart, B, rows, l, st);
-  return cholqr_apply(Qout, Zin, G, M, B, rows, l, nullptr, st);
+  gram(Qout, G, sc, B, rows, l, st);
+  chol_factor(G, B, l, nullptr, st, M, true);
+  return apply_factor(Qout, Zin, pq, G, M, B, rows, l, false, st);
 }
 
 template <typename T>
@@ -1168,6 +1403,17 @@ int32_t run_fit_typed(const svdc_shape& s, const FitPlan& pl, const T* F, float*
   const int64_t nq = (int64_t)B * s.D * l;
   // fro accumulators, status words and Jacobi counters are adjacent 256-byte aligned areas: one fill clears them all
   zero_f64(misc, (int64_t)((pl.off_jcnt - pl.off_misc) + align_up((size_t)B * 4 * sizeof(int32_t), 8)) / 8, st);
+  // Partial Gram matrices go where there is most room: into their own area, or into whichever of Y and Z is not in use
+  auto scratch = [&](void* other, int64_t rows) {
+    const GramScratch own{Gp, (int64_t)B * kGramSlices * l * l}, lent{(double*)other, (int64_t)B * rows * l / 2};
+    return lent.doubles > own.doubles ? lent : own;
+  };
+  void* Qp = ws + pl.off_Qp;
+  const PackedQ pq = pl.mfma ? fit_mfma_packed_q(s, l, Qp) : PackedQ{};
+  bool packed = false;                       // Q is in its packed form already
+  // bf16 features with several row groups accumulate Z with atomics: it has to be clear beforehand
+  const bool zero_z = pl.mfma && fit_mfma_backproject_accumulates(s, l);
+  bool z_clear = false;
   // With power iterations the Gaussian test matrix (D x l) is used as it is: its columns are well conditioned
   // and every product F^T F Q is re-orthonormalised afterwards.  With none, the sketch is Z = F^T Omega with a
   // Gaussian Omega (N x l) -- the plain randomized range finder, exact when rank(F) <= l -- and Q <- orth(Z), two
@@ -1175,15 +1421,15 @@ int32_t run_fit_typed(const svdc_shape& s, const FitPlan& pl, const T* F, float*
   if (pl.q == 0) {
     const int64_t ny = (int64_t)B * s.N * l;
     init_omega_kernel<<<(unsigned)((ny + 255) / 256), 256, 0, st>>>(Y, (int64_t)s.N * l, ny, pl.seed);
-    if (pl.mfma) fit_mfma_backproject(s, l, F, Y, nullptr, Z, st);
+    if (pl.mfma) fit_mfma_backproject(s, l, F, Y, nullptr, Z, false, st);
     else gemm_fty<T>(s, l, F, Y, Z, st);
-    if (orth(Z, Q, G, Gp, M, B, s.D, l, true, info, st) != SVDC_OK) return SVDC_E_HIP;
+    if (orth(Z, Q, G, scratch(Y, s.N), M, B, s.D, l, true, pq, false, info, st) != SVDC_OK) return SVDC_E_HIP;
+    packed = pl.mfma;
     std::swap(Q, Z);
   } else {
     init_omega_kernel<<<(unsigned)((nq + 255) / 256), 256, 0, st>>>(Q, (int64_t)s.D * l, nq, pl.seed);
   }
 
-  void* Qp = ws + pl.off_Qp;
   const bool want_fro = fro2 != nullptr;
   bool fro_done = false;
   // Y = F Q.  The last product feeds the Rayleigh-Ritz step and uses the full-precision operand split.
@@ -1191,7 +1437,7 @@ int32_t run_fit_typed(const svdc_shape& s, const FitPlan& pl, const T* F, float*
   constexpr bool kF32 = std::is_same<T, float>::value;
   auto project = [&](bool last) {
     if (pl.mfma) {
-      fit_mfma_pack_q(s, l, Q, Qp, st);
+      if (!packed) fit_mfma_pack_q(s, l, Q, Qp, st);
       fit_mfma_project(s, l, F, Qp, Y, (last || kF32) ? nullptr : (void*)Y, (last && want_fro) ? misc : nullptr,
                        last || kF32, st);
       if (last && want_fro) fro_done = true;
@@ -1202,19 +1448,22 @@ int32_t run_fit_typed(const svdc_shape& s, const FitPlan& pl, const T* F, float*
   for (int it = 0; it < pl.q; ++it) {
     project(false);
     if (pl.mfma) {
-      fit_mfma_backproject(s, l, F, Y, kF32 ? nullptr : Y, Z, st);   // bf16: Y holds the packed form here
+      fit_mfma_backproject(s, l, F, Y, kF32 ? nullptr : Y, Z, z_clear, st);   // bf16: Y holds the packed form here
     } else {
       gemm_fty<T>(s, l, F, Y, Z, st);
     }
     const bool last_it = it + 1 == pl.q;
-    if (orth(Z, Q, G, Gp, M, B, s.D, l, last_it, info, st) != SVDC_OK) return SVDC_E_HIP;
+    if (orth(Z, Q, G, scratch(Y, s.N), M, B, s.D, l, last_it, pq, zero_z && !last_it, info, st) != SVDC_OK)
+      return SVDC_E_HIP;
+    z_clear = zero_z;
+    packed = pl.mfma;
     if (last_it) std::swap(Q, Z);
   }
 
   // Rayleigh-Ritz on span(Q)
   project(true);
-  gram(Y, G, Gp, B, s.N, l, st);
-  if (chol_factor(G, B, l, info, st, M) != SVDC_OK) return SVDC_E_HIP;   // M: scratch until the Jacobi writes it
+  gram(Y, G, scratch(Z, s.D), B, s.N, l, st);
+  chol_factor(G, B, l, info, st, M, false);   // M: scratch until the Jacobi writes it
   if (want_fro && !fro_done) {
     const int rpg = 64;
     sumsq_kernel<T><<<dim3((s.N + rpg - 1) / rpg, B), 256, 0, st>>>(F, misc, s.N, s.D, s.ldf, s.block_stride, rpg);
@@ -1251,7 +1500,7 @@ int32_t run_fit_typed(const svdc_shape& s, const FitPlan& pl, const T* F, float*
     jacobi_finish_kernel<<<B, 256, 0, st>>>(Wg, M, sigma, l, s.k, misc, fro2, pl.max_sweeps, cnt, info);
   }
   if (jrc != SVDC_OK) return jrc;
-  if (rows_times_small(Q, M, V, B, s.D, l, s.k, l, st) != SVDC_OK) return SVDC_E_HIP;
+  rows_times_small(Q, M, V, B, s.D, l, s.k, l, st);
   return launch_status();
 }
 

@@ -760,30 +760,46 @@ void backproject_one(const svdc_shape& s, int l, const void* F, const float* Y, 
 template <int KT>
 constexpr int width_for_f32() { return KT <= 2 ? 6 : (KT == 4 ? 3 : 2); }
 
+// Widest slab (chunks per wave) that the back-projection of this shape may take.
+// Small batches: narrower slabs give more workgroups without more row groups, whose partial sums meet in float
+// atomics (one per element and row group): the widest slab that still gives 64 slabs over all blocks, if any.
+// Measured at 4608 x 3072, width 64: 42 -> 15 us for one block, 55 -> 36 us for 4, 72 -> 53 us for 8; from 28
+// blocks on the widest slab is the fastest again.  Not for float32 features, whose back-projection reads and
+// splits Y as float32 rows once per slab (18432 x 3072, one block: 3.7 -> 4.7 ms per fit at width 128 when tried).
 template <typename T, int KT>
-void backproject_kt(const svdc_shape& s, int l, const void* F, const float* Y, const u32x4* Yp, float* Z,
-                    Strides ld, hipStream_t st) {
-  constexpr int cap = std::is_same<T, float>::value ? width_for_f32<KT>() : width_for<KT>();
-  // Small batches: narrower slabs give more workgroups without more row groups, whose partial sums meet in float
-  // atomics (one per element and row group): the widest slab that still gives 64 slabs over all blocks, if any.
-  // Measured at 4608 x 3072, width 64: 42 -> 15 us for one block, 55 -> 36 us for 4, 72 -> 53 us for 8; from 28
-  // blocks on the widest slab is the fastest again.  Not for float32 features, whose back-projection reads and
-  // splits Y as float32 rows once per slab (18432 x 3072, one block: 3.7 -> 4.7 ms per fit at width 128 when tried).
+constexpr int backproject_cap() { return std::is_same<T, float>::value ? width_for_f32<KT>() : width_for<KT>(); }
+template <typename T, int KT>
+int backproject_max_width(const svdc_shape& s, bool packed) {
+  constexpr int cap = backproject_cap<T, KT>();
   constexpr int64_t kMinSlabs = 64;
   const int m = s.D / 128;
   int maxw = cap;
-  if (!std::is_same<T, float>::value && Yp) {   // packed Y only: float32 rows of Y cost the same once per slab
+  if (!std::is_same<T, float>::value && packed) {   // packed Y only: float32 rows of Y cost the same once per slab
     maxw = 1;
     for (int w : {2, 3, 4, 6, 12})
       if (w <= cap && m % w == 0 && (int64_t)(m / w) * s.B >= kMinSlabs) maxw = w;
   }
+  return maxw;
+}
+
+// calls fn(NCW) with the slab width of this shape as a compile-time constant
+template <typename T, int KT, typename Fn>
+void backproject_by_width(const svdc_shape& s, bool packed, Fn fn) {
+  constexpr int cap = backproject_cap<T, KT>();
   by_width<cap>(
-      s.D / 128, maxw, [&] { backproject_one<T, (cap >= 12 ? 12 : 1), KT>(s, l, F, Y, Yp, Z, ld, st); },
-      [&] { backproject_one<T, (cap >= 6 ? 6 : 1), KT>(s, l, F, Y, Yp, Z, ld, st); },
-      [&] { backproject_one<T, (cap >= 4 ? 4 : 1), KT>(s, l, F, Y, Yp, Z, ld, st); },
-      [&] { backproject_one<T, (cap >= 3 ? 3 : 1), KT>(s, l, F, Y, Yp, Z, ld, st); },
-      [&] { backproject_one<T, 2, KT>(s, l, F, Y, Yp, Z, ld, st); },
-      [&] { backproject_one<T, 1, KT>(s, l, F, Y, Yp, Z, ld, st); });
+      s.D / 128, backproject_max_width<T, KT>(s, packed), [&] { fn(std::integral_constant<int, (cap >= 12 ? 12 : 1)>{}); },
+      [&] { fn(std::integral_constant<int, (cap >= 6 ? 6 : 1)>{}); },
+      [&] { fn(std::integral_constant<int, (cap >= 4 ? 4 : 1)>{}); },
+      [&] { fn(std::integral_constant<int, (cap >= 3 ? 3 : 1)>{}); }, [&] { fn(std::integral_constant<int, 2>{}); },
+      [&] { fn(std::integral_constant<int, 1>{}); });
+}
+
+template <typename T, int KT>
+void backproject_kt(const svdc_shape& s, int l, const void* F, const float* Y, const u32x4* Yp, float* Z,
+                    Strides ld, hipStream_t st) {
+  backproject_by_width<T, KT>(s, Yp != nullptr, [&](auto ncw) {
+    backproject_one<T, decltype(ncw)::value, KT>(s, l, F, Y, Yp, Z, ld, st);
+  });
 }
 
 // Sketches wider than 128 are handled as two column ranges (128 and the rest), each with the kernels of its own
@@ -860,13 +876,46 @@ void fit_mfma_project(const svdc_shape& s, int l, const void* F, const void* Qp,
   }
 }
 
+PackedQ fit_mfma_packed_q(const svdc_shape& s, int l, void* Qp) {
+  ColRange r[2];
+  PackedQ q;
+  q.p = static_cast<char*>(Qp);
+  q.ranges = col_ranges(l, r);
+  int64_t off = 0;
+  for (int h = 0; h < q.ranges; ++h) {
+    q.kt[h] = kt_for(r[h].l);
+    q.offset[h] = off;
+    off += (int64_t)packed_q_bytes_one(s, r[h].l);
+  }
+  return q;
+}
+
+bool fit_mfma_backproject_accumulates(const svdc_shape& s, int l) {
+  ColRange r[2];
+  const int n = col_ranges(l, r);
+  bool any = false;
+  for (int h = 0; h < n; ++h)
+    by_kt(r[h].l, [&](auto kt) {
+      constexpr int KT = decltype(kt)::value;
+      auto groups = [&](auto ncw) {
+        int gpb, rows;
+        backproject_groups<decltype(ncw)::value>(s, &gpb, &rows);
+        any = any || gpb > 1;
+      };
+      // the power iterations hand bf16 features' Y over in packed form
+      if (s.dtype == SVDC_F32) backproject_by_width<float, KT>(s, false, groups);
+      else backproject_by_width<bf16_t, KT>(s, true, groups);
+    });
+  return any;
+}
+
 void fit_mfma_backproject(const svdc_shape& s, int l, const void* F, const float* Y, const void* Ypacked, float* Z,
-                          hipStream_t st) {
+                          bool z_clear, hipStream_t st) {
   ColRange r[2];
   const int n = col_ranges(l, r);
   const char* yp = static_cast<const char*>(Ypacked);
-  bool cleared = false;
-  if (n > 1) {   // the column ranges interleave in memory: clear all of Z once, for whichever range accumulates
+  bool cleared = z_clear;
+  if (n > 1 && !cleared) {   // the column ranges interleave in memory: clear all of Z once, for whichever range accumulates
     const int64_t cnt = (int64_t)s.B * s.D * l;
     clear_f32_kernel<<<(unsigned)((cnt + 255) / 256), 256, 0, st>>>(Z, cnt);
     cleared = true;

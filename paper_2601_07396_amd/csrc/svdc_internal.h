@@ -76,14 +76,25 @@ int32_t run_fit(const svdc_shape& s, const FitPlan& plan, const void* F, float* 
 bool fit_mfma_supported(const svdc_shape& s, int l);
 size_t fit_mfma_packed_q_bytes(const svdc_shape& s, int l);
 void fit_mfma_pack_q(const svdc_shape& s, int l, const float* Q, void* Qp, hipStream_t st);
+// Where the operand words of Q go, for a kernel that writes them itself: per column range its 16-column tiles and byte
+// offset (see pack_q_kernel).
+struct PackedQ {
+  char* p = nullptr;
+  int ranges = 0;
+  int kt[2] = {0, 0};
+  int64_t offset[2] = {0, 0};
+};
+PackedQ fit_mfma_packed_q(const svdc_shape& s, int l, void* Qp);
 // Bytes of Y rounded to bf16 in the operand layout of the back-projection (written by fit_mfma_project when asked)
 size_t fit_mfma_packed_y_bytes(const svdc_shape& s, int l);
 // Y = F Q;  fro_acc (nullable) += ||F||_F^2;  split: bf16 high + low parts of Q.
 // Ypacked != nullptr (plain operands only): the result goes there in packed bf16 form and Y is not written.
 void fit_mfma_project(const svdc_shape& s, int l, const void* F, const void* Qp, float* Y, void* Ypacked,
                       double* fro_acc, bool split, hipStream_t st);
-// Z = F^T Y, with Y as float32 rows or (Ypacked != nullptr) in the packed form
+// Z = F^T Y, with Y as float32 rows or (Ypacked != nullptr) in the packed form; z_clear: Z holds zeros already
 void fit_mfma_backproject(const svdc_shape& s, int l, const void* F, const float* Y, const void* Ypacked, float* Z,
-                          hipStream_t st);
+                          bool z_clear, hipStream_t st);
+// whether the product of a power iteration accumulates into Z (several row groups), which then has to hold zeros
+bool fit_mfma_backproject_accumulates(const svdc_shape& s, int l);
 
 }  // namespace svdc

@@ -454,6 +454,34 @@ def test_fit_basis_sketch_widths_65_to_256(dtype, N, D, k, p):
         _fit_checks(F[b], V[b], sigma[b], fro2[b], k, store)
 
 
+@pytest.mark.parametrize("dtype,B,D,l", [(torch.float32, 2, 256, 1), (torch.bfloat16, 1, 256, 16), (torch.float32, 1, 200, 17),
+                                         (torch.float32, 1, 384, 63), (torch.bfloat16, 2, 384, 64), (torch.float32, 1, 328, 65),
+                                         (torch.float32, 2, 384, 127), (torch.bfloat16, 1, 384, 129), (torch.float32, 1, 384, 144),
+                                         (torch.float32, 1, 384, 193), (torch.float32, 1, 640, 256)])
+def test_fit_basis_at_the_block_edges_of_the_small_matrices(dtype, B, D, l):
+    """Sketch widths around the 16- and 64-column blocks of the Gram matrix, the factor, its inverse and their application,
+    on features whose rank is the sketch width: every direction is found.  float32 values are accurate to the bf16
+    high + low split, bf16 ones to the rounding of the features (compared with the exact values of the rounded F)."""
+    g = torch.Generator().manual_seed(l)
+    N = l + 150
+    U = torch.linalg.qr(torch.randn(B, N, l, generator=g, dtype=torch.float64))[0]
+    W = torch.linalg.qr(torch.randn(B, D, l, generator=g, dtype=torch.float64))[0]
+    s = torch.linspace(1.0, 0.3, l, dtype=torch.float64) * 30.0
+    F = ((U * s) @ W.transpose(1, 2)).to(dtype)
+    V, sigma, fro2, status = pkg.fit_basis(F.to(DEV), l, p=-1, q=2, return_status=True)
+    torch.cuda.synchronize()
+    assert status.tolist() == [0] * B
+    for b in range(B):
+        Fb, Vb = to_np(F[b]), to_np(V[b])
+        exact = np.linalg.svd(Fb, compute_uv=False)[:l]
+        assert np.abs(Vb.T @ Vb - np.eye(l)).max() <= 1e-5
+        # bf16: the directions below the rounding noise of F (2^-9 of its entries) are not the sketch's to find
+        tol = 1e-4 if dtype == torch.float32 else 2e-2
+        assert np.abs(to_np(sigma[b]) / exact - 1).max() <= tol
+        assert 1.0 - np.sum((Fb @ Vb) ** 2) / np.sum(exact ** 2) <= tol
+        assert abs(float(fro2[b]) / np.sum(Fb * Fb) - 1) <= 1e-5
+
+
 @pytest.mark.parametrize("dtype,N,D,k,p", [(torch.float32, 300, 128, 12, 20), (torch.bfloat16, 400, 256, 24, 40),
                                             (torch.bfloat16, 500, 256, 70, 90)], ids=["f32", "bf16-mfma", "bf16-l160"])
 def test_fit_basis_without_power_iterations(dtype, N, D, k, p):
