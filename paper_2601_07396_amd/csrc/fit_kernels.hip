@@ -931,24 +931,72 @@ __device__ __forceinline__ double row_sum(double x) {
   return x;
 }
 
+// x from lane i ^ (8 S), S = 1, 2 or 4: rows of 16 lanes rotated by 8, then neighbouring rows or halves of the wave swapped
+// (v_permlane16_swap exchanges the odd rows of its first operand with the even rows of its second, v_permlane32_swap
+// the upper half with the lower one: given the same value twice, each result holds what half of the lanes need).
+template <int S>
+__device__ __forceinline__ uint32_t xor_rows_word(uint32_t x, bool odd) {
+  if constexpr (S == 1) return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x128, 0xf, 0xf, true);   // row_ror:8
+  if constexpr (S == 2) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    return odd ? r[0] : r[1];
+  }
+  const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return odd ? r[0] : r[1];
+}
+template <int S>
+__device__ __forceinline__ double xor_rows(double x) {
+  if constexpr (S == 0) return x;
+  if constexpr ((S & 1) && S != 1) return xor_rows<S & ~1>(xor_rows<1>(x));
+  if constexpr ((S & 2) && S != 2) return xor_rows<S & ~2>(xor_rows<2>(x));
+  const bool odd = (threadIdx.x & (8 * S)) != 0;
+  return __hiloint2double((int)xor_rows_word<S>((uint32_t)__double2hiint(x), odd),
+                          (int)xor_rows_word<S>((uint32_t)__double2loint(x), odd));
+}
+
 constexpr int kJacobiThreads = 512;
 
-// One plane rotation of the one-sided Jacobi: the TP lanes of a pair (lane gl of TP, a compile-time power of two:
-// with a run-time width every level of the sums below is a branch) make columns ap and aq (length l, in LDS)
+// The rotation that makes two columns with squared norms al, be and inner product ga orthogonal: x' = cs x - sn y,
+// y' = sn x + cs y.  False (and nothing set) when they are orthogonal to 1e-7 already (compared in squares, no sqrt): the
+// outputs are float32, and a sweep that finds nothing above the threshold ends the iteration.  *big is set when the cosine of
+// the angle between the columns was above 3.2e-5.
+// The ANGLE only steers convergence, so tan(theta) = sign(z) / (|z| + sqrt(1 + z^2)) comes from the float32 reciprocal and
+// square root of the hardware (each good to an ulp; the exact division and square root were a third of the dependent
+// chain of a rotation).  cos and sin belong to exactly that tangent in float64: 1 / sqrt(1 + t^2) from the float32
+// estimate (1e-7) and one step of third order.
+__device__ __forceinline__ bool jacobi_angle(double al, double be, double ga, double* tt, double* cs, double* sn, int* big) {
+  const double g2 = ga * ga, ab = al * be;
+  if (!(g2 > 1e-14 * ab)) return false;
+  const float z = (float)((be - al) * 0.5 * __builtin_amdgcn_rcp(ga));
+  const float az = fabsf(z), am = fminf(az, 1e9f);
+  const float tf = __builtin_copysignf(
+      az > 1e9f ? 0.5f * __builtin_amdgcn_rcpf(az) : __builtin_amdgcn_rcpf(am + __builtin_amdgcn_sqrtf(fmaf(am, am, 1.f))), z);
+  *tt = (double)tf;
+  const double n2 = fma(*tt, *tt, 1.0);
+  const double c0 = (double)__builtin_amdgcn_rsqf(fmaf(tf, tf, 1.f));
+  const double e1 = fma(-(n2 * c0), c0, 1.0);
+  *cs = fma(c0 * e1, fma(0.375, e1, 0.5), c0);
+  *sn = *cs * *tt;
+  if (g2 > 1e-9 * ab) *big = 1;
+  return true;
+}
+
+// One plane rotation of the one-sided Jacobi on columns in LDS: the TP lanes of a pair (lane gl of TP, a compile-time
+// power of two <= 16: with a run-time width every level of the sums below is a branch) make columns ap and aq (length l)
 // orthogonal.  A lane handles exactly NE elements of a column, NE >= ceil(l / tp), so the element loops
 // unroll with a fixed trip count, their LDS loads are issued together, and the elements stay in registers between
-// the dot products and the rotation.  A rotation sets *rot, and *big when the cosine of the angle between the
-// columns was above 3.2e-5 (flags in registers: the caller publishes them once per sweep).
+// the dot products and the rotation.  A rotation above the threshold of jacobi_angle sets *big (a flag in a register:
+// the caller publishes it once per sweep).
 // PAD: the columns are stored with TP * NE elements, zero beyond l (zeros stay zero under a rotation), so that no
 // load or store needs a bounds check (each conditional store is a branch).
 template <int NE, int TP, bool PAD>
-__device__ __forceinline__ void jacobi_rotate(double* ap, double* aq, int l, int gl, int* rot, int* big) {
-  constexpr int tp = TP;
+__device__ __forceinline__ void jacobi_rotate(double* ap, double* aq, int l, int gl, int* big) {
+  static_assert(TP <= 16, "sums inside a row of 16 lanes");
   double al = 0.0, be = 0.0, ga = 0.0;
   double xs[NE], ys[NE];
 #pragma unroll
   for (int e = 0; e < NE; ++e) {
-    const int r = gl + e * tp;
+    const int r = gl + e * TP;
     xs[e] = (PAD || r < l) ? ap[r] : 0.0;
     ys[e] = (PAD || r < l) ? aq[r] : 0.0;
   }
@@ -956,43 +1004,17 @@ __device__ __forceinline__ void jacobi_rotate(double* ap, double* aq, int l, int
   for (int e = 0; e < NE; ++e) {
     al += xs[e] * xs[e]; be += ys[e] * ys[e]; ga += xs[e] * ys[e];
   }
-  // sums over the tp lanes of the pair: inside a row of 16 lanes with data-parallel-primitive moves (no LDS
-  // round trip as in a shuffle), across rows with shuffles
   al = row_sum<TP>(al); be = row_sum<TP>(be); ga = row_sum<TP>(ga);
-#pragma unroll
-  for (int o = tp >> 1; o >= 16; o >>= 1) {
-    al += __shfl_xor(al, o, kWave);
-    be += __shfl_xor(be, o, kWave);
-    ga += __shfl_xor(ga, o, kWave);
-  }
-  // rotate when the columns are not yet orthogonal to 1e-7 (compared in squares, no sqrt): the outputs are
-  // float32, and a sweep that finds nothing above the threshold ends the iteration
-  if (ga * ga > 1e-14 * al * be) {
-    // The rotation ANGLE only steers convergence, so tan(theta) is computed in float32; cos and sin
-    // are then formed in float64 so that the rotation is orthogonal to double round-off.
-    const double zd = (be - al) * 0.5 * __builtin_amdgcn_rcp(ga);     // approximate reciprocal is enough
-    double tt;
-    if (fabs(zd) < 1e15) {
-      const float zeta = (float)zd;
-      tt = (double)((zeta >= 0.f ? 1.f : -1.f) / (fabsf(zeta) + sqrtf(1.f + zeta * zeta)));
-    } else {
-      tt = 0.5 * __builtin_amdgcn_rcp(zd);
-    }
-    const double n2 = 1.0 + tt * tt;
-    double cs = __builtin_amdgcn_rsq(n2);
-    cs = cs * (1.5 - 0.5 * n2 * cs * cs);
-    cs = cs * (1.5 - 0.5 * n2 * cs * cs);
-    const double sn = cs * tt;
+  double tt, cs, sn;
+  if (jacobi_angle(al, be, ga, &tt, &cs, &sn, big)) {
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
-      const int r = gl + e * tp;
+      const int r = gl + e * TP;
       if (PAD || r < l) {
         ap[r] = cs * xs[e] - sn * ys[e];
         aq[r] = sn * xs[e] + cs * ys[e];
       }
     }
-    *rot = 1;
-    if (ga * ga > 1e-9 * al * be) *big = 1;
   }
 }
 
@@ -1020,74 +1042,207 @@ struct RoundRobin {
   }
 };
 
-// Whole matrix in LDS (l <= 138), one workgroup per block.
-template <int NE, int NT, int TP, bool PAD>
+// Singular values, rank order and normalised columns from the orthogonal columns A (LDS, column stride la) of an
+// l <= 138 Jacobi, for a workgroup of nt threads.
+struct JacobiOrder { double nrm[138], inv[138]; int order[138]; };
+__device__ __forceinline__ void jacobi_output(const double* A, int la, int l, int k, int nt, JacobiOrder& o, double* wo,
+                                              float* sigma) {
+  const int t = threadIdx.x;
+  for (int j = t >> 3; j < l; j += nt / 8) {
+    double s = 0.0;
+    for (int r = t & 7; r < l; r += 8) s += A[j * la + r] * A[j * la + r];
+    s = row_sum<8>(s);
+    if ((t & 7) == 0) o.nrm[j] = s;
+  }
+  __syncthreads();
+  for (int j = t; j < l; j += nt) {
+    const double nj = o.nrm[j];
+    int rank = 0;
+#pragma unroll 8
+    for (int i = 0; i < l; ++i) rank += (o.nrm[i] > nj || (o.nrm[i] == nj && i < j)) ? 1 : 0;
+    if (rank < k) sigma[rank] = (float)sqrt(nj);
+    o.order[rank] = j;
+    o.inv[rank] = nj > 0.0 ? 1.0 / sqrt(nj) : 0.0;
+  }
+  __syncthreads();
+  for (int idx = t; idx < l * l; idx += nt) {
+    const int i = idx / l, r = idx - i * l;
+    wo[idx] = A[o.order[r] * la + i] * o.inv[r];
+  }
+}
+
+// l <= 128, one workgroup per block.  The columns form blocks of 8, and a wave takes two blocks at a time into registers: 8
+// lanes per column, row g of the wave (lanes 8 g .. 8 g + 7) holds column g of the first block and, to begin with, column
+// g of the second.  Eight rounds pair every column of the first with every one of the second, the second block moving
+// by exclusive-or of the row number (in Gray code order, one bit per round) through lane permutations: no LDS, no
+// barrier.  A round-robin over the blocks, LDS in between, pairs every block with every other once per sweep; in its first
+// step the columns inside each block are paired too.  Per sweep of 64 columns that is 7 trips through LDS and 7
+// barriers instead of 63 -- with a trip per rotation the LDS reads, writes and the barrier were half of a round at 64
+// columns and the LDS bandwidth bound 128 columns.  The squared norms are formed once per trip and follow the rotations
+// (al - t ga, be + t ga), so that a rotation sums one inner product over the lanes.
+// Measured: 174 us at 64 columns and 771 us at 128, against 273 and 1212 us with 16 lanes per pair, every
+// rotation from and to LDS.
+template <int NE>
+__global__ __launch_bounds__(512) void jacobi_wave_kernel(const double* __restrict__ Lfac, double* Wout, float* sigma, int l,
+                                                          int k, const double* fro_acc, float* fro2, int max_sweeps,
+                                                          int32_t* info) {
+  constexpr int la = 8 * NE + 8;        // 8 columns that lie 8 doubles past a multiple of 32 apart: no bank conflicts
+  extern __shared__ double A[];         // [nbe 8][la], column-major, zeros beyond l
+  __shared__ JacobiOrder ord;
+  __shared__ int s_big[2];
+  const int b = blockIdx.x, t = threadIdx.x, nt = blockDim.x, wave = t >> 6, g = (t & 63) >> 3, gl = t & 7;
+  const double* Lf = Lfac + (int64_t)b * l * l;
+  const int nbe = nt / 32;              // blocks of 8 columns, even: two per wave
+  for (int idx = t; idx < 8 * nbe * 8 * NE; idx += nt) {
+    const int c = idx / (8 * NE), r = idx % (8 * NE);
+    if (r >= l || c >= l || c > r) A[c * la + r] = 0.0;
+  }
+  for (int idx = t; idx < l * l; idx += nt) {
+    const int r = idx / l, c = idx - r * l;
+    if (c <= r) A[c * la + r] = Lf[idx];   // A = L
+  }
+  if (t == 0 && fro2) fro2[b] = (float)fro_acc[b];
+  if (t == 0) s_big[0] = 0;
+  __syncthreads();
+
+  double xs[NE], ys[NE], nx, ny;
+  int big;
+  // rotate the wave's columns x with the columns y of the same rows
+  auto rotate = [&] {
+    double g0 = 0.0, g1 = 0.0;
+#pragma unroll
+    for (int e = 0; e < NE; e += 2) { g0 = fma(xs[e], ys[e], g0); g1 = fma(xs[e + 1], ys[e + 1], g1); }
+    const double ga = row_sum<8>(g0 + g1);
+    double tt, cs, sn;
+    if (jacobi_angle(nx, ny, ga, &tt, &cs, &sn, &big)) {
+#pragma unroll
+      for (int e = 0; e < NE; ++e) {
+        const double x = xs[e], y = ys[e];
+        xs[e] = cs * x - sn * y;
+        ys[e] = sn * x + cs * y;
+      }
+      nx = fma(-tt, ga, nx);
+      ny = fma(tt, ga, ny);
+    }
+  };
+  auto move_y = [&](auto s) {
+#pragma unroll
+    for (int e = 0; e < NE; ++e) ys[e] = xor_rows<decltype(s)::value>(ys[e]);
+    ny = xor_rows<decltype(s)::value>(ny);
+  };
+  // rotate column g with column g ^ S of the same block: both rows form the rotation, each keeps its own column
+  auto rotate_inside = [&](auto s, double (&xv)[NE], double& n) {
+    constexpr int S = decltype(s)::value;
+    constexpr int kTop = S >= 4 ? 4 : (S >= 2 ? 2 : 1);
+    const bool lower = (g & kTop) == 0;                 // which of the two plays x: they differ in the highest bit of S
+    double pv[NE], g0 = 0.0, g1 = 0.0;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) pv[e] = xor_rows<S>(xv[e]);
+    const double pn = xor_rows<S>(n);
+#pragma unroll
+    for (int e = 0; e < NE; e += 2) { g0 = fma(xv[e], pv[e], g0); g1 = fma(xv[e + 1], pv[e + 1], g1); }
+    const double ga = row_sum<8>(g0 + g1);
+    double tt, cs, sn;
+    if (jacobi_angle(lower ? n : pn, lower ? pn : n, ga, &tt, &cs, &sn, &big)) {
+      if (lower) { sn = -sn; tt = -tt; }
+#pragma unroll
+      for (int e = 0; e < NE; ++e) xv[e] = cs * xv[e] + sn * pv[e];
+      n = fma(tt, ga, n);
+    }
+  };
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I4 = std::integral_constant<int, 4>;
+
+  bool converged = false;
+  for (int sweep = 0; sweep < max_sweeps; ++sweep) {
+    big = 0;
+    RoundRobin rr;
+    rr.start(nbe, wave);
+    for (int step = 0; step < nbe - 1; ++step) {
+      double* px = A + (8 * rr.p + g) * la + gl;
+      double* py = A + (8 * rr.q + g) * la + gl;
+      double n0 = 0.0, n1 = 0.0;
+#pragma unroll
+      for (int e = 0; e < NE; ++e) { xs[e] = px[8 * e]; ys[e] = py[8 * e]; }
+#pragma unroll
+      for (int e = 0; e < NE; ++e) { n0 = fma(xs[e], xs[e], n0); n1 = fma(ys[e], ys[e], n1); }
+      nx = row_sum<8>(n0);
+      ny = row_sum<8>(n1);
+      if (step == 0) {
+        rotate_inside(I1{}, xs, nx); rotate_inside(I1{}, ys, ny);
+        rotate_inside(I2{}, xs, nx); rotate_inside(I2{}, ys, ny);
+        rotate_inside(std::integral_constant<int, 3>{}, xs, nx); rotate_inside(std::integral_constant<int, 3>{}, ys, ny);
+        rotate_inside(I4{}, xs, nx); rotate_inside(I4{}, ys, ny);
+        rotate_inside(std::integral_constant<int, 5>{}, xs, nx); rotate_inside(std::integral_constant<int, 5>{}, ys, ny);
+        rotate_inside(std::integral_constant<int, 6>{}, xs, nx); rotate_inside(std::integral_constant<int, 6>{}, ys, ny);
+        rotate_inside(std::integral_constant<int, 7>{}, xs, nx); rotate_inside(std::integral_constant<int, 7>{}, ys, ny);
+      }
+      rotate(); move_y(I1{});   // rows of y now hold column g ^ 1
+      rotate(); move_y(I2{});   // 3
+      rotate(); move_y(I1{});   // 2
+      rotate(); move_y(I4{});   // 6
+      rotate(); move_y(I1{});   // 7
+      rotate(); move_y(I2{});   // 5
+      rotate(); move_y(I1{});   // 4
+      rotate();
+      py = A + (8 * rr.q + (g ^ 4)) * la + gl;
+#pragma unroll
+      for (int e = 0; e < NE; ++e) { px[8 * e] = xs[e]; py[8 * e] = ys[e]; }
+      rr.next();
+      __syncthreads();
+    }
+    if (big && gl == 0) atomicOr(&s_big[sweep & 1], 1);
+    if (t == 0) s_big[(sweep + 1) & 1] = 0;
+    __syncthreads();
+    // Done when a sweep rotated nothing, or only pairs whose cosine was below 3.2e-5: cyclic Jacobi converges
+    // quadratically, so what such a sweep leaves behind is of the order of the square of that, far below the 1e-7
+    // threshold, and the sweep that would merely confirm it (a seventh of the kernel's time) is not run.
+    if (s_big[sweep & 1] == 0) { converged = true; break; }
+  }
+  if (t == 0 && !converged && info) atomicOr(info + b, SVDC_FIT_JACOBI_CAPPED);
+  jacobi_output(A, la, l, k, nt, ord, Wout + (int64_t)b * l * l, sigma + (int64_t)b * k);
+}
+
+// 128 < l <= 138: the whole matrix still fits the LDS, but not padded; every rotation from and to LDS.
+template <int NE, int NT, int TP>
 __global__ __launch_bounds__(NT) void jacobi_kernel(const double* __restrict__ Lfac, double* Wout, float* sigma,
-                                                     int l, int k, const double* fro_acc, float* fro2,
-                                                     int max_sweeps, int32_t* info) {
-  extern __shared__ double dyn_lds[];
-  __shared__ double nrm[256];
-  __shared__ int s_rot, s_big;
+                                                    int l, int k, const double* fro_acc, float* fro2,
+                                                    int max_sweeps, int32_t* info) {
+  extern __shared__ double A[];         // column-major
+  __shared__ JacobiOrder ord;
+  __shared__ int s_big[2];
   const int b = blockIdx.x, t = threadIdx.x;
   const double* Lf = Lfac + (int64_t)b * l * l;
-  // column stride: odd, so that concurrently rotated columns spread over the LDS banks
-  const int la = PAD ? TP * NE + 1 : l + 1;
-  double* A = dyn_lds;    // column-major
+  const int la = l | 1;                 // odd column stride: concurrently rotated columns spread over the LDS banks
   for (int idx = t; idx < l * l; idx += NT) {
     const int r = idx / l, c = idx % l;
     A[c * la + r] = (c <= r) ? Lf[idx] : 0.0;   // A = L
   }
-  if (PAD) {
-    const int np = la - l;
-    for (int idx = t; idx < l * np; idx += NT) A[(idx / np) * la + l + idx % np] = 0.0;
-  }
   if (t == 0 && fro2) fro2[b] = (float)fro_acc[b];
+  if (t == 0) s_big[0] = 0;
   __syncthreads();
-
   const int le = (l + 1) & ~1;         // players in the round-robin (one dummy if l is odd)
   const int npairs = le / 2;           // <= 69; the host picks TP with TP * npairs <= NT
   const int group = t / TP, gl = t % TP;
   const bool active = group < npairs;
-
   bool converged = false;
   for (int sweep = 0; sweep < max_sweeps; ++sweep) {
-    if (t == 0) { s_rot = 0; s_big = 0; }
-    __syncthreads();
-    int my_rot = 0, my_big = 0;
+    int my_big = 0;
     RoundRobin rr;
     rr.start(le, active ? group : 0);
     for (int step = 0; step < le - 1; ++step) {
-      if (active && rr.p < l && rr.q < l) jacobi_rotate<NE, TP, PAD>(A + rr.p * la, A + rr.q * la, l, gl, &my_rot, &my_big);
+      if (active && rr.p < l && rr.q < l) jacobi_rotate<NE, TP, false>(A + rr.p * la, A + rr.q * la, l, gl, &my_big);
       rr.next();
       __syncthreads();
     }
-    if (my_rot && gl == 0) atomicOr(&s_rot, 1);
-    if (my_big && gl == 0) atomicOr(&s_big, 1);
+    if (my_big && gl == 0) atomicOr(&s_big[sweep & 1], 1);
+    if (t == 0) s_big[(sweep + 1) & 1] = 0;
     __syncthreads();
-    const int rot = s_rot, big = s_big;
-    __syncthreads();
-    // Done when a sweep rotates nothing -- or only pairs whose cosine was below 3.2e-5: cyclic Jacobi converges
-    // quadratically, so what such a sweep leaves behind is of the order of the square of that, far below the 1e-7
-    // threshold, and the sweep that would merely confirm it (a seventh of the kernel's time) is not run.
-    if (rot == 0 || big == 0) { converged = true; break; }
+    if (s_big[sweep & 1] == 0) { converged = true; break; }
   }
   if (t == 0 && !converged && info) atomicOr(info + b, SVDC_FIT_JACOBI_CAPPED);
-
-  for (int j = t; j < l; j += NT) {
-    double s = 0.0;
-    for (int r = 0; r < l; ++r) s += A[(int64_t)j * la + r] * A[(int64_t)j * la + r];
-    nrm[j] = s;
-  }
-  __syncthreads();
-  double* wo = Wout + (int64_t)b * l * l;
-  for (int j = t; j < l; j += NT) {
-    const double nj = nrm[j];
-    int rank = 0;
-    for (int i = 0; i < l; ++i) rank += (nrm[i] > nj || (nrm[i] == nj && i < j)) ? 1 : 0;
-    if (rank < k) sigma[(int64_t)b * k + rank] = (float)sqrt(nj);
-    const double inv = nj > 0.0 ? 1.0 / sqrt(nj) : 0.0;
-    for (int i = 0; i < l; ++i) wo[(int64_t)i * l + rank] = A[(int64_t)j * la + i] * inv;
-  }
+  jacobi_output(A, la, l, k, NT, ord, Wout + (int64_t)b * l * l, sigma + (int64_t)b * k);
 }
 
 // ---------------------------------------------------------------------------
@@ -1109,7 +1264,7 @@ template <int NE>
 __global__ __launch_bounds__(kJacobiThreads) void jacobi_block_kernel(const double* __restrict__ Lfac, double* gA, int l,
                                                                       int step, int sweep, int first, int* cnt) {
   extern __shared__ double dyn_lds[];
-  __shared__ int s_rot, s_big;
+  __shared__ int s_big;
   constexpr int NT = kJacobiThreads, NC = 2 * kJbCols, TP = NT / kJbCols;   // 64 local columns, 16 lanes per pair
   static_assert(TP == 16, "lanes per pair");
   const int b = blockIdx.y, t = threadIdx.x;
@@ -1137,17 +1292,17 @@ __global__ __launch_bounds__(kJacobiThreads) void jacobi_block_kernel(const doub
     }
   }
   for (int idx = t; idx < NC * (la - l); idx += NT) A[(idx / (la - l)) * la + l + idx % (la - l)] = 0.0;
-  if (t == 0) { s_rot = 0; s_big = 0; }
+  if (t == 0) s_big = 0;
   __syncthreads();
   const int group = t / TP, gl = t % TP;
-  int my_rot = 0, my_big = 0;
+  int my_big = 0;
   if (step == 0) {
     // first step of a sweep: every pair among the 64 columns, i.e. also the pairs inside each block (every block is
     // in exactly one pair of step 0)
     RoundRobin rr;
     rr.start(NC, group);
     for (int st = 0; st < NC - 1; ++st) {
-      if (gcol(rr.p) < l && gcol(rr.q) < l) jacobi_rotate<NE, TP, true>(A + rr.p * la, A + rr.q * la, l, gl, &my_rot, &my_big);
+      if (gcol(rr.p) < l && gcol(rr.q) < l) jacobi_rotate<NE, TP, true>(A + rr.p * la, A + rr.q * la, l, gl, &my_big);
       rr.next();
       __syncthreads();
     }
@@ -1156,7 +1311,7 @@ __global__ __launch_bounds__(kJacobiThreads) void jacobi_block_kernel(const doub
     const bool ok_p = gcol(group) < l;
     for (int st = 0; st < kJbCols; ++st) {
       const int q = kJbCols + ((group + st) & (kJbCols - 1));
-      if (ok_p && gcol(q) < l) jacobi_rotate<NE, TP, true>(A + group * la, A + q * la, l, gl, &my_rot, &my_big);
+      if (ok_p && gcol(q) < l) jacobi_rotate<NE, TP, true>(A + group * la, A + q * la, l, gl, &my_big);
       __syncthreads();
     }
   }
@@ -1470,21 +1625,22 @@ int32_t run_fit_typed(const svdc_shape& s, const FitPlan& pl, const T* F, float*
   }
   int32_t jrc = SVDC_OK;
   if ((size_t)l * (l + 1) * sizeof(double) <= kLdsBudget) {   // l <= 138: the whole matrix in the LDS of one workgroup
-    // lanes per pair: the largest power of two <= 64 with pairs x lanes <= threads (1024 threads from 33 pairs on),
-    // and the elements of a column per lane that follow from it; columns padded to lanes x elements up to l = 128
-    const int npairs = ((l + 1) & ~1) / 2;
-    auto launch = [&](auto kernel, int nt, int la) -> int32_t {
-      const size_t mat = (size_t)l * la * sizeof(double);
-      if (set_dyn_lds((const void*)kernel, mat) != SVDC_OK) return SVDC_E_HIP;
-      kernel<<<B, nt, mat, st>>>(G, M, sigma, l, s.k, misc, fro2, pl.max_sweeps, info);
+    auto launch = [&](auto kernel, int nt, size_t lds) -> int32_t {
+      if (set_dyn_lds((const void*)kernel, lds) != SVDC_OK) return SVDC_E_HIP;
+      kernel<<<B, nt, lds, st>>>(G, M, sigma, l, s.k, misc, fro2, pl.max_sweeps, info);
       return SVDC_OK;
     };
-    constexpr int NT = kJacobiThreads;
-    if (npairs <= 8) jrc = launch(jacobi_kernel<1, NT, 64, true>, NT, 65);             // l <= 16
-    else if (npairs <= 16) jrc = launch(jacobi_kernel<1, NT, 32, true>, NT, 33);       // l <= 32
-    else if (npairs <= 32) jrc = launch(jacobi_kernel<4, NT, 16, true>, NT, 65);       // l <= 64
-    else if (npairs <= 64) jrc = launch(jacobi_kernel<8, 1024, 16, true>, 1024, 129);  // l <= 128
-    else jrc = launch(jacobi_kernel<18, 1024, 8, false>, 1024, l + 1);                 // l <= 138
+    // a wave per pair of 8-column blocks, columns of 8 lanes x NE elements
+    auto by_waves = [&](auto ne) -> int32_t {
+      constexpr int NE = decltype(ne)::value;
+      const int waves = (l + 15) / 16;
+      return launch(jacobi_wave_kernel<NE>, 64 * waves, (size_t)16 * waves * (8 * NE + 8) * sizeof(double));
+    };
+    if (l <= 16) jrc = by_waves(std::integral_constant<int, 2>{});
+    else if (l <= 32) jrc = by_waves(std::integral_constant<int, 4>{});
+    else if (l <= 64) jrc = by_waves(std::integral_constant<int, 8>{});
+    else if (l <= 128) jrc = by_waves(std::integral_constant<int, 16>{});
+    else jrc = launch(jacobi_kernel<18, 1024, 8>, 1024, (size_t)l * (l | 1) * sizeof(double));
   } else {                                          // by column blocks, one launch per round-robin step
     const int nb = (l + kJbCols - 1) / kJbCols, nbe = (nb + 1) & ~1;
     const size_t lds = (size_t)2 * kJbCols * (l <= 192 ? 193 : 257) * sizeof(double);   // columns of 16 lanes x 12 or 16
