@@ -645,11 +645,23 @@ int32_t forecast_launch(const svdc_shape& s, const CoefStates& cs, const void* p
   const int cus = num_compute_units();
   int tpg = 8;
   double best = 0.0;
-  for (int cand = 16; cand >= 6; --cand) {
+  const int fewest = NCW > 3 ? 6 : 1;
+  for (int cand = 16; cand >= fewest; --cand) {
     const int64_t w = (int64_t)NS * ((ntile + cand - 1) / cand) * s.B;
     const double rounds = (double)w / cus;
     const double eff = rounds / std::ceil(rounds) * ((double)ntile / (cand * ((ntile + cand - 1) / cand)));
     if (eff > best + 1e-9) { best = eff; tpg = cand; }
+  }
+  // A call too small for that leaves compute units idle (one block of 4608 rows: 96 workgroups).  Narrow slabs give more
+  // workgroups with less of the basis to load in each (384 channels instead of 1536), and as few as one row tile per
+  // workgroup: 23 -> 13 us for that block at rank 32, 23 -> 17 us at rank 64.  Twice that size is no faster for it.
+  if constexpr (NCW > 3) {
+    if (best < 0.7) {
+      constexpr int kNarrowPD = PD < 2 ? 2 : PD;
+      const int m = s.D / 128;
+      if (m % 3 == 0) return forecast_launch<T, 3, KT2, SPLIT, kNarrowPD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
+      if (m % 2 == 0) return forecast_launch<T, 2, KT2, SPLIT, kNarrowPD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
+    }
   }
   const int gpb = (ntile + tpg - 1) / tpg;
   const int64_t grid = (int64_t)NS * gpb * s.B;
@@ -756,7 +768,9 @@ constexpr int ring_depth(int CH, int W, int KT2) {
 }
 
 // A launch with fewer tiles than compute units leaves units idle: such small problems take tiles one step
-// smaller (their packed-basis traffic does not matter at that size).
+// smaller (their packed-basis traffic does not matter at that size), and tiles of 16 rows where those still fit into
+// one round (4 x 700 rows at rank 32: 23 -> 17 us, 2000 rows 21 -> 16 us; with more tiles than units the second round
+// costs more than the taller tile: 4608 rows 24 against 30 us).
 template <typename T, int CH, int KT2, bool SPLIT>
 int32_t full_step_by_size(const svdc_shape& s, const void* F, const void* packed, void* R, float* S, float* C,
                           float alpha, int init, ResidualEma re, hipStream_t st) {
@@ -780,6 +794,10 @@ int32_t full_step_by_size(const svdc_shape& s, const void* F, const void* packed
   }
   if constexpr (RT > 1) {
     const int64_t tiles = (int64_t)((s.N + 16 * RT - 1) / (16 * RT)) * s.B;
+    if constexpr (RT > 2) {
+      if ((int64_t)((s.N + 15) / 16) * s.B <= num_compute_units())
+        return full_step_launch<T, CH, 1, KT2, SPLIT, RD, false>(s, F, packed, R, S, C, alpha, init, re, st);
+    }
     if (tiles < num_compute_units())
       return full_step_launch<T, CH, RT - 1, KT2, SPLIT, RD, false>(s, F, packed, R, S, C, alpha, init, re, st);
   }

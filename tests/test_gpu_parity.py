@@ -315,6 +315,47 @@ def test_mfma_and_general_paths_agree():
     assert rel_err(to_np(Fa), to_np(Fb)) <= 3e-3
 
 
+@pytest.mark.parametrize("dtype,B,N,D,k,pad", [(torch.bfloat16, 1, 33, 3072, 32, 0), (torch.bfloat16, 2, 1001, 3072, 64, 64),
+                                               (torch.bfloat16, 1, 2290, 4096, 32, 0), (torch.float32, 1, 403, 1536, 24, 32),
+                                               (torch.bfloat16, 1, 4097, 3072, 32, 8)])
+def test_small_calls_take_narrow_slabs_and_short_tiles(dtype, B, N, D, k, pad):
+    """Calls that do not fill the machine: cached steps over narrow channel slabs with few row tiles per workgroup (packed
+    and plain state, two forecaster states), full steps over 16-row tiles, ragged last tiles, padded rows."""
+    from oracle import ref_forecast_combine
+    store = "f32" if dtype == torch.float32 else "bf16"
+    g = torch.Generator().manual_seed(N + k)
+    wide = torch.randn(B, N, D + pad, generator=g).to(dtype)
+    V = torch.linalg.qr(torch.randn(B, D, k, generator=g, dtype=torch.float64))[0].float().contiguous()
+    S0 = torch.randn(B, N, k, generator=g)
+    buf = wide.to(DEV)
+    F = buf[:, :, :D]
+    R, Fh, Fp, Fc = (torch.zeros_like(buf)[:, :, :D] for _ in range(4))
+    S = S0.to(DEV)
+    C = torch.empty_like(S)
+    shape = pkg.make_shape(F, k)
+    Vd = V.to(DEV)
+    packed = pkg.pack_basis(shape, Vd)
+    Sp = pkg.alloc_packed_state(shape, DEV)
+    pkg.svdcache_full_step(shape, F, Vd, packed, R, S, C, 0.3, False)
+    pkg.svdcache_pack_state(shape, S, Sp)
+    pkg.svdcache_forecast(shape, S, Vd, packed, R, Fh)
+    pkg.svdcache_forecast_packed(shape, Sp, packed, R, Fp)
+    pkg.svdcache_forecast_combine(shape, [S, C], [1.5, -0.5], Vd, packed, R, F, Fc)
+    torch.cuda.synchronize()
+    assert torch.equal(Fh, Fp)
+    rows = slice(0, N) if N < 500 else torch.tensor([0, 1, 15, 16, 17, N // 2, N - 17, N - 2, N - 1])
+    for b in range(B):
+        Fb, Vb = to_np(wide[b, rows, :D]), to_np(V[b])
+        Rr, Sr, Cr = ref_full_step(Fb, Vb, to_np(S0[b, rows]), 0.3, False, store)
+        assert_close(to_np(R[b].cpu()[rows]), Rr, store, f"R[{b}]", floor_of=Fb)
+        assert_close(to_np(S[b].cpu()[rows]), Sr, "f32", f"S[{b}]")
+        assert_close(to_np(Fh[b].cpu()[rows]), ref_forecast(Sr, Vb, Rr, store), store, f"Fhat[{b}]", scale_of=Fb, ulp_of=Rr)
+        want = ref_forecast_combine([Sr, Cr], [1.5, -0.5], Vb, Rr, Fb, store)
+        assert_close(to_np(Fc[b].cpu()[rows]), want, store, f"combine[{b}]", scale_of=Fb, ulp_of=Rr)
+    if pad:
+        assert float(torch.as_strided(Fh, (B, N, pad), Fh.stride(), D).abs().max()) == 0.0
+
+
 @pytest.mark.parametrize("k", [32, 64, 128])
 def test_mfma_inplace_and_strided(k):
     """In-place residual (R aliases F), padded row stride, no coefficient output."""
