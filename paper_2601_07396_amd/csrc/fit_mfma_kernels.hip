@@ -635,46 +635,58 @@ void project_launch(const svdc_shape& s, int l, const void* F, const void* Qp, f
   // the split operand doubles the Q registers: halve the slab width when it is wide
   constexpr int NCWS = (NCW * KT > 12 && NCW % 2 == 0) ? NCW / 2 : NCW;
   const int ntile = (s.N + 15) / 16;
-  const int gpb = (ntile + TG - 1) / TG;
-  const unsigned grid = (unsigned)((int64_t)gpb * s.B);
   const T* f = (const T*)F;
   const uint16_t* q = (const uint16_t*)Qp;
   if (kF32) split = true;
+  constexpr int64_t kUnits = 256;
+  auto stationary = [&](auto tg) {
+    constexpr int G = decltype(tg)::value;
+    const int gpb = (ntile + G - 1) / G;
+    const unsigned grid = (unsigned)((int64_t)gpb * s.B);
+    if (split) {
+      const int NS = s.D / (128 * NCWS);
+      if (fro_acc)
+        fit_project_mfma_kernel<T, NCWS, KT, G, true, true><<<grid, 256, 0, st>>>(
+            f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, NS, gpb, ld.ldy);
+      else
+        fit_project_mfma_kernel<T, NCWS, KT, G, true, false><<<grid, 256, 0, st>>>(
+            f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, NS, gpb, ld.ldy);
+    } else if constexpr (!kF32) {
+      const int NS = s.D / (128 * NCW);
+      fit_project_mfma_kernel<T, NCW, KT, G, false, false><<<grid, 256, 0, st>>>(
+          f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, NS, gpb, ld.ldy);
+    }
+  };
+  // Small batches, where TG tiles per workgroup leave more than half of the compute units idle: two tiles.  One block of
+  // 4608 x 3072, sketch 64: 11.9 us with plain operands (17.7 with four tiles), 24.3 us with split ones (67 with
+  // the rows split over the waves in groups of 12 tiles, 42 in groups of 4).
+  if constexpr (KT <= 4) {
+    if ((int64_t)((ntile + TG - 1) / TG) * s.B <= kUnits / 2) return stationary(std::integral_constant<int, 2>{});
+  }
   // wide sketches: rows split over the waves, Q shared through LDS
   if constexpr (KT >= 4) {
     constexpr int RTW = (KT == 8) ? 2 : 3;
-    auto rows_grid = [&] { return (ntile + kWaves * RTW - 1) / (kWaves * RTW); };
+    auto rows = [&](auto rtw, auto sc, auto sp, auto fr) {
+      constexpr int R = decltype(rtw)::value;
+      const int g = (ntile + kWaves * R - 1) / (kWaves * R);
+      fit_project_rows_kernel<T, KT, R, decltype(sc)::value, decltype(sp)::value, decltype(fr)::value>
+          <<<(unsigned)((int64_t)g * s.B), 256, 0, st>>>(f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, g, ld.ldy);
+    };
     if (split) {
-      constexpr int SC = (KT == 8) ? 2 : 4;
-      const int g = rows_grid();
-      if (fro_acc)
-        fit_project_rows_kernel<T, KT, RTW, SC, true, true><<<(unsigned)((int64_t)g * s.B), 256, 0, st>>>(
-            f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, g, ld.ldy);
-      else
-        fit_project_rows_kernel<T, KT, RTW, SC, true, false><<<(unsigned)((int64_t)g * s.B), 256, 0, st>>>(
-            f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, g, ld.ldy);
+      using SC = std::integral_constant<int, (KT == 8) ? 2 : 4>;
+      auto tall = [&](auto rtw) {
+        if (fro_acc) rows(rtw, SC{}, std::true_type{}, std::true_type{});
+        else rows(rtw, SC{}, std::true_type{}, std::false_type{});
+      };
+      // fewer workgroups than compute units: 16 rows per wave (18432 float32 rows, sketch 128: 122 -> 110 us)
+      if ((int64_t)((ntile + kWaves * RTW - 1) / (kWaves * RTW)) * s.B < kUnits) tall(std::integral_constant<int, 1>{});
+      else tall(std::integral_constant<int, RTW>{});
       return;
     }
-    if constexpr (KT == 8 && !kF32) {
-      const int g = rows_grid();
-      fit_project_rows_kernel<T, KT, RTW, 4, false, false><<<(unsigned)((int64_t)g * s.B), 256, 0, st>>>(
-          f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, g, ld.ldy);
-      return;
-    }
+    if constexpr (KT == 8 && !kF32)
+      return rows(std::integral_constant<int, RTW>{}, std::integral_constant<int, 4>{}, std::false_type{}, std::false_type{});
   }
-  if (split) {
-    const int NS = s.D / (128 * NCWS);
-    if (fro_acc)
-      fit_project_mfma_kernel<T, NCWS, KT, TG, true, true><<<grid, 256, 0, st>>>(
-          f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, NS, gpb, ld.ldy);
-    else
-      fit_project_mfma_kernel<T, NCWS, KT, TG, true, false><<<grid, 256, 0, st>>>(
-          f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, NS, gpb, ld.ldy);
-  } else if constexpr (!kF32) {
-    const int NS = s.D / (128 * NCW);
-    fit_project_mfma_kernel<T, NCW, KT, TG, false, false><<<grid, 256, 0, st>>>(
-        f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, NS, gpb, ld.ldy);
-  }
+  stationary(std::integral_constant<int, TG>{});
 }
 
 template <typename T, int NCW, int KT>
