@@ -1414,7 +1414,7 @@ bool make_fit_plan(const svdc_shape& s, const svdc_fit_params* p, FitPlan* plan)
   // Y as float32 rows; the matrix-core path also keeps its packed bf16 form there between a projection and the
   // back-projection that follows (never both at once)
   size_t y_bytes = B * (size_t)s.N * l * sizeof(float);
-  if (fit_mfma_supported(s, l)) y_bytes = std::max(y_bytes, fit_mfma_packed_y_bytes(s, l));
+  if (fit_mfma_supported(s, l)) y_bytes = std::max(y_bytes, fit_mfma_packed_y_bytes(s, l, 1));
   plan->off_Y = off; off = align_up(off + y_bytes, 256);
   plan->off_G = off; off = align_up(off + B * l * l * sizeof(double), 256);
   plan->off_Gp = off; off = align_up(off + B * kGramSlices * (size_t)l * l * sizeof(double), 256);
@@ -1588,12 +1588,15 @@ int32_t run_fit_typed(const svdc_shape& s, const FitPlan& pl, const T* F, float*
   const bool want_fro = fro2 != nullptr;
   bool fro_done = false;
   // Y = F Q.  The last product feeds the Rayleigh-Ritz step and uses the full-precision operand split.
-  // float32 features: every product splits both operands, and Y stays float32 rows between the two products
+  // float32 features: every product splits both operands.  Between the two products Y has its packed form, which for
+  // float32 features is in two parts as large as the float32 rows themselves, up to the padding of N and l: it may run on
+  // into the Gram matrices' areas, not in use at that time, and stays float32 rows where even that is too small.
   constexpr bool kF32 = std::is_same<T, float>::value;
+  void* Yp = kF32 && fit_mfma_packed_y_bytes(s, l, 2) > pl.off_M - pl.off_Y ? nullptr : (void*)Y;
   auto project = [&](bool last) {
     if (pl.mfma) {
       if (!packed) fit_mfma_pack_q(s, l, Q, Qp, st);
-      fit_mfma_project(s, l, F, Qp, Y, (last || kF32) ? nullptr : (void*)Y, (last && want_fro) ? misc : nullptr,
+      fit_mfma_project(s, l, F, Qp, Y, last ? nullptr : Yp, (last && want_fro) ? misc : nullptr,
                        last || kF32, st);
       if (last && want_fro) fro_done = true;
     } else {
@@ -1603,7 +1606,7 @@ int32_t run_fit_typed(const svdc_shape& s, const FitPlan& pl, const T* F, float*
   for (int it = 0; it < pl.q; ++it) {
     project(false);
     if (pl.mfma) {
-      fit_mfma_backproject(s, l, F, Y, kF32 ? nullptr : Y, Z, z_clear, st);   // bf16: Y holds the packed form here
+      fit_mfma_backproject(s, l, F, Y, Yp, Z, z_clear, st);
     } else {
       gemm_fty<T>(s, l, F, Y, Z, st);
     }

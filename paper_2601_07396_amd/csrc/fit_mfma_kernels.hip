@@ -112,6 +112,20 @@ __device__ __forceinline__ u32x4 pack_y_word(const f32x4& t0, const f32x4& t1, i
   return u32x4{pack_bf16(a[0], a[1]), pack_bf16(a[2], a[3]), pack_bf16(c[0], c[1]), pack_bf16(c[2], c[3])};
 }
 
+// float32 features: the same words in two parts, bf16 high then low, word ((b nsteps + s) KT + jt) 2 + part.  The four
+// accumulator rows of one 16-row tile are 8 bytes of each.
+__device__ __forceinline__ void store_y_half_words(u32x4* Yp, int64_t word, int half, const f32x4& t, int row, int N) {
+  f32x4 a = t;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (row + i >= N) a[i] = 0.f;
+  const uint32_t h0 = pack_bf16(a[0], a[1]), h1 = pack_bf16(a[2], a[3]);
+  const uint32_t l0 = pack_bf16(a[0] - bf16_lo(h0), a[1] - bf16_hi(h0)), l1 = pack_bf16(a[2] - bf16_lo(h1), a[3] - bf16_hi(h1));
+  uint2* out = reinterpret_cast<uint2*>(Yp + word * 2 * 64 + (threadIdx.x & 63)) + half;
+  out[0] = make_uint2(h0, h1);
+  out[2 * 64] = make_uint2(l0, l1);
+}
+
 // ---------------------------------------------------------------------------
 // project: Y = F Q for a group of TG 16-row tiles per workgroup, no atomics.
 // The workgroup walks over the channel slabs (128 * NCW channels each); for one
@@ -228,7 +242,15 @@ __global__ __launch_bounds__(256) void fit_project_mfma_kernel(const T* __restri
           }
           s2[tt] = s;
         }
-        if (step < nsteps) Yp[(((int64_t)b * nsteps + step) * KT + jt) * 64 + lane] = pack_y_word(s2[0], s2[1], 32 * step + 4 * g, N);
+        if (step < nsteps) {
+          const int64_t word = ((int64_t)b * nsteps + step) * KT + jt;
+          if constexpr (FPiece<T>::kTwoParts) {
+            store_y_half_words(Yp, word, 0, s2[0], 32 * step + 4 * g, N);
+            store_y_half_words(Yp, word, 1, s2[1], 32 * step + 16 + 4 * g, N);
+          } else {
+            Yp[word * 64 + lane] = pack_y_word(s2[0], s2[1], 32 * step + 4 * g, N);
+          }
+        }
       }
       __syncthreads();
       continue;
@@ -265,20 +287,22 @@ __global__ __launch_bounds__(256) void fit_project_mfma_kernel(const T* __restri
 // 128 (0.66 against 0.88 ms with split operands), 0.41 against 0.53 ms at width 64 with split operands; at width
 // 64 with plain operands the register-stationary kernel stays ahead (0.36 against 0.42 ms).
 // ---------------------------------------------------------------------------
-template <typename T, int KT, int RTW, int SC, bool SPLIT, bool FRO>
+// PD chunks of F in flight per wave, SD slabs between the request of a slab's operand words and their move to LDS.  Loads
+// return in order, so waiting for the words also waits for every chunk requested before them: with one workgroup per
+// compute unit and little work per chunk (RTW = 1) a slab cannot take less than the memory latency divided by SD.
+template <typename T, int KT, int RTW, int SC, bool SPLIT, bool FRO, int PD = 4, int SD = 1>
 __global__ __launch_bounds__(256) void fit_project_rows_kernel(const T* __restrict__ F,
                                                                const uint16_t* __restrict__ Qp, float* Y,
                                                                u32x4* Yp, double* fro_acc, int N, int D, int l,
                                                                int64_t ldf, int64_t bstride,
                                                                int groups_per_block, int ldy) {
-  // Four chunks of F in flight per wave.  With split operands they are requested two at a time: the two 64-byte
+  // With split operands the chunks of F are requested two at a time: the two 64-byte
   // pieces of a 128-byte line belong to neighbouring chunks, and asked for a whole chunk's work apart the line comes
   // from L2 twice (4 % slower).  With plain operands a slot is refilled as soon as its chunk is done (two chunks
   // in flight instead of four: 3 % slower at width 128).
   constexpr bool PAIRED = SPLIT;
-  constexpr int PD = 4;
   static_assert(SC == 2 || SC == 4, "slab of 2 or 4 chunks");
-  static_assert(PAIRED || SC == PD, "without pairing the ring slot of a chunk is its index in the slab");
+  static_assert(PAIRED || (SC == PD && SD == 1), "without pairing the ring slot of a chunk is its index in the slab");
   constexpr int NP = SPLIT ? 2 : 1;           // operand parts (high, low)
   constexpr int WPW = SC * KT / kWaves;       // operand words a wave stages per slab and part
   static_assert(SC * KT % kWaves == 0, "staging must divide among the waves");
@@ -306,33 +330,40 @@ __global__ __launch_bounds__(256) void fit_project_rows_kernel(const T* __restri
 #pragma unroll
     for (int t = 0; t < RTW; ++t) fi[t].load(fbase + rowoff[t] + 32 * chunk);
   };
-  u32x4 stg[NP][WPW];
-  auto load_stage = [&](int slab) {
+  u32x4 stg[SD][NP][WPW];
+  auto load_stage = [&](int slab, u32x4(&st)[NP][WPW]) {
 #pragma unroll
     for (int i = 0; i < WPW; ++i) {
       const int64_t w = (int64_t)slab * SC * KT + wave * WPW + i;
-      stg[0][i] = Qhi[w * 64 + lane];
-      if (SPLIT) stg[NP - 1][i] = Qlo[w * 64 + lane];
+      st[0][i] = Qhi[w * 64 + lane];
+      if (SPLIT) st[NP - 1][i] = Qlo[w * 64 + lane];
     }
   };
-  auto store_stage = [&](int buf) {
+  auto store_stage = [&](int buf, const u32x4(&st)[NP][WPW]) {
 #pragma unroll
     for (int i = 0; i < WPW; ++i)
 #pragma unroll
-      for (int p = 0; p < NP; ++p) qs[buf][p][wave * WPW + i][lane] = stg[p][i];
+      for (int p = 0; p < NP; ++p) qs[buf][p][wave * WPW + i][lane] = st[p][i];
   };
-  load_stage(0);
+  // slab n's words pass through the register set n % SD
+  load_stage(0, stg[0]);
 #pragma unroll
-  for (int u = 0; u < PD; ++u) load_chunk(u, fin[u]);
-  store_stage(0);
+  for (int u = 0; u < PD; ++u)
+    if (u < NC) load_chunk(u, fin[u]);
+  store_stage(0, stg[0]);
+#pragma unroll
+  for (int i = 1; i < SD; ++i)
+    if (i < NS) load_stage(i, stg[i]);
   __syncthreads();
 
   float ssq = 0.f;
-  // one slab; with paired requests PAR = slab & 1 is a compile-time value, so that the ring slots are static
+  // one slab; with paired requests PAR = slab % kCycle is a compile-time value, so that the ring slots and sets are static
+  constexpr int kCycle = PAIRED ? (PD / SC > 2 ? PD / SC : 2) : 1;
+  static_assert(!PAIRED || (kCycle * SC % PD == 0 && kCycle % SD == 0), "ring and sets repeat with the cycle");
   auto do_slab = [&](int slab, auto par) {
     constexpr int PAR = decltype(par)::value;
-    const int buf = PAIRED ? PAR : (slab & 1);
-    if (slab + 1 < NS) load_stage(slab + 1);
+    const int buf = PAIRED ? (PAR & 1) : (slab & 1);
+    if (slab + SD < NS) load_stage(slab + SD, stg[PAR % SD]);
 #pragma unroll
     for (int c = 0; c < SC; ++c) {
       const int chunk = slab * SC + c;
@@ -367,13 +398,18 @@ __global__ __launch_bounds__(256) void fit_project_rows_kernel(const T* __restri
         if (chunk + PD < NC) load_chunk(chunk + PD, fin[u]);
       }
     }
-    if (slab + 1 < NS) store_stage(buf ^ 1);
+    if (slab + 1 < NS) store_stage(buf ^ 1, stg[(PAR + 1) % SD]);
     __syncthreads();
   };
   if constexpr (PAIRED) {
-    for (int slab = 0; slab < NS; slab += 2) {
+    for (int slab = 0; slab < NS; slab += kCycle) {
       do_slab(slab, std::integral_constant<int, 0>{});
       if (slab + 1 < NS) do_slab(slab + 1, std::integral_constant<int, 1>{});
+      if constexpr (kCycle > 2) {
+        static_assert(kCycle == 4, "two or four slabs");
+        if (slab + 2 < NS) do_slab(slab + 2, std::integral_constant<int, 2>{});
+        if (slab + 3 < NS) do_slab(slab + 3, std::integral_constant<int, 3>{});
+      }
     }
   } else {
     for (int slab = 0; slab < NS; ++slab) do_slab(slab, std::integral_constant<int, 0>{});
@@ -382,7 +418,20 @@ __global__ __launch_bounds__(256) void fit_project_rows_kernel(const T* __restri
     const double s = wave_sum((double)ssq);
     if (lane == 0) atomicAdd(fro_acc + b, s);
   }
-  if constexpr (RTW == 2) {
+  if constexpr (FPiece<T>::kTwoParts) {
+    if (Yp) {   // packed output for the back-projection, tile by tile
+      const int nsteps = (N + 31) / 32;
+#pragma unroll
+      for (int t = 0; t < RTW; ++t) {
+        const int tile = tile0 + t;
+        if (tile / 2 >= nsteps) break;
+#pragma unroll
+        for (int jt = 0; jt < KT; ++jt)
+          store_y_half_words(Yp, ((int64_t)b * nsteps + tile / 2) * KT + jt, tile & 1, acc[t][jt], 16 * tile + 4 * g, N);
+      }
+      return;
+    }
+  } else if constexpr (RTW == 2) {
     if (Yp) {   // packed output for the back-projection: the wave's two tiles are one 32-row step
       const int nsteps = (N + 31) / 32, step = tile0 / 2;
       if (step < nsteps) {
@@ -520,13 +569,16 @@ __global__ __launch_bounds__(256) void fit_backproject_mfma_kernel(const bf16_t*
 
 // ---------------------------------------------------------------------------
 // backproject for float32 features: the same contraction, Z[d][j] += sum_rows F[row][d] Y[row][j], with both
-// operands split into bf16 high + low parts on the fly (F_hi Y_hi + F_lo Y_hi + F_hi Y_lo).  A lane loads, for each
-// of its 8 rows, the two float32 channels (2 r, 2 r + 1) of a chunk; Y comes as float32 rows.  Same output mapping
-// and row-group scheme as the bf16 kernel.
+// operands split into bf16 high + low parts (F_hi Y_hi + F_lo Y_hi + F_hi Y_lo).  A lane loads, for each
+// of its 8 rows, the two float32 channels (2 r, 2 r + 1) of a chunk and splits them.  PACKED: Y comes as the two-part
+// operand words that the projection wrote (store_y_half_words), with the rows of a step in that word's order; otherwise as
+// float32 rows, 8 scalar loads and a split per operand in every wave, which bounded the kernel (18432 x 3072, sketch 128:
+// 134 us, 75 us with the words).  Same output mapping and row-group scheme as the bf16 kernel.
 // ---------------------------------------------------------------------------
-template <int NCW, int KT>
+template <int NCW, int KT, bool PACKED>
 __global__ __launch_bounds__(256) void fit_backproject_f32_kernel(const float* __restrict__ F,
-                                                                  const float* __restrict__ Y, float* Z, int N,
+                                                                  const float* __restrict__ Y,
+                                                                  const u32x4* __restrict__ Yp, float* Z, int N,
                                                                   int D, int l, int64_t ldf, int64_t bstride,
                                                                   int NS, int groups_per_block, int rows_per_group,
                                                                   int ldy, int ldz) {
@@ -540,6 +592,7 @@ __global__ __launch_bounds__(256) void fit_backproject_f32_kernel(const float* _
   const float* ybase = Y + (int64_t)b * N * ldy;
   const int row_begin = rg * rows_per_group;
   const int row_end = min(N, row_begin + rows_per_group);
+  const int nsteps = (N + 31) / 32;
 
   f32x4 acc[NCW][2][KT];
 #pragma unroll
@@ -550,29 +603,43 @@ __global__ __launch_bounds__(256) void fit_backproject_f32_kernel(const float* _
       for (int jt = 0; jt < KT; ++jt) acc[c][p][jt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   f32x2 fw[NCW][8];
-  float yv[KT][8];
+  float yv[PACKED ? 1 : KT][8];
+  u32x4 yw[PACKED ? KT : 1][2];
   auto load_step = [&](int row0) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int row = row0 + 8 * g + e;
+      const int row = PACKED ? row0 + 16 * (e / 4) + 4 * g + e % 4 : row0 + 8 * g + e;
       const int rowc = min(row, N - 1);
 #pragma unroll
       for (int c = 0; c < NCW; ++c) {
-        const f32x2 x = fbase[(int64_t)rowc * ldw + 16 * c];
-        fw[c][e] = row < row_end ? x : f32x2{0.f, 0.f};
+        fw[c][e] = fbase[(int64_t)rowc * ldw + 16 * c];
+        if constexpr (!PACKED) {
+          if (row >= row_end) fw[c][e] = f32x2{0.f, 0.f};
+        }
       }
+      if constexpr (!PACKED) {
 #pragma unroll
-      for (int jt = 0; jt < KT; ++jt) {
-        const int j = 16 * jt + r;
-        yv[jt][e] = (row < row_end && j < l) ? ybase[(int64_t)row * ldy + j] : 0.f;
+        for (int jt = 0; jt < KT; ++jt) {
+          const int j = 16 * jt + r;
+          yv[jt][e] = (row < row_end && j < l) ? ybase[(int64_t)row * ldy + j] : 0.f;
+        }
       }
+    }
+    if constexpr (PACKED) {   // row groups start at multiples of 32 rows; rows >= N are zero in the packed words
+#pragma unroll
+      for (int jt = 0; jt < KT; ++jt)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) yw[jt][p] = Yp[((((int64_t)b * nsteps + row0 / 32) * KT + jt) * 2 + p) * 64 + lane];
     }
   };
   if (row_begin < row_end) load_step(row_begin);
   for (int row0 = row_begin; row0 < row_end; row0 += 32) {
     u32x4 yhi[KT], ylo[KT];
 #pragma unroll
-    for (int jt = 0; jt < KT; ++jt) split_operand(yv[jt], &yhi[jt], &ylo[jt]);
+    for (int jt = 0; jt < KT; ++jt) {
+      if constexpr (PACKED) { yhi[jt] = yw[jt][0]; ylo[jt] = yw[jt][1]; }
+      else split_operand(yv[jt], &yhi[jt], &ylo[jt]);
+    }
     u32x4 fhi[NCW][2], flo[NCW][2];
 #pragma unroll
     for (int c = 0; c < NCW; ++c)
@@ -668,8 +735,9 @@ void project_launch(const svdc_shape& s, int l, const void* F, const void* Qp, f
     constexpr int RTW = (KT == 8) ? 2 : 3;
     auto rows = [&](auto rtw, auto sc, auto sp, auto fr) {
       constexpr int R = decltype(rtw)::value;
+      constexpr bool kDeep = R == 1 && KT == 8;      // one workgroup per compute unit
       const int g = (ntile + kWaves * R - 1) / (kWaves * R);
-      fit_project_rows_kernel<T, KT, R, decltype(sc)::value, decltype(sp)::value, decltype(fr)::value>
+      fit_project_rows_kernel<T, KT, R, decltype(sc)::value, decltype(sp)::value, decltype(fr)::value, kDeep ? 8 : 4, kDeep ? 2 : 1>
           <<<(unsigned)((int64_t)g * s.B), 256, 0, st>>>(f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, g, ld.ldy);
     };
     if (split) {
@@ -678,7 +746,8 @@ void project_launch(const svdc_shape& s, int l, const void* F, const void* Qp, f
         if (fro_acc) rows(rtw, SC{}, std::true_type{}, std::true_type{});
         else rows(rtw, SC{}, std::true_type{}, std::false_type{});
       };
-      // fewer workgroups than compute units: 16 rows per wave (18432 float32 rows, sketch 128: 122 -> 110 us)
+      // fewer workgroups than compute units: 16 rows per wave, deeper prefetch (18432 float32 rows, sketch 128: 122 ->
+      // 110 -> 99 us; 32 rows by half of the coefficient tiles per wave, which halves the LDS reads: 128 us)
       if ((int64_t)((ntile + kWaves * RTW - 1) / (kWaves * RTW)) * s.B < kUnits) tall(std::integral_constant<int, 1>{});
       else tall(std::integral_constant<int, RTW>{});
       return;
@@ -695,8 +764,12 @@ void backproject_launch(const svdc_shape& s, int l, const void* F, const float* 
   const int NS = s.D / (128 * NCW);
   const unsigned grid = (unsigned)((int64_t)NS * gpb * s.B);
   if constexpr (std::is_same<T, float>::value) {
-    fit_backproject_f32_kernel<NCW, KT><<<grid, 256, 0, st>>>((const float*)F, Y, Z, s.N, s.D, l, s.ldf,
-                                                              s.block_stride, NS, gpb, rows, ld.ldy, ld.ldz);
+    if (Yp)
+      fit_backproject_f32_kernel<NCW, KT, true><<<grid, 256, 0, st>>>((const float*)F, Y, Yp, Z, s.N, s.D, l, s.ldf,
+                                                                      s.block_stride, NS, gpb, rows, ld.ldy, ld.ldz);
+    else
+      fit_backproject_f32_kernel<NCW, KT, false><<<grid, 256, 0, st>>>((const float*)F, Y, Yp, Z, s.N, s.D, l, s.ldf,
+                                                                       s.block_stride, NS, gpb, rows, ld.ldy, ld.ldz);
   } else {
     if (Yp)
       fit_backproject_mfma_kernel<NCW, KT, true><<<grid, 256, 0, st>>>((const bf16_t*)F, Y, Yp, Z, s.N, s.D, l, s.ldf,
@@ -825,7 +898,10 @@ inline int col_ranges(int l, ColRange (&r)[2]) {
 }
 inline int kt_for(int l) { return l <= 16 ? 1 : (l <= 32 ? 2 : (l <= 64 ? 4 : 8)); }
 inline size_t packed_q_bytes_one(const svdc_shape& s, int l) { return (size_t)s.B * 2 * s.D * kt_for(l) * 16 * sizeof(uint16_t); }
-inline size_t packed_y_bytes_one(const svdc_shape& s, int l) { return (size_t)s.B * (((size_t)s.N + 31) / 32) * kt_for(l) * 1024; }
+// parts: 1 (bf16 features) or 2 (float32 features: high and low)
+inline size_t packed_y_bytes_one(const svdc_shape& s, int l, int parts) {
+  return (size_t)s.B * (((size_t)s.N + 31) / 32) * kt_for(l) * parts * 1024;
+}
 
 template <typename Fn>
 void by_kt(int l, Fn fn) {
@@ -849,11 +925,11 @@ size_t fit_mfma_packed_q_bytes(const svdc_shape& s, int l) {
   return bytes;
 }
 
-size_t fit_mfma_packed_y_bytes(const svdc_shape& s, int l) {
+size_t fit_mfma_packed_y_bytes(const svdc_shape& s, int l, int parts) {
   ColRange r[2];
   const int n = col_ranges(l, r);
   size_t bytes = 0;
-  for (int h = 0; h < n; ++h) bytes += packed_y_bytes_one(s, r[h].l);
+  for (int h = 0; h < n; ++h) bytes += packed_y_bytes_one(s, r[h].l, parts);
   return bytes;
 }
 
@@ -879,12 +955,12 @@ void fit_mfma_project(const svdc_shape& s, int l, const void* F, const void* Qp,
     by_kt(r[h].l, [&](auto kt) {
       constexpr int KT = decltype(kt)::value;
       if (s.dtype == SVDC_F32)
-        project_kt<float, KT>(s, r[h].l, F, qp, Y + r[h].j0, nullptr, h == 0 ? fro_acc : nullptr, true, ld, st);
+        project_kt<float, KT>(s, r[h].l, F, qp, Y + r[h].j0, (u32x4*)yp, h == 0 ? fro_acc : nullptr, true, ld, st);
       else
         project_kt<bf16_t, KT>(s, r[h].l, F, qp, Y + r[h].j0, (u32x4*)yp, h == 0 ? fro_acc : nullptr, split, ld, st);
     });
     qp += packed_q_bytes_one(s, r[h].l);
-    if (yp) yp += packed_y_bytes_one(s, r[h].l);
+    if (yp) yp += packed_y_bytes_one(s, r[h].l, s.dtype == SVDC_F32 ? 2 : 1);
   }
 }
 
@@ -937,11 +1013,11 @@ void fit_mfma_backproject(const svdc_shape& s, int l, const void* F, const float
     by_kt(r[h].l, [&](auto kt) {
       constexpr int KT = decltype(kt)::value;
       if (s.dtype == SVDC_F32)
-        backproject_kt<float, KT>(s, r[h].l, F, Y + r[h].j0, nullptr, Z + r[h].j0, ld, st);
+        backproject_kt<float, KT>(s, r[h].l, F, Y ? Y + r[h].j0 : nullptr, (const u32x4*)yp, Z + r[h].j0, ld, st);
       else
         backproject_kt<bf16_t, KT>(s, r[h].l, F, Y ? Y + r[h].j0 : nullptr, (const u32x4*)yp, Z + r[h].j0, ld, st);
     });
-    if (yp) yp += packed_y_bytes_one(s, r[h].l);
+    if (yp) yp += packed_y_bytes_one(s, r[h].l, s.dtype == SVDC_F32 ? 2 : 1);
   }
 }
 

@@ -85,10 +85,11 @@ struct PackedQ {
   int64_t offset[2] = {0, 0};
 };
 PackedQ fit_mfma_packed_q(const svdc_shape& s, int l, void* Qp);
-// Bytes of Y rounded to bf16 in the operand layout of the back-projection (written by fit_mfma_project when asked)
-size_t fit_mfma_packed_y_bytes(const svdc_shape& s, int l);
+// Bytes of Y in the operand layout of the back-projection (written by fit_mfma_project when asked): rounded to bf16, one
+// part, for bf16 features; bf16 high and low parts, two, for float32 features
+size_t fit_mfma_packed_y_bytes(const svdc_shape& s, int l, int parts);
 // Y = F Q;  fro_acc (nullable) += ||F||_F^2;  split: bf16 high + low parts of Q.
-// Ypacked != nullptr (plain operands only): the result goes there in packed bf16 form and Y is not written.
+// Ypacked != nullptr (bf16 features: plain operands only): the result goes there in packed form and Y is not written.
 void fit_mfma_project(const svdc_shape& s, int l, const void* F, const void* Qp, float* Y, void* Ypacked,
                       double* fro_acc, bool split, hipStream_t st);
 // Z = F^T Y, with Y as float32 rows or (Ypacked != nullptr) in the packed form; z_clear: Z holds zeros already

@@ -495,16 +495,20 @@ def test_fit_basis_sketch_widths_65_to_256(dtype, N, D, k, p):
         _fit_checks(F[b], V[b], sigma[b], fro2[b], k, store)
 
 
-@pytest.mark.parametrize("dtype,B,D,l", [(torch.float32, 2, 256, 1), (torch.bfloat16, 1, 256, 16), (torch.float32, 1, 200, 17),
-                                         (torch.float32, 1, 384, 63), (torch.bfloat16, 2, 384, 64), (torch.float32, 1, 328, 65),
-                                         (torch.float32, 2, 384, 127), (torch.bfloat16, 1, 384, 129), (torch.float32, 1, 384, 144),
-                                         (torch.float32, 1, 384, 193), (torch.float32, 1, 640, 256)])
-def test_fit_basis_at_the_block_edges_of_the_small_matrices(dtype, B, D, l):
+@pytest.mark.parametrize("dtype,B,D,l,more", [
+    (torch.float32, 2, 256, 1, 150), (torch.bfloat16, 1, 256, 16, 150), (torch.float32, 1, 200, 17, 150),
+    (torch.float32, 1, 384, 63, 150), (torch.bfloat16, 2, 384, 64, 150), (torch.float32, 1, 328, 65, 150),
+    (torch.float32, 2, 384, 127, 150), (torch.bfloat16, 1, 384, 129, 150), (torch.float32, 1, 384, 144, 150),
+    (torch.float32, 1, 384, 193, 150), (torch.float32, 1, 640, 256, 150),
+    # float32 features whose sketch between the two products has its two-part packed form, runs on into the areas behind
+    # it (ragged rows), or is too large for them and stays float32 rows (66 columns padded to 128)
+    (torch.float32, 1, 256, 128, 2880), (torch.float32, 2, 256, 64, 1937), (torch.float32, 1, 256, 66, 4001)])
+def test_fit_basis_at_the_block_edges_of_the_small_matrices(dtype, B, D, l, more):
     """Sketch widths around the 16- and 64-column blocks of the Gram matrix, the factor, its inverse and their application,
     on features whose rank is the sketch width: every direction is found.  float32 values are accurate to the bf16
     high + low split, bf16 ones to the rounding of the features (compared with the exact values of the rounded F)."""
     g = torch.Generator().manual_seed(l)
-    N = l + 150
+    N = l + more
     U = torch.linalg.qr(torch.randn(B, N, l, generator=g, dtype=torch.float64))[0]
     W = torch.linalg.qr(torch.randn(B, D, l, generator=g, dtype=torch.float64))[0]
     s = torch.linspace(1.0, 0.3, l, dtype=torch.float64) * 30.0
