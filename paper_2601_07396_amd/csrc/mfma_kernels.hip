@@ -711,6 +711,14 @@ int32_t forecast_by_width(const svdc_shape& s, const CoefStates& cs, const void*
   if constexpr (kMax == 6 && KT2 == 2 && SPLIT && sizeof(T) == 2 && !EXT) {
     if (m % 8 == 0) return forecast_launch<T, 8, KT2, SPLIT, PD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
   }
+  // float32 features at rank 64 and 128: the estimate gives 3 and 2 chunks, twice as many fit and cover twice as much of
+  // a row per workgroup (18432 x 3072: 107 -> 97 us and 142 -> 117 us); not where that leaves less than two rounds of
+  // workgroups of six row tiles (4608 rows at rank 64: 29 against 32 us)
+  if constexpr (sizeof(T) == 4 && !EXT && KT2 >= 2) {
+    constexpr int kWide = KT2 == 2 ? 6 : 4;
+    if (m % kWide == 0 && (int64_t)(m / kWide) * ((s.N + 15) / 16) * s.B >= (int64_t)12 * num_compute_units())
+      return forecast_launch<T, kWide, KT2, SPLIT, PD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
+  }
   if constexpr (kMax >= 6) {
     if (m % 6 == 0) return forecast_launch<T, 6, KT2, SPLIT, PD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
     if constexpr (!EXT) {   // 1920 = 15 x 128
