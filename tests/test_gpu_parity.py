@@ -356,6 +356,47 @@ def test_small_calls_take_narrow_slabs_and_short_tiles(dtype, B, N, D, k, pad):
         assert float(torch.as_strided(Fh, (B, N, pad), Fh.stride(), D).abs().max()) == 0.0
 
 
+@pytest.mark.parametrize("dtype,B,N,D,k,pad", [(torch.float32, 1, 12311, 3072, 64, 0), (torch.float32, 2, 5003, 3072, 128, 4),
+                                               (torch.float32, 1, 1001, 2304, 100, 0), (torch.bfloat16, 28, 1009, 1152, 32, 0),
+                                               (torch.bfloat16, 3, 5407, 1152, 24, 8)])
+def test_wide_float32_slabs_and_full_height_smoothing_tiles(dtype, B, N, D, k, pad):
+    """Large calls: float32 cached steps over six- and four-chunk slabs, float32 full steps with the deeper operand ring,
+    smoothed residuals over full-height row tiles; ragged last tiles, padded rows."""
+    from oracle import ref_full_step_residual_ema
+    store = "f32" if dtype == torch.float32 else "bf16"
+    g = torch.Generator().manual_seed(N + k)
+    wide = torch.randn(B, N, D + pad, generator=g).to(dtype)
+    prev = torch.randn(N, D + pad, generator=g).to(dtype)
+    V = torch.linalg.qr(torch.randn(B, D, k, generator=g, dtype=torch.float64))[0].float().contiguous()
+    S0 = torch.randn(B, N, k, generator=g)
+    buf = wide.to(DEV)
+    F = buf[:, :, :D]
+    R, Fh = (torch.zeros_like(buf)[:, :, :D] for _ in range(2))
+    Rs = prev.to(DEV).expand(B, -1, -1).contiguous()[:, :, :D]
+    S, Ss = S0.to(DEV), S0.to(DEV)
+    C = torch.empty_like(S)
+    shape = pkg.make_shape(F, k)
+    Vd = V.to(DEV)
+    packed = pkg.pack_basis(shape, Vd)
+    pkg.svdcache_full_step(shape, F, Vd, packed, R, S, C, 0.3, False)
+    pkg.svdcache_forecast(shape, S, Vd, packed, R, Fh)
+    pkg.svdcache_full_step_residual_ema(shape, F, Vd, packed, Rs, Rs, Ss, None, 0.3, 0.25, False)
+    torch.cuda.synchronize()
+    rows = torch.tensor([0, 1, 15, 16, 47, 48, 63, 64, N // 2, N - 64, N - 49, N - 17, N - 16, N - 2, N - 1])
+    for b in {0, B // 2, B - 1}:
+        Fb, Vb, Sb = to_np(wide[b, rows, :D]), to_np(V[b]), to_np(S0[b, rows])
+        Rr, Sr, Cr = ref_full_step(Fb, Vb, Sb, 0.3, False, store)
+        assert_close(to_np(R[b].cpu()[rows]), Rr, store, f"R[{b}]", floor_of=Fb)
+        assert_close(to_np(S[b].cpu()[rows]), Sr, "f32", f"S[{b}]")
+        assert_close(to_np(C[b].cpu()[rows]), Cr, "f32", f"C[{b}]")
+        assert_close(to_np(Fh[b].cpu()[rows]), ref_forecast(Sr, Vb, Rr, store), store, f"Fhat[{b}]", scale_of=Fb, ulp_of=Rr)
+        Re, Se, _ = ref_full_step_residual_ema(Fb, Vb, Sb, to_np(prev[rows, :D]), 0.3, 0.25, False, store)
+        assert_close(to_np(Rs[b].cpu()[rows]), Re, store, f"smoothed R[{b}]", floor_of=Fb)
+        assert_close(to_np(Ss[b].cpu()[rows]), Se, "f32", f"smoothed S[{b}]")
+    if pad:
+        assert float(torch.as_strided(Fh, (B, N, pad), Fh.stride(), D).abs().max()) == 0.0
+
+
 @pytest.mark.parametrize("k", [32, 64, 128])
 def test_mfma_inplace_and_strided(k):
     """In-place residual (R aliases F), padded row stride, no coefficient output."""
