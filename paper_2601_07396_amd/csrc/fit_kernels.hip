@@ -1043,7 +1043,9 @@ struct RoundRobin {
 };
 
 // Singular values, rank order and normalised columns from the orthogonal columns A (LDS, column stride la) of an
-// l <= 138 Jacobi, for a workgroup of nt threads.
+// l <= 138 Jacobi, for a workgroup of nt threads.  The squared norms are ranked by their bit patterns (the sign of a NaN
+// removed): the order of the values, and a total one where features with an infinity or a NaN leave norms that compare
+// with nothing, so that the ranks are a permutation and every entry of `order` that is read below has been written.
 struct JacobiOrder { double nrm[138], inv[138]; int order[138]; };
 __device__ __forceinline__ void jacobi_output(const double* A, int la, int l, int k, int nt, JacobiOrder& o, double* wo,
                                               float* sigma) {
@@ -1052,14 +1054,18 @@ __device__ __forceinline__ void jacobi_output(const double* A, int la, int l, in
     double s = 0.0;
     for (int r = t & 7; r < l; r += 8) s += A[j * la + r] * A[j * la + r];
     s = row_sum<8>(s);
-    if ((t & 7) == 0) o.nrm[j] = s;
+    if ((t & 7) == 0) o.nrm[j] = fabs(s);
   }
   __syncthreads();
   for (int j = t; j < l; j += nt) {
     const double nj = o.nrm[j];
+    const long long kj = __double_as_longlong(nj);
     int rank = 0;
 #pragma unroll 8
-    for (int i = 0; i < l; ++i) rank += (o.nrm[i] > nj || (o.nrm[i] == nj && i < j)) ? 1 : 0;
+    for (int i = 0; i < l; ++i) {
+      const long long ki = __double_as_longlong(o.nrm[i]);
+      rank += (ki > kj || (ki == kj && i < j)) ? 1 : 0;
+    }
     if (rank < k) sigma[rank] = (float)sqrt(nj);
     o.order[rank] = j;
     o.inv[rank] = nj > 0.0 ? 1.0 / sqrt(nj) : 0.0;

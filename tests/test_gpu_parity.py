@@ -568,6 +568,26 @@ def test_fit_basis_at_the_block_edges_of_the_small_matrices(dtype, B, D, l, more
         assert abs(float(fro2[b]) / np.sum(Fb * Fb) - 1) <= 1e-5
 
 
+@pytest.mark.parametrize("k,p", [(4, -1), (24, 0), (96, -1), (120, 16)])     # the wave Jacobi by width, and the one of 129..138 columns
+@pytest.mark.parametrize("value", [float("nan"), float("-inf")], ids=["nan", "inf"])
+def test_fit_writes_every_rank_of_a_block_that_is_not_finite(k, p, value):
+    """Norms that compare with nothing still have one rank each: no output of such a block is left unwritten, and the other
+    block's fit is not affected."""
+    g = torch.Generator().manual_seed(k)
+    F = ((torch.randn(2, 200, k, generator=g) * torch.logspace(0, -1, k)) @ torch.randn(2, k, 256, generator=g)).contiguous()
+    F[0, 17, 33] = value
+    shape = pkg.make_shape(F, k)
+    V, sigma = torch.full((2, 256, k), -7.0, device=DEV), torch.full((2, k), -7.0, device=DEV)
+    fro2 = torch.empty(2, device=DEV)
+    ws = torch.empty(pkg.svdcache_workspace_bytes(shape, p), device=DEV, dtype=torch.uint8)
+    pkg.svdcache_fit_basis(shape, F.to(DEV), V, sigma, fro2, ws, p)
+    torch.cuda.synchronize()
+    assert not (sigma == -7.0).any() and not (V == -7.0).any()
+    # (the last pivot of the factor is clamped from below, which replaces a NaN: its value is a zero, ranked last)
+    assert not torch.isfinite(sigma[0, 0]) and not torch.isfinite(V[0]).any() and not torch.isfinite(fro2[0])
+    _fit_checks(F[1], V[1], sigma[1], fro2[1], k, "f32")
+
+
 @pytest.mark.parametrize("dtype,N,D,k,p", [(torch.float32, 300, 128, 12, 20), (torch.bfloat16, 400, 256, 24, 40),
                                             (torch.bfloat16, 500, 256, 70, 90)], ids=["f32", "bf16-mfma", "bf16-l160"])
 def test_fit_basis_without_power_iterations(dtype, N, D, k, p):
