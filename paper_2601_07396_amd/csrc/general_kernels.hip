@@ -144,9 +144,12 @@ __device__ __forceinline__ void reconstruct(const float* v, const float* cs, flo
 }
 
 // Full-compute step (Eq. 8-11): C = F V, R = F - C V^T, EMA update of S.  A workgroup takes 16 token rows; its eight
-// waves take every eighth chunk of 32 channels.  Phase 1 projects, 16 KT coefficients at a time: four accumulators per
-// result tile and eight waves keep the chains of additions short, float64 joins them (no less accurate than one chain per
-// lane and a tree over 64 lanes), and that leaves registers for two workgroups per compute unit; the waves' partial sums meet in LDS.
+// waves take every eighth chunk of 32 channels.  Phase 1 projects, 16 KT coefficients at a time, with four accumulators per
+// result tile, which leaves registers for two workgroups per compute unit; the waves' partial sums meet in LDS.  The
+// accumulators are added up every two chunks, so that no chain of float32 additions is longer than 16 products, and float64
+// joins what is left.  Without that the chains grow with the channels: C of 2040 channels was off by 1.5e-7 of its norm,
+// 1.25e-7 with one chain per lane and a tree over 64 lanes, 0.95e-7 like this.  It costs nothing to 5 %, 9 % at
+// 256 rows and ranks of several passes.
 // Phase 2 forms the residual chunk by chunk.  F and R may alias, R and Rp too: phase 1 has read all of the workgroup's
 // rows before the barrier, and phase 2 reads every element in the lane that overwrites it.
 constexpr int kStepWaves = 8;
@@ -169,11 +172,13 @@ __global__ __launch_bounds__(64 * kStepWaves, 4) void full_step_general_kernel(c
   const int64_t roff = (int64_t)b * bstride + (int64_t)min(row0 + r, N - 1) * ldf;
 
   for (int j0 = 0; j0 < k; j0 += 16 * KT) {
-    f32x4 acc[KT][4];
+    f32x4 acc[KT][4], tot[KT];
 #pragma unroll
-    for (int jt = 0; jt < KT; ++jt)
+    for (int jt = 0; jt < KT; ++jt) {
+      tot[jt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int h = 0; h < 4; ++h) acc[jt][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     Piece<T> fn;
     VPiece<KT> vp;
     if (wave < nchunk) {
@@ -186,6 +191,14 @@ __global__ __launch_bounds__(64 * kStepWaves, 4) void full_step_general_kernel(c
       if (c + kStepWaves < nchunk) {
         fn.load(F + roff, 32 * (c + kStepWaves) + 8 * g, D);
         vp.load(v, D, k, c + kStepWaves, j0);
+      }
+      if (c >= 2 * kStepWaves && (c / kStepWaves) % 2 == 0) {
+#pragma unroll
+        for (int jt = 0; jt < KT; ++jt) {
+          tot[jt] += (acc[jt][0] + acc[jt][1]) + (acc[jt][2] + acc[jt][3]);
+#pragma unroll
+          for (int h = 0; h < 4; ++h) acc[jt][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
       }
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -203,7 +216,7 @@ __global__ __launch_bounds__(64 * kStepWaves, 4) void full_step_general_kernel(c
       f32x4 s;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        s[i] = (float)(((double)acc[jt][0][i] + acc[jt][1][i]) + ((double)acc[jt][2][i] + acc[jt][3][i]));
+        s[i] = (float)((((double)acc[jt][0][i] + acc[jt][1][i]) + ((double)acc[jt][2][i] + acc[jt][3][i])) + tot[jt][i]);
       part[jt * 64 + lane] = s;
     }
     __syncthreads();

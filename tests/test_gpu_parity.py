@@ -93,6 +93,22 @@ def test_general_kernels_at_the_edges_of_their_tiles(dtype, B, N, D, k):
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+def test_general_projection_sums_in_short_chains(dtype):
+    """C of many channels: float32 chains of at most 16 products, their sums in a chain of one link per 512 channels.  A chain
+    of n terms of random sign is off by 0.41 u sqrt(n / 2) of its result (0.41 u: root mean square of the rounding of one
+    addition, u = 2^-24), so 16 links and D / 512 links with the two additions between them and the final rounding give
+    0.41 u sqrt(8 + D / 1024 + 3), 1.35e-7 at 20000 channels; one chain per accumulator would be at 4.4e-7."""
+    N, D, k = 256, 20000, 21
+    g = torch.Generator().manual_seed(D + k)
+    F = torch.randn(1, N, D, generator=g).to(dtype)
+    V = torch.randn(1, D, k, generator=g) / D ** 0.5
+    R, S, Cc, _, pk = _run_full(F, D, V, torch.zeros(1, N, k), 0.3, True)
+    assert pk is None
+    bound = 1.5 * 0.41 * 2.0 ** -24 * (8 + D / 1024 + 3) ** 0.5
+    assert rel_err(to_np(Cc[0]), to_np(F[0]) @ to_np(V[0])) <= bound
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
 def test_strided_rows_inplace_and_null_C(dtype):
     store = "f32" if dtype == torch.float32 else "bf16"
     B, N, D, k, ldf = 2, 50, 64, 8, 96
