@@ -20,8 +20,8 @@
 // as bf16 "high" and "low" parts (V = hi + lo to ~16 significant bits) in
 // per-wavefront tiles of 64 lanes x 16 bytes.
 #include <algorithm>
-#include <cmath>
 
+#include "step_tiling.h"
 #include "svdc_device.h"
 #include "svdc_internal.h"
 
@@ -635,33 +635,22 @@ int32_t launch_pack_basis(const svdc_shape& s, const float* V, void* packed, hip
 
 namespace {
 
+// tpg: row tiles per workgroup, 0: not chosen yet (see step_tiling.h, which may also choose a narrower slab)
 template <typename T, int NCW, int KT2, bool SPLIT, int PD, bool EXT, bool PS = false>
 int32_t forecast_launch(const svdc_shape& s, const CoefStates& cs, const void* packed, const void* R, const void* X,
-                        void* Fhat, hipStream_t st) {
+                        void* Fhat, hipStream_t st, int tpg = 0) {
   const int NS = s.D / (128 * NCW);
   const int ntile = (s.N + 15) / 16;
-  // Row tiles per workgroup: 6..16, chosen so that the workgroups fill whole rounds of the machine
-  // (a grid of e.g. 16.03 x the number of compute units costs a 17th, nearly empty round).
-  const int cus = num_compute_units();
-  int tpg = 8;
-  double best = 0.0;
-  const int fewest = NCW > 3 ? 6 : 1;
-  for (int cand = 16; cand >= fewest; --cand) {
-    const int64_t w = (int64_t)NS * ((ntile + cand - 1) / cand) * s.B;
-    const double rounds = (double)w / cus;
-    const double eff = rounds / std::ceil(rounds) * ((double)ntile / (cand * ((ntile + cand - 1) / cand)));
-    if (eff > best + 1e-9) { best = eff; tpg = cand; }
-  }
-  // A call too small for that leaves compute units idle (one block of 4608 rows: 96 workgroups).  Narrow slabs give more
-  // workgroups with less of the basis to load in each (384 channels instead of 1536), and as few as one row tile per
-  // workgroup: 23 -> 13 us for that block at rank 32, 23 -> 17 us at rank 64.  Twice that size is no faster for it.
-  if constexpr (NCW > 3) {
-    if (best < 0.7) {
+  if (tpg == 0) {
+    const int m = s.D / 128;
+    const CachedCall call{m, ntile, s.B, KT2, SPLIT ? 2 : 1, (int)sizeof(T), num_compute_units()};
+    const CachedTiling t = cached_tiling(call, NCW, NCW <= 3 ? 0 : (m % 3 == 0 ? 3 : (m % 2 == 0 ? 2 : 0)));
+    if constexpr (NCW > 3) {
       constexpr int kNarrowPD = PD < 2 ? 2 : PD;
-      const int m = s.D / 128;
-      if (m % 3 == 0) return forecast_launch<T, 3, KT2, SPLIT, kNarrowPD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
-      if (m % 2 == 0) return forecast_launch<T, 2, KT2, SPLIT, kNarrowPD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
+      if (t.chunks == 3) return forecast_launch<T, 3, KT2, SPLIT, kNarrowPD, EXT, PS>(s, cs, packed, R, X, Fhat, st, t.tiles);
+      if (t.chunks == 2) return forecast_launch<T, 2, KT2, SPLIT, kNarrowPD, EXT, PS>(s, cs, packed, R, X, Fhat, st, t.tiles);
     }
+    tpg = t.tiles;
   }
   const int gpb = (ntile + tpg - 1) / tpg;
   const int64_t grid = (int64_t)NS * gpb * s.B;

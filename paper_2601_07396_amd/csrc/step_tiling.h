@@ -1,0 +1,67 @@
+// Channel slab and row tiles per workgroup of the cached step: host arithmetic only, apart from the launcher so that it
+// can be checked without a GPU.
+#pragma once
+#include <stdint.h>
+
+#include <algorithm>
+#include <cmath>
+
+namespace svdc {
+
+// What a cached step launches: slabs of `chunks` x 128 channels, `tiles` row tiles of 16 per workgroup.
+struct CachedTiling {
+  int chunks, tiles;
+};
+
+// One launch: m = D / 128 chunks of channels, ntile row tiles, B blocks; kt2 = padded rank / 32, parts = 2 where the basis
+// operands have a high and a low part and 1 otherwise, elem = bytes of a feature, cus compute units.
+struct CachedCall {
+  int m, ntile;
+  int64_t B;
+  int kt2, parts, elem, cus;
+
+  int64_t groups(int tiles) const { return (ntile + tiles - 1) / tiles; }
+  int64_t workgroups(CachedTiling t) const { return (int64_t)(m / t.chunks) * groups(t.tiles) * B; }
+  // share of the machine's workgroup slots, over whole rounds, that do work
+  double fill(CachedTiling t) const {
+    const double rounds = (double)workgroups(t) / cus;
+    return rounds / std::ceil(rounds) * ((double)ntile / ((double)t.tiles * groups(t.tiles)));
+  }
+  // Rounds x (row tiles + basis operands of the slab), in units of the features of one bf16 row tile and chunk (4 KB in,
+  // 4 KB out).  The operands of a chunk are 8 KB per part and 32 coefficients and come out of L2 about twice as fast; the
+  // matrix instructions add a twentieth per 32 coefficients and product.
+  double cost(CachedTiling t) const {
+    const int64_t rounds = (workgroups(t) + cus - 1) / cus;
+    const double tile = elem / 2 + 0.05 * kt2 * (parts == 2 ? 3 : 1), basis = 0.5 * kt2 * parts;
+    return (double)rounds * t.chunks * (std::min(t.tiles, ntile) * tile + basis);
+  }
+};
+
+// Every workgroup loads the operands of its slab once and uses them for each of its row tiles, so a call that fills the
+// machine takes 6 to 16 of them, the number whose grid fills whole rounds best (a grid of e.g. 16.03 x the compute units
+// costs a 17th, nearly empty round): with fewer the operands outweigh the features, and rounding better gains little
+// (28 x 1548 x 1920 float32, rank 96: 335 us with one tile, 243 us like this; two states 2 x 22551 x 4096 bf16, rank 96:
+// 1278 and 828 us).
+// A call for which even the best of these fills less than 0.7 leaves compute units idle (one block of 4608 x 3072 rows:
+// 96 workgroups of 1536 channels).  It may take fewer tiles, and a slab of 3 or 2 chunks (`narrow`, 0 if there is none)
+// instead of the widest one, where that costs less: 23 -> 13 us for that block at rank 32, 23 -> 17 us at rank 64.  Not
+// where many small workgroups would only load operands (43 x 129 x 2048, rank 128: 29 us wide, 46 us narrow); over 460
+// sampled calls of up to two rounds this is within 4 % of the best of all choices.
+inline CachedTiling cached_tiling(const CachedCall& call, int chunks, int narrow) {
+  CachedTiling best{chunks, 16};
+  for (int cand = 15; cand >= 6; --cand)
+    if (call.fill({chunks, cand}) > call.fill(best) + 1e-9) best.tiles = cand;
+  if (call.fill(best) >= 0.7) return best;
+  double least = 0.85 * call.cost(best);
+  const int few = chunks > 3 ? narrow : chunks;
+  for (int cand = std::min(16, call.ntile); few > 0 && cand >= 1; --cand) {
+    const double c = call.cost({few, cand});
+    if (c < least) {
+      least = c;
+      best = {few, cand};
+    }
+  }
+  return best;
+}
+
+}  // namespace svdc

@@ -1,0 +1,93 @@
+"""Channel slab and row tiles per workgroup of the cached step (host arithmetic, compiled on its own: no GPU)."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <cstdio>
+#include "step_tiling.h"
+// m ntile B kt2 parts elem cus, widest slab, narrow slab -> chunks tiles, the best of 16..6 at the widest slab and its fill
+int main() {
+  svdc::CachedCall c;
+  long long B;
+  int chunks, narrow;
+  while (std::scanf("%d %d %lld %d %d %d %d %d %d", &c.m, &c.ntile, &B, &c.kt2, &c.parts, &c.elem, &c.cus, &chunks, &narrow) == 9) {
+    c.B = B;
+    const svdc::CachedTiling t = svdc::cached_tiling(c, chunks, narrow);
+    int best = 16;
+    for (int n = 15; n >= 6; --n)
+      if (c.fill({chunks, n}) > c.fill({chunks, best}) + 1e-9) best = n;
+    std::printf("%d %d %d %.9f\n", t.chunks, t.tiles, best, c.fill({chunks, best}));
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def tiling(tmp_path_factory):
+    d = tmp_path_factory.mktemp("tiling")
+    src, exe = str(d / "tiling.cpp"), str(d / "tiling")
+    with open(src, "w") as f:
+        f.write(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2601_07396_amd", "csrc"), "-o", exe,
+                    src], check=True)
+
+    def run(calls):
+        text = "\n".join(" ".join(str(int(x)) for x in c) for c in calls)
+        out = subprocess.run([exe], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout
+        return [(int(a), int(b), int(c), float(d)) for a, b, c, d in (line.split() for line in out.splitlines())]
+    return run
+
+
+def _narrow(m, chunks):
+    return 0 if chunks <= 3 else (3 if m % 3 == 0 else (2 if m % 2 == 0 else 0))
+
+
+def _calls():
+    for m in (2, 4, 8, 9, 12, 15, 16, 20, 24, 32, 40):
+        for chunks in (1, 2, 3, 4, 6, 8, 9, 12):
+            if m % chunks:
+                continue
+            for B in (1, 2, 4, 19, 28, 57, 300):
+                for ntile in (1, 2, 5, 13, 42, 63, 125, 288, 423, 1152, 7441):
+                    for kt2, parts, elem in ((1, 2, 2), (2, 1, 2), (4, 2, 2), (4, 2, 4)):
+                        for cus in (32, 256):
+                            yield m, ntile, B, kt2, parts, elem, cus, chunks, _narrow(m, chunks)
+
+
+def test_a_call_that_fills_the_machine_reuses_its_basis(tiling):
+    """Every workgroup loads the basis operands of its slab once and uses them for each of its row tiles.  Fewer than six
+    tiles are for calls that leave the machine unfilled otherwise, whatever the width of the slab; in a call that fills it
+    they trade basis traffic for a rounder grid."""
+    calls = list(_calls())
+    filled = 0
+    for call, (chunks, tiles, tiles6, fill6) in zip(calls, tiling(calls)):
+        assert call[0] % chunks == 0 and 1 <= tiles <= 16, call
+        if fill6 >= 0.7:
+            filled += 1
+            assert (chunks, tiles) == (call[7], tiles6), call
+        elif tiles < 6:
+            assert chunks <= 3 and tiles <= call[1], call
+    assert filled > 1000
+
+
+@pytest.mark.parametrize("m,ntile,B,kt2,parts,elem,chunks,tiles", [
+    (24, 7442, 2, 2, 2, 2, 3, 13), (24, 125, 24, 2, 2, 2, 3, 16), (24, 125, 24, 4, 2, 2, 1, 7), (9, 288, 57, 4, 2, 2, 3, 9),
+    (2, 7442, 2, 1, 2, 2, 2, 15), (15, 97, 28, 4, 2, 4, 1, 7)])
+def test_large_calls_with_slabs_of_at_most_three_chunks(tiling, m, ntile, B, kt2, parts, elem, chunks, tiles):
+    """Several-state forecasts and cached steps for which three chunks or fewer are the widest slab: 2 x 119056 and 24 x 2000
+    rows of 3072 channels at rank 64 and 128, 57 x 4608 x 1152, 2 x 119056 x 256, 28 x 1548 x 1920 in float32."""
+    assert tiling([(m, ntile, B, kt2, parts, elem, 256, chunks, 0)])[0][:2] == (chunks, tiles)
+
+
+def test_small_calls(tiling):
+    """A single block of 4608 x 3072 takes narrow slabs; blocks of a few rows at rank 128, whose basis operands outweigh their
+    features, stay on the widest one."""
+    assert tiling([(24, 288, 1, 1, 2, 2, 256, 12, 3)])[0][0] == 3
+    assert tiling([(24, 288, 1, 2, 2, 2, 256, 8, 3)])[0][0] == 3
+    assert tiling([(16, 9, 43, 4, 2, 2, 256, 4, 2)])[0][0] == 4
+    chunks, tiles = tiling([(15, 8, 19, 4, 2, 2, 256, 3, 0)])[0][:2]
+    assert chunks == 3 and 5 * 19 * -(-8 // tiles) <= 256     # 19 blocks of 128 x 1920: one round, not three with one tile each
