@@ -333,25 +333,30 @@ constexpr double kRankTol = 1e-12;
 // L = L' D^(1/2), L^-1 = D^(-1/2) U.  Measured at 64 columns: 22 us with the inverse, against 18.6 us for the factor
 // alone with a square root per column and 26 us (57 us for 57 blocks of 3072 rows) for the substitution that the inverse
 // replaces in apply_factor_kernel.
-//   w <= 64; columns from w on are padded with the identity.  Lower triangle of the block of G = L, upper part zeroed.
+//   H = 64, or 16 for l <= 16, which one wave does without waiting for others: 3.8 us for 6 columns against 6.1 us with
+//          H = 64.  In either the panels and the levels of the inverse stop at w (22 us if they do not).
+//   w <= H; columns from w on are padded with the identity.  Lower triangle of the block of G = L, upper part zeroed.
 //   Minv   out  (want_inv) row-major [w x w] at row stride ldm, block b at Minv + b * m_bstride
 //   slot   the shift: computed from the diag_n diagonal entries of G and stored when c0 = 0, read otherwise (nullable when
 //          there is one block only)
 // ---------------------------------------------------------------------------
 constexpr int kCholBlock = 64;
 
-__global__ __launch_bounds__(256) void chol_inv_kernel(double* G, int l, int c0, int w, double* Minv, int64_t m_bstride,
-                                                       int ldm, int want_inv, double* slot, int64_t slot_bstride,
-                                                       double rel_shift, int32_t* info) {
-  constexpr int H = kCholBlock, LD = H + 1;
+template <int H>
+__global__ __launch_bounds__(H == 64 ? 256 : 64) void chol_inv_kernel(double* G, int l, int c0, int w, double* Minv,
+                                                                      int64_t m_bstride, int ldm, int want_inv, double* slot,
+                                                                      int64_t slot_bstride, double rel_shift, int32_t* info) {
+  static_assert(H == 64 || H == 16, "a 16 x 16 or 4 x 4 grid of threads with 4 x 4 elements each");
+  constexpr int LD = H + 1, NG = H / 4, NT = H == 64 ? 256 : 64;
   __shared__ double Lp[H * LD];        // L' (strictly lower 4 x 4 blocks); first the staging area of the update
   __shared__ double U[H * LD];         // L'^-1; first the update itself
-  __shared__ double Tm[32 * 33];       // L'_21 U_11
+  __shared__ double Tm[H == 64 ? 32 * 33 : 64];   // L'_21 U_11
   __shared__ __align__(16) double py[4][H];   // panel: columns of L' D, rows contiguous
   __shared__ double dl[2][6], dr[2][4];   // strict lower part and reciprocal pivots of the diagonal block, by panel parity
   __shared__ double dv[H], sq[H], rs[H];  // pivots, their square roots and reciprocal square roots
   __shared__ double s_shift;
-  const int b = blockIdx.x, t = threadIdx.x, tj = t >> 4, ti = t & 15;
+  const int b = blockIdx.x, t = threadIdx.x, tj = t / NG, ti = t % NG;
+  const bool own = t < NG * NG;
   double* g = G + (int64_t)b * l * l;
   double* gd = g + (int64_t)c0 * l + c0;
   double a[4][4];
@@ -373,7 +378,7 @@ __global__ __launch_bounds__(256) void chol_inv_kernel(double* G, int l, int c0,
       s_shift = slot[(int64_t)b * slot_bstride];
     }
   }
-  if (c0 > 0) {   // sum_c L[i][c] L[j][c], 16 columns c per step, c0 a multiple of 64
+  if (H == 64 && c0 > 0) {   // sum_c L[i][c] L[j][c], 16 columns c per step, c0 a multiple of 64
     const Quadrant q;
     f64x4 acc[2][2];
 #pragma unroll
@@ -386,7 +391,7 @@ __global__ __launch_bounds__(256) void chol_inv_kernel(double* G, int l, int c0,
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = g[(int64_t)(k0 + kr) * l + c0 + min(col + e, w - 1)];   // beyond w: not used
     };
-    static_assert(16 * kM64Stride <= H * LD, "staging fits");
+    static_assert(H != 64 || 16 * kM64Stride <= H * LD, "staging fits");
     fetch(0);
     for (int k0 = 0; k0 < c0; k0 += 16) {
       if (k0 > 0) __syncthreads();
@@ -421,9 +426,10 @@ __global__ __launch_bounds__(256) void chol_inv_kernel(double* G, int l, int c0,
 
   const double pivot_floor = shift * (kRankTol / rel_shift);
   bool dependent = false;
-  for (int cb = 0; cb < H / 4; ++cb) {
+  if (t < H && t >= (w + 3) / 4 * 4) dv[t] = 1.0;   // pivots of the panels that are identity throughout
+  for (int cb = 0; 4 * cb < w; ++cb) {
     const int par = cb & 1;
-    if (ti == cb && tj == cb) {
+    if (own && ti == cb && tj == cb) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         dependent |= (4 * cb + q < w) && a[q][q] < pivot_floor;
@@ -452,7 +458,7 @@ __global__ __launch_bounds__(256) void chol_inv_kernel(double* G, int l, int c0,
       dl[par][3] = a[3][0]; dl[par][4] = a[3][1]; dl[par][5] = a[3][2];
     }
     __syncthreads();
-    if (tj == cb && ti > cb) {    // rows of L' D: Y = B L'_d^-T, published; and of L', kept
+    if (own && tj == cb && ti > cb) {    // rows of L' D: Y = B L'_d^-T, published; and of L', kept
       const double l10 = dl[par][0], l20 = dl[par][1], l21 = dl[par][2], l30 = dl[par][3], l31 = dl[par][4], l32 = dl[par][5];
       double y[4][4];
 #pragma unroll
@@ -473,7 +479,7 @@ __global__ __launch_bounds__(256) void chol_inv_kernel(double* G, int l, int c0,
         for (int ii = 0; ii < 4; ++ii) a[ii][q] = y[q][ii] * dr[par][q];
     }
     __syncthreads();
-    if (tj > cb && ti >= tj) {
+    if (own && tj > cb && ti >= tj) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const double r = dr[par][q];
@@ -503,7 +509,7 @@ __global__ __launch_bounds__(256) void chol_inv_kernel(double* G, int l, int c0,
     sq[t] = d * r;
   }
   // L' to LDS; the diagonal 4 x 4 blocks and their inverses, zeros above
-  if (ti == tj) {
+  if (own && ti == tj) {
     const double u10 = -a[1][0], u21 = -a[2][1], u32 = -a[3][2];
     const double u20 = -(a[2][0] + a[2][1] * u10), u31 = -(a[3][1] + a[3][2] * u21);
     const double u30 = -(a[3][0] + a[3][1] * u10 + a[3][2] * u20);
@@ -515,7 +521,7 @@ __global__ __launch_bounds__(256) void chol_inv_kernel(double* G, int l, int c0,
         U[(4 * ti + ii) * LD + 4 * tj + jj] = u[ii][jj];
         Lp[(4 * ti + ii) * LD + 4 * tj + jj] = jj < ii ? a[ii][jj] : (ii == jj ? 1.0 : 0.0);
       }
-  } else {
+  } else if (own) {
 #pragma unroll
     for (int ii = 0; ii < 4; ++ii)
 #pragma unroll
@@ -525,8 +531,8 @@ __global__ __launch_bounds__(256) void chol_inv_kernel(double* G, int l, int c0,
       }
   }
   __syncthreads();
-  if (want_inv) {
-    if (t < 128) {   // pairs of 4 x 4 blocks
+  if (want_inv && w > 4) {   // w is uniform; columns beyond it are not written
+    if (t < 2 * H) { // pairs of 4 x 4 blocks
       const int p = t >> 4, i = (t >> 2) & 3, j = t & 3, rb = 8 * p + 4, cb = 8 * p;
       double s = 0.0;
 #pragma unroll
@@ -539,7 +545,7 @@ __global__ __launch_bounds__(256) void chol_inv_kernel(double* G, int l, int c0,
       U[(rb + i) * LD + cb + j] = -s;
     }
     __syncthreads();
-    {                // pairs of 8 x 8 blocks, one element per thread
+    if (w > 8) {     // pairs of 8 x 8 blocks, one element per thread
       const int p = t >> 6, i = (t >> 3) & 7, j = t & 7, rb = 16 * p + 8, cb = 16 * p;
       double x = 0.0;
 #pragma unroll
@@ -552,48 +558,50 @@ __global__ __launch_bounds__(256) void chol_inv_kernel(double* G, int l, int c0,
       U[(rb + i) * LD + cb + j] = -s;
     }
     __syncthreads();
-    const int wave = t >> 6, lane = t & 63, m = lane & 15, kq = lane >> 4;
-    // 16 x 16 tile sum_k A[i][k] B[k][j] over K = 4 k4n
-    auto product = [&](const double* A, int lda, const double* Bm, int ldb, int k4n) {
-      f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-      for (int k4 = 0; k4 < k4n; ++k4)
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[m * lda + 4 * k4 + kq], Bm[(4 * k4 + kq) * ldb + m], acc, 0, 0, 0);
-      return acc;
-    };
-    {                // pairs of 16 x 16 blocks: waves 0 and 1
-      const int rb = 32 * wave + 16, cb = 32 * wave;
-      double* tm = Tm + 272 * wave;
-      if (wave < 2) {
-        const f64x4 x = product(Lp + rb * LD + cb, LD, U + cb * LD + cb, LD, 4);
+    if constexpr (H == 64) {
+      const int wave = t >> 6, lane = t & 63, m = lane & 15, kq = lane >> 4;
+      // 16 x 16 tile sum_k A[i][k] B[k][j] over K = 4 k4n
+      auto product = [&](const double* A, int lda, const double* Bm, int ldb, int k4n) {
+        f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+        for (int k4 = 0; k4 < k4n; ++k4)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[m * lda + 4 * k4 + kq], Bm[(4 * k4 + kq) * ldb + m], acc, 0, 0, 0);
+        return acc;
+      };
+      if (w > 16) {    // pairs of 16 x 16 blocks: waves 0 and 1
+        const int rb = 32 * wave + 16, cb = 32 * wave;
+        double* tm = Tm + 272 * wave;
+        if (wave < 2) {
+          const f64x4 x = product(Lp + rb * LD + cb, LD, U + cb * LD + cb, LD, 4);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) tm[(4 * v + kq) * 17 + m] = x[v];
+          for (int v = 0; v < 4; ++v) tm[(4 * v + kq) * 17 + m] = x[v];
+        }
+        __syncthreads();
+        if (wave < 2) {
+          const f64x4 x = product(U + rb * LD + rb, LD, tm, 17, 4);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) U[(rb + 4 * v + kq) * LD + cb + m] = -x[v];
+        }
       }
       __syncthreads();
-      if (wave < 2) {
-        const f64x4 x = product(U + rb * LD + rb, LD, tm, 17, 4);
+      if (w > 32) {    // the pair of 32 x 32 blocks: a 16 x 16 tile per wave
+        const int i0 = 16 * (wave >> 1), j0 = 16 * (wave & 1);
+        const f64x4 x = product(Lp + (32 + i0) * LD, LD, U + j0, LD, 8);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) U[(rb + 4 * v + kq) * LD + cb + m] = -x[v];
+        for (int v = 0; v < 4; ++v) Tm[(i0 + 4 * v + kq) * 33 + j0 + m] = x[v];
+        __syncthreads();
+        const f64x4 y = product(U + (32 + i0) * LD + 32, LD, Tm + j0, 33, 8);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) U[(32 + i0 + 4 * v + kq) * LD + j0 + m] = -y[v];
       }
-    }
-    __syncthreads();
-    {                // the pair of 32 x 32 blocks: a 16 x 16 tile per wave
-      const int i0 = 16 * (wave >> 1), j0 = 16 * (wave & 1);
-      const f64x4 x = product(Lp + (32 + i0) * LD, LD, U + j0, LD, 8);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) Tm[(i0 + 4 * v + kq) * 33 + j0 + m] = x[v];
-      __syncthreads();
-      const f64x4 y = product(U + (32 + i0) * LD + 32, LD, Tm + j0, 33, 8);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) U[(32 + i0 + 4 * v + kq) * LD + j0 + m] = -y[v];
     }
   }
   __syncthreads();
   double* mi = Minv + (int64_t)b * m_bstride;
-  const int j = t & 63;
+  const int j = t % H;
   const double sj = sq[j], rj = rs[j];
 #pragma unroll
-  for (int n = 0; n < H / 4; ++n) {
-    const int i = (t >> 6) + 4 * n;
+  for (int n = 0; n < H * H / NT; ++n) {
+    const int i = t / H + NT / H * n;
     const double lv = j <= i ? Lp[i * LD + j] * sj : 0.0, uv = j >= i ? U[j * LD + i] * rj : 0.0;
     if (i < w && j < w) {
       gd[(int64_t)i * l + j] = lv;
@@ -743,13 +751,15 @@ __global__ __launch_bounds__(256) void chol_panel_kernel(double* G, const double
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void pack_rows(const float* ot, int ldo, int row0, int D, int b, int l, PackedQ pq);
 
-template <bool ONE_BLOCK>
-__global__ __launch_bounds__(256, ONE_BLOCK ? 3 : 1) void apply_factor_kernel(float* In, const double* __restrict__ G,
+// NT: 16-column tiles of the only column block, 1 (l <= 16) or 4 (l <= 64); 0: several blocks of 64 columns.
+template <int NT>
+__global__ __launch_bounds__(256, NT == 1 ? 6 : (NT == 4 ? 3 : 1)) void apply_factor_kernel(float* In, const double* __restrict__ G,
                                                            const double* __restrict__ Minv, int64_t m_bstride, float* out,
                                                            PackedQ pq, int rows, int l, int zero_in) {
-  constexpr int H = kCholBlock, LT = H + 2;
+  constexpr bool ONE_BLOCK = NT > 0;
+  constexpr int H = kCholBlock, LT = H + 2, TY = ONE_BLOCK ? NT : 4;
   extern __shared__ __align__(16) char dyn[];
-  const int nb = ONE_BLOCK ? 1 : (l + H - 1) / H, ldo = nb * H + 4;
+  const int nb = ONE_BLOCK ? 1 : (l + H - 1) / H, ldo = ONE_BLOCK ? 16 * TY + 4 : nb * H + 4;
   float* ot = reinterpret_cast<float*>(dyn);                                             // [64][ldo]
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, m = lane & 15, kq = lane >> 4;
   // the wave's right-hand sides on their way from the result layout to the operand layout, [16][LT]
@@ -760,22 +770,22 @@ __global__ __launch_bounds__(256, ONE_BLOCK ? 3 : 1) void apply_factor_kernel(fl
   for (int j0 = 0; j0 < l; j0 += H) {
     const int w = min(H, l - j0), ldm = l <= H ? l : H;
     const double* mi = Minv + (int64_t)b * m_bstride + (int64_t)(j0 / H) * H * H;
-    double bm[4][4][4];                        // [s][e][y], y >= s: L_jj^-T[16 s + 4 kq + e][16 y + m]
+    double bm[TY][4][TY];                        // [s][e][y], y >= s: L_jj^-T[16 s + 4 kq + e][16 y + m]
     auto load_b = [&](int s) {
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int y = s; y < 4; ++y) {
+        for (int y = s; y < TY; ++y) {
           const int k = 16 * s + 4 * kq + e, j = 16 * y + m;
           bm[s][e][y] = mi[min(k, w - 1) * ldm + min(j, w - 1)];     // columns beyond w are not used
         }
     };
     load_b(0);
-    double a[4][4];
+    double a[TY][4];
     if (j0 == 0) {
       const float* row = in + (int64_t)min(rw + m, rows - 1) * l;
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
+      for (int s = 0; s < TY; ++s) {
         const int k = 16 * s + 4 * kq;
         if ((l & 3) == 0) {
           float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -833,24 +843,24 @@ __global__ __launch_bounds__(256, ONE_BLOCK ? 3 : 1) void apply_factor_kernel(fl
 #pragma unroll
         for (int e = 0; e < 4; ++e) a[s][e] = tt[m * LT + 16 * s + 4 * kq + e];
     }
-    f64x4 acc[4];
+    f64x4 acc[TY];
 #pragma unroll
-    for (int y = 0; y < 4; ++y) acc[y] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int y = 0; y < TY; ++y) acc[y] = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      if (s < 3) load_b(s + 1);                // one step ahead
+    for (int s = 0; s < TY; ++s) {
+      if (s < TY - 1) load_b(s + 1);                // one step ahead
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int y = s; y < 4; ++y) {
-          const double bv = w < H && 16 * s + 4 * kq + e >= w ? 0.0 : bm[s][e][y];
+        for (int y = s; y < TY; ++y) {
+          const double bv = w < 16 * TY && 16 * s + 4 * kq + e >= w ? 0.0 : bm[s][e][y];
           acc[y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s][e], bv, acc[y], 0, 0, 0);
         }
       __builtin_amdgcn_sched_barrier(0);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
-    for (int y = 0; y < 4; ++y)
+    for (int y = 0; y < TY; ++y)
 #pragma unroll
       for (int v = 0; v < 4; ++v) ot[(16 * wave + 4 * v + kq) * ldo + j0 + 16 * y + m] = (float)acc[y][v];
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // a wave reads back only its own rows until here
@@ -1159,6 +1169,17 @@ __global__ __launch_bounds__(512) void jacobi_wave_kernel(const double* __restri
   using I1 = std::integral_constant<int, 1>;
   using I2 = std::integral_constant<int, 2>;
   using I4 = std::integral_constant<int, 4>;
+  // every pair of the block's first n columns (the others are zero)
+  auto rotate_all_inside = [&](int n, double (&xv)[NE], double& nv) {
+    if (n > 1) rotate_inside(I1{}, xv, nv);
+    if (n > 2) { rotate_inside(I2{}, xv, nv); rotate_inside(std::integral_constant<int, 3>{}, xv, nv); }
+    if (n > 4) {
+      rotate_inside(I4{}, xv, nv);
+      rotate_inside(std::integral_constant<int, 5>{}, xv, nv);
+      rotate_inside(std::integral_constant<int, 6>{}, xv, nv);
+      rotate_inside(std::integral_constant<int, 7>{}, xv, nv);
+    }
+  };
 
   bool converged = false;
   for (int sweep = 0; sweep < max_sweeps; ++sweep) {
@@ -1176,23 +1197,20 @@ __global__ __launch_bounds__(512) void jacobi_wave_kernel(const double* __restri
       nx = row_sum<8>(n0);
       ny = row_sum<8>(n1);
       if (step == 0) {
-        rotate_inside(I1{}, xs, nx); rotate_inside(I1{}, ys, ny);
-        rotate_inside(I2{}, xs, nx); rotate_inside(I2{}, ys, ny);
-        rotate_inside(std::integral_constant<int, 3>{}, xs, nx); rotate_inside(std::integral_constant<int, 3>{}, ys, ny);
-        rotate_inside(I4{}, xs, nx); rotate_inside(I4{}, ys, ny);
-        rotate_inside(std::integral_constant<int, 5>{}, xs, nx); rotate_inside(std::integral_constant<int, 5>{}, ys, ny);
-        rotate_inside(std::integral_constant<int, 6>{}, xs, nx); rotate_inside(std::integral_constant<int, 6>{}, ys, ny);
-        rotate_inside(std::integral_constant<int, 7>{}, xs, nx); rotate_inside(std::integral_constant<int, 7>{}, ys, ny);
+        rotate_all_inside(l - 8 * rr.p, xs, nx);
+        rotate_all_inside(l - 8 * rr.q, ys, ny);
       }
-      rotate(); move_y(I1{});   // rows of y now hold column g ^ 1
-      rotate(); move_y(I2{});   // 3
-      rotate(); move_y(I1{});   // 2
-      rotate(); move_y(I4{});   // 6
-      rotate(); move_y(I1{});   // 7
-      rotate(); move_y(I2{});   // 5
-      rotate(); move_y(I1{});   // 4
-      rotate();
-      py = A + (8 * rr.q + (g ^ 4)) * la + gl;
+      if (8 * rr.p < l && 8 * rr.q < l) {   // both blocks have columns (l is the same for the whole wave)
+        rotate(); move_y(I1{});   // rows of y now hold column g ^ 1
+        rotate(); move_y(I2{});   // 3
+        rotate(); move_y(I1{});   // 2
+        rotate(); move_y(I4{});   // 6
+        rotate(); move_y(I1{});   // 7
+        rotate(); move_y(I2{});   // 5
+        rotate(); move_y(I1{});   // 4
+        rotate();
+        py = A + (8 * rr.q + (g ^ 4)) * la + gl;
+      }
 #pragma unroll
       for (int e = 0; e < NE; ++e) { px[8 * e] = xs[e]; py[8 * e] = ys[e]; }
       rr.next();
@@ -1499,8 +1517,12 @@ void chol_factor(double* G, int B, int l, int32_t* info, hipStream_t st, double*
   for (int c0 = 0; c0 < l; c0 += H) {
     const int w = std::min(H, l - c0);
     const bool last = c0 + w >= l;
-    chol_inv_kernel<<<B, 256, 0, st>>>(G, l, c0, w, M + (int64_t)(c0 / H) * H * H, ll, l <= H ? l : H,
-                                       (want_inv || !last) ? 1 : 0, slot, ll, 1e-14, info);
+    auto factor = [&](auto kernel, int threads) {
+      kernel<<<B, threads, 0, st>>>(G, l, c0, w, M + (int64_t)(c0 / H) * H * H, ll, l <= H ? l : H,
+                                    (want_inv || !last) ? 1 : 0, slot, ll, 1e-14, info);
+    };
+    if (l <= 16) factor(chol_inv_kernel<16>, 64);
+    else factor(chol_inv_kernel<H>, 256);
     if (!last)
       chol_panel_kernel<<<dim3((l - c0 - w + H - 1) / H, B), 256, 0, st>>>(G, M + (int64_t)(c0 / H) * H * H, ll, l, c0);
   }
@@ -1518,14 +1540,15 @@ int32_t apply_factor(float* In, float* out, PackedQ pq, const double* G, const d
                      bool zero_in, hipStream_t st) {
   constexpr int H = kCholBlock;
   const int nb = (l + H - 1) / H;
-  const size_t lds = (size_t)H * (nb * H + 4) * sizeof(float) + (nb > 1 ? (size_t)H * (H + 2) * sizeof(double) : 0);
+  const size_t lds = (size_t)H * ((l <= 16 ? 16 : nb * H) + 4) * sizeof(float) + (nb > 1 ? (size_t)H * (H + 2) * sizeof(double) : 0);
   const dim3 grid((rows + H - 1) / H, B);
   auto launch = [&](auto kernel) -> int32_t {
     if (set_dyn_lds((const void*)kernel, lds) != SVDC_OK) return SVDC_E_HIP;
     kernel<<<grid, 256, lds, st>>>(In, G, M, (int64_t)l * l, out, pq, rows, l, zero_in ? 1 : 0);
     return SVDC_OK;
   };
-  return nb == 1 ? launch(apply_factor_kernel<true>) : launch(apply_factor_kernel<false>);
+  if (l <= 16) return launch(apply_factor_kernel<1>);
+  return nb == 1 ? launch(apply_factor_kernel<4>) : launch(apply_factor_kernel<0>);
 }
 
 // Orthonormalise the columns of Zin by CholeskyQR (Gram matrix, Cholesky factor and products with it in float64).

@@ -584,6 +584,14 @@ def test_fit_basis_at_the_block_edges_of_the_small_matrices(dtype, B, D, l, more
         assert abs(float(fro2[b]) / np.sum(Fb * Fb) - 1) <= 1e-5
 
 
+@pytest.mark.parametrize("l", [2, 3, 4, 5, 8, 9, 12, 15, 24, 25, 32, 33, 41, 49])
+@pytest.mark.parametrize("D", [104, 256])       # the general products, and the matrix-core ones (the sketch goes on as operand words)
+def test_fit_basis_at_the_widths_of_narrow_sketches(l, D):
+    """Panels of 4 columns, levels of the inverse at 4, 8, 16 and 32 columns, 8-column blocks of the Jacobi that are empty or
+    partly filled."""
+    test_fit_basis_at_the_block_edges_of_the_small_matrices(torch.float32, 2, D, l, 150)
+
+
 @pytest.mark.parametrize("k,p", [(4, -1), (24, 0), (96, -1), (120, 16)])     # the wave Jacobi by width, and the one of 129..138 columns
 @pytest.mark.parametrize("value", [float("nan"), float("-inf")], ids=["nan", "inf"])
 def test_fit_writes_every_rank_of_a_block_that_is_not_finite(k, p, value):
