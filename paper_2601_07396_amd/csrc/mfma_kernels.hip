@@ -777,16 +777,10 @@ int32_t full_step_by_size(const svdc_shape& s, const void* F, const void* packed
   constexpr int W = sizeof(T) == 4 ? 2 : 1;
   constexpr int RT = tile_rows(CH, W, KT2), RD = ring_depth(CH, W, KT2);
   // the variant that also smooths the residual keeps a few chunks of the previous residual in flight: one row
-  // tile less, except where the registers hold them beside the full tile and the persistent grid then takes less time
-  // (rounds x cost of a tile; streaming the basis costs about as much as 1.3 row tiles, measured at 3072 channels):
-  // 28 blocks of 1024 x 1152 in two rounds of 64 rows instead of three of 48, 60.7 -> 57.7 us
+  // tile less, except where the registers hold them beside the full tile and that takes less time (see step_tiling.h)
   if (re.prev) {
     if constexpr (RT > 1 && full_step_regs(CH, W, KT2, RT, RD) + 4 * RT * 4 * W <= 440) {
-      auto cost = [&](int rt) {
-        const int64_t tiles = (int64_t)((s.N + 16 * rt - 1) / (16 * rt)) * s.B, cus = num_compute_units();
-        return (double)((tiles + cus - 1) / cus) * (rt + 1.3);
-      };
-      if (cost(RT) < cost(RT - 1))
+      if (smoothing_takes_full_tiles(RT, KT2, s.N, s.B, num_compute_units()))
         return full_step_launch<T, CH, RT, KT2, SPLIT, RD, true>(s, F, packed, R, S, C, alpha, init, re, st);
     }
     return full_step_launch<T, CH, (RT > 1 ? RT - 1 : 1), KT2, SPLIT, RD, true>(s, F, packed, R, S, C, alpha, init, re, st);

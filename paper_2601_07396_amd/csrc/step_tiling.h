@@ -1,4 +1,4 @@
-// Channel slab and row tiles per workgroup of the cached step: host arithmetic only, apart from the launcher so that it
+// Channel slab and row tiles per workgroup of the cached step, row tiles of the full step that smooths the residual: host arithmetic only, apart from the launcher so that it
 // can be checked without a GPU.
 #pragma once
 #include <stdint.h>
@@ -62,6 +62,22 @@ inline CachedTiling cached_tiling(const CachedCall& call, int chunks, int narrow
     }
   }
   return best;
+}
+
+// Whether the full step that smooths the residual takes rt row tiles of 16 at a time, for which the previous residual
+// still fits beside them, or one less: the persistent grid takes rounds x (rt + x), x = the basis stream in row tiles.
+// Timed at 250 sampled calls (bf16, the widths and ranks where there is a choice: 256 to 1152 channels at rank 32, 256 at
+// rank 64, 256 to 1536 at rank 128; 1 to 12 rounds): a round of 4 tiles takes 1.33 of one of 3 at rank 32 and 1.38 at
+// rank 64, of 2 tiles 1.42 (split operands) to 1.47 of one of 1 at rank 128, which is x = 0.3 per 32 coefficients, split or
+// not.  Short calls scatter by 8 % around that, so the taller tile has to promise as much: with it none of the 250 is
+// slower than one tile less, and they take 11 % less time on average (28 blocks of 1024 x 1152 in two rounds of 64 rows
+// instead of three of 48: 60.7 -> 57.7 us).
+inline bool smoothing_takes_full_tiles(int rt, int kt2, int N, int64_t B, int cus) {
+  auto cost = [&](int r) {
+    const int64_t tiles = (int64_t)((N + 16 * r - 1) / (16 * r)) * B;
+    return (double)((tiles + cus - 1) / cus) * (r + 0.3 * kt2);
+  };
+  return cost(rt) < 0.92 * cost(rt - 1);
 }
 
 }  // namespace svdc

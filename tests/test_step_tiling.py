@@ -1,4 +1,4 @@
-"""Channel slab and row tiles per workgroup of the cached step (host arithmetic, compiled on its own: no GPU)."""
+"""Channel slab and row tiles per workgroup of the step kernels (host arithmetic, compiled on its own: no GPU)."""
 import os
 import subprocess
 
@@ -10,7 +10,15 @@ PROGRAM = r"""
 #include <cstdio>
 #include "step_tiling.h"
 // m ntile B kt2 parts elem cus, widest slab, narrow slab -> chunks tiles, the best of 16..6 at the widest slab and its fill
-int main() {
+// with an argument: rt kt2 N B cus -> whether the smoothing full step takes rt row tiles
+int main(int argc, char**) {
+  if (argc > 1) {
+    int rt, kt2, N, cus;
+    long long B;
+    while (std::scanf("%d %d %d %lld %d", &rt, &kt2, &N, &B, &cus) == 5)
+      std::printf("%d\n", (int)svdc::smoothing_takes_full_tiles(rt, kt2, N, B, cus));
+    return 0;
+  }
   svdc::CachedCall c;
   long long B;
   int chunks, narrow;
@@ -35,9 +43,11 @@ def tiling(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2601_07396_amd", "csrc"), "-o", exe,
                     src], check=True)
 
-    def run(calls):
+    def run(calls, smoothing=False):
         text = "\n".join(" ".join(str(int(x)) for x in c) for c in calls)
-        out = subprocess.run([exe], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout
+        out = subprocess.run([exe] + ["smoothing"] * smoothing, input=text, stdout=subprocess.PIPE, text=True, check=True).stdout
+        if smoothing:
+            return [bool(int(line)) for line in out.split()]
         return [(int(a), int(b), int(c), float(d)) for a, b, c, d in (line.split() for line in out.splitlines())]
     return run
 
@@ -91,3 +101,11 @@ def test_small_calls(tiling):
     assert tiling([(16, 9, 43, 4, 2, 2, 256, 4, 2)])[0][0] == 4
     chunks, tiles = tiling([(15, 8, 19, 4, 2, 2, 256, 3, 0)])[0][:2]
     assert chunks == 3 and 5 * 19 * -(-8 // tiles) <= 256     # 19 blocks of 128 x 1920: one round, not three with one tile each
+
+
+def test_smoothing_full_step_takes_the_taller_tile_where_it_saves_time(tiling):
+    """Measured (us with the taller tile, with one less).  64 rows: 1 x 96983 x 512 rank 8 single operands 69.8 / 66.0,
+    1 x 52658 x 256 rank 48 35.0 / 33.5, 19 x 17388 x 512 rank 8 233.8 / 225.7; 28 x 1024 x 1152 rank 32 57.7 / 60.7.
+    32 rows at rank 128: 19 x 352 x 1024 33.8 / 38.8, 19 x 751 x 1024 36.6 / 47.5."""
+    calls = [(4, 1, 96983, 1), (4, 2, 52658, 1), (4, 1, 17388, 19), (4, 1, 1024, 28), (2, 4, 352, 19), (2, 4, 751, 19)]
+    assert tiling([c + (256,) for c in calls], smoothing=True) == [False, False, False, True, True, True]
