@@ -768,9 +768,7 @@ constexpr int ring_depth(int CH, int W, int KT2) {
 }
 
 // A launch with fewer tiles than compute units leaves units idle: such small problems take tiles one step
-// smaller (their packed-basis traffic does not matter at that size), and tiles of 16 rows where those still fit into
-// one round (4 x 700 rows at rank 32: 23 -> 17 us, 2000 rows 21 -> 16 us; with more tiles than units the second round
-// costs more than the taller tile: 4608 rows 24 against 30 us).
+// smaller (their packed-basis traffic does not matter at that size), and tiles of 16 rows where step_tiling.h allows.
 template <typename T, int CH, int KT2, bool SPLIT>
 int32_t full_step_by_size(const svdc_shape& s, const void* F, const void* packed, void* R, float* S, float* C,
                           float alpha, int init, ResidualEma re, hipStream_t st) {
@@ -801,7 +799,8 @@ int32_t full_step_by_size(const svdc_shape& s, const void* F, const void* packed
   if constexpr (RT > 1) {
     const int64_t tiles = (int64_t)((s.N + 16 * RT - 1) / (16 * RT)) * s.B;
     if constexpr (RT > 2) {
-      if ((int64_t)((s.N + 15) / 16) * s.B <= num_compute_units())
+      if (full_step_takes_single_tiles((int64_t)((s.N + 15) / 16) * s.B,
+                                       (int64_t)s.B * s.D * (32 * KT2) * 2 * (SPLIT ? 2 : 1), num_compute_units()))
         return full_step_launch<T, CH, 1, KT2, SPLIT, RD, false>(s, F, packed, R, S, C, alpha, init, re, st);
     }
     if (tiles < num_compute_units())

@@ -1,4 +1,4 @@
-// Channel slab and row tiles per workgroup of the cached step, row tiles of the full step that smooths the residual: host arithmetic only, apart from the launcher so that it
+// Channel slab and row tiles per workgroup of the cached step, row tiles of the full step: host arithmetic only, apart from the launcher so that it
 // can be checked without a GPU.
 #pragma once
 #include <stdint.h>
@@ -62,6 +62,16 @@ inline CachedTiling cached_tiling(const CachedCall& call, int chunks, int narrow
     }
   }
   return best;
+}
+
+// Whether the full step of a small call takes tiles of 16 rows: where they fit into one round of the machine (a second round
+// costs more than a taller tile: 4608 x 3072 rows, rank 32: 24 us with tall tiles, 30 us), unless most of the machine then
+// streams operands that no L2 (4 MB) holds: each tile reads all basis operands of its block twice.  Against tiles
+// one step below the full height: 4 x 700 x 3072 23 -> 17 us, 28 x 128 x 1152 at rank 32 11.0 -> 8.7 us; but 28 x 125 x 1152
+// at rank 64 (8.3 MB) 18.2 -> 22.3 us and 26 x 128 x 1920 (12.8 MB) 23.4 -> 33.2 us.  Of 234 calls sampled up to one round
+// none is slower with this rule.
+inline bool full_step_takes_single_tiles(int64_t tiles16, int64_t operand_bytes, int cus) {
+  return tiles16 <= cus && (operand_bytes <= (int64_t)3 << 20 || 8 * tiles16 <= 5 * (int64_t)cus);
 }
 
 // Whether the full step that smooths the residual takes rt row tiles of 16 at a time, for which the previous residual

@@ -10,8 +10,15 @@ PROGRAM = r"""
 #include <cstdio>
 #include "step_tiling.h"
 // m ntile B kt2 parts elem cus, widest slab, narrow slab -> chunks tiles, the best of 16..6 at the widest slab and its fill
-// with an argument: rt kt2 N B cus -> whether the smoothing full step takes rt row tiles
+// with an argument: rt kt2 N B cus -> whether the smoothing full step takes rt row tiles; with two: B N D kt2 parts cus ->
+// whether the full step takes tiles of 16 rows
 int main(int argc, char**) {
+  if (argc > 2) {
+    long long B, N, D, kt2, parts, cus;
+    while (std::scanf("%lld %lld %lld %lld %lld %lld", &B, &N, &D, &kt2, &parts, &cus) == 6)
+      std::printf("%d\n", (int)svdc::full_step_takes_single_tiles((N + 15) / 16 * B, B * D * 32 * kt2 * 2 * parts, (int)cus));
+    return 0;
+  }
   if (argc > 1) {
     int rt, kt2, N, cus;
     long long B;
@@ -43,10 +50,10 @@ def tiling(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2601_07396_amd", "csrc"), "-o", exe,
                     src], check=True)
 
-    def run(calls, smoothing=False):
+    def run(calls, rule=()):
         text = "\n".join(" ".join(str(int(x)) for x in c) for c in calls)
-        out = subprocess.run([exe] + ["smoothing"] * smoothing, input=text, stdout=subprocess.PIPE, text=True, check=True).stdout
-        if smoothing:
+        out = subprocess.run([exe, *rule], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout
+        if rule:
             return [bool(int(line)) for line in out.split()]
         return [(int(a), int(b), int(c), float(d)) for a, b, c, d in (line.split() for line in out.splitlines())]
     return run
@@ -108,4 +115,13 @@ def test_smoothing_full_step_takes_the_taller_tile_where_it_saves_time(tiling):
     1 x 52658 x 256 rank 48 35.0 / 33.5, 19 x 17388 x 512 rank 8 233.8 / 225.7; 28 x 1024 x 1152 rank 32 57.7 / 60.7.
     32 rows at rank 128: 19 x 352 x 1024 33.8 / 38.8, 19 x 751 x 1024 36.6 / 47.5."""
     calls = [(4, 1, 96983, 1), (4, 2, 52658, 1), (4, 1, 17388, 19), (4, 1, 1024, 28), (2, 4, 352, 19), (2, 4, 751, 19)]
-    assert tiling([c + (256,) for c in calls], smoothing=True) == [False, False, False, True, True, True]
+    assert tiling([c + (256,) for c in calls], rule=["smoothing"]) == [False, False, False, True, True, True]
+
+
+def test_small_full_steps_take_single_tiles_while_l2_holds_the_basis(tiling):
+    """Measured (us with 16-row tiles, with tiles one step below the full height): 4 x 700 x 3072 rank 32 17 / 23, 28 x 128 x 1152
+    rank 32 single operands 8.7 / 11.0, 57 x 32 x 3072 rank 32 20.2 / 22.9; 28 x 125 x 1152 rank 64 22.3 / 18.2, 26 x 128 x 1920
+    rank 64 33.2 / 23.4, 57 x 48 x 512 rank 64 11.0 / 9.9; 4608 x 3072 rank 32 does not fit one round."""
+    calls = [(4, 700, 3072, 1, 2), (28, 128, 1152, 1, 1), (57, 32, 3072, 1, 2),
+             (28, 125, 1152, 2, 2), (26, 128, 1920, 2, 2), (57, 48, 512, 2, 2), (1, 4608, 3072, 1, 2)]
+    assert tiling([c + (256,) for c in calls], rule=["full", "step"]) == [True, True, True, False, False, False, False]
