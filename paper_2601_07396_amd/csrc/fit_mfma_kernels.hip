@@ -706,19 +706,24 @@ void project_launch(const svdc_shape& s, int l, const void* F, const void* Qp, f
   const uint16_t* q = (const uint16_t*)Qp;
   if (kF32) split = true;
   constexpr int64_t kUnits = 256;
-  auto stationary = [&](auto tg) {
+  // with_split: whether split operands can come this way (their kernels are not built otherwise)
+  auto stationary = [&](auto tg, auto with_split) {
     constexpr int G = decltype(tg)::value;
     const int gpb = (ntile + G - 1) / G;
     const unsigned grid = (unsigned)((int64_t)gpb * s.B);
-    if (split) {
-      const int NS = s.D / (128 * NCWS);
-      if (fro_acc)
-        fit_project_mfma_kernel<T, NCWS, KT, G, true, true><<<grid, 256, 0, st>>>(
-            f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, NS, gpb, ld.ldy);
-      else
-        fit_project_mfma_kernel<T, NCWS, KT, G, true, false><<<grid, 256, 0, st>>>(
-            f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, NS, gpb, ld.ldy);
-    } else if constexpr (!kF32) {
+    if constexpr (decltype(with_split)::value) {
+      if (split) {
+        const int NS = s.D / (128 * NCWS);
+        if (fro_acc)
+          fit_project_mfma_kernel<T, NCWS, KT, G, true, true><<<grid, 256, 0, st>>>(
+              f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, NS, gpb, ld.ldy);
+        else
+          fit_project_mfma_kernel<T, NCWS, KT, G, true, false><<<grid, 256, 0, st>>>(
+              f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, NS, gpb, ld.ldy);
+        return;
+      }
+    }
+    if constexpr (!kF32) {
       const int NS = s.D / (128 * NCW);
       fit_project_mfma_kernel<T, NCW, KT, G, false, false><<<grid, 256, 0, st>>>(
           f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, NS, gpb, ld.ldy);
@@ -728,7 +733,7 @@ void project_launch(const svdc_shape& s, int l, const void* F, const void* Qp, f
   // 4608 x 3072, sketch 64: 11.9 us with plain operands (17.7 with four tiles), 24.3 us with split ones (67 with
   // the rows split over the waves in groups of 12 tiles, 42 in groups of 4).
   if constexpr (KT <= 4) {
-    if ((int64_t)((ntile + TG - 1) / TG) * s.B <= kUnits / 2) return stationary(std::integral_constant<int, 2>{});
+    if ((int64_t)((ntile + TG - 1) / TG) * s.B <= kUnits / 2) return stationary(std::integral_constant<int, 2>{}, std::true_type{});
   }
   // wide sketches: rows split over the waves, Q shared through LDS
   if constexpr (KT >= 4) {
@@ -752,10 +757,14 @@ void project_launch(const svdc_shape& s, int l, const void* F, const void* Qp, f
       else tall(std::integral_constant<int, RTW>{});
       return;
     }
+    // plain operands from here on: never float32 features
     if constexpr (KT == 8 && !kF32)
-      return rows(std::integral_constant<int, RTW>{}, std::integral_constant<int, 4>{}, std::false_type{}, std::false_type{});
+      rows(std::integral_constant<int, RTW>{}, std::integral_constant<int, 4>{}, std::false_type{}, std::false_type{});
+    else if constexpr (!kF32)
+      stationary(std::integral_constant<int, TG>{}, std::false_type{});
+  } else {
+    stationary(std::integral_constant<int, TG>{}, std::true_type{});
   }
-  stationary(std::integral_constant<int, TG>{});
 }
 
 template <typename T, int NCW, int KT>
