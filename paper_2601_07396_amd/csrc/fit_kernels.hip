@@ -1494,7 +1494,7 @@ struct GramScratch { double* p; int64_t doubles; };
 void gram(const float* A, double* G, GramScratch sc, int B, int rows, int l, hipStream_t st) {
   const int ntile = (l + 63) / 64, tiles = ntile * (ntile + 1) / 2;
   const int64_t ll = (int64_t)l * l;
-  int64_t want = std::max<int64_t>(1, (l <= 64 ? 768 : 512) / ((int64_t)tiles * B));
+  int64_t want = std::max<int64_t>(1, (l <= 64 ? 3 : 2) * num_compute_units() / ((int64_t)tiles * B));
   want = std::min<int64_t>(want, std::max<int64_t>(kGramSlices, sc.doubles / (ll * B)));
   int rows_per_slice = (int)(((rows + want - 1) / want + 15) / 16 * 16);
   if (rows_per_slice < 64) rows_per_slice = 64;

@@ -705,7 +705,7 @@ void project_launch(const svdc_shape& s, int l, const void* F, const void* Qp, f
   const T* f = (const T*)F;
   const uint16_t* q = (const uint16_t*)Qp;
   if (kF32) split = true;
-  constexpr int64_t kUnits = 256;
+  const int64_t units = num_compute_units();
   // with_split: whether split operands can come this way (their kernels are not built otherwise)
   auto stationary = [&](auto tg, auto with_split) {
     constexpr int G = decltype(tg)::value;
@@ -733,7 +733,7 @@ void project_launch(const svdc_shape& s, int l, const void* F, const void* Qp, f
   // 4608 x 3072, sketch 64: 11.9 us with plain operands (17.7 with four tiles), 24.3 us with split ones (67 with
   // the rows split over the waves in groups of 12 tiles, 42 in groups of 4).
   if constexpr (KT <= 4) {
-    if ((int64_t)((ntile + TG - 1) / TG) * s.B <= kUnits / 2) return stationary(std::integral_constant<int, 2>{}, std::true_type{});
+    if ((int64_t)((ntile + TG - 1) / TG) * s.B <= units / 2) return stationary(std::integral_constant<int, 2>{}, std::true_type{});
   }
   // wide sketches: rows split over the waves, Q shared through LDS
   if constexpr (KT >= 4) {
@@ -753,7 +753,7 @@ void project_launch(const svdc_shape& s, int l, const void* F, const void* Qp, f
       };
       // fewer workgroups than compute units: 16 rows per wave, deeper prefetch (18432 float32 rows, sketch 128: 122 ->
       // 110 -> 99 us; 32 rows by half of the coefficient tiles per wave, which halves the LDS reads: 128 us)
-      if ((int64_t)((ntile + kWaves * RTW - 1) / (kWaves * RTW)) * s.B < kUnits) tall(std::integral_constant<int, 1>{});
+      if ((int64_t)((ntile + kWaves * RTW - 1) / (kWaves * RTW)) * s.B < units) tall(std::integral_constant<int, 1>{});
       else tall(std::integral_constant<int, RTW>{});
       return;
     }
@@ -799,10 +799,7 @@ __global__ void clear_f32_kernel(float* p, int64_t n) {
 // workgroup per compute unit, otherwise just enough groups to reach that.
 template <int NCW>
 void backproject_groups(const svdc_shape& s, int* gpb, int* rows) {
-  int dev = 0, cus = 256;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-    cus = 256;
+  const int cus = num_compute_units();
   const int64_t slabs = (int64_t)(s.D / (128 * NCW)) * s.B;
   int g = (int)((cus + slabs / 2) / slabs);
   if (g < 1) g = 1;

@@ -42,13 +42,6 @@ __device__ __forceinline__ void load_to_lds16(const void* gsrc_lane, void* lds_w
   __builtin_amdgcn_global_load_lds(gsrc_lane, lds_wave_base, 16, 0, 0);
 }
 
-int num_compute_units() {
-  int dev = 0, n = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 256;
-  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 256;
-  return n;
-}
-
 // rank padded to 32, 64 or 128 (one reconstruction MFMA contracts 32 coefficients)
 __host__ __device__ inline int padded_rank(int k) { return k <= 32 ? 32 : (k <= 64 ? 64 : 128); }
 

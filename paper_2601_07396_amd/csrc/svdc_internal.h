@@ -8,6 +8,15 @@
 
 namespace svdc {
 
+// Compute units of the current device (a partition of a card has fewer than the 256 of a whole one); every rule of a launch
+// that depends on how much of the machine a grid fills asks for it.
+inline int num_compute_units() {
+  int dev = 0, n = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 256;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 256;
+  return n;
+}
+
 inline int32_t launch_status() { return hipGetLastError() == hipSuccess ? SVDC_OK : SVDC_E_HIP; }
 
 // Coefficient states of a forecaster that is linear in them: C_hat = sum_{i < m} w[i] * s[i] (device pointers,
