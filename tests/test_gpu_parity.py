@@ -413,6 +413,62 @@ def test_wide_float32_slabs_and_full_height_smoothing_tiles(dtype, B, N, D, k, p
         assert float(torch.as_strided(Fh, (B, N, pad), Fh.stride(), D).abs().max()) == 0.0
 
 
+@pytest.mark.parametrize("dtype,B,N,D,k,pad", [(torch.float32, 1, 16391, 1536, 100, 0), (torch.float32, 3, 4099, 2048, 128, 4)])
+def test_wide_float32_slabs_below_3072_channels(dtype, B, N, D, k, pad):
+    """The four-chunk slabs at rank 65..128 for widths that have a packed basis and are not the largest."""
+    assert pkg.svdcache_has_mfma_path(pkg.make_shape(torch.empty(1, 1024, D, dtype=dtype, device="meta"), k))
+    test_wide_float32_slabs_and_full_height_smoothing_tiles(dtype, B, N, D, k, pad)
+
+
+@pytest.mark.parametrize("B,N,D,k,pad", [(28, 1009, 1152, 32, 0), (19, 751, 1024, 128, 8), (28, 1009, 256, 64, 0)])
+def test_full_height_smoothing_tiles_with_single_operands(B, N, D, k, pad):
+    """SVDC_FAST smoothing full steps of the sizes that take the tallest tile; ragged last tiles, padded rows, in place."""
+    from oracle import ref_full_step_residual_ema
+    g = torch.Generator().manual_seed(N + k)
+    wide, prev = (torch.randn(N, D + pad, generator=g).to(torch.bfloat16) for _ in range(2))
+    V = torch.linalg.qr(torch.randn(D, k, generator=g, dtype=torch.float64))[0].float().contiguous()
+    S0 = torch.randn(N, k, generator=g)
+    F, R = (t.to(DEV).expand(B, -1, -1).contiguous()[:, :, :D] for t in (wide, prev))
+    Vd, S = (t.to(DEV).expand(B, -1, -1).contiguous() for t in (V, S0))
+    C = torch.empty_like(S)
+    shape = pkg.make_shape(F, k, pkg.SVDC_FAST)
+    pkg.svdcache_full_step_residual_ema(shape, F, Vd, pkg.pack_basis(shape, Vd), R, R, S, C, 0.3, 0.25, False)
+    torch.cuda.synchronize()
+    assert all(torch.equal(t[b], t[0]) for t in (R, S, C) for b in range(1, B))     # the blocks are copies of one
+    Rr, Sr, Cr = ref_full_step_residual_ema(to_np(wide[:, :D]), to_np(V), to_np(S0), to_np(prev[:, :D]), 0.3, 0.25, False, "bf16")
+    assert_close(to_np(R[0]), Rr, "bf16", "smoothed R", floor_of=to_np(wide[:, :D]), fast=True)
+    assert_close(to_np(S[0]), Sr, "bf16", "S", fast=True)
+    assert_close(to_np(C[0]), Cr, "bf16", "C", fast=True)
+
+
+@pytest.mark.parametrize("dtype,B,N,D,k,m", [(torch.bfloat16, 28, 435, 1024, 48, 2), (torch.bfloat16, 4, 1368, 5120, 64, 4),
+                                             (torch.bfloat16, 2, 6753, 1920, 128, 3), (torch.float32, 28, 1548, 1920, 96, 2)])
+def test_several_states_in_calls_that_fill_the_machine(dtype, B, N, D, k, m):
+    """Slabs of one to three chunks are the widest for several states above rank 32: six to sixteen row tiles per workgroup,
+    ragged last tiles and groups, with the added tensor and in its place."""
+    from oracle import ref_forecast_combine
+    store = "f32" if dtype == torch.float32 else "bf16"
+    g = torch.Generator().manual_seed(N + k)
+    R, X = (torch.randn(N, D, generator=g).to(dtype) for _ in range(2))
+    V = torch.linalg.qr(torch.randn(D, k, generator=g, dtype=torch.float64))[0].float().contiguous()
+    states = [torch.randn(N, k, generator=g) for _ in range(m)]
+    w = [1.5, -0.75, 0.5, -0.25][:m]
+    Rd, Xd, Vd, *Sd = (t.to(DEV).expand(B, -1, -1).contiguous() for t in (R, X, V, *states))
+    shape = pkg.make_shape(Rd, k)
+    packed = pkg.pack_basis(shape, Vd)
+    Out = torch.empty_like(Rd)
+    pkg.svdcache_forecast_combine(shape, Sd, w, Vd, packed, Rd, None, Out)
+    pkg.svdcache_forecast_combine(shape, Sd, w, Vd, packed, Rd, Xd, Xd)
+    torch.cuda.synchronize()
+    assert all(torch.equal(t[b], t[0]) for t in (Out, Xd) for b in range(1, B))     # the blocks are copies of one
+    rows = torch.tensor([0, 1, 15, 16, 95, 96, N // 2, N - 97, N - 17, N - 2, N - 1])
+    Rn, Vn, Xn = to_np(R[rows]), to_np(V), to_np(X[rows])
+    Sn = [to_np(t[rows]) for t in states]
+    for got, added, what in ((Out, None, "without"), (Xd, Xn, "with the added tensor")):
+        want = ref_forecast_combine(Sn, w, Vn, Rn, added, store)
+        assert_close(to_np(got[0].cpu()[rows]), want, store, what, scale_of=Rn, ulp_of=Rn)
+
+
 @pytest.mark.parametrize("k", [32, 64, 128])
 def test_mfma_inplace_and_strided(k):
     """In-place residual (R aliases F), padded row stride, no coefficient output."""
