@@ -125,8 +125,10 @@ __global__ __launch_bounds__(256) void rebase_state_kernel(const float* __restri
 // Fig. 1(b): cosine similarity times magnitude similarity for every pair of basis directions and for the two
 // singular-value vectors, float64 sums.  A workgroup takes 16 columns of both bases: 16 neighbouring threads read 64
 // consecutive bytes of a row, the 64 groups of 16 threads take every 64th row.  (One wave per column read 4 bytes of
-// every row: 89 us at 3072 channels, rank 32, one block, 150 us for 57, against 7.3 and 18 us.)
-constexpr int kSimThreads = 1024;
+// every row: 89 us at 3072 channels, rank 32, one block, 150 us for 57, against 7.3 and 18 us.)  kSimThreads: 1024, or 256
+// where several workgroups share a compute unit and a thread still has no more than 32 rows (300 blocks of 320 x 1:
+// 4.8 -> 4.3 us; 300 of 192 x 4: 4.5 -> 4.0 us).
+template <int kSimThreads>
 __global__ __launch_bounds__(kSimThreads) void basis_similarity_kernel(const float* __restrict__ Va,
                                                                        const float* __restrict__ sa,
                                                                        const float* __restrict__ Vb,
@@ -218,8 +220,12 @@ int32_t launch_rebase_state(const svdc_shape& s, const float* M, const float* S_
 
 int32_t launch_basis_similarity(const svdc_shape& s, const float* V_a, const float* sigma_a, const float* V_b,
                                 const float* sigma_b, float* sim_dir, float* sim_sigma, hipStream_t st) {
-  basis_similarity_kernel<<<dim3((s.k + 15) / 16, s.B), kSimThreads, 0, st>>>(V_a, sigma_a, V_b, sigma_b, sim_dir,
-                                                                              sim_sigma, s.D, s.k);
+  const dim3 grid((s.k + 15) / 16, s.B);
+  auto launch = [&](auto kernel, int threads) {
+    kernel<<<grid, threads, 0, st>>>(V_a, sigma_a, V_b, sigma_b, sim_dir, sim_sigma, s.D, s.k);
+  };
+  if (s.D <= 512 && (int64_t)grid.x * s.B >= num_compute_units()) launch(basis_similarity_kernel<256>, 256);
+  else launch(basis_similarity_kernel<1024>, 1024);
   return launch_status();
 }
 

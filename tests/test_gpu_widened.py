@@ -376,6 +376,23 @@ def test_basis_kernels_at_the_edges_of_their_tiles(B, N, D, k):
             assert_close(to_np(out[b]), ref_rebase_state(to_np(S[b]), to_np(M[b]), "f32"), "f32", f"block {b}")
 
 
+@pytest.mark.parametrize("B,D,k", [(300, 320, 1), (257, 12, 4), (150, 512, 20)])
+def test_basis_similarity_of_many_short_bases(B, D, k):
+    """Enough workgroups for every compute unit and at most 512 channels: 256 threads each."""
+    from oracle import ref_basis_similarity
+    g = torch.Generator().manual_seed(B + D)
+    Va, Vb = (torch.randn(B, D, k, generator=g) for _ in range(2))
+    Va = (Vb + 0.5 * Va).contiguous()
+    sa, sb = (torch.rand(B, k, generator=g) + 0.1 for _ in range(2))
+    shape = pkg.make_shape(torch.empty(B, max(k, 16), D), k)
+    sd, ss = torch.empty(B, k, device=DEV), torch.empty(B, device=DEV)
+    pkg.svdcache_basis_similarity(shape, Va.to(DEV), sa.to(DEV), Vb.to(DEV), sb.to(DEV), sd, ss)
+    torch.cuda.synchronize()
+    for b in (0, 1, B // 2, B - 1):
+        rd, rs = ref_basis_similarity(to_np(Va[b]), to_np(sa[b]), to_np(Vb[b]), to_np(sb[b]))
+        assert np.abs(to_np(sd[b]) - rd).max() <= 1e-6 and abs(float(ss[b]) - rs) <= 1e-6
+
+
 def test_rebase_rejects_ranks_beyond_its_limit():
     shape = pkg.make_shape(torch.empty(1, 200, 256), 160)
     t = torch.empty(1, 256, 160, device=DEV)
