@@ -973,7 +973,11 @@ constexpr int kJacobiThreads = 512;
 // The ANGLE only steers convergence, so tan(theta) = sign(z) / (|z| + sqrt(1 + z^2)) comes from the float32 reciprocal and
 // square root of the hardware (each good to an ulp; the exact division and square root were a third of the dependent
 // chain of a rotation).  cos and sin belong to exactly that tangent in float64: 1 / sqrt(1 + t^2) from the float32
-// estimate (1e-7) and one step of third order.
+// estimate (1e-7) and one step of third order.  jacobi_wave_kernel hands over norms that followed the rotations since their
+// columns were loaded (al - t ga, be + t ga) and not sums over the elements.  For columns that are nearly parallel the error of
+// t, some 3e-7 of be, can exceed the norm that is left or make it negative; the test below then rotates a pair that needs no
+// rotation, or by a wrong angle.  That costs rotations and no accuracy: the rotation is orthogonal whatever its angle, such
+// a pair sets *big, so that another sweep follows, and the norms are summed anew at every load and again for sigma.
 __device__ __forceinline__ bool jacobi_angle(double al, double be, double ga, double* tt, double* cs, double* sn, int* big) {
   const double g2 = ga * ga, ab = al * be;
   if (!(g2 > 1e-14 * ab)) return false;
@@ -1096,8 +1100,8 @@ __device__ __forceinline__ void jacobi_output(const double* A, int la, int l, in
 // barriers instead of 63 -- with a trip per rotation the LDS reads, writes and the barrier were half of a round at 64
 // columns and the LDS bandwidth bound 128 columns.  The squared norms are formed once per trip and follow the rotations
 // (al - t ga, be + t ga), so that a rotation sums one inner product over the lanes.
-// Measured: 174 us at 64 columns and 771 us at 128, against 273 and 1212 us with 16 lanes per pair, every
-// rotation from and to LDS.
+// Measured inside the fit of one block of 4608 x 3072 bf16, rank 32: 154 us (64 columns); of 18432 x 3072 float32, rank 64:
+// 743 us (128 columns); against 254 and 1106 us with 16 lanes per pair, every rotation from and to LDS.
 template <int NE>
 __global__ __launch_bounds__(512) void jacobi_wave_kernel(const double* __restrict__ Lfac, double* Wout, float* sigma, int l,
                                                           int k, const double* fro_acc, float* fro2, int max_sweeps,
@@ -1169,11 +1173,14 @@ __global__ __launch_bounds__(512) void jacobi_wave_kernel(const double* __restri
   using I1 = std::integral_constant<int, 1>;
   using I2 = std::integral_constant<int, 2>;
   using I4 = std::integral_constant<int, 4>;
-  // every pair of the block's first n columns (the others are zero)
+  // Every pair of the block's first n columns; the others are zero.  Up to 16 columns (NE = 2) that is looked at, since most
+  // of a block may be zeros there (3 columns: 15.6 -> 6.9 us); beyond, the branches cost more than they save (64: 157 us, 154
+  // without them).
+  constexpr bool kFull = NE > 2;
   auto rotate_all_inside = [&](int n, double (&xv)[NE], double& nv) {
-    if (n > 1) rotate_inside(I1{}, xv, nv);
-    if (n > 2) { rotate_inside(I2{}, xv, nv); rotate_inside(std::integral_constant<int, 3>{}, xv, nv); }
-    if (n > 4) {
+    if (kFull || n > 1) rotate_inside(I1{}, xv, nv);
+    if (kFull || n > 2) { rotate_inside(I2{}, xv, nv); rotate_inside(std::integral_constant<int, 3>{}, xv, nv); }
+    if (kFull || n > 4) {
       rotate_inside(I4{}, xv, nv);
       rotate_inside(std::integral_constant<int, 5>{}, xv, nv);
       rotate_inside(std::integral_constant<int, 6>{}, xv, nv);
@@ -1200,7 +1207,7 @@ __global__ __launch_bounds__(512) void jacobi_wave_kernel(const double* __restri
         rotate_all_inside(l - 8 * rr.p, xs, nx);
         rotate_all_inside(l - 8 * rr.q, ys, ny);
       }
-      if (8 * rr.p < l && 8 * rr.q < l) {   // both blocks have columns (l is the same for the whole wave)
+      if (kFull || (8 * rr.p < l && 8 * rr.q < l)) {   // both blocks have columns (l is the same for the whole wave)
         rotate(); move_y(I1{});   // rows of y now hold column g ^ 1
         rotate(); move_y(I2{});   // 3
         rotate(); move_y(I1{});   // 2
@@ -1595,7 +1602,7 @@ int32_t run_fit_typed(const svdc_shape& s, const FitPlan& pl, const T* F, float*
   void* Qp = ws + pl.off_Qp;
   const PackedQ pq = pl.mfma ? fit_mfma_packed_q(s, l, Qp) : PackedQ{};
   bool packed = false;                       // Q is in its packed form already
-  // bf16 features with several row groups accumulate Z with atomics: it has to be clear beforehand
+  // several row groups accumulate Z with atomics: it has to be clear beforehand
   const bool zero_z = pl.mfma && fit_mfma_backproject_accumulates(s, l);
   bool z_clear = false;
   // With power iterations the Gaussian test matrix (D x l) is used as it is: its columns are well conditioned
