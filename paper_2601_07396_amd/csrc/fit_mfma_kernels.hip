@@ -8,7 +8,7 @@
 // 32-row tiles, on v_mfma_f32_16x16x32_bf16 (operand layouts: see mfma_kernels.hip).  A projection that is followed by a back-projection hands Y over as
 // packed bf16 operand words (pack_y_word) instead of float32 rows; the last projection of a fit writes float32 rows
 // for the Gram matrix.  backproject stores Z directly when one workgroup covers all rows of a block and otherwise
-// combines the partial results of its row groups with float atomics (it clears Z itself).
+// combines the partial results of its row groups with float atomics (into a Z that its caller cleared, or that it clears itself).
 #include <type_traits>
 
 #include "svdc_device.h"
@@ -855,8 +855,9 @@ constexpr int width_for_f32() { return KT <= 2 ? 6 : (KT == 4 ? 3 : 2); }
 // Small batches: narrower slabs give more workgroups without more row groups, whose partial sums meet in float
 // atomics (one per element and row group): the widest slab that still gives 64 slabs over all blocks, if any.
 // Measured at 4608 x 3072, width 64: 42 -> 15 us for one block, 55 -> 36 us for 4, 72 -> 53 us for 8; from 28
-// blocks on the widest slab is the fastest again.  Not for float32 features, whose back-projection reads and
-// splits Y as float32 rows once per slab (18432 x 3072, one block: 3.7 -> 4.7 ms per fit at width 128 when tried).
+// blocks on the widest slab is the fastest again.  Not for float32 features: their slabs are narrow already (2 chunks at
+// width 128, 3 at 64), and every further slab loads the two-part words of Y again (one block of 18432 x 3072, width 128,
+// slabs of one chunk: 74 -> 100 us; 4 of 4608, width 64: 54 -> 61 us).
 template <typename T, int KT>
 constexpr int backproject_cap() { return std::is_same<T, float>::value ? width_for_f32<KT>() : width_for<KT>(); }
 template <typename T, int KT>
@@ -996,7 +997,7 @@ bool fit_mfma_backproject_accumulates(const svdc_shape& s, int l) {
         backproject_groups<decltype(ncw)::value>(s, &gpb, &rows);
         any = any || gpb > 1;
       };
-      // the power iterations hand bf16 features' Y over in packed form
+      // the power iterations hand bf16 features' Y over in packed form; the width for float32 features does not depend on it
       if (s.dtype == SVDC_F32) backproject_by_width<float, KT>(s, false, groups);
       else backproject_by_width<bf16_t, KT>(s, true, groups);
     });

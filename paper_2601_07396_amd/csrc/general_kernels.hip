@@ -7,7 +7,9 @@
 // results D[m = 4 g + i][n = r].  The contraction index is permuted so that loads are wide: a lane loads eight
 // consecutive channels 32 c + 8 g + e of its token row, and step e of eight contracts the channels {32 c + 8 g + e}.
 //
-// What bounds them: the matrix pipe (256 flop per clock and compute unit; 40-45 % of its rate is reached) behind the
+// What bounds them: the matrix pipe (256 flop per clock and compute unit; busy 44 % of a unit's time in the cached step and
+// 48 % in the full step below by its counter, which at rank 50, padded to 64, and with the units that wait for the last
+// ones is 30 % of the rate over the whole launch) behind the
 // latency of V, which has no packed form here and comes from L2 as it is.  A workgroup holds 16 token rows, so V is
 // read once per 16 rows and not once per row, and the operands of the next 32 channels are requested before the current
 // ones are multiplied.  Measured at 4 x 2173 x 1408 bf16, rank 50: full step 904 -> 67 us, cached step 290 -> 33 us; at

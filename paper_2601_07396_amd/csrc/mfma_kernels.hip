@@ -753,8 +753,9 @@ constexpr int ring_depth(int CH, int W, int KT2) {
   const int rt = tile_rows(CH, W, KT2);
   int rd = KT2 == 1 ? 12 : (KT2 == 2 ? 16 : 8);   // measured best at 3072 channels
   if (CH == 24 && W == 1) return rd;
-  // float32 features at rank 128: the estimate is about 100 registers too high (370 used at 3072 channels and a depth of
-  // 4), and the basis stream is what bounds those 16-row tiles: 18432 x 3072, depth 4 -> 8: 297 -> 234 us
+  // float32 features at rank 65..128 and 3072 channels (the only width that this changes: the others have the same depth with
+  // 478): the estimate is about 100 registers too high (370 used at a depth of 4, 511 at 8, all 512 in the variant that
+  // smooths the residual, none spilled to memory), and the basis stream is what bounds those 16-row tiles: 18432 rows, 297 -> 234 us
   const int limit = W == 2 && KT2 == 4 && CH <= 24 ? 568 : 478;   // 4096 channels and up spill
   while (rd > 2 && full_step_regs(CH, W, KT2, rt, rd) > limit) rd -= 2;
   return rd;
