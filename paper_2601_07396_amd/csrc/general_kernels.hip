@@ -12,7 +12,7 @@
 // ones is 30 % of the rate over the whole launch) behind the
 // latency of V, which has no packed form here and comes from L2 as it is.  A workgroup holds 16 token rows, so V is
 // read once per 16 rows and not once per row, and the operands of the next 32 channels are requested before the current
-// ones are multiplied.  Measured at 4 x 2173 x 1408 bf16, rank 50: full step 904 -> 67 us, cached step 290 -> 33 us; at
+// ones are multiplied.  Measured at 4 x 2173 x 1408 bf16, rank 50: full step 904 -> 68 us, cached step 290 -> 33 us; at
 // 22848 x 2136, rank 21: 1454 -> 108 and 490 -> 67 us, against one wave per token row on the vector units, which read
 // all of V for every row.  Tiles of 32 rows were no faster (half as many waves to hide the latency).
 #include <algorithm>
