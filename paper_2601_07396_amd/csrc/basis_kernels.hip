@@ -1,5 +1,7 @@
 // Basis reuse across prompts and re-basing of the coefficient state (Sec. 3.3, Fig. 1(b)).
 // All three kernels touch only the D x k bases and the N x k states, never the features.
+#include <type_traits>
+
 #include "svdc_device.h"
 #include "svdc_internal.h"
 
@@ -21,7 +23,9 @@ __device__ __forceinline__ f32x4 mfma_f32(float a, float b, const f32x4& c) {
 // are added in wave order.  One wave per row of the tile walking over all D channels through LDS, as this was done
 // before, took 201 us at 3072 channels, rank 32, one block (242 us for 57, 362 us at rank 64); this takes 9.6 us
 // (28 and 13 us).  D is a multiple of 4 (svdc_shape); columns beyond k are clamped, their results are not stored.
-constexpr int kOvWaves = 16;
+// kOvWaves: 16, or 4 where many tiles fill the machine and the contraction is short (at most 256 channels): 300 blocks of
+// 48 x 48 11.6 -> 5.9 us, of 80 x 80 33.4 -> 20.0 us (8.3 and 26.7 us by one thread per 1 x 8 elements of M).
+template <int kOvWaves>
 __global__ __launch_bounds__(64 * kOvWaves) void basis_overlap_kernel(const float* __restrict__ Vo,
                                                                       const float* __restrict__ Vn, float* M, int D,
                                                                       int k) {
@@ -123,21 +127,21 @@ __global__ __launch_bounds__(256) void rebase_state_kernel(const float* __restri
 }
 
 // Fig. 1(b): cosine similarity times magnitude similarity for every pair of basis directions and for the two
-// singular-value vectors, float64 sums.  A workgroup takes 16 columns of both bases: 16 neighbouring threads read 64
-// consecutive bytes of a row, the 64 groups of 16 threads take every 64th row.  (One wave per column read 4 bytes of
-// every row: 89 us at 3072 channels, rank 32, one block, 150 us for 57, against 7.3 and 18 us.)  kSimThreads: 1024, or 256
-// where several workgroups share a compute unit and a thread still has no more than 32 rows (300 blocks of 320 x 1:
-// 4.8 -> 4.3 us; 300 of 192 x 4: 4.5 -> 4.0 us).
-template <int kSimThreads>
+// singular-value vectors, float64 sums.  A workgroup takes C columns of both bases, 16 (or 4 or 1 for ranks that have no
+// more): neighbouring threads read consecutive floats of a row, the groups of C threads take the rows in turn.  (One wave per
+// column read 4 bytes of every row: 89 us at 3072 channels, rank 32, one block, 150 us for 57, against 7.3 and 18 us.)
+// kSimThreads: 1024, or 256 where a thread then has at most 8 rows, or 32 if many workgroups fill the machine (300 blocks of
+// 320 x 1 with 16 columns and 1024 threads 4.8 us, of 1504 x 1 8.2 us; like this 4.0 and 4.2).
+template <int kSimThreads, int C>
 __global__ __launch_bounds__(kSimThreads) void basis_similarity_kernel(const float* __restrict__ Va,
                                                                        const float* __restrict__ sa,
                                                                        const float* __restrict__ Vb,
                                                                        const float* __restrict__ sb, float* sim_dir,
                                                                        float* sim_sigma, int D, int k) {
-  constexpr int kRowGroups = kSimThreads / 16, kWaves = kSimThreads / 64;
-  __shared__ double part[kWaves][16][3];
-  const int b = blockIdx.y, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = threadIdx.x & 15;
-  const int j = blockIdx.x * 16 + c;
+  constexpr int kRowGroups = kSimThreads / C, kWaves = kSimThreads / 64;
+  __shared__ double part[kWaves][C][3];
+  const int b = blockIdx.y, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = threadIdx.x % C;
+  const int j = blockIdx.x * C + c;
   const float* va = Va + (int64_t)b * D * k + min(j, k - 1);
   const float* vb = Vb + (int64_t)b * D * k + min(j, k - 1);
   auto score = [](double dot, double na2, double nb2, bool take_abs) -> float {
@@ -148,17 +152,17 @@ __global__ __launch_bounds__(kSimThreads) void basis_similarity_kernel(const flo
   };
   double dot = 0.0, na = 0.0, nb = 0.0;
 #pragma unroll 8
-  for (int d = threadIdx.x >> 4; d < D; d += kRowGroups) {
+  for (int d = threadIdx.x / C; d < D; d += kRowGroups) {
     const double x = va[(int64_t)d * k], y = vb[(int64_t)d * k];
     dot += x * y; na += x * x; nb += y * y;
   }
 #pragma unroll
-  for (int o = 16; o < kWave; o <<= 1) {      // the four row groups of a wave
+  for (int o = C; o < kWave; o <<= 1) {       // the row groups of a wave
     dot += __shfl_xor(dot, o, kWave); na += __shfl_xor(na, o, kWave); nb += __shfl_xor(nb, o, kWave);
   }
-  if (lane < 16) { part[wave][c][0] = dot; part[wave][c][1] = na; part[wave][c][2] = nb; }
+  if (lane < C) { part[wave][c][0] = dot; part[wave][c][1] = na; part[wave][c][2] = nb; }
   __syncthreads();
-  if (threadIdx.x < 16 && j < k) {
+  if (threadIdx.x < C && j < k) {
     dot = na = nb = 0.0;
     for (int w = 0; w < kWaves; ++w) { dot += part[w][c][0]; na += part[w][c][1]; nb += part[w][c][2]; }
     sim_dir[(int64_t)b * k + j] = score(dot, na, nb, true);
@@ -180,7 +184,11 @@ bool rebase_rank_supported(int k) { return k >= 1 && k <= kMaxRank; }
 
 int32_t launch_basis_overlap(const svdc_shape& s, const float* V_old, const float* V_new, float* M, hipStream_t st) {
   const int tiles = (s.k + 15) / 16;
-  basis_overlap_kernel<<<dim3(tiles * tiles, s.B), 64 * kOvWaves, 0, st>>>(V_old, V_new, M, s.D, s.k);
+  const dim3 grid(tiles * tiles, s.B);
+  if (s.D <= 256 && (int64_t)grid.x * s.B >= num_compute_units())
+    basis_overlap_kernel<4><<<grid, 256, 0, st>>>(V_old, V_new, M, s.D, s.k);
+  else
+    basis_overlap_kernel<16><<<grid, 1024, 0, st>>>(V_old, V_new, M, s.D, s.k);
   return launch_status();
 }
 
@@ -220,12 +228,18 @@ int32_t launch_rebase_state(const svdc_shape& s, const float* M, const float* S_
 
 int32_t launch_basis_similarity(const svdc_shape& s, const float* V_a, const float* sigma_a, const float* V_b,
                                 const float* sigma_b, float* sim_dir, float* sim_sigma, hipStream_t st) {
-  const dim3 grid((s.k + 15) / 16, s.B);
-  auto launch = [&](auto kernel, int threads) {
-    kernel<<<grid, threads, 0, st>>>(V_a, sigma_a, V_b, sigma_b, sim_dir, sim_sigma, s.D, s.k);
+  auto launch = [&](auto columns) {
+    constexpr int C = decltype(columns)::value;
+    const dim3 grid((s.k + C - 1) / C, s.B);
+    const int64_t rows = ((int64_t)s.D * C + 255) / 256;       // of each of 256 threads
+    if (rows <= 8 || (rows <= 32 && (int64_t)grid.x * s.B >= num_compute_units()))
+      basis_similarity_kernel<256, C><<<grid, 256, 0, st>>>(V_a, sigma_a, V_b, sigma_b, sim_dir, sim_sigma, s.D, s.k);
+    else
+      basis_similarity_kernel<1024, C><<<grid, 1024, 0, st>>>(V_a, sigma_a, V_b, sigma_b, sim_dir, sim_sigma, s.D, s.k);
   };
-  if (s.D <= 512 && (int64_t)grid.x * s.B >= num_compute_units()) launch(basis_similarity_kernel<256>, 256);
-  else launch(basis_similarity_kernel<1024>, 1024);
+  if (s.k == 1) launch(std::integral_constant<int, 1>{});
+  else if (s.k <= 4) launch(std::integral_constant<int, 4>{});
+  else launch(std::integral_constant<int, 16>{});
   return launch_status();
 }
 

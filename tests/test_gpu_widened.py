@@ -376,9 +376,10 @@ def test_basis_kernels_at_the_edges_of_their_tiles(B, N, D, k):
             assert_close(to_np(out[b]), ref_rebase_state(to_np(S[b]), to_np(M[b]), "f32"), "f32", f"block {b}")
 
 
-@pytest.mark.parametrize("B,D,k", [(300, 320, 1), (257, 12, 4), (150, 512, 20)])
-def test_basis_similarity_of_many_short_bases(B, D, k):
-    """Enough workgroups for every compute unit and at most 512 channels: 256 threads each."""
+@pytest.mark.parametrize("B,D,k", [(300, 320, 1), (257, 12, 4), (150, 512, 20), (1, 4096, 1), (2, 8, 1), (3, 1028, 3), (1, 136, 30)])
+def test_basis_similarity_by_columns_and_threads(B, D, k):
+    """One, four or sixteen columns per workgroup of 256 or 1024 threads: many short bases, one long one, a remainder of
+    columns."""
     from oracle import ref_basis_similarity
     g = torch.Generator().manual_seed(B + D)
     Va, Vb = (torch.randn(B, D, k, generator=g) for _ in range(2))
@@ -388,9 +389,23 @@ def test_basis_similarity_of_many_short_bases(B, D, k):
     sd, ss = torch.empty(B, k, device=DEV), torch.empty(B, device=DEV)
     pkg.svdcache_basis_similarity(shape, Va.to(DEV), sa.to(DEV), Vb.to(DEV), sb.to(DEV), sd, ss)
     torch.cuda.synchronize()
-    for b in (0, 1, B // 2, B - 1):
+    for b in {0, B // 2, B - 1}:
         rd, rs = ref_basis_similarity(to_np(Va[b]), to_np(sa[b]), to_np(Vb[b]), to_np(sb[b]))
         assert np.abs(to_np(sd[b]) - rd).max() <= 1e-6 and abs(float(ss[b]) - rs) <= 1e-6
+
+
+@pytest.mark.parametrize("B,D,k", [(300, 48, 48), (130, 256, 17), (257, 12, 12)])
+def test_basis_overlap_of_many_short_bases(B, D, k):
+    """At most 256 channels and a tile for every compute unit: four waves per tile."""
+    from oracle import ref_basis_overlap
+    g = torch.Generator().manual_seed(B + D)
+    Va, Vb = (torch.randn(B, D, k, generator=g) / D ** 0.5 for _ in range(2))
+    shape = pkg.make_shape(torch.empty(B, max(k, 16), D), k)
+    M = torch.empty(B, k, k, device=DEV)
+    pkg.svdcache_basis_overlap(shape, Va.to(DEV), Vb.to(DEV), M)
+    torch.cuda.synchronize()
+    for b in (0, 1, B // 2, B - 1):
+        assert np.abs(to_np(M[b]) - ref_basis_overlap(to_np(Va[b]), to_np(Vb[b]))).max() <= 5e-6   # sums of D terms of size 1 / D
 
 
 def test_rebase_rejects_ranks_beyond_its_limit():
