@@ -364,10 +364,14 @@ int32_t forecast_general_typed(const svdc_shape& s, const CoefStates& cs, const 
     const size_t lds = (size_t)16 * coef_stride(s.k) * sizeof(float);
     if (allow_lds(kernel, lds) != SVDC_OK) return SVDC_E_HIP;
     const int64_t tiles = (s.N + 15) / 16;
-    // shares of the channels: until there are about four workgroups per compute unit, at least two chunks per wave
-    const int nchunk = (s.D + 31) / 32;
-    const int64_t want = (4 * (int64_t)num_compute_units() + tiles * s.B - 1) / (tiles * s.B);
-    const int shares = (int)std::max<int64_t>(1, std::min<int64_t>(want, nchunk / (2 * kCachedWaves)));
+    // shares of the channels: until there are about four workgroups per compute unit, at least two chunks per wave (few
+    // channels have one share only, whatever the device: its query is a fiftieth of the smallest calls)
+    const int most = (s.D + 31) / 32 / (2 * kCachedWaves);
+    int shares = 1;
+    if (most > 1) {
+      const int64_t want = (4 * (int64_t)num_compute_units() + tiles * s.B - 1) / (tiles * s.B);
+      shares = (int)std::max<int64_t>(1, std::min<int64_t>(want, most));
+    }
     kernel<<<dim3((unsigned)tiles, s.B, shares), 64 * kCachedWaves, lds, st>>>(cs, V, (const T*)R, (const T*)X, (T*)Out,
                                                                                s.N, s.D, s.k, s.ldf, s.block_stride);
     return launch_status();
