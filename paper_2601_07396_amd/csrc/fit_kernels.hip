@@ -18,6 +18,7 @@
 
 #include <type_traits>
 
+#include "chol_kernels.h"
 #include "svdc_device.h"
 #include "svdc_internal.h"
 
@@ -147,7 +148,6 @@ __global__ __launch_bounds__(256) void fit_gemm_kernel(const T* __restrict__ F, 
 // so a lane reads As[4 k4 + lane / 16][i0 + lane % 16]: 16 consecutive doubles per group of 16 lanes, and with a row
 // stride of 80 doubles the two groups of a half wave fall into different halves of the LDS banks.
 // ---------------------------------------------------------------------------
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int kM64Stride = 80;
 
 struct Quadrant {
@@ -313,303 +313,6 @@ __global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restri
   if (q == 0 && in) G[(int64_t)b * ll + e] = (s + share[0][lane]) + (share[1][lane] + share[2][lane]);
 }
 
-// A pivot of the Cholesky factorisation below kRankTol x the largest diagonal entry of the Gram matrix means that a
-// column of the sketch depends on the others to within (1e-6)^2, the round-off of the float32 sketch itself: the
-// matrix has numerical rank < l.  The shift keeps the factorisation going (the result stays orthonormal, directions
-// beyond the numerical rank are arbitrary) and the block's status word reports it.
-constexpr double kRankTol = 1e-12;
-
-// ---------------------------------------------------------------------------
-// Cholesky factor of a diagonal block of at most 64 columns, and its inverse, by one workgroup:
-//   A = G[c0 .. c0 + w, same] + shift I - sum_{c < c0} L[., c] L[., c]^T  =  L L^T,       Minv = L^-T
-// (the finished columns of its rows come transposed from the upper triangle of G: G[c][r] = L[r][c]).
-// Thread (ti, tj) of a 16 x 16 grid owns the 4 x 4 block (ti, tj) in registers.  The factorisation is right-looking by
-// panels of 4 columns, two barriers per panel: the thread on the diagonal factors its 4 x 4 block, the threads below it
-// solve theirs and publish the panel, every thread to the right subtracts a rank-4 product.  What bounds it is the chain
-// of dependent float64 operations on the diagonal, so the factor is kept as L' D L'^T with unit diagonal: a column then
-// costs a reciprocal (estimate and two Newton steps, two operations each) instead of a reciprocal square root, and the
-// square roots are taken side by side at the end.  The unit triangle is inverted without divisions: 4 x 4 blocks on the
-// way, then pairs of blocks of 4, 8, 16 and 32, U_21 = -U_22 (L'_21 U_11), from 16 on as matrix instructions.
-// L = L' D^(1/2), L^-1 = D^(-1/2) U.  Measured at 64 columns: 22 us with the inverse, against 18.6 us for the factor
-// alone with a square root per column and 26 us (57 us for 57 blocks of 3072 rows) for the substitution that the inverse
-// replaces in apply_factor_kernel.
-//   H = 64, or 16 for l <= 16, which one wave does without waiting for others: 3.8 us for 6 columns against 6.1 us with
-//          H = 64.  In either the panels and the levels of the inverse stop at w (22 us if they do not).
-//   w <= H; columns from w on are padded with the identity.  Lower triangle of the block of G = L, upper part zeroed.
-//   Minv   out  (want_inv) row-major [w x w] at row stride ldm, block b at Minv + b * m_bstride
-//   slot   the shift: computed from the diag_n diagonal entries of G and stored when c0 = 0, read otherwise (nullable when
-//          there is one block only)
-// ---------------------------------------------------------------------------
-constexpr int kCholBlock = 64;
-
-template <int H>
-__global__ __launch_bounds__(H == 64 ? 256 : 64) void chol_inv_kernel(double* G, int l, int c0, int w, double* Minv,
-                                                                      int64_t m_bstride, int ldm, int want_inv, double* slot,
-                                                                      int64_t slot_bstride, double rel_shift, int32_t* info) {
-  static_assert(H == 64 || H == 16, "a 16 x 16 or 4 x 4 grid of threads with 4 x 4 elements each");
-  constexpr int LD = H + 1, NG = H / 4, NT = H == 64 ? 256 : 64;
-  __shared__ double Lp[H * LD];        // L' (strictly lower 4 x 4 blocks); first the staging area of the update
-  __shared__ double U[H * LD];         // L'^-1; first the update itself
-  __shared__ double Tm[H == 64 ? 32 * 33 : 64];   // L'_21 U_11
-  __shared__ __align__(16) double py[4][H];   // panel: columns of L' D, rows contiguous
-  __shared__ double dl[2][6], dr[2][4];   // strict lower part and reciprocal pivots of the diagonal block, by panel parity
-  __shared__ double dv[H], sq[H], rs[H];  // pivots, their square roots and reciprocal square roots
-  __shared__ double s_shift;
-  const int b = blockIdx.x, t = threadIdx.x, tj = t / NG, ti = t % NG;
-  const bool own = t < NG * NG;
-  double* g = G + (int64_t)b * l * l;
-  double* gd = g + (int64_t)c0 * l + c0;
-  double a[4][4];
-#pragma unroll
-  for (int ii = 0; ii < 4; ++ii)
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) a[ii][jj] = gd[(int64_t)min(4 * ti + ii, w - 1) * l + min(4 * tj + jj, w - 1)];
-  if (t < kWave) {
-    if (c0 == 0) {
-      double mx = 0.0;
-      for (int i = t; i < l; i += kWave) mx = fmax(mx, g[(int64_t)i * l + i]);
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, kWave));
-      if (t == 0) {
-        s_shift = mx * rel_shift;
-        if (slot) slot[(int64_t)b * slot_bstride] = mx * rel_shift;
-      }
-    } else if (t == 0) {
-      s_shift = slot[(int64_t)b * slot_bstride];
-    }
-  }
-  if (H == 64 && c0 > 0) {   // sum_c L[i][c] L[j][c], 16 columns c per step, c0 a multiple of 64
-    const Quadrant q;
-    f64x4 acc[2][2];
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-      for (int y = 0; y < 2; ++y) acc[x][y] = f64x4{0.0, 0.0, 0.0, 0.0};
-    const int kr = t >> 4, col = 4 * (t & 15);
-    double v[4];
-    auto fetch = [&](int k0) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = g[(int64_t)(k0 + kr) * l + c0 + min(col + e, w - 1)];   // beyond w: not used
-    };
-    static_assert(H != 64 || 16 * kM64Stride <= H * LD, "staging fits");
-    fetch(0);
-    for (int k0 = 0; k0 < c0; k0 += 16) {
-      if (k0 > 0) __syncthreads();
-#pragma unroll
-      for (int e = 0; e < 4; ++e) Lp[kr * kM64Stride + col + e] = v[e];
-      __syncthreads();
-      if (k0 + 16 < c0) fetch(k0 + 16);
-      mfma64_accumulate<4>(Lp, Lp, q, acc);
-    }
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-      for (int y = 0; y < 2; ++y)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) U[q.row(x, e) * LD + q.col(y)] = acc[x][y][e];
-    __syncthreads();
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii)
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) a[ii][jj] -= U[(4 * ti + ii) * LD + 4 * tj + jj];
-  }
-  __syncthreads();
-  const double shift = s_shift;
-#pragma unroll
-  for (int ii = 0; ii < 4; ++ii)
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-      const int i = 4 * ti + ii, j = 4 * tj + jj;
-      if (i >= w || j >= w) a[ii][jj] = i == j ? 1.0 : 0.0;   // identity padding
-      else if (i == j) a[ii][jj] += shift;
-    }
-
-  const double pivot_floor = shift * (kRankTol / rel_shift);
-  bool dependent = false;
-  if (t < H && t >= (w + 3) / 4 * 4) dv[t] = 1.0;   // pivots of the panels that are identity throughout
-  for (int cb = 0; 4 * cb < w; ++cb) {
-    const int par = cb & 1;
-    if (own && ti == cb && tj == cb) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        dependent |= (4 * cb + q < w) && a[q][q] < pivot_floor;
-        const double d = fmax(a[q][q], 1e-300);
-        double y[4], yy[4][4];
-#pragma unroll
-        for (int i = q + 1; i < 4; ++i) {
-          y[i] = a[i][q];
-#pragma unroll
-          for (int j = q + 1; j <= i; ++j) yy[i][j] = y[i] * a[j][q];
-        }
-        // 1 / d: the hardware's estimate (about 2^-23) and one step of third order
-        double x = __builtin_amdgcn_rcp(d);
-        const double e1 = fma(-d, x, 1.0);
-        x = fma(x, fma(e1, e1, e1), x);
-        dv[4 * cb + q] = d;
-        dr[par][q] = x;
-#pragma unroll
-        for (int j = q + 1; j < 4; ++j)
-#pragma unroll
-          for (int i = j; i < 4; ++i) a[i][j] = fma(-yy[i][j], x, a[i][j]);
-#pragma unroll
-        for (int i = q + 1; i < 4; ++i) a[i][q] = y[i] * x;
-      }
-      dl[par][0] = a[1][0]; dl[par][1] = a[2][0]; dl[par][2] = a[2][1];
-      dl[par][3] = a[3][0]; dl[par][4] = a[3][1]; dl[par][5] = a[3][2];
-    }
-    __syncthreads();
-    if (own && tj == cb && ti > cb) {    // rows of L' D: Y = B L'_d^-T, published; and of L', kept
-      const double l10 = dl[par][0], l20 = dl[par][1], l21 = dl[par][2], l30 = dl[par][3], l31 = dl[par][4], l32 = dl[par][5];
-      double y[4][4];
-#pragma unroll
-      for (int ii = 0; ii < 4; ++ii) {
-        y[0][ii] = a[ii][0];
-        y[1][ii] = a[ii][1] - y[0][ii] * l10;
-        y[2][ii] = a[ii][2] - y[0][ii] * l20 - y[1][ii] * l21;
-        y[3][ii] = a[ii][3] - y[0][ii] * l30 - y[1][ii] * l31 - y[2][ii] * l32;
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int ii = 0; ii < 4; ii += 2)
-          *reinterpret_cast<double2*>(&py[q][4 * ti + ii]) = make_double2(y[q][ii], y[q][ii + 1]);
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii) a[ii][q] = y[q][ii] * dr[par][q];
-    }
-    __syncthreads();
-    if (own && tj > cb && ti >= tj) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const double r = dr[par][q];
-        double x[4], y[4];
-#pragma unroll
-        for (int ii = 0; ii < 4; ii += 2) {
-          const double2 xv = *reinterpret_cast<const double2*>(&py[q][4 * ti + ii]);
-          const double2 yv = *reinterpret_cast<const double2*>(&py[q][4 * tj + ii]);
-          x[ii] = xv.x; x[ii + 1] = xv.y;
-          y[ii] = yv.x * r; y[ii + 1] = yv.y * r;
-        }
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-          for (int ii = 0; ii < 4; ++ii) a[ii][jj] -= x[ii] * y[jj];
-      }
-    }
-  }
-  // every thread on the diagonal has seen the pivots of its own block
-  if (info && dependent) atomicOr(info + b, SVDC_FIT_RANK_DEFICIENT);
-  if (t < H) {
-    const double d = dv[t];
-    double r = __builtin_amdgcn_rsq(d);
-    r = r * (1.5 - 0.5 * d * r * r);
-    r = r * (1.5 - 0.5 * d * r * r);
-    rs[t] = r;
-    sq[t] = d * r;
-  }
-  // L' to LDS; the diagonal 4 x 4 blocks and their inverses, zeros above
-  if (own && ti == tj) {
-    const double u10 = -a[1][0], u21 = -a[2][1], u32 = -a[3][2];
-    const double u20 = -(a[2][0] + a[2][1] * u10), u31 = -(a[3][1] + a[3][2] * u21);
-    const double u30 = -(a[3][0] + a[3][1] * u10 + a[3][2] * u20);
-    const double u[4][4] = {{1.0, 0.0, 0.0, 0.0}, {u10, 1.0, 0.0, 0.0}, {u20, u21, 1.0, 0.0}, {u30, u31, u32, 1.0}};
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii)
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        U[(4 * ti + ii) * LD + 4 * tj + jj] = u[ii][jj];
-        Lp[(4 * ti + ii) * LD + 4 * tj + jj] = jj < ii ? a[ii][jj] : (ii == jj ? 1.0 : 0.0);
-      }
-  } else if (own) {
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii)
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        if (ti > tj) Lp[(4 * ti + ii) * LD + 4 * tj + jj] = a[ii][jj];
-        else U[(4 * ti + ii) * LD + 4 * tj + jj] = 0.0;
-      }
-  }
-  __syncthreads();
-  if (want_inv && w > 4) {   // w is uniform; columns beyond it are not written
-    if (t < 2 * H) { // pairs of 4 x 4 blocks
-      const int p = t >> 4, i = (t >> 2) & 3, j = t & 3, rb = 8 * p + 4, cb = 8 * p;
-      double s = 0.0;
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        double x = 0.0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) x += Lp[(rb + m) * LD + cb + k] * U[(cb + k) * LD + cb + j];
-        s += U[(rb + i) * LD + rb + m] * x;
-      }
-      U[(rb + i) * LD + cb + j] = -s;
-    }
-    __syncthreads();
-    if (w > 8) {     // pairs of 8 x 8 blocks, one element per thread
-      const int p = t >> 6, i = (t >> 3) & 7, j = t & 7, rb = 16 * p + 8, cb = 16 * p;
-      double x = 0.0;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) x += Lp[(rb + i) * LD + cb + k] * U[(cb + k) * LD + cb + j];
-      Tm[64 * p + 8 * i + j] = x;
-      __syncthreads();
-      double s = 0.0;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) s += U[(rb + i) * LD + rb + k] * Tm[64 * p + 8 * k + j];
-      U[(rb + i) * LD + cb + j] = -s;
-    }
-    __syncthreads();
-    if constexpr (H == 64) {
-      const int wave = t >> 6, lane = t & 63, m = lane & 15, kq = lane >> 4;
-      // 16 x 16 tile sum_k A[i][k] B[k][j] over K = 4 k4n
-      auto product = [&](const double* A, int lda, const double* Bm, int ldb, int k4n) {
-        f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-        for (int k4 = 0; k4 < k4n; ++k4)
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[m * lda + 4 * k4 + kq], Bm[(4 * k4 + kq) * ldb + m], acc, 0, 0, 0);
-        return acc;
-      };
-      if (w > 16) {    // pairs of 16 x 16 blocks: waves 0 and 1
-        const int rb = 32 * wave + 16, cb = 32 * wave;
-        double* tm = Tm + 272 * wave;
-        if (wave < 2) {
-          const f64x4 x = product(Lp + rb * LD + cb, LD, U + cb * LD + cb, LD, 4);
-#pragma unroll
-          for (int v = 0; v < 4; ++v) tm[(4 * v + kq) * 17 + m] = x[v];
-        }
-        __syncthreads();
-        if (wave < 2) {
-          const f64x4 x = product(U + rb * LD + rb, LD, tm, 17, 4);
-#pragma unroll
-          for (int v = 0; v < 4; ++v) U[(rb + 4 * v + kq) * LD + cb + m] = -x[v];
-        }
-      }
-      __syncthreads();
-      if (w > 32) {    // the pair of 32 x 32 blocks: a 16 x 16 tile per wave
-        const int i0 = 16 * (wave >> 1), j0 = 16 * (wave & 1);
-        const f64x4 x = product(Lp + (32 + i0) * LD, LD, U + j0, LD, 8);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) Tm[(i0 + 4 * v + kq) * 33 + j0 + m] = x[v];
-        __syncthreads();
-        const f64x4 y = product(U + (32 + i0) * LD + 32, LD, Tm + j0, 33, 8);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) U[(32 + i0 + 4 * v + kq) * LD + j0 + m] = -y[v];
-      }
-    }
-  }
-  __syncthreads();
-  double* mi = Minv + (int64_t)b * m_bstride;
-  const int j = t % H;
-  const double sj = sq[j], rj = rs[j];
-#pragma unroll
-  for (int n = 0; n < H * H / NT; ++n) {
-    const int i = t / H + NT / H * n;
-    const double lv = j <= i ? Lp[i * LD + j] * sj : 0.0, uv = j >= i ? U[j * LD + i] * rj : 0.0;
-    if (i < w && j < w) {
-      gd[(int64_t)i * l + j] = lv;
-      if (want_inv) mi[(int64_t)i * ldm + j] = uv;
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------
 // 64 x 64 tile of a product A[64 x K] (rows of type TA) * Bm[K x 64] (float64), accumulated in float64 on the matrix
 // cores by one workgroup of 256 threads (mfma64_accumulate).  The inner dimension is walked in chunks of 32 staged in
@@ -696,8 +399,8 @@ __global__ __launch_bounds__(256) void rows_times_small_kernel(const float* __re
 }
 
 // ---------------------------------------------------------------------------
-// Blocked Cholesky factorisation for l > 64, left-looking over column blocks of 64: for block k at columns c0..c0+63
-//   L_kk = chol(A_kk - sum_{c < c0} L[k, c] L[k, c]^T), and L_kk^-T              (chol_inv_kernel)
+// Blocked Cholesky factorisation for l > 128, left-looking over column blocks of 64: for block k at columns c0..c0+63
+//   L_kk = chol(A_kk - sum_{c < c0} L[k, c] L[k, c]^T), and L_kk^-T              (chol_tiles_kernel)
 //   L_ik = (A_ik - sum_{c < c0} L[i, c] L[k, c]^T) L_kk^-T  for rows i below      (this kernel, 64 rows per workgroup)
 // The finished columns are kept twice, as L in the lower triangle and as L^T in the upper one (G[c][r] = L[r][c]).
 // Both products run on the float64 matrix cores: 21 -> 11 us at 128 columns against a substitution row by row.
@@ -738,7 +441,7 @@ __global__ __launch_bounds__(256) void chol_panel_kernel(double* G, const double
 // ---------------------------------------------------------------------------
 // Out = In L^-T for 64 rows per workgroup, all columns: by column blocks of 64,
 //   Out_j = (In_j - sum_{i < j} Out_i L_ji^T) L_jj^-T
-// with the inverses of the diagonal blocks (chol_inv_kernel) and L^T from the upper triangle of G, every product on the
+// with the inverses of the diagonal blocks (chol_tiles_kernel) and L^T from the upper triangle of G, every product on the
 // float64 matrix cores.  A wave has 16 rows to itself: its rows of In and the small matrices (which all workgroups
 // share, so they come from L2) are loaded in operand layout straight into registers, and of the 16 x 16 tiles of the
 // triangular L_jj^-T only the ten that are not zero are used.  The contraction index of step (s, e) is
@@ -1515,21 +1218,22 @@ void gram(const float* A, double* G, GramScratch sc, int B, int rows, int l, hip
 // Cholesky factor of G + shift I in place, l <= 256: L in the lower triangle; for l > 64 the strict upper triangle
 // holds L^T outside the 64 x 64 diagonal blocks (whose upper halves are zeroed).  M (block stride l * l doubles)
 // receives the transposed inverses of the diagonal blocks: row stride l for the only one of l <= 64, otherwise 64 and
-// 64 * 64 doubles apart; with l > 64 its last entry carries the shift from the first block to the later ones.
+// 64 * 64 doubles apart; with l > 128 its last entry carries the shift from the first block to the later ones.
 // want_inv = false (the factor is all that is asked for): the inverse of the last block is not formed.
 void chol_factor(double* G, int B, int l, int32_t* info, hipStream_t st, double* M, bool want_inv) {
   const int64_t ll = (int64_t)l * l;
   constexpr int H = kCholBlock;
-  double* slot = l > H ? M + ll - 1 : nullptr;
+  auto factor = [&](auto kernel, int tiles, int c0, int w, double* slot, bool inverse) {
+    kernel<<<B, tiles == 1 ? 64 : 128 * tiles, 0, st>>>(G, l, c0, w, M + (int64_t)(c0 / H) * H * H, ll, l <= H ? l : H, inverse ? 1 : 0, slot, ll,
+                                     1e-14, info);
+  };
+  if (l <= 16) return factor(chol_tiles_kernel<1>, 1, 0, l, nullptr, want_inv);
+  if (l <= H) return factor(chol_tiles_kernel<4>, 4, 0, l, nullptr, want_inv);
+  if (l <= 2 * H) return factor(chol_tiles_kernel<8>, 8, 0, l, nullptr, want_inv);
   for (int c0 = 0; c0 < l; c0 += H) {
     const int w = std::min(H, l - c0);
     const bool last = c0 + w >= l;
-    auto factor = [&](auto kernel, int threads) {
-      kernel<<<B, threads, 0, st>>>(G, l, c0, w, M + (int64_t)(c0 / H) * H * H, ll, l <= H ? l : H,
-                                    (want_inv || !last) ? 1 : 0, slot, ll, 1e-14, info);
-    };
-    if (l <= 16) factor(chol_inv_kernel<16>, 64);
-    else factor(chol_inv_kernel<H>, 256);
+    factor(chol_tiles_kernel<4>, 4, c0, w, M + ll - 1, want_inv || !last);
     if (!last)
       chol_panel_kernel<<<dim3((l - c0 - w + H - 1) / H, B), 256, 0, st>>>(G, M + (int64_t)(c0 / H) * H * H, ll, l, c0);
   }

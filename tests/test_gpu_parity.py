@@ -648,6 +648,12 @@ def test_fit_basis_at_the_widths_of_narrow_sketches(l, D):
     test_fit_basis_at_the_block_edges_of_the_small_matrices(torch.float32, 2, D, l, 150)
 
 
+@pytest.mark.parametrize("B,l", [(2, 48), (1, 80), (2, 81), (1, 96), (2, 112), (1, 113), (3, 128), (1, 208), (1, 209)])
+def test_fit_basis_at_the_tile_edges_of_the_factor(B, l):
+    """Panels of 16 columns: sketches of 65 to 128 columns are factored as a whole, wider ones by blocks of 64."""
+    test_fit_basis_at_the_block_edges_of_the_small_matrices(torch.float32, B, 256, l, 150)
+
+
 @pytest.mark.parametrize("k,p", [(4, -1), (24, 0), (96, -1), (120, 16)])     # the wave Jacobi by width, and the one of 129..138 columns
 @pytest.mark.parametrize("value", [float("nan"), float("-inf")], ids=["nan", "inf"])
 def test_fit_writes_every_rank_of_a_block_that_is_not_finite(k, p, value):
