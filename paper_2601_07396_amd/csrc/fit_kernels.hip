@@ -11,14 +11,15 @@
 // condition number of F's leading part and its Gram matrix squares it again.
 // The tall matrices Q, Z (D x l) and Y (N x l) are float32.
 //
-// This file holds the small-matrix kernels, the host orchestration and the general (vector-ALU) versions of the two
-// products with F; their matrix-core versions are in fit_mfma_kernels.hip.
+// This file holds the small-matrix kernels, the host orchestration and the versions of the two products with F for any
+// hidden size; those for multiples of 128 are in fit_mfma_kernels.hip.
 #include <algorithm>
 #include <utility>
 
 #include <type_traits>
 
 #include "chol_kernels.h"
+#include "f32_tiles.h"
 #include "svdc_device.h"
 #include "svdc_internal.h"
 
@@ -56,84 +57,193 @@ __global__ void fill_zero_f32_kernel(float* p, int64_t n) {
 }
 
 // ---------------------------------------------------------------------------
-// products with F (general fp32 version)
-//   TRANS = false:  Out[N x l]  = F[N x D] * Bm[D x l]
-//   TRANS = true :  Out[D x l] += F^T      * Bm[N x l]   (rows of F split over grid.z, atomic accumulate)
-// 64 x 64 output tile per workgroup, 4 x 4 per thread, 16-deep steps through LDS.
+// Products with F for hidden sizes that are not multiples of 128, on the float32 matrix cores: Y = F Q and Z = F^T Y.
+// Bound by the matrix rate at wide sketches (256 flop per clock and compute unit, columns padded to 16, 32 or 64) and by the
+// latency of their loads at narrow ones.  One block of 15752 x 1440 bf16, 8 columns: 14 us (Y) and 16 us (Z), 1905 x 1312 with
+// 192 columns: 20 and 23 us, against 160 and 112, 153 and 111 us on the vector units with both operands staged in LDS an
+// element at a time.
 // ---------------------------------------------------------------------------
-template <typename T, bool TRANS>
-__global__ __launch_bounds__(256) void fit_gemm_kernel(const T* __restrict__ F, const float* __restrict__ Bm,
-                                                       float* Out, int N, int D, int l, int64_t ldf,
-                                                       int64_t bstride, int ksplit_len, int nsplit) {
-  __shared__ float As[16][64 + 4];
-  __shared__ float Bs[16][64 + 4];
-  const int b = blockIdx.z / nsplit, split = blockIdx.z % nsplit;
-  const int M = TRANS ? D : N, K = TRANS ? N : D;
-  const int m0 = blockIdx.x * 64, j0 = blockIdx.y * 64;
-  const int kbeg = split * ksplit_len, kend = min(K, kbeg + ksplit_len);
-  const T* f = F + (int64_t)b * bstride;
-  const float* bm = Bm + (int64_t)b * K * l;
-  float* out = Out + (int64_t)b * M * l;
-  const int t = threadIdx.x, tx = t & 15, ty = t >> 4;
-  float acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
 
-  for (int k0 = kbeg; k0 < kend; k0 += 16) {
-    if (!TRANS) {
-      const int m = t >> 2, kk = (t & 3) * 4;
-      const int64_t row = m0 + m;
+// Y[N x l] = F[N x D] Q[D x l], 16 KT columns of Y.  A wave has 16 RT token rows and walks over chunks of 32 channels: a lane's
+// eight channels 32 c + 8 g + e of its row are one (bf16) or two loads, step e of eight contracts the channels
+// {32 c + 8 g + e}, and the rows of Q pass through the wave's own LDS area a chunk ahead (VPiece).  The four waves of a
+// workgroup take WK shares of the chunks each for 4 / WK row groups; with WK = 4 their sums meet in LDS.
+constexpr int kFitWaves = 4;
+template <typename T, int KT, int RT, int WK>
+__global__ __launch_bounds__(64 * kFitWaves) void fit_rows_general_kernel(const T* __restrict__ F, const float* __restrict__ Q,
+                                                                          float* __restrict__ Y, int N, int D, int l,
+                                                                          int64_t ldf, int64_t bstride) {
+  using Stage = VPiece<KT>;
+  static_assert(WK == 1 || WK == kFitWaves, "a wave alone, or all four on the same rows");
+  static_assert(Stage::kFloats >= RT * KT * 256, "partial sums fit");
+  __shared__ __align__(16) float stage[kFitWaves][Stage::kFloats];
+  struct alignas(4 * KT) RowVec { float v[KT]; };
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int b = blockIdx.z, j0 = blockIdx.y * 16 * KT, nchunk = (D + 31) / 32;
+  const int row0 = (blockIdx.x * (kFitWaves / WK) + (WK == 1 ? wave : 0)) * 16 * RT;
+  if (WK == 1 && row0 >= N) return;
+  const float* q = Q + (int64_t)b * D * l;
+  float* lds = stage[wave];
+  const T* frow[RT];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int kidx = k0 + kk + e;
-        As[kk + e][m] = (row < M && kidx < kend) ? ld_elem(f, row * ldf + kidx) : 0.f;
-      }
-    } else {
-      const int kk = t >> 4, m = (t & 15) * 4;
-      const int64_t n = k0 + kk;
+  for (int rt = 0; rt < RT; ++rt) frow[rt] = F + (int64_t)b * bstride + (int64_t)min(row0 + 16 * rt + r, N - 1) * ldf;
+
+  constexpr int NH = KT * RT >= 4 ? 1 : 4 / (KT * RT);   // accumulators per result tile: four chains at least
+  f32x4 acc[RT][KT][NH];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int d = m0 + m + e;
-        As[kk][m + e] = (n < kend && d < M) ? ld_elem(f, n * ldf + d) : 0.f;
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int jt = 0; jt < KT; ++jt)
+#pragma unroll
+      for (int h = 0; h < NH; ++h) acc[rt][jt][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int c0 = WK == 1 ? 0 : wave;
+  Piece<T> fn[RT];
+  Stage vp;
+  if (c0 < nchunk) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) fn[rt].load(frow[rt], 32 * c0 + 8 * g, D);
+    vp.load(q, D, l, c0, j0);
+  }
+  for (int c = c0; c < nchunk; c += WK) {
+    Piece<T> f[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) f[rt] = fn[rt];
+    vp.to_lds(lds);
+    if (c + WK < nchunk) {
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) fn[rt].load(frow[rt], 32 * (c + WK) + 8 * g, D);
+      vp.load(q, D, l, c + WK, j0);
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      // columns of the result tile jt: j0 + KT r + jt, so that one wide LDS read brings the operands of all tiles
+      const RowVec qv = *reinterpret_cast<const RowVec*>(lds + (8 * g + e) * Stage::KS + KT * r);
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const float x = f[rt].get(e);
+#pragma unroll
+        for (int jt = 0; jt < KT; ++jt) acc[rt][jt][e % NH] = mfma_f32(x, qv.v[jt], acc[rt][jt][e % NH]);
       }
     }
-    {
-      const int kk = t >> 4, j = (t & 15) * 4;
-      const int64_t kidx = k0 + kk;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int col = j0 + j + e;
-        Bs[kk][j + e] = (kidx < kend && col < l) ? bm[kidx * l + col] : 0.f;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], bb[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bb[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * bb[j];
-    }
-    __syncthreads();
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t row = m0 + ty * 4 + i;
-    if (row >= M) continue;
+  for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = j0 + tx * 4 + j;
-      if (col >= l) continue;
-      if (TRANS) atomicAdd(&out[row * l + col], acc[i][j]);
-      else out[row * l + col] = acc[i][j];
+    for (int jt = 0; jt < KT; ++jt)
+#pragma unroll
+      for (int h = 1; h < NH; ++h) acc[rt][jt][0] += acc[rt][jt][h];
+  // D[m = 4 g + i][n = r]: row 4 g + i, column j0 + KT r + jt
+  auto store = [&](int rt, int jt, const f32x4& x) {
+    const int j = j0 + KT * r + jt;
+    if (j >= l) return;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = row0 + 16 * rt + 4 * g + i;
+      if (row < N) Y[((int64_t)b * N + row) * l + j] = x[i];
     }
+  };
+  if constexpr (WK == 1) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int jt = 0; jt < KT; ++jt) store(rt, jt, acc[rt][jt][0]);
+  } else {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    f32x4* mine = reinterpret_cast<f32x4*>(lds);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int jt = 0; jt < KT; ++jt) mine[(rt * KT + jt) * 64 + lane] = acc[rt][jt][0];
+    __syncthreads();
+#pragma unroll
+    for (int n = 0; n < RT * KT; ++n) {
+      if (n % kFitWaves != wave) continue;
+      f32x4 x = reinterpret_cast<const f32x4*>(stage[0])[n * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < kFitWaves; ++w) x += reinterpret_cast<const f32x4*>(stage[w])[n * 64 + lane];
+      store(n / KT, n % KT, x);
+    }
+  }
+}
+
+// Z[D x l] (+)= F^T Y over the token rows of one share, 128 channels x 16 KT columns.  A lane holds the eight channels
+// d0 + 8 r .. of token n + g, element e of which is the operand of the tile of channels {d0 + 8 m + e}, and the
+// columns j0 + 16 t + r of the same token: both come straight from memory, whole lines at a time.  The waves take every
+// fourth group of four tokens, their sums meet in LDS in a fixed order, those of several shares in float atomics.
+template <typename T, int KT>
+__global__ __launch_bounds__(64 * kFitWaves) void fit_cols_general_kernel(const T* __restrict__ F, const float* __restrict__ Y,
+                                                                          float* __restrict__ Z, int N, int D, int l,
+                                                                          int64_t ldf, int64_t bstride, int share, int nshare) {
+  constexpr int UN = KT >= 4 ? 2 : 4;               // token groups requested at a time, one such set ahead
+  __shared__ __align__(16) f32x4 part[kFitWaves][2 * KT][64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int b = blockIdx.z / nshare, d0 = blockIdx.x * 128, j0 = blockIdx.y * 16 * KT;
+  const int n0 = (blockIdx.z % nshare) * share, n1 = min(N, n0 + share);
+  const T* f = F + (int64_t)b * bstride;
+  const float* y = Y + (int64_t)b * N * l + j0 + r;
+  f32x4 acc[8][KT];
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+#pragma unroll
+    for (int t = 0; t < KT; ++t) acc[e][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  Piece<T> fp[UN];
+  float yp[UN][KT];
+  auto load = [&](int n) {                          // the wave's groups of the UN x 16 tokens from n
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int tok = n + 16 * u + 4 * wave + g, at = min(tok, n1 - 1);
+      fp[u].load(f + (int64_t)at * ldf, d0 + 8 * r, tok < n1 ? D : 0);
+#pragma unroll
+      for (int t = 0; t < KT; ++t) {
+        const bool in = tok < n1 && j0 + 16 * t + r < l;
+        yp[u][t] = in ? y[(int64_t)at * l + 16 * t] : 0.f;
+      }
+    }
+  };
+  load(n0);
+  for (int n = n0; n < n1; n += 16 * UN) {
+    Piece<T> fc[UN];
+    float yc[UN][KT];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      fc[u] = fp[u];
+#pragma unroll
+      for (int t = 0; t < KT; ++t) yc[u][t] = yp[u][t];
+    }
+    if (n + 16 * UN < n1) load(n + 16 * UN);
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float x = fc[u].get(e);
+#pragma unroll
+        for (int t = 0; t < KT; ++t) acc[e][t] = mfma_f32(x, yc[u][t], acc[e][t]);
+      }
+  }
+#pragma unroll
+  for (int e = 0; e < 8; e += 2) {                  // two channel tiles at a time through LDS
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int t = 0; t < KT; ++t) part[wave][s * KT + t][lane] = acc[e + s][t];
+    __syncthreads();
+#pragma unroll
+    for (int n = 0; n < 2 * KT; ++n) {
+      if (n % kFitWaves != wave) continue;
+      f32x4 x = part[0][n][lane];
+#pragma unroll
+      for (int w = 1; w < kFitWaves; ++w) x += part[w][n][lane];
+      const int j = j0 + 16 * (n % KT) + r;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int d = d0 + 8 * (4 * g + i) + e + n / KT;
+        if (d >= D || j >= l) continue;
+        float* z = Z + ((int64_t)b * D + d) * l + j;
+        if (nshare > 1) atomicAdd(z, x[i]);
+        else *z = x[i];
+      }
+    }
+    __syncthreads();
   }
 }
 
@@ -1094,20 +1204,32 @@ __global__ __launch_bounds__(256) void jacobi_finish_kernel(const double* __rest
 // ---------------------------------------------------------------------------
 // sum of squares of F[b] in float64 (||F||_F^2 for the energy rule, Eq. 6)
 // ---------------------------------------------------------------------------
+// Eight channels per lane and load, four loads in flight; a workgroup takes every gridDim.x-th group of 256 pieces.
 template <typename T>
 __global__ __launch_bounds__(256) void sumsq_kernel(const T* __restrict__ F, double* acc, int N, int D,
-                                                    int64_t ldf, int64_t bstride, int rows_per_group) {
+                                                    int64_t ldf, int64_t bstride) {
   __shared__ double part[4];
-  const int b = blockIdx.y, t = threadIdx.x;
+  const int b = blockIdx.y, t = threadIdx.x, per_row = (D + 7) / 8;
   const T* f = F + (int64_t)b * bstride;
-  const int r0 = blockIdx.x * rows_per_group, r1 = min(N, r0 + rows_per_group);
-  double s = 0.0;
-  for (int r = r0; r < r1; ++r)
-    for (int d = t; d < D; d += 256) {
-      const float x = ld_elem(f, (int64_t)r * ldf + d);
-      s += (double)x * (double)x;
+  const int64_t total = (int64_t)N * per_row, step = (int64_t)gridDim.x * 256;
+  double s0 = 0.0, s1 = 0.0;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + t; i < total; i += 4 * step) {
+    Piece<T> p[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t at = min(i + u * step, total - 1), row = at / per_row;
+      p[u].load(f + row * ldf, i + u * step < total ? 8 * (int)(at - row * per_row) : D, D);
     }
-  s = wave_sum(s);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int e = 0; e < 8; e += 2) {
+        const double x = (double)p[u].get(e), y = (double)p[u].get(e + 1);
+        s0 = fma(x, x, s0);
+        s1 = fma(y, y, s1);
+      }
+  }
+  const double s = wave_sum(s0 + s1);
   if ((t & 63) == 0) part[t >> 6] = s;
   __syncthreads();
   if (t == 0) atomicAdd(&acc[b], part[0] + part[1] + part[2] + part[3]);
@@ -1184,16 +1306,36 @@ void zero_f32(float* p, int64_t n, hipStream_t st) {
 
 template <typename T>
 void gemm_fq(const svdc_shape& s, int l, const T* F, const float* Q, float* Y, hipStream_t st) {
-  dim3 grid((s.N + 63) / 64, (l + 63) / 64, s.B);
-  fit_gemm_kernel<T, false><<<grid, 256, 0, st>>>(F, Q, Y, s.N, s.D, l, s.ldf, s.block_stride, s.D, 1);
+  auto launch = [&](auto kernel, int rows, int cols) {
+    kernel<<<dim3((s.N + rows - 1) / rows, (l + cols - 1) / cols, s.B), 64 * kFitWaves, 0, st>>>(F, Q, Y, s.N, s.D, l, s.ldf,
+                                                                                                s.block_stride);
+  };
+  // 128 rows per workgroup read Q once for eight tiles; 32 (four waves on the same rows) while those would be fewer than two
+  // workgroups per compute unit, 16 while even those of 32 would be
+  auto by_rows = [&](auto kt) {
+    constexpr int KT = decltype(kt)::value;
+    const int64_t tiles = (int64_t)((s.N + 15) / 16) * ((l + 16 * KT - 1) / (16 * KT)) * s.B, cus = num_compute_units();
+    if (tiles >= 16 * cus) launch(fit_rows_general_kernel<T, KT, 2, 1>, 128, 16 * KT);
+    else if (tiles >= 4 * cus) launch(fit_rows_general_kernel<T, KT, 2, kFitWaves>, 32, 16 * KT);
+    else launch(fit_rows_general_kernel<T, KT, 1, kFitWaves>, 16, 16 * KT);
+  };
+  if (l <= 16) by_rows(std::integral_constant<int, 1>{});
+  else if (l <= 32) by_rows(std::integral_constant<int, 2>{});
+  else by_rows(std::integral_constant<int, 4>{});
 }
 template <typename T>
 void gemm_fty(const svdc_shape& s, int l, const T* F, const float* Y, float* Z, hipStream_t st) {
-  zero_f32(Z, (int64_t)s.B * s.D * l, st);
-  const int split_len = 1024;
-  const int nsplit = (s.N + split_len - 1) / split_len;
-  dim3 grid((s.D + 63) / 64, (l + 63) / 64, s.B * nsplit);
-  fit_gemm_kernel<T, true><<<grid, 256, 0, st>>>(F, Y, Z, s.N, s.D, l, s.ldf, s.block_stride, split_len, nsplit);
+  auto launch = [&](auto kernel, int kt) {
+    const int slabs = (s.D + 127) / 128, cols = (l + 16 * kt - 1) / (16 * kt);
+    // shares of the tokens: two workgroups per compute unit, at least 64 tokens each
+    const int64_t want = std::max<int64_t>(1, 2 * (int64_t)num_compute_units() / ((int64_t)slabs * cols * s.B));
+    const int share = (int)std::max<int64_t>(64, (((s.N + want - 1) / want) + 15) / 16 * 16), nshare = (s.N + share - 1) / share;
+    if (nshare > 1) zero_f32(Z, (int64_t)s.B * s.D * l, st);
+    kernel<<<dim3(slabs, cols, s.B * nshare), 64 * kFitWaves, 0, st>>>(F, Y, Z, s.N, s.D, l, s.ldf, s.block_stride, share, nshare);
+  };
+  if (l <= 16) launch(fit_cols_general_kernel<T, 1>, 1);
+  else if (l <= 32) launch(fit_cols_general_kernel<T, 2>, 2);
+  else launch(fit_cols_general_kernel<T, 4>, 4);
 }
 
 // Scratch for partial Gram matrices: `doubles` float64 values.
@@ -1363,8 +1505,10 @@ int32_t run_fit_typed(const svdc_shape& s, const FitPlan& pl, const T* F, float*
   gram(Y, G, scratch(Z, s.D), B, s.N, l, st);
   chol_factor(G, B, l, info, st, M, false);   // M: scratch until the Jacobi writes it
   if (want_fro && !fro_done) {
-    const int rpg = 64;
-    sumsq_kernel<T><<<dim3((s.N + rpg - 1) / rpg, B), 256, 0, st>>>(F, misc, s.N, s.D, s.ldf, s.block_stride, rpg);
+    // at most four workgroups per compute unit, at least 8192 elements each: all of a block's add to one word
+    const int64_t pieces = (int64_t)s.N * ((s.D + 7) / 8);
+    const int64_t groups = std::min<int64_t>((pieces + 1023) / 1024, std::max<int64_t>(1, 4 * (int64_t)num_compute_units() / B));
+    sumsq_kernel<T><<<dim3((unsigned)groups, B), 256, 0, st>>>(F, misc, s.N, s.D, s.ldf, s.block_stride);
   }
   int32_t jrc = SVDC_OK;
   if ((size_t)l * (l + 1) * sizeof(double) <= kLdsBudget) {   // l <= 138: the whole matrix in the LDS of one workgroup

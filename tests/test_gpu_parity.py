@@ -648,6 +648,16 @@ def test_fit_basis_at_the_widths_of_narrow_sketches(l, D):
     test_fit_basis_at_the_block_edges_of_the_small_matrices(torch.float32, 2, D, l, 150)
 
 
+@pytest.mark.parametrize("dtype,B,D,l,N", [
+    (torch.float32, 1, 76, 5, 66001), (torch.bfloat16, 1, 136, 40, 65999), (torch.float32, 1, 72, 17, 16401),
+    (torch.bfloat16, 2, 200, 33, 9001), (torch.float32, 1, 1028, 16, 33), (torch.float32, 3, 132, 32, 1000),
+    (torch.bfloat16, 40, 264, 12, 131), (torch.float32, 1, 264, 136, 4099)])
+def test_fit_basis_general_products(dtype, B, D, l, N):
+    """The products with F for hidden sizes that are not multiples of 128: workgroups of 128, 32 and 16 rows, one or several
+    shares of the tokens, ragged rows, channels (of F and of the 32- and 128-channel pieces) and columns."""
+    test_fit_basis_at_the_block_edges_of_the_small_matrices(dtype, B, D, l, N - l)
+
+
 @pytest.mark.parametrize("B,l", [(2, 48), (1, 80), (2, 81), (1, 96), (2, 112), (1, 113), (3, 128), (1, 208), (1, 209)])
 def test_fit_basis_at_the_tile_edges_of_the_factor(B, l):
     """Panels of 16 columns: sketches of 65 to 128 columns are factored as a whole, wider ones by blocks of 64."""
