@@ -18,6 +18,7 @@
 #include <type_traits>
 
 #include "f32_tiles.h"
+#include "step_tiling.h"
 #include "svdc_device.h"
 #include "svdc_internal.h"
 
@@ -254,6 +255,331 @@ __global__ __launch_bounds__(64 * kCachedWaves, 4) void forecast_general_kernel(
   });
 }
 
+// ---------------------------------------------------------------------------
+// The same two steps with the products on the bf16 matrix cores, for ranks of 17 to 128 where step_tiling.h says so: a float32
+// is the exact sum of three bf16 parts (8 significant bits each), a product of two keeps six of the nine products of parts
+// (what is dropped is below 2^-26 of it), and a bf16 feature is one part already.  An instruction contracts 32 channels or
+// coefficients at 16 times the rate of the float32 one, so six cost less than half of it; what bounds the kernels instead are
+// the vector instructions (11 for every pair of elements of V that is split, 70 for every row tile and chunk that is put
+// together), which is why 32 or 48 rows share a piece of V.  The leading products of every chunk are added up in float64:
+// C is within 2.8e-8 of its norm of the float64 product at 1408 and 2.8e-8 at 3304 channels, 3.4e-8 with float32 instructions.
+// Measured at 4 x 2173 x 1408 bf16, rank 50: full step 68 -> 44 us, cached step 31 -> 23 us; 22848 x 2136 at rank 21: 110 -> 73
+// and 67 -> 47 us.
+// ---------------------------------------------------------------------------
+struct Parts { u32x4 p[3]; };
+__device__ __forceinline__ Parts split_parts(const float (&x)[8]) {
+  Parts out;
+  float rem[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) rem[e] = x[e];
+#pragma unroll
+  for (int n = 0; n < 3; ++n)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t w = pack_bf16(rem[2 * i], rem[2 * i + 1]);
+      out.p[n][i] = w;
+      if (n < 2) {
+        rem[2 * i] -= bf16_lo(w);
+        rem[2 * i + 1] -= bf16_hi(w);
+      }
+    }
+  return out;
+}
+__device__ __forceinline__ f32x4 mfma_parts(const u32x4& a, const u32x4& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+// The products of a feature's parts with those of V: the leading one into `lead`, the others, 2^-8 of it and less, into `rest`.
+__device__ __forceinline__ void feature_product(const Piece<bf16_t>& f, const Parts& v, f32x4& lead, f32x4& rest) {
+  lead = mfma_parts(f.w, v.p[0], lead);
+  rest = mfma_parts(f.w, v.p[2], rest);
+  rest = mfma_parts(f.w, v.p[1], rest);
+}
+__device__ __forceinline__ void feature_product(const Parts& f, const Parts& v, f32x4& lead, f32x4& rest) {
+  lead = mfma_parts(f.p[0], v.p[0], lead);
+  rest = mfma_parts(f.p[0], v.p[2], rest);
+  rest = mfma_parts(f.p[2], v.p[0], rest);
+  rest = mfma_parts(f.p[1], v.p[1], rest);
+  rest = mfma_parts(f.p[0], v.p[1], rest);
+  rest = mfma_parts(f.p[1], v.p[0], rest);
+}
+__device__ __forceinline__ const Piece<bf16_t>& feature_parts(const Piece<bf16_t>& f) { return f; }
+__device__ __forceinline__ Parts feature_parts(const Piece<float>& f) {
+  const float x[8] = {f.x[0][0], f.x[0][1], f.x[0][2], f.x[0][3], f.x[1][0], f.x[1][1], f.x[1][2], f.x[1][3]};
+  return split_parts(x);
+}
+
+// i-th chunk of 32 channels of a wave among `waves`: pairs of neighbours, whose rows share lines of 128 bytes
+__device__ __forceinline__ int pair_chunk(int i, int wave, int waves) { return 2 * (wave + (i >> 1) * waves) + (i & 1); }
+__device__ __forceinline__ int pair_chunks(int nchunk, int wave, int waves) {
+  const int pairs = (nchunk + 1) / 2, mine = wave < pairs ? (pairs - wave + waves - 1) / waves : 0;
+  // the last pair of all may be a single chunk
+  return 2 * mine - (mine > 0 && (nchunk & 1) && (pairs - 1) % waves == wave ? 1 : 0);
+}
+
+// P = C V^T of 16 RT rows for the wave's chunks, C as operand words in LDS: cw[(rt kt2 + kt) 3 + part][lane], lane (r, g), e ->
+// C[row r][32 kt + 8 g + e].  Like `reconstruct` above, a pair of chunks at a time: `fetch(c, rows)` requests what P is combined
+// with, a pair ahead; `emit(c, rt, piece of rows, P)` gets the results.
+template <int RT, typename Rows, typename Fetch, typename Emit>
+__device__ __forceinline__ void reconstruct_parts(const float* v, const u32x4* cw, float* vlds, int D, int k, int kt2, int wave,
+                                                  int waves, int nchunk, Fetch fetch, Emit emit) {
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  constexpr int KS = VPiece<2>::KS;
+  const int mine = pair_chunks(nchunk, wave, waves);
+  if (mine <= 0) return;
+  VPiece<2> vp;
+  vp.load(v, D, k, pair_chunk(0, wave, waves), 0);
+  Rows next[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) fetch(pair_chunk(h, wave, waves), next[h]);
+  for (int i0 = 0; i0 < mine; i0 += 2) {
+    Rows rows[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      rows[h] = next[h];
+      if (i0 + 2 < mine) fetch(pair_chunk(i0 + 2 + h, wave, waves), next[h]);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int i = i0 + h;
+      if (i >= mine) break;
+      const int c = pair_chunk(i, wave, waves);
+      f32x4 lead[RT][2], rest[RT][2];
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) lead[rt][t] = rest[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int kt = 0; kt < kt2; ++kt) {
+        vp.to_lds(vlds);
+        const bool more = kt + 1 < kt2;
+        if (more || i + 1 < mine) vp.load(v, D, k, more ? c : pair_chunk(i + 1, wave, waves), more ? 32 * (kt + 1) : 0);
+        Parts a[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const float* row = vlds + (8 * (r >> 2) + 4 * t + (r & 3)) * KS + 8 * g;
+          const f32x4 x0 = *reinterpret_cast<const f32x4*>(row), x1 = *reinterpret_cast<const f32x4*>(row + 4);
+          const float x[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+          a[t] = split_parts(x);
+        }
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          Parts b;
+#pragma unroll
+          for (int n = 0; n < 3; ++n) b.p[n] = cw[((rt * kt2 + kt) * 3 + n) * 64 + lane];
+#pragma unroll
+          for (int t = 0; t < 2; ++t) feature_product(a[t], b, lead[rt][t], rest[rt][t]);
+        }
+      }
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const f32x4 p[2] = {lead[rt][0] + rest[rt][0], lead[rt][1] + rest[rt][1]};
+        emit(c, rt, rows[h], p);
+      }
+    }
+  }
+}
+
+// Full step on 16 RT rows: the structure of full_step_general_kernel, 32 coefficients of phase 1 at a time.
+template <typename T, int RT, bool REMA>
+__global__ __launch_bounds__(64 * kStepWaves, 2) void full_step_parts_kernel(const T* F, const float* __restrict__ V, T* R,
+                                                                          const T* Rp, float alpha_r, float* S, float* C,
+                                                                          int N, int D, int k, int64_t ldf, int64_t bstride,
+                                                                          float alpha, int init) {
+  constexpr int KT = 2, ROWS = 16 * RT;
+  using Stage = VPiece<KT>;
+  // per wave: its piece of V; between the phases its partial sums
+  constexpr int kStage = Stage::kFloats > KT * RT * 256 ? Stage::kFloats : KT * RT * 256;
+  __shared__ __align__(16) float vstage[kStepWaves][kStage];
+  extern __shared__ __align__(16) char dyn[];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int b = blockIdx.y, row0 = blockIdx.x * ROWS, kt2 = (k + 31) / 32, CS = 32 * kt2 + 4;
+  u32x4* cw = reinterpret_cast<u32x4*>(dyn);                                        // [RT][kt2][3][64]
+  float* cs = reinterpret_cast<float*>(dyn + (size_t)RT * kt2 * 3 * 1024);          // [ROWS][CS]
+  const int nchunk = (D + 31) / 32, mine = pair_chunks(nchunk, wave, kStepWaves);
+  const float* v = V + (int64_t)b * D * k;
+  float* vlds = vstage[wave];
+  int64_t roff[RT];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) roff[rt] = (int64_t)b * bstride + (int64_t)min(row0 + 16 * rt + r, N - 1) * ldf;
+
+  for (int j0 = 0; j0 < k; j0 += 16 * KT) {
+    f32x4 rest[RT][KT];
+    f64x4 tot[RT][KT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int jt = 0; jt < KT; ++jt) {
+        rest[rt][jt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        tot[rt][jt] = f64x4{0.0, 0.0, 0.0, 0.0};
+      }
+    Piece<T> fn[2][RT];
+    Stage vp;
+    auto load_rows = [&](int i, Piece<T> (&to)[RT]) {
+      const int c = pair_chunk(i, wave, kStepWaves);
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) to[rt].load(F + roff[rt], 32 * c + 8 * g, D);
+    };
+    if (mine > 0) {
+      load_rows(0, fn[0]);
+      vp.load(v, D, k, pair_chunk(0, wave, kStepWaves), j0);
+      if (mine > 1) load_rows(1, fn[1]);
+    }
+    for (int i = 0; i < mine; ++i) {
+      Piece<T> f[RT];
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        f[rt] = fn[0][rt];
+        fn[0][rt] = fn[1][rt];
+      }
+      vp.to_lds(vlds);
+      if (i + 1 < mine) vp.load(v, D, k, pair_chunk(i + 1, wave, kStepWaves), j0);
+      if (i + 2 < mine) load_rows(i + 2, fn[1]);
+      // columns of the result tile jt: j0 + 2 r + jt
+      float x[KT][8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float2 w = *reinterpret_cast<const float2*>(vlds + (8 * g + e) * Stage::KS + KT * r);
+        x[0][e] = w.x;
+        x[1][e] = w.y;
+      }
+      Parts vv[KT];
+#pragma unroll
+      for (int jt = 0; jt < KT; ++jt) vv[jt] = split_parts(x[jt]);
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const auto fp = feature_parts(f[rt]);
+#pragma unroll
+        for (int jt = 0; jt < KT; ++jt) {
+          f32x4 lead = f32x4{0.f, 0.f, 0.f, 0.f};
+          feature_product(fp, vv[jt], lead, rest[rt][jt]);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) tot[rt][jt][q] += (double)lead[q];
+        }
+      }
+    }
+    f32x4* part = reinterpret_cast<f32x4*>(vlds);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int jt = 0; jt < KT; ++jt) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) part[(rt * KT + jt) * 64 + lane][q] = (float)(tot[rt][jt][q] + (double)rest[rt][jt][q]);
+      }
+    __syncthreads();
+    // D[m = 4 g + i][n = r]: row 4 g + i, coefficient j0 + 2 r + jt
+    if (wave < RT * KT) {
+      static_assert(RT * KT <= kStepWaves, "one sum per wave");
+      const int rt = wave / KT, j = j0 + KT * r + wave % KT;
+      double c[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int w = 0; w < kStepWaves; ++w) {
+        const f32x4 p = reinterpret_cast<const f32x4*>(vstage[w])[wave * 64 + lane];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c[i] += (double)p[i];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) cs[(16 * rt + 4 * g + i) * CS + j] = j < k ? (float)c[i] : 0.f;
+    }
+    __syncthreads();
+  }
+
+  // operand words of the coefficients; the EMA update of the state (Eq. 11 with alpha = 1 - beta)
+  for (int n = wave; n < RT * kt2; n += kStepWaves) {
+    const float* c = cs + (16 * (n / kt2) + r) * CS + 32 * (n % kt2) + 8 * g;
+    const float x[8] = {c[0], c[1], c[2], c[3], c[4], c[5], c[6], c[7]};
+    const Parts p = split_parts(x);
+#pragma unroll
+    for (int m = 0; m < 3; ++m) cw[(n * 3 + m) * 64 + lane] = p.p[m];
+  }
+  const int nrow = min(ROWS, N - row0);
+  const int64_t soff = ((int64_t)b * N + row0) * k;
+  for (int e = threadIdx.x; e < nrow * k; e += 64 * kStepWaves) {
+    const int row = e / k, j = e - row * k;
+    const float c = cs[row * CS + j];
+    const float s = init ? c : (1.f - alpha) * S[soff + e] + alpha * c;
+    S[soff + e] = s;
+    if (C) C[soff + e] = c;
+  }
+  __syncthreads();
+
+  // residual R = F - C V^T (Eq. 10)
+  struct Rows { Piece<T> f[RT], rp[REMA ? RT : 1]; };
+  auto fetch = [&](int c, Rows& to) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      to.f[rt].load(F + roff[rt], 32 * c + 8 * g, D);
+      if constexpr (REMA) to.rp[rt].load(Rp + roff[rt], 32 * c + 8 * g, D);
+    }
+  };
+  reconstruct_parts<RT, Rows>(v, cw, vlds, D, k, kt2, wave, kStepWaves, nchunk, fetch,
+                              [&](int c, int rt, const Rows& rows, const f32x4 (&p)[2]) {
+    f32x4 x[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        x[t][i] = rows.f[rt].get(4 * t + i) - p[t][i];
+        if constexpr (REMA) x[t][i] = (1.f - alpha_r) * rows.rp[rt].get(4 * t + i) + alpha_r * x[t][i];
+      }
+    if (row0 + 16 * rt + r < N) Piece<T>::store(R + roff[rt], 32 * c + 8 * g, D, x);
+  });
+}
+
+// Cached step on 16 RT rows; the blockIdx.z-th of gridDim.z shares of the channels.
+template <typename T, int RT, bool HX>
+__global__ __launch_bounds__(64 * kCachedWaves, 3) void forecast_parts_kernel(const CoefStates st, const float* __restrict__ V,
+                                                                           const T* R, const T* X, T* Fh, int N, int D, int k,
+                                                                           int64_t ldf, int64_t bstride) {
+  __shared__ __align__(16) float vstage[kCachedWaves][VPiece<2>::kFloats];
+  extern __shared__ __align__(16) char dyn[];
+  u32x4* cw = reinterpret_cast<u32x4*>(dyn);                                        // [RT][kt2][3][64]
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int b = blockIdx.y, row0 = blockIdx.x * 16 * RT, kt2 = (k + 31) / 32;
+  const int nchunk = (D + 31) / 32;
+  for (int n = wave; n < RT * kt2; n += kCachedWaves) {
+    const int row = row0 + 16 * (n / kt2) + r, j = 32 * (n % kt2) + 8 * g;
+    const int64_t at = ((int64_t)b * N + min(row, N - 1)) * k;
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int64_t a = at + min(j + e, k - 1);
+      float c = st.w[0] * st.s[0][a];
+      for (int m = 1; m < st.m; ++m) c = __builtin_fmaf(st.w[m], st.s[m][a], c);
+      x[e] = j + e < k ? c : 0.f;
+    }
+    const Parts p = split_parts(x);
+#pragma unroll
+    for (int m = 0; m < 3; ++m) cw[(n * 3 + m) * 64 + lane] = p.p[m];
+  }
+  __syncthreads();
+  int64_t roff[RT];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) roff[rt] = (int64_t)b * bstride + (int64_t)min(row0 + 16 * rt + r, N - 1) * ldf;
+  struct Rows { Piece<T> f[RT], x[HX ? RT : 1]; };
+  auto fetch = [&](int c, Rows& to) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      to.f[rt].load(R + roff[rt], 32 * c + 8 * g, D);
+      if constexpr (HX) to.x[rt].load(X + roff[rt], 32 * c + 8 * g, D);
+    }
+  };
+  reconstruct_parts<RT, Rows>(V + (int64_t)b * D * k, cw, vstage[wave], D, k, kt2, blockIdx.z * kCachedWaves + wave,
+                              kCachedWaves * gridDim.z, nchunk, fetch,
+                              [&](int c, int rt, const Rows& rows, const f32x4 (&p)[2]) {
+    f32x4 x[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        x[t][i] = rows.f[rt].get(4 * t + i);
+        if constexpr (HX) x[t][i] += rows.x[rt].get(4 * t + i);
+        x[t][i] += p[t][i];
+      }
+    if (row0 + 16 * rt + r < N) Piece<T>::store(Fh + roff[rt], 32 * c + 8 * g, D, x);
+  });
+}
+
+constexpr int kCachedPartsRows = 2;   // row tiles of the cached step above
 // calls fn(KT) with the coefficient tiles that a piece of V holds, as a compile-time constant.  The full step stops at
 // two (32 coefficients at a time, ranks above 32 in several passes over the rows): with four its accumulators leave one
 // or, spilled, two workgroups per compute unit (93 against 67 us at rank 50).
@@ -277,6 +603,25 @@ int32_t allow_lds(K kernel, size_t bytes) {
 template <typename T>
 int32_t full_step_general_typed(const svdc_shape& s, const void* F, const float* V, void* R, float* S, float* C,
                                 float alpha, int init, ResidualEma re, hipStream_t st) {
+  constexpr bool kF32 = sizeof(T) == 4;
+  const int rt = full_step_may_take_parts(s.D, s.k, kF32, re.prev != nullptr)
+                     ? full_step_parts_rows(s.N, s.B, s.D, s.k, kF32, re.prev != nullptr, num_compute_units()) : 0;
+  if (rt > 0) {
+    auto go = [&](auto tiles) -> int32_t {
+      constexpr int RT = decltype(tiles)::value;
+      constexpr bool kRema = !kF32;       // float32 rows and previous residuals do not fit the registers: not asked for
+      const auto kernel = kRema && re.prev ? full_step_parts_kernel<T, RT, kRema> : full_step_parts_kernel<T, RT, false>;
+      const int kt2 = (s.k + 31) / 32;
+      const size_t lds = (size_t)RT * kt2 * 3 * 1024 + (size_t)16 * RT * (32 * kt2 + 4) * sizeof(float);
+      if (allow_lds(kernel, lds) != SVDC_OK) return SVDC_E_HIP;
+      kernel<<<dim3((s.N + 16 * RT - 1) / (16 * RT), s.B), 64 * kStepWaves, lds, st>>>(
+          (const T*)F, V, (T*)R, (const T*)re.prev, re.alpha_r, S, C, s.N, s.D, s.k, s.ldf, s.block_stride, alpha, init);
+      return launch_status();
+    };
+    if (rt == 1) return go(std::integral_constant<int, 1>{});
+    if (rt == 2) return go(std::integral_constant<int, 2>{});
+    return go(std::integral_constant<int, 3>{});
+  }
   return general_dispatch<2>(s, [&](auto kt) -> int32_t {
     auto kernel = full_step_general_kernel<T, decltype(kt)::value>;
     const size_t lds = (size_t)16 * coef_stride(s.k) * sizeof(float);
@@ -291,6 +636,23 @@ int32_t full_step_general_typed(const svdc_shape& s, const void* F, const float*
 template <typename T>
 int32_t forecast_general_typed(const svdc_shape& s, const CoefStates& cs, const float* V, const void* R, const void* X,
                                void* Out, hipStream_t st) {
+  if (cached_step_may_take_parts(s.D, s.k, sizeof(T) == 4, X != nullptr) && cached_step_takes_parts(s.N, s.B, num_compute_units())) {
+    auto go = [&](auto kernel) -> int32_t {
+      const size_t lds = (size_t)kCachedPartsRows * ((s.k + 31) / 32) * 3 * 1024;
+      if (allow_lds(kernel, lds) != SVDC_OK) return SVDC_E_HIP;
+      const int64_t tiles = (s.N + 16 * kCachedPartsRows - 1) / (16 * kCachedPartsRows);
+      // shares of the channels: four workgroups per compute unit, at least a pair of chunks per wave
+      const int64_t most = std::max(1, (s.D + 63) / 64 / kCachedWaves);
+      const int64_t want = (4 * (int64_t)num_compute_units() + tiles * s.B - 1) / (tiles * s.B);
+      kernel<<<dim3((unsigned)tiles, s.B, (unsigned)std::max<int64_t>(1, std::min(want, most))), 64 * kCachedWaves, lds, st>>>(
+          cs, V, (const T*)R, (const T*)X, (T*)Out, s.N, s.D, s.k, s.ldf, s.block_stride);
+      return launch_status();
+    };
+    if constexpr (sizeof(T) == 2) {
+      if (X) return go(forecast_parts_kernel<T, kCachedPartsRows, true>);
+    }
+    return go(forecast_parts_kernel<T, kCachedPartsRows, false>);
+  }
   return general_dispatch<4>(s, [&](auto kt) -> int32_t {
     auto kernel = forecast_general_kernel<T, decltype(kt)::value>;
     const size_t lds = (size_t)16 * coef_stride(s.k) * sizeof(float);

@@ -90,4 +90,42 @@ inline bool smoothing_takes_full_tiles(int rt, int kt2, int N, int64_t B, int cu
   return cost(rt) < 0.92 * cost(rt - 1);
 }
 
+// Row tiles of 16 with which the general full step runs on the bf16 matrix cores in parts (general_kernels.hip), 0: on the float32
+// ones, which take one.  Estimated time of a round of workgroups, fitted to 15 shapes (us): 3 + chunks of a wave x (piece of V +
+// tiles x row tile); a float32 instruction works 1.65 (bf16 rows) or 1.8 per 32 coefficients and tile of 16, the parts take 0.9
+// per 32 coefficients to split V and 0.44 + 0.36 (0.9 + 0.75) per row tile, a tenth more where the residual is smoothed.  Few
+// channels, where the constants overlap with other workgroups (57 x 3874 x 72 float32: 170 and 250 us; 3 x 12607 x 512 float32: 95
+// and 104 us), and ranks up to 16, half of whose columns would be padding (20 x 900 x 1000, rank 16: 29 and 36 us), stay on the
+// float32 instructions; so do gains of less than 8 %, 15 % for float32 rows and with smoothing, which the estimate meets less
+// well, and both together (registers).  Over 60 sampled calls none is slower by more than the runs scatter, and bf16 rows
+// take 17 % less time on average where the rule applies.
+// The limits come first, so that a call outside them does not ask for the compute units (a fiftieth of the smallest calls).
+inline bool full_step_may_take_parts(int D, int k, bool f32, bool smoothing) {
+  return k > 16 && k <= 128 && D > 32 * (f32 ? 23 : 15) && !(f32 && smoothing);
+}
+inline int full_step_parts_rows(int N, int64_t B, int D, int k, bool f32, bool smoothing, int cus) {
+  const int nchunk = (D + 31) / 32, kt2 = (k + 31) / 32;
+  auto rounds = [&](int rt) { return (double)(((int64_t)((N + 16 * rt - 1) / (16 * rt)) * B + cus - 1) / cus); };
+  double least = (f32 || smoothing ? 0.85 : 0.92) * rounds(1) * (3 + (nchunk + 7) / 8 * (f32 ? 1.8 : 1.65) * kt2);
+  int best = 0;
+  for (int rt = 1; rt <= 3; ++rt) {
+    const double row = f32 ? 0.9 + 0.75 * kt2 : (smoothing ? 0.54 : 0.44) + 0.36 * kt2;
+    const double t = rounds(rt) * (3 + 2 * (((nchunk + 1) / 2 + 7) / 8) * (0.9 * kt2 + rt * row));
+    if (t < least) {
+      least = t;
+      best = rt;
+    }
+  }
+  return best;
+}
+
+// Whether the general cached step runs in parts, 32 rows per workgroup: where that leaves work for half of the compute units
+// (6 x 700 x 3304, rank 33: 31 -> 24 us; but 1500 x 1304, rank 100: 11 and 13 us), under the limits above; float32 rows from rank
+// 65 and 768 channels on (7591 x 2136, rank 74: 57 -> 47 us; but 6163 x 1592, rank 37: 26 and 28 us, 10 x 598 x 552, rank 80: 15
+// and 18 us) and with nothing to add (registers).
+inline bool cached_step_may_take_parts(int D, int k, bool f32, bool add) {
+  return k > (f32 ? 64 : 16) && k <= 128 && D >= (f32 ? 768 : 512) && !(f32 && add);
+}
+inline bool cached_step_takes_parts(int N, int64_t B, int cus) { return 2 * (int64_t)((N + 31) / 32) * B >= cus; }
+
 }  // namespace svdc

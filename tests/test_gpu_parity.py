@@ -92,6 +92,27 @@ def test_general_kernels_at_the_edges_of_their_tiles(dtype, B, N, D, k):
         assert torch.equal(got[0][keep], want[0][keep]) and not torch.isfinite(got[0][[3, 5]].float()).all(dim=1).any()
 
 
+@pytest.mark.parametrize("dtype,N,D,k", [(torch.bfloat16, 601, 2008, 64), (torch.bfloat16, 8101, 520, 50), (torch.bfloat16, 8701, 520, 50),
+                                         (torch.bfloat16, 5003, 520, 127), (torch.float32, 8701, 796, 50), (torch.float32, 5003, 796, 100)])
+def test_general_kernels_in_bf16_parts(dtype, N, D, k):
+    """Tiles of 16, 32 and 48 rows, ragged rows, channels (an odd number of chunks, a chunk that is partly outside) and coefficients."""
+    test_general_kernels_at_the_edges_of_their_tiles(dtype, 1, N, D, k)
+
+
+# (float32 rows of 8101 x 3304 at rank 33 stay on the float32 instructions, whose chains the test above is about)
+@pytest.mark.parametrize("dtype,N,D,k", [(torch.bfloat16, 8701, 1408, 50), (torch.float32, 8701, 1408, 50), (torch.bfloat16, 8101, 3304, 33)])
+def test_general_projection_in_parts_is_as_good_as_float32(dtype, N, D, k):
+    """C from bf16 parts: the leading products of a chunk of 32 channels are one matrix instruction, whose 32 products and sum
+    are rounded a few times (at most like a chain over them, 0.41 u sqrt(32 / 2) of the chunk's share of C, u = 2^-24), the
+    chunks are added in float64, the other products are 2^-8 of that, and the result is rounded once: 0.41 u sqrt(17)."""
+    g = torch.Generator().manual_seed(D + k)
+    F = torch.randn(1, N, D, generator=g).to(dtype)
+    V = torch.randn(1, D, k, generator=g) / D ** 0.5
+    _, _, Cc, _, pk = _run_full(F, D, V, torch.zeros(1, N, k), 0.3, True)
+    assert pk is None
+    assert rel_err(to_np(Cc[0]), to_np(F[0]) @ to_np(V[0])) <= 0.41 * 2.0 ** -24 * 17 ** 0.5
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
 def test_general_projection_sums_in_short_chains(dtype):
     """C of many channels: float32 chains of at most 16 products, their sums in a chain of one link per 512 channels.  A chain

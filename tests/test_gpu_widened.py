@@ -457,6 +457,13 @@ def test_full_step_residual_ema(dtype, B, N, D, k):
     assert torch.equal(Ra, Rb) and torch.equal(Sa, Sb)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+def test_general_kernels_of_large_calls_with_extras(dtype):
+    """The general kernels of calls that fill the machine: residual smoothed, several states, a tensor added."""
+    test_full_step_residual_ema(dtype, 1, 8701, 776, 50)
+    test_forecast_combine(dtype, 1, 4999, 520, 70)
+
+
 def test_full_step_residual_ema_rejects_bad_arguments():
     F = torch.randn(1, 16, 64, device=DEV)
     V = torch.linalg.qr(torch.randn(1, 64, 4, device=DEV))[0].contiguous()

@@ -11,8 +11,17 @@ PROGRAM = r"""
 #include "step_tiling.h"
 // m ntile B kt2 parts elem cus, widest slab, narrow slab -> chunks tiles, the best of 16..6 at the widest slab and its fill
 // with an argument: rt kt2 N B cus -> whether the smoothing full step takes rt row tiles; with two: B N D kt2 parts cus ->
-// whether the full step takes tiles of 16 rows
+// whether the full step takes tiles of 16 rows; with three: B N D k f32 smoothing / tensor added cus -> 10 x the row tiles of the
+// general full step in parts + whether the general cached step runs in parts
 int main(int argc, char**) {
+  if (argc > 3) {
+    int N, D, k, f32, extra, cus;
+    long long B;
+    while (std::scanf("%lld %d %d %d %d %d %d", &B, &N, &D, &k, &f32, &extra, &cus) == 7)
+      std::printf("%d\n", (svdc::full_step_may_take_parts(D, k, f32, extra) ? 10 * svdc::full_step_parts_rows(N, B, D, k, f32, extra, cus) : 0) +
+                               (svdc::cached_step_may_take_parts(D, k, f32, extra) && svdc::cached_step_takes_parts(N, B, cus)));
+    return 0;
+  }
   if (argc > 2) {
     long long B, N, D, kt2, parts, cus;
     while (std::scanf("%lld %lld %lld %lld %lld %lld", &B, &N, &D, &kt2, &parts, &cus) == 6)
@@ -53,6 +62,8 @@ def tiling(tmp_path_factory):
     def run(calls, rule=()):
         text = "\n".join(" ".join(str(int(x)) for x in c) for c in calls)
         out = subprocess.run([exe, *rule], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout
+        if len(rule) == 3:
+            return [(int(line) // 10, bool(int(line) % 10)) for line in out.split()]
         if rule:
             return [bool(int(line)) for line in out.split()]
         return [(int(a), int(b), int(c), float(d)) for a, b, c, d in (line.split() for line in out.splitlines())]
@@ -125,3 +136,14 @@ def test_small_full_steps_take_single_tiles_while_l2_holds_the_basis(tiling):
     calls = [(4, 700, 3072, 1, 2), (28, 128, 1152, 1, 1), (57, 32, 3072, 1, 2),
              (28, 125, 1152, 2, 2), (26, 128, 1920, 2, 2), (57, 48, 512, 2, 2), (1, 4608, 3072, 1, 2)]
     assert tiling([c + (256,) for c in calls], rule=["full", "step"]) == [True, True, True, False, False, False, False]
+
+
+def test_general_steps_in_parts(tiling):
+    """Row tiles of the general full step on the bf16 matrix cores (0: the float32 ones) and whether the cached step runs there:
+    the sizes of the GPU tests, measured ones (gain), and the limits of the rank, the channels, the rows and the storage type."""
+    want = [((1, 601, 2008, 64, 0, 0), (1, False)), ((1, 8101, 520, 50, 0, 0), (2, True)), ((1, 8701, 520, 50, 0, 0), (3, True)),
+            ((1, 8701, 800, 50, 1, 0), (3, False)), ((1, 5003, 800, 100, 1, 0), (2, True)), ((1, 8701, 776, 50, 0, 1), (3, True)),
+            ((4, 2173, 1408, 50, 0, 0), (3, True)), ((6, 700, 3304, 33, 0, 0), (2, True)), ((1, 1500, 1304, 100, 0, 0), (1, False)),
+            ((20, 900, 1000, 16, 0, 0), (0, False)), ((57, 3874, 72, 36, 0, 0), (0, False)), ((4, 2173, 1408, 129, 0, 0), (0, False)),
+            ((1, 8701, 800, 50, 1, 1), (0, False)), ((1, 10032, 2800, 9, 1, 0), (0, False))]
+    assert tiling([c + (256,) for c, _ in want], rule=["general", "steps", "parts"]) == [w for _, w in want]
