@@ -754,27 +754,34 @@ __device__ __forceinline__ double row_sum(double x) {
   return x;
 }
 
-// x from lane i ^ (8 S), S = 1, 2 or 4: rows of 16 lanes rotated by 8, then neighbouring rows or halves of the wave swapped
-// (v_permlane16_swap exchanges the odd rows of its first operand with the even rows of its second, v_permlane32_swap
-// the upper half with the lower one: given the same value twice, each result holds what half of the lanes need).
+// x and y from lane i ^ (8 S), S = 1, 2 or 4: rows of 16 lanes rotated by 8, then neighbouring rows or halves of the wave
+// swapped.  v_permlane16_swap exchanges the odd rows of its first operand with the even rows of its second,
+// v_permlane32_swap the upper half with the lower one: applied to a word of x and one of y and then to the same two in the other
+// order, it moves both and leaves each in the other's register, so that a double costs two instructions and no copy.
 template <int S>
-__device__ __forceinline__ uint32_t xor_rows_word(uint32_t x, bool odd) {
-  if constexpr (S == 1) return (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, 0x128, 0xf, 0xf, true);   // row_ror:8
-  if constexpr (S == 2) {
-    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-    return odd ? r[0] : r[1];
+__device__ __forceinline__ void xor_rows(double& x, double& y) {
+  if constexpr (S == 1) {     // row_ror:8
+    x = dpp_move<0x128>(x);
+    y = dpp_move<0x128>(y);
+  } else if constexpr (S == 2 || S == 4) {
+    auto swap = [](uint32_t u, uint32_t v) {
+      if constexpr (S == 2) {
+        const auto r = __builtin_amdgcn_permlane16_swap(u, v, false, false);
+        return __builtin_amdgcn_permlane16_swap(r[1], r[0], false, false);
+      } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(u, v, false, false);
+        return __builtin_amdgcn_permlane32_swap(r[1], r[0], false, false);
+      }
+    };
+    const auto lo = swap((uint32_t)__double2loint(x), (uint32_t)__double2loint(y));
+    const auto hi = swap((uint32_t)__double2hiint(x), (uint32_t)__double2hiint(y));
+    x = __hiloint2double((int)hi[0], (int)lo[0]);
+    y = __hiloint2double((int)hi[1], (int)lo[1]);
+  } else {                    // several bits, one after the other
+    if constexpr (S & 1) xor_rows<1>(x, y);
+    if constexpr (S & 2) xor_rows<2>(x, y);
+    if constexpr (S & 4) xor_rows<4>(x, y);
   }
-  const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-  return odd ? r[0] : r[1];
-}
-template <int S>
-__device__ __forceinline__ double xor_rows(double x) {
-  if constexpr (S == 0) return x;
-  if constexpr ((S & 1) && S != 1) return xor_rows<S & ~1>(xor_rows<1>(x));
-  if constexpr ((S & 2) && S != 2) return xor_rows<S & ~2>(xor_rows<2>(x));
-  const bool odd = (threadIdx.x & (8 * S)) != 0;
-  return __hiloint2double((int)xor_rows_word<S>((uint32_t)__double2hiint(x), odd),
-                          (int)xor_rows_word<S>((uint32_t)__double2loint(x), odd));
 }
 
 constexpr int kJacobiThreads = 512;
@@ -795,9 +802,8 @@ __device__ __forceinline__ bool jacobi_angle(double al, double be, double ga, do
   const double g2 = ga * ga, ab = al * be;
   if (!(g2 > 1e-14 * ab)) return false;
   const float z = (float)((be - al) * 0.5 * __builtin_amdgcn_rcp(ga));
-  const float az = fabsf(z), am = fminf(az, 1e9f);
-  const float tf = __builtin_copysignf(
-      az > 1e9f ? 0.5f * __builtin_amdgcn_rcpf(az) : __builtin_amdgcn_rcpf(am + __builtin_amdgcn_sqrtf(fmaf(am, am, 1.f))), z);
+  const float az = fabsf(z), am = fminf(az, 1e9f);     // the root is |z| to the last bit from there on (and z^2 may overflow)
+  const float tf = __builtin_copysignf(__builtin_amdgcn_rcpf(az + fmaxf(__builtin_amdgcn_sqrtf(fmaf(am, am, 1.f)), az)), z);
   *tt = (double)tf;
   const double n2 = fma(*tt, *tt, 1.0);
   const double c0 = (double)__builtin_amdgcn_rsqf(fmaf(tf, tf, 1.f));
@@ -913,8 +919,11 @@ __device__ __forceinline__ void jacobi_output(const double* A, int la, int l, in
 // barriers instead of 63 -- with a trip per rotation the LDS reads, writes and the barrier were half of a round at 64
 // columns and the LDS bandwidth bound 128 columns.  The squared norms are formed once per trip and follow the rotations
 // (al - t ga, be + t ga), so that a rotation sums one inner product over the lanes.
-// Measured inside the fit of one block of 4608 x 3072 bf16, rank 32: 154 us (64 columns); of 18432 x 3072 float32, rank 64:
-// 743 us (128 columns); against 254 and 1106 us with 16 lanes per pair, every rotation from and to LDS.
+// What bounds it: the dependent chain of a rotation at 64 columns (one wave per SIMD), the number of instructions at 128 (two):
+// 16 multiply-adds for an inner product, 32 to rotate, 32 to 40 to move 16 elements, 45 for sums and angle, each 5 clocks.
+// Measured inside the fit of one block of 4608 x 3072 bf16, rank 32: 116 us (64 columns); of 18432 x 3072 float32, rank 64:
+// 570 us (128 columns); against 154 and 762 us with four operations per rotated pair of elements, copies and selections
+// where columns move and a branch in the angle, 254 and 1106 us with 16 lanes per pair, every rotation from and to LDS.
 template <int NE>
 __global__ __launch_bounds__(512) void jacobi_wave_kernel(const double* __restrict__ Lfac, double* Wout, float* sigma, int l,
                                                           int k, const double* fro_acc, float* fro2, int max_sweeps,
@@ -938,49 +947,63 @@ __global__ __launch_bounds__(512) void jacobi_wave_kernel(const double* __restri
   if (t == 0) s_big[0] = 0;
   __syncthreads();
 
-  double xs[NE], ys[NE], nx, ny;
+  // The columns x and y of a row and what they are scaled by: column = d * elements, id = 1 / d, n = its squared norm.  The
+  // rotation x <- cs (x - t y), y <- cs (y + t x) of the columns is, of the elements, x <- x - (t dy / dx) y and then, with the new x,
+  // y <- y + (t cs^2 dx / dy) x, and dx <- cs dx, dy <- dy / cs: two operations in place per pair of elements instead of four
+  // and copies.  Every trip to LDS starts again with scales of one.
+  struct Scale { double n, d, id; };
+  double xs[NE], ys[NE];
+  Scale sx, sy;
   int big;
   // rotate the wave's columns x with the columns y of the same rows
   auto rotate = [&] {
     double g0 = 0.0, g1 = 0.0;
 #pragma unroll
     for (int e = 0; e < NE; e += 2) { g0 = fma(xs[e], ys[e], g0); g1 = fma(xs[e + 1], ys[e + 1], g1); }
-    const double ga = row_sum<8>(g0 + g1);
+    const double ga = row_sum<8>(g0 + g1) * (sx.d * sy.d);
     double tt, cs, sn;
-    if (jacobi_angle(nx, ny, ga, &tt, &cs, &sn, &big)) {
+    if (jacobi_angle(sx.n, sy.n, ga, &tt, &cs, &sn, &big)) {
+      const double a = -tt * (sy.d * sx.id), c = (sn * cs) * (sx.d * sy.id), ics = cs * fma(tt, tt, 1.0);
 #pragma unroll
       for (int e = 0; e < NE; ++e) {
-        const double x = xs[e], y = ys[e];
-        xs[e] = cs * x - sn * y;
-        ys[e] = sn * x + cs * y;
+        xs[e] = fma(a, ys[e], xs[e]);
+        ys[e] = fma(c, xs[e], ys[e]);
       }
-      nx = fma(-tt, ga, nx);
-      ny = fma(tt, ga, ny);
+      sx = {fma(-tt, ga, sx.n), sx.d * cs, sx.id * ics};
+      sy = {fma(tt, ga, sy.n), sy.d * ics, sy.id * cs};
     }
   };
-  auto move_y = [&](auto s) {
+  // columns (and scales) from the row with the exclusive-or of the number; elements by pairs
+  auto move = [](auto s, double (&v)[NE], Scale& sc) {
+    constexpr int S = decltype(s)::value;
+    static_assert(NE % 2 == 0, "moved by pairs");
 #pragma unroll
-    for (int e = 0; e < NE; ++e) ys[e] = xor_rows<decltype(s)::value>(ys[e]);
-    ny = xor_rows<decltype(s)::value>(ny);
+    for (int e = 0; e < NE; e += 2) xor_rows<S>(v[e], v[e + 1]);
+    double twin = sc.id;
+    xor_rows<S>(sc.n, sc.d);
+    xor_rows<S>(sc.id, twin);
   };
+  auto move_y = [&](auto s) { move(s, ys, sy); };
   // rotate column g with column g ^ S of the same block: both rows form the rotation, each keeps its own column
-  auto rotate_inside = [&](auto s, double (&xv)[NE], double& n) {
+  auto rotate_inside = [&](auto s, double (&xv)[NE], Scale& sv) {
     constexpr int S = decltype(s)::value;
     constexpr int kTop = S >= 4 ? 4 : (S >= 2 ? 2 : 1);
     const bool lower = (g & kTop) == 0;                 // which of the two plays x: they differ in the highest bit of S
     double pv[NE], g0 = 0.0, g1 = 0.0;
+    Scale sp = sv;
 #pragma unroll
-    for (int e = 0; e < NE; ++e) pv[e] = xor_rows<S>(xv[e]);
-    const double pn = xor_rows<S>(n);
+    for (int e = 0; e < NE; ++e) pv[e] = xv[e];
+    move(s, pv, sp);
 #pragma unroll
     for (int e = 0; e < NE; e += 2) { g0 = fma(xv[e], pv[e], g0); g1 = fma(xv[e + 1], pv[e + 1], g1); }
-    const double ga = row_sum<8>(g0 + g1);
+    const double ga = row_sum<8>(g0 + g1) * (sv.d * sp.d);
     double tt, cs, sn;
-    if (jacobi_angle(lower ? n : pn, lower ? pn : n, ga, &tt, &cs, &sn, &big)) {
-      if (lower) { sn = -sn; tt = -tt; }
+    if (jacobi_angle(lower ? sv.n : sp.n, lower ? sp.n : sv.n, ga, &tt, &cs, &sn, &big)) {
+      if (lower) tt = -tt;
+      const double a = tt * (sp.d * sv.id), ics = cs * fma(tt, tt, 1.0);
 #pragma unroll
-      for (int e = 0; e < NE; ++e) xv[e] = cs * xv[e] + sn * pv[e];
-      n = fma(tt, ga, n);
+      for (int e = 0; e < NE; ++e) xv[e] = fma(a, pv[e], xv[e]);
+      sv = {fma(tt, ga, sv.n), sv.d * cs, sv.id * ics};
     }
   };
   using I1 = std::integral_constant<int, 1>;
@@ -990,7 +1013,7 @@ __global__ __launch_bounds__(512) void jacobi_wave_kernel(const double* __restri
   // of a block may be zeros there (3 columns: 15.6 -> 6.9 us); beyond, the branches cost more than they save (64: 157 us, 154
   // without them).
   constexpr bool kFull = NE > 2;
-  auto rotate_all_inside = [&](int n, double (&xv)[NE], double& nv) {
+  auto rotate_all_inside = [&](int n, double (&xv)[NE], Scale& nv) {
     if (kFull || n > 1) rotate_inside(I1{}, xv, nv);
     if (kFull || n > 2) { rotate_inside(I2{}, xv, nv); rotate_inside(std::integral_constant<int, 3>{}, xv, nv); }
     if (kFull || n > 4) {
@@ -1014,11 +1037,11 @@ __global__ __launch_bounds__(512) void jacobi_wave_kernel(const double* __restri
       for (int e = 0; e < NE; ++e) { xs[e] = px[8 * e]; ys[e] = py[8 * e]; }
 #pragma unroll
       for (int e = 0; e < NE; ++e) { n0 = fma(xs[e], xs[e], n0); n1 = fma(ys[e], ys[e], n1); }
-      nx = row_sum<8>(n0);
-      ny = row_sum<8>(n1);
+      sx = {row_sum<8>(n0), 1.0, 1.0};
+      sy = {row_sum<8>(n1), 1.0, 1.0};
       if (step == 0) {
-        rotate_all_inside(l - 8 * rr.p, xs, nx);
-        rotate_all_inside(l - 8 * rr.q, ys, ny);
+        rotate_all_inside(l - 8 * rr.p, xs, sx);
+        rotate_all_inside(l - 8 * rr.q, ys, sy);
       }
       if (kFull || (8 * rr.p < l && 8 * rr.q < l)) {   // both blocks have columns (l is the same for the whole wave)
         rotate(); move_y(I1{});   // rows of y now hold column g ^ 1
@@ -1032,7 +1055,7 @@ __global__ __launch_bounds__(512) void jacobi_wave_kernel(const double* __restri
         py = A + (8 * rr.q + (g ^ 4)) * la + gl;
       }
 #pragma unroll
-      for (int e = 0; e < NE; ++e) { px[8 * e] = xs[e]; py[8 * e] = ys[e]; }
+      for (int e = 0; e < NE; ++e) { px[8 * e] = xs[e] * sx.d; py[8 * e] = ys[e] * sy.d; }
       rr.next();
       __syncthreads();
     }
