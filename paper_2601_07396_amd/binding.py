@@ -1,4 +1,5 @@
-"""ctypes binding of the C ABI in include/svdcache.h (argument marshalling only)."""
+"""Binding of the C ABI in include/svdcache.h (argument marshalling only): ctypes, and for the step calls with ordinary
+arguments the compiled module _fast_calls, which makes the same call from the same tensors with less host time."""
 from __future__ import annotations
 
 import ctypes as C
@@ -73,6 +74,7 @@ EXPORTS = {
 }
 
 _lib = None
+_fast = None      # the module _fast_calls, bound to the functions of _lib
 
 
 def lib_path() -> str:
@@ -85,7 +87,7 @@ def exported_symbols():
 
 def load_library():
     """Load libsvdcache.so from the package directory; raises if it was not built."""
-    global _lib
+    global _lib, _fast
     if _lib is not None:
         return _lib
     path = lib_path()
@@ -97,6 +99,13 @@ def load_library():
         fn = getattr(lib, name)
         fn.restype = res
         fn.argtypes = args
+    if os.path.exists(os.path.join(PKG_DIR, "_fast_calls.so")):
+        import importlib.util
+        spec = importlib.util.spec_from_file_location("_fast_calls", os.path.join(PKG_DIR, "_fast_calls.so"))
+        fast = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(fast)
+        fast.bind({name: C.cast(getattr(lib, name), C.c_void_p).value for name in EXPORTS})
+        _fast = fast
     _lib = lib
     return lib
 
@@ -184,6 +193,16 @@ def _check_step_args(shape: Shape, V, packed, coefs: dict, feats: dict):
                              "(a buffer packed for another rank or width?)")
 
 
+def _fast_call(name: str, *args) -> bool:
+    """Whether _fast_calls made the call; False where the arguments are not ordinary (or the module was not built)."""
+    if _lib is None:
+        load_library()
+    code = None if _fast is None else getattr(_fast, name)(*args)
+    if code:
+        raise SvdcError(code, "svdcache_" + name)
+    return code is not None
+
+
 def _check(code: int, where: str):
     if code != 0:
         raise SvdcError(code, where)
@@ -256,6 +275,8 @@ def svdcache_pack_basis(shape: Shape, V, packed):
 
 
 def svdcache_full_step(shape: Shape, F, V, packed, R, S, Cout, alpha: float, init: bool):
+    if _fast_call("full_step", shape, F, V, packed, R, S, Cout, alpha, init):
+        return
     _check_step_args(shape, V, packed, {"S": S, "C": Cout}, {"F": F, "R": R})
     _need_gpu(F, V, packed, R, S, Cout)
     rc = load_library().svdcache_full_step(C.byref(shape), _ptr(F), _ptr(V), _ptr(packed), _ptr(R), _ptr(S),
@@ -265,6 +286,8 @@ def svdcache_full_step(shape: Shape, F, V, packed, R, S, Cout, alpha: float, ini
 
 def svdcache_full_step_residual_ema(shape: Shape, F, V, packed, R_prev, R, S, Cout, alpha: float, alpha_r: float,
                                     init: bool):
+    if _fast_call("full_step_residual_ema", shape, F, V, packed, R_prev, R, S, Cout, alpha, alpha_r, init):
+        return
     _check_step_args(shape, V, packed, {"S": S, "C": Cout}, {"F": F, "R": R, "R_prev": R_prev})
     _need_gpu(F, V, packed, R_prev, R, S, Cout)
     rc = load_library().svdcache_full_step_residual_ema(C.byref(shape), _ptr(F), _ptr(V), _ptr(packed), _ptr(R_prev),
@@ -274,6 +297,8 @@ def svdcache_full_step_residual_ema(shape: Shape, F, V, packed, R_prev, R, S, Co
 
 
 def svdcache_forecast(shape: Shape, S, V, packed, R, Fhat):
+    if _fast_call("forecast", shape, S, V, packed, R, Fhat):
+        return
     _check_step_args(shape, V, packed, {"S": S}, {"R": R, "Fhat": Fhat})
     _need_gpu(S, V, packed, R, Fhat)
     rc = load_library().svdcache_forecast(C.byref(shape), _ptr(S), _ptr(V), _ptr(packed), _ptr(R), _ptr(Fhat),
@@ -301,6 +326,8 @@ def svdcache_pack_state(shape: Shape, S, S_packed):
 
 
 def svdcache_full_step_packed(shape: Shape, F, V, packed, R, S, Cout, S_packed, alpha: float, init: bool):
+    if _fast_call("full_step_packed", shape, F, V, packed, R, S, Cout, S_packed, alpha, init):
+        return
     if packed is None:
         raise ValueError("packed: the packed-state full step needs the packed basis")
     _check_step_args(shape, V, packed, {"S": S, "C": Cout}, {"F": F, "R": R})
@@ -314,6 +341,8 @@ def svdcache_full_step_packed(shape: Shape, F, V, packed, R, S, Cout, S_packed, 
 
 
 def svdcache_forecast_packed(shape: Shape, S_packed, packed, R, Fhat):
+    if _fast_call("forecast_packed", shape, S_packed, packed, R, Fhat):
+        return
     if packed is None:
         raise ValueError("packed: the packed-state cached step needs the packed basis")
     _like_features(shape, R=R, Fhat=Fhat)
@@ -351,6 +380,8 @@ def svdcache_extrapolation_weights(order: int, offset: float, interval: float):
 
 
 def svdcache_forecast_combine(shape: Shape, S_list, weights, V, packed, R, X, Out):
+    if _fast_call("forecast_combine", shape, S_list, weights, V, packed, R, X, Out):
+        return
     m = len(S_list)
     if m != len(weights):
         raise ValueError("one weight per state")

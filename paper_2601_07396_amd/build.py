@@ -8,6 +8,7 @@ import sys
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(PKG_DIR, "libsvdcache.so")
+FAST_CALLS_PATH = os.path.join(PKG_DIR, "_fast_calls.so")          # step calls of the binding, host code only
 PROBES_LIB_PATH = os.path.join(PKG_DIR, "libsvdcache_probes.so")   # memory-system probes for the benchmark only
 
 HIPCC_FLAGS = [
@@ -20,6 +21,19 @@ HIPCC_FLAGS = [
     "-mllvm", "-pragma-unroll-threshold=1000000",
     "-Wno-unused-command-line-argument",
 ]
+
+
+def _torch_flags() -> list:
+    """Headers and libraries of the installed torch, for the part of the binding that reads its tensors."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension as ext
+    flags = [f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-DUSE_ROCM=1", "-D__HIP_PLATFORM_AMD__=1"]
+    for path in [*ext.include_paths("cuda"), sysconfig.get_paths()["include"]]:
+        flags += ["-isystem", path]
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    return [*flags, f"-L{lib}", f"-Wl,-rpath,{lib}", "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
 
 
 def build(verbose: bool = False) -> str:
@@ -45,6 +59,8 @@ def build(verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(len(srcs), os.cpu_count() or 1, 8)) as pool:
         list(pool.map(lambda so: run(["hipcc", *HIPCC_FLAGS, "-c", "-o", so[1], so[0]]), zip(srcs, objs)))
     run(["hipcc", "--offload-arch=gfx950", "-fPIC", "-shared", "-o", LIB_PATH, *objs])
+    run(["hipcc", "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-o", FAST_CALLS_PATH,
+         os.path.join(PKG_DIR, "csrc", "binding", "fast_calls.cpp"), *_torch_flags()])
     probe_srcs = sorted(glob.glob(os.path.join(PKG_DIR, "csrc", "probes", "*.hip")))
     run(["hipcc", *HIPCC_FLAGS, "-shared", "-o", PROBES_LIB_PATH, *probe_srcs])
     return LIB_PATH

@@ -1153,3 +1153,71 @@ def test_flux_block_trajectory_against_a_free_running_oracle():
             torch.cuda.synchronize()
             assert_close(to_np(Fh[0][rows]), ref_forecast(Sr, Vn, Rr, "bf16"), "bf16", f"t={t} Fhat", scale_of=Frows,
                          ulp_of=Rr)
+
+
+@pytest.mark.parametrize("dtype,D,k", [(torch.float32, 64, 8), (torch.bfloat16, 256, 32)])
+def test_step_calls_by_both_routes_of_the_binding(dtype, D, k, monkeypatch):
+    """The compiled step calls and the ctypes ones make the same calls, on the current stream, and refuse the same arguments
+    with the same errors: other strides, types, sizes and devices, buffers that are too small, numbers out of range."""
+    from paper_2601_07396_amd import binding
+    fast = binding._fast
+    assert fast is not None
+    B, N = 2, 50
+    Fbuf, V, S0 = _rand_problem(B, N, D, k, dtype, seed=D)
+    F, V, Rp = Fbuf.to(DEV), V.to(DEV), Fbuf.flip(1).contiguous().to(DEV)
+    shape = pkg.make_shape(F, k)
+    packed = pkg.pack_basis(shape, V)
+    Sp = pkg.alloc_packed_state(shape, F.device) if packed is not None else None
+
+    def good():
+        S, Cc, R, Fh = S0.to(DEV), torch.empty(B, N, k, device=DEV), torch.empty_like(F), torch.empty_like(F)
+        out = []
+        pkg.svdcache_full_step(shape, F, V, packed, R, S, Cc, 0.3, False)
+        pkg.svdcache_forecast(shape, S, V, packed, R, Fh)
+        out += [R.clone(), S.clone(), Cc, Fh.clone()]
+        pkg.svdcache_full_step_residual_ema(shape, F, V, packed, Rp, R, S, None, 0.5, 0.25, False)
+        pkg.svdcache_forecast_combine(shape, [S, Cc], [1.5, -0.5], V, packed, R, F, Fh)
+        out += [R.clone(), S.clone(), Fh.clone()]
+        if Sp is not None:
+            pkg.svdcache_full_step_packed(shape, F, V, packed, R, S, None, Sp, 0.5, False)
+            pkg.svdcache_forecast_packed(shape, Sp, packed, R, Fh)
+            out += [R.clone(), S.clone(), Fh.clone(), Sp.clone()]
+        return out
+
+    S, R, Fh = S0.to(DEV), torch.empty_like(F), torch.empty_like(F)
+    wide = torch.empty(B, N, D + 8, device=DEV, dtype=dtype)[:, :, :D]
+    other = torch.float64 if dtype == torch.float32 else torch.float32
+    full = lambda **kw: pkg.svdcache_full_step(*[{**dict(shape=shape, F=F, V=V, P=packed, R=R, S=S, C=None, a=0.5, i=False), **kw}[n]
+                                                for n in ("shape", "F", "V", "P", "R", "S", "C", "a", "i")])
+    bad = [lambda: full(R=wide), lambda: full(F=F.to(other)), lambda: full(V=V[:, :, :-1]), lambda: full(S=S.double()),
+           lambda: full(S=S.transpose(1, 2)), lambda: full(C=S[:1]), lambda: full(F=F.cpu()), lambda: full(a=0.0), lambda: full(a=1.5),
+           lambda: full(a=float("nan")), lambda: full(a="x"), lambda: full(V=None), lambda: full(P=torch.empty(8, device=DEV)),
+           lambda: pkg.svdcache_forecast(shape, S, V, packed, R[:1], Fh), lambda: pkg.svdcache_forecast(shape, S, V, packed, R, wide),
+           lambda: pkg.svdcache_forecast_combine(shape, [S], [1.0, 2.0], V, packed, R, None, Fh),
+           lambda: pkg.svdcache_forecast_combine(shape, [S] * 5, [1.0] * 5, V, packed, R, None, Fh),
+           lambda: pkg.svdcache_forecast_combine(shape, [S], [float("nan")], V, packed, R, None, Fh)]
+
+    def refusals():
+        texts = []
+        for call in bad:
+            with pytest.raises(Exception) as e:
+                call()
+            texts.append((type(e.value).__name__, str(e.value)))
+        return texts
+
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        by_module, said_module = good(), refusals()
+    monkeypatch.setattr(binding, "_fast", None)
+    with torch.cuda.stream(side):
+        by_ctypes, said_ctypes = good(), refusals()
+    torch.cuda.synchronize()
+    assert said_module == said_ctypes
+    assert all(torch.equal(x, y) for x, y in zip(by_module, by_ctypes)) and len(by_module) == len(by_ctypes)
+    # what is only another way to hand over the same arguments still works
+    monkeypatch.setattr(binding, "_fast", fast)
+    two = pkg.make_shape(F[0], k)
+    pkg.svdcache_full_step(two, F[0], V[:1], None, R[0], S[:1].contiguous(), None, np.float32(0.5), 1)
+    pkg.svdcache_forecast_combine(shape, (S, S), (0.5, 0.5), V, packed, R, None, Fh)
+    torch.cuda.synchronize()
