@@ -287,11 +287,15 @@ __global__ __launch_bounds__(256) void fit_project_mfma_kernel(const T* __restri
 // 128 (0.66 against 0.88 ms with split operands), 0.41 against 0.53 ms at width 64 with split operands; at width
 // 64 with plain operands the register-stationary kernel stays ahead (0.36 against 0.42 ms).
 // ---------------------------------------------------------------------------
-// PD chunks of F in flight per wave, SD slabs between the request of a slab's operand words and their move to LDS.  Loads
-// return in order, so waiting for the words also waits for every chunk requested before them: with one workgroup per
-// compute unit and little work per chunk (RTW = 1) a slab cannot take less than the memory latency divided by SD.
-template <typename T, int KT, int RTW, int SC, bool SPLIT, bool FRO, int PD = 4, int SD = 1>
-__global__ __launch_bounds__(256) void fit_project_rows_kernel(const T* __restrict__ F,
+// SD slabs between the request of a slab's operand words and their move to LDS.  Loads return in order, so waiting for the
+// words also waits for every chunk requested before them: with one workgroup per compute unit a slab takes the memory
+// latency divided by SD, whatever its work.  So the channels may be cut into KS shares, each with four waves and slabs of its
+// own, and the shares' sums meet in LDS at the end: half as many slabs one after the other, twice the waves to hide them.
+// Width 128, 3072 channels, one share (with SD = 2 and twice the chunks in flight up to 24576 rows) and two: split operands of
+// float32 rows, 4608 rows 84 -> 62 us, 18432 104 -> 95, 32768 150 -> 121, 16 x 4608 441 -> 349; of bf16 rows, 57 x 4608
+// 1033 -> 840; plain operands, 4608 rows 50 -> 37, 4 x 4608 53 -> 41.
+template <typename T, int KT, int RTW, int SC, bool SPLIT, bool FRO, int SD, int KS>
+__global__ __launch_bounds__(256 * KS) void fit_project_rows_kernel(const T* __restrict__ F,
                                                                const uint16_t* __restrict__ Qp, float* Y,
                                                                u32x4* Yp, double* fro_acc, int N, int D, int l,
                                                                int64_t ldf, int64_t bstride,
@@ -301,20 +305,25 @@ __global__ __launch_bounds__(256) void fit_project_rows_kernel(const T* __restri
   // from L2 twice (4 % slower).  With plain operands a slot is refilled as soon as its chunk is done (two chunks
   // in flight instead of four: 3 % slower at width 128).
   constexpr bool PAIRED = SPLIT;
+  constexpr int PD = 4;                       // chunks of F in flight per wave
   static_assert(SC == 2 || SC == 4, "slab of 2 or 4 chunks");
   static_assert(PAIRED || (SC == PD && SD == 1), "without pairing the ring slot of a chunk is its index in the slab");
   constexpr int NP = SPLIT ? 2 : 1;           // operand parts (high, low)
   constexpr int WPW = SC * KT / kWaves;       // operand words a wave stages per slab and part
   static_assert(SC * KT % kWaves == 0, "staging must divide among the waves");
-  __shared__ u32x4 qs[2][NP][SC * KT][64];
+  extern __shared__ u32x4 lds_words[];
   const int b = blockIdx.x / groups_per_block, rg = blockIdx.x % groups_per_block;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int wave = (threadIdx.x >> 6) % kWaves, share = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / 256);
+  auto qs = reinterpret_cast<u32x4(*)[NP][SC * KT][64]>(lds_words + share * 2 * NP * SC * KT * 64);   // two buffers
   const int64_t per = (int64_t)D * KT * 16;
-  const u32x4* Qhi = reinterpret_cast<const u32x4*>(Qp + (int64_t)b * 2 * per);
-  const u32x4* Qlo = reinterpret_cast<const u32x4*>(Qp + (int64_t)b * 2 * per + per);
-  const T* fbase = F + (int64_t)b * bstride + 8 * g;
+  // the slabs of this share (the last one may have one less, or none); all run through `rounds` of them for the barriers
+  const int all = D / (32 * SC), rounds = (all + KS - 1) / KS, first = share * rounds;
+  const int NS = KS == 1 ? all : min(rounds, all - first), NC = NS * SC;
+  const u32x4* Qhi = reinterpret_cast<const u32x4*>(Qp + (int64_t)b * 2 * per) + (int64_t)first * SC * KT * 64;
+  const u32x4* Qlo = reinterpret_cast<const u32x4*>(Qp + (int64_t)b * 2 * per + per) + (int64_t)first * SC * KT * 64;
+  const T* fbase = F + (int64_t)b * bstride + 8 * g + (int64_t)first * SC * 32;
   const int tile0 = (rg * kWaves + wave) * RTW;
-  const int NS = D / (32 * SC), NC = D / 32;
 
   f32x4 acc[RTW][KT];
 #pragma unroll
@@ -346,7 +355,7 @@ __global__ __launch_bounds__(256) void fit_project_rows_kernel(const T* __restri
       for (int p = 0; p < NP; ++p) qs[buf][p][wave * WPW + i][lane] = st[p][i];
   };
   // slab n's words pass through the register set n % SD
-  load_stage(0, stg[0]);
+  if (KS == 1 || NS > 0) load_stage(0, stg[0]);
 #pragma unroll
   for (int u = 0; u < PD; ++u)
     if (u < NC) load_chunk(u, fin[u]);
@@ -357,15 +366,15 @@ __global__ __launch_bounds__(256) void fit_project_rows_kernel(const T* __restri
   __syncthreads();
 
   float ssq = 0.f;
-  // one slab; with paired requests PAR = slab % kCycle is a compile-time value, so that the ring slots and sets are static
-  constexpr int kCycle = PAIRED ? (PD / SC > 2 ? PD / SC : 2) : 1;
-  static_assert(!PAIRED || (kCycle * SC % PD == 0 && kCycle % SD == 0), "ring and sets repeat with the cycle");
+  // one slab; with paired requests PAR = slab % 2 is a compile-time value, so that the ring slots and sets are static
+  static_assert(!PAIRED || (2 * SC % PD == 0 && 2 % SD == 0), "ring and sets repeat with every second slab");
   auto do_slab = [&](int slab, auto par) {
     constexpr int PAR = decltype(par)::value;
     const int buf = PAIRED ? (PAR & 1) : (slab & 1);
     if (slab + SD < NS) load_stage(slab + SD, stg[PAR % SD]);
 #pragma unroll
     for (int c = 0; c < SC; ++c) {
+      if (KS > 1 && slab >= NS) break;
       const int chunk = slab * SC + c;
       constexpr int kSlotBase = (PAR * SC) % PD;
       const int u = (kSlotBase + c) % PD;     // = chunk % PD
@@ -402,21 +411,32 @@ __global__ __launch_bounds__(256) void fit_project_rows_kernel(const T* __restri
     __syncthreads();
   };
   if constexpr (PAIRED) {
-    for (int slab = 0; slab < NS; slab += kCycle) {
+    for (int slab = 0; slab < rounds; slab += 2) {
       do_slab(slab, std::integral_constant<int, 0>{});
-      if (slab + 1 < NS) do_slab(slab + 1, std::integral_constant<int, 1>{});
-      if constexpr (kCycle > 2) {
-        static_assert(kCycle == 4, "two or four slabs");
-        if (slab + 2 < NS) do_slab(slab + 2, std::integral_constant<int, 2>{});
-        if (slab + 3 < NS) do_slab(slab + 3, std::integral_constant<int, 3>{});
-      }
+      if (slab + 1 < rounds) do_slab(slab + 1, std::integral_constant<int, 1>{});
     }
   } else {
-    for (int slab = 0; slab < NS; ++slab) do_slab(slab, std::integral_constant<int, 0>{});
+    for (int slab = 0; slab < rounds; ++slab) do_slab(slab, std::integral_constant<int, 0>{});
   }
   if (FRO) {
     const double s = wave_sum((double)ssq);
     if (lane == 0) atomicAdd(fro_acc + b, s);
+  }
+  if constexpr (KS > 1) {     // the shares meet in LDS (every wave is past the barrier of the last slab)
+    static_assert(KS == 2 && RTW * KT * kWaves <= KS * 2 * NP * SC * KT, "one share's sums fit");
+    f32x4* part = reinterpret_cast<f32x4*>(lds_words) + (int64_t)wave * RTW * KT * 64 + lane;
+    if (share == 1) {
+#pragma unroll
+      for (int t = 0; t < RTW; ++t)
+#pragma unroll
+        for (int jt = 0; jt < KT; ++jt) part[(t * KT + jt) * 64] = acc[t][jt];
+    }
+    __syncthreads();
+    if (share == 1) return;
+#pragma unroll
+    for (int t = 0; t < RTW; ++t)
+#pragma unroll
+      for (int jt = 0; jt < KT; ++jt) acc[t][jt] += part[(t * KT + jt) * 64];
   }
   if constexpr (FPiece<T>::kTwoParts) {
     if (Yp) {   // packed output for the back-projection, tile by tile
@@ -738,28 +758,41 @@ void project_launch(const svdc_shape& s, int l, const void* F, const void* Qp, f
   // wide sketches: rows split over the waves, Q shared through LDS
   if constexpr (KT >= 4) {
     constexpr int RTW = (KT == 8) ? 2 : 3;
-    auto rows = [&](auto rtw, auto sc, auto sp, auto fr) {
-      constexpr int R = decltype(rtw)::value;
-      constexpr bool kDeep = R == 1 && KT == 8;      // one workgroup per compute unit
+    using One = std::integral_constant<int, 1>;
+    using Two = std::integral_constant<int, 2>;
+    using Four = std::integral_constant<int, 4>;
+    auto groups = [&](int rtw) { return (int64_t)((ntile + kWaves * rtw - 1) / (kWaves * rtw)) * s.B; };
+    auto rows = [&](auto rtw, auto sc, auto sp, auto fr, auto sd, auto shares) {
+      constexpr int R = decltype(rtw)::value, KS = decltype(shares)::value;
       const int g = (ntile + kWaves * R - 1) / (kWaves * R);
-      fit_project_rows_kernel<T, KT, R, decltype(sc)::value, decltype(sp)::value, decltype(fr)::value, kDeep ? 8 : 4, kDeep ? 2 : 1>
-          <<<(unsigned)((int64_t)g * s.B), 256, 0, st>>>(f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, g, ld.ldy);
+      auto kernel = fit_project_rows_kernel<T, KT, R, decltype(sc)::value, decltype(sp)::value, decltype(fr)::value, decltype(sd)::value, KS>;
+      constexpr int lds = KS * 2 * (decltype(sp)::value ? 2 : 1) * decltype(sc)::value * KT * 1024;
+      static_assert(lds <= 160 * 1024, "operand buffers");
+      // beyond what a launch may ask for by itself; without it the launch fails, which the caller's check reports
+      if constexpr (lds > 64 * 1024) (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+      kernel<<<(unsigned)((int64_t)g * s.B), 256 * KS, lds, st>>>(f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, g, ld.ldy);
     };
     if (split) {
+      // Width 128: the channels in two shares.  16 rows per wave while that is one round of workgroups (one per compute unit),
+      // 32 from there on (18432 float32 rows: 95 us, 128 us with 16).
+      // Width 64: one share; two take 16 % more time (57 x 4608 bf16 rows: 452 and 529 us).  16 rows where 48 leave compute units idle.
       using SC = std::integral_constant<int, (KT == 8) ? 2 : 4>;
+      using KS = std::integral_constant<int, (KT == 8) ? 2 : 1>;
       auto tall = [&](auto rtw) {
-        if (fro_acc) rows(rtw, SC{}, std::true_type{}, std::true_type{});
-        else rows(rtw, SC{}, std::true_type{}, std::false_type{});
+        if (fro_acc) rows(rtw, SC{}, std::true_type{}, std::true_type{}, KS{}, KS{});
+        else rows(rtw, SC{}, std::true_type{}, std::false_type{}, KS{}, KS{});
       };
-      // fewer workgroups than compute units: 16 rows per wave, deeper prefetch (18432 float32 rows, sketch 128: 122 ->
-      // 110 -> 99 us; 32 rows by half of the coefficient tiles per wave, which halves the LDS reads: 128 us)
-      if ((int64_t)((ntile + kWaves * RTW - 1) / (kWaves * RTW)) * s.B < units) tall(std::integral_constant<int, 1>{});
+      if (KT == 8 ? groups(1) <= units : groups(RTW) < units) tall(One{});
       else tall(std::integral_constant<int, RTW>{});
       return;
     }
     // plain operands from here on: never float32 features
-    if constexpr (KT == 8 && !kF32)
-      rows(std::integral_constant<int, RTW>{}, std::integral_constant<int, 4>{}, std::false_type{}, std::false_type{});
+    if constexpr (KT == 8 && !kF32) {
+      // two shares while that is one round; beyond it two workgroups of one share fit on a compute unit (8 blocks of 4608 x 3072:
+      // 78 us, 86 us with two shares)
+      if (groups(RTW) <= units) rows(Two{}, Four{}, std::false_type{}, std::false_type{}, One{}, Two{});
+      else rows(Two{}, Four{}, std::false_type{}, std::false_type{}, One{}, One{});
+    }
     else if constexpr (!kF32)
       stationary(std::integral_constant<int, TG>{}, std::false_type{});
   } else {

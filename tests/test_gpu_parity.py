@@ -679,6 +679,15 @@ def test_fit_basis_general_products(dtype, B, D, l, N):
     test_fit_basis_at_the_block_edges_of_the_small_matrices(dtype, B, D, l, N - l)
 
 
+@pytest.mark.parametrize("dtype,B,D,l,N", [
+    (torch.bfloat16, 1, 128, 128, 300), (torch.bfloat16, 2, 384, 100, 1001), (torch.float32, 1, 128, 65, 16385),
+    (torch.float32, 1, 640, 128, 515), (torch.bfloat16, 2, 128, 70, 16401)])
+def test_fit_basis_products_in_shares_of_the_channels(dtype, B, D, l, N):
+    """Sketches of 65 to 128 columns: slabs of 2 and 4 chunks in two shares, the second one with as many, one less or none;
+    ragged rows, 16 and 32 per wave, and more of them than the two shares take."""
+    test_fit_basis_at_the_block_edges_of_the_small_matrices(dtype, B, D, l, N - l)
+
+
 @pytest.mark.parametrize("B,l", [(2, 48), (1, 80), (2, 81), (1, 96), (2, 112), (1, 113), (3, 128), (1, 208), (1, 209)])
 def test_fit_basis_at_the_tile_edges_of_the_factor(B, l):
     """Panels of 16 columns: sketches of 65 to 128 columns are factored as a whole, wider ones by blocks of 64."""
