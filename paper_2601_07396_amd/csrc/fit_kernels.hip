@@ -1569,8 +1569,13 @@ int32_t run_fit_typed(const svdc_shape& s, const FitPlan& pl, const T* F, float*
   void* Qp = ws + pl.off_Qp;
   const PackedQ pq = pl.mfma ? fit_mfma_packed_q(s, l, Qp) : PackedQ{};
   bool packed = false;                       // Q is in its packed form already
+  // Between the two products Y has its packed form, which for float32 features is in two parts as large as the float32 rows
+  // themselves, up to the padding of N and l: it may run on into the Gram matrices' areas, not in use at that time, and
+  // stays float32 rows where even that is too small.
+  constexpr bool kF32 = std::is_same<T, float>::value;
+  void* Yp = kF32 && fit_mfma_packed_y_bytes(s, l, 2) > pl.off_M - pl.off_Y ? nullptr : (void*)Y;
   // several row groups accumulate Z with atomics: it has to be clear beforehand
-  const bool zero_z = pl.mfma && fit_mfma_backproject_accumulates(s, l);
+  const bool zero_z = pl.mfma && fit_mfma_backproject_accumulates(s, l, Yp != nullptr);
   bool z_clear = false;
   // With power iterations the Gaussian test matrix (D x l) is used as it is: its columns are well conditioned
   // and every product F^T F Q is re-orthonormalised afterwards.  With none, the sketch is Z = F^T Omega with a
@@ -1591,11 +1596,7 @@ int32_t run_fit_typed(const svdc_shape& s, const FitPlan& pl, const T* F, float*
   const bool want_fro = fro2 != nullptr;
   bool fro_done = false;
   // Y = F Q.  The last product feeds the Rayleigh-Ritz step and uses the full-precision operand split.
-  // float32 features: every product splits both operands.  Between the two products Y has its packed form, which for
-  // float32 features is in two parts as large as the float32 rows themselves, up to the padding of N and l: it may run on
-  // into the Gram matrices' areas, not in use at that time, and stays float32 rows where even that is too small.
-  constexpr bool kF32 = std::is_same<T, float>::value;
-  void* Yp = kF32 && fit_mfma_packed_y_bytes(s, l, 2) > pl.off_M - pl.off_Y ? nullptr : (void*)Y;
+  // float32 features: every product splits both operands.
   auto project = [&](bool last) {
     if (pl.mfma) {
       if (!packed) fit_mfma_pack_q(s, l, Q, Qp, st);

@@ -9,6 +9,7 @@
 // packed bf16 operand words (pack_y_word) instead of float32 rows; the last projection of a fit writes float32 rows
 // for the Gram matrix.  backproject stores Z directly when one workgroup covers all rows of a block and otherwise
 // combines the partial results of its row groups with float atomics (into a Z that its caller cleared, or that it clears itself).
+#include <algorithm>
 #include <type_traits>
 
 #include "svdc_device.h"
@@ -476,6 +477,25 @@ __global__ __launch_bounds__(256 * KS) void fit_project_rows_kernel(const T* __r
     }
 }
 
+// The CW x RS waves of a workgroup, RS of which took different rows of the same channels, add their TILES accumulator tiles: tile t ends up in
+// the wave of share t % RS.
+template <int TILES, int CW, int RS>
+__device__ __forceinline__ void sum_row_shares(f32x4* acc, int wave, int lane) {
+  extern __shared__ u32x4 lds_words[];
+  f32x4* part = reinterpret_cast<f32x4*>(lds_words);
+  const int share = wave / CW;
+#pragma unroll
+  for (int t = 0; t < TILES; ++t)
+    if (t % RS != share) part[(wave * TILES + t) * 64 + lane] = acc[t];
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < TILES; ++t)
+    if (t % RS == share) {
+#pragma unroll
+      for (int o = 1; o < RS; ++o) acc[t] += part[(((wave + o * CW) % (CW * RS)) * TILES + t) * 64 + lane];
+    }
+}
+
 // ---------------------------------------------------------------------------
 // backproject: Z[d][j] += sum_rows F[row][d] Y[row][j] over the workgroup's rows.
 // The contraction runs over token rows, so both operands need 8 consecutive
@@ -490,7 +510,8 @@ __global__ __launch_bounds__(256 * KS) void fit_project_rows_kernel(const T* __r
 // ---------------------------------------------------------------------------
 // PACKED: Y comes as the operand words that the projection wrote (pack_y_word); the rows of a 32-row step are then
 // contracted in that word's order, kk = 8 g + e  <->  row 16 (e / 4) + 4 g + e % 4.
-template <int NCW, int KT, bool PACKED>
+// RS: waves that take every RS-th step of the same channels (backproject_plan).
+template <int NCW, int KT, bool PACKED, int RS>
 __global__ __launch_bounds__(256) void fit_backproject_mfma_kernel(const bf16_t* __restrict__ F,
                                                                    const float* __restrict__ Y,
                                                                    const u32x4* __restrict__ Yp, float* Z, int N,
@@ -500,13 +521,14 @@ __global__ __launch_bounds__(256) void fit_backproject_mfma_kernel(const bf16_t*
   const int slab = blockIdx.x % NS;
   const int rgb = blockIdx.x / NS;
   const int b = rgb / groups_per_block, rg = rgb % groups_per_block;
+  constexpr int CW = kWaves / RS;          // waves that take different channels
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  const int cg0 = (slab * kWaves + wave) * NCW;
+  const int share = wave / CW;
+  const int cg0 = (slab * CW + wave % CW) * NCW;
   const uint32_t* fbase = reinterpret_cast<const uint32_t*>(F + (int64_t)b * bstride + 32 * cg0) + r;
   const int64_t ldw = ldf / 2;   // row stride in 32-bit words
   const float* ybase = Y + (int64_t)b * N * ldy;
-  const int row_begin = rg * rows_per_group;
-  const int row_end = min(N, row_begin + rows_per_group);
+  const int row_end = min(N, (rg + 1) * rows_per_group), row_begin = rg * rows_per_group + 32 * share;
 
   f32x4 acc[NCW][2][KT];
 #pragma unroll
@@ -541,7 +563,7 @@ __global__ __launch_bounds__(256) void fit_backproject_mfma_kernel(const bf16_t*
     }
   };
   if (row_begin < row_end) load_step(row_begin);
-  for (int row0 = row_begin; row0 < row_end; row0 += 32) {
+  for (int row0 = row_begin; row0 < row_end; row0 += 32 * RS) {
     u32x4 yop[KT];
 #pragma unroll
     for (int jt = 0; jt < KT; ++jt) {
@@ -559,7 +581,7 @@ __global__ __launch_bounds__(256) void fit_backproject_mfma_kernel(const bf16_t*
         fop[c][0][w] = __builtin_amdgcn_perm(fw[c][2 * w + 1], fw[c][2 * w], 0x05040100u);
         fop[c][1][w] = __builtin_amdgcn_perm(fw[c][2 * w + 1], fw[c][2 * w], 0x07060302u);
       }
-    if (row0 + 32 < row_end) load_step(row0 + 32);
+    if (row0 + 32 * RS < row_end) load_step(row0 + 32 * RS);
 #pragma unroll
     for (int c = 0; c < NCW; ++c)
 #pragma unroll
@@ -567,6 +589,8 @@ __global__ __launch_bounds__(256) void fit_backproject_mfma_kernel(const bf16_t*
 #pragma unroll
         for (int jt = 0; jt < KT; ++jt) acc[c][p][jt] = mfma16(fop[c][p], yop[jt], acc[c][p][jt]);
   }
+
+  if constexpr (RS > 1) sum_row_shares<NCW * 2 * KT, CW, RS>(&acc[0][0][0], wave, lane);
 
   float* zbase = Z + (int64_t)b * D * ldz;
 #pragma unroll
@@ -576,7 +600,7 @@ __global__ __launch_bounds__(256) void fit_backproject_mfma_kernel(const bf16_t*
 #pragma unroll
       for (int jt = 0; jt < KT; ++jt) {
         const int j = 16 * jt + r;
-        if (j >= l) continue;
+        if (j >= l || (RS > 1 && ((c * 2 + p) * KT + jt) % RS != share)) continue;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int d = 32 * (cg0 + c) + 2 * (4 * g + i) + p;
@@ -593,9 +617,9 @@ __global__ __launch_bounds__(256) void fit_backproject_mfma_kernel(const bf16_t*
 // of its 8 rows, the two float32 channels (2 r, 2 r + 1) of a chunk and splits them.  PACKED: Y comes as the two-part
 // operand words that the projection wrote (store_y_half_words), with the rows of a step in that word's order; otherwise as
 // float32 rows, 8 scalar loads and a split per operand in every wave, which bounded the kernel (18432 x 3072, sketch 128:
-// 134 us, 75 us with the words).  Same output mapping and row-group scheme as the bf16 kernel.
+// 134 us, 75 us with the words, 61 with the waves on different rows).  Same output mapping and row-group scheme as the bf16 kernel.
 // ---------------------------------------------------------------------------
-template <int NCW, int KT, bool PACKED>
+template <int NCW, int KT, bool PACKED, int RS>
 __global__ __launch_bounds__(256) void fit_backproject_f32_kernel(const float* __restrict__ F,
                                                                   const float* __restrict__ Y,
                                                                   const u32x4* __restrict__ Yp, float* Z, int N,
@@ -605,13 +629,14 @@ __global__ __launch_bounds__(256) void fit_backproject_f32_kernel(const float* _
   const int slab = blockIdx.x % NS;
   const int rgb = blockIdx.x / NS;
   const int b = rgb / groups_per_block, rg = rgb % groups_per_block;
+  constexpr int CW = kWaves / RS;          // waves that take different channels
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  const int cg0 = (slab * kWaves + wave) * NCW;
+  const int share = wave / CW;
+  const int cg0 = (slab * CW + wave % CW) * NCW;
   const f32x2* fbase = reinterpret_cast<const f32x2*>(F + (int64_t)b * bstride + 32 * cg0) + r;
   const int64_t ldw = ldf / 2;   // row stride in channel pairs
   const float* ybase = Y + (int64_t)b * N * ldy;
-  const int row_begin = rg * rows_per_group;
-  const int row_end = min(N, row_begin + rows_per_group);
+  const int row_end = min(N, (rg + 1) * rows_per_group), row_begin = rg * rows_per_group + 32 * share;
   const int nsteps = (N + 31) / 32;
 
   f32x4 acc[NCW][2][KT];
@@ -653,7 +678,7 @@ __global__ __launch_bounds__(256) void fit_backproject_f32_kernel(const float* _
     }
   };
   if (row_begin < row_end) load_step(row_begin);
-  for (int row0 = row_begin; row0 < row_end; row0 += 32) {
+  for (int row0 = row_begin; row0 < row_end; row0 += 32 * RS) {
     u32x4 yhi[KT], ylo[KT];
 #pragma unroll
     for (int jt = 0; jt < KT; ++jt) {
@@ -670,7 +695,7 @@ __global__ __launch_bounds__(256) void fit_backproject_f32_kernel(const float* _
         for (int e = 0; e < 8; ++e) c8[e] = fw[c][e][p];
         split_operand(c8, &fhi[c][p], &flo[c][p]);
       }
-    if (row0 + 32 < row_end) load_step(row0 + 32);
+    if (row0 + 32 * RS < row_end) load_step(row0 + 32 * RS);
 #pragma unroll
     for (int c = 0; c < NCW; ++c)
 #pragma unroll
@@ -683,6 +708,8 @@ __global__ __launch_bounds__(256) void fit_backproject_f32_kernel(const float* _
         }
   }
 
+  if constexpr (RS > 1) sum_row_shares<NCW * 2 * KT, CW, RS>(&acc[0][0][0], wave, lane);
+
   float* zbase = Z + (int64_t)b * D * ldz;
 #pragma unroll
   for (int c = 0; c < NCW; ++c)
@@ -691,7 +718,7 @@ __global__ __launch_bounds__(256) void fit_backproject_f32_kernel(const float* _
 #pragma unroll
       for (int jt = 0; jt < KT; ++jt) {
         const int j = 16 * jt + r;
-        if (j >= l) continue;
+        if (j >= l || (RS > 1 && ((c * 2 + p) * KT + jt) % RS != share)) continue;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int d = 32 * (cg0 + c) + 2 * (4 * g + i) + p;
@@ -800,25 +827,24 @@ void project_launch(const svdc_shape& s, int l, const void* F, const void* Qp, f
   }
 }
 
-template <typename T, int NCW, int KT>
+template <typename T, int NCW, int KT, int RS>
 void backproject_launch(const svdc_shape& s, int l, const void* F, const float* Y, const u32x4* Yp, float* Z, int gpb, int rows,
                         Strides ld, hipStream_t st) {
-  const int NS = s.D / (128 * NCW);
+  const int NS = s.D / (32 * NCW * (kWaves / RS));
   const unsigned grid = (unsigned)((int64_t)NS * gpb * s.B);
+  constexpr int lds = RS > 1 ? kWaves * NCW * 2 * KT * 1024 : 0;
+  static_assert(lds <= 160 * 1024, "partial sums");
+  auto go = [&](auto kernel, auto f) {
+    // beyond what a launch may ask for by itself; without it the launch fails, which the caller's check reports
+    if constexpr (lds > 64 * 1024) (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    kernel<<<grid, 256, lds, st>>>(f, Y, Yp, Z, s.N, s.D, l, s.ldf, s.block_stride, NS, gpb, rows, ld.ldy, ld.ldz);
+  };
   if constexpr (std::is_same<T, float>::value) {
-    if (Yp)
-      fit_backproject_f32_kernel<NCW, KT, true><<<grid, 256, 0, st>>>((const float*)F, Y, Yp, Z, s.N, s.D, l, s.ldf,
-                                                                      s.block_stride, NS, gpb, rows, ld.ldy, ld.ldz);
-    else
-      fit_backproject_f32_kernel<NCW, KT, false><<<grid, 256, 0, st>>>((const float*)F, Y, Yp, Z, s.N, s.D, l, s.ldf,
-                                                                       s.block_stride, NS, gpb, rows, ld.ldy, ld.ldz);
+    if (RS > 1 || Yp) go(fit_backproject_f32_kernel<NCW, KT, true, RS>, (const float*)F);
+    else if constexpr (RS == 1) go(fit_backproject_f32_kernel<NCW, KT, false, 1>, (const float*)F);
   } else {
-    if (Yp)
-      fit_backproject_mfma_kernel<NCW, KT, true><<<grid, 256, 0, st>>>((const bf16_t*)F, Y, Yp, Z, s.N, s.D, l, s.ldf,
-                                                                      s.block_stride, NS, gpb, rows, ld.ldy, ld.ldz);
-    else
-      fit_backproject_mfma_kernel<NCW, KT, false><<<grid, 256, 0, st>>>((const bf16_t*)F, Y, Yp, Z, s.N, s.D, l, s.ldf,
-                                                                       s.block_stride, NS, gpb, rows, ld.ldy, ld.ldz);
+    if (RS > 1 || Yp) go(fit_backproject_mfma_kernel<NCW, KT, true, RS>, (const bf16_t*)F);
+    else if constexpr (RS == 1) go(fit_backproject_mfma_kernel<NCW, KT, false, 1>, (const bf16_t*)F);
   }
 }
 
@@ -827,19 +853,36 @@ __global__ void clear_f32_kernel(float* p, int64_t n) {
   if (i < n) p[i] = 0.0f;
 }
 
-// Row groups per block in backproject.  Partial sums of different groups meet in float atomics, which cost
-// more than the parallelism they buy: one group per block as soon as the slabs of all blocks give about one
-// workgroup per compute unit, otherwise just enough groups to reach that.
-template <int NCW>
-void backproject_groups(const svdc_shape& s, int* gpb, int* rows) {
-  const int cus = num_compute_units();
-  const int64_t slabs = (int64_t)(s.D / (128 * NCW)) * s.B;
-  int g = (int)((cus + slabs / 2) / slabs);
-  if (g < 1) g = 1;
-  int r = ((s.N + g - 1) / g + 31) / 32 * 32;
-  if (r < 32) r = 32;
-  *rows = r;
-  *gpb = (s.N + r - 1) / r;
+// How a back-projection runs: whether the waves of a workgroup take different rows of 64 channels (backproject_plan), row groups
+// per block and their rows.
+struct BackPlan {
+  bool shares;
+  int gpb, rows;
+};
+inline BackPlan backproject_rows(const svdc_shape& s, bool shares, int64_t groups) {
+  const int64_t g = std::max<int64_t>(1, groups);
+  const int r = (int)std::max<int64_t>(32, ((s.N + g - 1) / g + 31) / 32 * 32);
+  return {shares, (s.N + r - 1) / r, r};
+}
+// Partial sums of different row groups meet in float atomics (about 250 G/s), which cost more than the parallelism they buy:
+// one group per block as soon as the slabs of all blocks give about one workgroup per compute unit, otherwise just enough
+// groups to reach that.  Then the four waves of a workgroup had better take different rows of 64 channels than different channels
+// of 128 NCW: their sums meet in LDS, and with narrower slabs there are fewer groups and atomics.  One block of 4608 x 3072
+// (18432 x 3072): bf16 width 64 15 -> 12 us (37 -> 25), 128 23 -> 17 (55 -> 33); float32 width 64 29 -> 16 (55 -> 41), 128 45 -> 24
+// (74 -> 61).  Eight waves on 64 channels of 32 each: 10, 25, 15, 36 us for the bf16 figures, 15, 41, 23, 63 for the float32 ones, no better.
+// - Only while the slabs are one round of workgroups (float32, width 64, 6 blocks of 4608 x 3072: 24 us slower), or at width 128,
+//   where few workgroups fit on a compute unit (8 float32 blocks: 52 us faster, 20 bf16 ones 41 us).
+// - From 512 rows on: with fewer the waves have hardly a step each (300 x 1024, bf16, width 64: a fit takes 329 us and 331 us).
+// - As many groups as fit into one round (float32, width 64, 2 blocks of 4608 x 3072: 3 groups in a little more than one round
+//   7 us slower than 2), rounded up where several workgroups fit on a compute unit (bf16, 2 blocks of 9000 x 4224: 12 us faster), and
+//   so that each wave has a step.
+template <typename T, int NCW, int KT>
+BackPlan backproject_plan(const svdc_shape& s, bool packed) {
+  const int64_t cus = num_compute_units(), slabs = (int64_t)(s.D / (128 * NCW)) * s.B, narrow = (int64_t)(s.D / 64) * s.B;
+  const BackPlan wide = backproject_rows(s, false, (cus + slabs / 2) / slabs);
+  if (!packed || wide.gpb == 1 || s.N < 512 || (narrow > cus && KT < 8)) return wide;
+  constexpr bool kSeveral = std::is_same<T, bf16_t>::value && KT <= 4;    // workgroups on a compute unit
+  return backproject_rows(s, true, std::min<int64_t>((kSeveral ? cus + narrow / 2 : cus) / narrow, (s.N + 127) / 128));
 }
 
 // largest instantiated slab width (chunks per wave) that divides D / 128 and is at most `cap` (compile time: what
@@ -871,13 +914,13 @@ void project_kt(const svdc_shape& s, int l, const void* F, const void* Qp, float
 template <typename T, int NCW, int KT>
 void backproject_one(const svdc_shape& s, int l, const void* F, const float* Y, const u32x4* Yp, float* Z,
                      Strides ld, hipStream_t st) {
-  int gpb, rows;
-  backproject_groups<NCW>(s, &gpb, &rows);
-  if (gpb > 1 && !ld.z_cleared) {   // atomics accumulate into Z (a single column range: Z is contiguous)
+  const BackPlan plan = backproject_plan<T, NCW, KT>(s, Yp != nullptr);
+  if (plan.gpb > 1 && !ld.z_cleared) {   // atomics accumulate into Z (a single column range: Z is contiguous)
     const int64_t n = (int64_t)s.B * s.D * l;
     clear_f32_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(Z, n);
   }
-  backproject_launch<T, NCW, KT>(s, l, F, Y, Yp, Z, gpb, rows, ld, st);
+  if (plan.shares) backproject_launch<T, 2, KT, kWaves>(s, l, F, Y, Yp, Z, plan.gpb, plan.rows, ld, st);
+  else backproject_launch<T, NCW, KT, 1>(s, l, F, Y, Yp, Z, plan.gpb, plan.rows, ld, st);
 }
 
 // slab widths of the float32 back-projection (twice the registers per loaded row, two operand parts on each side)
@@ -1018,21 +1061,19 @@ PackedQ fit_mfma_packed_q(const svdc_shape& s, int l, void* Qp) {
   return q;
 }
 
-bool fit_mfma_backproject_accumulates(const svdc_shape& s, int l) {
+bool fit_mfma_backproject_accumulates(const svdc_shape& s, int l, bool packed) {
   ColRange r[2];
   const int n = col_ranges(l, r);
   bool any = false;
   for (int h = 0; h < n; ++h)
     by_kt(r[h].l, [&](auto kt) {
       constexpr int KT = decltype(kt)::value;
-      auto groups = [&](auto ncw) {
-        int gpb, rows;
-        backproject_groups<decltype(ncw)::value>(s, &gpb, &rows);
-        any = any || gpb > 1;
+      auto asks = [&](auto elem) {
+        using T = decltype(elem);
+        backproject_by_width<T, KT>(s, packed, [&](auto ncw) { any = any || backproject_plan<T, decltype(ncw)::value, KT>(s, packed).gpb > 1; });
       };
-      // the power iterations hand bf16 features' Y over in packed form; the width for float32 features does not depend on it
-      if (s.dtype == SVDC_F32) backproject_by_width<float, KT>(s, false, groups);
-      else backproject_by_width<bf16_t, KT>(s, true, groups);
+      if (s.dtype == SVDC_F32) asks(float{});
+      else asks(bf16_t{});
     });
   return any;
 }

@@ -104,7 +104,7 @@ void fit_mfma_project(const svdc_shape& s, int l, const void* F, const void* Qp,
 // Z = F^T Y, with Y as float32 rows or (Ypacked != nullptr) in the packed form; z_clear: Z holds zeros already
 void fit_mfma_backproject(const svdc_shape& s, int l, const void* F, const float* Y, const void* Ypacked, float* Z,
                           bool z_clear, hipStream_t st);
-// whether the product of a power iteration accumulates into Z (several row groups), which then has to hold zeros
-bool fit_mfma_backproject_accumulates(const svdc_shape& s, int l);
+// whether the product of a power iteration accumulates into Z (several row groups), which then has to hold zeros; packed: Y's form
+bool fit_mfma_backproject_accumulates(const svdc_shape& s, int l, bool packed);
 
 }  // namespace svdc

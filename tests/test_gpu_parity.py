@@ -688,6 +688,17 @@ def test_fit_basis_products_in_shares_of_the_channels(dtype, B, D, l, N):
     test_fit_basis_at_the_block_edges_of_the_small_matrices(dtype, B, D, l, N - l)
 
 
+@pytest.mark.parametrize("dtype,B,D,l,N", [
+    (torch.bfloat16, 1, 128, 12, 513), (torch.bfloat16, 2, 640, 30, 1300), (torch.bfloat16, 5, 1152, 64, 512),
+    (torch.bfloat16, 1, 384, 128, 700), (torch.bfloat16, 1, 640, 200, 1029), (torch.float32, 1, 128, 20, 545),
+    (torch.float32, 5, 1152, 40, 600), (torch.float32, 1, 384, 100, 1029), (torch.float32, 1, 640, 136, 2017),
+    (torch.float32, 22, 768, 80, 514)])
+def test_fit_basis_products_in_shares_of_the_rows(dtype, B, D, l, N):
+    """Back-projections of small batches: the waves of a workgroup take every fourth step of 32 rows, some of them none; one and
+    several groups of rows, one and two column ranges, more slabs than compute units."""
+    test_fit_basis_at_the_block_edges_of_the_small_matrices(dtype, B, D, l, N - l)
+
+
 @pytest.mark.parametrize("B,l", [(2, 48), (1, 80), (2, 81), (1, 96), (2, 112), (1, 113), (3, 128), (1, 208), (1, 209)])
 def test_fit_basis_at_the_tile_edges_of_the_factor(B, l):
     """Panels of 16 columns: sketches of 65 to 128 columns are factored as a whole, wider ones by blocks of 64."""
