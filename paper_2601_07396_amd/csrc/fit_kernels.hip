@@ -784,8 +784,6 @@ __device__ __forceinline__ void xor_rows(double& x, double& y) {
   }
 }
 
-constexpr int kJacobiThreads = 512;
-
 // The rotation that makes two columns with squared norms al, be and inner product ga orthogonal: x' = cs x - sn y,
 // y' = sn x + cs y.  False (and nothing set) when they are orthogonal to 1e-7 already (compared in squares, no sqrt): the
 // outputs are float32, and a sweep that finds nothing above the threshold ends the iteration.  *big is set when the cosine of
@@ -820,9 +818,7 @@ __device__ __forceinline__ bool jacobi_angle(double al, double be, double ga, do
 // unroll with a fixed trip count, their LDS loads are issued together, and the elements stay in registers between
 // the dot products and the rotation.  A rotation above the threshold of jacobi_angle sets *big (a flag in a register:
 // the caller publishes it once per sweep).
-// PAD: the columns are stored with TP * NE elements, zero beyond l (zeros stay zero under a rotation), so that no
-// load or store needs a bounds check (each conditional store is a branch).
-template <int NE, int TP, bool PAD>
+template <int NE, int TP>
 __device__ __forceinline__ void jacobi_rotate(double* ap, double* aq, int l, int gl, int* big) {
   static_assert(TP <= 16, "sums inside a row of 16 lanes");
   double al = 0.0, be = 0.0, ga = 0.0;
@@ -830,8 +826,8 @@ __device__ __forceinline__ void jacobi_rotate(double* ap, double* aq, int l, int
 #pragma unroll
   for (int e = 0; e < NE; ++e) {
     const int r = gl + e * TP;
-    xs[e] = (PAD || r < l) ? ap[r] : 0.0;
-    ys[e] = (PAD || r < l) ? aq[r] : 0.0;
+    xs[e] = r < l ? ap[r] : 0.0;
+    ys[e] = r < l ? aq[r] : 0.0;
   }
 #pragma unroll
   for (int e = 0; e < NE; ++e) {
@@ -843,7 +839,7 @@ __device__ __forceinline__ void jacobi_rotate(double* ap, double* aq, int l, int
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
       const int r = gl + e * TP;
-      if (PAD || r < l) {
+      if (r < l) {
         ap[r] = cs * xs[e] - sn * ys[e];
         aq[r] = sn * xs[e] + cs * ys[e];
       }
@@ -1165,7 +1161,7 @@ __global__ __launch_bounds__(NT) void jacobi_kernel(const double* __restrict__ L
     RoundRobin rr;
     rr.start(le, active ? group : 0);
     for (int step = 0; step < le - 1; ++step) {
-      if (active && rr.p < l && rr.q < l) jacobi_rotate<NE, TP, false>(A + rr.p * la, A + rr.q * la, l, gl, &my_big);
+      if (active && rr.p < l && rr.q < l) jacobi_rotate<NE, TP>(A + rr.p * la, A + rr.q * la, l, gl, &my_big);
       rr.next();
       __syncthreads();
     }
