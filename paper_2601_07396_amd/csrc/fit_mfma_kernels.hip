@@ -293,10 +293,11 @@ __global__ __launch_bounds__(256) void fit_project_mfma_kernel(const T* __restri
 // latency divided by SD, whatever its work.  So the channels may be cut into KS shares, each with four waves and slabs of its
 // own, and the shares' sums meet in LDS at the end: half as many slabs one after the other, twice the waves to hide them.
 // Width 128, 3072 channels, one share (with SD = 2 and twice the chunks in flight up to 24576 rows) and two: split operands of
-// float32 rows, 4608 rows 84 -> 62 us, 18432 104 -> 95, 32768 150 -> 121, 16 x 4608 441 -> 349; of bf16 rows, 57 x 4608
-// 1033 -> 840; plain operands, 4608 rows 50 -> 37, 4 x 4608 53 -> 41.
+// float32 rows, 4608 rows 84 -> 62 us, 18432 104 -> 95, 32768 150 -> 117, 16 x 4608 448 -> 341; of bf16 rows, 4608 rows 70 -> 56;
+// plain operands, 4608 rows 50 -> 37, 4 x 4608 53 -> 41.  bf16 rows in larger calls keep one share and two workgroups per compute
+// unit, which the bound on the registers is for (57 x 4608, split: 657 us, 840 with two shares).
 template <typename T, int KT, int RTW, int SC, bool SPLIT, bool FRO, int SD, int KS>
-__global__ __launch_bounds__(256 * KS) void fit_project_rows_kernel(const T* __restrict__ F,
+__global__ __launch_bounds__(256 * KS, KS == 1 && KT == 8 ? 2 : 1) void fit_project_rows_kernel(const T* __restrict__ F,
                                                                const uint16_t* __restrict__ Qp, float* Y,
                                                                u32x4* Yp, double* fro_acc, int N, int D, int l,
                                                                int64_t ldf, int64_t bstride,
@@ -312,11 +313,18 @@ __global__ __launch_bounds__(256 * KS) void fit_project_rows_kernel(const T* __r
   constexpr int NP = SPLIT ? 2 : 1;           // operand parts (high, low)
   constexpr int WPW = SC * KT / kWaves;       // operand words a wave stages per slab and part
   static_assert(SC * KT % kWaves == 0, "staging must divide among the waves");
-  extern __shared__ u32x4 lds_words[];
   const int b = blockIdx.x / groups_per_block, rg = blockIdx.x % groups_per_block;
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
   const int wave = (threadIdx.x >> 6) % kWaves, share = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / 256);
-  auto qs = reinterpret_cast<u32x4(*)[NP][SC * KT][64]>(lds_words + share * 2 * NP * SC * KT * 64);   // two buffers
+  u32x4* words;
+  if constexpr (KS == 1) {
+    __shared__ u32x4 own[2 * NP * SC * KT * 64];
+    words = own;
+  } else {                                    // more than a static allocation may have
+    extern __shared__ u32x4 lds_words[];
+    words = lds_words + share * 2 * NP * SC * KT * 64;
+  }
+  auto qs = reinterpret_cast<u32x4(*)[NP][SC * KT][64]>(words);   // two buffers
   const int64_t per = (int64_t)D * KT * 16;
   // the slabs of this share (the last one may have one less, or none); all run through `rounds` of them for the barriers
   const int all = D / (32 * SC), rounds = (all + KS - 1) / KS, first = share * rounds;
@@ -425,7 +433,7 @@ __global__ __launch_bounds__(256 * KS) void fit_project_rows_kernel(const T* __r
   }
   if constexpr (KS > 1) {     // the shares meet in LDS (every wave is past the barrier of the last slab)
     static_assert(KS == 2 && RTW * KT * kWaves <= KS * 2 * NP * SC * KT, "one share's sums fit");
-    f32x4* part = reinterpret_cast<f32x4*>(lds_words) + (int64_t)wave * RTW * KT * 64 + lane;
+    f32x4* part = reinterpret_cast<f32x4*>(words - share * 2 * NP * SC * KT * 64) + (int64_t)wave * RTW * KT * 64 + lane;
     if (share == 1) {
 #pragma unroll
       for (int t = 0; t < RTW; ++t)
@@ -523,8 +531,8 @@ __global__ __launch_bounds__(256) void fit_backproject_mfma_kernel(const bf16_t*
   const int b = rgb / groups_per_block, rg = rgb % groups_per_block;
   constexpr int CW = kWaves / RS;          // waves that take different channels
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  const int share = wave / CW;
-  const int cg0 = (slab * CW + wave % CW) * NCW;
+  const int share = RS == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave / CW);
+  const int cg0 = (slab * CW + (RS == 1 ? wave : wave % CW)) * NCW;
   const uint32_t* fbase = reinterpret_cast<const uint32_t*>(F + (int64_t)b * bstride + 32 * cg0) + r;
   const int64_t ldw = ldf / 2;   // row stride in 32-bit words
   const float* ybase = Y + (int64_t)b * N * ldy;
@@ -631,8 +639,8 @@ __global__ __launch_bounds__(256) void fit_backproject_f32_kernel(const float* _
   const int b = rgb / groups_per_block, rg = rgb % groups_per_block;
   constexpr int CW = kWaves / RS;          // waves that take different channels
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  const int share = wave / CW;
-  const int cg0 = (slab * CW + wave % CW) * NCW;
+  const int share = RS == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave / CW);
+  const int cg0 = (slab * CW + (RS == 1 ? wave : wave % CW)) * NCW;
   const f32x2* fbase = reinterpret_cast<const f32x2*>(F + (int64_t)b * bstride + 32 * cg0) + r;
   const int64_t ldw = ldf / 2;   // row stride in channel pairs
   const float* ybase = Y + (int64_t)b * N * ldy;
@@ -793,24 +801,30 @@ void project_launch(const svdc_shape& s, int l, const void* F, const void* Qp, f
       constexpr int R = decltype(rtw)::value, KS = decltype(shares)::value;
       const int g = (ntile + kWaves * R - 1) / (kWaves * R);
       auto kernel = fit_project_rows_kernel<T, KT, R, decltype(sc)::value, decltype(sp)::value, decltype(fr)::value, decltype(sd)::value, KS>;
-      constexpr int lds = KS * 2 * (decltype(sp)::value ? 2 : 1) * decltype(sc)::value * KT * 1024;
+      constexpr int lds = KS == 1 ? 0 : KS * 2 * (decltype(sp)::value ? 2 : 1) * decltype(sc)::value * KT * 1024;
       static_assert(lds <= 160 * 1024, "operand buffers");
       // beyond what a launch may ask for by itself; without it the launch fails, which the caller's check reports
       if constexpr (lds > 64 * 1024) (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
       kernel<<<(unsigned)((int64_t)g * s.B), 256 * KS, lds, st>>>(f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, g, ld.ldy);
     };
     if (split) {
-      // Width 128: the channels in two shares.  16 rows per wave while that is one round of workgroups (one per compute unit),
-      // 32 from there on (18432 float32 rows: 95 us, 128 us with 16).
+      // Width 128: the channels in two shares, 16 rows per wave while that is one round of workgroups (one per compute unit),
+      // 32 from there on (18432 float32 rows: 95 us, 128 us with 16); bf16 rows beyond that in one share (kernel comment).
       // Width 64: one share; two take 16 % more time (57 x 4608 bf16 rows: 452 and 529 us).  16 rows where 48 leave compute units idle.
       using SC = std::integral_constant<int, (KT == 8) ? 2 : 4>;
-      using KS = std::integral_constant<int, (KT == 8) ? 2 : 1>;
-      auto tall = [&](auto rtw) {
-        if (fro_acc) rows(rtw, SC{}, std::true_type{}, std::true_type{}, KS{}, KS{});
-        else rows(rtw, SC{}, std::true_type{}, std::false_type{}, KS{}, KS{});
+      auto tall = [&](auto rtw, auto ks) {
+        if (fro_acc) rows(rtw, SC{}, std::true_type{}, std::true_type{}, ks, ks);
+        else rows(rtw, SC{}, std::true_type{}, std::false_type{}, ks, ks);
       };
-      if (KT == 8 ? groups(1) <= units : groups(RTW) < units) tall(One{});
-      else tall(std::integral_constant<int, RTW>{});
+      if constexpr (KT == 8) {
+        if (groups(1) <= units) tall(One{}, Two{});
+        else if (kF32 || groups(RTW) <= units) tall(Two{}, Two{});
+        else if constexpr (!kF32) tall(Two{}, One{});
+      } else if (groups(RTW) < units) {
+        tall(One{}, One{});
+      } else {
+        tall(std::integral_constant<int, RTW>{}, One{});
+      }
       return;
     }
     // plain operands from here on: never float32 features
@@ -871,7 +885,8 @@ inline BackPlan backproject_rows(const svdc_shape& s, bool shares, int64_t group
 // (18432 x 3072): bf16 width 64 15 -> 12 us (37 -> 25), 128 23 -> 17 (55 -> 33); float32 width 64 29 -> 16 (55 -> 41), 128 45 -> 24
 // (74 -> 61).  Eight waves on 64 channels of 32 each: 10, 25, 15, 36 us for the bf16 figures, 15, 41, 23, 63 for the float32 ones, no better.
 // - Only while the slabs are one round of workgroups (float32, width 64, 6 blocks of 4608 x 3072: 24 us slower), or at width 128,
-//   where few workgroups fit on a compute unit (8 float32 blocks: 52 us faster, 20 bf16 ones 41 us).
+//   where few workgroups fit on a compute unit, instead of three or more groups (8 blocks: float32 45 us faster, bf16 78 -> 67 us;
+//   16 bf16 blocks, 2 groups: 125 -> 141 us).
 // - From 512 rows on: with fewer the waves have hardly a step each (300 x 1024, bf16, width 64: a fit takes 329 us and 331 us).
 // - As many groups as fit into one round (float32, width 64, 2 blocks of 4608 x 3072: 3 groups in a little more than one round
 //   7 us slower than 2), rounded up where several workgroups fit on a compute unit (bf16, 2 blocks of 9000 x 4224: 12 us faster), and
@@ -880,7 +895,7 @@ template <typename T, int NCW, int KT>
 BackPlan backproject_plan(const svdc_shape& s, bool packed) {
   const int64_t cus = num_compute_units(), slabs = (int64_t)(s.D / (128 * NCW)) * s.B, narrow = (int64_t)(s.D / 64) * s.B;
   const BackPlan wide = backproject_rows(s, false, (cus + slabs / 2) / slabs);
-  if (!packed || wide.gpb == 1 || s.N < 512 || (narrow > cus && KT < 8)) return wide;
+  if (!packed || wide.gpb == 1 || s.N < 512 || (narrow > cus && !(KT == 8 && wide.gpb >= 3))) return wide;
   constexpr bool kSeveral = std::is_same<T, bf16_t>::value && KT <= 4;    // workgroups on a compute unit
   return backproject_rows(s, true, std::min<int64_t>((kSeveral ? cus + narrow / 2 : cus) / narrow, (s.N + 127) / 128));
 }
