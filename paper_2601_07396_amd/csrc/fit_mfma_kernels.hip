@@ -625,7 +625,7 @@ __global__ __launch_bounds__(256) void fit_backproject_mfma_kernel(const bf16_t*
 // of its 8 rows, the two float32 channels (2 r, 2 r + 1) of a chunk and splits them.  PACKED: Y comes as the two-part
 // operand words that the projection wrote (store_y_half_words), with the rows of a step in that word's order; otherwise as
 // float32 rows, 8 scalar loads and a split per operand in every wave, which bounded the kernel (18432 x 3072, sketch 128:
-// 134 us, 75 us with the words, 61 with the waves on different rows).  Same output mapping and row-group scheme as the bf16 kernel.
+// 134 us, 75 us with the words, 55 with the waves on different rows).  Same output mapping and row-group scheme as the bf16 kernel.
 // ---------------------------------------------------------------------------
 template <int NCW, int KT, bool PACKED, int RS>
 __global__ __launch_bounds__(256) void fit_backproject_f32_kernel(const float* __restrict__ F,
@@ -883,7 +883,7 @@ inline BackPlan backproject_rows(const svdc_shape& s, bool shares, int64_t group
 // groups to reach that.  Then the four waves of a workgroup had better take different rows of 64 channels than different channels
 // of 128 NCW: their sums meet in LDS, and with narrower slabs there are fewer groups and atomics.  One block of 4608 x 3072
 // (18432 x 3072): bf16 width 64 15 -> 12 us (37 -> 25), 128 23 -> 17 (55 -> 33); float32 width 64 29 -> 16 (55 -> 41), 128 45 -> 24
-// (74 -> 61).  Eight waves on 64 channels of 32 each: 10, 25, 15, 36 us for the bf16 figures, 15, 41, 23, 63 for the float32 ones, no better.
+// (74 -> 55).  Eight waves on 64 channels of 32 each: 10, 25, 15, 36 us for the bf16 figures, 15, 41, 23, 63 for the float32 ones, no better.
 // - Only while the slabs are one round of workgroups (float32, width 64, 6 blocks of 4608 x 3072: 24 us slower), or at width 128,
 //   where few workgroups fit on a compute unit, instead of three or more groups (8 blocks: float32 45 us faster, bf16 78 -> 67 us;
 //   16 bf16 blocks, 2 groups: 125 -> 141 us).
