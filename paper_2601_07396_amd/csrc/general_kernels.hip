@@ -78,6 +78,76 @@ __device__ __forceinline__ void reconstruct(const float* v, const float* cs, flo
   }
 }
 
+// A wave's share of C = F V on the float32 matrix cores: its lane's token row `frow` x the 16 KT coefficients from j0, every
+// kStepWaves-th chunk of 32 channels.  Leaves the sums in vlds, [KT][64] results of four, and ends with a barrier.
+constexpr int kStepWaves = 8;
+template <typename T, int KT>
+__device__ __forceinline__ void project_share(const T* frow, const float* v, float* vlds, int D, int k, int j0, int wave,
+                                              int nchunk) {
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  struct alignas(4 * KT) RowVec { float v[KT]; };
+  f32x4 acc[KT][4], tot[KT];
+#pragma unroll
+  for (int jt = 0; jt < KT; ++jt) {
+    tot[jt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int h = 0; h < 4; ++h) acc[jt][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  Piece<T> fn;
+  VPiece<KT> vp;
+  if (wave < nchunk) {
+    fn.load(frow, 32 * wave + 8 * g, D);
+    vp.load(v, D, k, wave, j0);
+  }
+  for (int c = wave; c < nchunk; c += kStepWaves) {
+    const Piece<T> f = fn;
+    vp.to_lds(vlds);
+    if (c + kStepWaves < nchunk) {
+      fn.load(frow, 32 * (c + kStepWaves) + 8 * g, D);
+      vp.load(v, D, k, c + kStepWaves, j0);
+    }
+    if (c >= 2 * kStepWaves && (c / kStepWaves) % 2 == 0) {
+#pragma unroll
+      for (int jt = 0; jt < KT; ++jt) {
+        tot[jt] += (acc[jt][0] + acc[jt][1]) + (acc[jt][2] + acc[jt][3]);
+#pragma unroll
+        for (int h = 0; h < 4; ++h) acc[jt][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      // columns of the result tile jt: j0 + KT r + jt, so that one wide LDS read brings the operands of all tiles
+      const float x = f.get(e);
+      const RowVec vv = *reinterpret_cast<const RowVec*>(vlds + (8 * g + e) * VPiece<KT>::KS + KT * r);
+#pragma unroll
+      for (int jt = 0; jt < KT; ++jt) acc[jt][e & 3] = mfma_f32(x, vv.v[jt], acc[jt][e & 3]);
+    }
+  }
+  f32x4* part = reinterpret_cast<f32x4*>(vlds);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+  for (int jt = 0; jt < KT; ++jt) {
+    f32x4 s;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      s[i] = (float)((((double)acc[jt][0][i] + acc[jt][1][i]) + ((double)acc[jt][2][i] + acc[jt][3][i])) + tot[jt][i]);
+    part[jt * 64 + lane] = s;
+  }
+  __syncthreads();
+}
+
+// The sum of the waves' results of a tile, `stage` floats apart.
+__device__ __forceinline__ f32x4 sum_shares(const float* part, int stage, int tile) {
+  double c[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int w = 0; w < kStepWaves; ++w) {
+    const f32x4 p = reinterpret_cast<const f32x4*>(part + w * stage)[tile * 64 + (threadIdx.x & 63)];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c[i] += (double)p[i];
+  }
+  return f32x4{(float)c[0], (float)c[1], (float)c[2], (float)c[3]};
+}
+
 // Full-compute step (Eq. 8-11): C = F V, R = F - C V^T, EMA update of S.  A workgroup takes 16 token rows; its eight
 // waves take every eighth chunk of 32 channels.  Phase 1 projects, 16 KT coefficients at a time, with four accumulators per
 // result tile, which leaves registers for two workgroups per compute unit; the waves' partial sums meet in LDS.  The
@@ -87,7 +157,6 @@ __device__ __forceinline__ void reconstruct(const float* v, const float* cs, flo
 // 256 rows and ranks of several passes.
 // Phase 2 forms the residual chunk by chunk.  F and R may alias, R and Rp too: phase 1 has read all of the workgroup's
 // rows before the barrier, and phase 2 reads every element in the lane that overwrites it.
-constexpr int kStepWaves = 8;
 template <typename T, int KT>
 __global__ __launch_bounds__(64 * kStepWaves, 4) void full_step_general_kernel(const T* F, const float* __restrict__ V, T* R,
                                                                             const T* Rp, float alpha_r, float* S,
@@ -103,71 +172,17 @@ __global__ __launch_bounds__(64 * kStepWaves, 4) void full_step_general_kernel(c
   const int nchunk = (D + 31) / 32;
   const float* v = V + (int64_t)b * D * k;
   float* vlds = vstage[wave];
-  struct alignas(4 * KT) RowVec { float v[KT]; };
   const int64_t roff = (int64_t)b * bstride + (int64_t)min(row0 + r, N - 1) * ldf;
 
   for (int j0 = 0; j0 < k; j0 += 16 * KT) {
-    f32x4 acc[KT][4], tot[KT];
-#pragma unroll
-    for (int jt = 0; jt < KT; ++jt) {
-      tot[jt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int h = 0; h < 4; ++h) acc[jt][h] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-    Piece<T> fn;
-    VPiece<KT> vp;
-    if (wave < nchunk) {
-      fn.load(F + roff, 32 * wave + 8 * g, D);
-      vp.load(v, D, k, wave, j0);
-    }
-    for (int c = wave; c < nchunk; c += kStepWaves) {
-      const Piece<T> f = fn;
-      vp.to_lds(vlds);
-      if (c + kStepWaves < nchunk) {
-        fn.load(F + roff, 32 * (c + kStepWaves) + 8 * g, D);
-        vp.load(v, D, k, c + kStepWaves, j0);
-      }
-      if (c >= 2 * kStepWaves && (c / kStepWaves) % 2 == 0) {
-#pragma unroll
-        for (int jt = 0; jt < KT; ++jt) {
-          tot[jt] += (acc[jt][0] + acc[jt][1]) + (acc[jt][2] + acc[jt][3]);
-#pragma unroll
-          for (int h = 0; h < 4; ++h) acc[jt][h] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        // columns of the result tile jt: j0 + KT r + jt, so that one wide LDS read brings the operands of all tiles
-        const float x = f.get(e);
-        const RowVec vv = *reinterpret_cast<const RowVec*>(vlds + (8 * g + e) * VPiece<KT>::KS + KT * r);
-#pragma unroll
-        for (int jt = 0; jt < KT; ++jt) acc[jt][e & 3] = mfma_f32(x, vv.v[jt], acc[jt][e & 3]);
-      }
-    }
-    f32x4* part = reinterpret_cast<f32x4*>(vlds);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-#pragma unroll
-    for (int jt = 0; jt < KT; ++jt) {
-      f32x4 s;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        s[i] = (float)((((double)acc[jt][0][i] + acc[jt][1][i]) + ((double)acc[jt][2][i] + acc[jt][3][i])) + tot[jt][i]);
-      part[jt * 64 + lane] = s;
-    }
-    __syncthreads();
+    project_share<T, KT>(F + roff, v, vlds, D, k, j0, wave, nchunk);
     // D[m = 4 g + i][n = r]: row 4 g + i, coefficient j0 + KT r + jt
     if (wave < KT) {
       const int j = j0 + KT * r + wave;
-      double c[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int w = 0; w < kStepWaves; ++w) {
-        const f32x4 p = reinterpret_cast<const f32x4*>(vstage[w])[wave * 64 + lane];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) c[i] += (double)p[i];
-      }
+      const f32x4 c = sum_shares(vstage[0], VPiece<KT>::kFloats, wave);
       if (j < CS - 4) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) cs[(4 * g + i) * CS + j] = j < k ? (float)c[i] : 0.f;
+        for (int i = 0; i < 4; ++i) cs[(4 * g + i) * CS + j] = j < k ? c[i] : 0.f;
       }
     }
     __syncthreads();
@@ -257,21 +272,29 @@ __global__ __launch_bounds__(64 * kCachedWaves, 4) void forecast_general_kernel(
 
 // ---------------------------------------------------------------------------
 // The same two steps with the products on the bf16 matrix cores, for ranks of 17 to 128 where step_tiling.h says so: a float32
-// is the exact sum of three bf16 parts (8 significant bits each), a product of two keeps six of the nine products of parts
-// (what is dropped is below 2^-26 of it), and a bf16 feature is one part already.  An instruction contracts 32 channels or
+// is the exact sum of three bf16 parts (8 significant bits each), a product of two keeps six of the nine products of parts,
+// and a bf16 feature is one part already, whose products with V are whole.  The three that are dropped are at most 2^-24 of the
+// product, half a unit of a float32 in the last place (parts are up to 2^-8 and 2^-17 of what is split), and 2^-27.5 in the mean.  An instruction contracts 32 channels or
 // coefficients at 16 times the rate of the float32 one, so six cost less than half of it; what bounds the kernels instead are
 // the vector instructions (11 for every pair of elements of V that is split, 70 for every row tile and chunk that is put
 // together), which is why 32 or 48 rows share a piece of V.  The leading products of every chunk are added up in float64:
 // C is within 2.8e-8 of its norm of the float64 product at 1408 and 2.8e-8 at 3304 channels, 3.4e-8 with float32 instructions.
-// Measured at 4 x 2173 x 1408 bf16, rank 50: full step 68 -> 44 us, cached step 31 -> 23 us; 22848 x 2136 at rank 21: 110 -> 73
-// and 67 -> 47 us.
+// Measured at 4 x 2173 x 1408 bf16, rank 50: full step 68 -> 46 us, cached step 31 -> 24 us (44 and 23 with parts that do not
+// reach the whole range); 22848 x 2136 at rank 21: 110 -> 73 and 67 -> 47 us.
 // ---------------------------------------------------------------------------
+// What is split is multiplied by 2^24 first, so that the third part of the smallest normal float32 is a normal bf16 too: the sum
+// of the parts is exact for everything below 2^104 in magnitude.  Beyond that, at an infinity or a NaN the parts hold an infinity
+// or a NaN and so does every result that they are part of; those results are formed once more on the float32 matrix cores
+// (the second pass of the full step, reconstruct_parts), as the kernels above do.
+constexpr float kPartScale = 0x1p24f;
+constexpr float kPartProduct = 0x1p-48f;      // of a product whose factors were both split
+constexpr float kMaxFinite = 3.402823466e38f;
 struct Parts { u32x4 p[3]; };
 __device__ __forceinline__ Parts split_parts(const float (&x)[8]) {
   Parts out;
   float rem[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) rem[e] = x[e];
+  for (int e = 0; e < 8; ++e) rem[e] = x[e] * kPartScale;
 #pragma unroll
   for (int n = 0; n < 3; ++n)
 #pragma unroll
@@ -316,16 +339,59 @@ __device__ __forceinline__ int pair_chunks(int nchunk, int wave, int waves) {
   return 2 * mine - (mine > 0 && (nchunk & 1) && (pairs - 1) % waves == wave ? 1 : 0);
 }
 
+// A piece of V in LDS times 32 coefficients of 16 RT rows, as operand words `cw` of the piece's first row tile, `tiles` row tiles apart.
+template <int RT>
+__device__ __forceinline__ void piece_products(const float* vlds, const u32x4* cw, int tiles, f32x4 (&lead)[RT][2], f32x4 (&rest)[RT][2]) {
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  Parts a[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    const float* row = vlds + (8 * (r >> 2) + 4 * t + (r & 3)) * VPiece<2>::KS + 8 * g;
+    const f32x4 x0 = *reinterpret_cast<const f32x4*>(row), x1 = *reinterpret_cast<const f32x4*>(row + 4);
+    const float x[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+    a[t] = split_parts(x);
+  }
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+    Parts b;
+#pragma unroll
+    for (int n = 0; n < 3; ++n) b.p[n] = cw[(rt * tiles * 3 + n) * 64 + lane];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) feature_product(a[t], b, lead[rt][t], rest[rt][t]);
+  }
+}
+template <int RT>
+__device__ __forceinline__ void clear_products(f32x4 (&lead)[RT][2], f32x4 (&rest)[RT][2]) {
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) lead[rt][t] = rest[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+// lead += rest; whether all of the wave's results are finite
+template <int RT>
+__device__ __forceinline__ bool finish_products(f32x4 (&lead)[RT][2], const f32x4 (&rest)[RT][2]) {
+  float top = 0.f;
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      lead[rt][t] += rest[rt][t];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) top = __builtin_elementwise_maximum(top, __builtin_fabsf(lead[rt][t][q]));   // a NaN stays
+    }
+  return __builtin_amdgcn_ballot_w64(!(top <= kMaxFinite)) == 0;
+}
+
 // P = C V^T of 16 RT rows for the wave's chunks, C as operand words in LDS: cw[(rt kt2 + kt) 3 + part][lane], lane (r, g), e ->
 // C[row r][32 kt + 8 g + e].  Like `reconstruct` above, a pair of chunks at a time: `fetch(c, rows)` requests what P is combined
-// with, a pair ahead; `emit(c, rt, piece of rows, P)` gets the results.
+// with, a pair ahead; `emit(c, rt, piece of rows, P, scale)` gets the results, P times a scale.  Stops before the first chunk whose
+// results are not all finite and returns its index, the number of chunks if there is none: what a result is combined with may be
+// overwritten by it, so that nothing can be formed again afterwards, and to do it in this loop costs registers (40 spilled).
 template <int RT, typename Rows, typename Fetch, typename Emit>
-__device__ __forceinline__ void reconstruct_parts(const float* v, const u32x4* cw, float* vlds, int D, int k, int kt2, int wave,
-                                                  int waves, int nchunk, Fetch fetch, Emit emit) {
-  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  constexpr int KS = VPiece<2>::KS;
+__device__ __forceinline__ int reconstruct_parts(const float* v, const u32x4* cw, float* vlds, int D, int k, int kt2, int wave,
+                                                 int waves, int nchunk, Fetch fetch, Emit emit) {
   const int mine = pair_chunks(nchunk, wave, waves);
-  if (mine <= 0) return;
+  if (mine <= 0) return mine;
   VPiece<2> vp;
   vp.load(v, D, k, pair_chunk(0, wave, waves), 0);
   Rows next[2];
@@ -344,37 +410,72 @@ __device__ __forceinline__ void reconstruct_parts(const float* v, const u32x4* c
       if (i >= mine) break;
       const int c = pair_chunk(i, wave, waves);
       f32x4 lead[RT][2], rest[RT][2];
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int t = 0; t < 2; ++t) lead[rt][t] = rest[rt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      clear_products<RT>(lead, rest);
       for (int kt = 0; kt < kt2; ++kt) {
         vp.to_lds(vlds);
         const bool more = kt + 1 < kt2;
         if (more || i + 1 < mine) vp.load(v, D, k, more ? c : pair_chunk(i + 1, wave, waves), more ? 32 * (kt + 1) : 0);
-        Parts a[2];
+        piece_products<RT>(vlds, cw + kt * 3 * 64, kt2, lead, rest);
+      }
+      if (!finish_products<RT>(lead, rest)) return i;
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) emit(c, rt, rows[h], lead[rt], kPartProduct);
+    }
+  }
+  return mine;
+}
+
+// The same from the wave's chunk i on, with results that are not finite replaced by those of the float32 instructions, formed as in
+// `reconstruct`; `coef(rt, j)` gives C[row 16 rt + r][j .. j + 3].
+template <int RT, typename Rows, typename Fetch, typename Coef, typename Emit>
+__device__ __forceinline__ void reconstruct_rest(int i, const float* v, const u32x4* cw, float* vlds, int D, int k, int kt2, int wave,
+                                                 int waves, int nchunk, Fetch fetch, Coef coef, Emit emit) {
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4, mine = pair_chunks(nchunk, wave, waves);
+#pragma nounroll
+  for (; i < mine; ++i) {
+    const int c = pair_chunk(i, wave, waves);
+    f32x4 lead[RT][2], rest[RT][2];
+    clear_products<RT>(lead, rest);
+#pragma nounroll
+    for (int kt = 0; kt < kt2; ++kt) {
+      VPiece<2> vp;
+      vp.load(v, D, k, c, 32 * kt);
+      vp.to_lds(vlds);
+      piece_products<RT>(vlds, cw + kt * 3 * 64, kt2, lead, rest);
+    }
+    finish_products<RT>(lead, rest);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      f32x4 acc[2][4];
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[t][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma nounroll
+      for (int j0 = 0; j0 < k; j0 += 16) {
+        VPiece<1> vp;
+        vp.load(v, D, k, c, j0);
+        vp.to_lds(vlds);
+        const f32x4 b = coef(rt, j0 + 4 * g);
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-          const float* row = vlds + (8 * (r >> 2) + 4 * t + (r & 3)) * KS + 8 * g;
-          const f32x4 x0 = *reinterpret_cast<const f32x4*>(row), x1 = *reinterpret_cast<const f32x4*>(row + 4);
-          const float x[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
-          a[t] = split_parts(x);
-        }
+          const f32x4 a = *reinterpret_cast<const f32x4*>(vlds + (8 * (r >> 2) + 4 * t + (r & 3)) * VPiece<1>::KS + 4 * g);
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-          Parts b;
-#pragma unroll
-          for (int n = 0; n < 3; ++n) b.p[n] = cw[((rt * kt2 + kt) * 3 + n) * 64 + lane];
-#pragma unroll
-          for (int t = 0; t < 2; ++t) feature_product(a[t], b, lead[rt][t], rest[rt][t]);
+          for (int e = 0; e < 4; ++e) acc[t][e] = mfma_f32(a[e], b[e], acc[t][e]);
         }
       }
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        const f32x4 p[2] = {lead[rt][0] + rest[rt][0], lead[rt][1] + rest[rt][1]};
-        emit(c, rt, rows[h], p);
-      }
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float x = lead[rt][t][q], plain = (acc[t][0][q] + acc[t][1][q]) + (acc[t][2][q] + acc[t][3][q]);
+          lead[rt][t][q] = __builtin_fabsf(x) <= kMaxFinite ? x * kPartProduct : plain;
+        }
     }
+    Rows rows;
+    fetch(c, rows);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) emit(c, rt, rows, lead[rt], 1.f);
   }
 }
 
@@ -389,6 +490,7 @@ __global__ __launch_bounds__(64 * kStepWaves, 2) void full_step_parts_kernel(con
   // per wave: its piece of V; between the phases its partial sums
   constexpr int kStage = Stage::kFloats > KT * RT * 256 ? Stage::kFloats : KT * RT * 256;
   __shared__ __align__(16) float vstage[kStepWaves][kStage];
+  __shared__ int s_redo;                 // 1 + the first coefficient of the pass that left sums that are not finite
   extern __shared__ __align__(16) char dyn[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
   const int b = blockIdx.y, row0 = blockIdx.x * ROWS, kt2 = (k + 31) / 32, CS = 32 * kt2 + 4;
@@ -401,6 +503,8 @@ __global__ __launch_bounds__(64 * kStepWaves, 2) void full_step_parts_kernel(con
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) roff[rt] = (int64_t)b * bstride + (int64_t)min(row0 + 16 * rt + r, N - 1) * ldf;
 
+  if (threadIdx.x == 0) s_redo = 0;      // ahead of the barriers of the first pass
+  constexpr double kProduct = sizeof(T) == 2 ? 1.0 / kPartScale : (double)kPartProduct;
   for (int j0 = 0; j0 < k; j0 += 16 * KT) {
     f32x4 rest[RT][KT];
     f64x4 tot[RT][KT];
@@ -463,24 +567,38 @@ __global__ __launch_bounds__(64 * kStepWaves, 2) void full_step_parts_kernel(con
 #pragma unroll
       for (int jt = 0; jt < KT; ++jt) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) part[(rt * KT + jt) * 64 + lane][q] = (float)(tot[rt][jt][q] + (double)rest[rt][jt][q]);
+        for (int q = 0; q < 4; ++q) part[(rt * KT + jt) * 64 + lane][q] = (float)((tot[rt][jt][q] + (double)rest[rt][jt][q]) * kProduct);
       }
     __syncthreads();
     // D[m = 4 g + i][n = r]: row 4 g + i, coefficient j0 + 2 r + jt
     if (wave < RT * KT) {
       static_assert(RT * KT <= kStepWaves, "one sum per wave");
       const int rt = wave / KT, j = j0 + KT * r + wave % KT;
-      double c[4] = {0.0, 0.0, 0.0, 0.0};
+      const f32x4 c = sum_shares(vstage[0], kStage, wave);
 #pragma unroll
-      for (int w = 0; w < kStepWaves; ++w) {
-        const f32x4 p = reinterpret_cast<const f32x4*>(vstage[w])[wave * 64 + lane];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) c[i] += (double)p[i];
+      for (int i = 0; i < 4; ++i) {
+        const float x = j < k ? c[i] : 0.f;
+        cs[(16 * rt + 4 * g + i) * CS + j] = x;
+        if (!(__builtin_fabsf(x) <= kMaxFinite)) s_redo = j0 + 1;
       }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) cs[(16 * rt + 4 * g + i) * CS + j] = j < k ? (float)c[i] : 0.f;
     }
     __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(s_redo) == j0 + 1) {
+#pragma nounroll
+      for (int rt = 0; rt < RT; ++rt) {
+        project_share<T, KT>(F + (int64_t)b * bstride + (int64_t)min(row0 + 16 * rt + r, N - 1) * ldf, v, vlds, D, k, j0, wave, nchunk);
+        const int j = j0 + KT * r + wave;
+        if (wave < KT && j < k) {
+          const f32x4 c = sum_shares(vstage[0], kStage, wave);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            float& x = cs[(16 * rt + 4 * g + i) * CS + j];
+            if (!(__builtin_fabsf(x) <= kMaxFinite)) x = c[i];
+          }
+        }
+        __syncthreads();
+      }
+    }
   }
 
   // operand words of the coefficients; the EMA update of the state (Eq. 11 with alpha = 1 - beta)
@@ -511,18 +629,21 @@ __global__ __launch_bounds__(64 * kStepWaves, 2) void full_step_parts_kernel(con
       if constexpr (REMA) to.rp[rt].load(Rp + roff[rt], 32 * c + 8 * g, D);
     }
   };
-  reconstruct_parts<RT, Rows>(v, cw, vlds, D, k, kt2, wave, kStepWaves, nchunk, fetch,
-                              [&](int c, int rt, const Rows& rows, const f32x4 (&p)[2]) {
+  auto emit = [&](int c, int rt, const Rows& rows, const f32x4 (&p)[2], float scale) {
     f32x4 x[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        x[t][i] = rows.f[rt].get(4 * t + i) - p[t][i];
+        x[t][i] = __builtin_fmaf(-p[t][i], scale, rows.f[rt].get(4 * t + i));
         if constexpr (REMA) x[t][i] = (1.f - alpha_r) * rows.rp[rt].get(4 * t + i) + alpha_r * x[t][i];
       }
     if (row0 + 16 * rt + r < N) Piece<T>::store(R + roff[rt], 32 * c + 8 * g, D, x);
-  });
+  };
+  const int done = reconstruct_parts<RT, Rows>(v, cw, vlds, D, k, kt2, wave, kStepWaves, nchunk, fetch, emit);
+  if (done < mine)
+    reconstruct_rest<RT, Rows>(done, v, cw, vlds, D, k, kt2, wave, kStepWaves, nchunk, fetch,
+                               [&](int rt, int j) { return *reinterpret_cast<const f32x4*>(cs + (16 * rt + r) * CS + j); }, emit);
 }
 
 // Cached step on 16 RT rows; the blockIdx.z-th of gridDim.z shares of the channels.
@@ -536,17 +657,16 @@ __global__ __launch_bounds__(64 * kCachedWaves, 3) void forecast_parts_kernel(co
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
   const int b = blockIdx.y, row0 = blockIdx.x * 16 * RT, kt2 = (k + 31) / 32;
   const int nchunk = (D + 31) / 32;
+  auto coefficient = [&](int rt, int j) {              // of row 16 rt + r, zero beyond k
+    const int64_t a = ((int64_t)b * N + min(row0 + 16 * rt + r, N - 1)) * k + min(j, k - 1);
+    float c = st.w[0] * st.s[0][a];
+    for (int m = 1; m < st.m; ++m) c = __builtin_fmaf(st.w[m], st.s[m][a], c);
+    return j < k ? c : 0.f;
+  };
   for (int n = wave; n < RT * kt2; n += kCachedWaves) {
-    const int row = row0 + 16 * (n / kt2) + r, j = 32 * (n % kt2) + 8 * g;
-    const int64_t at = ((int64_t)b * N + min(row, N - 1)) * k;
     float x[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int64_t a = at + min(j + e, k - 1);
-      float c = st.w[0] * st.s[0][a];
-      for (int m = 1; m < st.m; ++m) c = __builtin_fmaf(st.w[m], st.s[m][a], c);
-      x[e] = j + e < k ? c : 0.f;
-    }
+    for (int e = 0; e < 8; ++e) x[e] = coefficient(n / kt2, 32 * (n % kt2) + 8 * g + e);
     const Parts p = split_parts(x);
 #pragma unroll
     for (int m = 0; m < 3; ++m) cw[(n * 3 + m) * 64 + lane] = p.p[m];
@@ -563,9 +683,7 @@ __global__ __launch_bounds__(64 * kCachedWaves, 3) void forecast_parts_kernel(co
       if constexpr (HX) to.x[rt].load(X + roff[rt], 32 * c + 8 * g, D);
     }
   };
-  reconstruct_parts<RT, Rows>(V + (int64_t)b * D * k, cw, vstage[wave], D, k, kt2, blockIdx.z * kCachedWaves + wave,
-                              kCachedWaves * gridDim.z, nchunk, fetch,
-                              [&](int c, int rt, const Rows& rows, const f32x4 (&p)[2]) {
+  auto emit = [&](int c, int rt, const Rows& rows, const f32x4 (&p)[2], float scale) {
     f32x4 x[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -573,10 +691,18 @@ __global__ __launch_bounds__(64 * kCachedWaves, 3) void forecast_parts_kernel(co
       for (int i = 0; i < 4; ++i) {
         x[t][i] = rows.f[rt].get(4 * t + i);
         if constexpr (HX) x[t][i] += rows.x[rt].get(4 * t + i);
-        x[t][i] += p[t][i];
+        x[t][i] = __builtin_fmaf(p[t][i], scale, x[t][i]);
       }
     if (row0 + 16 * rt + r < N) Piece<T>::store(Fh + roff[rt], 32 * c + 8 * g, D, x);
-  });
+  };
+  const float* v = V + (int64_t)b * D * k;
+  const int share = blockIdx.z * kCachedWaves + wave, shares = kCachedWaves * gridDim.z;
+  const int done = reconstruct_parts<RT, Rows>(v, cw, vstage[wave], D, k, kt2, share, shares, nchunk, fetch, emit);
+  if (done < pair_chunks(nchunk, share, shares))
+    reconstruct_rest<RT, Rows>(done, v, cw, vstage[wave], D, k, kt2, share, shares, nchunk, fetch,
+                               [&](int rt, int j) {
+                                 return f32x4{coefficient(rt, j), coefficient(rt, j + 1), coefficient(rt, j + 2), coefficient(rt, j + 3)};
+                               }, emit);
 }
 
 constexpr int kCachedPartsRows = 2;   // row tiles of the cached step above

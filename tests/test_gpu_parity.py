@@ -113,6 +113,68 @@ def test_general_projection_in_parts_is_as_good_as_float32(dtype, N, D, k):
     assert rel_err(to_np(Cc[0]), to_np(F[0]) @ to_np(V[0])) <= 0.41 * 2.0 ** -24 * 17 ** 0.5
 
 
+@pytest.mark.parametrize("dtype,N,D,k", [(torch.bfloat16, 601, 2008, 64), (torch.bfloat16, 8101, 520, 50), (torch.bfloat16, 8701, 520, 50),
+                                         (torch.float32, 8701, 796, 50), (torch.float32, 5003, 796, 100)])
+def test_general_kernels_in_parts_keep_the_range_of_float32(dtype, N, D, k):
+    """Infinities, a NaN, values next to the largest float32, and rows and basis columns down to the smallest normal ones: what
+    float64 says is infinite, NaN or finite is so in the results, and finite results are within 16 u (u = 2^-24) of the norm of
+    their row and, for a basis column of its own scale, of that column (the sums of a product are off by 0.41 u sqrt(17) or less)."""
+    store = "f32" if dtype == torch.float32 else "bf16"
+    tol, inf, nan, big = 16 * 2.0 ** -24, float("inf"), float("nan"), 3.395e38 if store == "f32" else 3.38e38
+    Fbuf, V, S0 = _rand_problem(1, N, D, k, dtype, seed=N + k)
+    F, S0 = Fbuf.clone(), S0 * 1e-3
+    odd = {3: "inf", 17: "-inf and inf", 40: "big", 100: "tiny", 130: "nan", N - 1: "big and last"}
+    F[0, 3, 1], F[0, 17, 2], F[0, 17, D - 1], F[0, 40, 7], F[0, 130, 0], F[0, N - 1, D - 2] = inf, -inf, inf, big, nan, -big
+    F[0, 100] *= 2.0 ** -112
+    S0[0, list(odd)] = 0.0                                # S is 0.25 C there
+    cols = {5: 2.0 ** -112, 9: 2.0 ** 100}
+    Vs = V.clone()
+    for j, scale in cols.items():
+        Vs[0, :, j] *= scale
+
+    def check(got, want, what, along=1):
+        got = to_np(got)
+        assert np.array_equal(np.isnan(got), np.isnan(want)), f"{what}: NaN"
+        assert np.array_equal(np.isposinf(got), np.isposinf(want)) and np.array_equal(np.isneginf(got), np.isneginf(want)), f"{what}: inf"
+        fin = np.isfinite(want).all(axis=along)
+        got, want = (got[fin], want[fin]) if along == 1 else (got[:, fin].T, want[:, fin].T)
+        err, ref = np.linalg.norm(got - want, axis=1), np.linalg.norm(want, axis=1)
+        assert (err <= (2.0 ** -8 if what in ("R", "Fhat") and store == "bf16" else tol) * ref).all(), f"{what}: {(err / ref).max():.2e}"
+
+    with np.errstate(all="ignore"):
+        R, S, Cc, _, pk = _run_full(F, D, V, S0, 0.25, False)
+        assert pk is None
+        C64 = to_np(F[0]) @ to_np(V[0])
+        check(Cc[0], C64, "C")
+        check(S[0][list(odd)], 0.25 * C64[list(odd)], "S")
+        Cg = to_np(Cc[0])
+        R64 = to_np(F[0]) - Cg @ to_np(V[0]).T
+        check(R[0], R64, "R")
+        assert not np.isfinite(R64[[3, 17, 130]]).any() and np.isfinite(np.delete(R64, [3, 17, 130], axis=0)).all()
+        # columns of very different scales: each to its own norm; then the rows of a state, with a residual of its scale
+        _, _, Cs, _, _ = _run_full(Fbuf, D, Vs, S0, 0.25, True)
+        check(Cs[0], to_np(Fbuf[0]) @ to_np(Vs[0]), "C", along=0)
+        Sx = Cc.clone()                                   # with the infinities and the NaN of the features' rows
+        Rx = Fbuf.to(DEV) * 0.5
+        Rx[0, 100] *= 2.0 ** -112
+        Fh = torch.empty_like(Rx)
+        shape = pkg.make_shape(Rx, k)
+        pkg.svdcache_forecast(shape, Sx, V.to(DEV), None, Rx, Fh)
+        torch.cuda.synchronize()
+        Fh64 = to_np(Sx[0]) @ to_np(V[0]).T + to_np(Rx[0])
+        check(Fh[0], Fh64, "Fhat")
+        pkg.svdcache_forecast_combine(shape, [Sx, S], [1.5, -0.5], V.to(DEV), None, Rx, Rx, Fh)
+        torch.cuda.synchronize()
+        Fh64 = (1.5 * to_np(Sx[0]) - 0.5 * to_np(S[0])) @ to_np(V[0]).T + 2 * to_np(Rx[0])
+        check(Fh[0][:100], Fh64[:100], "Fhat")
+        # the same with the results in place of the residual
+        want = Fh.clone() * 0
+        pkg.svdcache_forecast(shape, Sx, V.to(DEV), None, Rx, want)
+        pkg.svdcache_forecast(shape, Sx, V.to(DEV), None, Rx, Rx)
+        torch.cuda.synchronize()
+        assert torch.equal(torch.nan_to_num(want.float()), torch.nan_to_num(Rx.float()))
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
 def test_general_projection_sums_in_short_chains(dtype):
     """C of many channels: float32 chains of at most 16 products, their sums in a chain of one link per 512 channels.  A chain
