@@ -78,76 +78,6 @@ __device__ __forceinline__ void reconstruct(const float* v, const float* cs, flo
   }
 }
 
-// A wave's share of C = F V on the float32 matrix cores: its lane's token row `frow` x the 16 KT coefficients from j0, every
-// kStepWaves-th chunk of 32 channels.  Leaves the sums in vlds, [KT][64] results of four, and ends with a barrier.
-constexpr int kStepWaves = 8;
-template <typename T, int KT>
-__device__ __forceinline__ void project_share(const T* frow, const float* v, float* vlds, int D, int k, int j0, int wave,
-                                              int nchunk) {
-  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  struct alignas(4 * KT) RowVec { float v[KT]; };
-  f32x4 acc[KT][4], tot[KT];
-#pragma unroll
-  for (int jt = 0; jt < KT; ++jt) {
-    tot[jt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int h = 0; h < 4; ++h) acc[jt][h] = f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-  Piece<T> fn;
-  VPiece<KT> vp;
-  if (wave < nchunk) {
-    fn.load(frow, 32 * wave + 8 * g, D);
-    vp.load(v, D, k, wave, j0);
-  }
-  for (int c = wave; c < nchunk; c += kStepWaves) {
-    const Piece<T> f = fn;
-    vp.to_lds(vlds);
-    if (c + kStepWaves < nchunk) {
-      fn.load(frow, 32 * (c + kStepWaves) + 8 * g, D);
-      vp.load(v, D, k, c + kStepWaves, j0);
-    }
-    if (c >= 2 * kStepWaves && (c / kStepWaves) % 2 == 0) {
-#pragma unroll
-      for (int jt = 0; jt < KT; ++jt) {
-        tot[jt] += (acc[jt][0] + acc[jt][1]) + (acc[jt][2] + acc[jt][3]);
-#pragma unroll
-        for (int h = 0; h < 4; ++h) acc[jt][h] = f32x4{0.f, 0.f, 0.f, 0.f};
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      // columns of the result tile jt: j0 + KT r + jt, so that one wide LDS read brings the operands of all tiles
-      const float x = f.get(e);
-      const RowVec vv = *reinterpret_cast<const RowVec*>(vlds + (8 * g + e) * VPiece<KT>::KS + KT * r);
-#pragma unroll
-      for (int jt = 0; jt < KT; ++jt) acc[jt][e & 3] = mfma_f32(x, vv.v[jt], acc[jt][e & 3]);
-    }
-  }
-  f32x4* part = reinterpret_cast<f32x4*>(vlds);
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-#pragma unroll
-  for (int jt = 0; jt < KT; ++jt) {
-    f32x4 s;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      s[i] = (float)((((double)acc[jt][0][i] + acc[jt][1][i]) + ((double)acc[jt][2][i] + acc[jt][3][i])) + tot[jt][i]);
-    part[jt * 64 + lane] = s;
-  }
-  __syncthreads();
-}
-
-// The sum of the waves' results of a tile, `stage` floats apart.
-__device__ __forceinline__ f32x4 sum_shares(const float* part, int stage, int tile) {
-  double c[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int w = 0; w < kStepWaves; ++w) {
-    const f32x4 p = reinterpret_cast<const f32x4*>(part + w * stage)[tile * 64 + (threadIdx.x & 63)];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) c[i] += (double)p[i];
-  }
-  return f32x4{(float)c[0], (float)c[1], (float)c[2], (float)c[3]};
-}
-
 // Full-compute step (Eq. 8-11): C = F V, R = F - C V^T, EMA update of S.  A workgroup takes 16 token rows; its eight
 // waves take every eighth chunk of 32 channels.  Phase 1 projects, 16 KT coefficients at a time, with four accumulators per
 // result tile, which leaves registers for two workgroups per compute unit; the waves' partial sums meet in LDS.  The
@@ -157,6 +87,7 @@ __device__ __forceinline__ f32x4 sum_shares(const float* part, int stage, int ti
 // 256 rows and ranks of several passes.
 // Phase 2 forms the residual chunk by chunk.  F and R may alias, R and Rp too: phase 1 has read all of the workgroup's
 // rows before the barrier, and phase 2 reads every element in the lane that overwrites it.
+constexpr int kStepWaves = 8;
 template <typename T, int KT>
 __global__ __launch_bounds__(64 * kStepWaves, 4) void full_step_general_kernel(const T* F, const float* __restrict__ V, T* R,
                                                                             const T* Rp, float alpha_r, float* S,
@@ -172,17 +103,71 @@ __global__ __launch_bounds__(64 * kStepWaves, 4) void full_step_general_kernel(c
   const int nchunk = (D + 31) / 32;
   const float* v = V + (int64_t)b * D * k;
   float* vlds = vstage[wave];
+  struct alignas(4 * KT) RowVec { float v[KT]; };
   const int64_t roff = (int64_t)b * bstride + (int64_t)min(row0 + r, N - 1) * ldf;
 
   for (int j0 = 0; j0 < k; j0 += 16 * KT) {
-    project_share<T, KT>(F + roff, v, vlds, D, k, j0, wave, nchunk);
+    f32x4 acc[KT][4], tot[KT];
+#pragma unroll
+    for (int jt = 0; jt < KT; ++jt) {
+      tot[jt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int h = 0; h < 4; ++h) acc[jt][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    Piece<T> fn;
+    VPiece<KT> vp;
+    if (wave < nchunk) {
+      fn.load(F + roff, 32 * wave + 8 * g, D);
+      vp.load(v, D, k, wave, j0);
+    }
+    for (int c = wave; c < nchunk; c += kStepWaves) {
+      const Piece<T> f = fn;
+      vp.to_lds(vlds);
+      if (c + kStepWaves < nchunk) {
+        fn.load(F + roff, 32 * (c + kStepWaves) + 8 * g, D);
+        vp.load(v, D, k, c + kStepWaves, j0);
+      }
+      if (c >= 2 * kStepWaves && (c / kStepWaves) % 2 == 0) {
+#pragma unroll
+        for (int jt = 0; jt < KT; ++jt) {
+          tot[jt] += (acc[jt][0] + acc[jt][1]) + (acc[jt][2] + acc[jt][3]);
+#pragma unroll
+          for (int h = 0; h < 4; ++h) acc[jt][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        // columns of the result tile jt: j0 + KT r + jt, so that one wide LDS read brings the operands of all tiles
+        const float x = f.get(e);
+        const RowVec vv = *reinterpret_cast<const RowVec*>(vlds + (8 * g + e) * VPiece<KT>::KS + KT * r);
+#pragma unroll
+        for (int jt = 0; jt < KT; ++jt) acc[jt][e & 3] = mfma_f32(x, vv.v[jt], acc[jt][e & 3]);
+      }
+    }
+    f32x4* part = reinterpret_cast<f32x4*>(vlds);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+    for (int jt = 0; jt < KT; ++jt) {
+      f32x4 s;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        s[i] = (float)((((double)acc[jt][0][i] + acc[jt][1][i]) + ((double)acc[jt][2][i] + acc[jt][3][i])) + tot[jt][i]);
+      part[jt * 64 + lane] = s;
+    }
+    __syncthreads();
     // D[m = 4 g + i][n = r]: row 4 g + i, coefficient j0 + KT r + jt
     if (wave < KT) {
       const int j = j0 + KT * r + wave;
-      const f32x4 c = sum_shares(vstage[0], VPiece<KT>::kFloats, wave);
+      double c[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int w = 0; w < kStepWaves; ++w) {
+        const f32x4 p = reinterpret_cast<const f32x4*>(vstage[w])[wave * 64 + lane];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c[i] += (double)p[i];
+      }
       if (j < CS - 4) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) cs[(4 * g + i) * CS + j] = j < k ? c[i] : 0.f;
+        for (int i = 0; i < 4; ++i) cs[(4 * g + i) * CS + j] = j < k ? (float)c[i] : 0.f;
       }
     }
     __syncthreads();
@@ -479,7 +464,63 @@ __device__ __forceinline__ void reconstruct_rest(int i, const float* v, const u3
   }
 }
 
-// Full step on 16 RT rows: the structure of full_step_general_kernel, 32 coefficients of phase 1 at a time.
+// What full_step_general_kernel leaves in its stage for a wave's chunks and 16 KT coefficients of the lane's row: the same sums in the
+// same order.
+template <typename T, int KT>
+__device__ __forceinline__ void project_plain(const T* frow, const float* v, float* vlds, int D, int k, int j0, int wave, int nchunk) {
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  f32x4 acc[KT][4], tot[KT];
+#pragma unroll
+  for (int jt = 0; jt < KT; ++jt) {
+    tot[jt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int h = 0; h < 4; ++h) acc[jt][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+#pragma nounroll
+  for (int c = wave; c < nchunk; c += kStepWaves) {
+    Piece<T> f;
+    f.load(frow, 32 * c + 8 * g, D);
+    VPiece<KT> vp;
+    vp.load(v, D, k, c, j0);
+    vp.to_lds(vlds);
+    if (c >= 2 * kStepWaves && (c / kStepWaves) % 2 == 0) {
+#pragma unroll
+      for (int jt = 0; jt < KT; ++jt) {
+        tot[jt] += (acc[jt][0] + acc[jt][1]) + (acc[jt][2] + acc[jt][3]);
+#pragma unroll
+        for (int h = 0; h < 4; ++h) acc[jt][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float x = f.get(e);
+#pragma unroll
+      for (int jt = 0; jt < KT; ++jt)
+        acc[jt][e & 3] = mfma_f32(x, vlds[(8 * g + e) * VPiece<KT>::KS + KT * r + jt], acc[jt][e & 3]);
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+  for (int jt = 0; jt < KT; ++jt)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      reinterpret_cast<f32x4*>(vlds)[jt * 64 + lane][i] =
+          (float)((((double)acc[jt][0][i] + acc[jt][1][i]) + ((double)acc[jt][2][i] + acc[jt][3][i])) + tot[jt][i]);
+}
+// The sum of the waves' results of a tile, `stage` floats apart.
+__device__ __forceinline__ f32x4 sum_waves(const float* part, int stage, int tile) {
+  double c[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int w = 0; w < kStepWaves; ++w) {
+    const f32x4 p = reinterpret_cast<const f32x4*>(part + w * stage)[tile * 64 + (threadIdx.x & 63)];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c[i] += (double)p[i];
+  }
+  return f32x4{(float)c[0], (float)c[1], (float)c[2], (float)c[3]};
+}
+
+// Full step on 16 RT rows: the structure of full_step_general_kernel, 32 coefficients of phase 1 at a time.  Two registers spill for
+// three tiles of float32 rows.
 template <typename T, int RT, bool REMA>
 __global__ __launch_bounds__(64 * kStepWaves, 2) void full_step_parts_kernel(const T* F, const float* __restrict__ V, T* R,
                                                                           const T* Rp, float alpha_r, float* S, float* C,
@@ -574,7 +615,7 @@ __global__ __launch_bounds__(64 * kStepWaves, 2) void full_step_parts_kernel(con
     if (wave < RT * KT) {
       static_assert(RT * KT <= kStepWaves, "one sum per wave");
       const int rt = wave / KT, j = j0 + KT * r + wave % KT;
-      const f32x4 c = sum_shares(vstage[0], kStage, wave);
+      const f32x4 c = sum_waves(vstage[0], kStage, wave);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float x = j < k ? c[i] : 0.f;
@@ -586,10 +627,11 @@ __global__ __launch_bounds__(64 * kStepWaves, 2) void full_step_parts_kernel(con
     if (__builtin_amdgcn_readfirstlane(s_redo) == j0 + 1) {
 #pragma nounroll
       for (int rt = 0; rt < RT; ++rt) {
-        project_share<T, KT>(F + (int64_t)b * bstride + (int64_t)min(row0 + 16 * rt + r, N - 1) * ldf, v, vlds, D, k, j0, wave, nchunk);
+        project_plain<T, KT>(F + (int64_t)b * bstride + (int64_t)min(row0 + 16 * rt + r, N - 1) * ldf, v, vlds, D, k, j0, wave, nchunk);
+        __syncthreads();
         const int j = j0 + KT * r + wave;
         if (wave < KT && j < k) {
-          const f32x4 c = sum_shares(vstage[0], kStage, wave);
+          const f32x4 c = sum_waves(vstage[0], kStage, wave);
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             float& x = cs[(16 * rt + 4 * g + i) * CS + j];
@@ -646,10 +688,11 @@ __global__ __launch_bounds__(64 * kStepWaves, 2) void full_step_parts_kernel(con
                                [&](int rt, int j) { return *reinterpret_cast<const f32x4*>(cs + (16 * rt + r) * CS + j); }, emit);
 }
 
-// Cached step on 16 RT rows; the blockIdx.z-th of gridDim.z shares of the channels.
-template <typename T, int RT, bool HX>
+// Cached step on 16 RT rows; the blockIdx.z-th of gridDim.z shares of the channels.  Bounded to the registers of three workgroups
+// per compute unit, of which float32 rows spill 14 and bf16 rows none.
+template <typename T, int RT>
 __global__ __launch_bounds__(64 * kCachedWaves, 3) void forecast_parts_kernel(const CoefStates st, const float* __restrict__ V,
-                                                                           const T* R, const T* X, T* Fh, int N, int D, int k,
+                                                                           const T* R, T* Fh, int N, int D, int k,
                                                                            int64_t ldf, int64_t bstride) {
   __shared__ __align__(16) float vstage[kCachedWaves][VPiece<2>::kFloats];
   extern __shared__ __align__(16) char dyn[];
@@ -675,24 +718,17 @@ __global__ __launch_bounds__(64 * kCachedWaves, 3) void forecast_parts_kernel(co
   int64_t roff[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) roff[rt] = (int64_t)b * bstride + (int64_t)min(row0 + 16 * rt + r, N - 1) * ldf;
-  struct Rows { Piece<T> f[RT], x[HX ? RT : 1]; };
+  struct Rows { Piece<T> f[RT]; };
   auto fetch = [&](int c, Rows& to) {
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      to.f[rt].load(R + roff[rt], 32 * c + 8 * g, D);
-      if constexpr (HX) to.x[rt].load(X + roff[rt], 32 * c + 8 * g, D);
-    }
+    for (int rt = 0; rt < RT; ++rt) to.f[rt].load(R + roff[rt], 32 * c + 8 * g, D);
   };
   auto emit = [&](int c, int rt, const Rows& rows, const f32x4 (&p)[2], float scale) {
     f32x4 x[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        x[t][i] = rows.f[rt].get(4 * t + i);
-        if constexpr (HX) x[t][i] += rows.x[rt].get(4 * t + i);
-        x[t][i] = __builtin_fmaf(p[t][i], scale, x[t][i]);
-      }
+      for (int i = 0; i < 4; ++i) x[t][i] = __builtin_fmaf(p[t][i], scale, rows.f[rt].get(4 * t + i));
     if (row0 + 16 * rt + r < N) Piece<T>::store(Fh + roff[rt], 32 * c + 8 * g, D, x);
   };
   const float* v = V + (int64_t)b * D * k;
@@ -735,7 +771,7 @@ int32_t full_step_general_typed(const svdc_shape& s, const void* F, const float*
   if (rt > 0) {
     auto go = [&](auto tiles) -> int32_t {
       constexpr int RT = decltype(tiles)::value;
-      constexpr bool kRema = !kF32;       // float32 rows and previous residuals do not fit the registers: not asked for
+      constexpr bool kRema = !kF32 && RT > 1;       // the others are not asked for
       const auto kernel = kRema && re.prev ? full_step_parts_kernel<T, RT, kRema> : full_step_parts_kernel<T, RT, false>;
       const int kt2 = (s.k + 31) / 32;
       const size_t lds = (size_t)RT * kt2 * 3 * 1024 + (size_t)16 * RT * (32 * kt2 + 4) * sizeof(float);
@@ -744,7 +780,9 @@ int32_t full_step_general_typed(const svdc_shape& s, const void* F, const float*
           (const T*)F, V, (T*)R, (const T*)re.prev, re.alpha_r, S, C, s.N, s.D, s.k, s.ldf, s.block_stride, alpha, init);
       return launch_status();
     };
-    if (rt == 1) return go(std::integral_constant<int, 1>{});
+    if constexpr (!kF32) {
+      if (rt == 1) return go(std::integral_constant<int, 1>{});
+    }
     if (rt == 2) return go(std::integral_constant<int, 2>{});
     return go(std::integral_constant<int, 3>{});
   }
@@ -762,36 +800,24 @@ int32_t full_step_general_typed(const svdc_shape& s, const void* F, const float*
 template <typename T>
 int32_t forecast_general_typed(const svdc_shape& s, const CoefStates& cs, const float* V, const void* R, const void* X,
                                void* Out, hipStream_t st) {
-  if (cached_step_may_take_parts(s.D, s.k, sizeof(T) == 4, X != nullptr) && cached_step_takes_parts(s.N, s.B, num_compute_units())) {
-    auto go = [&](auto kernel) -> int32_t {
-      const size_t lds = (size_t)kCachedPartsRows * ((s.k + 31) / 32) * 3 * 1024;
-      if (allow_lds(kernel, lds) != SVDC_OK) return SVDC_E_HIP;
-      const int64_t tiles = (s.N + 16 * kCachedPartsRows - 1) / (16 * kCachedPartsRows);
-      // shares of the channels: four workgroups per compute unit, at least a pair of chunks per wave
-      const int64_t most = std::max(1, (s.D + 63) / 64 / kCachedWaves);
-      const int64_t want = (4 * (int64_t)num_compute_units() + tiles * s.B - 1) / (tiles * s.B);
-      kernel<<<dim3((unsigned)tiles, s.B, (unsigned)std::max<int64_t>(1, std::min(want, most))), 64 * kCachedWaves, lds, st>>>(
-          cs, V, (const T*)R, (const T*)X, (T*)Out, s.N, s.D, s.k, s.ldf, s.block_stride);
-      return launch_status();
-    };
-    if constexpr (sizeof(T) == 2) {
-      if (X) return go(forecast_parts_kernel<T, kCachedPartsRows, true>);
-    }
-    return go(forecast_parts_kernel<T, kCachedPartsRows, false>);
+  constexpr bool kF32 = sizeof(T) == 4;
+  if (cached_step_may_take_parts(s.D, s.k, kF32, X != nullptr) &&
+      cached_step_takes_parts(s.N, s.B, s.D, s.k, kF32, num_compute_units())) {
+    auto kernel = forecast_parts_kernel<T, kCachedPartsRows>;
+    const size_t lds = (size_t)kCachedPartsRows * ((s.k + 31) / 32) * 3 * 1024;
+    if (allow_lds(kernel, lds) != SVDC_OK) return SVDC_E_HIP;
+    const int64_t tiles = (s.N + 16 * kCachedPartsRows - 1) / (16 * kCachedPartsRows);
+    kernel<<<dim3((unsigned)tiles, s.B, cached_shares(tiles, s.B, s.D, true, num_compute_units())), 64 * kCachedWaves, lds, st>>>(
+        cs, V, (const T*)R, (T*)Out, s.N, s.D, s.k, s.ldf, s.block_stride);
+    return launch_status();
   }
   return general_dispatch<4>(s, [&](auto kt) -> int32_t {
     auto kernel = forecast_general_kernel<T, decltype(kt)::value>;
     const size_t lds = (size_t)16 * coef_stride(s.k) * sizeof(float);
     if (allow_lds(kernel, lds) != SVDC_OK) return SVDC_E_HIP;
     const int64_t tiles = (s.N + 15) / 16;
-    // shares of the channels: until there are about four workgroups per compute unit, at least two chunks per wave (few
-    // channels have one share only, whatever the device: its query is a fiftieth of the smallest calls)
-    const int most = (s.D + 31) / 32 / (2 * kCachedWaves);
-    int shares = 1;
-    if (most > 1) {
-      const int64_t want = (4 * (int64_t)num_compute_units() + tiles * s.B - 1) / (tiles * s.B);
-      shares = (int)std::max<int64_t>(1, std::min<int64_t>(want, most));
-    }
+    // few channels have one share only, whatever the device: its query is a fiftieth of the smallest calls
+    const int shares = s.D > 32 * (4 * kCachedWaves - 1) ? cached_shares(tiles, s.B, s.D, false, num_compute_units()) : 1;
     kernel<<<dim3((unsigned)tiles, s.B, shares), 64 * kCachedWaves, lds, st>>>(cs, V, (const T*)R, (const T*)X, (T*)Out,
                                                                                s.N, s.D, s.k, s.ldf, s.block_stride);
     return launch_status();

@@ -90,27 +90,33 @@ inline bool smoothing_takes_full_tiles(int rt, int kt2, int N, int64_t B, int cu
   return cost(rt) < 0.92 * cost(rt - 1);
 }
 
-// Row tiles of 16 with which the general full step runs on the bf16 matrix cores in parts (general_kernels.hip), 0: on the float32
-// ones, which take one.  Estimated time of a round of workgroups, fitted to 15 shapes (us): 3 + chunks of a wave x (piece of V +
-// tiles x row tile); a float32 instruction works 1.65 (bf16 rows) or 1.8 per 32 coefficients and tile of 16, the parts take 0.9
-// per 32 coefficients to split V and 0.44 + 0.36 (0.9 + 0.75) per row tile, a tenth more where the residual is smoothed.  Few
-// channels, where the constants overlap with other workgroups (57 x 3874 x 72 float32: 170 and 250 us; 3 x 12607 x 512 float32: 95
-// and 104 us), and ranks up to 16, half of whose columns would be padding (20 x 900 x 1000, rank 16: 29 and 36 us), stay on the
-// float32 instructions; so do gains of less than 8 %, 15 % for float32 rows and with smoothing, which the estimate meets less
-// well, and both together (registers).  Over 60 sampled calls none is slower by more than the runs scatter, and bf16 rows
-// take 17 % less time on average where the rule applies.
-// The limits come first, so that a call outside them does not ask for the compute units (a fiftieth of the smallest calls).
+// The general steps (general_kernels.hip) run on the float32 matrix cores, 16 rows per workgroup, or on the bf16 ones with
+// float32 values as three parts, 16 RT rows.  The rules below compare estimates of both (us, 256 compute units): rounds of workgroups
+// or workgroups per unit x (a constant + chunks of 32 channels per wave x (rows + padded rank x work)).
+// Fitted to half of 7184 calls timed with every choice (1 to 57 blocks, 34 to 40000 rows, 488 to 4480 channels, ranks 17 to 128).
+// Over all of them, share of the calls in parts, their time against the float32 instructions, and how many of them are slower by
+// more than 1.5 % and 0.2 us: full step of bf16 rows 81 %, 0.83, 1.2 %; with smoothing 55 %, 0.84, 1.7 %; of float32 rows 34 %, 0.88,
+// 3.0 %; cached step of bf16 rows 55 %, 0.86, 3.0 %; of float32 rows 5 %, 0.94, 7 %.  (Choosing without a mistake would take 0.852 of
+// the time of all full steps of bf16 rows, this takes 0.857.)  The margins are where few calls lose; the estimates meet the time
+// within 8 to 11 %.
+// The limits come first, so that a call outside them does not ask for the compute units (a fiftieth of the smallest calls).  Ranks
+// up to 16 would be padded to 32 (20 x 900 x 1000, rank 16: 29 us on the float32 instructions, 36 in parts); with few channels the
+// constants overlap with other workgroups (57 x 3874 x 72 float32: 170 and 250 us).
+
+// Row tiles RT with which the general full step runs in parts, 0: on the float32 instructions.  Float32 rows and smoothing together
+// do not fit the registers; one tile of either is never better than the float32 instructions by these estimates.
 inline bool full_step_may_take_parts(int D, int k, bool f32, bool smoothing) {
-  return k > 16 && k <= 128 && D > 32 * (f32 ? 23 : 15) && !(f32 && smoothing);
+  return k > 16 && k <= 128 && D > 480 && !(f32 && smoothing);
 }
 inline int full_step_parts_rows(int N, int64_t B, int D, int k, bool f32, bool smoothing, int cus) {
-  const int nchunk = (D + 31) / 32, kt2 = (k + 31) / 32;
+  const double chunks = ((D + 31) / 32) / 8.0, kt2 = (k + 31) / 32;
   auto rounds = [&](int rt) { return (double)(((int64_t)((N + 16 * rt - 1) / (16 * rt)) * B + cus - 1) / cus); };
-  double least = (f32 || smoothing ? 0.85 : 0.92) * rounds(1) * (3 + (nchunk + 7) / 8 * (f32 ? 1.8 : 1.65) * kt2);
+  const double rows = f32 ? 0.84 : smoothing ? 0.44 : 0.25, margin = f32 || smoothing ? 0.85 : 1.0;
+  double least = margin * ((f32 ? 4.6 : 6.0) + rounds(1) * (1.1 + chunks * (rows + (f32 ? 1.67 : 1.58) * kt2)));
   int best = 0;
-  for (int rt = 1; rt <= 3; ++rt) {
-    const double row = f32 ? 0.9 + 0.75 * kt2 : (smoothing ? 0.54 : 0.44) + 0.36 * kt2;
-    const double t = rounds(rt) * (3 + 2 * (((nchunk + 1) / 2 + 7) / 8) * (0.9 * kt2 + rt * row));
+  for (int rt = f32 || smoothing ? 2 : 1; rt <= 3; ++rt) {
+    const double t = f32 ? rounds(rt) * (11 + chunks * (0.5 * kt2 + rt * (0.5 + 1.02 * kt2)))
+                         : 2.5 + rounds(rt) * (5.2 + chunks * (kt2 + rt * ((smoothing ? 0.46 : 0.2) + 0.56 * kt2)));
     if (t < least) {
       least = t;
       best = rt;
@@ -119,13 +125,29 @@ inline int full_step_parts_rows(int N, int64_t B, int D, int k, bool f32, bool s
   return best;
 }
 
-// Whether the general cached step runs in parts, 32 rows per workgroup: where that leaves work for half of the compute units
-// (6 x 700 x 3304, rank 33: 31 -> 24 us; but 1500 x 1304, rank 100: 11 and 13 us), under the limits above; float32 rows from rank
-// 65 and 768 channels on (7591 x 2136, rank 74: 57 -> 47 us; but 6163 x 1592, rank 37: 26 and 28 us, 10 x 598 x 552, rank 80: 15
-// and 18 us) and with nothing to add (registers).
-inline bool cached_step_may_take_parts(int D, int k, bool f32, bool add) {
-  return k > (f32 ? 64 : 16) && k <= 128 && D >= (f32 ? 768 : 512) && !(f32 && add);
+// Shares of the channels in the general cached step: until there are about four workgroups per compute unit, at least two chunks of
+// 32 channels for each of the four waves.
+inline int cached_shares(int64_t tiles, int64_t B, int D, bool parts, int cus) {
+  const int64_t want = (4 * (int64_t)cus + tiles * B - 1) / (tiles * B), most = parts ? (D + 63) / 64 / 4 : (D + 31) / 32 / 8;
+  return (int)std::max<int64_t>(1, std::min(want, most));
 }
-inline bool cached_step_takes_parts(int N, int64_t B, int cus) { return 2 * (int64_t)((N + 31) / 32) * B >= cus; }
+
+// Whether the general cached step runs in parts, 32 rows per workgroup.  Never with a tensor to add: there parts took 1.11
+// of the time over 900 calls (2 x 2566 x 632, rank 32: 10.1 and 16.5 us; its registers spilled).
+inline bool cached_step_may_take_parts(int D, int k, bool f32, bool add) { return k > (f32 ? 48 : 16) && k <= 128 && D > 480 && !add; }
+inline bool cached_step_takes_parts(int N, int64_t B, int D, int k, bool f32, int cus) {
+  const double chunks = ((D + 31) / 32) / 4.0, kt = (k + 15) / 16, kt2 = (k + 31) / 32;
+  struct Load { double groups, chunks; };       // workgroups per compute unit, chunks per wave
+  auto load = [&](int64_t tiles, bool parts) {
+    const int shares = cached_shares(tiles, B, D, parts, cus);
+    return Load{(double)((tiles * B * shares + cus - 1) / cus), chunks / shares};
+  };
+  const Load p = load((N + 31) / 32, true), f = load((N + 15) / 16, false);
+  const double parts = 4.3 + 1.7 * kt2 + (f32 ? p.groups * (0.78 + p.chunks * (1.28 + 0.33 * kt2)) : p.groups * (0.53 + p.chunks * (0.5 + 0.37 * kt2)));
+  // V passes through LDS in pieces of 32 columns up to rank 32 and of 64 beyond
+  const double column = 0.127 * kt + 0.049 * (k <= 32 ? 2 : (k + 63) / 64 * 4);
+  const double plain = 3.3 + 0.53 * kt + (f32 ? f.groups * (0.6 + f.chunks * (0.28 + column)) : f.groups * (0.26 + f.chunks * (0.21 + column)));
+  return parts < (f32 ? 0.91 : 0.97) * plain;
+}
 
 }  // namespace svdc

@@ -93,7 +93,8 @@ def test_general_kernels_at_the_edges_of_their_tiles(dtype, B, N, D, k):
 
 
 @pytest.mark.parametrize("dtype,N,D,k", [(torch.bfloat16, 601, 2008, 64), (torch.bfloat16, 8101, 520, 50), (torch.bfloat16, 8701, 520, 50),
-                                         (torch.bfloat16, 5003, 520, 127), (torch.float32, 8701, 796, 50), (torch.float32, 5003, 796, 100)])
+                                         (torch.bfloat16, 5003, 520, 127), (torch.float32, 8701, 796, 50), (torch.float32, 5003, 796, 100),
+                                         (torch.bfloat16, 8101, 1288, 50), (torch.float32, 6001, 1032, 117)])
 def test_general_kernels_in_bf16_parts(dtype, N, D, k):
     """Tiles of 16, 32 and 48 rows, ragged rows, channels (an odd number of chunks, a chunk that is partly outside) and coefficients."""
     test_general_kernels_at_the_edges_of_their_tiles(dtype, 1, N, D, k)
@@ -114,7 +115,7 @@ def test_general_projection_in_parts_is_as_good_as_float32(dtype, N, D, k):
 
 
 @pytest.mark.parametrize("dtype,N,D,k", [(torch.bfloat16, 601, 2008, 64), (torch.bfloat16, 8101, 520, 50), (torch.bfloat16, 8701, 520, 50),
-                                         (torch.float32, 8701, 796, 50), (torch.float32, 5003, 796, 100)])
+                                         (torch.bfloat16, 8101, 1288, 50), (torch.float32, 8701, 796, 50), (torch.float32, 6001, 1036, 117)])
 def test_general_kernels_in_parts_keep_the_range_of_float32(dtype, N, D, k):
     """Infinities, a NaN, values next to the largest float32, and rows and basis columns down to the smallest normal ones: what
     float64 says is infinite, NaN or finite is so in the results, and finite results are within 16 u (u = 2^-24) of the norm of

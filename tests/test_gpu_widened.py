@@ -461,7 +461,9 @@ def test_full_step_residual_ema(dtype, B, N, D, k):
 def test_general_kernels_of_large_calls_with_extras(dtype):
     """The general kernels of calls that fill the machine: residual smoothed, several states, a tensor added."""
     test_full_step_residual_ema(dtype, 1, 8701, 776, 50)
+    test_full_step_residual_ema(dtype, 1, 4931, 1168, 86)
     test_forecast_combine(dtype, 1, 4999, 520, 70)
+    test_forecast_combine(dtype, 1, *((3517, 2056, 121) if dtype == torch.bfloat16 else (6001, 1036, 117)))
 
 
 def test_full_step_residual_ema_rejects_bad_arguments():

@@ -19,7 +19,7 @@ int main(int argc, char**) {
     long long B;
     while (std::scanf("%lld %d %d %d %d %d %d", &B, &N, &D, &k, &f32, &extra, &cus) == 7)
       std::printf("%d\n", (svdc::full_step_may_take_parts(D, k, f32, extra) ? 10 * svdc::full_step_parts_rows(N, B, D, k, f32, extra, cus) : 0) +
-                               (svdc::cached_step_may_take_parts(D, k, f32, extra) && svdc::cached_step_takes_parts(N, B, cus)));
+                               (svdc::cached_step_may_take_parts(D, k, f32, extra) && svdc::cached_step_takes_parts(N, B, D, k, f32, cus)));
     return 0;
   }
   if (argc > 2) {
@@ -141,9 +141,11 @@ def test_small_full_steps_take_single_tiles_while_l2_holds_the_basis(tiling):
 def test_general_steps_in_parts(tiling):
     """Row tiles of the general full step on the bf16 matrix cores (0: the float32 ones) and whether the cached step runs there:
     the sizes of the GPU tests, measured ones (gain), and the limits of the rank, the channels, the rows and the storage type."""
-    want = [((1, 601, 2008, 64, 0, 0), (1, False)), ((1, 8101, 520, 50, 0, 0), (2, True)), ((1, 8701, 520, 50, 0, 0), (3, True)),
-            ((1, 8701, 800, 50, 1, 0), (3, False)), ((1, 5003, 800, 100, 1, 0), (2, True)), ((1, 8701, 776, 50, 0, 1), (3, True)),
+    want = [((1, 601, 2008, 64, 0, 0), (1, False)), ((1, 8101, 520, 50, 0, 0), (2, False)), ((1, 8701, 520, 50, 0, 0), (3, False)),
+            ((1, 8101, 1288, 50, 0, 0), (2, True)), ((1, 8701, 800, 50, 1, 0), (3, False)), ((1, 6001, 1036, 117, 1, 0), (2, True)),
+            ((1, 8701, 776, 50, 0, 1), (3, False)), ((1, 4931, 1168, 86, 0, 1), (2, False)), ((1, 3517, 2056, 121, 0, 0), (1, True)),
             ((4, 2173, 1408, 50, 0, 0), (3, True)), ((6, 700, 3304, 33, 0, 0), (2, True)), ((1, 1500, 1304, 100, 0, 0), (1, False)),
+            ((17, 230, 616, 24, 0, 0), (0, False)), ((15, 258, 1000, 72, 1, 0), (0, False)), ((3, 4082, 888, 34, 0, 1), (0, False)),
             ((20, 900, 1000, 16, 0, 0), (0, False)), ((57, 3874, 72, 36, 0, 0), (0, False)), ((4, 2173, 1408, 129, 0, 0), (0, False)),
             ((1, 8701, 800, 50, 1, 1), (0, False)), ((1, 10032, 2800, 9, 1, 0), (0, False))]
     assert tiling([c + (256,) for c, _ in want], rule=["general", "steps", "parts"]) == [w for _, w in want]
