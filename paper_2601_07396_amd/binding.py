@@ -104,7 +104,7 @@ def load_library():
         spec = importlib.util.spec_from_file_location("_fast_calls", os.path.join(PKG_DIR, "_fast_calls.so"))
         fast = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(fast)
-        fast.bind({name: C.cast(getattr(lib, name), C.c_void_p).value for name in EXPORTS})
+        fast.bind({name: C.cast(getattr(lib, name), C.c_void_p).value for name in EXPORTS}, Shape)
         _fast = fast
     _lib = lib
     return lib

@@ -15,6 +15,8 @@
 
 namespace {
 
+PyTypeObject* shape_type;       // binding.Shape
+
 // addresses inside the library that the binding loaded
 struct Library {
   decltype(&svdcache_packed_basis_bytes) packed_basis_bytes;
@@ -34,7 +36,7 @@ struct Args {
 
   explicit Args(PyObject* shape) {
     Py_buffer view;
-    if (PyObject_GetBuffer(shape, &view, PyBUF_SIMPLE) != 0) return;
+    if (Py_TYPE(shape) != shape_type || PyObject_GetBuffer(shape, &view, PyBUF_SIMPLE) != 0) return;
     if (view.len == (Py_ssize_t)sizeof(s)) {
       std::memcpy(&s, view.buf, sizeof(s));
       ok = s.dtype == SVDC_F32 || s.dtype == SVDC_BF16;
@@ -74,15 +76,16 @@ struct Args {
   }
   void* packed_basis(PyObject* o) { return ok ? bytes(o, lib.packed_basis_bytes(&s)) : nullptr; }
   void* optional(PyObject* o, void* (Args::*get)(PyObject*)) { return o == Py_None ? nullptr : (this->*get)(o); }
+  // Python's own numbers only: the conversion of any other object runs its code, which may change the list that is being read
   float number(PyObject* o) {
-    const double x = PyFloat_AsDouble(o);
-    if (x == -1.0 && PyErr_Occurred()) ok = false;
+    ok = ok && (PyFloat_CheckExact(o) || PyLong_CheckExact(o));
+    const double x = ok ? PyFloat_AsDouble(o) : 0.0;
+    if (x == -1.0 && PyErr_Occurred()) ok = false;         // an integer beyond the doubles
     return (float)x;
   }
   int32_t flag(PyObject* o) {
-    const int x = PyObject_IsTrue(o);
-    if (x < 0) ok = false;
-    return x > 0;
+    ok = ok && (PyBool_Check(o) || PyLong_CheckExact(o));
+    return ok && PyObject_IsTrue(o) > 0;
   }
 };
 
@@ -173,8 +176,10 @@ PyObject* forecast_combine(PyObject*, PyObject* const* v, Py_ssize_t n) {   // s
   });
 }
 
-// the functions of the loaded library, by name and address
-PyObject* bind(PyObject*, PyObject* addresses) {
+// bind(addresses of the loaded library's functions by name, the class of the shape)
+PyObject* bind(PyObject*, PyObject* args) {
+  PyObject *addresses, *type;
+  if (!PyArg_ParseTuple(args, "O!O!", &PyDict_Type, &addresses, &PyType_Type, &type)) return nullptr;
   auto get = [&](const char* name) -> void* {
     PyObject* o = PyDict_GetItemString(addresses, name);
     return o ? PyLong_AsVoidPtr(o) : nullptr;
@@ -197,6 +202,9 @@ PyObject* bind(PyObject*, PyObject* addresses) {
     return nullptr;
   }
   lib = l;
+  Py_INCREF(type);
+  Py_XDECREF(shape_type);
+  shape_type = reinterpret_cast<PyTypeObject*>(type);
   Py_RETURN_NONE;
 }
 
@@ -206,7 +214,7 @@ PyMethodDef methods[] = {{"full_step", (PyCFunction)(void (*)())full_step, METH_
                          {"forecast", (PyCFunction)(void (*)())forecast, METH_FASTCALL, nullptr},
                          {"forecast_packed", (PyCFunction)(void (*)())forecast_packed, METH_FASTCALL, nullptr},
                          {"forecast_combine", (PyCFunction)(void (*)())forecast_combine, METH_FASTCALL, nullptr},
-                         {"bind", bind, METH_O, nullptr},
+                         {"bind", bind, METH_VARARGS, nullptr},
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fast_calls", "Step calls with ordinary arguments.", -1, methods,
                       nullptr, nullptr, nullptr, nullptr};

@@ -1243,8 +1243,19 @@ def test_step_calls_by_both_routes_of_the_binding(dtype, D, k, monkeypatch):
     """The compiled step calls and the ctypes ones make the same calls, on the current stream, and refuse the same arguments
     with the same errors: other strides, types, sizes and devices, buffers that are too small, numbers out of range."""
     from paper_2601_07396_amd import binding
+    pkg.load_library()
     fast = binding._fast
     assert fast is not None
+    answers = {}                                     # what the module said, by function: 0 made, None not ordinary
+
+    class Recorder:
+        def __getattr__(self, name):
+            def call(*args):
+                answers.setdefault(name, []).append(getattr(fast, name)(*args))
+                return answers[name][-1]
+            return call
+
+    monkeypatch.setattr(binding, "_fast", Recorder())
     B, N = 2, 50
     Fbuf, V, S0 = _rand_problem(B, N, D, k, dtype, seed=D)
     F, V, Rp = Fbuf.to(DEV), V.to(DEV), Fbuf.flip(1).contiguous().to(DEV)
@@ -1278,7 +1289,9 @@ def test_step_calls_by_both_routes_of_the_binding(dtype, D, k, monkeypatch):
            lambda: pkg.svdcache_forecast(shape, S, V, packed, R[:1], Fh), lambda: pkg.svdcache_forecast(shape, S, V, packed, R, wide),
            lambda: pkg.svdcache_forecast_combine(shape, [S], [1.0, 2.0], V, packed, R, None, Fh),
            lambda: pkg.svdcache_forecast_combine(shape, [S] * 5, [1.0] * 5, V, packed, R, None, Fh),
-           lambda: pkg.svdcache_forecast_combine(shape, [S], [float("nan")], V, packed, R, None, Fh)]
+           lambda: pkg.svdcache_forecast_combine(shape, [S], [float("nan")], V, packed, R, None, Fh),
+           lambda: full(shape=bytes(shape)), lambda: full(shape=np.frombuffer(bytes(shape), np.uint8)),
+           lambda: pkg.svdcache_forecast(bytes(shape), S, V, packed, R, Fh)]
 
     def refusals():
         texts = []
@@ -1291,7 +1304,16 @@ def test_step_calls_by_both_routes_of_the_binding(dtype, D, k, monkeypatch):
     side = torch.cuda.Stream()
     torch.cuda.synchronize()
     with torch.cuda.stream(side):
-        by_module, said_module = good(), refusals()
+        by_module = good()
+        made = {name: set(v) for name, v in answers.items()}
+        answers.clear()
+        said_module = refusals()
+    assert made == {name: {0} for name in ("full_step", "forecast", "full_step_residual_ema", "forecast_combine") +
+                    (("full_step_packed", "forecast_packed") if Sp is not None else ())}
+    # a number out of range, or a state too many, is for the library to refuse; all other refusals are Python's
+    assert sorted(answers) == ["forecast", "forecast_combine", "full_step"]
+    assert answers["forecast"] == [None] * 3 and answers["forecast_combine"] == [None, None, -5]
+    assert answers["full_step"] == [None] * 7 + [-5] * 3 + [None] * 5
     monkeypatch.setattr(binding, "_fast", None)
     with torch.cuda.stream(side):
         by_ctypes, said_ctypes = good(), refusals()
@@ -1303,4 +1325,12 @@ def test_step_calls_by_both_routes_of_the_binding(dtype, D, k, monkeypatch):
     two = pkg.make_shape(F[0], k)
     pkg.svdcache_full_step(two, F[0], V[:1], None, R[0], S[:1].contiguous(), None, np.float32(0.5), 1)
     pkg.svdcache_forecast_combine(shape, (S, S), (0.5, 0.5), V, packed, R, None, Fh)
+    # a weight whose conversion takes the other weights away
+    class Greedy:
+        def __float__(self):
+            del weights[1:]
+            return 0.5
+
+    weights = [Greedy()] + [0.5] * 3
+    assert fast.forecast_combine(shape, [S] * 4, weights, V, packed, R, None, Fh) is None and len(weights) == 4
     torch.cuda.synchronize()
