@@ -4,6 +4,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 from typing import Optional
 
 import torch
@@ -99,15 +100,28 @@ def load_library():
         fn = getattr(lib, name)
         fn.restype = res
         fn.argtypes = args
-    if os.path.exists(os.path.join(PKG_DIR, "_fast_calls.so")):
+    _fast = _load_fast_calls(lib)
+    _lib = lib
+    return lib
+
+
+def _load_fast_calls(lib):
+    """The module _fast_calls bound to `lib`, None where it was not built.  It is built against one torch: with another it may
+    not load, and then all calls go through ctypes, which needs none of it."""
+    path = os.path.join(PKG_DIR, "_fast_calls.so")
+    if not os.path.exists(path):
+        return None
+    try:
         import importlib.util
-        spec = importlib.util.spec_from_file_location("_fast_calls", os.path.join(PKG_DIR, "_fast_calls.so"))
+        spec = importlib.util.spec_from_file_location("_fast_calls", path)
         fast = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(fast)
         fast.bind({name: C.cast(getattr(lib, name), C.c_void_p).value for name in EXPORTS}, Shape)
-        _fast = fast
-    _lib = lib
-    return lib
+    except Exception as e:
+        warnings.warn(f"{path} does not load ({e}): step calls take about 4 us more host time each; "
+                      "build it again with `python -m paper_2601_07396_amd.build`", RuntimeWarning, stacklevel=3)
+        return None
+    return fast
 
 
 def svdcache_version() -> int:

@@ -226,3 +226,16 @@ def test_bench_reads_its_traffic_figure_from_the_tracked_profile():
         assert row.rstrip(" |").endswith(str(got))
     assert bench.traffic_from_profile("no_such_kernel") is None
     assert "MEASURED_TRAFFIC" not in open(os.path.join(ROOT, "bench.py")).read()
+
+
+def test_binding_loads_without_its_compiled_step_calls(tmp_path, monkeypatch, lib):
+    """A _fast_calls.so that does not load (built against another torch) leaves the library and the ctypes route as they are."""
+    from paper_2601_07396_amd import binding
+    os.symlink(pkg.lib_path(), tmp_path / "libsvdcache.so")
+    (tmp_path / "_fast_calls.so").write_bytes(b"not a library")
+    monkeypatch.setattr(binding, "PKG_DIR", str(tmp_path))
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_fast", "stale")
+    with pytest.warns(RuntimeWarning, match="_fast_calls.so does not load"):
+        assert binding.load_library() is not None
+    assert binding._fast is None and binding.svdcache_version() == lib.svdcache_version()
