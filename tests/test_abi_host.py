@@ -239,3 +239,27 @@ def test_binding_loads_without_its_compiled_step_calls(tmp_path, monkeypatch, li
     with pytest.warns(RuntimeWarning, match="_fast_calls.so does not load"):
         assert binding.load_library() is not None
     assert binding._fast is None and binding.svdcache_version() == lib.svdcache_version()
+
+
+def test_build_without_torch_headers_keeps_the_libraries(tmp_path, monkeypatch):
+    """Where the compiled step calls cannot be built, both libraries are, and none from an earlier build is left."""
+    from paper_2601_07396_amd import build
+    made = []
+
+    class Done:
+        returncode, stdout = 0, ""
+
+    def run(cmd, **kw):
+        made.append(os.path.basename(cmd[cmd.index("-o") + 1]))
+        return Done()
+
+    def no_torch():
+        raise ImportError("no headers")
+
+    fast = tmp_path / "_fast_calls.so"
+    fast.write_bytes(b"old")
+    monkeypatch.setattr(build.subprocess, "run", run)
+    monkeypatch.setattr(build, "_torch_flags", no_torch)
+    monkeypatch.setattr(build, "FAST_CALLS_PATH", str(fast))
+    assert build.build() == build.LIB_PATH
+    assert {"libsvdcache.so", "libsvdcache_probes.so"} <= set(made) and not fast.exists()
