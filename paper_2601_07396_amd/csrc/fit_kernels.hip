@@ -1302,14 +1302,18 @@ __global__ __launch_bounds__(1024) void jacobi_finish_kernel(const double* __res
     double s = 0.0;
     for (int r = lane; r < l; r += kWave) s += A[(int64_t)j * l + r] * A[(int64_t)j * l + r];
     s = wave_sum(s);
-    if (lane == 0) nrm[j] = s;
+    if (lane == 0) nrm[j] = fabs(s);
   }
   __syncthreads();
   double* wo = Wout + (int64_t)b * l * l;
   for (int j = wave; j < l; j += 16) {
     const double nj = nrm[j];
+    const long long kj = __double_as_longlong(nj);       // ranked by bit pattern, as in jacobi_output
     int rank = 0;
-    for (int i = lane; i < l; i += kWave) rank += (nrm[i] > nj || (nrm[i] == nj && i < j)) ? 1 : 0;
+    for (int i = lane; i < l; i += kWave) {
+      const long long ki = __double_as_longlong(nrm[i]);
+      rank += (ki > kj || (ki == kj && i < j)) ? 1 : 0;
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) rank += __shfl_xor(rank, o, kWave);
     if (lane == 0 && rank < k) sigma[(int64_t)b * k + rank] = (float)sqrt(nj);

@@ -768,7 +768,8 @@ def test_fit_basis_at_the_tile_edges_of_the_factor(B, l):
     test_fit_basis_at_the_block_edges_of_the_small_matrices(torch.float32, B, 256, l, 150)
 
 
-@pytest.mark.parametrize("k,p", [(4, -1), (24, 0), (96, -1), (120, 16)])     # the wave Jacobi by width, and the one of 129..138 columns
+@pytest.mark.parametrize("k,p", [(4, -1), (24, 0), (96, -1), (120, 16),      # the wave Jacobi by width, the one of 129..138 columns,
+                                 (96, 64), (128, 72)])                        # and the one by column blocks
 @pytest.mark.parametrize("value", [float("nan"), float("-inf")], ids=["nan", "inf"])
 def test_fit_writes_every_rank_of_a_block_that_is_not_finite(k, p, value):
     """Norms that compare with nothing still have one rank each: no output of such a block is left unwritten, and the other
