@@ -114,6 +114,27 @@ def test_general_projection_in_parts_is_as_good_as_float32(dtype, N, D, k):
     assert rel_err(to_np(Cc[0]), to_np(F[0]) @ to_np(V[0])) <= 0.41 * 2.0 ** -24 * 17 ** 0.5
 
 
+@pytest.mark.parametrize("N,D,k,cached", [(6001, 1036, 117, True), (8701, 1408, 50, False)])
+def test_general_reconstruction_in_parts_is_as_good_as_float32(N, D, k, cached):
+    """R and Fhat of float32 rows that lie mostly in the span of the basis.  P = C V^T from bf16 parts: the leading products of 32
+    coefficients are one matrix instruction (0.41 u sqrt(32 / 2) of P at most, as for C), up to four of them and the other products
+    are added to it, and R or Fhat is rounded once more: 0.41 u sqrt(20) of P, 1.1e-7; the float32 instructions stay within that too."""
+    g = torch.Generator().manual_seed(D + k)
+    V = torch.linalg.qr(torch.randn(1, D, k, generator=g, dtype=torch.float64))[0].float().contiguous()
+    A = torch.randn(1, N, k, generator=g)
+    F = ((A.double() @ V.double().transpose(1, 2)) + 0.05 * torch.randn(1, N, D, generator=g) * (k / D) ** 0.5).float()
+    R, S, Cc, shape, pk = _run_full(F, D, V, torch.zeros(1, N, k), 0.3, True)
+    assert pk is None
+    P = to_np(Cc[0]) @ to_np(V[0]).T
+    bound = 0.41 * 2.0 ** -24 * 20 ** 0.5 * np.linalg.norm(P)
+    assert np.linalg.norm(to_np(R[0]) - (to_np(F[0]) - P)) <= bound
+    if cached:
+        Fh = torch.empty_like(R)
+        pkg.svdcache_forecast(shape, S, V.to(DEV), None, R, Fh)
+        torch.cuda.synchronize()
+        assert np.linalg.norm(to_np(Fh[0]) - (to_np(S[0]) @ to_np(V[0]).T + to_np(R[0]))) <= bound
+
+
 @pytest.mark.parametrize("dtype,N,D,k", [(torch.bfloat16, 601, 2008, 64), (torch.bfloat16, 8101, 520, 50), (torch.bfloat16, 8701, 520, 50),
                                          (torch.bfloat16, 8101, 1288, 50), (torch.float32, 8701, 796, 50), (torch.float32, 6001, 1036, 117)])
 def test_general_kernels_in_parts_keep_the_range_of_float32(dtype, N, D, k):
@@ -727,8 +748,8 @@ def test_fit_basis_at_the_block_edges_of_the_small_matrices(dtype, B, D, l, more
 @pytest.mark.parametrize("l", [2, 3, 4, 5, 8, 9, 12, 15, 24, 25, 32, 33, 41, 49])
 @pytest.mark.parametrize("D", [104, 256])       # the general products, and the matrix-core ones (the sketch goes on as operand words)
 def test_fit_basis_at_the_widths_of_narrow_sketches(l, D):
-    """Panels of 4 columns, levels of the inverse at 4, 8, 16 and 32 columns, 8-column blocks of the Jacobi that are empty or
-    partly filled."""
+    """Panels of 16 columns of the factor and its inverse, whole or padded, 8-column blocks of the Jacobi that are empty or partly
+    filled."""
     test_fit_basis_at_the_block_edges_of_the_small_matrices(torch.float32, 2, D, l, 150)
 
 
