@@ -1,6 +1,6 @@
 // The step calls of the Python binding for their ordinary arguments: tensors of exactly the layout that the shape describes, in
 // GPU memory.  What the binding checks attribute by attribute in Python and marshals through ctypes is read here from the tensors
-// themselves: 7 -> 3.4 us of host time a call (a full and two cached steps of 2 x 256 x 64 float32 back to back: 21 -> 10.2 us).
+// themselves: 7 -> 3.4 us of host time a call (a full and two cached steps of 2 x 256 x 64 float32 back to back: 20-21 -> 10-12 us).
 // Anything else -- another layout, a subclass, a tensor without storage, a wrong type -- returns None, and the binding goes on in
 // Python, which accepts or refuses it with its own message.  No arithmetic and no kernels here.
 #include <Python.h>

@@ -1,7 +1,8 @@
-// General (any shape, any k <= 1024) kernels for the full-compute step and the cached step, on the float32 matrix
-// cores (v_mfma_f32_16x16x4_f32: float32 operands as they are, float32 accumulation).  They serve the shapes that the
-// bf16 matrix-core kernels do not cover (hidden sizes that are not one of the instantiated multiples of 128, ranks above
-// 128 or not a multiple of 4) and calls without a packed basis, for either storage type.
+// General (any shape, any k <= 1024) kernels for the full-compute step and the cached step, for either storage type.  They serve
+// the shapes that the packed-basis kernels do not cover (hidden sizes that are not one of the instantiated multiples of 128, ranks
+// above 128 or not a multiple of 4) and calls without a packed basis.  There are two kinds of each, between which step_tiling.h
+// decides: on the float32 matrix cores (v_mfma_f32_16x16x4_f32: float32 operands as they are, float32 accumulation), and, further
+// down, on the bf16 ones with float32 values in three parts, for larger calls of ranks 17 to 128.  This is about the first.
 //
 // The layout of the instruction is in f32_tiles.h.  The contraction index is permuted so that loads are wide: a lane loads eight
 // consecutive channels 32 c + 8 g + e of its token row, and step e of eight contracts the channels {32 c + 8 g + e}.
@@ -13,7 +14,7 @@
 // read once per 16 rows and not once per row, and the operands of the next 32 channels are requested before the current
 // ones are multiplied.  Measured at 4 x 2173 x 1408 bf16, rank 50: full step 904 -> 68 us, cached step 290 -> 33 us; at
 // 22848 x 2136, rank 21: 1454 -> 108 and 490 -> 67 us, against one wave per token row on the vector units, which read
-// all of V for every row.  Tiles of 32 rows were no faster (half as many waves to hide the latency).
+// all of V for every row.  Tiles of 32 rows were no faster with these instructions (half as many waves to hide the latency).
 #include <algorithm>
 #include <type_traits>
 
@@ -264,7 +265,7 @@ __global__ __launch_bounds__(64 * kCachedWaves, 4) void forecast_general_kernel(
 // the vector instructions (11 for every pair of elements of V that is split, 70 for every row tile and chunk that is put
 // together), which is why 32 or 48 rows share a piece of V.  The leading products of every chunk are added up in float64:
 // C is within 2.8e-8 of its norm of the float64 product at 1408 and 2.8e-8 at 3304 channels, 3.4e-8 with float32 instructions.
-// Measured at 4 x 2173 x 1408 bf16, rank 50: full step 68 -> 46 us, cached step 31 -> 24 us (44 and 23 with parts that do not
+// Measured at 4 x 2173 x 1408 bf16, rank 50: full step 68 -> 46 us, cached step 31 -> 23 us (44 and 22.5 with parts that do not
 // reach the whole range); 22848 x 2136 at rank 21: 110 -> 73 and 67 -> 47 us.
 // ---------------------------------------------------------------------------
 // What is split is multiplied by 2^24 first, so that the third part of the smallest normal float32 is a normal bf16 too: the sum
