@@ -34,9 +34,7 @@ __device__ __forceinline__ double from_row(double x) {
 // x of lane J of the same row of 16 lanes (row_newbcast)
 template <int J>
 __device__ __forceinline__ double from_lane(double x) {
-  const int lo = __double2loint(x), hi = __double2hiint(x);
-  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x150 + J, 0xf, 0xf, true),
-                          __builtin_amdgcn_update_dpp(lo, lo, 0x150 + J, 0xf, 0xf, true));
+  return __builtin_amdgcn_update_dpp(x, x, 0x150 + J, 0xf, 0xf, true);      // one v_mov_b64_dpp
 }
 
 __device__ __forceinline__ double wave_max(double x) {
@@ -55,10 +53,10 @@ __device__ __forceinline__ double wave_max(double x) {
 
 // 16 x 16 tile A = L' D L'^T by one wave, with U = L'^-1.  Lane (m = lane % 16, kq = lane / 16) holds A[m][4 c + kq] in a[c],
 // which for a symmetric matrix is the result layout of the float64 matrix instruction; lo and u receive L' (without its
-// unit diagonal) and U in the same places, dcol[c] the pivot of column 4 c + kq, drow that of row m.  Column j of the
+// unit diagonal) and U in the same places, drow the pivot of row m.  Column j of the
 // elimination is brought to every row of lanes, its pivot and row j to every lane of a row: no LDS and no barrier.
 struct TileFactor {
-  double a[4], lo[4], u[4], dcol[4], drow;
+  double a[4], lo[4], u[4], drow;
   bool dependent;
   template <int J>
   __device__ __forceinline__ void column(int m, int kq, int w, double pivot_floor) {
@@ -71,20 +69,21 @@ struct TileFactor {
     double x = __builtin_amdgcn_rcp(d);
     const double e1 = fma(-d, x, 1.0);
     x = fma(x, fma(e1, e1, e1), x);
-    const double f = m > J ? -(y * x) : 0.0;
+    const double below = m > J ? y : 0.0, f = -(below * x);
+    // the two factors of A first: the same bits on both sides of the diagonal, which (f times the row) would drift apart until what
+    // rows and columns of a small pivot say differs by more than the pivots of dependent columns
 #pragma unroll
     for (int c = cj; c < 4; ++c)
-      if (4 * c + 3 > J) a[c] = fma(f, from_lane<J>(a[c]), a[c]);
+      if (4 * c + 3 > J) a[c] = fma(-(below * from_lane<J>(a[c])), x, a[c]);
 #pragma unroll
     for (int c = 0; c <= cj; ++c) u[c] = fma(f, from_lane<J>(u[c]), u[c]);
-    if (kq == gj) { lo[cj] = -f; dcol[cj] = d; }
+    if (kq == gj) lo[cj] = -f;
     if (m == J) drow = d;
   }
   __device__ __forceinline__ void run(int m, int kq, int w, double pivot_floor) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       lo[c] = 0.0;
-      dcol[c] = 1.0;
       u[c] = m == 4 * c + kq ? 1.0 : 0.0;
     }
     drow = 1.0;
@@ -100,6 +99,25 @@ struct TileFactor {
   }
 };
 
+// X = A L'^-T for 16 rows in the result layout (row 4 v + lane / 16, column lane % 16), by substitution: column J is final when its
+// turn comes, and every lane takes it times L'[m][J] from its own.  l[J] = L'[m][J0 + J] of the lane's column m, zero from m on.
+// Not as a product with the inverse: where a panel holds columns of the matrix' own scale and columns that depend on them to 1e-7, that
+// is A times 1e7 / A, of whose sum all but a few digits cancel, and the error can exceed the shift that holds the pivots of the
+// next panels up: negative ones in 1 to 4 of 100 matrices of rank 10, none in 6000 like this.
+template <int J0, int J = 0>          // columns J0 .. J0 + 7
+__device__ __forceinline__ void substitute(f64x4& x, const double (&l)[8]) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) x[v] = fma(-from_lane<J0 + J>(x[v]), l[J], x[v]);
+  if constexpr (J < 7) substitute<J0, J + 1>(x, l);
+}
+
+// l[J] / diagonal entry J0 + J, which that lane has the reciprocal of: rows of L to rows of the unit triangle
+template <int J0, int J = 0>
+__device__ __forceinline__ void unit_columns(double (&l)[8], double rinv) {
+  l[J] *= from_lane<J0 + J>(rinv);
+  if constexpr (J < 7) unit_columns<J0, J + 1>(l, rinv);
+}
+
 __device__ __forceinline__ double rsqrt_f64(double d) {
   const double r = __builtin_amdgcn_rsq(d);      // the hardware's estimate and one step of third order
   const double e = fma(-(d * r), r, 1.0);
@@ -114,11 +132,12 @@ __device__ __forceinline__ double rsqrt_f64(double d) {
 // The matrix lives in registers as 16 x 16 tiles in the result layout of v_mfma_f64_16x16x4_f64, negated: the first NT waves
 // own a diagonal tile each, the others share the rest and the tiles of the inverse.  Right-looking, a panel of 16 columns at a time:
 //   the wave of the diagonal tile factors it and forms D = L_pp^-1                       (TileFactor)
-//   L_ip = A_ip D^T,   M_pj = -D sum_{k < p} L_pk M_kj           one matrix product each; only these pass through LDS
+//   L_ip = A_ip L_pp^-T by substitution,   M_pj = -D sum_{k < p} L_pk M_kj by a product; only these pass through LDS
 //   A_ij -= L_ip L_jp^T,   the sums of the inverse grow by L_ip M_pj
 // What bounds it is a chain: of 34000 clocks at 64 columns 6000 go by before the first pivot, 3500 in the 16 pivots of each
-// panel (40 instructions a column), and another 3500 a panel in the two products and the barriers between one tile's pivots
-// and the next one's.  So the diagonal tiles have waves of their own, which update the next tile first and go on while the
+// panel (40 instructions a column), and another 3500 a panel in the substitution, the product and the barriers between one
+// tile's pivots and the next one's (with a product instead of the substitution and two moves instead of one for a lane's
+// double: as much).  So the diagonal tiles have waves of their own, which update the next tile first and go on while the
 // others finish; the square roots and all stores wait until the end.  Measured inside a fit: 4.6 us at 8 columns, 16 us at 64,
 // 37 us at 128, against 5.4, 24 and 61 us (in three launches) with panels of 4 columns in blocks of 4 x 4 per thread.
 //   NT = 1: l <= 16; 4: blocks of 64 columns; 8: 65 to 128 columns at once
@@ -137,7 +156,9 @@ __global__ __launch_bounds__(NT == 1 ? 64 : 128 * NT) void chol_tiles_kernel(dou
   constexpr int TS = 16 * LT;
   constexpr int NA = NT * (NT - 1) / 2, NH = NT >= 4 ? NT / 4 : 0, NM = 6 * NH, NS = (NA + NM) / NT;
   static_assert((NA + NM) % NT == 0, "the tiles off the diagonal are dealt out evenly");
-  __shared__ __align__(16) double panel[2][NT][TS];   // A_ip, then L_ip, by panel parity
+  __shared__ __align__(16) double panel[NT][TS];      // L_ip
+  __shared__ __align__(16) double lpp[TS], rsv[16];   // unit triangle of the diagonal tile, without its diagonal, and 1 / sqrt(pivots)
+  __shared__ double pivot[NT][16];
   __shared__ __align__(16) double dinv[2][TS];        // D
   __shared__ __align__(16) double mrow[2][3][TS];     // sums, then M_pj, j < p in the same block of 64
   __shared__ double s_shift;
@@ -257,11 +278,8 @@ __global__ __launch_bounds__(NT == 1 ? 64 : 128 * NT) void chol_tiles_kernel(dou
 #pragma unroll
     for (int v = 0; v < 4; ++v) T[(4 * v + kq) * LT + m] = sign * x[v];
   };
-#pragma unroll
-  for (int s = 0; s < NS; ++s)
-    if (!inv[s] && tj[s] == 0 && ti[s] < np) put(panel[0][ti[s]], acc[s], -1.0);
 
-  double dd[4], dcol[4];                              // D and the pivots of the wave's diagonal tile
+  double dd[4];                                       // D of the wave's diagonal tile
   bool dependent = false;
   for (int p = 0; p < np; ++p) {
     const int par = p & 1;
@@ -275,18 +293,27 @@ __global__ __launch_bounds__(NT == 1 ? 64 : 128 * NT) void chol_tiles_kernel(dou
       for (int c = 0; c < 4; ++c) {
         dd[c] = f.u[c] * rs;
         dinv[par][m * LT + 4 * c + kq] = dd[c];
+        lpp[m * LT + 4 * c + kq] = f.lo[c];
         diag[c] = f.lo[c];
-        dcol[c] = f.dcol[c];
       }
+      rsv[m] = rs;                                    // the four rows of lanes hold the same
+      pivot[p][m] = f.drow;
       dependent = f.dependent;
     }
     __syncthreads();
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       if (!inv[s] && tj[s] == p && ti[s] < np) {
-        acc[s] = times_t(panel[par][ti[s]], dinv[par], f64x4{0.0, 0.0, 0.0, 0.0});
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        put(panel[par][ti[s]], acc[s], 1.0);
+        f64x4 x = -acc[s];
+        double l8[8];                                 // half of a row at a time (registers)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) l8[j] = lpp[m * LT + j];
+        substitute<0>(x, l8);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) l8[j] = lpp[m * LT + 8 + j];
+        substitute<8>(x, l8);
+        acc[s] = x * rsv[m];
+        put(panel[ti[s]], acc[s], 1.0);
       }
       if (inv[s] && ti[s] == p && want_inv) {
         acc[s] = -times(dinv[par], mrow[par][tj[s] % 4], f64x4{0.0, 0.0, 0.0, 0.0});
@@ -296,16 +323,15 @@ __global__ __launch_bounds__(NT == 1 ? 64 : 128 * NT) void chol_tiles_kernel(dou
     }
     if (p + 1 == np) break;
     __syncthreads();
-    if (wave > p && wave < np) diag = times_t(panel[par][wave], panel[par][wave], diag);
+    if (wave > p && wave < np) diag = times_t(panel[wave], panel[wave], diag);
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       if (ti[s] <= p || ti[s] >= np) continue;
       if (!inv[s]) {
         if (tj[s] <= p) continue;
-        acc[s] = times_t(panel[par][ti[s]], panel[par][tj[s]], acc[s]);
-        if (tj[s] == p + 1) put(panel[par ^ 1][ti[s]], acc[s], -1.0);
+        acc[s] = times_t(panel[ti[s]], panel[tj[s]], acc[s]);
       } else if (want_inv && tj[s] <= p && ti[s] / 4 == p / 4) {
-        acc[s] = times(panel[par][ti[s]], tj[s] == p ? dinv[par] : mrow[par][tj[s] % 4], acc[s]);
+        acc[s] = times(panel[ti[s]], tj[s] == p ? dinv[par] : mrow[par][tj[s] % 4], acc[s]);
         if (ti[s] == p + 1) put(mrow[par ^ 1][tj[s] % 4], acc[s], 1.0);
       }
     }
@@ -319,7 +345,7 @@ __global__ __launch_bounds__(NT == 1 ? 64 : 128 * NT) void chol_tiles_kernel(dou
     for (int c = 0; c < 4; ++c) {
       const int r = 16 * wave + m, cc = 16 * wave + 4 * c + kq;
       if (r < w && cc < w) {
-        const double sq = dcol[c] * rsqrt_f64(dcol[c]);
+        const double d = pivot[wave][4 * c + kq], sq = d * rsqrt_f64(d);
         gd[(int64_t)r * l + cc] = r == cc ? sq : (r > cc ? diag[c] * sq : 0.0);
         if (want_inv) mh[(int64_t)(cc % kCholBlock) * ldm + r % kCholBlock] = dd[c];
       }

@@ -789,6 +789,30 @@ def test_fit_basis_at_the_tile_edges_of_the_factor(B, l):
     test_fit_basis_at_the_block_edges_of_the_small_matrices(torch.float32, B, 256, l, 150)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("N,D,k,rank", [(64, 264, 12, 10), (64, 264, 16, 10), (64, 256, 32, 10), (130, 264, 50, 10), (130, 256, 64, 3),
+                                        (150, 264, 69, 10), (210, 256, 100, 10)])
+def test_fit_of_many_rank_deficient_blocks(N, D, k, rank, dtype):
+    """Features of a rank far below the sketch width: the Gram matrix has `rank` pivots of its own scale and, from somewhere inside
+    a panel of the factor on, only those that its shift of 1e-14 leaves, which float64 resolves with a few digits.  A factor
+    that loses those (products with an explicit inverse across such a panel) meets a negative pivot in one block of a hundred to a
+    thousand and fills it with NaN; here every one of 400 blocks has to come out."""
+    B = 400
+    g = torch.Generator().manual_seed(N + k)
+    left, right = torch.randn(B, N, rank, generator=g), torch.randn(B, rank, D, generator=g)
+    F = (left @ right).to(dtype)
+    V, sigma, fro2, status = pkg.fit_basis(F.to(DEV), k, return_status=True)
+    torch.cuda.synchronize()
+    assert torch.isfinite(sigma).all() and torch.isfinite(V).all()
+    exact = torch.linalg.svdvals(torch.linalg.qr(left.double())[1] @ torch.linalg.qr(right.double().mT)[1].mT)
+    tol = 1e-5 if dtype == torch.float32 else 2e-2
+    assert ((sigma[:, :rank].double().cpu() - exact).abs() <= tol * exact[:, :1]).all()
+    lead = V[:, :, :rank].double().cpu()
+    assert (lead.mT @ lead - torch.eye(rank)).abs().max() <= 1e-5
+    if dtype == torch.float32:
+        assert (status & pkg.SVDC_FIT_RANK_DEFICIENT).all()
+
+
 @pytest.mark.parametrize("k,p", [(4, -1), (24, 0), (96, -1), (120, 16),      # the wave Jacobi by width, the one of 129..138 columns,
                                  (96, 64), (128, 72)])                        # and the one by column blocks
 @pytest.mark.parametrize("value", [float("nan"), float("-inf")], ids=["nan", "inf"])
