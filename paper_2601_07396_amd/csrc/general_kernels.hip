@@ -260,11 +260,12 @@ __global__ __launch_bounds__(64 * kCachedWaves, 4) void forecast_general_kernel(
 // The same two steps with the products on the bf16 matrix cores, for ranks of 17 to 128 where step_tiling.h says so: a float32
 // is the exact sum of three bf16 parts (8 significant bits each), a product of two keeps six of the nine products of parts,
 // and a bf16 feature is one part already, whose products with V are whole.  The three that are dropped are at most 2^-24 of the
-// product, half a unit of a float32 in the last place (parts are up to 2^-8 and 2^-17 of what is split), and 2^-27.5 in the mean.  An instruction contracts 32 channels or
-// coefficients at 16 times the rate of the float32 one, so six cost less than half of it; what bounds the kernels instead are
-// the vector instructions (11 for every pair of elements of V that is split, 70 for every row tile and chunk that is put
-// together), which is why 32 or 48 rows share a piece of V.  The leading products of every chunk are added up in float64:
-// C is within 2.8e-8 of its norm of the float64 product at 1408 and 2.8e-8 at 3304 channels, 3.4e-8 with float32 instructions.
+// product, half a unit of a float32 in the last place (parts are up to 2^-8 and 2^-17 of what is split), and 2^-27.5 in the mean.
+// An instruction contracts 32 channels or coefficients at 16 times the rate of the float32 one, so six cost less than half of it;
+// what bounds the kernels instead are the vector instructions (13 for every pair of elements of V that is split, 74 for every row
+// tile and chunk that is put together), which is why 32 or 48 rows share a piece of V.  The leading products of every chunk are
+// added up in float64: C is within 2.8e-8 of its norm of the float64 product at 1408 and 2.8e-8 at 3304 channels, 3.4e-8 with
+// float32 instructions.
 // Measured at 4 x 2173 x 1408 bf16, rank 50: full step 68 -> 46 us, cached step 31 -> 23 us (44 and 22.5 with parts that do not
 // reach the whole range); 22848 x 2136 at rank 21: 110 -> 73 and 67 -> 47 us.
 // ---------------------------------------------------------------------------
@@ -802,8 +803,8 @@ template <typename T>
 int32_t forecast_general_typed(const svdc_shape& s, const CoefStates& cs, const float* V, const void* R, const void* X,
                                void* Out, hipStream_t st) {
   constexpr bool kF32 = sizeof(T) == 4;
-  if (cached_step_may_take_parts(s.D, s.k, kF32, X != nullptr) &&
-      cached_step_takes_parts(s.N, s.B, s.D, s.k, kF32, num_compute_units())) {
+  if (cached_step_may_take_parts(s.D, s.k, kF32, cs.m, X != nullptr) &&
+      cached_step_takes_parts(s.N, s.B, s.D, s.k, kF32, cs.m, num_compute_units())) {
     auto kernel = forecast_parts_kernel<T, kCachedPartsRows>;
     const size_t lds = (size_t)kCachedPartsRows * ((s.k + 31) / 32) * 3 * 1024;
     if (allow_lds(kernel, lds) != SVDC_OK) return SVDC_E_HIP;

@@ -134,8 +134,13 @@ inline int cached_shares(int64_t tiles, int64_t B, int D, bool parts, int cus) {
 
 // Whether the general cached step runs in parts, 32 rows per workgroup.  Never with a tensor to add: there parts took 1.11
 // of the time over 900 calls (2 x 2566 x 632, rank 32: 10.1 and 16.5 us; its registers spilled).
-inline bool cached_step_may_take_parts(int D, int k, bool f32, bool add) { return k > (f32 ? 48 : 16) && k <= 128 && D > 480 && !add; }
-inline bool cached_step_takes_parts(int N, int64_t B, int D, int k, bool f32, int cus) {
+// Several states are combined once per row tile and share of the channels, of which the parts have more: float32 rows gain
+// nothing then (280 calls: 1.002 of the time) and stay, bf16 rows have to promise more (418 calls: 18 slower by up to 15 % with the
+// margin of one state).
+inline bool cached_step_may_take_parts(int D, int k, bool f32, int states, bool add) {
+  return k > (f32 ? 48 : 16) && k <= 128 && D > 480 && !add && !(f32 && states > 1);
+}
+inline bool cached_step_takes_parts(int N, int64_t B, int D, int k, bool f32, int states, int cus) {
   const double chunks = ((D + 31) / 32) / 4.0, kt = (k + 15) / 16, kt2 = (k + 31) / 32;
   struct Load { double groups, chunks; };       // workgroups per compute unit, chunks per wave
   auto load = [&](int64_t tiles, bool parts) {
@@ -143,11 +148,13 @@ inline bool cached_step_takes_parts(int N, int64_t B, int D, int k, bool f32, in
     return Load{(double)((tiles * B * shares + cus - 1) / cus), chunks / shares};
   };
   const Load p = load((N + 31) / 32, true), f = load((N + 15) / 16, false);
-  const double parts = 4.3 + 1.7 * kt2 + (f32 ? p.groups * (0.78 + p.chunks * (1.28 + 0.33 * kt2)) : p.groups * (0.53 + p.chunks * (0.5 + 0.37 * kt2)));
   // V passes through LDS in pieces of 32 columns up to rank 32 and of 64 beyond
   const double column = 0.127 * kt + 0.049 * (k <= 32 ? 2 : (k + 63) / 64 * 4);
-  const double plain = 3.3 + 0.53 * kt + (f32 ? f.groups * (0.6 + f.chunks * (0.28 + column)) : f.groups * (0.26 + f.chunks * (0.21 + column)));
-  return parts < (f32 ? 0.91 : 0.97) * plain;
+  const double parts = 4.3 + 1.7 * kt2 + (f32 ? p.groups * (0.78 + p.chunks * (1.28 + 0.33 * kt2))
+                                              : p.groups * (0.53 + p.chunks * (0.5 + 0.37 * kt2)));
+  const double plain = 3.3 + 0.53 * kt + (f32 ? f.groups * (0.6 + f.chunks * (0.28 + column))
+                                              : f.groups * (0.26 + f.chunks * (0.21 + column)));
+  return parts < (f32 ? 0.91 : states > 1 ? 0.9 : 0.97) * plain;
 }
 
 }  // namespace svdc

@@ -12,14 +12,22 @@ PROGRAM = r"""
 // m ntile B kt2 parts elem cus, widest slab, narrow slab -> chunks tiles, the best of 16..6 at the widest slab and its fill
 // with an argument: rt kt2 N B cus -> whether the smoothing full step takes rt row tiles; with two: B N D kt2 parts cus ->
 // whether the full step takes tiles of 16 rows; with three: B N D k f32 smoothing / tensor added cus -> 10 x the row tiles of the
-// general full step in parts + whether the general cached step runs in parts
+// general full step in parts + whether the general cached step runs in parts; with four: B N D k f32 states cus -> the latter
 int main(int argc, char**) {
+  if (argc > 4) {
+    int N, D, k, f32, states, cus;
+    long long B;
+    while (std::scanf("%lld %d %d %d %d %d %d", &B, &N, &D, &k, &f32, &states, &cus) == 7)
+      std::printf("%d\n", (int)(svdc::cached_step_may_take_parts(D, k, f32, states, false) &&
+                                svdc::cached_step_takes_parts(N, B, D, k, f32, states, cus)));
+    return 0;
+  }
   if (argc > 3) {
     int N, D, k, f32, extra, cus;
     long long B;
     while (std::scanf("%lld %d %d %d %d %d %d", &B, &N, &D, &k, &f32, &extra, &cus) == 7)
       std::printf("%d\n", (svdc::full_step_may_take_parts(D, k, f32, extra) ? 10 * svdc::full_step_parts_rows(N, B, D, k, f32, extra, cus) : 0) +
-                               (svdc::cached_step_may_take_parts(D, k, f32, extra) && svdc::cached_step_takes_parts(N, B, D, k, f32, cus)));
+                               (svdc::cached_step_may_take_parts(D, k, f32, 1, extra) && svdc::cached_step_takes_parts(N, B, D, k, f32, 1, cus)));
     return 0;
   }
   if (argc > 2) {
@@ -149,3 +157,10 @@ def test_general_steps_in_parts(tiling):
             ((20, 900, 1000, 16, 0, 0), (0, False)), ((57, 3874, 72, 36, 0, 0), (0, False)), ((4, 2173, 1408, 129, 0, 0), (0, False)),
             ((1, 8701, 800, 50, 1, 1), (0, False)), ((1, 10032, 2800, 9, 1, 0), (0, False))]
     assert tiling([c + (256,) for c, _ in want], rule=["general", "steps", "parts"]) == [w for _, w in want]
+
+
+def test_general_cached_steps_of_several_states_in_parts(tiling):
+    """Several states have to promise more; those of float32 rows stay on the float32 instructions."""
+    calls = [(1, 3517, 2056, 121, 0, 2), (1, 8101, 1288, 50, 0, 4), (4, 1292, 976, 128, 0, 1), (4, 1292, 976, 128, 0, 2),
+             (1, 6001, 1036, 117, 1, 1), (1, 6001, 1036, 117, 1, 2)]
+    assert tiling([c + (256,) for c in calls], rule=["cached", "steps", "of", "states"]) == [True, True, True, False, True, False]
