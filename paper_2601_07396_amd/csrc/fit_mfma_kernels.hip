@@ -1,17 +1,19 @@
 // Matrix-core versions of the two products with F in the basis fit (bf16 features as they are; float32 features
 // split into bf16 high + low parts on the fly, see FPiece and fit_backproject_f32_kernel):
-//   project      Y[N x l] = F * Q           Q stationary in registers (fit_project_mfma_kernel), or, for wide sketches
-//                                           and split operands, shared through LDS by waves that split the rows
-//                                           (fit_project_rows_kernel)
+//   project      Y[N x l] = F * Q           both operands streamed through registers (project_stream.h); in large bf16 calls with
+//                                           wide sketches Q shared through LDS by waves that split the rows
+//                                           (fit_project_rows_kernel), or with narrow ones stationary in registers for the last
+//                                           product (fit_project_mfma_kernel)
 //   backproject  Z[D x l] += F[rows, :]^T * Y[rows, :]         (Z accumulators stationary in registers)
 // Both stream F exactly once per column range of the sketch (one range up to width 128, two up to 256), in 16- or
 // 32-row tiles, on v_mfma_f32_16x16x32_bf16 (operand layouts: see mfma_kernels.hip).  A projection that is followed by a back-projection hands Y over as
-// packed bf16 operand words (pack_y_word) instead of float32 rows; the last projection of a fit writes float32 rows
+// packed bf16 operand words (store_y_half) instead of float32 rows; the last projection of a fit writes float32 rows
 // for the Gram matrix.  backproject stores Z directly when one workgroup covers all rows of a block and otherwise
 // combines the partial results of its row groups with float atomics (into a Z that its caller cleared, or that it clears itself).
 #include <algorithm>
 #include <type_traits>
 
+#include "fit_operands.h"
 #include "svdc_device.h"
 #include "svdc_internal.h"
 
@@ -20,52 +22,6 @@ namespace svdc {
 namespace {
 
 constexpr int kWaves = 4;
-
-__device__ __forceinline__ f32x4 mfma16(const u32x4& a, const u32x4& b, const f32x4& c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
-                                                 0, 0, 0);
-}
-
-// Eight consecutive channels of one token as they are loaded, and as matrix-core operands.  bf16 features are the
-// operand; float32 features are split into bf16 high + low parts when used (the products then take the high part
-// against both parts of the other operand and the low part against its high part: about 16 significant bits).
-template <typename T>
-struct FPiece;
-template <>
-struct FPiece<bf16_t> {
-  static constexpr bool kTwoParts = false;
-  u32x4 w;
-  __device__ __forceinline__ void load(const bf16_t* p) { w = *reinterpret_cast<const u32x4*>(p); }
-  __device__ __forceinline__ void operands(u32x4* hi, u32x4* lo) const { *hi = w; *lo = w; }
-  __device__ __forceinline__ float sumsq() const {
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float x0 = bf16_lo(w[i]), x1 = bf16_hi(w[i]);
-      s += x0 * x0 + x1 * x1;
-    }
-    return s;
-  }
-};
-template <>
-struct FPiece<float> {
-  static constexpr bool kTwoParts = true;
-  f32x4 x[2];
-  __device__ __forceinline__ void load(const float* p) {
-    x[0] = *reinterpret_cast<const f32x4*>(p);
-    x[1] = *reinterpret_cast<const f32x4*>(p + 4);
-  }
-  __device__ __forceinline__ void operands(u32x4* hi, u32x4* lo) const {
-    const float c8[8] = {x[0][0], x[0][1], x[0][2], x[0][3], x[1][0], x[1][1], x[1][2], x[1][3]};
-    split_operand(c8, hi, lo);
-  }
-  __device__ __forceinline__ float sumsq() const {
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) s += x[0][i] * x[0][i] + x[1][i] * x[1][i];
-    return s;
-  }
-};
 
 // Q [B, D, l] float32 -> bf16 high / low operand tiles (projection layout):
 //   tile (cg, jt), lane (r, g), e  ->  Q[d = 32 cg + 8 g + e][j = 16 jt + r]   (0 for j >= l)
@@ -97,36 +53,6 @@ __global__ __launch_bounds__(256) void pack_q_kernel(const float* __restrict__ Q
   }
 }
 
-// Packed Y for the back-projection: Y rounded to bf16, already in the layout of its MFMA operand, so that the
-// back-projection fetches an operand with one 16-byte load per lane instead of 8 scalar loads and 4 conversions.
-// A 32-row step s and coefficient tile jt form one 1 KB word; lane (r, g), element e holds
-//   Y[32 s + 16 (e / 4) + 4 g + e % 4][16 jt + r]      (0 for rows >= N),
-// i.e. the lane's four accumulator rows of the step's first 16-row tile followed by those of the second.  The
-// back-projection contracts over the rows of a step in this same order.  Index: ((b nsteps + s) KT + jt) 64 + lane.
-__device__ __forceinline__ u32x4 pack_y_word(const f32x4& t0, const f32x4& t1, int row, int N) {
-  f32x4 a = t0, c = t1;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if (row + i >= N) a[i] = 0.f;
-    if (row + 16 + i >= N) c[i] = 0.f;
-  }
-  return u32x4{pack_bf16(a[0], a[1]), pack_bf16(a[2], a[3]), pack_bf16(c[0], c[1]), pack_bf16(c[2], c[3])};
-}
-
-// float32 features: the same words in two parts, bf16 high then low, word ((b nsteps + s) KT + jt) 2 + part.  The four
-// accumulator rows of one 16-row tile are 8 bytes of each.
-__device__ __forceinline__ void store_y_half_words(u32x4* Yp, int64_t word, int half, const f32x4& t, int row, int N) {
-  f32x4 a = t;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (row + i >= N) a[i] = 0.f;
-  const uint32_t h0 = pack_bf16(a[0], a[1]), h1 = pack_bf16(a[2], a[3]);
-  const uint32_t l0 = pack_bf16(a[0] - bf16_lo(h0), a[1] - bf16_hi(h0)), l1 = pack_bf16(a[2] - bf16_lo(h1), a[3] - bf16_hi(h1));
-  uint2* out = reinterpret_cast<uint2*>(Yp + word * 2 * 64 + (threadIdx.x & 63)) + half;
-  out[0] = make_uint2(h0, h1);
-  out[2 * 64] = make_uint2(l0, l1);
-}
-
 // ---------------------------------------------------------------------------
 // project: Y = F Q for a group of TG 16-row tiles per workgroup, no atomics.
 // The workgroup walks over the channel slabs (128 * NCW channels each); for one
@@ -138,12 +64,13 @@ __device__ __forceinline__ void store_y_half_words(u32x4* Yp, int64_t word, int 
 //   A operand = F tile   (m = token row, kk = channel)   -- the natural 16-byte row pieces
 //   B operand = Q tile   (kk = channel, n = coefficient)
 //   D[m = 4 g + i][n = r]  ->  Y[row 16 tile + 4 g + i][16 jt + r]
-// FRO: also accumulate sum F^2 (for ||F||_F^2).
+// For the last product of large calls with sketches of up to 32 columns, in bf16 with both parts of Q: 57 x 4608 x 3072, width 16
+// 305 us, 328 streamed (fit_project_stream_kernel); 32 356 and 366.  Also accumulates sum F^2 (for ||F||_F^2, fro_acc nullable).
 // ---------------------------------------------------------------------------
-template <typename T, int NCW, int KT, int TG, bool SPLIT, bool FRO>
-__global__ __launch_bounds__(256) void fit_project_mfma_kernel(const T* __restrict__ F,
+template <int NCW, int KT, int TG>
+__global__ __launch_bounds__(256) void fit_project_mfma_kernel(const bf16_t* __restrict__ F,
                                                                const uint16_t* __restrict__ Qp, float* Y,
-                                                               u32x4* Yp, double* fro_acc, int N, int D, int l,
+                                                               double* fro_acc, int N, int D, int l,
                                                                int64_t ldf, int64_t bstride, int NS,
                                                                int groups_per_block, int ldy) {
   constexpr int PD = 2;
@@ -154,7 +81,7 @@ __global__ __launch_bounds__(256) void fit_project_mfma_kernel(const T* __restri
   const int64_t per = (int64_t)D * KT * 16;
   const u32x4* Qhi = reinterpret_cast<const u32x4*>(Qp + (int64_t)b * 2 * per);
   const u32x4* Qlo = reinterpret_cast<const u32x4*>(Qp + (int64_t)b * 2 * per + per);
-  const T* fbase = F + (int64_t)b * bstride + 8 * g;
+  const bf16_t* fbase = F + (int64_t)b * bstride + 8 * g;
   const int tile0 = rg * TG;
   const int ntiles = min(TG, (N + 15) / 16 - tile0);
 
@@ -164,8 +91,8 @@ __global__ __launch_bounds__(256) void fit_project_mfma_kernel(const T* __restri
 #pragma unroll
     for (int jt = 0; jt < KT; ++jt) acc[t][jt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  FPiece<T> fin[PD][NCW];
-  auto load_tile = [&](int slab, int t, FPiece<T>(&fi)[NCW]) {
+  FPiece<bf16_t> fin[PD][NCW];
+  auto load_tile = [&](int slab, int t, FPiece<bf16_t>(&fi)[NCW]) {
     const int row = min((tile0 + t) * 16 + r, N - 1);
     const int cg0 = (slab * kWaves + wave) * NCW;
 #pragma unroll
@@ -184,7 +111,7 @@ __global__ __launch_bounds__(256) void fit_project_mfma_kernel(const T* __restri
       for (int jt = 0; jt < KT; ++jt) {
         const int64_t ti = (int64_t)(cg0 + c) * KT + jt;
         q_hi[c][jt] = Qhi[ti * 64 + lane];
-        if (SPLIT) q_lo[c][jt] = Qlo[ti * 64 + lane];
+        q_lo[c][jt] = Qlo[ti * 64 + lane];
       }
 #pragma unroll
     for (int t = 0; t < TG; ++t) {
@@ -192,15 +119,13 @@ __global__ __launch_bounds__(256) void fit_project_mfma_kernel(const T* __restri
       if (t < ntiles) {
 #pragma unroll
         for (int c = 0; c < NCW; ++c) {
-          u32x4 fh, fl;
-          fin[u][c].operands(&fh, &fl);
+          const u32x4 fh = fin[u][c].w;
 #pragma unroll
           for (int jt = 0; jt < KT; ++jt) {
             acc[t][jt] = mfma16(fh, q_hi[c][jt], acc[t][jt]);
-            if (FPiece<T>::kTwoParts) acc[t][jt] = mfma16(fl, q_hi[c][jt], acc[t][jt]);
-            if (SPLIT) acc[t][jt] = mfma16(fh, q_lo[c][jt], acc[t][jt]);
+            acc[t][jt] = mfma16(fh, q_lo[c][jt], acc[t][jt]);
           }
-          if (FRO && (tile0 + t) * 16 + r < N) ssq += fin[u][c].sumsq();
+          if ((tile0 + t) * 16 + r < N) ssq += fin[u][c].sumsq();
         }
       }
       // refill this ring slot with the tile PD steps ahead (possibly in the next slab)
@@ -211,14 +136,13 @@ __global__ __launch_bounds__(256) void fit_project_mfma_kernel(const T* __restri
       }
     }
   }
-  if (FRO) {
+  if (fro_acc) {
     const double s = wave_sum((double)ssq);
     if (lane == 0) atomicAdd(fro_acc + b, s);
   }
 
   // add the four waves' partial sums, two row tiles per round
   float* ybase = Y + (int64_t)b * N * ldy;
-  const int nsteps = (N + 31) / 32;
 #pragma unroll
   for (int rd = 0; rd < TG / 2; ++rd) {
 #pragma unroll
@@ -226,36 +150,6 @@ __global__ __launch_bounds__(256) void fit_project_mfma_kernel(const T* __restri
 #pragma unroll
       for (int jt = 0; jt < KT; ++jt) part[wave][tt][jt][lane] = acc[2 * rd + tt][jt];
     __syncthreads();
-    if (Yp) {
-      // packed output for the back-projection: the two tiles of this pass of the loop are one 32-row step (see pack_y_word)
-      const int step = (tile0 + 2 * rd) / 2;
-#pragma unroll
-      for (int jt = 0; jt < KT; ++jt) {
-        if ((jt % kWaves) != wave) continue;
-        f32x4 s2[2];
-#pragma unroll
-        for (int tt = 0; tt < 2; ++tt) {
-          f32x4 s = part[0][tt][jt][lane];
-#pragma unroll
-          for (int w = 1; w < kWaves; ++w) {
-            const f32x4 p = part[w][tt][jt][lane];
-            s[0] += p[0]; s[1] += p[1]; s[2] += p[2]; s[3] += p[3];
-          }
-          s2[tt] = s;
-        }
-        if (step < nsteps) {
-          const int64_t word = ((int64_t)b * nsteps + step) * KT + jt;
-          if constexpr (FPiece<T>::kTwoParts) {
-            store_y_half_words(Yp, word, 0, s2[0], 32 * step + 4 * g, N);
-            store_y_half_words(Yp, word, 1, s2[1], 32 * step + 16 + 4 * g, N);
-          } else {
-            Yp[word * 64 + lane] = pack_y_word(s2[0], s2[1], 32 * step + 4 * g, N);
-          }
-        }
-      }
-      __syncthreads();
-      continue;
-    }
 #pragma unroll
     for (int item = 0; item < 2 * KT; ++item) {
       if ((item % kWaves) != wave) continue;
@@ -278,26 +172,22 @@ __global__ __launch_bounds__(256) void fit_project_mfma_kernel(const T* __restri
 }
 
 // ---------------------------------------------------------------------------
-// project, row-split version for wide sketches: the four waves of a workgroup take different row tiles (RTW
-// each) and all channels, so no partial sums have to be combined, and they share the Q operands through LDS:
+// project, row-split version for large bf16 calls with wide sketches: the four waves of a workgroup take different row tiles
+// (RTW each) and all channels, so no partial sums have to be combined, and they share the Q operands through LDS:
 // the operand words of a slab of SC 32-channel chunks are fetched once per workgroup (registers -> LDS, double
 // buffered, one barrier per slab) and every wave reads them from there.  Per token row the packed sketch is then
-// read from L2 once per 64 RTW rows and from LDS once per 16 RTW rows; with the operands stationary in registers
-// (kernel above) it is read from L2 once per 64 rows, which at sketch width 128 is twice the bytes of F itself.
-// Same operand roles and output mapping as above.  Measured at 57 x 4608 x 3072: 0.47 ms against 0.63 ms at width
-// 128 (0.66 against 0.88 ms with split operands), 0.41 against 0.53 ms at width 64 with split operands; at width
-// 64 with plain operands the register-stationary kernel stays ahead (0.36 against 0.42 ms).
+// read from L2 once per 64 RTW rows and from LDS once per 16 RTW rows, against once per 16 to 96 rows when both operands are
+// streamed (fit_project_stream_kernel), at the price of a memory latency and a barrier per slab, which only several workgroups on a
+// compute unit hide.  57 x 4608 x 3072, this and streamed: split operands, width 64 394 and 447 us, width 128 575 and 587; plain
+// ones, width 128 431 and 457 us.  20 blocks: 146 and 164, 225 and 216, 166 and 170; 8 blocks: 92 and 72, 118 and 95, 88 and 76.
+//   A operand = F tile   (m = token row, kk = channel)   -- the natural 16-byte row pieces
+//   B operand = Q tile   (kk = channel, n = coefficient)
+//   D[m = 4 g + i][n = r]  ->  Y[row 16 tile + 4 g + i][16 jt + r]
+// SPLIT (the last product of a fit): both parts of Q, float32 rows of Y and sum F^2 (fro_acc nullable); otherwise the
+// words of the back-projection.
 // ---------------------------------------------------------------------------
-// SD slabs between the request of a slab's operand words and their move to LDS.  Loads return in order, so waiting for the
-// words also waits for every chunk requested before them: with one workgroup per compute unit a slab takes the memory
-// latency divided by SD, whatever its work.  So the channels may be cut into KS shares, each with four waves and slabs of its
-// own, and the shares' sums meet in LDS at the end: half as many slabs one after the other, twice the waves to hide them.
-// Width 128, 3072 channels, one share (with SD = 2 and twice the chunks in flight up to 24576 rows) and two: split operands of
-// float32 rows, 4608 rows 84 -> 62 us, 18432 104 -> 95, 32768 150 -> 117, 16 x 4608 448 -> 341; of bf16 rows, 4608 rows 70 -> 56;
-// plain operands, 4608 rows 50 -> 37, 4 x 4608 53 -> 41.  bf16 rows in larger calls keep one share and two workgroups per compute
-// unit, which the bound on the registers is for (57 x 4608, split: 657 us, 840 with two shares).
-template <typename T, int KT, int RTW, int SC, bool SPLIT, bool FRO, int SD, int KS>
-__global__ __launch_bounds__(256 * KS, KS == 1 && KT == 8 ? 2 : 1) void fit_project_rows_kernel(const T* __restrict__ F,
+template <int KT, int RTW, int SC, bool SPLIT>
+__global__ __launch_bounds__(256, KT == 8 ? 2 : 1) void fit_project_rows_kernel(const bf16_t* __restrict__ F,
                                                                const uint16_t* __restrict__ Qp, float* Y,
                                                                u32x4* Yp, double* fro_acc, int N, int D, int l,
                                                                int64_t ldf, int64_t bstride,
@@ -309,29 +199,19 @@ __global__ __launch_bounds__(256 * KS, KS == 1 && KT == 8 ? 2 : 1) void fit_proj
   constexpr bool PAIRED = SPLIT;
   constexpr int PD = 4;                       // chunks of F in flight per wave
   static_assert(SC == 2 || SC == 4, "slab of 2 or 4 chunks");
-  static_assert(PAIRED || (SC == PD && SD == 1), "without pairing the ring slot of a chunk is its index in the slab");
+  static_assert(PAIRED || SC == PD, "without pairing the ring slot of a chunk is its index in the slab");
   constexpr int NP = SPLIT ? 2 : 1;           // operand parts (high, low)
   constexpr int WPW = SC * KT / kWaves;       // operand words a wave stages per slab and part
   static_assert(SC * KT % kWaves == 0, "staging must divide among the waves");
   const int b = blockIdx.x / groups_per_block, rg = blockIdx.x % groups_per_block;
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  const int wave = (threadIdx.x >> 6) % kWaves, share = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / 256);
-  u32x4* words;
-  if constexpr (KS == 1) {
-    __shared__ u32x4 own[2 * NP * SC * KT * 64];
-    words = own;
-  } else {                                    // more than a static allocation may have
-    extern __shared__ u32x4 lds_words[];
-    words = lds_words + share * 2 * NP * SC * KT * 64;
-  }
-  auto qs = reinterpret_cast<u32x4(*)[NP][SC * KT][64]>(words);   // two buffers
+  const int wave = threadIdx.x >> 6;
+  __shared__ u32x4 qs[2][NP][SC * KT][64];
   const int64_t per = (int64_t)D * KT * 16;
-  // the slabs of this share (the last one may have one less, or none); all run through `rounds` of them for the barriers
-  const int all = D / (32 * SC), rounds = (all + KS - 1) / KS, first = share * rounds;
-  const int NS = KS == 1 ? all : min(rounds, all - first), NC = NS * SC;
-  const u32x4* Qhi = reinterpret_cast<const u32x4*>(Qp + (int64_t)b * 2 * per) + (int64_t)first * SC * KT * 64;
-  const u32x4* Qlo = reinterpret_cast<const u32x4*>(Qp + (int64_t)b * 2 * per + per) + (int64_t)first * SC * KT * 64;
-  const T* fbase = F + (int64_t)b * bstride + 8 * g + (int64_t)first * SC * 32;
+  const int NS = D / (32 * SC), NC = NS * SC;
+  const u32x4* Qhi = reinterpret_cast<const u32x4*>(Qp + (int64_t)b * 2 * per);
+  const u32x4* Qlo = reinterpret_cast<const u32x4*>(Qp + (int64_t)b * 2 * per + per);
+  const bf16_t* fbase = F + (int64_t)b * bstride + 8 * g;
   const int tile0 = (rg * kWaves + wave) * RTW;
 
   f32x4 acc[RTW][KT];
@@ -343,53 +223,48 @@ __global__ __launch_bounds__(256 * KS, KS == 1 && KT == 8 ? 2 : 1) void fit_proj
   int64_t rowoff[RTW];
 #pragma unroll
   for (int t = 0; t < RTW; ++t) rowoff[t] = (int64_t)min((tile0 + t) * 16 + r, N - 1) * ldf;
-  FPiece<T> fin[PD][RTW];
-  auto load_chunk = [&](int chunk, FPiece<T>(&fi)[RTW]) {
+  FPiece<bf16_t> fin[PD][RTW];
+  auto load_chunk = [&](int chunk, FPiece<bf16_t>(&fi)[RTW]) {
 #pragma unroll
     for (int t = 0; t < RTW; ++t) fi[t].load(fbase + rowoff[t] + 32 * chunk);
   };
-  u32x4 stg[SD][NP][WPW];
-  auto load_stage = [&](int slab, u32x4(&st)[NP][WPW]) {
+  u32x4 stg[NP][WPW];
+  auto load_stage = [&](int slab) {
 #pragma unroll
     for (int i = 0; i < WPW; ++i) {
       const int64_t w = (int64_t)slab * SC * KT + wave * WPW + i;
-      st[0][i] = Qhi[w * 64 + lane];
-      if (SPLIT) st[NP - 1][i] = Qlo[w * 64 + lane];
+      stg[0][i] = Qhi[w * 64 + lane];
+      if (SPLIT) stg[NP - 1][i] = Qlo[w * 64 + lane];
     }
   };
-  auto store_stage = [&](int buf, const u32x4(&st)[NP][WPW]) {
+  auto store_stage = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < WPW; ++i)
 #pragma unroll
-      for (int p = 0; p < NP; ++p) qs[buf][p][wave * WPW + i][lane] = st[p][i];
+      for (int p = 0; p < NP; ++p) qs[buf][p][wave * WPW + i][lane] = stg[p][i];
   };
-  // slab n's words pass through the register set n % SD
-  if (KS == 1 || NS > 0) load_stage(0, stg[0]);
+  load_stage(0);
 #pragma unroll
   for (int u = 0; u < PD; ++u)
     if (u < NC) load_chunk(u, fin[u]);
-  store_stage(0, stg[0]);
-#pragma unroll
-  for (int i = 1; i < SD; ++i)
-    if (i < NS) load_stage(i, stg[i]);
+  store_stage(0);
   __syncthreads();
 
   float ssq = 0.f;
-  // one slab; with paired requests PAR = slab % 2 is a compile-time value, so that the ring slots and sets are static
-  static_assert(!PAIRED || (2 * SC % PD == 0 && 2 % SD == 0), "ring and sets repeat with every second slab");
+  // one slab; with paired requests PAR = slab % 2 is a compile-time value, so that the ring slots are static
+  static_assert(!PAIRED || 2 * SC % PD == 0, "the ring repeats with every second slab");
   auto do_slab = [&](int slab, auto par) {
     constexpr int PAR = decltype(par)::value;
     const int buf = PAIRED ? (PAR & 1) : (slab & 1);
-    if (slab + SD < NS) load_stage(slab + SD, stg[PAR % SD]);
+    if (slab + 1 < NS) load_stage(slab + 1);
 #pragma unroll
     for (int c = 0; c < SC; ++c) {
-      if (KS > 1 && slab >= NS) break;
       const int chunk = slab * SC + c;
       constexpr int kSlotBase = (PAR * SC) % PD;
       const int u = (kSlotBase + c) % PD;     // = chunk % PD
-      u32x4 fh[RTW], fl[RTW];
+      u32x4 fh[RTW];
 #pragma unroll
-      for (int t = 0; t < RTW; ++t) fin[u][t].operands(&fh[t], &fl[t]);
+      for (int t = 0; t < RTW; ++t) fh[t] = fin[u][t].w;
 #pragma unroll
       for (int jt = 0; jt < KT; ++jt) {
         const u32x4 bh = qs[buf][0][c * KT + jt][lane];
@@ -398,11 +273,10 @@ __global__ __launch_bounds__(256 * KS, KS == 1 && KT == 8 ? 2 : 1) void fit_proj
 #pragma unroll
         for (int t = 0; t < RTW; ++t) {
           acc[t][jt] = mfma16(fh[t], bh, acc[t][jt]);
-          if (FPiece<T>::kTwoParts) acc[t][jt] = mfma16(fl[t], bh, acc[t][jt]);
           if (SPLIT) acc[t][jt] = mfma16(fh[t], bl, acc[t][jt]);
         }
       }
-      if (FRO) {
+      if (SPLIT) {
 #pragma unroll
         for (int t = 0; t < RTW; ++t)
           if ((tile0 + t) * 16 + r < N) ssq += fin[u][t].sumsq();
@@ -416,60 +290,32 @@ __global__ __launch_bounds__(256 * KS, KS == 1 && KT == 8 ? 2 : 1) void fit_proj
         if (chunk + PD < NC) load_chunk(chunk + PD, fin[u]);
       }
     }
-    if (slab + 1 < NS) store_stage(buf ^ 1, stg[(PAR + 1) % SD]);
+    if (slab + 1 < NS) store_stage(buf ^ 1);
     __syncthreads();
   };
   if constexpr (PAIRED) {
-    for (int slab = 0; slab < rounds; slab += 2) {
+    for (int slab = 0; slab < NS; slab += 2) {
       do_slab(slab, std::integral_constant<int, 0>{});
-      if (slab + 1 < rounds) do_slab(slab + 1, std::integral_constant<int, 1>{});
+      if (slab + 1 < NS) do_slab(slab + 1, std::integral_constant<int, 1>{});
     }
   } else {
-    for (int slab = 0; slab < rounds; ++slab) do_slab(slab, std::integral_constant<int, 0>{});
+    for (int slab = 0; slab < NS; ++slab) do_slab(slab, std::integral_constant<int, 0>{});
   }
-  if (FRO) {
+  if (SPLIT && fro_acc) {
     const double s = wave_sum((double)ssq);
     if (lane == 0) atomicAdd(fro_acc + b, s);
   }
-  if constexpr (KS > 1) {     // the shares meet in LDS (every wave is past the barrier of the last slab)
-    static_assert(KS == 2 && RTW * KT * kWaves <= KS * 2 * NP * SC * KT, "one share's sums fit");
-    f32x4* part = reinterpret_cast<f32x4*>(words - share * 2 * NP * SC * KT * 64) + (int64_t)wave * RTW * KT * 64 + lane;
-    if (share == 1) {
+  if constexpr (!SPLIT) {   // the wave's two tiles are one 32-row step
+    static_assert(RTW == 2, "two tiles");
+    const int nsteps = (N + 31) / 32, step = tile0 / 2;
+    if (step < nsteps) {
 #pragma unroll
-      for (int t = 0; t < RTW; ++t)
+      for (int jt = 0; jt < KT; ++jt)
 #pragma unroll
-        for (int jt = 0; jt < KT; ++jt) part[(t * KT + jt) * 64] = acc[t][jt];
+        for (int t = 0; t < 2; ++t)
+          store_y_half(FPiece<bf16_t>{}, Yp, ((int64_t)b * nsteps + step) * KT + jt, t, acc[t][jt], 16 * (tile0 + t) + 4 * g, N);
     }
-    __syncthreads();
-    if (share == 1) return;
-#pragma unroll
-    for (int t = 0; t < RTW; ++t)
-#pragma unroll
-      for (int jt = 0; jt < KT; ++jt) acc[t][jt] += part[(t * KT + jt) * 64];
-  }
-  if constexpr (FPiece<T>::kTwoParts) {
-    if (Yp) {   // packed output for the back-projection, tile by tile
-      const int nsteps = (N + 31) / 32;
-#pragma unroll
-      for (int t = 0; t < RTW; ++t) {
-        const int tile = tile0 + t;
-        if (tile / 2 >= nsteps) break;
-#pragma unroll
-        for (int jt = 0; jt < KT; ++jt)
-          store_y_half_words(Yp, ((int64_t)b * nsteps + tile / 2) * KT + jt, tile & 1, acc[t][jt], 16 * tile + 4 * g, N);
-      }
-      return;
-    }
-  } else if constexpr (RTW == 2) {
-    if (Yp) {   // packed output for the back-projection: the wave's two tiles are one 32-row step
-      const int nsteps = (N + 31) / 32, step = tile0 / 2;
-      if (step < nsteps) {
-#pragma unroll
-        for (int jt = 0; jt < KT; ++jt)
-          Yp[(((int64_t)b * nsteps + step) * KT + jt) * 64 + lane] = pack_y_word(acc[0][jt], acc[1][jt], 32 * step + 4 * g, N);
-      }
-      return;
-    }
+    return;
   }
   float* ybase = Y + (int64_t)b * N * ldy;
 #pragma unroll
@@ -516,7 +362,7 @@ __device__ __forceinline__ void sum_row_shares(f32x4* acc, int wave, int lane) {
 //   D[m = 4 g + i][n = r]  ->  Z[32 chunk + 2 (4 g + i) + parity][16 jt + r]
 // Accumulators (NCW chunks x 2 parities x KT tiles) stay in registers over all rows.
 // ---------------------------------------------------------------------------
-// PACKED: Y comes as the operand words that the projection wrote (pack_y_word); the rows of a 32-row step are then
+// PACKED: Y comes as the operand words that the projection wrote (store_y_half); the rows of a 32-row step are then
 // contracted in that word's order, kk = 8 g + e  <->  row 16 (e / 4) + 4 g + e % 4.
 // RS: waves that take every RS-th step of the same channels (backproject_plan).
 template <int NCW, int KT, bool PACKED, int RS>
@@ -623,7 +469,7 @@ __global__ __launch_bounds__(256) void fit_backproject_mfma_kernel(const bf16_t*
 // backproject for float32 features: the same contraction, Z[d][j] += sum_rows F[row][d] Y[row][j], with both
 // operands split into bf16 high + low parts (F_hi Y_hi + F_lo Y_hi + F_hi Y_lo).  A lane loads, for each
 // of its 8 rows, the two float32 channels (2 r, 2 r + 1) of a chunk and splits them.  PACKED: Y comes as the two-part
-// operand words that the projection wrote (store_y_half_words), with the rows of a step in that word's order; otherwise as
+// operand words that the projection wrote (store_y_half), with the rows of a step in that word's order; otherwise as
 // float32 rows, 8 scalar loads and a split per operand in every wave, which bounded the kernel (18432 x 3072, sketch 128:
 // 134 us, 75 us with the words, 55 with the waves on different rows).  Same output mapping and row-group scheme as the bf16 kernel.
 // ---------------------------------------------------------------------------
@@ -746,101 +592,6 @@ struct Strides {
   bool z_cleared;
 };
 
-template <typename T, int NCW, int KT>
-void project_launch(const svdc_shape& s, int l, const void* F, const void* Qp, float* Y, u32x4* Yp,
-                    double* fro_acc, bool split, Strides ld, hipStream_t st) {
-  constexpr bool kF32 = std::is_same<T, float>::value;   // float32 features always take the split sketch
-  // 4 row tiles per workgroup from sketch width 64 on: with a 4-chunk slab that is about 250 registers, so two
-  // workgroups share a compute unit and one streams F while the other loads its Q operands (measured 8 % / 13 %
-  // faster than 8 tiles x 6 chunks at 3072 channels, plain / split operands)
-  constexpr int TG = KT <= 2 ? 8 : 4;
-  // the split operand doubles the Q registers: halve the slab width when it is wide
-  constexpr int NCWS = (NCW * KT > 12 && NCW % 2 == 0) ? NCW / 2 : NCW;
-  const int ntile = (s.N + 15) / 16;
-  const T* f = (const T*)F;
-  const uint16_t* q = (const uint16_t*)Qp;
-  if (kF32) split = true;
-  const int64_t units = num_compute_units();
-  // with_split: whether split operands can come this way (their kernels are not built otherwise)
-  auto stationary = [&](auto tg, auto with_split) {
-    constexpr int G = decltype(tg)::value;
-    const int gpb = (ntile + G - 1) / G;
-    const unsigned grid = (unsigned)((int64_t)gpb * s.B);
-    if constexpr (decltype(with_split)::value) {
-      if (split) {
-        const int NS = s.D / (128 * NCWS);
-        if (fro_acc)
-          fit_project_mfma_kernel<T, NCWS, KT, G, true, true><<<grid, 256, 0, st>>>(
-              f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, NS, gpb, ld.ldy);
-        else
-          fit_project_mfma_kernel<T, NCWS, KT, G, true, false><<<grid, 256, 0, st>>>(
-              f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, NS, gpb, ld.ldy);
-        return;
-      }
-    }
-    if constexpr (!kF32) {
-      const int NS = s.D / (128 * NCW);
-      fit_project_mfma_kernel<T, NCW, KT, G, false, false><<<grid, 256, 0, st>>>(
-          f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, NS, gpb, ld.ldy);
-    }
-  };
-  // Small batches, where TG tiles per workgroup leave more than half of the compute units idle: two tiles.  One block of
-  // 4608 x 3072, sketch 64: 11.9 us with plain operands (17.7 with four tiles), 24.3 us with split ones (67 with
-  // the rows split over the waves in groups of 12 tiles, 42 in groups of 4).
-  if constexpr (KT <= 4) {
-    if ((int64_t)((ntile + TG - 1) / TG) * s.B <= units / 2) return stationary(std::integral_constant<int, 2>{}, std::true_type{});
-  }
-  // wide sketches: rows split over the waves, Q shared through LDS
-  if constexpr (KT >= 4) {
-    constexpr int RTW = (KT == 8) ? 2 : 3;
-    using One = std::integral_constant<int, 1>;
-    using Two = std::integral_constant<int, 2>;
-    using Four = std::integral_constant<int, 4>;
-    auto groups = [&](int rtw) { return (int64_t)((ntile + kWaves * rtw - 1) / (kWaves * rtw)) * s.B; };
-    auto rows = [&](auto rtw, auto sc, auto sp, auto fr, auto sd, auto shares) {
-      constexpr int R = decltype(rtw)::value, KS = decltype(shares)::value;
-      const int g = (ntile + kWaves * R - 1) / (kWaves * R);
-      auto kernel = fit_project_rows_kernel<T, KT, R, decltype(sc)::value, decltype(sp)::value, decltype(fr)::value, decltype(sd)::value, KS>;
-      constexpr int lds = KS == 1 ? 0 : KS * 2 * (decltype(sp)::value ? 2 : 1) * decltype(sc)::value * KT * 1024;
-      static_assert(lds <= 160 * 1024, "operand buffers");
-      // beyond what a launch may ask for by itself; without it the launch fails, which the caller's check reports
-      if constexpr (lds > 64 * 1024) (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-      kernel<<<(unsigned)((int64_t)g * s.B), 256 * KS, lds, st>>>(f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, g, ld.ldy);
-    };
-    if (split) {
-      // Width 128: the channels in two shares, 16 rows per wave while that is one round of workgroups (one per compute unit),
-      // 32 from there on (18432 float32 rows: 95 us, 128 us with 16); bf16 rows beyond that in one share (kernel comment).
-      // Width 64: one share; two take 16 % more time (57 x 4608 bf16 rows: 452 and 529 us).  16 rows where 48 leave compute units idle.
-      using SC = std::integral_constant<int, (KT == 8) ? 2 : 4>;
-      auto tall = [&](auto rtw, auto ks) {
-        if (fro_acc) rows(rtw, SC{}, std::true_type{}, std::true_type{}, ks, ks);
-        else rows(rtw, SC{}, std::true_type{}, std::false_type{}, ks, ks);
-      };
-      if constexpr (KT == 8) {
-        if (groups(1) <= units) tall(One{}, Two{});
-        else if (kF32 || groups(RTW) <= units) tall(Two{}, Two{});
-        else if constexpr (!kF32) tall(Two{}, One{});
-      } else if (groups(RTW) < units) {
-        tall(One{}, One{});
-      } else {
-        tall(std::integral_constant<int, RTW>{}, One{});
-      }
-      return;
-    }
-    // plain operands from here on: never float32 features
-    if constexpr (KT == 8 && !kF32) {
-      // two shares while that is one round; beyond it two workgroups of one share fit on a compute unit (8 blocks of 4608 x 3072:
-      // 78 us, 86 us with two shares)
-      if (groups(RTW) <= units) rows(Two{}, Four{}, std::false_type{}, std::false_type{}, One{}, Two{});
-      else rows(Two{}, Four{}, std::false_type{}, std::false_type{}, One{}, One{});
-    }
-    else if constexpr (!kF32)
-      stationary(std::integral_constant<int, TG>{}, std::false_type{});
-  } else {
-    stationary(std::integral_constant<int, TG>{}, std::true_type{});
-  }
-}
-
 template <typename T, int NCW, int KT, int RS>
 void backproject_launch(const svdc_shape& s, int l, const void* F, const float* Y, const u32x4* Yp, float* Z, int gpb, int rows,
                         Strides ld, hipStream_t st) {
@@ -912,18 +663,64 @@ void by_width(int m, int maxw, Fn12 f12, Fn6 f6, Fn4 f4, Fn3 f3, Fn2 f2, Fn1 f1)
   return f1();
 }
 
-template <typename T, int KT>
-void project_kt(const svdc_shape& s, int l, const void* F, const void* Qp, float* Y, u32x4* Yp, double* fro, bool split,
+// Row tiles of 16 that a workgroup of the streamed projection takes (project_stream.h), 1 to 6: those of the least rounds x
+// (rows + x).  The operands of Q that a workgroup reads once cost it as much as x = 1.25 tiles, at every width and for both
+// storage types: over 14 shapes and 12 kinds of operands (1 x 300 x 1024 to 57 x 4608 x 3072) the choice is within 3 % of the best height.
+// Plain bf16 operands of width 64 have two workgroups on a compute unit up to 5 tiles, which evens out the rounds of larger calls (57 x 4608
+// x 3072: 339 us with 5 tiles, 364 with 6).
+inline int stream_rows(const svdc_shape& s, bool plain64, bool large) {
+  if (plain64 && large) return 5;
+  const int64_t cus = num_compute_units(), ntile = (s.N + 15) / 16;
+  auto cost = [&](int rt) { return (double)(((ntile + rt - 1) / rt * s.B + cus - 1) / cus) * (rt + 1.25); };
+  int best = 1;
+  for (int rt = 2; rt <= 6; ++rt)
+    if (cost(rt) < cost(best)) best = rt;
+  return best;
+}
+
+template <int KT>
+void project_kt(const svdc_shape& s, int l, const void* F, const void* Qp, float* Y, u32x4* Yp, double* fro_acc, bool split,
                 Strides ld, hipStream_t st) {
-  // float32 features hold 8 registers per piece in flight and always carry both sketch parts: narrower slabs
-  constexpr int cap = std::is_same<T, float>::value ? 3 : (KT == 4 ? 4 : width_for<KT>());
-  by_width<cap>(
-      s.D / 128, cap, [&] { project_launch<T, (cap >= 12 ? 12 : 1), KT>(s, l, F, Qp, Y, Yp, fro, split, ld, st); },
-      [&] { project_launch<T, (cap >= 6 ? 6 : 1), KT>(s, l, F, Qp, Y, Yp, fro, split, ld, st); },
-      [&] { project_launch<T, (cap >= 4 ? 4 : 1), KT>(s, l, F, Qp, Y, Yp, fro, split, ld, st); },
-      [&] { project_launch<T, (cap >= 3 ? 3 : 1), KT>(s, l, F, Qp, Y, Yp, fro, split, ld, st); },
-      [&] { project_launch<T, 2, KT>(s, l, F, Qp, Y, Yp, fro, split, ld, st); },
-      [&] { project_launch<T, 1, KT>(s, l, F, Qp, Y, Yp, fro, split, ld, st); });
+  const int64_t tiles = (int64_t)((s.N + 15) / 16) * s.B;
+  const bool large = tiles >= 16 * (int64_t)num_compute_units();
+  const int rt = stream_rows(s, KT == 4 && !split, large);
+  if (s.dtype == SVDC_F32) return fit_project_stream_f32(KT, rt, s, l, ld.ldy, F, Qp, Y, Yp, fro_acc != nullptr, fro_acc, st);
+  // Large bf16 calls with both parts of Q, or wide plain ones, have kernels of their own (9 tiles per compute unit: streamed
+  // 20 to 30 % ahead; 22: 0 to 12 % behind).
+  if (!large || !(split || KT == 8)) return fit_project_stream_bf16(KT, rt, s, l, ld.ldy, F, Qp, Y, Yp, split, fro_acc, st);
+  const bf16_t* f = (const bf16_t*)F;
+  const uint16_t* q = (const uint16_t*)Qp;
+  if constexpr (KT >= 4) {
+    auto rows = [&](auto rtw, auto sc, auto sp) {
+      constexpr int R = decltype(rtw)::value;
+      const int g = ((s.N + 15) / 16 + kWaves * R - 1) / (kWaves * R);
+      fit_project_rows_kernel<KT, R, decltype(sc)::value, decltype(sp)::value>
+          <<<(unsigned)((int64_t)g * s.B), 256, 0, st>>>(f, q, Y, Yp, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, g, ld.ldy);
+    };
+    using Two = std::integral_constant<int, 2>;
+    using Three = std::integral_constant<int, 3>;
+    using Four = std::integral_constant<int, 4>;
+    if constexpr (KT == 8) {
+      if (split) rows(Two{}, Two{}, std::true_type{});
+      else rows(Two{}, Four{}, std::false_type{});
+    } else {
+      rows(Three{}, Four{}, std::true_type{});
+    }
+  } else {
+    // the widest slab of channels that divides them and whose two parts the registers hold
+    constexpr int cap = KT == 1 ? 12 : 6, TG = 8;
+    auto stationary = [&](auto ncw) {
+      constexpr int NCW = decltype(ncw)::value;
+      const int gpb = ((s.N + 15) / 16 + TG - 1) / TG;
+      fit_project_mfma_kernel<NCW, KT, TG><<<(unsigned)((int64_t)gpb * s.B), 256, 0, st>>>(
+          f, q, Y, fro_acc, s.N, s.D, l, s.ldf, s.block_stride, s.D / (128 * NCW), gpb, ld.ldy);
+    };
+    by_width<cap>(
+        s.D / 128, cap, [&] { stationary(std::integral_constant<int, (cap >= 12 ? 12 : 1)>{}); },
+        [&] { stationary(std::integral_constant<int, 6>{}); }, [&] { stationary(std::integral_constant<int, 4>{}); },
+        [&] { stationary(std::integral_constant<int, 3>{}); }, [&] { stationary(std::integral_constant<int, 2>{}); },
+        [&] { stationary(std::integral_constant<int, 1>{}); });
+  }
 }
 
 template <typename T, int NCW, int KT>
@@ -1052,10 +849,7 @@ void fit_mfma_project(const svdc_shape& s, int l, const void* F, const void* Qp,
     const Strides ld{l, l, false};
     by_kt(r[h].l, [&](auto kt) {
       constexpr int KT = decltype(kt)::value;
-      if (s.dtype == SVDC_F32)
-        project_kt<float, KT>(s, r[h].l, F, qp, Y + r[h].j0, (u32x4*)yp, h == 0 ? fro_acc : nullptr, true, ld, st);
-      else
-        project_kt<bf16_t, KT>(s, r[h].l, F, qp, Y + r[h].j0, (u32x4*)yp, h == 0 ? fro_acc : nullptr, split, ld, st);
+      project_kt<KT>(s, r[h].l, F, qp, Y + r[h].j0, (u32x4*)yp, h == 0 ? fro_acc : nullptr, split, ld, st);
     });
     qp += packed_q_bytes_one(s, r[h].l);
     if (yp) yp += packed_y_bytes_one(s, r[h].l, s.dtype == SVDC_F32 ? 2 : 1);

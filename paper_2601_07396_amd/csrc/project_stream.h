@@ -1,0 +1,236 @@
+// Y = F Q for one group of 16-row tiles per workgroup, both operands streamed through registers (gfx950): kernel, its variants by
+// tile height and the rule that picks one.  Included by one translation unit per storage type.
+#pragma once
+#include <algorithm>
+#include <type_traits>
+
+#include "fit_operands.h"
+#include "svdc_internal.h"
+
+namespace svdc {
+namespace {
+
+// ---------------------------------------------------------------------------
+// project, streamed: the NW waves of a workgroup take different channels of the same RT row tiles and keep RT x KT accumulators;
+// pieces of F and operand words of Q pass through a ring of DEPTH slots of CS chunks of 32 channels, the next slot's loads
+// requested as soon as a slot is used, with no barrier until the waves' sums meet in LDS (in the order of the waves: the same
+// bits every run).  Operand roles and output layouts as in fit_project_rows_kernel.
+// What bounds it: F from HBM, the operand words of Q out of L2, once per workgroup, which queue in the same return path of the
+// compute unit, and the latency of the last loads.  With every unit busy for the same number of rounds a call takes
+// rounds x (RT + 1.25) (stream_rows), so the height is chosen for even rounds: 18432 rows on 256 units are 231 tiles of 80 rows, where 128
+// rows left 112 units idle and 64 rows took two rounds.  4608 / 18432 / 20 x 4608 rows of 3072 channels, us, against waves that
+// split the rows or hold slabs of Q (KT = 4 and less) in registers: float32 width 128 67 / 103 / 349 -> 34 / 67 / 312, width 64
+// 27 / 86 / 289 -> 26 / 53 / 245; bf16 split width 128 53 / 68 / 225 -> 28 / 47 / 216, width 64 24 / 51 -> 20 / 37; bf16 plain
+// width 128 44 / 47 -> 20 / 37, width 64 15.1 / 40 / 131 -> 14.8 / 30 / 126.
+// FRO: also accumulate sum F^2 (for ||F||_F^2).
+// ---------------------------------------------------------------------------
+template <typename T, int KT, int RT, int NW, int DEPTH, int CS, bool SPLIT, bool FRO, int WPE>
+__global__ __launch_bounds__(64 * NW, WPE) void fit_project_stream_kernel(const T* __restrict__ F, const uint16_t* __restrict__ Qp, float* Y,
+                                                                          u32x4* Yp, double* fro_acc, int N, int D, int l, int64_t ldf,
+                                                                          int64_t bstride, int groups_per_block, int ldy) {
+  constexpr int NP = SPLIT ? 2 : 1;           // operand parts (high, low)
+  constexpr int G = NW * KT >= 64 ? 1 : 2;    // row tiles that meet in LDS at a time (64 KB)
+  __shared__ f32x4 part[NW][G][KT][64];
+  __shared__ double norm[NW];
+  const int b = blockIdx.x / groups_per_block, rg = blockIdx.x % groups_per_block;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  const int64_t per = (int64_t)D * KT * 16;
+  // the slots of CS chunks that are this wave's (D / 32 is a multiple of 4)
+  const int all = D / (32 * CS), first = wave * all / NW, n = (wave + 1) * all / NW - first;
+  const u32x4* Qhi = reinterpret_cast<const u32x4*>(Qp + (int64_t)b * 2 * per) + (int64_t)first * CS * KT * 64 + lane;
+  const u32x4* Qlo = Qhi + per / 8;
+  const int tile0 = rg * RT;
+  const T* rows[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+    rows[t] = F + (int64_t)b * bstride + (int64_t)min((tile0 + t) * 16 + r, N - 1) * ldf + 32 * CS * first + 8 * g;
+
+  struct Slot {
+    FPiece<T> f[RT][CS];
+    u32x4 q[CS][KT][NP];
+  };
+  Slot ring[DEPTH];
+  f32x4 acc[RT][KT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t)
+#pragma unroll
+    for (int jt = 0; jt < KT; ++jt) acc[t][jt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // bf16: the two 64-byte halves of a 128-byte line belong to neighbouring chunks and are requested together where CS = 2
+  auto load = [&](Slot& s, int i) {
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+      for (int c = 0; c < CS; ++c) s.f[t][c].load(rows[t] + 32 * (CS * i + c));
+#pragma unroll
+    for (int c = 0; c < CS; ++c)
+#pragma unroll
+      for (int jt = 0; jt < KT; ++jt) {
+        const int64_t w = ((int64_t)CS * i + c) * KT + jt;
+        s.q[c][jt][0] = Qhi[w * 64];
+        if (SPLIT) s.q[c][jt][NP - 1] = Qlo[w * 64];
+      }
+  };
+  float ssq = 0.f;
+  auto use = [&](const Slot& s) {
+#pragma unroll
+    for (int c = 0; c < CS; ++c) {
+      u32x4 fh[RT], fl[RT];
+#pragma unroll
+      for (int t = 0; t < RT; ++t) s.f[t][c].operands(&fh[t], &fl[t]);
+#pragma unroll
+      for (int jt = 0; jt < KT; ++jt) {
+#pragma unroll
+        for (int t = 0; t < RT; ++t) acc[t][jt] = mfma16(fh[t], s.q[c][jt][0], acc[t][jt]);
+        if (FPiece<T>::kTwoParts) {
+#pragma unroll
+          for (int t = 0; t < RT; ++t) acc[t][jt] = mfma16(fl[t], s.q[c][jt][0], acc[t][jt]);
+        }
+        if (SPLIT) {
+#pragma unroll
+          for (int t = 0; t < RT; ++t) acc[t][jt] = mfma16(fh[t], s.q[c][jt][NP - 1], acc[t][jt]);
+        }
+      }
+      if (FRO) {
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+          if ((tile0 + t) * 16 + r < N) ssq += s.f[t][c].sumsq();
+      }
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < DEPTH; ++u)
+    if (u < n) load(ring[u], u);
+  int i = 0;
+  for (; i + 2 * DEPTH <= n; i += DEPTH) {    // no condition inside, so that only a slot's own loads are waited for
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) {
+      use(ring[u]);
+      load(ring[u], i + u + DEPTH);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < DEPTH; ++u) {
+    if (i + u < n) use(ring[u]);
+    if (i + u + DEPTH < n) load(ring[u], i + u + DEPTH);
+  }
+#pragma unroll
+  for (int u = 0; u < DEPTH; ++u)
+    if (i + u + DEPTH < n) use(ring[u]);
+
+  if (FRO) {
+    const double s = wave_sum((double)ssq);
+    if (lane == 0) norm[wave] = s;
+  }
+
+  float* ybase = Y + (int64_t)b * N * ldy;
+  const int nsteps = (N + 31) / 32;
+#pragma unroll
+  for (int t0 = 0; t0 < RT; t0 += G) {
+#pragma unroll
+    for (int tt = 0; tt < G; ++tt)
+#pragma unroll
+      for (int jt = 0; jt < KT; ++jt)
+        if (t0 + tt < RT) part[wave][tt][jt][lane] = acc[t0 + tt][jt];
+    __syncthreads();
+    if (FRO && t0 == 0 && fro_acc && threadIdx.x == 0) {
+      // one atomic per workgroup: all of a block's add to one word (one per wave: 1152 of them took 5 us of 4608 rows' 25)
+      double s = norm[0];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) s += norm[w];
+      atomicAdd(fro_acc + b, s);
+    }
+    for (int item = wave; item < G * KT; item += NW) {
+      const int tt = item / KT, jt = item % KT;
+      if (t0 + tt >= RT) break;
+      f32x4 s = part[0][tt][jt][lane];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) s += part[w][tt][jt][lane];
+      const int tile = tile0 + t0 + tt, row = 16 * tile + 4 * g;
+      if (Yp) {
+        // packed output for the back-projection: a tile is one half of the words of a 32-row step
+        if (tile / 2 >= nsteps) continue;
+        const int64_t word = ((int64_t)b * nsteps + tile / 2) * KT + jt;
+        store_y_half(FPiece<T>{}, Yp, word, tile & 1, s, row, N);
+        if ((tile & 1) == 0 && 16 * (tile + 1) >= N)        // no tile has the other half of the last step: zeros
+          store_y_half(FPiece<T>{}, Yp, word, 1, s, row + 16, N);
+      } else {
+        const int j = 16 * jt + r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (row + e < N && j < l) ybase[(int64_t)(row + e) * ldy + j] = s[e];
+      }
+    }
+    if (t0 + G < RT) __syncthreads();
+  }
+}
+
+// Waves, ring slots and chunks per slot for 1 to 6 row tiles.  Eight waves share the channels while the accumulators leave room
+// for it (two waves per SIMD hide each other's waits), four where they do not; a deeper ring gained nothing or spilled.  Each the
+// fastest or within 3 % of it among 7 to 15 variants per height, timed at 15 shapes.
+struct StreamVariant {
+  int waves, depth, chunks;
+};
+template <typename T, bool SPLIT>
+constexpr StreamVariant stream_variant(int kt, int rt) {
+  const int x = kt == 1 ? 0 : (kt == 2 ? 1 : (kt == 4 ? 2 : 3));
+  constexpr StreamVariant f32[4][6] = {
+      {{8, 4, 1}, {8, 4, 1}, {8, 3, 1}, {4, 3, 1}, {8, 2, 1}, {4, 2, 1}},
+      {{8, 4, 1}, {8, 3, 1}, {8, 3, 1}, {4, 3, 1}, {8, 2, 1}, {8, 2, 1}},
+      {{8, 3, 1}, {8, 1, 2}, {8, 2, 1}, {4, 2, 1}, {8, 1, 1}, {8, 1, 1}},
+      {{8, 2, 1}, {8, 1, 2}, {8, 1, 1}, {4, 2, 1}, {4, 2, 1}, {4, 2, 1}}};
+  constexpr StreamVariant plain[4][6] = {
+      {{8, 6, 2}, {8, 6, 2}, {8, 6, 2}, {4, 4, 2}, {4, 3, 2}, {4, 3, 2}},
+      {{8, 4, 2}, {8, 3, 2}, {8, 4, 2}, {4, 3, 2}, {4, 3, 2}, {4, 2, 2}},
+      {{8, 3, 2}, {8, 3, 2}, {8, 2, 2}, {4, 2, 2}, {4, 2, 2}, {4, 3, 2}},
+      {{8, 2, 2}, {8, 2, 2}, {8, 3, 1}, {4, 2, 1}, {4, 2, 2}, {4, 2, 2}}};
+  constexpr StreamVariant split[4][6] = {
+      {{8, 4, 2}, {8, 3, 2}, {8, 5, 2}, {4, 3, 2}, {8, 3, 2}, {8, 2, 2}},
+      {{8, 3, 2}, {8, 2, 2}, {8, 3, 2}, {4, 2, 2}, {8, 2, 2}, {8, 2, 2}},
+      {{8, 3, 1}, {8, 2, 2}, {8, 3, 1}, {4, 3, 1}, {8, 1, 1}, {8, 1, 1}},
+      {{8, 2, 1}, {8, 2, 1}, {4, 3, 1}, {4, 2, 1}, {4, 2, 1}, {4, 1, 1}}};
+  return std::is_same<T, float>::value ? f32[x][rt - 1] : (SPLIT ? split[x][rt - 1] : plain[x][rt - 1]);
+}
+
+struct StreamCall {
+  const svdc_shape& s;
+  int l, ldy;
+  const void *F, *Qp;
+  float* Y;
+  u32x4* Yp;
+  double* fro_acc;
+  hipStream_t st;
+};
+
+template <typename T, int KT, int RT, bool SPLIT, bool FRO>
+void stream_launch(const StreamCall& c) {
+  constexpr StreamVariant v = stream_variant<T, SPLIT>(KT, RT);
+  // registers of the accumulators and the ring: two waves per SIMD where they fit
+  constexpr int regs = 4 * RT * KT + v.depth * v.chunks * (RT * (int)sizeof(FPiece<T>) / 4 + KT * (SPLIT ? 8 : 4));
+  constexpr int wpe = v.waves == 8 || regs <= 232 ? 2 : 1;
+  const int groups = ((c.s.N + 15) / 16 + RT - 1) / RT;
+  fit_project_stream_kernel<T, KT, RT, v.waves, v.depth, v.chunks, SPLIT, FRO, wpe>
+      <<<(unsigned)((int64_t)groups * c.s.B), 64 * v.waves, 0, c.st>>>((const T*)c.F, (const uint16_t*)c.Qp, c.Y, c.Yp, c.fro_acc, c.s.N, c.s.D, c.l,
+                                                                  c.s.ldf, c.s.block_stride, groups, c.ldy);
+}
+template <typename T, int KT, bool SPLIT, bool FRO>
+void stream_by_rows(int rt, const StreamCall& c) {
+  switch (rt) {
+    case 1: return stream_launch<T, KT, 1, SPLIT, FRO>(c);
+    case 2: return stream_launch<T, KT, 2, SPLIT, FRO>(c);
+    case 3: return stream_launch<T, KT, 3, SPLIT, FRO>(c);
+    case 4: return stream_launch<T, KT, 4, SPLIT, FRO>(c);
+    case 5: return stream_launch<T, KT, 5, SPLIT, FRO>(c);
+    default: return stream_launch<T, KT, 6, SPLIT, FRO>(c);
+  }
+}
+template <typename T, bool SPLIT, bool FRO>
+void stream_by_width(int kt, int rt, const StreamCall& c) {
+  if (kt == 1) stream_by_rows<T, 1, SPLIT, FRO>(rt, c);
+  else if (kt == 2) stream_by_rows<T, 2, SPLIT, FRO>(rt, c);
+  else if (kt == 4) stream_by_rows<T, 4, SPLIT, FRO>(rt, c);
+  else stream_by_rows<T, 8, SPLIT, FRO>(rt, c);
+}
+
+}  // namespace
+}  // namespace svdc

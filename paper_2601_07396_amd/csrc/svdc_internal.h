@@ -101,6 +101,12 @@ size_t fit_mfma_packed_y_bytes(const svdc_shape& s, int l, int parts);
 // Ypacked != nullptr (bf16 features: plain operands only): the result goes there in packed form and Y is not written.
 void fit_mfma_project(const svdc_shape& s, int l, const void* F, const void* Qp, float* Y, void* Ypacked,
                       double* fro_acc, bool split, hipStream_t st);
+// The streamed form of it, kt tiles of 16 columns and rt row tiles per workgroup (project_f32.hip, project_bf16.hip); last: accumulates
+// ||F||_F^2, and for bf16 features takes both parts of Q (the others are plain).
+void fit_project_stream_f32(int kt, int rt, const svdc_shape& s, int l, int ldy, const void* F, const void* Qp, float* Y, void* Yp, bool last,
+                            double* fro_acc, hipStream_t st);
+void fit_project_stream_bf16(int kt, int rt, const svdc_shape& s, int l, int ldy, const void* F, const void* Qp, float* Y, void* Yp, bool last,
+                             double* fro_acc, hipStream_t st);
 // Z = F^T Y, with Y as float32 rows or (Ypacked != nullptr) in the packed form; z_clear: Z holds zeros already
 void fit_mfma_backproject(const svdc_shape& s, int l, const void* F, const float* Y, const void* Ypacked, float* Z,
                           bool z_clear, hipStream_t st);

@@ -772,6 +772,20 @@ def test_fit_basis_products_in_shares_of_the_channels(dtype, B, D, l, N):
     test_fit_basis_at_the_block_edges_of_the_small_matrices(dtype, B, D, l, N - l)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("B,D,l,N", [
+    (1, 128, 8, 15), (3, 128, 100, 209),                       # 1 tile per workgroup, waves without channels; an odd number of tiles
+    (1, 384, 30, 4801), (2, 256, 64, 4505),                    # 2 and 3 tiles
+    (7, 384, 16, 4081), (7, 128, 64, 4081),                    # 4
+    (4, 640, 60, 4577), (1, 256, 128, 18417), (1, 384, 9, 18417),    # 5, the last workgroup with fewer
+    (1, 128, 33, 22001), (6, 256, 70, 4001),                   # 6
+    (20, 128, 12, 3333), (20, 256, 40, 3299), (20, 384, 128, 3333)])  # more tiles than 16 per compute unit
+def test_fit_basis_streamed_projections(dtype, B, D, l, N):
+    """Every number of row tiles that a workgroup of the streamed projection takes, with ragged rows, an odd last tile (half of the
+    last operand word of Y is zero) and fewer chunks of channels than waves; large bf16 calls, which have other kernels."""
+    test_fit_basis_at_the_block_edges_of_the_small_matrices(dtype, B, D, min(l, D), N - min(l, D))
+
+
 @pytest.mark.parametrize("dtype,B,D,l,N", [
     (torch.bfloat16, 1, 128, 12, 513), (torch.bfloat16, 2, 640, 30, 1300), (torch.bfloat16, 5, 1152, 64, 512),
     (torch.bfloat16, 1, 384, 128, 700), (torch.bfloat16, 1, 640, 200, 1029), (torch.float32, 1, 128, 20, 545),
