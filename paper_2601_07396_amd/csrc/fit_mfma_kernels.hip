@@ -14,6 +14,7 @@
 #include <type_traits>
 
 #include "fit_operands.h"
+#include "step_tiling.h"
 #include "svdc_device.h"
 #include "svdc_internal.h"
 
@@ -65,7 +66,7 @@ __global__ __launch_bounds__(256) void pack_q_kernel(const float* __restrict__ Q
 //   B operand = Q tile   (kk = channel, n = coefficient)
 //   D[m = 4 g + i][n = r]  ->  Y[row 16 tile + 4 g + i][16 jt + r]
 // For the last product of large calls with sketches of up to 32 columns, in bf16 with both parts of Q: 57 x 4608 x 3072, width 16
-// 305 us, 328 streamed (fit_project_stream_kernel); 32 356 and 366.  Also accumulates sum F^2 (for ||F||_F^2, fro_acc nullable).
+// 305 us, 328 streamed (project_stream_kernel); 32 356 and 366.  Also accumulates sum F^2 (for ||F||_F^2, fro_acc nullable).
 // ---------------------------------------------------------------------------
 template <int NCW, int KT, int TG>
 __global__ __launch_bounds__(256) void fit_project_mfma_kernel(const bf16_t* __restrict__ F,
@@ -177,7 +178,7 @@ __global__ __launch_bounds__(256) void fit_project_mfma_kernel(const bf16_t* __r
 // the operand words of a slab of SC 32-channel chunks are fetched once per workgroup (registers -> LDS, double
 // buffered, one barrier per slab) and every wave reads them from there.  Per token row the packed sketch is then
 // read from L2 once per 64 RTW rows and from LDS once per 16 RTW rows, against once per 16 to 96 rows when both operands are
-// streamed (fit_project_stream_kernel), at the price of a memory latency and a barrier per slab, which only several workgroups on a
+// streamed (project_stream_kernel), at the price of a memory latency and a barrier per slab, which only several workgroups on a
 // compute unit hide.  57 x 4608 x 3072, this and streamed: split operands, width 64 394 and 447 us, width 128 575 and 587; plain
 // ones, width 128 431 and 457 us.  20 blocks: 146 and 164, 225 and 216, 166 and 170; 8 blocks: 92 and 72, 118 and 95, 88 and 76.
 //   A operand = F tile   (m = token row, kk = channel)   -- the natural 16-byte row pieces
@@ -663,27 +664,14 @@ void by_width(int m, int maxw, Fn12 f12, Fn6 f6, Fn4 f4, Fn3 f3, Fn2 f2, Fn1 f1)
   return f1();
 }
 
-// Row tiles of 16 that a workgroup of the streamed projection takes (project_stream.h), 1 to 6: those of the least rounds x
-// (rows + x).  The operands of Q that a workgroup reads once cost it as much as x = 1.25 tiles, at every width and for both
-// storage types: over 14 shapes and 12 kinds of operands (1 x 300 x 1024 to 57 x 4608 x 3072) the choice is within 3 % of the best height.
-// Plain bf16 operands of width 64 have two workgroups on a compute unit up to 5 tiles, which evens out the rounds of larger calls (57 x 4608
-// x 3072: 339 us with 5 tiles, 364 with 6).
-inline int stream_rows(const svdc_shape& s, bool plain64, bool large) {
-  if (plain64 && large) return 5;
-  const int64_t cus = num_compute_units(), ntile = (s.N + 15) / 16;
-  auto cost = [&](int rt) { return (double)(((ntile + rt - 1) / rt * s.B + cus - 1) / cus) * (rt + 1.25); };
-  int best = 1;
-  for (int rt = 2; rt <= 6; ++rt)
-    if (cost(rt) < cost(best)) best = rt;
-  return best;
-}
-
 template <int KT>
 void project_kt(const svdc_shape& s, int l, const void* F, const void* Qp, float* Y, u32x4* Yp, double* fro_acc, bool split,
                 Strides ld, hipStream_t st) {
   const int64_t tiles = (int64_t)((s.N + 15) / 16) * s.B;
   const bool large = tiles >= 16 * (int64_t)num_compute_units();
-  const int rt = stream_rows(s, KT == 4 && !split, large);
+  // Plain bf16 operands of width 64 have two workgroups on a compute unit up to 5 tiles, which evens out the rounds of large calls
+  // (57 x 4608 x 3072: 339 us with 5 tiles, 364 with 6).
+  const int rt = KT == 4 && !split && large ? 5 : stream_rows((s.N + 15) / 16, s.B, num_compute_units());
   if (s.dtype == SVDC_F32) return fit_project_stream_f32(KT, rt, s, l, ld.ldy, F, Qp, Y, Yp, fro_acc != nullptr, fro_acc, st);
   // Large bf16 calls with both parts of Q, or wide plain ones, have kernels of their own (9 tiles per compute unit: streamed
   // 20 to 30 % ahead; 22: 0 to 12 % behind).

@@ -185,7 +185,7 @@ __global__ __launch_bounds__(256) void forecast_mfma_kernel(const CoefStates cs,
   const T* rbase = R + (int64_t)b * bstride + 32 * cg0 + 8 * g;
   T* obase = Fh + (int64_t)b * bstride + 32 * cg0 + 8 * g;
   // EXT: the coefficient forecast is sum_m w_m S_m over up to kMaxStates stored states, and a tensor X
-  // (nullable) is added to the result; otherwise the single state cs.s[0] with weight one.
+  // (nullable) is added to the result; otherwise the single state cs.s[0] with weight 1, or -1 for a residual (R - S V^T).
   constexpr int MS = EXT ? MSX : 1;
   const int ntile_block = (N + 15) / 16;
   const bool has_x = EXT && HX && X != nullptr;
@@ -273,7 +273,7 @@ __global__ __launch_bounds__(256) void forecast_mfma_kernel(const CoefStates cs,
                 if (ms < cs.m) v = __builtin_fmaf(cs.w[ms], sraw[u][ms][kt][t][i], v);
               c8[4 * t + i] = -v;
             } else {
-              c8[4 * t + i] = -sraw[u][0][kt][t][i];
+              c8[4 * t + i] = -cs.w[0] * sraw[u][0][kt][t][i];
             }
           }
         split_operand(c8, &shi[kt], &slo[kt]);
@@ -504,7 +504,7 @@ __global__ __launch_bounds__(256) void full_step_mfma_kernel(const T* F, const u
         if (!init) {
           const f32x4 old = *reinterpret_cast<const f32x4*>(S + srow + j);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) s4[i] = (1.f - alpha) * old[i] + alpha * c4[i];
+          for (int i = 0; i < 4; ++i) s4[i] = ema(old[i], c4[i], alpha);
         }
         *reinterpret_cast<f32x4*>(S + srow + j) = s4;
         if (C) *reinterpret_cast<f32x4*>(C + srow + j) = c4;
@@ -761,8 +761,28 @@ constexpr int ring_depth(int CH, int W, int KT2) {
   return rd;
 }
 
-// A launch with fewer tiles than compute units leaves units idle: such small problems take tiles one step
-// smaller (their packed-basis traffic does not matter at that size), and tiles of 16 rows where step_tiling.h allows.
+// Whether a workgroup tile can have one more row tile in LDS (LT): bf16 at 3072 channels, rank 33..64.  Measured at the HunyuanVideo
+// shape: 4 % (split operands) to 8 % (single operands) less time per launch, 8-10 % on a single 18432-row block.  At rank <= 32 the
+// packed-basis stream is small enough that a fourth tile gains nothing, at rank 128 the LDS tile only replaces the second register tile at
+// equal speed.
+constexpr bool has_lds_tile(int CH, int W, int KT2) { return CH == 24 && W == 1 && KT2 == 2; }
+
+// Row tiles that a full step (without smoothing) takes at a time, the one in LDS included.
+// A taller tile can leave more of the last round of the persistent grid empty, so the choice of the LDS tile compares rounds x tile height x
+// cost per row (0.92 of the register-only tile's).  A launch with fewer tiles than compute units leaves units idle: such small
+// problems take tiles one step smaller (their packed-basis traffic does not matter at that size), and tiles of 16 rows where step_tiling.h allows.
+inline int full_step_rows(int CH, int W, int KT2, bool split, int N, int64_t B, int D) {
+  const int RT = tile_rows(CH, W, KT2);
+  const int64_t cus = num_compute_units();
+  auto tile_count = [&](int ra) { return (int64_t)((N + 16 * ra - 1) / (16 * ra)) * B; };
+  if (has_lds_tile(CH, W, KT2)) {
+    auto rounds = [&](int ra) { return (double)((tile_count(ra) + cus - 1) / cus); };
+    if (tile_count(RT + 1) >= cus && rounds(RT + 1) * (RT + 1) * 0.92 <= rounds(RT) * RT) return RT + 1;
+  }
+  if (RT > 2 && full_step_takes_single_tiles(tile_count(1), B * D * (32 * KT2) * 2 * (split ? 2 : 1), (int)cus)) return 1;
+  return RT > 1 && tile_count(RT) < cus ? RT - 1 : RT;
+}
+
 template <typename T, int CH, int KT2, bool SPLIT>
 int32_t full_step_by_size(const svdc_shape& s, const void* F, const void* packed, void* R, float* S, float* C,
                           float alpha, int init, ResidualEma re, hipStream_t st) {
@@ -777,28 +797,16 @@ int32_t full_step_by_size(const svdc_shape& s, const void* F, const void* packed
     }
     return full_step_launch<T, CH, (RT > 1 ? RT - 1 : 1), KT2, SPLIT, RD, true>(s, F, packed, R, S, C, alpha, init, re, st);
   }
-  // bf16 at 3072 channels, rank 33..64: a third row tile in LDS.  Measured at the HunyuanVideo shape: 4 % (split
-  // operands) to 8 % (single operands) less time per launch, 8-10 % on a single 18432-row block.  At rank <= 32 the
-  // packed-basis stream is small enough that a fourth tile gains nothing, at rank 128 the LDS tile only replaces
-  // the second register tile at equal speed.  A taller tile can leave more of the last round of the persistent
-  // grid empty, so the choice compares rounds x tile height x cost per row (0.92 of the register-only tile's).
-  if constexpr (CH == 24 && W == 1 && KT2 == 2) {
+  const int rows = full_step_rows(CH, W, KT2, SPLIT, s.N, s.B, s.D);
+  if constexpr (has_lds_tile(CH, W, KT2)) {
     constexpr int RDL = SPLIT ? 12 : 16;
-    const int64_t cus = num_compute_units();
-    auto tile_count = [&](int ra) { return (int64_t)((s.N + 16 * ra - 1) / (16 * ra)) * s.B; };
-    auto rounds = [&](int ra) { return (double)((tile_count(ra) + cus - 1) / cus); };
-    if (tile_count(RT + 1) >= cus && rounds(RT + 1) * (RT + 1) * 0.92 <= rounds(RT) * RT)
-      return full_step_launch<T, CH, RT, KT2, SPLIT, RDL, false, 1>(s, F, packed, R, S, C, alpha, init, re, st);
+    if (rows == RT + 1) return full_step_launch<T, CH, RT, KT2, SPLIT, RDL, false, 1>(s, F, packed, R, S, C, alpha, init, re, st);
+  }
+  if constexpr (RT > 2) {
+    if (rows == 1) return full_step_launch<T, CH, 1, KT2, SPLIT, RD, false>(s, F, packed, R, S, C, alpha, init, re, st);
   }
   if constexpr (RT > 1) {
-    const int64_t tiles = (int64_t)((s.N + 16 * RT - 1) / (16 * RT)) * s.B;
-    if constexpr (RT > 2) {
-      if (full_step_takes_single_tiles((int64_t)((s.N + 15) / 16) * s.B,
-                                       (int64_t)s.B * s.D * (32 * KT2) * 2 * (SPLIT ? 2 : 1), num_compute_units()))
-        return full_step_launch<T, CH, 1, KT2, SPLIT, RD, false>(s, F, packed, R, S, C, alpha, init, re, st);
-    }
-    if (tiles < num_compute_units())
-      return full_step_launch<T, CH, RT - 1, KT2, SPLIT, RD, false>(s, F, packed, R, S, C, alpha, init, re, st);
+    if (rows == RT - 1) return full_step_launch<T, CH, RT - 1, KT2, SPLIT, RD, false>(s, F, packed, R, S, C, alpha, init, re, st);
   }
   return full_step_launch<T, CH, RT, KT2, SPLIT, RD, false>(s, F, packed, R, S, C, alpha, init, re, st);
 }
@@ -833,15 +841,6 @@ int32_t full_step_by_width(const svdc_shape& s, const void* F, const void* packe
 
 }  // namespace
 
-int32_t launch_full_step_mfma(const svdc_shape& s, const void* F, const void* packed, void* R, float* S,
-                              float* C, float alpha, int init, ResidualEma re, hipStream_t st) {
-  // float32 features always use the full operand split (a single bf16 operand would cost 8 of their 24 bits)
-  if (s.dtype == SVDC_F32) return full_step_by_width<float, true>(s, F, packed, R, S, C, alpha, init, re, st);
-  return s.precision == SVDC_PRECISE
-             ? full_step_by_width<bf16_t, true>(s, F, packed, R, S, C, alpha, init, re, st)
-             : full_step_by_width<bf16_t, false>(s, F, packed, R, S, C, alpha, init, re, st);
-}
-
 namespace {
 
 template <bool EXT, bool PS = false>
@@ -866,6 +865,30 @@ int32_t forecast_dispatch(const svdc_shape& s, const CoefStates& cs, const void*
 }
 
 }  // namespace
+
+int32_t launch_full_step_mfma(const svdc_shape& s, const void* F, const void* packed, void* R, float* S,
+                              float* C, float alpha, int init, ResidualEma re, hipStream_t st) {
+  const bool f32 = s.dtype == SVDC_F32, split = f32 || s.precision == SVDC_PRECISE;
+  if (C && !re.prev && full_step_may_take_two_launches(s.D, s.k, f32, split)) {
+    const int kt2 = padded_rank(s.k) / 32, rows = full_step_rows(s.D / 128, f32 ? 2 : 1, kt2, split, s.N, s.B, s.D), cus = num_compute_units();
+    const int64_t tiles = (int64_t)((s.N + 16 * rows - 1) / (16 * rows)) * s.B;
+    if (full_step_in_two_launches({rows, tiles}, s.N, s.B, s.D, s.k, f32, split, cus)) {
+      const int rt = stream_rows((s.N + 15) / 16, s.B, cus);
+      if (f32) step_project_stream_f32(2 * kt2, rt, s, F, packed, S, C, alpha, init, re.packed_state, st);
+      else step_project_stream_bf16(2 * kt2, rt, s, F, packed, S, C, alpha, init, re.packed_state, st);
+      CoefStates cs{};
+      cs.s[0] = C;
+      cs.w[0] = -1.f;
+      cs.m = 1;
+      return forecast_dispatch<false>(s, cs, packed, F, nullptr, R, st);
+    }
+  }
+  // float32 features always use the full operand split (a single bf16 operand would cost 8 of their 24 bits)
+  if (f32) return full_step_by_width<float, true>(s, F, packed, R, S, C, alpha, init, re, st);
+  return s.precision == SVDC_PRECISE
+             ? full_step_by_width<bf16_t, true>(s, F, packed, R, S, C, alpha, init, re, st)
+             : full_step_by_width<bf16_t, false>(s, F, packed, R, S, C, alpha, init, re, st);
+}
 
 int32_t launch_forecast_mfma(const svdc_shape& s, const float* S, const void* packed, const void* R,
                              void* Fhat, hipStream_t st) {

@@ -1,13 +1,21 @@
-// Streamed projection of the basis fit for float32 features (both operands in two bf16 parts).
+// Streamed projection for float32 features (both operands in two bf16 parts).
 #include "project_stream.h"
 
 namespace svdc {
 
 void fit_project_stream_f32(int kt, int rt, const svdc_shape& s, int l, int ldy, const void* F, const void* Qp, float* Y, void* Yp, bool last,
                             double* fro_acc, hipStream_t st) {
-  const StreamCall c{s, l, ldy, F, Qp, Y, (u32x4*)Yp, fro_acc, st};
-  if (last) stream_by_width<float, true, true>(kt, rt, c);
-  else stream_by_width<float, true, false>(kt, rt, c);
+  const int64_t q_block = (int64_t)2 * s.D * kt * 16;
+  const StreamCall<FitOut<true>> norm{s, F, Qp, q_block, {Y, (u32x4*)Yp, fro_acc, l, ldy}, st};
+  const StreamCall<FitOut<false>> plain{s, F, Qp, q_block, {Y, (u32x4*)Yp, nullptr, l, ldy}, st};
+  if (last) stream_by_width<float, true>(kt, rt, norm);
+  else stream_by_width<float, true>(kt, rt, plain);
+}
+
+void step_project_stream_f32(int kt, int rt, const svdc_shape& s, const void* F, const void* packed, float* S, float* C, float alpha, int init,
+                             void* Sp, hipStream_t st) {
+  const StreamCall<StepOut> c{s, F, packed, (int64_t)4 * s.D * kt * 16, {S, C, alpha, init, s.k, (uint2*)Sp}, st};
+  stream_by_width<float, true, 2>(kt, rt, c);
 }
 
 }  // namespace svdc

@@ -1,5 +1,6 @@
-// Y = F Q for one group of 16-row tiles per workgroup, both operands streamed through registers (gfx950): kernel, its variants by
-// tile height and the rule that picks one.  Included by one translation unit per storage type.
+// Y = F Q, or the coefficients C = F V of a full step, for one group of 16-row tiles per workgroup, both operands streamed through
+// registers (gfx950): kernel, its variants by tile height and the rule that picks one.  Included by one translation unit per
+// storage type.
 #pragma once
 #include <algorithm>
 #include <type_traits>
@@ -22,12 +23,74 @@ namespace {
 // split the rows or hold slabs of Q (KT = 4 and less) in registers: float32 width 128 67 / 103 / 349 -> 34 / 67 / 312, width 64
 // 27 / 86 / 289 -> 26 / 53 / 245; bf16 split width 128 53 / 68 / 225 -> 28 / 47 / 216, width 64 24 / 51 -> 20 / 37; bf16 plain
 // width 128 44 / 47 -> 20 / 37, width 64 15.1 / 40 / 131 -> 14.8 / 30 / 126.
-// FRO: also accumulate sum F^2 (for ||F||_F^2).
+// What becomes of a tile of the product is up to Out:
+//   FitOut<FRO>  Y as operand words of the back-projection or as float32 rows; FRO: also accumulates sum F^2 (for ||F||_F^2)
+//   StepOut      coefficients C and the state S of a full step; operand roles exchanged, so that a lane has four
+//                neighbouring coefficients of one row
 // ---------------------------------------------------------------------------
-template <typename T, int KT, int RT, int NW, int DEPTH, int CS, bool SPLIT, bool FRO, int WPE>
-__global__ __launch_bounds__(64 * NW, WPE) void fit_project_stream_kernel(const T* __restrict__ F, const uint16_t* __restrict__ Qp, float* Y,
-                                                                          u32x4* Yp, double* fro_acc, int N, int D, int l, int64_t ldf,
-                                                                          int64_t bstride, int groups_per_block, int ldy) {
+template <bool FRO>
+struct FitOut {
+  static constexpr bool kNorm = FRO, kRowInLane = false;
+  float* Y;
+  u32x4* Yp;
+  double* fro_acc;
+  int l, ldy;
+  // s: rows 4 g + i of the tile, column 16 jt + r
+  template <typename T, int KT>
+  __device__ __forceinline__ void store(const f32x4& s, int b, int tile, int jt, int N, int r, int g) const {
+    const int row = 16 * tile + 4 * g, nsteps = (N + 31) / 32;
+    if (Yp) {
+      // packed output for the back-projection: a tile is one half of the words of a 32-row step
+      if (tile / 2 >= nsteps) return;
+      const int64_t word = ((int64_t)b * nsteps + tile / 2) * KT + jt;
+      store_y_half(FPiece<T>{}, Yp, word, tile & 1, s, row, N);
+      if ((tile & 1) == 0 && 16 * (tile + 1) >= N)        // no tile has the other half of the last step: zeros
+        store_y_half(FPiece<T>{}, Yp, word, 1, s, row + 16, N);
+      return;
+    }
+    const int j = 16 * jt + r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (row + e < N && j < l) Y[((int64_t)b * N + row + e) * ldy + j] = s[e];
+  }
+};
+struct StepOut {
+  static constexpr bool kNorm = false, kRowInLane = true;
+  float *S, *C;         // C nullable
+  float alpha;
+  int init, k;
+  uint2* Sp;            // nullable: the new state as operand words of the cached step too (negated, see pack_state_kernel)
+  // s: row r of the tile, columns 16 jt + 4 g + i
+  template <typename T, int KT>
+  __device__ __forceinline__ void store(const f32x4& s, int b, int tile, int jt, int N, int r, int g) const {
+    const int row = 16 * tile + r, j = 16 * jt + 4 * g, ntile = (N + 15) / 16;
+    if (tile >= ntile) return;
+    f32x4 snew = {0.f, 0.f, 0.f, 0.f};
+    if (row < N && j < k) {                                // k is a multiple of 4
+      const int64_t at = ((int64_t)b * N + row) * k + j;
+      snew = s;
+      if (!init) {
+        const f32x4 old = *reinterpret_cast<const f32x4*>(S + at);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) snew[i] = ema(old[i], s[i], alpha);
+      }
+      *reinterpret_cast<f32x4*>(S + at) = snew;
+      if (C) *reinterpret_cast<f32x4*>(C + at) = s;
+    }
+    if (Sp) {
+      uint2* w = Sp + ((((int64_t)b * ntile + tile) * (KT / 2) + jt / 2) * 2 * 64 + (threadIdx.x & 63)) * 2 + jt % 2;
+      const uint32_t h0 = pack_bf16(-snew[0], -snew[1]), h1 = pack_bf16(-snew[2], -snew[3]);
+      w[0] = make_uint2(h0, h1);
+      w[2 * 64] = make_uint2(pack_bf16(-snew[0] - bf16_lo(h0), -snew[1] - bf16_hi(h0)), pack_bf16(-snew[2] - bf16_lo(h1), -snew[3] - bf16_hi(h1)));
+    }
+  }
+};
+
+// q_block: elements from one block's operand words to the next one's
+template <typename T, int KT, int RT, int NW, int DEPTH, int CS, bool SPLIT, int WPE, typename Out>
+__global__ __launch_bounds__(64 * NW, WPE) void project_stream_kernel(const T* __restrict__ F, const uint16_t* __restrict__ Qp, int64_t q_block, Out out,
+                                                                      int N, int D, int64_t ldf, int64_t bstride, int groups_per_block) {
+  constexpr bool FRO = Out::kNorm;
   constexpr int NP = SPLIT ? 2 : 1;           // operand parts (high, low)
   constexpr int G = NW * KT >= 64 ? 1 : 2;    // row tiles that meet in LDS at a time (64 KB)
   __shared__ f32x4 part[NW][G][KT][64];
@@ -37,7 +100,7 @@ __global__ __launch_bounds__(64 * NW, WPE) void fit_project_stream_kernel(const 
   const int64_t per = (int64_t)D * KT * 16;
   // the slots of CS chunks that are this wave's (D / 32 is a multiple of 4)
   const int all = D / (32 * CS), first = wave * all / NW, n = (wave + 1) * all / NW - first;
-  const u32x4* Qhi = reinterpret_cast<const u32x4*>(Qp + (int64_t)b * 2 * per) + (int64_t)first * CS * KT * 64 + lane;
+  const u32x4* Qhi = reinterpret_cast<const u32x4*>(Qp + b * q_block) + (int64_t)first * CS * KT * 64 + lane;
   const u32x4* Qlo = Qhi + per / 8;
   const int tile0 = rg * RT;
   const T* rows[RT];
@@ -79,16 +142,13 @@ __global__ __launch_bounds__(64 * NW, WPE) void fit_project_stream_kernel(const 
       for (int t = 0; t < RT; ++t) s.f[t][c].operands(&fh[t], &fl[t]);
 #pragma unroll
       for (int jt = 0; jt < KT; ++jt) {
+        auto times = [&](const u32x4(&f)[RT], const u32x4& q) {
 #pragma unroll
-        for (int t = 0; t < RT; ++t) acc[t][jt] = mfma16(fh[t], s.q[c][jt][0], acc[t][jt]);
-        if (FPiece<T>::kTwoParts) {
-#pragma unroll
-          for (int t = 0; t < RT; ++t) acc[t][jt] = mfma16(fl[t], s.q[c][jt][0], acc[t][jt]);
-        }
-        if (SPLIT) {
-#pragma unroll
-          for (int t = 0; t < RT; ++t) acc[t][jt] = mfma16(fh[t], s.q[c][jt][NP - 1], acc[t][jt]);
-        }
+          for (int t = 0; t < RT; ++t) acc[t][jt] = Out::kRowInLane ? mfma16(q, f[t], acc[t][jt]) : mfma16(f[t], q, acc[t][jt]);
+        };
+        times(fh, s.q[c][jt][0]);
+        if (FPiece<T>::kTwoParts) times(fl, s.q[c][jt][0]);
+        if (SPLIT) times(fh, s.q[c][jt][NP - 1]);
       }
       if (FRO) {
 #pragma unroll
@@ -123,8 +183,6 @@ __global__ __launch_bounds__(64 * NW, WPE) void fit_project_stream_kernel(const 
     if (lane == 0) norm[wave] = s;
   }
 
-  float* ybase = Y + (int64_t)b * N * ldy;
-  const int nsteps = (N + 31) / 32;
 #pragma unroll
   for (int t0 = 0; t0 < RT; t0 += G) {
 #pragma unroll
@@ -133,12 +191,14 @@ __global__ __launch_bounds__(64 * NW, WPE) void fit_project_stream_kernel(const 
       for (int jt = 0; jt < KT; ++jt)
         if (t0 + tt < RT) part[wave][tt][jt][lane] = acc[t0 + tt][jt];
     __syncthreads();
-    if (FRO && t0 == 0 && fro_acc && threadIdx.x == 0) {
-      // one atomic per workgroup: all of a block's add to one word (one per wave: 1152 of them took 5 us of 4608 rows' 25)
-      double s = norm[0];
+    if constexpr (FRO) {
+      if (t0 == 0 && out.fro_acc && threadIdx.x == 0) {
+        // one atomic per workgroup: all of a block's add to one word (one per wave: 1152 of them took 5 us of 4608 rows' 25)
+        double s = norm[0];
 #pragma unroll
-      for (int w = 1; w < NW; ++w) s += norm[w];
-      atomicAdd(fro_acc + b, s);
+        for (int w = 1; w < NW; ++w) s += norm[w];
+        atomicAdd(out.fro_acc + b, s);
+      }
     }
     for (int item = wave; item < G * KT; item += NW) {
       const int tt = item / KT, jt = item % KT;
@@ -146,20 +206,7 @@ __global__ __launch_bounds__(64 * NW, WPE) void fit_project_stream_kernel(const 
       f32x4 s = part[0][tt][jt][lane];
 #pragma unroll
       for (int w = 1; w < NW; ++w) s += part[w][tt][jt][lane];
-      const int tile = tile0 + t0 + tt, row = 16 * tile + 4 * g;
-      if (Yp) {
-        // packed output for the back-projection: a tile is one half of the words of a 32-row step
-        if (tile / 2 >= nsteps) continue;
-        const int64_t word = ((int64_t)b * nsteps + tile / 2) * KT + jt;
-        store_y_half(FPiece<T>{}, Yp, word, tile & 1, s, row, N);
-        if ((tile & 1) == 0 && 16 * (tile + 1) >= N)        // no tile has the other half of the last step: zeros
-          store_y_half(FPiece<T>{}, Yp, word, 1, s, row + 16, N);
-      } else {
-        const int j = 16 * jt + r;
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (row + e < N && j < l) ybase[(int64_t)(row + e) * ldy + j] = s[e];
-      }
+      out.template store<T, KT>(s, b, tile0 + t0 + tt, jt, N, r, g);
     }
     if (t0 + G < RT) __syncthreads();
   }
@@ -192,44 +239,61 @@ constexpr StreamVariant stream_variant(int kt, int rt) {
   return std::is_same<T, float>::value ? f32[x][rt - 1] : (SPLIT ? split[x][rt - 1] : plain[x][rt - 1]);
 }
 
+// A full step adds the channels up in the order of full_step_mfma_kernel, four waves and a chunk at a time, so that its results do not
+// depend on which of the two a call takes (only one with a buffer for C comes here).  Ring slots for padded rank 32, 64, 128; 4608 x 3072
+// float32 rows at rank 128 with eight waves 33 us, with four 37, elsewhere within 5 %.
+template <typename T, bool SPLIT>
+constexpr StreamVariant step_variant(int kt, int rt) {
+  const int x = kt == 2 ? 0 : (kt == 4 ? 1 : 2);
+  constexpr int f32[3][6] = {{4, 3, 3, 3, 2, 2}, {4, 3, 2, 2, 3, 2}, {2, 2, 3, 2, 2, 2}};
+  constexpr int split[3][6] = {{4, 4, 3, 3, 2, 2}, {4, 4, 3, 3, 2, 3}, {2, 4, 3, 2, 2, 1}};
+  constexpr int plain[3][6] = {{4, 4, 4, 4, 3, 3}, {4, 4, 4, 4, 3, 3}, {4, 4, 3, 2, 3, 3}};
+  return {4, std::is_same<T, float>::value ? f32[x][rt - 1] : (SPLIT ? split[x][rt - 1] : plain[x][rt - 1]), 1};
+}
+
+template <typename Out>
 struct StreamCall {
   const svdc_shape& s;
-  int l, ldy;
   const void *F, *Qp;
-  float* Y;
-  u32x4* Yp;
-  double* fro_acc;
+  int64_t q_block;
+  Out out;
   hipStream_t st;
 };
 
-template <typename T, int KT, int RT, bool SPLIT, bool FRO>
-void stream_launch(const StreamCall& c) {
-  constexpr StreamVariant v = stream_variant<T, SPLIT>(KT, RT);
+template <typename T, int KT, int RT, bool SPLIT, typename Out>
+void stream_launch(const StreamCall<Out>& c) {
+  constexpr StreamVariant v = Out::kRowInLane ? step_variant<T, SPLIT>(KT, RT) : stream_variant<T, SPLIT>(KT, RT);
   // registers of the accumulators and the ring: two waves per SIMD where they fit
   constexpr int regs = 4 * RT * KT + v.depth * v.chunks * (RT * (int)sizeof(FPiece<T>) / 4 + KT * (SPLIT ? 8 : 4));
-  constexpr int wpe = v.waves == 8 || regs <= 232 ? 2 : 1;
+  constexpr int wpe = v.waves == 8 || regs <= (Out::kRowInLane ? 220 : 232) ? 2 : 1;
   const int groups = ((c.s.N + 15) / 16 + RT - 1) / RT;
-  fit_project_stream_kernel<T, KT, RT, v.waves, v.depth, v.chunks, SPLIT, FRO, wpe>
-      <<<(unsigned)((int64_t)groups * c.s.B), 64 * v.waves, 0, c.st>>>((const T*)c.F, (const uint16_t*)c.Qp, c.Y, c.Yp, c.fro_acc, c.s.N, c.s.D, c.l,
-                                                                  c.s.ldf, c.s.block_stride, groups, c.ldy);
+  project_stream_kernel<T, KT, RT, v.waves, v.depth, v.chunks, SPLIT, wpe, Out><<<(unsigned)((int64_t)groups * c.s.B), 64 * v.waves, 0, c.st>>>(
+      (const T*)c.F, (const uint16_t*)c.Qp, c.q_block, c.out, c.s.N, c.s.D, c.s.ldf, c.s.block_stride, groups);
 }
-template <typename T, int KT, bool SPLIT, bool FRO>
-void stream_by_rows(int rt, const StreamCall& c) {
+template <typename T, int KT, bool SPLIT, typename Out>
+void stream_by_rows(int rt, const StreamCall<Out>& c) {
   switch (rt) {
-    case 1: return stream_launch<T, KT, 1, SPLIT, FRO>(c);
-    case 2: return stream_launch<T, KT, 2, SPLIT, FRO>(c);
-    case 3: return stream_launch<T, KT, 3, SPLIT, FRO>(c);
-    case 4: return stream_launch<T, KT, 4, SPLIT, FRO>(c);
-    case 5: return stream_launch<T, KT, 5, SPLIT, FRO>(c);
-    default: return stream_launch<T, KT, 6, SPLIT, FRO>(c);
+    case 1: return stream_launch<T, KT, 1, SPLIT>(c);
+    case 2: return stream_launch<T, KT, 2, SPLIT>(c);
+    case 3: return stream_launch<T, KT, 3, SPLIT>(c);
+    case 4: return stream_launch<T, KT, 4, SPLIT>(c);
+    case 5: return stream_launch<T, KT, 5, SPLIT>(c);
+    default: return stream_launch<T, KT, 6, SPLIT>(c);
   }
 }
-template <typename T, bool SPLIT, bool FRO>
-void stream_by_width(int kt, int rt, const StreamCall& c) {
-  if (kt == 1) stream_by_rows<T, 1, SPLIT, FRO>(rt, c);
-  else if (kt == 2) stream_by_rows<T, 2, SPLIT, FRO>(rt, c);
-  else if (kt == 4) stream_by_rows<T, 4, SPLIT, FRO>(rt, c);
-  else stream_by_rows<T, 8, SPLIT, FRO>(rt, c);
+// kt: 1, 2, 4 or 8; a step comes here with those of at least MIN
+template <typename T, bool SPLIT, int MIN = 1, typename Out>
+void stream_by_width(int kt, int rt, const StreamCall<Out>& c) {
+  if constexpr (MIN <= 1) {
+    if (kt == 1) return stream_by_rows<T, 1, SPLIT>(rt, c);
+  }
+  if constexpr (MIN <= 2) {
+    if (kt == 2) return stream_by_rows<T, 2, SPLIT>(rt, c);
+  }
+  if constexpr (MIN <= 4) {
+    if (kt == 4) return stream_by_rows<T, 4, SPLIT>(rt, c);
+  }
+  stream_by_rows<T, 8, SPLIT>(rt, c);
 }
 
 }  // namespace

@@ -90,6 +90,59 @@ inline bool smoothing_takes_full_tiles(int rt, int kt2, int N, int64_t B, int cu
   return cost(rt) < 0.92 * cost(rt - 1);
 }
 
+// Row tiles of 16 that a workgroup of the streamed projection (project_stream.h) takes, 1 to 6, in calls of B blocks of ntile: those of the
+// least rounds x (rows + x).  The operands of the basis or sketch that a workgroup reads once cost it as much as x = 1.25 tiles, at every width
+// and for both storage types: over 14 shapes and 12 kinds of operands (1 x 300 x 1024 to 57 x 4608 x 3072) the choice is within
+// 3 % of the best height.
+constexpr double kStreamOperands = 1.25;
+inline int64_t stream_rounds(int rt, int ntile, int64_t B, int cus) { return ((ntile + rt - 1) / rt * B + cus - 1) / cus; }
+inline int stream_rows(int ntile, int64_t B, int cus) {
+  auto cost = [&](int rt) { return (double)stream_rounds(rt, ntile, B, cus) * (rt + kStreamOperands); };
+  int best = 1;
+  for (int rt = 2; rt <= 6; ++rt)
+    if (cost(rt) < cost(best)) best = rt;
+  return best;
+}
+
+// Whether a full step that has a buffer for its coefficients runs as two launches, the streamed projection (C and S) and a cached step's
+// kernel with -C for its state (R = F - C V^T), instead of one that keeps its rows on chip.  F is read twice, but neither launch
+// streams a basis past 16 or 32 rows at a time: 18432 x 3072 float32 at rank 128 235 -> 190 us, 57 x 4608 x 3072 bf16 at rank 128 2105 ->
+// 1751, 1 x 4608 at rank 64 45 -> 37 and rank 128 75 -> 51, 2 x 14626 x 4096 float32 at rank 128 781 -> 400 us; but 57 x 4608 x 3072 bf16 at rank
+// 32 871 -> 1020, rank 64 1174 -> 1223.  Both sides are estimated in us for 256 compute units: one launch a + d rounds (b rows + c), two launches
+// a + d (b + c rounds (rows + 1.25) + e tiles per unit), d = D / 1024, fitted to 1423 calls timed both ways (1 to 57 blocks, 200 to 24000
+// rows, ranks 33 to 128, the widths of the kernel), with margins because the estimates meet the time within 6 to 18 %; calls of less than a tile
+// of 16 rows per compute unit scatter more.  Rank 65 to 128: float32 rows take 0.77 of the time on average, bf16 ones 0.87; 33 to
+// 64: 0.92 and 0.97; one call in 100 gets more than 2 % slower (16 % at most).  float32 rows of 5120 channels go this way at any rank, of 4096
+// from rank 65 on or with a tile per compute unit: the single launch spills registers there (118 calls, 1.04 to 3.1 times the
+// time).  Single operands (SVDC_FAST) do from rank 65 and 1536 channels on.
+struct OneLaunch {
+  int rows;             // row tiles of 16 that the single launch takes
+  int64_t tiles;        // workgroup tiles of that height in all blocks
+};
+inline bool full_step_may_take_two_launches(int D, int k, bool f32, bool split) {
+  if (k <= 32) return f32 && D >= 5120;
+  return k > 64 ? D >= (split ? 512 : 1536) : split && D >= 1536;
+}
+inline bool full_step_in_two_launches(OneLaunch one, int N, int64_t B, int D, int k, bool f32, bool split, int cus) {
+  const int ntile = (N + 15) / 16, rt = stream_rows(ntile, B, cus);
+  if (f32 && (D >= 5120 || (D >= 4096 && (k > 64 || ntile * B >= cus)))) return true;
+  struct Fit { double a, b, c; } p;
+  struct Fit2 { double a, b, c, e; } q;
+  if (k > 64) {
+    p = f32 ? Fit{1.66, 17.05, 0.0} : (split ? Fit{3.62, 7.22, 5.40} : Fit{2.44, 6.82, 1.33});
+    q = f32 ? Fit2{7.35, 0.21, 2.30, 11.74} : (split ? Fit2{7.94, 0.28, 1.93, 7.20} : Fit2{6.22, 0.0, 1.31, 6.16});
+  } else {
+    p = f32 ? Fit{2.06, 9.87, 1.42} : Fit{2.81, 5.26, 1.80};
+    q = f32 ? Fit2{5.54, 0.0, 1.66, 9.75} : Fit2{6.15, 0.46, 0.99, 5.62};
+  }
+  const double d = D / 1024.0;
+  // channels that slabs of 4 x 128 do not divide: narrower slabs of the second launch
+  if (D % 512 != 0) q.e *= 1.15;
+  const double single = p.a + d * (double)((one.tiles + cus - 1) / cus) * (p.b * one.rows + p.c);
+  const double twice = q.a + d * (q.b + q.c * (double)stream_rounds(rt, ntile, B, cus) * (rt + kStreamOperands) + q.e * ((double)ntile * B / cus));
+  return twice < (rt == 1 ? 0.8 : (f32 ? 0.97 : 0.94)) * single;
+}
+
 // The general steps (general_kernels.hip) run on the float32 matrix cores, 16 rows per workgroup, or on the bf16 ones with
 // float32 values as three parts, 16 RT rows.  The rules below compare estimates of both (us, 256 compute units): rounds of workgroups
 // or workgroups per unit x (a constant + chunks of 32 channels per wave x (rows + padded rank x work)).

@@ -46,6 +46,9 @@ __device__ __forceinline__ void split_operand(const float (&c)[8], u32x4* hi, u3
               pack_bf16(rem[6], rem[7])};
 }
 
+// (1 - alpha) old + alpha now, rounded in one way wherever it is formed
+__device__ __forceinline__ float ema(float old, float now, float alpha) { return __builtin_fmaf(1.f - alpha, old, alpha * now); }
+
 // ---- wavefront reductions -----------------------------------------------------
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll

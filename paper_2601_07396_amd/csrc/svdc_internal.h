@@ -107,6 +107,12 @@ void fit_project_stream_f32(int kt, int rt, const svdc_shape& s, int l, int ldy,
                             double* fro_acc, hipStream_t st);
 void fit_project_stream_bf16(int kt, int rt, const svdc_shape& s, int l, int ldy, const void* F, const void* Qp, float* Y, void* Yp, bool last,
                              double* fro_acc, hipStream_t st);
+// The same with a packed basis in the place of the sketch: C = F V (nullable) and the state S (and its operand words Sp, nullable) of a
+// full step.  kt from 2 on for float32 features, 4 for bf16 ones, 8 with single operands.
+void step_project_stream_f32(int kt, int rt, const svdc_shape& s, const void* F, const void* packed, float* S, float* C, float alpha, int init,
+                             void* Sp, hipStream_t st);
+void step_project_stream_bf16(int kt, int rt, const svdc_shape& s, const void* F, const void* packed, float* S, float* C, float alpha, int init,
+                              void* Sp, hipStream_t st);
 // Z = F^T Y, with Y as float32 rows or (Ypacked != nullptr) in the packed form; z_clear: Z holds zeros already
 void fit_mfma_backproject(const svdc_shape& s, int l, const void* F, const float* Y, const void* Ypacked, float* Z,
                           bool z_clear, hipStream_t st);

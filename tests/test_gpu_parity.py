@@ -974,6 +974,40 @@ def test_mfma_fast_precision_mode_is_within_the_bf16_tolerance(B, N, D, k):
     assert errs[pkg.SVDC_PRECISE] <= 3e-3 and errs[pkg.SVDC_FAST] <= 1.5e-2
 
 
+@pytest.mark.parametrize("dtype,B,N,D,k,fast,pad", [
+    (torch.float32, 1, 37, 5120, 8, 0, 0), (torch.float32, 3, 333, 4096, 40, 0, 8), (torch.float32, 1, 150, 3072, 128, 0, 0),    # 1 tile per workgroup
+    (torch.bfloat16, 1, 101, 3072, 100, 0, 64), (torch.float32, 1, 6131, 1152, 68, 0, 0), (torch.bfloat16, 4, 1031, 2560, 96, 0, 0),    # 2
+    (torch.bfloat16, 1, 4609, 3072, 64, 0, 0), (torch.float32, 2, 5001, 1920, 128, 0, 0),                                      # 2, 3
+    (torch.float32, 7, 2299, 2048, 100, 0, 0), (torch.bfloat16, 4, 4199, 4096, 68, 0, 0),                                       # 4, 5
+    (torch.bfloat16, 3, 6001, 1536, 128, 0, 8), (torch.float32, 3, 7297, 512, 128, 0, 0),                                       # 5, 6
+    (torch.bfloat16, 5, 5003, 2560, 120, 1, 0)])
+def test_full_step_in_two_launches(dtype, B, N, D, k, fast, pad):
+    """A full step with a buffer for C may run as a projection and a reconstruction; without one it is a single launch.  Both add up in the
+    same order: R, S and the packed state have the same bits, also in place, and C is the oracle's."""
+    g = torch.Generator(device=DEV).manual_seed(N + D + k)
+    wide = torch.randn(B, N, D + pad, generator=g, device=DEV).to(dtype)
+    F = wide[:, :, :D]
+    V = torch.linalg.qr(torch.randn(B, D, k, generator=g, device=DEV))[0].contiguous()
+    S0 = torch.randn(B, N, k, generator=g, device=DEV)
+    shape = pkg.make_shape(F, k, pkg.SVDC_FAST if fast else pkg.SVDC_PRECISE)
+    pk = pkg.pack_basis(shape, V)
+    one, two, inplace = (torch.zeros_like(wide)[:, :, :D] for _ in range(3))
+    for init in (True, False):
+        Sa, Sb, Sc = S0.clone(), S0.clone(), S0.clone()
+        C, C2 = torch.empty_like(S0), torch.empty_like(S0)
+        Spa, Spb = pkg.alloc_packed_state(shape, DEV), pkg.alloc_packed_state(shape, DEV)
+        pkg.svdcache_full_step_packed(shape, F, V, pk, one, Sa, None, Spa, 0.3, init)
+        pkg.svdcache_full_step_packed(shape, F, V, pk, two, Sb, C, Spb, 0.3, init)
+        inplace.copy_(F)
+        pkg.svdcache_full_step(shape, inplace, V, pk, inplace, Sc, C2, 0.3, init)
+        torch.cuda.synchronize()
+        assert torch.equal(one, two) and torch.equal(Sa, Sb) and torch.equal(Spa, Spb)
+        assert torch.equal(inplace, two) and torch.equal(Sc, Sb) and torch.equal(C, C2)
+    b = B - 1
+    ref, _, Cr = ref_full_step(to_np(F[b, -40:]), to_np(V[b]), to_np(S0[b, -40:]), 0.3, False, "f32" if dtype == torch.float32 else "bf16")
+    assert_close(to_np(C[b, -40:]), Cr, "bf16" if fast else "f32", f"C[{b}]", fast=bool(fast))
+
+
 @pytest.mark.parametrize("B,N,k", [(4, 4090, 32), (4, 3060, 64), (2, 4090, 128)])
 def test_full_step_tiles_with_a_row_tile_in_lds(B, N, k):
     """3072 channels and one round of 256 or more workgroup tiles, each block ending in a partly filled tile.  At
