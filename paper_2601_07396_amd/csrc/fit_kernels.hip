@@ -36,15 +36,44 @@ __device__ __forceinline__ uint64_t mix64(uint64_t x) {
   return x;
 }
 
-__global__ void init_omega_kernel(float* Q, int64_t per_block, int64_t total, uint64_t seed) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
+// element i of the Gaussian test matrix
+__device__ __forceinline__ float omega(int64_t i, uint64_t seed) {
   const uint64_t h = mix64(seed * 0x9e3779b97f4a7c15ull + (uint64_t)i + 1);
   const uint32_t a = (uint32_t)h, c = (uint32_t)(h >> 32);
   const float u1 = ((float)(a >> 8) + 0.5f) * (1.0f / 16777216.0f);   // (0,1)
   const float u2 = ((float)(c >> 8) + 0.5f) * (1.0f / 16777216.0f);
-  Q[i] = sqrtf(-2.0f * __logf(u1)) * __cosf(6.283185307179586f * u2);  // Box-Muller
-  (void)per_block;
+  return sqrtf(-2.0f * __logf(u1)) * __cosf(6.283185307179586f * u2);  // Box-Muller
+}
+__global__ void init_omega_kernel(float* Q, int64_t total, uint64_t seed) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < total) Q[i] = omega(i, seed);
+}
+
+// Start of a fit with power iterations on the matrix cores: the test matrix [B, D, l] as operand words of the projection (layout: see
+// PackedQ; low parts where the first product takes them), the accumulators and status words (`misc`) cleared, and Z where it has to be.
+// One launch instead of four (one block of 4608 x 3072, rank 32: 18 -> 5 us).
+__global__ __launch_bounds__(256) void init_sketch_kernel(PackedQ pq, int B, int D, int l, bool low_parts, uint64_t seed, double* misc, int64_t nmisc,
+                                                          float* Z, int64_t nz) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < nmisc) misc[i] = 0.0;
+  if (4 * i + 3 < nz) *reinterpret_cast<float4*>(Z + 4 * i) = make_float4(0.f, 0.f, 0.f, 0.f);
+  else
+    for (int64_t j = 4 * i; j < nz; ++j) Z[j] = 0.f;
+  const int kts = pq.kt[0] + (pq.ranges > 1 ? pq.kt[1] : 0), lane = (int)(i & 63), r = lane & 15, g = lane >> 4;
+  const int64_t word = i >> 6;
+  const int jt = (int)(word % kts), cg = (int)(word / kts % (D / 32)), h = jt >= pq.kt[0] ? 1 : 0;
+  const int64_t b = word / kts / (D / 32);
+  if (b >= B) return;
+  const int KT = pq.kt[h], tile = jt - (h ? pq.kt[0] : 0), col = 128 * h + 16 * tile + r;
+  const int64_t per = (int64_t)D * KT * 16;                     // elements of one part of one block
+  float x[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) x[e] = col < l ? omega((b * D + 32 * cg + 8 * g + e) * l + col, seed) : 0.f;
+  u32x4 hi, lo;
+  split_operand(x, &hi, &lo);
+  u32x4* p = reinterpret_cast<u32x4*>(pq.p + pq.offset[h]) + b * 2 * (per / 8) + ((int64_t)cg * KT + tile) * 64 + lane;
+  p[0] = hi;
+  if (low_parts) p[per / 8] = lo;
 }
 
 __global__ void fill_zero_kernel(double* p, int64_t n) {
@@ -598,7 +627,7 @@ __global__ __launch_bounds__(256) void chol_panel_kernel(double* G, int l, int c
 // triangular L_jj^-T only the ten that are not zero are used.  The contraction index of step (s, e) is
 // 16 s + 4 (lane / 16) + e, so that a lane's four steps are one 16-byte piece of a float32 row.
 // The result leaves as float32 rows (out, nullable) and/or as the operand words of the projection (pq.p, nullable; see
-// pack_q_kernel), so that an iteration that goes on with the projection writes nothing else.  zero_in: the rows of In are
+// PackedQ), so that an iteration that goes on with the projection writes nothing else.  zero_in: the rows of In are
 // cleared once they have been read (the next back-projection accumulates into them).  Bound by the float64 matrix rate
 // (11 us for 57 blocks of 3072 x 64) and the latency of its loads: 38 us there and 8.4 us for one block, against 57 + 20 and 26 + 5 us for a
 // forward substitution per row followed by a packing kernel.
@@ -1600,7 +1629,7 @@ int32_t run_fit_typed(const svdc_shape& s, const FitPlan& pl, const T* F, float*
 
   const int64_t nq = (int64_t)B * s.D * l;
   // fro accumulators, status words and Jacobi counters are adjacent 256-byte aligned areas: one fill clears them all
-  zero_f64(misc, (int64_t)((pl.off_jcnt - pl.off_misc) + align_up((size_t)B * 4 * sizeof(int32_t), 8)) / 8, st);
+  const int64_t nmisc = (int64_t)((pl.off_jcnt - pl.off_misc) + align_up((size_t)B * 4 * sizeof(int32_t), 8)) / 8;
   // Partial Gram matrices go where there is most room: into their own area, or into whichever of Y and Z is not in use
   auto scratch = [&](void* other, int64_t rows) {
     const GramScratch own{Gp, (int64_t)B * kGramSlices * l * l}, lent{(double*)other, (int64_t)B * rows * l / 2};
@@ -1608,7 +1637,6 @@ int32_t run_fit_typed(const svdc_shape& s, const FitPlan& pl, const T* F, float*
   };
   void* Qp = ws + pl.off_Qp;
   const PackedQ pq = pl.mfma ? fit_mfma_packed_q(s, l, Qp) : PackedQ{};
-  bool packed = false;                       // Q is in its packed form already
   // Between the two products Y has its packed form, which for float32 features is in two parts as large as the float32 rows
   // themselves, up to the padding of N and l: it may run on into the Gram matrices' areas, not in use at that time, and
   // stays float32 rows where even that is too small.
@@ -1623,14 +1651,21 @@ int32_t run_fit_typed(const svdc_shape& s, const FitPlan& pl, const T* F, float*
   // passes, goes straight into the Rayleigh-Ritz step.
   if (pl.q == 0) {
     const int64_t ny = (int64_t)B * s.N * l;
-    init_omega_kernel<<<(unsigned)((ny + 255) / 256), 256, 0, st>>>(Y, (int64_t)s.N * l, ny, pl.seed);
+    zero_f64(misc, nmisc, st);
+    init_omega_kernel<<<(unsigned)((ny + 255) / 256), 256, 0, st>>>(Y, ny, pl.seed);
     if (pl.mfma) fit_mfma_backproject(s, l, F, Y, nullptr, Z, false, st);
     else gemm_fty<T>(s, l, F, Y, Z, st);
     if (orth(Z, Q, G, scratch(Y, s.N), M, B, s.D, l, true, pq, false, info, st) != SVDC_OK) return SVDC_E_HIP;
-    packed = pl.mfma;
     std::swap(Q, Z);
+  } else if (pl.mfma) {
+    // one launch: the test matrix as operand words, the cleared words, and Z where several row groups accumulate in it
+    const int64_t nz = zero_z ? nq : 0, nw = (int64_t)B * (s.D / 32) * (pq.kt[0] + (pq.ranges > 1 ? pq.kt[1] : 0)) * 64;
+    const int64_t n = std::max(std::max((nz + 3) / 4, nmisc), nw);
+    init_sketch_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(pq, B, s.D, l, kF32, pl.seed, misc, nmisc, Z, nz);
+    z_clear = zero_z;
   } else {
-    init_omega_kernel<<<(unsigned)((nq + 255) / 256), 256, 0, st>>>(Q, (int64_t)s.D * l, nq, pl.seed);
+    zero_f64(misc, nmisc, st);
+    init_omega_kernel<<<(unsigned)((nq + 255) / 256), 256, 0, st>>>(Q, nq, pl.seed);
   }
 
   const bool want_fro = fro2 != nullptr;
@@ -1639,7 +1674,6 @@ int32_t run_fit_typed(const svdc_shape& s, const FitPlan& pl, const T* F, float*
   // float32 features: every product splits both operands.
   auto project = [&](bool last) {
     if (pl.mfma) {
-      if (!packed) fit_mfma_pack_q(s, l, Q, Qp, st);
       fit_mfma_project(s, l, F, Qp, Y, last ? nullptr : Yp, (last && want_fro) ? misc : nullptr,
                        last || kF32, st);
       if (last && want_fro) fro_done = true;
@@ -1658,7 +1692,6 @@ int32_t run_fit_typed(const svdc_shape& s, const FitPlan& pl, const T* F, float*
     if (orth(Z, Q, G, scratch(Y, s.N), M, B, s.D, l, last_it, pq, zero_z && !last_it, info, st) != SVDC_OK)
       return SVDC_E_HIP;
     z_clear = zero_z;
-    packed = pl.mfma;
     if (last_it) std::swap(Q, Z);
   }
 

@@ -84,9 +84,9 @@ int32_t run_fit(const svdc_shape& s, const FitPlan& plan, const void* F, float* 
 // ---- matrix-core products of the basis fit: fit_mfma_kernels.hip ------------------------
 bool fit_mfma_supported(const svdc_shape& s, int l);
 size_t fit_mfma_packed_q_bytes(const svdc_shape& s, int l);
-void fit_mfma_pack_q(const svdc_shape& s, int l, const float* Q, void* Qp, hipStream_t st);
-// Where the operand words of Q go, for a kernel that writes them itself: per column range its 16-column tiles and byte
-// offset (see pack_q_kernel).
+// Where the operand words of Q go (projection layout): per column range (sketches wider than 128 are multiplied as two, 128 and the rest) its
+// 16-column tiles KT and byte offset.  Per block the hi part, D * 16 KT elements, then the lo part; in each, word (cg, jt) of 64
+// lanes x 8 bf16, lane (r, g), e  ->  Q[d = 32 cg + 8 g + e][j = 16 jt + r], 0 for columns beyond the range.
 struct PackedQ {
   char* p = nullptr;
   int ranges = 0;
