@@ -20,6 +20,7 @@
 // as bf16 "high" and "low" parts (V = hi + lo to ~16 significant bits) in
 // per-wavefront tiles of 64 lanes x 16 bytes.
 #include <algorithm>
+#include <type_traits>
 
 #include "step_tiling.h"
 #include "svdc_device.h"
@@ -167,8 +168,15 @@ struct RowPiece<float> {
 // output) instead of float32 rows: nothing is converted per tile.
 // MSX, HX (EXT only): registers are held for MSX coefficient states per tile in flight, and for the added tensor only
 // with HX -- a forecaster of two states that adds nothing should not pay for four states and a second row tile.
-template <typename T, int NCW, int KT2, bool SPLIT, int PD, bool EXT, bool PS = false, int MSX = kMaxStates, bool HX = true>
-__global__ __launch_bounds__(256) void forecast_mfma_kernel(const CoefStates cs, const uint16_t* __restrict__ P,
+// SHARED: each wave loads (and combines, and converts) a quarter of a tile's coefficients and the four pass the operand words to each
+// other through LDS, one barrier per tile; otherwise every wave loads all of them.  What a compute unit loads per time is limited (6 B per clock
+// here, whether it comes from HBM or a cache), and at rank 64 the coefficients were a third of it for bf16 rows, at rank 128 a half.  With the
+// registers that this frees, two workgroups per compute unit where the table (forecast_variant) says so.  us, before and now:
+// 2 x 119056 x 3072 bf16 rank 64 674 -> 597, 16 x 4608 rank 64 223 -> 193, rank 128 312 -> 250, single operands 194 -> 184 and 237 -> 201;
+// 18432 rows of float32, rank 32, 64, 128 93 -> 89, 98 -> 92, 116 -> 103; two states and an added tensor, 19 x 4608 bf16 rank 16 304 -> 266, 16
+// blocks rank 64 326 -> 236, 8 blocks rank 128 306 -> 171.  Not for plain bf16 calls up to rank 32 (57 x 4608: 606 and 610 us).
+template <typename T, int NCW, int KT2, bool SPLIT, int PD, bool EXT, bool PS, int MSX, bool HX, bool SHARED, int WPE>
+__global__ __launch_bounds__(256, WPE) void forecast_mfma_kernel(const CoefStates cs, const uint16_t* __restrict__ P,
                                                             const T* R, const T* X, T* Fh, int N, int D, int k,
                                                             int64_t ldf, int64_t bstride, int NS,
                                                             int groups_per_block, int tiles_per_group) {
@@ -176,8 +184,14 @@ __global__ __launch_bounds__(256) void forecast_mfma_kernel(const CoefStates cs,
   const int slab = blockIdx.x % NS;
   const int rgb = blockIdx.x / NS;
   const int b = rgb / groups_per_block, rg = rgb % groups_per_block;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  constexpr int KP = KT2 * 32;
+  const int wave = SHARED ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+  constexpr int KP = KT2 * 32, NP = SPLIT ? 2 : 1;
+  // coefficients of a tile as items: 16 of the rank for all rows (half an operand word), or a packed word; the first, how many and in which
+  // steps a wave loads them
+  constexpr int ITEMS = PS ? KT2 * NP : KT2 * 2, MINE = SHARED ? (ITEMS + kWavesPerGroup - 1) / kWavesPerGroup : ITEMS;
+  const int item0 = SHARED ? wave : 0;
+  constexpr int kItemStep = SHARED ? kWavesPerGroup : 1;
+  __shared__ u32x4 shared_words[SHARED ? 2 : 1][SHARED ? KT2 : 1][NP][SHARED ? 64 : 1];   // two buffers: one barrier per tile
   const int64_t per = (int64_t)D * KP;
   const u32x4* P2hi = reinterpret_cast<const u32x4*>(P + (int64_t)b * 4 * per + 2 * per);
   const u32x4* P2lo = reinterpret_cast<const u32x4*>(P + (int64_t)b * 4 * per + 3 * per);
@@ -198,30 +212,26 @@ __global__ __launch_bounds__(256) void forecast_mfma_kernel(const CoefStates cs,
 
   RowPiece<T> rin[PD][NCW];
   RowPiece<T> xin[PD][(EXT && HX) ? NCW : 1];
-  f32x4 sraw[PD][PS ? 1 : MS][PS ? 1 : KT2][2];
-  u32x4 spk[PD][PS ? KT2 : 1][2];   // packed state: high and low operand words
+  f32x4 sraw[PD][PS ? 1 : MS][PS ? 1 : MINE];
+  u32x4 spk[PD][PS ? MINE : 1];   // packed state
   const u32x4* spbase = PS ? reinterpret_cast<const u32x4*>(cs.s[0]) + (int64_t)b * ntile_block * KT2 * 2 * 64 + lane : nullptr;
-  // lane (r, g) needs S[row][j = 32 kt + 16 t + 4 g + i], i = 0..3 (zero beyond k)
+  // lane (r, g) needs S[row][j = 16 item + 4 g + i], i = 0..3 (zero beyond k)
   auto load_tile = [&](int tile, int u) {
     const int row = min(tile * 16 + r, N - 1);
-    if constexpr (PS) {
 #pragma unroll
-      for (int kt = 0; kt < KT2; ++kt)
+    for (int q = 0; q < MINE; ++q) {
+      const int item = item0 + kItemStep * q;
+      if (SHARED && item >= ITEMS) break;
+      if constexpr (PS) {
+        spk[u][q] = spbase[(((int64_t)tile * KT2 + item / NP) * 2 + item % NP) * 64];
+      } else {
+        const int j = 16 * item + 4 * g;
 #pragma unroll
-        for (int part = 0; part < (SPLIT ? 2 : 1); ++part)
-          spk[u][kt][part] = spbase[(((int64_t)tile * KT2 + kt) * 2 + part) * 64];
-    }
-#pragma unroll
-    for (int ms = 0; ms < (PS ? 0 : MS); ++ms) {
-      if (ms >= cs.m) break;
-#pragma unroll
-      for (int kt = 0; kt < KT2; ++kt)
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          const int j = 32 * kt + 16 * t + 4 * g;
-          sraw[u][ms][kt][t] = (j < k) ? *reinterpret_cast<const f32x4*>(cs.s[ms] + soff + (int64_t)row * k + j)
-                                       : f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int ms = 0; ms < MS; ++ms) {
+          if (ms >= cs.m) break;
+          sraw[u][ms][q] = (j < k) ? *reinterpret_cast<const f32x4*>(cs.s[ms] + soff + (int64_t)row * k + j) : f32x4{0.f, 0.f, 0.f, 0.f};
         }
+      }
     }
 #pragma unroll
     for (int c = 0; c < NCW; ++c) rin[u][c].load(rbase + (int64_t)row * ldf + 32 * c);
@@ -253,30 +263,54 @@ __global__ __launch_bounds__(256) void forecast_mfma_kernel(const CoefStates cs,
     for (int u = 0; u < PD; ++u) {
       if (it + u >= ntiles) continue;
       const int tile = rg + (it + u) * groups_per_block;
-      u32x4 shi[KT2], slo[KT2];
+      u32x4 words[KT2][NP];
+      auto at = [&](int kt, int part) -> u32x4& {
+        if constexpr (SHARED) return shared_words[(it + u) & 1][kt][part][lane];
+        else return words[kt][part];
+      };
 #pragma unroll
-      for (int kt = 0; kt < (PS ? KT2 : 0); ++kt) {
-        shi[kt] = spk[u][kt][0];
-        if (SPLIT) slo[kt] = spk[u][kt][1];
-      }
-#pragma unroll
-      for (int kt = 0; kt < (PS ? 0 : KT2); ++kt) {
-        float c8[8];
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
+      for (int q = 0; q < MINE; ++q) {
+        const int item = item0 + kItemStep * q;
+        if (SHARED && item >= ITEMS) break;
+        if constexpr (PS) {
+          at(item / NP, item % NP) = spk[u][q];
+        } else {
+          float c4[4];
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             if constexpr (EXT) {
-              float v = cs.w[0] * sraw[u][0][kt][t][i];
+              float x = cs.w[0] * sraw[u][0][q][i];
 #pragma unroll
               for (int ms = 1; ms < MS; ++ms)
-                if (ms < cs.m) v = __builtin_fmaf(cs.w[ms], sraw[u][ms][kt][t][i], v);
-              c8[4 * t + i] = -v;
+                if (ms < cs.m) x = __builtin_fmaf(cs.w[ms], sraw[u][ms][q][i], x);
+              c4[i] = -x;
             } else {
-              c8[4 * t + i] = -cs.w[0] * sraw[u][0][kt][t][i];
+              c4[i] = -cs.w[0] * sraw[u][0][q][i];
             }
           }
-        split_operand(c8, &shi[kt], &slo[kt]);
+          const uint32_t h0 = pack_bf16(c4[0], c4[1]), h1 = pack_bf16(c4[2], c4[3]);
+          auto put = [&](int part, uint32_t a, uint32_t c) {
+            if constexpr (SHARED) {
+              reinterpret_cast<uint2*>(&at(item / 2, part))[item % 2] = make_uint2(a, c);
+            } else {
+              words[item / 2][part][2 * (item % 2)] = a;
+              words[item / 2][part][2 * (item % 2) + 1] = c;
+            }
+          };
+          put(0, h0, h1);
+          if (SPLIT)
+            put(NP - 1, pack_bf16(c4[0] - bf16_lo(h0), c4[1] - bf16_hi(h0)), pack_bf16(c4[2] - bf16_lo(h1), c4[3] - bf16_hi(h1)));
+        }
+      }
+      if constexpr (SHARED) {
+        // only LDS has to be in order here: loads and stores of rows stay in flight
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+#pragma unroll
+        for (int kt = 0; kt < KT2; ++kt)
+#pragma unroll
+          for (int part = 0; part < NP; ++part) words[kt][part] = at(kt, part);
       }
       const int row = tile * 16 + r;
 #pragma unroll
@@ -293,10 +327,10 @@ __global__ __launch_bounds__(256) void forecast_mfma_kernel(const CoefStates cs,
           }
 #pragma unroll
           for (int kt = 0; kt < KT2; ++kt) {
-            acc = mfma16(a_hi[c][t][kt], shi[kt], acc);
+            acc = mfma16(a_hi[c][t][kt], words[kt][0], acc);
             if (SPLIT) {
-              acc = mfma16(a_hi[c][t][kt], slo[kt], acc);
-              acc = mfma16(a_lo[c][t][kt], shi[kt], acc);
+              acc = mfma16(a_hi[c][t][kt], words[kt][NP - 1], acc);
+              acc = mfma16(a_lo[c][t][kt], words[kt][0], acc);
             }
           }
           res[t] = acc;
@@ -628,98 +662,151 @@ int32_t launch_pack_basis(const svdc_shape& s, const float* V, void* packed, hip
 
 namespace {
 
+// Whether a kind of call shares the coefficients among the waves of a workgroup, where they are a fair part of what it loads, and whether only
+// calls of more than one workgroup per compute unit do: one that has only a few row tiles does not win back the barriers.  Against
+// every wave loading all of them in such short calls: packed states (nothing to convert) of rank 64 and 128 4 to 11 % slower (4 x 703 x 1920,
+// rank 112: 12.3 and 13.9 us), one or several states of rank <= 32 in float32 up to 15 % (12 x 691 x 512: 9.5 and 10.9 us), in bf16
+// without an added tensor 3 to 7 %; all others 1 to 40 % faster (370 sampled calls).
+enum class Share { kNever, kLongCalls, kAlways };
+template <typename T, int KT2, bool EXT, bool PS, bool HX>
+constexpr Share forecast_share() {
+  constexpr bool kF32 = sizeof(T) == 4;
+  if (KT2 == 1 && !EXT) return kF32 ? Share::kLongCalls : Share::kNever;
+  if (PS || (KT2 == 1 && (kF32 || !HX))) return Share::kLongCalls;
+  return Share::kAlways;
+}
+
+// Row tiles in flight (PD) and waves per SIMD that the registers are cut for, by the chunks of a slab.  Shared: the fastest, or
+// within 3 % of it, of 5 to 8 variants timed per kind at 3072 channels with 6 to 16 tiles per workgroup (kernel comment); the others keep
+// one workgroup per compute unit.  NARROW: a slab that cached_tiling chose instead of the widest one.
+struct ForecastVariant { int pd, wpe; };
+template <typename T, int KT2, bool SPLIT, bool EXT, bool HX, int MSX>
+constexpr ForecastVariant forecast_variant(int ncw, bool shared, bool narrow) {
+  constexpr bool kF32 = sizeof(T) == 4;
+  if (!shared) return {KT2 == 1 ? (narrow ? 2 : 1) : (KT2 == 2 && SPLIT && !kF32 ? 4 : 2), 1};
+  if (KT2 == 1) {
+    if (kF32) return ncw >= 5 ? ForecastVariant{1, 1} : ForecastVariant{EXT ? 1 : 2, EXT ? 1 : 2};
+    if (!HX) return {1, 1};
+    return ncw >= 6 ? ForecastVariant{MSX > 2 ? 1 : 2, 2} : ForecastVariant{2, 2};
+  }
+  if (KT2 == 2) {
+    if (kF32) return EXT ? ForecastVariant{ncw >= 4 ? 1 : 2, 1} : ForecastVariant{ncw >= 3 ? 2 : 3, 2};
+    if (EXT) return {2, ncw >= 5 || MSX > 2 ? 1 : 2};
+    return SPLIT ? ForecastVariant{ncw >= 4 ? 3 : 4, ncw >= 5 ? 1 : 2} : ForecastVariant{ncw >= 8 ? 2 : (ncw >= 5 ? 3 : 4), 2};
+  }
+  if (kF32) return EXT ? ForecastVariant{ncw >= 3 ? 1 : 2, 1} : ForecastVariant{2, ncw >= 3 ? 1 : 2};
+  if (EXT) return {2, SPLIT && ncw <= 2 && MSX <= 2 ? 2 : 1};
+  return SPLIT ? ForecastVariant{ncw >= 4 ? 3 : 4, ncw >= 3 ? 1 : 2} : ForecastVariant{ncw >= 4 ? 3 : 4, ncw >= 5 ? 1 : 2};
+}
+
 // tpg: row tiles per workgroup, 0: not chosen yet (see step_tiling.h, which may also choose a narrower slab)
-template <typename T, int NCW, int KT2, bool SPLIT, int PD, bool EXT, bool PS = false>
+template <typename T, int NCW, int KT2, bool SPLIT, bool EXT, bool PS = false, bool NARROW = false>
 int32_t forecast_launch(const svdc_shape& s, const CoefStates& cs, const void* packed, const void* R, const void* X,
-                        void* Fhat, hipStream_t st, int tpg = 0) {
+                        void* Fhat, hipStream_t st, int cus, int tpg = 0) {
   const int NS = s.D / (128 * NCW);
   const int ntile = (s.N + 15) / 16;
   if (tpg == 0) {
     const int m = s.D / 128;
-    const CachedCall call{m, ntile, s.B, KT2, SPLIT ? 2 : 1, (int)sizeof(T), num_compute_units()};
-    const CachedTiling t = cached_tiling(call, NCW, NCW <= 3 ? 0 : (m % 3 == 0 ? 3 : (m % 2 == 0 ? 2 : 0)));
+    constexpr bool kToOne = NCW == 3 && KT2 == 4 && sizeof(T) == 4;
+    const CachedCall call{m, ntile, s.B, KT2, SPLIT ? 2 : 1, (int)sizeof(T), cus};
+    const CachedTiling t = cached_tiling(call, NCW, NCW > 3 ? (m % 3 == 0 ? 3 : (m % 2 == 0 ? 2 : 0)) : (kToOne ? 1 : 0));
+    if constexpr (kToOne) {
+      if (t.chunks == 1) return forecast_launch<T, 1, KT2, SPLIT, EXT, PS, true>(s, cs, packed, R, X, Fhat, st, cus, t.tiles);
+    }
     if constexpr (NCW > 3) {
-      constexpr int kNarrowPD = PD < 2 ? 2 : PD;
-      if (t.chunks == 3) return forecast_launch<T, 3, KT2, SPLIT, kNarrowPD, EXT, PS>(s, cs, packed, R, X, Fhat, st, t.tiles);
-      if (t.chunks == 2) return forecast_launch<T, 2, KT2, SPLIT, kNarrowPD, EXT, PS>(s, cs, packed, R, X, Fhat, st, t.tiles);
+      if (t.chunks == 3) return forecast_launch<T, 3, KT2, SPLIT, EXT, PS, true>(s, cs, packed, R, X, Fhat, st, cus, t.tiles);
+      if (t.chunks == 2) return forecast_launch<T, 2, KT2, SPLIT, EXT, PS, true>(s, cs, packed, R, X, Fhat, st, cus, t.tiles);
     }
     tpg = t.tiles;
   }
   const int gpb = (ntile + tpg - 1) / tpg;
   const int64_t grid = (int64_t)NS * gpb * s.B;
   if (grid > 0x7fffffff) return SVDC_E_SHAPE;
-  auto launch = [&](auto kernel) {
-    kernel<<<(unsigned)grid, 256, 0, st>>>(cs, (const uint16_t*)packed, (const T*)R, (const T*)X, (T*)Fhat, s.N, s.D,
-                                           s.k, s.ldf, s.block_stride, NS, gpb, tpg);
-  };
-  if constexpr (EXT) {
-    // registers for two or four states, with or without the added tensor
-    if (cs.m <= 2) {
-      if (X) launch(forecast_mfma_kernel<T, NCW, KT2, SPLIT, PD, true, false, 2, true>);
-      else launch(forecast_mfma_kernel<T, NCW, KT2, SPLIT, PD, true, false, 2, false>);
-    } else {
-      if (X) launch(forecast_mfma_kernel<T, NCW, KT2, SPLIT, PD, true, false, kMaxStates, true>);
-      else launch(forecast_mfma_kernel<T, NCW, KT2, SPLIT, PD, true, false, kMaxStates, false>);
+  auto launch = [&](auto states, auto adds) {
+    constexpr int MSX = decltype(states)::value;
+    constexpr bool HX = decltype(adds)::value;
+    constexpr Share share = forecast_share<T, KT2, EXT, PS, HX>();
+    auto go = [&](auto shared) {
+      constexpr bool SHARED = decltype(shared)::value;
+      constexpr ForecastVariant v = forecast_variant<T, KT2, SPLIT, EXT, HX, MSX>(NCW, SHARED, NARROW);
+      forecast_mfma_kernel<T, NCW, KT2, SPLIT, v.pd, EXT, PS, MSX, HX, SHARED, v.wpe><<<(unsigned)grid, 256, 0, st>>>(
+          cs, (const uint16_t*)packed, (const T*)R, (const T*)X, (T*)Fhat, s.N, s.D, s.k, s.ldf, s.block_stride, NS, gpb, tpg);
+    };
+    if constexpr (share != Share::kNever) {
+      if (share == Share::kAlways || grid > cus) {
+        go(std::true_type{});
+        return;
+      }
     }
+    if constexpr (share != Share::kAlways) go(std::false_type{});
+  };
+  using Two = std::integral_constant<int, 2>;
+  using Most = std::integral_constant<int, kMaxStates>;
+  if constexpr (EXT) {
+    // registers for two or four states, with or without the added tensor (forecast_by_width gives the widest slabs of rank <= 32 no
+    // added tensor)
+    auto by_states = [&](auto adds) {
+      if (cs.m <= 2) launch(Two{}, adds);
+      else launch(Most{}, adds);
+    };
+    if constexpr (KT2 > 1 || NCW <= 6) {
+      if (X) {
+        by_states(std::true_type{});
+        return launch_status();
+      }
+    }
+    by_states(std::false_type{});
   } else {
-    launch(forecast_mfma_kernel<T, NCW, KT2, SPLIT, PD, false, PS>);
+    launch(Most{}, std::false_type{});
   }
   return launch_status();
 }
 
-// widest slab per wave (NCW chunks) that divides D / 128 and keeps the basis operands in registers
-template <typename T, int KT2, bool SPLIT, int PD, bool EXT, bool PS = false>
+// Slab per wave (NCW chunks): the first of the widths that suit the kind of call and divide D / 128.  Plain bf16 calls up to rank 32 take the widest
+// that keeps the basis operands in registers; hidden sizes that 12 does not divide (1152 = 9 x 128, 2560 and 5120 = 20 and 40 x
+// 128, 4096 = 32 x 128, 1920 = 15 x 128) the next.  The kinds that share the coefficients: see forecast_mfma_kernel.
+template <typename T, int KT2, bool SPLIT, bool EXT, bool PS>
+struct ForecastCall {
+  const svdc_shape& s;
+  const CoefStates& cs;
+  const void *packed, *R, *X;
+  void* Fhat;
+  hipStream_t st;
+  int cus;
+  template <int NCW, int... Rest>
+  int32_t first() const {
+    if constexpr (sizeof...(Rest) == 0) {
+      return forecast_launch<T, NCW, KT2, SPLIT, EXT, PS>(s, cs, packed, R, X, Fhat, st, cus);
+    } else {
+      if ((s.D / 128) % NCW == 0) return forecast_launch<T, NCW, KT2, SPLIT, EXT, PS>(s, cs, packed, R, X, Fhat, st, cus);
+      return first<Rest...>();
+    }
+  }
+};
+template <typename T, int KT2, bool SPLIT, bool EXT, bool PS = false>
 int32_t forecast_by_width(const svdc_shape& s, const CoefStates& cs, const void* packed, const void* R, const void* X,
                           void* Fhat, hipStream_t st) {
-  // registers: basis operands 8 (16 with the low parts) per chunk and 32 coefficients, row pieces 4 (8 for f32)
-  // (the extended kernel also holds up to 4 coefficient states and the added tensor per tile in flight)
-  constexpr int kBudget = (SPLIT ? 12 : 24) / KT2 / (sizeof(T) == 4 ? 2 : 1) / (EXT && KT2 >= 2 ? 2 : 1);
-  constexpr int kMax =
-      kBudget >= 12 ? 12 : (kBudget >= 6 ? 6 : (kBudget >= 4 ? 4 : (kBudget >= 3 ? 3 : ((kBudget >= 2 || !EXT) ? 2 : 1))));
-  const int m = s.D / 128;
-  if constexpr (kMax >= 12) {
-    if (m % 12 == 0) return forecast_launch<T, 12, KT2, SPLIT, PD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
-    // hidden sizes that 12 does not divide (1152 = 9 x 128, 2560 and 5120 = 20 and 40 x 128, 4096 = 32 x 128); only
-    // the basic kernel, to bound the number of instantiations
+  constexpr bool kF32 = sizeof(T) == 4;
+  const ForecastCall<T, KT2, SPLIT, EXT, PS> call{s, cs, packed, R, X, Fhat, st, num_compute_units()};
+  if constexpr (KT2 == 1 && !kF32) {
     if constexpr (!EXT) {
-      if (m % 10 == 0) return forecast_launch<T, 10, KT2, SPLIT, PD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
-      if (m % 9 == 0) return forecast_launch<T, 9, KT2, SPLIT, PD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
-      if (m % 8 == 0) return forecast_launch<T, 8, KT2, SPLIT, PD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
+      return call.template first<12, 10, 9, 8, 6, 5, 4, 3, 2, 1>();
+    } else {
+      if (X) return call.template first<6, 4, 3, 2, 1>();
+      return call.template first<12, 6, 4, 3, 2, 1>();
     }
+  } else if constexpr (KT2 == 1) {
+    return call.template first<6, 5, 4, 3, 2, 1>();
+  } else if constexpr (KT2 == 2) {
+    if constexpr (kF32) return call.template first<3, 4, 2, 1>();
+    else if constexpr (!SPLIT) return call.template first<6, 8, 5, 4, 3, 2, 1>();
+    else if constexpr (PS) return call.template first<5, 4, 3, 2, 1>();
+    else return call.template first<4, 3, 2, 1>();
+  } else {
+    if constexpr (kF32 || (EXT && SPLIT)) return call.template first<2, 3, 1>();
+    else if constexpr (PS && !SPLIT) return call.template first<5, 4, 3, 2, 1>();
+    else return call.template first<4, 3, 2, 1>();
   }
-  // bf16 features at rank 64 with split operands: the estimate above gives 6, but 8 chunks still fit (500 of the 512
-  // registers, no spills); a workgroup then covers a third of a 3072-channel row instead of a quarter
-  // (0.760 -> 0.725 ms at 57 x 4608 x 3072)
-  if constexpr (kMax == 6 && KT2 == 2 && SPLIT && sizeof(T) == 2 && !EXT) {
-    if (m % 8 == 0) return forecast_launch<T, 8, KT2, SPLIT, PD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
-  }
-  // float32 features at rank 64 and 128: the estimate gives 3 and 2 chunks, twice as many fit and cover twice as much of
-  // a row per workgroup (18432 x 3072: 107 -> 97 us and 142 -> 117 us); not where that leaves less than two rounds of
-  // workgroups of six row tiles (4608 rows at rank 64: 29 against 32 us)
-  if constexpr (sizeof(T) == 4 && !EXT && KT2 >= 2) {
-    constexpr int kWide = KT2 == 2 ? 6 : 4;
-    if (m % kWide == 0 && (int64_t)(m / kWide) * ((s.N + 15) / 16) * s.B >= (int64_t)12 * num_compute_units())
-      return forecast_launch<T, kWide, KT2, SPLIT, PD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
-  }
-  if constexpr (kMax >= 6) {
-    if (m % 6 == 0) return forecast_launch<T, 6, KT2, SPLIT, PD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
-    if constexpr (!EXT) {   // 1920 = 15 x 128
-      if (m % 5 == 0) return forecast_launch<T, 5, KT2, SPLIT, PD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
-    }
-  }
-  if constexpr (kMax == 3 && KT2 == 4 && SPLIT && sizeof(T) == 2 && !EXT) {   // likewise 4 chunks at rank 128
-    if (m % 4 == 0) return forecast_launch<T, 4, KT2, SPLIT, PD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
-  }
-  if constexpr (kMax >= 4) {
-    if (m % 4 == 0) return forecast_launch<T, 4, KT2, SPLIT, PD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
-  }
-  if constexpr (kMax >= 3) {
-    if (m % 3 == 0) return forecast_launch<T, 3, KT2, SPLIT, PD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
-  }
-  if constexpr (kMax >= 2) {
-    if (m % 2 == 0) return forecast_launch<T, 2, KT2, SPLIT, PD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
-  }
-  return forecast_launch<T, 1, KT2, SPLIT, PD, EXT, PS>(s, cs, packed, R, X, Fhat, st);
 }
 
 template <typename T, int CH, int RT, int KT2, bool SPLIT, int RD, bool REMA, int LT = 0>
@@ -848,20 +935,18 @@ int32_t forecast_dispatch(const svdc_shape& s, const CoefStates& cs, const void*
                           const void* X, void* Fhat, hipStream_t st) {
   const int kp = padded_rank(s.k);
   if (s.dtype == SVDC_F32) {
-    if (kp == 32) return forecast_by_width<float, 1, true, 1, EXT, PS>(s, cs, packed, R, X, Fhat, st);
-    if (kp == 64) return forecast_by_width<float, 2, true, 2, EXT, PS>(s, cs, packed, R, X, Fhat, st);
-    return forecast_by_width<float, 4, true, 2, EXT, PS>(s, cs, packed, R, X, Fhat, st);
-  }
-  if (s.precision == SVDC_PRECISE) {
-    if (kp == 32) return forecast_by_width<bf16_t, 1, true, 1, EXT, PS>(s, cs, packed, R, X, Fhat, st);
-    // at rank 64 the matrix-core time per tile is no longer small next to its memory time: more tiles in flight
-    if (kp == 64) return forecast_by_width<bf16_t, 2, true, (EXT ? 2 : 4), EXT, PS>(s, cs, packed, R, X, Fhat, st);
-    return forecast_by_width<bf16_t, 4, true, 2, EXT, PS>(s, cs, packed, R, X, Fhat, st);
+    if (kp == 32) return forecast_by_width<float, 1, true, EXT, PS>(s, cs, packed, R, X, Fhat, st);
+    if (kp == 64) return forecast_by_width<float, 2, true, EXT, PS>(s, cs, packed, R, X, Fhat, st);
+    return forecast_by_width<float, 4, true, EXT, PS>(s, cs, packed, R, X, Fhat, st);
   }
   // at rank <= 32 the split-operand kernel is the faster one (its matrix-core work is hidden anyway)
-  if (kp == 32) return forecast_by_width<bf16_t, 1, true, 1, EXT, PS>(s, cs, packed, R, X, Fhat, st);
-  if (kp == 64) return forecast_by_width<bf16_t, 2, false, 2, EXT, PS>(s, cs, packed, R, X, Fhat, st);
-  return forecast_by_width<bf16_t, 4, false, 2, EXT, PS>(s, cs, packed, R, X, Fhat, st);
+  if (kp == 32) return forecast_by_width<bf16_t, 1, true, EXT, PS>(s, cs, packed, R, X, Fhat, st);
+  if (s.precision == SVDC_PRECISE) {
+    if (kp == 64) return forecast_by_width<bf16_t, 2, true, EXT, PS>(s, cs, packed, R, X, Fhat, st);
+    return forecast_by_width<bf16_t, 4, true, EXT, PS>(s, cs, packed, R, X, Fhat, st);
+  }
+  if (kp == 64) return forecast_by_width<bf16_t, 2, false, EXT, PS>(s, cs, packed, R, X, Fhat, st);
+  return forecast_by_width<bf16_t, 4, false, EXT, PS>(s, cs, packed, R, X, Fhat, st);
 }
 
 }  // namespace

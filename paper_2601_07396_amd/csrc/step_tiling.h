@@ -44,7 +44,8 @@ struct CachedCall {
 // 1278 and 828 us).
 // A call for which even the best of these fills less than 0.7 leaves compute units idle (one block of 4608 x 3072 rows:
 // 96 workgroups of 1536 channels).  It may take fewer tiles, and a slab of 3 or 2 chunks (`narrow`, 0 if there is none)
-// instead of the widest one, where that costs less: 23 -> 13 us for that block at rank 32, 23 -> 17 us at rank 64.  Not
+// instead of the widest one, where that costs less: 23 -> 13 us for that block at rank 32, 23 -> 17 us at rank 64; one chunk instead of
+// 3 for float32 rows at rank 128 of an odd number of chunks (1 x 439 x 1152: 5.1 us with 3, 4.3 with one).  Not
 // where many small workgroups would only load operands (43 x 129 x 2048, rank 128: 29 us wide, 46 us narrow); over 460
 // sampled calls of up to two rounds this is within 4 % of the best of all choices.
 inline CachedTiling cached_tiling(const CachedCall& call, int chunks, int narrow) {
@@ -53,7 +54,7 @@ inline CachedTiling cached_tiling(const CachedCall& call, int chunks, int narrow
     if (call.fill({chunks, cand}) > call.fill(best) + 1e-9) best.tiles = cand;
   if (call.fill(best) >= 0.7) return best;
   double least = 0.85 * call.cost(best);
-  const int few = chunks > 3 ? narrow : chunks;
+  const int few = chunks > 3 || narrow > 0 ? narrow : chunks;
   for (int cand = std::min(16, call.ntile); few > 0 && cand >= 1; --cand) {
     const double c = call.cost({few, cand});
     if (c < least) {

@@ -1008,6 +1008,63 @@ def test_full_step_in_two_launches(dtype, B, N, D, k, fast, pad):
     assert_close(to_np(C[b, -40:]), Cr, "bf16" if fast else "f32", f"C[{b}]", fast=bool(fast))
 
 
+@pytest.mark.parametrize("dtype,B,N,D,k,fast,pad", [
+    (torch.float32, 1, 6150, 3072, 32, 0, 0), (torch.float32, 3, 2777, 1920, 20, 0, 8), (torch.float32, 2, 13001, 256, 8, 0, 0),      # slabs of 6, 5, 2
+    (torch.float32, 1, 4403, 3072, 64, 0, 0), (torch.float32, 2, 3333, 2048, 40, 0, 64),                                       # 3, 4
+    (torch.float32, 1, 3333, 3072, 128, 0, 0), (torch.float32, 3, 4111, 1152, 100, 0, 0), (torch.float32, 1, 77, 1536, 64, 0, 0),
+    (torch.bfloat16, 1, 12100, 3072, 16, 0, 0), (torch.bfloat16, 3, 6007, 1152, 32, 0, 8),                                     # 6 and 12, 3
+    (torch.bfloat16, 2, 5003, 2560, 64, 0, 0), (torch.bfloat16, 1, 9007, 3072, 52, 0, 0), (torch.bfloat16, 5, 5555, 256, 48, 0, 0),   # 4 and 5, 4, 2
+    (torch.bfloat16, 1, 5001, 3072, 128, 0, 0), (torch.bfloat16, 3, 5003, 1152, 72, 0, 64), (torch.bfloat16, 1, 129, 3072, 128, 0, 0),
+    (torch.bfloat16, 1, 7001, 3072, 64, 1, 0), (torch.bfloat16, 2, 6001, 2048, 48, 1, 0),                                      # 6, 8
+    (torch.bfloat16, 2, 4999, 2560, 100, 1, 8), (torch.bfloat16, 1, 5005, 1920, 128, 1, 0)])
+def test_cached_steps_share_their_coefficients(dtype, B, N, D, k, fast, pad):
+    """The waves of a workgroup load and convert a quarter of a row tile's coefficients each and pass the operands on: plain and packed
+    state, 2 to 4 states with and without an added tensor, in place.  Every element against float64, and the same bits as a call
+    of the last rows alone, whose workgroups have one row tile or share nothing.
+    Bound: bf16 has 8 bits, so a coefficient or a basis element is off by 2^-8 of itself as one bf16, by 2^-16 as two (a high and a low part); two
+    such factors, and the dropped low x low product, make 2^-7 (1 + 2^-9) or 3 x 2^-16; weighting and adding up in float32 at most (k + 8) 2^-24 < 2^-16 of
+    sum |w s v|; then the sum with R and X and the storage rounding."""
+    g = torch.Generator(device=DEV).manual_seed(N + D + k)
+    wide = torch.randn(B, N, D + pad, generator=g, device=DEV).to(dtype)
+    R = wide[:, :, :D]
+    X = torch.randn(B, N, D + pad, generator=g, device=DEV).to(dtype)[:, :, :D]
+    V = (torch.randn(B, D, k, generator=g, device=DEV) / D ** 0.5).contiguous()
+    S = [torch.randn(B, N, k, generator=g, device=DEV) for _ in range(4)]
+    shape = pkg.make_shape(R, k, pkg.SVDC_FAST if fast else pkg.SVDC_PRECISE)
+    pk = pkg.pack_basis(shape, V)
+    n0 = N - min(N, k + 13)
+    tail = [s[-1:, n0:].contiguous() for s in S]
+    tshape, tpk = pkg.make_shape(R[-1:, n0:], k, pkg.SVDC_FAST if fast else pkg.SVDC_PRECISE), pkg.pack_basis(shape, V)[-pk.numel() // B:]
+    unit = 2.0 ** -8 if dtype == torch.bfloat16 else 2.0 ** -24
+    product = (2.0 ** -7 * (1 + 2.0 ** -9) if fast and k > 32 else 3 * 2.0 ** -16) + 2.0 ** -16
+    empty = lambda: torch.empty_like(wide)[:, :, :D]
+    for w, x in (([1.0], False), ([1.5, -0.5], True), ([2.0, -1.0], False), ([0.5, 0.25, -1.25], True), ([0.5, 0.25, -1.25, 2.0], False)):
+        out, again, part = empty(), empty(), empty()[-1:, n0:]
+        if len(w) == 1:
+            pkg.svdcache_forecast(shape, S[0], V, pk, R, out)
+            pkg.svdcache_forecast(tshape, tail[0], V[-1:], tpk, R[-1:, n0:], part)
+            Sp = pkg.alloc_packed_state(shape, DEV)
+            pkg.svdcache_pack_state(shape, S[0], Sp)
+            pkg.svdcache_forecast_packed(shape, Sp, pk, R, again)
+        else:
+            m = len(w)
+            pkg.svdcache_forecast_combine(shape, S[:m], w, V, pk, R, X if x else None, out)
+            pkg.svdcache_forecast_combine(tshape, tail[:m], w, V[-1:], tpk, R[-1:, n0:], X[-1:, n0:] if x else None, part)
+            again.copy_(X if x else R)
+            pkg.svdcache_forecast_combine(shape, S[:m], w, V, pk, R if x else again, again if x else None, again)
+        torch.cuda.synchronize()
+        assert torch.equal(out, again) and torch.equal(out[-1:, n0:], part), (w, x)
+        for b in range(B):
+            c, size = sum(wi * s[b].double() for wi, s in zip(w, S)), sum(abs(wi) * s[b].double().abs() for wi, s in zip(w, S))
+            added = X[b].double() if x else 0.0
+            want = c @ V[b].double().T + R[b].double() + added
+            size = size @ V[b].double().abs().T
+            bound = product * size + 2.0 ** -22 * (size + R[b].double().abs() + abs(added))
+            bound = bound + unit * (want.abs() + bound) + 1e-30
+            worst = float(((out[b].double() - want).abs() / bound).max())
+            assert worst <= 1.0, (w, x, b, worst)
+
+
 @pytest.mark.parametrize("B,N,k", [(4, 4090, 32), (4, 3060, 64), (2, 4090, 128)])
 def test_full_step_tiles_with_a_row_tile_in_lds(B, N, k):
     """3072 channels and one round of 256 or more workgroup tiles, each block ending in a partly filled tile.  At
