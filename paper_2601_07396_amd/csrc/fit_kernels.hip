@@ -415,9 +415,18 @@ __device__ __forceinline__ void gram_tile(const float* a, double* g, f64x4 (*par
     }
 }
 
+// Where the partial Gram matrices (l x l doubles each) lie: the first end[0] in p[0], up to end[1] in p[1], the others in p[2].
+struct GramParts {
+  double* p[3];
+  int64_t end[2];
+  __device__ __forceinline__ double* at(int64_t i, int64_t ll) const {
+    return i < end[0] ? p[0] + i * ll : (i < end[1] ? p[1] + (i - end[0]) * ll : p[2] + (i - end[1]) * ll);
+  }
+};
+
 // ONE_TILE: l <= 64, a single tile on the diagonal (a kernel of its own: 150 instead of 330 registers)
 template <bool ONE_TILE>
-__global__ __launch_bounds__(256, ONE_TILE ? 3 : 1) void gram_f64_kernel(const float* __restrict__ A, double* G, int rows, int l,
+__global__ __launch_bounds__(256, ONE_TILE ? 3 : 1) void gram_f64_kernel(const float* __restrict__ A, GramParts parts, int rows, int l,
                                                        int rows_per_slice) {
   __shared__ f64x4 part[2 * (ONE_TILE ? 10 : 16) * 64];
   const int b = blockIdx.z;
@@ -425,7 +434,7 @@ __global__ __launch_bounds__(256, ONE_TILE ? 3 : 1) void gram_f64_kernel(const f
   while ((ti + 1) * (ti + 2) / 2 <= (int)blockIdx.y) ++ti;
   const int tj = blockIdx.y - ti * (ti + 1) / 2;
   const float* a = A + (int64_t)b * rows * l;
-  double* g = G + ((int64_t)b * gridDim.x + blockIdx.x) * l * l;   // partial Gram matrix of this row slice
+  double* g = parts.at((int64_t)b * gridDim.x + blockIdx.x, (int64_t)l * l);   // partial Gram matrix of this row slice
   const int rbeg = blockIdx.x * rows_per_slice, rend = min(rows, rbeg + rows_per_slice);
   if (ONE_TILE || ti == tj) gram_tile<true>(a, g, reinterpret_cast<f64x4(*)[10][64]>(part), rows, l, ti, tj, rbeg, rend);
   else if constexpr (!ONE_TILE) gram_tile<false>(a, g, reinterpret_cast<f64x4(*)[16][64]>(part), rows, l, ti, tj, rbeg, rend);
@@ -434,18 +443,16 @@ __global__ __launch_bounds__(256, ONE_TILE ? 3 : 1) void gram_f64_kernel(const f
 // G[b] = sum over the row slices of the partial Gram matrices, in a fixed order (no atomics: the same bits every run);
 // lower block triangle only, like the partial matrices.  64 elements per workgroup, the slices in four shares with
 // several loads in flight each (one thread per element walking over 16 slices took 6.2 us at any size, this 3 us).
-__global__ __launch_bounds__(256) void gram_reduce_kernel(const double* __restrict__ part, double* G, int nslice,
-                                                          int l) {
+__global__ __launch_bounds__(256) void gram_reduce_kernel(GramParts parts, double* G, int nslice, int l) {
   __shared__ double share[3][64];
-  const int b = blockIdx.y, lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const int b = blockIdx.y, lane = threadIdx.x & 63, q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t ll = (int64_t)l * l;
   const int64_t e = (int64_t)blockIdx.x * 64 + lane;
   const bool in = e < ll && (e % l) / 64 <= (e / l) / 64;
   double s = 0.0;
   if (in) {
-    const double* p = part + (int64_t)b * nslice * ll + e;
 #pragma unroll 6
-    for (int i = q; i < nslice; i += 4) s += p[(int64_t)i * ll];
+    for (int i = q; i < nslice; i += 4) s += parts.at((int64_t)b * nslice + i, ll)[e];
   }
   if (q > 0) share[q - 1][lane] = s;
   __syncthreads();
@@ -1529,23 +1536,26 @@ void gemm_fty(const svdc_shape& s, int l, const T* F, const float* Y, float* Z, 
   else launch(fit_cols_general_kernel<T, 4>, 4);
 }
 
-// Scratch for partial Gram matrices: `doubles` float64 values.
-struct GramScratch { double* p; int64_t doubles; };
+// Scratch for partial Gram matrices: areas of float64 values.
+struct GramScratch { double* p[3]; int64_t doubles[3]; };
 
 // Row slices: as many as fit into one round of two workgroups per compute unit (three for l <= 64), of at least 64 rows
-// each and as the scratch holds.
+// each and as the areas hold together.  One block of 3072 channels: 18432 rows, l = 128, 16 slices in the largest area 57 us, 40 in all three
+// 30; l = 64, the five Gram matrices of a fit of 4608 rows 43 -> 37 us.
 void gram(const float* A, double* G, GramScratch sc, int B, int rows, int l, hipStream_t st) {
   const int ntile = (l + 63) / 64, tiles = ntile * (ntile + 1) / 2;
   const int64_t ll = (int64_t)l * l;
   int64_t want = std::max<int64_t>(1, (l <= 64 ? 3 : 2) * num_compute_units() / ((int64_t)tiles * B));
-  want = std::min<int64_t>(want, std::max<int64_t>(kGramSlices, sc.doubles / (ll * B)));
+  const int64_t held[3] = {sc.doubles[0] / ll, sc.doubles[1] / ll, sc.doubles[2] / ll};
+  want = std::min<int64_t>(want, (held[0] + held[1] + held[2]) / B);
+  const GramParts parts{{sc.p[0], sc.p[1], sc.p[2]}, {held[0], held[0] + held[1]}};
   int rows_per_slice = (int)(((rows + want - 1) / want + 15) / 16 * 16);
   if (rows_per_slice < 64) rows_per_slice = 64;
   const int nslice = (rows + rows_per_slice - 1) / rows_per_slice;
   const dim3 grid(nslice, tiles, B);
-  if (l <= 64) gram_f64_kernel<true><<<grid, 256, 0, st>>>(A, sc.p, rows, l, rows_per_slice);
-  else gram_f64_kernel<false><<<grid, 256, 0, st>>>(A, sc.p, rows, l, rows_per_slice);
-  gram_reduce_kernel<<<dim3((unsigned)((ll + 63) / 64), B), 256, 0, st>>>(sc.p, G, nslice, l);
+  if (l <= 64) gram_f64_kernel<true><<<grid, 256, 0, st>>>(A, parts, rows, l, rows_per_slice);
+  else gram_f64_kernel<false><<<grid, 256, 0, st>>>(A, parts, rows, l, rows_per_slice);
+  gram_reduce_kernel<<<dim3((unsigned)((ll + 63) / 64), B), 256, 0, st>>>(parts, G, nslice, l);
 }
 
 // Cholesky factor of G + shift I in place, l <= 256: L in the lower triangle; for l > 64 the strict upper triangle
@@ -1630,12 +1640,13 @@ int32_t run_fit_typed(const svdc_shape& s, const FitPlan& pl, const T* F, float*
   const int64_t nq = (int64_t)B * s.D * l;
   // fro accumulators, status words and Jacobi counters are adjacent 256-byte aligned areas: one fill clears them all
   const int64_t nmisc = (int64_t)((pl.off_jcnt - pl.off_misc) + align_up((size_t)B * 4 * sizeof(int32_t), 8)) / 8;
-  // Partial Gram matrices go where there is most room: into their own area, or into whichever of Y and Z is not in use
-  auto scratch = [&](void* other, int64_t rows) {
-    const GramScratch own{Gp, (int64_t)B * kGramSlices * l * l}, lent{(double*)other, (int64_t)B * rows * l / 2};
-    return lent.doubles > own.doubles ? lent : own;
-  };
   void* Qp = ws + pl.off_Qp;
+  // Partial Gram matrices go into their own area, into whichever of Y and Z is not in use and into the operand words of Q, which the
+  // last product has read and apply_factor writes again.
+  auto scratch = [&](void* other, int64_t rows) {
+    return GramScratch{{(double*)other, Gp, (double*)Qp},
+                       {(int64_t)B * rows * l / 2, (int64_t)B * kGramSlices * l * l, (int64_t)((pl.total - pl.off_Qp) / sizeof(double))}};
+  };
   const PackedQ pq = pl.mfma ? fit_mfma_packed_q(s, l, Qp) : PackedQ{};
   // Between the two products Y has its packed form, which for float32 features is in two parts as large as the float32 rows
   // themselves, up to the padding of N and l: it may run on into the Gram matrices' areas, not in use at that time, and

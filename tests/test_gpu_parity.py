@@ -974,6 +974,14 @@ def test_mfma_fast_precision_mode_is_within_the_bf16_tolerance(B, N, D, k):
     assert errs[pkg.SVDC_PRECISE] <= 3e-3 and errs[pkg.SVDC_FAST] <= 1.5e-2
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("B,D,l,N", [(1, 128, 36, 4000), (3, 256, 64, 6001), (2, 384, 128, 5003), (1, 264, 50, 3001)])
+def test_fit_basis_partial_gram_matrices_in_several_areas(dtype, B, D, l, N):
+    """Many more rows than channels: the partial Gram matrices of Y do not fit into one area of the workspace and lie in three
+    (the last case has no operand words, so in two), one block's in two of them."""
+    test_fit_basis_at_the_block_edges_of_the_small_matrices(dtype, B, D, l, N - l)
+
+
 @pytest.mark.parametrize("dtype,B,N,D,k,fast,pad", [
     (torch.float32, 1, 37, 5120, 8, 0, 0), (torch.float32, 3, 333, 4096, 40, 0, 8), (torch.float32, 1, 150, 3072, 128, 0, 0),    # 1 tile per workgroup
     (torch.bfloat16, 1, 101, 3072, 100, 0, 64), (torch.float32, 1, 6131, 1152, 68, 0, 0), (torch.bfloat16, 4, 1031, 2560, 96, 0, 0),    # 2
