@@ -725,7 +725,9 @@ int32_t forecast_launch(const svdc_shape& s, const CoefStates& cs, const void* p
   auto launch = [&](auto states, auto adds) {
     constexpr int MSX = decltype(states)::value;
     constexpr bool HX = decltype(adds)::value;
-    constexpr Share share = forecast_share<T, KT2, EXT, PS, HX>();
+    // the kind that may take slabs of 12 unshared (forecast_by_width), and the narrow ones chosen in their place
+    constexpr bool kWide = PS && !SPLIT && KT2 == 2;
+    constexpr Share share = kWide && NCW == 12 ? Share::kNever : forecast_share<T, KT2, EXT, PS, HX>();
     auto go = [&](auto shared) {
       constexpr bool SHARED = decltype(shared)::value;
       constexpr ForecastVariant v = forecast_variant<T, KT2, SPLIT, EXT, HX, MSX>(NCW, SHARED, NARROW);
@@ -733,7 +735,7 @@ int32_t forecast_launch(const svdc_shape& s, const CoefStates& cs, const void* p
           cs, (const uint16_t*)packed, (const T*)R, (const T*)X, (T*)Fhat, s.N, s.D, s.k, s.ldf, s.block_stride, NS, gpb, tpg);
     };
     if constexpr (share != Share::kNever) {
-      if (share == Share::kAlways || grid > cus) {
+      if (share == Share::kAlways || (grid > cus && !(kWide && NARROW && s.D % 1536 == 0))) {
         go(std::true_type{});
         return;
       }
@@ -799,7 +801,15 @@ int32_t forecast_by_width(const svdc_shape& s, const CoefStates& cs, const void*
     return call.template first<6, 5, 4, 3, 2, 1>();
   } else if constexpr (KT2 == 2) {
     if constexpr (kF32) return call.template first<3, 4, 2, 1>();
-    else if constexpr (!SPLIT) return call.template first<6, 8, 5, 4, 3, 2, 1>();
+    else if constexpr (!SPLIT && PS) {
+      // Single operand words that are loaded as they are: 2 KB per tile, and four waves hold 1536 channels.  Slabs of 12 unshared beat
+      // 6 shared in long calls, and in short ones, where they make way for narrow ones (57 x 4608 x 3072, 128 pieces of a tile per compute
+      // unit: 636 and 649 us; 1 x 4608, 2.25 pieces: 15.9 and 17.4), but not between them (9 and 18 pieces: 1 x 18432 x 3072 50.3 and 49.5 us,
+      // 16 x 4608 x 1536 100 and 95; 29: 149.6 and 150.2).
+      const int64_t pieces = (int64_t)((s.N + 15) / 16) * s.B * (s.D / 1536);
+      if (pieces <= 4 * (int64_t)call.cus || pieces >= 48 * (int64_t)call.cus) return call.template first<12, 6, 8, 5, 4, 3, 2, 1>();
+      return call.template first<6, 8, 5, 4, 3, 2, 1>();
+    } else if constexpr (!SPLIT) return call.template first<6, 8, 5, 4, 3, 2, 1>();
     else if constexpr (PS) return call.template first<5, 4, 3, 2, 1>();
     else return call.template first<4, 3, 2, 1>();
   } else {

@@ -1024,6 +1024,7 @@ def test_full_step_in_two_launches(dtype, B, N, D, k, fast, pad):
     (torch.bfloat16, 2, 5003, 2560, 64, 0, 0), (torch.bfloat16, 1, 9007, 3072, 52, 0, 0), (torch.bfloat16, 5, 5555, 256, 48, 0, 0),   # 4 and 5, 4, 2
     (torch.bfloat16, 1, 5001, 3072, 128, 0, 0), (torch.bfloat16, 3, 5003, 1152, 72, 0, 64), (torch.bfloat16, 1, 129, 3072, 128, 0, 0),
     (torch.bfloat16, 1, 7001, 3072, 64, 1, 0), (torch.bfloat16, 2, 6001, 2048, 48, 1, 0),                                      # 6, 8
+    (torch.bfloat16, 1, 9001, 3072, 64, 1, 0), (torch.bfloat16, 2, 50003, 3072, 40, 1, 0),                                     # between and beyond the unshared slabs of 12
     (torch.bfloat16, 2, 4999, 2560, 100, 1, 8), (torch.bfloat16, 1, 5005, 1920, 128, 1, 0)])
 def test_cached_steps_share_their_coefficients(dtype, B, N, D, k, fast, pad):
     """The waves of a workgroup load and convert a quarter of a row tile's coefficients each and pass the operands on: plain and packed
