@@ -86,8 +86,8 @@ struct StepOut {
   }
 };
 
-// q_block: elements from one block's operand words to the next one's
-template <typename T, int KT, int RT, int NW, int DEPTH, int CS, bool SPLIT, int WPE, typename Out>
+// q_block: elements from one block's operand words to the next one's.  RUN: the waves take runs of that many slots in turn; 0: one share each.
+template <typename T, int KT, int RT, int NW, int DEPTH, int CS, bool SPLIT, int WPE, int RUN, typename Out>
 __global__ __launch_bounds__(64 * NW, WPE) void project_stream_kernel(const T* __restrict__ F, const uint16_t* __restrict__ Qp, int64_t q_block, Out out,
                                                                       int N, int D, int64_t ldf, int64_t bstride, int groups_per_block) {
   constexpr bool FRO = Out::kNorm;
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(64 * NW, WPE) void project_stream_kernel(const T* _
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
   const int64_t per = (int64_t)D * KT * 16;
   // the slots of CS chunks that are this wave's (D / 32 is a multiple of 4)
-  const int all = D / (32 * CS), first = wave * all / NW, n = (wave + 1) * all / NW - first;
+  const int all = D / (32 * CS), begin = wave * all / NW, n = (wave + 1) * all / NW - begin, first = RUN ? wave * RUN : begin;
   const u32x4* Qhi = reinterpret_cast<const u32x4*>(Qp + b * q_block) + (int64_t)first * CS * KT * 64 + lane;
   const u32x4* Qlo = Qhi + per / 8;
   const int tile0 = rg * RT;
@@ -119,7 +119,8 @@ __global__ __launch_bounds__(64 * NW, WPE) void project_stream_kernel(const T* _
 #pragma unroll
     for (int jt = 0; jt < KT; ++jt) acc[t][jt] = f32x4{0.f, 0.f, 0.f, 0.f};
   // bf16: the two 64-byte halves of a 128-byte line belong to neighbouring chunks and are requested together where CS = 2
-  auto load = [&](Slot& s, int i) {
+  auto load = [&](Slot& s, int slot) {
+    const int i = RUN ? slot / max(RUN, 1) * NW * RUN + slot % max(RUN, 1) : slot;
 #pragma unroll
     for (int t = 0; t < RT; ++t)
 #pragma unroll
@@ -267,8 +268,18 @@ void stream_launch(const StreamCall<Out>& c) {
   constexpr int regs = 4 * RT * KT + v.depth * v.chunks * (RT * (int)sizeof(FPiece<T>) / 4 + KT * (SPLIT ? 8 : 4));
   constexpr int wpe = v.waves == 8 || regs <= (Out::kRowInLane ? 220 : 232) ? 2 : 1;
   const int groups = ((c.s.N + 15) / 16 + RT - 1) / RT;
-  project_stream_kernel<T, KT, RT, v.waves, v.depth, v.chunks, SPLIT, wpe, Out><<<(unsigned)((int64_t)groups * c.s.B), 64 * v.waves, 0, c.st>>>(
-      (const T*)c.F, (const uint16_t*)c.Qp, c.q_block, c.out, c.s.N, c.s.D, c.s.ldf, c.s.block_stride, groups);
+  auto launch = [&](auto run) {
+    project_stream_kernel<T, KT, RT, v.waves, v.depth, v.chunks, SPLIT, wpe, decltype(run)::value, Out><<<(unsigned)((int64_t)groups * c.s.B), 64 * v.waves, 0, c.st>>>(
+        (const T*)c.F, (const uint16_t*)c.Qp, c.q_block, c.out, c.s.N, c.s.D, c.s.ldf, c.s.block_stride, groups);
+  };
+  // Plain operands of width 64 at the height of large calls: the waves take 128 channels in turn, the order in which kernels that hold slabs of 512
+  // channels add up, so that the bits of such fits are theirs (Y is rounded to bf16 before its next use, and in another order a rounding flips now
+  // and then: R of 57 x 4608 x 3072 moved by 6e-4).  57 x 4608 x 3072, a whole fit 2894 us, with one share for each wave 2882.
+  if constexpr (!SPLIT && KT == 4 && RT == 5) {
+    static_assert(v.waves == 4 && 4 % v.chunks == 0, "slabs of 4 waves x 4 chunks");
+    if (c.s.D % 512 == 0) return launch(std::integral_constant<int, 4 / v.chunks>{});
+  }
+  launch(std::integral_constant<int, 0>{});
 }
 template <typename T, int KT, bool SPLIT, typename Out>
 void stream_by_rows(int rt, const StreamCall<Out>& c) {

@@ -1,6 +1,8 @@
 """GPU parity: the HIP path (through the C ABI) against the CPU oracle on the same seeded inputs.
 `assert_close` bounds the error of every element (one unit in the last place of the storage type plus the
 accumulated arithmetic error, scaled by the row), of every row and of the whole block."""
+import hashlib
+
 import numpy as np
 import pytest
 import torch
@@ -784,6 +786,20 @@ def test_fit_basis_streamed_projections(dtype, B, D, l, N):
     """Every number of row tiles that a workgroup of the streamed projection takes, with ragged rows, an odd last tile (half of the
     last operand word of Y is zero) and fewer chunks of channels than waves; large bf16 calls, which have other kernels."""
     test_fit_basis_at_the_block_edges_of_the_small_matrices(dtype, B, D, min(l, D), N - min(l, D))
+
+
+@pytest.mark.parametrize("B,N,D,V_digest,sigma_digest", [(130, 512, 1024, "69908a374b01abf9", "62f922c358e915a4"),
+                                                         (57, 1200, 3072, "027d9eb40febfd10", "42968fb35e9a79b2")])
+def test_large_fits_of_width_64_keep_their_bits(B, N, D, V_digest, sigma_digest):
+    """Calls that add nothing with atomics give the same bits every run, and those of bf16 features and width 64 the bits they gave when slabs of
+    Q were held in registers (the digests are from that library): the streamed projection adds their channels up in that order."""
+    h = torch.arange(B * N * D, device=DEV) * 6364136223846793005 + 1442695040888963407
+    h = (h ^ (h >> 29)) * -4658895280553007687
+    F = ((h >> 40) & 0xffff).float() / 65536 - 0.5
+    F = (F.view(B, N, D) / (1 + torch.arange(D, device=DEV) / 8)).to(torch.bfloat16)
+    V, sigma, _ = pkg.fit_basis(F, 32)
+    digests = [hashlib.sha256(t.cpu().numpy().tobytes()).hexdigest()[:16] for t in (V, sigma)]
+    assert digests == [V_digest, sigma_digest]
 
 
 @pytest.mark.parametrize("dtype,B,D,l,N", [
