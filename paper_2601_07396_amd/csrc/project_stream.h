@@ -134,7 +134,7 @@ __global__ __launch_bounds__(64 * NW, WPE) void project_stream_kernel(const T* _
         if (SPLIT) s.q[c][jt][NP - 1] = Qlo[w * 64];
       }
   };
-  float ssq = 0.f;
+  float ssq[RT] = {};      // per tile: rows beyond N leave the sum at the end, not in the loop
   auto use = [&](const Slot& s) {
 #pragma unroll
     for (int c = 0; c < CS; ++c) {
@@ -153,8 +153,7 @@ __global__ __launch_bounds__(64 * NW, WPE) void project_stream_kernel(const T* _
       }
       if (FRO) {
 #pragma unroll
-        for (int t = 0; t < RT; ++t)
-          if ((tile0 + t) * 16 + r < N) ssq += s.f[t][c].sumsq();
+        for (int t = 0; t < RT; ++t) ssq[t] += s.f[t][c].sumsq();
       }
     }
   };
@@ -180,7 +179,11 @@ __global__ __launch_bounds__(64 * NW, WPE) void project_stream_kernel(const T* _
     if (i + u + DEPTH < n) use(ring[u]);
 
   if (FRO) {
-    const double s = wave_sum((double)ssq);
+    double s = 0.0;
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+      if ((tile0 + t) * 16 + r < N) s += (double)ssq[t];
+    s = wave_sum(s);
     if (lane == 0) norm[wave] = s;
   }
 
@@ -213,14 +216,21 @@ __global__ __launch_bounds__(64 * NW, WPE) void project_stream_kernel(const T* _
   }
 }
 
-// Waves, ring slots and chunks per slot for 1 to 6 row tiles.  Eight waves share the channels while the accumulators leave room
-// for it (two waves per SIMD hide each other's waits), four where they do not; a deeper ring gained nothing or spilled.  Each the
-// fastest or within 3 % of it among 7 to 15 variants per height, timed at 15 shapes.
+// Waves, ring slots and chunks per slot for 1 to 6 row tiles: eight waves, two per SIMD to hide each other's waits, or four with twice the
+// registers, whichever was timed faster, at 15 shapes and without the squares; each within 3 % of the best of 7 to 15 variants.
+// norm: where the squares' sums would not fit beside them, so that no variant uses scratch (with the rows tested at every use 22 of the 48
+// with squares did, 8 to 916 bytes a lane).  The last product of a fit of one block of 3072 channels, us, before and now: 23000 float32 rows
+// width 32 75 -> 45, width 128 91 -> 67; 18432 width 128 72 -> 53; 12000 bf16 rows width 16 47 -> 18, width 64 38 -> 24.
 struct StreamVariant {
   int waves, depth, chunks;
 };
 template <typename T, bool SPLIT>
-constexpr StreamVariant stream_variant(int kt, int rt) {
+constexpr StreamVariant stream_variant(int kt, int rt, bool norm) {
+  if (norm && std::is_same<T, float>::value) {
+    if ((kt == 2 && rt == 6) || (kt == 8 && rt == 2) || (kt == 4 && rt == 4)) return {8, 1, 1};
+    if (kt == 8 && rt == 6) return {4, 1, 1};
+  }
+  if (norm && !std::is_same<T, float>::value && kt == 1 && rt == 4) return {4, 2, 2};
   const int x = kt == 1 ? 0 : (kt == 2 ? 1 : (kt == 4 ? 2 : 3));
   constexpr StreamVariant f32[4][6] = {
       {{8, 4, 1}, {8, 4, 1}, {8, 3, 1}, {4, 3, 1}, {8, 2, 1}, {4, 2, 1}},
@@ -242,11 +252,12 @@ constexpr StreamVariant stream_variant(int kt, int rt) {
 
 // A full step adds the channels up in the order of full_step_mfma_kernel, four waves and a chunk at a time, so that its results do not
 // depend on which of the two a call takes (only one with a buffer for C comes here).  Ring slots for padded rank 32, 64, 128; 4608 x 3072
-// float32 rows at rank 128 with eight waves 33 us, with four 37, elsewhere within 5 %.
+// float32 rows at rank 128 with eight waves 33 us, with four 37, elsewhere within 5 %.  A depth of 2 at six float32 tiles of rank 128 spilled: full
+// step of 24000 x 1536 133 -> 128 us, 20 x 4608 x 2048 539 -> 522.
 template <typename T, bool SPLIT>
 constexpr StreamVariant step_variant(int kt, int rt) {
   const int x = kt == 2 ? 0 : (kt == 4 ? 1 : 2);
-  constexpr int f32[3][6] = {{4, 3, 3, 3, 2, 2}, {4, 3, 2, 2, 3, 2}, {2, 2, 3, 2, 2, 2}};
+  constexpr int f32[3][6] = {{4, 3, 3, 3, 2, 2}, {4, 3, 2, 2, 3, 2}, {2, 2, 3, 2, 2, 1}};
   constexpr int split[3][6] = {{4, 4, 3, 3, 2, 2}, {4, 4, 3, 3, 2, 3}, {2, 4, 3, 2, 2, 1}};
   constexpr int plain[3][6] = {{4, 4, 4, 4, 3, 3}, {4, 4, 4, 4, 3, 3}, {4, 4, 3, 2, 3, 3}};
   return {4, std::is_same<T, float>::value ? f32[x][rt - 1] : (SPLIT ? split[x][rt - 1] : plain[x][rt - 1]), 1};
@@ -263,7 +274,7 @@ struct StreamCall {
 
 template <typename T, int KT, int RT, bool SPLIT, typename Out>
 void stream_launch(const StreamCall<Out>& c) {
-  constexpr StreamVariant v = Out::kRowInLane ? step_variant<T, SPLIT>(KT, RT) : stream_variant<T, SPLIT>(KT, RT);
+  constexpr StreamVariant v = Out::kRowInLane ? step_variant<T, SPLIT>(KT, RT) : stream_variant<T, SPLIT>(KT, RT, Out::kNorm);
   // registers of the accumulators and the ring: two waves per SIMD where they fit
   constexpr int regs = 4 * RT * KT + v.depth * v.chunks * (RT * (int)sizeof(FPiece<T>) / 4 + KT * (SPLIT ? 8 : 4));
   constexpr int wpe = v.waves == 8 || regs <= (Out::kRowInLane ? 220 : 232) ? 2 : 1;
