@@ -20,6 +20,7 @@
 
 #include "chol_kernels.h"
 #include "f32_tiles.h"
+#include "step_tiling.h"
 #include "svdc_device.h"
 #include "svdc_internal.h"
 
@@ -1539,18 +1540,12 @@ void gemm_fty(const svdc_shape& s, int l, const T* F, const float* Y, float* Z, 
 // Scratch for partial Gram matrices: areas of float64 values.
 struct GramScratch { double* p[3]; int64_t doubles[3]; };
 
-// Row slices: as many as fit into one round of two workgroups per compute unit (three for l <= 64), of at least 64 rows
-// each and as the areas hold together.  One block of 3072 channels: 18432 rows, l = 128, 16 slices in the largest area 57 us, 40 in all three
-// 30; l = 64, the five Gram matrices of a fit of 4608 rows 43 -> 37 us.
 void gram(const float* A, double* G, GramScratch sc, int B, int rows, int l, hipStream_t st) {
   const int ntile = (l + 63) / 64, tiles = ntile * (ntile + 1) / 2;
   const int64_t ll = (int64_t)l * l;
-  int64_t want = std::max<int64_t>(1, (l <= 64 ? 3 : 2) * num_compute_units() / ((int64_t)tiles * B));
   const int64_t held[3] = {sc.doubles[0] / ll, sc.doubles[1] / ll, sc.doubles[2] / ll};
-  want = std::min<int64_t>(want, (held[0] + held[1] + held[2]) / B);
+  const int rows_per_slice = gram_slice_rows(rows, l, (int64_t)tiles * B, (held[0] + held[1] + held[2]) / B, num_compute_units());
   const GramParts parts{{sc.p[0], sc.p[1], sc.p[2]}, {held[0], held[0] + held[1]}};
-  int rows_per_slice = (int)(((rows + want - 1) / want + 15) / 16 * 16);
-  if (rows_per_slice < 64) rows_per_slice = 64;
   const int nslice = (rows + rows_per_slice - 1) / rows_per_slice;
   const dim3 grid(nslice, tiles, B);
   if (l <= 64) gram_f64_kernel<true><<<grid, 256, 0, st>>>(A, parts, rows, l, rows_per_slice);

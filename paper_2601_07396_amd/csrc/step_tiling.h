@@ -211,4 +211,22 @@ inline bool cached_step_takes_parts(int N, int64_t B, int D, int k, bool f32, in
   return parts < (f32 ? 0.91 : states > 1 ? 0.9 : 0.97) * plain;
 }
 
+// Rows of a slice, a multiple of 16 and at least 64, for the partial Gram matrices of a fit: `tiles` workgroups per slice (64 x 64 tiles of l x l, all blocks), room
+// for `most` slices.  l <= 64: three workgroups fit on a compute unit, and as many slices as fill one round of that are taken.  Above, the 344 registers of
+// the kernel allow one, and its start and end (the waves' sums, 32 KB of partial matrix) take it as long as 300 rows: the number of slices whose
+// rounds x (rows + 300) is least.  us with rounds of two per unit, and like this, l = 128: 3 x 5120 rows 25.1 -> 17.1, 3 x 9179 30.4 -> 24.9, 4 x 14777 56 -> 43,
+// 20 x 3000 46 -> 41; over 37 sizes (l = 16 to 192) timed at up to 17 numbers of slices the choice is within 1 % of the best on average, 7 % at worst.
+inline int gram_slice_rows(int rows, int l, int64_t tiles, int64_t most, int cus) {
+  auto slice = [&](int64_t n) { return std::max(64, (int)((rows + n - 1) / n + 15) / 16 * 16); };
+  if (l <= 64) return slice(std::min(most, std::max<int64_t>(1, 3 * cus / tiles)));
+  int64_t least = INT64_MAX;
+  int best = 0;
+  for (int64_t n = 1; n <= most && n <= (rows + 63) / 64; ++n) {
+    const int r = slice(n);
+    const int64_t cost = ((rows + r - 1) / r * tiles + cus - 1) / cus * (r + 300);
+    if (cost < least) least = cost, best = r;
+  }
+  return best;
+}
+
 }  // namespace svdc

@@ -12,8 +12,16 @@ PROGRAM = r"""
 // m ntile B kt2 parts elem cus, widest slab, narrow slab -> chunks tiles, the best of 16..6 at the widest slab and its fill
 // with an argument: rt kt2 N B cus -> whether the smoothing full step takes rt row tiles; with two: B N D kt2 parts cus ->
 // whether the full step takes tiles of 16 rows; with three: B N D k f32 smoothing / tensor added cus -> 10 x the row tiles of the
-// general full step in parts + whether the general cached step runs in parts; with four: B N D k f32 states cus -> the latter
+// general full step in parts + whether the general cached step runs in parts; with four: B N D k f32 states cus -> the latter; with five:
+// rows l tiles most cus -> rows of a slice of the Gram matrices
 int main(int argc, char**) {
+  if (argc > 5) {
+    int rows, l, cus;
+    long long tiles, most;
+    while (std::scanf("%d %d %lld %lld %d", &rows, &l, &tiles, &most, &cus) == 5)
+      std::printf("%d\n", svdc::gram_slice_rows(rows, l, tiles, most, cus));
+    return 0;
+  }
   if (argc > 4) {
     int N, D, k, f32, states, cus;
     long long B;
@@ -70,6 +78,8 @@ def tiling(tmp_path_factory):
     def run(calls, rule=()):
         text = "\n".join(" ".join(str(int(x)) for x in c) for c in calls)
         out = subprocess.run([exe, *rule], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout
+        if len(rule) == 5:
+            return [int(line) for line in out.split()]
         if len(rule) == 3:
             return [(int(line) // 10, bool(int(line) % 10)) for line in out.split()]
         if rule:
@@ -164,3 +174,14 @@ def test_general_cached_steps_of_several_states_in_parts(tiling):
     calls = [(1, 3517, 2056, 121, 0, 2), (1, 8101, 1288, 50, 0, 4), (4, 1292, 976, 128, 0, 1), (4, 1292, 976, 128, 0, 2),
              (1, 6001, 1036, 117, 1, 1), (1, 6001, 1036, 117, 1, 2)]
     assert tiling([c + (256,) for c in calls], rule=["cached", "steps", "of", "states"]) == [True, True, True, False, True, False]
+
+
+def test_slices_of_the_gram_matrices(tiling):
+    """Above 64 columns a compute unit holds one workgroup: 3 x 5120 rows take 54 slices (486 workgroups) 25 us and 27 slices (243) 17, 4 x
+    14777 rows 24 slices (288) 56 us and 21 (252) 43, 20 x 3000 8 slices 46 and 4 41.  One block takes all that the workspace holds.  Up to 64 three fit."""
+    calls = [(5120, 128, 9, 100), (9179, 128, 9, 53), (14777, 128, 12, 24), (3000, 128, 60, 40), (18432, 128, 3, 40), (4608, 64, 57, 40), (33, 70, 3, 16)]
+    assert tiling([c + (256,) for c in calls], rule=["slices", "of", "the", "Gram", "matrices"]) == [192, 336, 704, 752, 464, 368, 64]
+    many = [(rows, l, tiles, most) for rows in (1, 63, 65, 1000, 18432) for l in (1, 64, 65, 256) for tiles in (1, 10, 300, 70000)
+            for most in (1, 16, 400)]
+    for (rows, _, _, most), r in zip(many, tiling([c + (256,) for c in many], rule=["slices", "of", "the", "Gram", "matrices"])):
+        assert r >= 64 and r % 16 == 0 and -(-rows // r) <= most
