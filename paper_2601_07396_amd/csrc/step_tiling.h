@@ -105,6 +105,18 @@ inline int stream_rows(int ntile, int64_t B, int cus) {
   return best;
 }
 
+// Whether a bf16 projection of a fit, B blocks of ntile row tiles of 16 with kt tiles of 16 columns, has enough of them for the kernels that keep or share
+// Q (fit_mfma_kernels.hip) in the place of the streamed one: 16 per compute unit; up to width 64 calls of 8 to 16 take the streamed one 2 to 6 % less of a
+// whole fit.  At width 128 a unit holds two workgroups of 8 tiles, and one round of those pays from 12 tiles per unit on (3 x 9179 x 5120, plain: 77 us,
+// streamed 94; 20 x 3000 x 1024 1.5 % of the fit, 15 x 3837 x 768 6 %), with up to 1024 channels, where the streamed waves' sums weigh more, from 8 on (4 x
+// 14777 x 1024: 28 and 43 us); above 1024 channels 8 to 12 tiles are streamed 1 to 5 % faster, and calls just beyond the round 3 %.  260 fits of 4 to
+// 20 tiles per unit timed both ways.
+inline bool projection_is_large(int ntile, int64_t B, int kt, int D, int cus) {
+  const int64_t tiles = ntile * B;
+  if (tiles >= 16 * (int64_t)cus) return true;
+  return kt == 8 && tiles >= (D <= 1024 ? 8 : 12) * (int64_t)cus && (ntile + 7) / 8 * B <= 2 * (int64_t)cus;
+}
+
 // Whether a full step that has a buffer for its coefficients runs as two launches, the streamed projection (C and S) and a cached step's
 // kernel with -C for its state (R = F - C V^T), instead of one that keeps its rows on chip.  F is read twice, but neither launch
 // streams a basis past 16 or 32 rows at a time: 18432 x 3072 float32 at rank 128 235 -> 190 us, 57 x 4608 x 3072 bf16 at rank 128 2105 ->

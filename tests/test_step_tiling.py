@@ -13,8 +13,14 @@ PROGRAM = r"""
 // with an argument: rt kt2 N B cus -> whether the smoothing full step takes rt row tiles; with two: B N D kt2 parts cus ->
 // whether the full step takes tiles of 16 rows; with three: B N D k f32 smoothing / tensor added cus -> 10 x the row tiles of the
 // general full step in parts + whether the general cached step runs in parts; with four: B N D k f32 states cus -> the latter; with five:
-// rows l tiles most cus -> rows of a slice of the Gram matrices
+// rows l tiles most cus -> rows of a slice of the Gram matrices; with six: ntile B kt D cus -> whether a projection is large
 int main(int argc, char**) {
+  if (argc > 6) {
+    long long B;
+    int ntile, kt, D, cus;
+    while (std::scanf("%d %lld %d %d %d", &ntile, &B, &kt, &D, &cus) == 5) std::printf("%d\n", (int)svdc::projection_is_large(ntile, B, kt, D, cus));
+    return 0;
+  }
   if (argc > 5) {
     int rows, l, cus;
     long long tiles, most;
@@ -185,3 +191,13 @@ def test_slices_of_the_gram_matrices(tiling):
             for most in (1, 16, 400)]
     for (rows, _, _, most), r in zip(many, tiling([c + (256,) for c in many], rule=["slices", "of", "the", "Gram", "matrices"])):
         assert r >= 64 and r % 16 == 0 and -(-rows // r) <= most
+
+
+def test_wide_projections_that_do_not_stream(tiling):
+    """Measured (us of the plain product, kernel that shares Q and streamed): 4 x 14777 x 1024 width 128 28 / 43, 34 x 1264 x 512 17 / 26; whole fits: 15 x 3837 x
+    768 width 72 767 / 818, 4 x 15877 x 4096 1918 / 2049; 2 x 17284 x 2560 width 100 1164 / 1107, 44 x 1417 x 1920 width 80 1714 / 1662 (528 workgroups).
+    Width 64 streams up to 16 tiles per unit."""
+    calls = [((924, 4, 8, 1024), True), ((79, 34, 8, 512), True), ((240, 15, 8, 768), True), ((993, 4, 8, 4096), True), ((1081, 2, 8, 2560), False),
+             ((89, 44, 8, 1920), False), ((182, 20, 4, 2560), False), ((288, 57, 4, 3072), True), ((30, 57, 8, 1024), False), ((2047, 1, 8, 1024), False),
+             ((2048, 1, 8, 1024), True), ((3071, 1, 8, 1152), False), ((3072, 1, 8, 1152), True), ((4095, 1, 4, 512), False), ((4096, 1, 1, 512), True)]
+    assert tiling([c + (256,) for c, _ in calls], rule=["which", "projections", "of", "a", "fit", "stream"]) == [w for _, w in calls]
