@@ -832,20 +832,7 @@ int32_t full_step_launch(const svdc_shape& s, const void* F, const void* packed,
   return launch_status();
 }
 
-// Row tiles per workgroup tile (RT) and depth of the basis-operand ring (RD items) for a feature width of
-// CH * 128 channels, W = 1 (bf16) or 2 (float32) registers per channel pair and KT2 = padded rank / 32.
-// Every basis byte is read once per tile, so the tile should have as many rows as the 512 registers of a lane
-// allow: estimate = row pieces + accumulators + coefficient operands + ring + addressing and temporaries.
-constexpr int full_step_regs(int CH, int W, int KT2, int RT, int RD) {
-  return RT * CH * 4 * W + 2 * KT2 * RT * 4 + RT * KT2 * 12 + RD * 8 + (W == 2 ? RT * 8 + 70 : 0) + 46 +
-         (KT2 == 4 ? 40 : 0);
-}
-constexpr int tile_rows(int CH, int W, int KT2) {
-  if (CH == 24 && W == 1) return KT2 == 1 ? 3 : 2;   // measured at 3072 channels (FLUX, HunyuanVideo)
-  for (int rt = 4; rt > 1; --rt)   // 2 KT2 rt <= 16: the reduction buffer (4 KB per accumulator) stays within 64 KB of LDS
-    if (full_step_regs(CH, W, KT2, rt, 8) <= 450 && 2 * KT2 * rt <= 16) return rt;
-  return 1;
-}
+// Depth of the basis-operand ring (items) for tiles of tile_rows row tiles.
 constexpr int ring_depth(int CH, int W, int KT2) {
   const int rt = tile_rows(CH, W, KT2);
   int rd = KT2 == 1 ? 12 : (KT2 == 2 ? 16 : 8);   // measured best at 3072 channels
@@ -856,28 +843,6 @@ constexpr int ring_depth(int CH, int W, int KT2) {
   const int limit = W == 2 && KT2 == 4 && CH <= 24 ? 568 : 478;   // 4096 channels and up spill
   while (rd > 2 && full_step_regs(CH, W, KT2, rt, rd) > limit) rd -= 2;
   return rd;
-}
-
-// Whether a workgroup tile can have one more row tile in LDS (LT): bf16 at 3072 channels, rank 33..64.  Measured at the HunyuanVideo
-// shape: 4 % (split operands) to 8 % (single operands) less time per launch, 8-10 % on a single 18432-row block.  At rank <= 32 the
-// packed-basis stream is small enough that a fourth tile gains nothing, at rank 128 the LDS tile only replaces the second register tile at
-// equal speed.
-constexpr bool has_lds_tile(int CH, int W, int KT2) { return CH == 24 && W == 1 && KT2 == 2; }
-
-// Row tiles that a full step (without smoothing) takes at a time, the one in LDS included.
-// A taller tile can leave more of the last round of the persistent grid empty, so the choice of the LDS tile compares rounds x tile height x
-// cost per row (0.92 of the register-only tile's).  A launch with fewer tiles than compute units leaves units idle: such small
-// problems take tiles one step smaller (their packed-basis traffic does not matter at that size), and tiles of 16 rows where step_tiling.h allows.
-inline int full_step_rows(int CH, int W, int KT2, bool split, int N, int64_t B, int D) {
-  const int RT = tile_rows(CH, W, KT2);
-  const int64_t cus = num_compute_units();
-  auto tile_count = [&](int ra) { return (int64_t)((N + 16 * ra - 1) / (16 * ra)) * B; };
-  if (has_lds_tile(CH, W, KT2)) {
-    auto rounds = [&](int ra) { return (double)((tile_count(ra) + cus - 1) / cus); };
-    if (tile_count(RT + 1) >= cus && rounds(RT + 1) * (RT + 1) * 0.92 <= rounds(RT) * RT) return RT + 1;
-  }
-  if (RT > 2 && full_step_takes_single_tiles(tile_count(1), B * D * (32 * KT2) * 2 * (split ? 2 : 1), (int)cus)) return 1;
-  return RT > 1 && tile_count(RT) < cus ? RT - 1 : RT;
 }
 
 template <typename T, int CH, int KT2, bool SPLIT>
@@ -894,7 +859,7 @@ int32_t full_step_by_size(const svdc_shape& s, const void* F, const void* packed
     }
     return full_step_launch<T, CH, (RT > 1 ? RT - 1 : 1), KT2, SPLIT, RD, true>(s, F, packed, R, S, C, alpha, init, re, st);
   }
-  const int rows = full_step_rows(CH, W, KT2, SPLIT, s.N, s.B, s.D);
+  const int rows = full_step_rows(CH, W, KT2, SPLIT, s.N, s.B, num_compute_units());
   if constexpr (has_lds_tile(CH, W, KT2)) {
     constexpr int RDL = SPLIT ? 12 : 16;
     if (rows == RT + 1) return full_step_launch<T, CH, RT, KT2, SPLIT, RDL, false, 1>(s, F, packed, R, S, C, alpha, init, re, st);
@@ -964,19 +929,15 @@ int32_t forecast_dispatch(const svdc_shape& s, const CoefStates& cs, const void*
 int32_t launch_full_step_mfma(const svdc_shape& s, const void* F, const void* packed, void* R, float* S,
                               float* C, float alpha, int init, ResidualEma re, hipStream_t st) {
   const bool f32 = s.dtype == SVDC_F32, split = f32 || s.precision == SVDC_PRECISE;
-  if (C && !re.prev && full_step_may_take_two_launches(s.D, s.k, f32, split)) {
-    const int kt2 = padded_rank(s.k) / 32, rows = full_step_rows(s.D / 128, f32 ? 2 : 1, kt2, split, s.N, s.B, s.D), cus = num_compute_units();
-    const int64_t tiles = (int64_t)((s.N + 16 * rows - 1) / (16 * rows)) * s.B;
-    if (full_step_in_two_launches({rows, tiles}, s.N, s.B, s.D, s.k, f32, split, cus)) {
-      const int rt = stream_rows((s.N + 15) / 16, s.B, cus);
-      if (f32) step_project_stream_f32(2 * kt2, rt, s, F, packed, S, C, alpha, init, re.packed_state, st);
-      else step_project_stream_bf16(2 * kt2, rt, s, F, packed, S, C, alpha, init, re.packed_state, st);
-      CoefStates cs{};
-      cs.s[0] = C;
-      cs.w[0] = -1.f;
-      cs.m = 1;
-      return forecast_dispatch<false>(s, cs, packed, F, nullptr, R, st);
-    }
+  if (const int rt = C && !re.prev ? full_step_projection_rows(s.N, s.B, s.D, s.k, f32, split, num_compute_units()) : 0) {
+    const int kt = padded_rank(s.k) / 16;
+    if (f32) step_project_stream_f32(kt, rt, s, F, packed, S, C, alpha, init, re.packed_state, st);
+    else step_project_stream_bf16(kt, rt, s, F, packed, S, C, alpha, init, re.packed_state, st);
+    CoefStates cs{};
+    cs.s[0] = C;
+    cs.w[0] = -1.f;
+    cs.m = 1;
+    return forecast_dispatch<false>(s, cs, packed, F, nullptr, R, st);
   }
   // float32 features always use the full operand split (a single bf16 operand would cost 8 of their 24 bits)
   if (f32) return full_step_by_width<float, true>(s, F, packed, R, S, C, alpha, init, re, st);

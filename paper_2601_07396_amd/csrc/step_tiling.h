@@ -75,6 +75,41 @@ inline bool full_step_takes_single_tiles(int64_t tiles16, int64_t operand_bytes,
   return tiles16 <= cus && (operand_bytes <= (int64_t)3 << 20 || 8 * tiles16 <= 5 * (int64_t)cus);
 }
 
+// Row tiles per workgroup tile (RT) of the full step, with a basis-operand ring of RD items, for a feature width of
+// CH * 128 channels, W = 1 (bf16) or 2 (float32) registers per channel pair and KT2 = padded rank / 32.
+// Every basis byte is read once per tile, so the tile should have as many rows as the 512 registers of a lane
+// allow: estimate = row pieces + accumulators + coefficient operands + ring + addressing and temporaries.
+constexpr int full_step_regs(int CH, int W, int KT2, int RT, int RD) {
+  return RT * CH * 4 * W + 2 * KT2 * RT * 4 + RT * KT2 * 12 + RD * 8 + (W == 2 ? RT * 8 + 70 : 0) + 46 +
+         (KT2 == 4 ? 40 : 0);
+}
+constexpr int tile_rows(int CH, int W, int KT2) {
+  if (CH == 24 && W == 1) return KT2 == 1 ? 3 : 2;   // measured at 3072 channels (FLUX, HunyuanVideo)
+  for (int rt = 4; rt > 1; --rt)   // 2 KT2 rt <= 16: the reduction buffer (4 KB per accumulator) stays within 64 KB of LDS
+    if (full_step_regs(CH, W, KT2, rt, 8) <= 450 && 2 * KT2 * rt <= 16) return rt;
+  return 1;
+}
+// Whether a workgroup tile can have one more row tile in LDS (LT): bf16 at 3072 channels, rank 33..64.  Measured at the HunyuanVideo
+// shape: 4 % (split operands) to 8 % (single operands) less time per launch, 8-10 % on a single 18432-row block.  At rank <= 32 the
+// packed-basis stream is small enough that a fourth tile gains nothing, at rank 128 the LDS tile only replaces the second register tile at
+// equal speed.
+constexpr bool has_lds_tile(int CH, int W, int KT2) { return CH == 24 && W == 1 && KT2 == 2; }
+
+// Row tiles that a full step (without smoothing) takes at a time, the one in LDS included.
+// A taller tile can leave more of the last round of the persistent grid empty, so the choice of the LDS tile compares rounds x tile height x
+// cost per row (0.92 of the register-only tile's).  A launch with fewer tiles than compute units leaves units idle: such small
+// problems take tiles one step smaller (their packed-basis traffic does not matter at that size), and tiles of 16 rows where the rule above allows.
+inline int full_step_rows(int CH, int W, int KT2, bool split, int N, int64_t B, int cus) {
+  const int RT = tile_rows(CH, W, KT2);
+  auto tile_count = [&](int ra) { return (int64_t)((N + 16 * ra - 1) / (16 * ra)) * B; };
+  if (has_lds_tile(CH, W, KT2)) {
+    auto rounds = [&](int ra) { return (double)((tile_count(ra) + cus - 1) / cus); };
+    if (tile_count(RT + 1) >= cus && rounds(RT + 1) * (RT + 1) * 0.92 <= rounds(RT) * RT) return RT + 1;
+  }
+  if (RT > 2 && full_step_takes_single_tiles(tile_count(1), B * CH * 128 * (32 * KT2) * 2 * (split ? 2 : 1), cus)) return 1;
+  return RT > 1 && tile_count(RT) < cus ? RT - 1 : RT;
+}
+
 // Whether the full step that smooths the residual takes rt row tiles of 16 at a time, for which the previous residual
 // still fits beside them, or one less: the persistent grid takes rounds x (rt + x), x = the basis stream in row tiles.
 // Timed at 250 sampled calls (bf16, the widths and ranks where there is a choice: 256 to 1152 channels at rank 32, 256 at
@@ -119,13 +154,13 @@ inline bool projection_is_large(int ntile, int64_t B, int kt, int D, int cus) {
 
 // Whether a full step that has a buffer for its coefficients runs as two launches, the streamed projection (C and S) and a cached step's
 // kernel with -C for its state (R = F - C V^T), instead of one that keeps its rows on chip.  F is read twice, but neither launch
-// streams a basis past 16 or 32 rows at a time: 18432 x 3072 float32 at rank 128 235 -> 190 us, 57 x 4608 x 3072 bf16 at rank 128 2105 ->
-// 1751, 1 x 4608 at rank 64 45 -> 37 and rank 128 75 -> 51, 2 x 14626 x 4096 float32 at rank 128 781 -> 400 us; but 57 x 4608 x 3072 bf16 at rank
+// streams a basis past 16 or 32 rows at a time: 18432 x 3072 float32 at rank 128 235 -> 190 us, 57 x 4608 x 3072 bf16 at rank 128 2117 ->
+// 1645, 1 x 4608 at rank 64 45 -> 37 and rank 128 75 -> 51, 2 x 14626 x 4096 float32 at rank 128 781 -> 400 us; but 57 x 4608 x 3072 bf16 at rank
 // 32 871 -> 1020, rank 64 1174 -> 1223.  Both sides are estimated in us for 256 compute units: one launch a + d rounds (b rows + c), two launches
 // a + d (b + c rounds (rows + 1.25) + e tiles per unit), d = D / 1024, fitted to 1423 calls timed both ways (1 to 57 blocks, 200 to 24000
 // rows, ranks 33 to 128, the widths of the kernel), with margins because the estimates meet the time within 6 to 18 %; calls of less than a tile
-// of 16 rows per compute unit scatter more.  Rank 65 to 128: float32 rows take 0.77 of the time on average, bf16 ones 0.87; 33 to
-// 64: 0.92 and 0.97; one call in 100 gets more than 2 % slower (16 % at most).  float32 rows of 5120 channels go this way at any rank, of 4096
+// of 16 rows per compute unit scatter more.  Of 769 other calls that go this way, timed both ways with inputs in turn, each takes 0.31 to 1.00
+// of the single launch's time, 0.69 on average.  float32 rows of 5120 channels go this way at any rank, of 4096
 // from rank 65 on or with a tile per compute unit: the single launch spills registers there (118 calls, 1.04 to 3.1 times the
 // time).  Single operands (SVDC_FAST) do from rank 65 and 1536 channels on.
 struct OneLaunch {
@@ -153,7 +188,15 @@ inline bool full_step_in_two_launches(OneLaunch one, int N, int64_t B, int D, in
   if (D % 512 != 0) q.e *= 1.15;
   const double single = p.a + d * (double)((one.tiles + cus - 1) / cus) * (p.b * one.rows + p.c);
   const double twice = q.a + d * (q.b + q.c * (double)stream_rounds(rt, ntile, B, cus) * (rt + kStreamOperands) + q.e * ((double)ntile * B / cus));
-  return twice < (rt == 1 ? 0.8 : (f32 ? 0.97 : 0.94)) * single;
+  return twice < (rt == 1 ? 0.8 : (f32 || k > 64 ? 0.97 : 0.94)) * single;
+}
+
+// Row tiles of the projection of a full step with a buffer for C that takes two launches, 0 where it takes one.
+inline int full_step_projection_rows(int N, int64_t B, int D, int k, bool f32, bool split, int cus) {
+  if (!full_step_may_take_two_launches(D, k, f32, split)) return 0;
+  const int rows = full_step_rows(D / 128, f32 ? 2 : 1, k <= 32 ? 1 : (k <= 64 ? 2 : 4), split, N, B, cus);
+  const int64_t tiles = (int64_t)((N + 16 * rows - 1) / (16 * rows)) * B;
+  return full_step_in_two_launches({rows, tiles}, N, B, D, k, f32, split, cus) ? stream_rows((N + 15) / 16, B, cus) : 0;
 }
 
 // The general steps (general_kernels.hip) run on the float32 matrix cores, 16 rows per workgroup, or on the bf16 ones with

@@ -4,6 +4,8 @@ import subprocess
 
 import pytest
 
+from util import TWO_LAUNCHES
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 PROGRAM = r"""
@@ -13,8 +15,16 @@ PROGRAM = r"""
 // with an argument: rt kt2 N B cus -> whether the smoothing full step takes rt row tiles; with two: B N D kt2 parts cus ->
 // whether the full step takes tiles of 16 rows; with three: B N D k f32 smoothing / tensor added cus -> 10 x the row tiles of the
 // general full step in parts + whether the general cached step runs in parts; with four: B N D k f32 states cus -> the latter; with five:
-// rows l tiles most cus -> rows of a slice of the Gram matrices; with six: ntile B kt D cus -> whether a projection is large
+// rows l tiles most cus -> rows of a slice of the Gram matrices; with six: ntile B kt D cus -> whether a projection is large; with
+// seven: B N D k f32 split cus -> row tiles of the projection of a full step that takes two launches, or 0
 int main(int argc, char**) {
+  if (argc > 7) {
+    long long B;
+    int N, D, k, f32, split, cus;
+    while (std::scanf("%lld %d %d %d %d %d %d", &B, &N, &D, &k, &f32, &split, &cus) == 7)
+      std::printf("%d\n", svdc::full_step_projection_rows(N, B, D, k, f32, split, cus));
+    return 0;
+  }
   if (argc > 6) {
     long long B;
     int ntile, kt, D, cus;
@@ -84,7 +94,7 @@ def tiling(tmp_path_factory):
     def run(calls, rule=()):
         text = "\n".join(" ".join(str(int(x)) for x in c) for c in calls)
         out = subprocess.run([exe, *rule], input=text, stdout=subprocess.PIPE, text=True, check=True).stdout
-        if len(rule) == 5:
+        if len(rule) in (5, 7):
             return [int(line) for line in out.split()]
         if len(rule) == 3:
             return [(int(line) // 10, bool(int(line) % 10)) for line in out.split()]
@@ -201,3 +211,20 @@ def test_wide_projections_that_do_not_stream(tiling):
              ((89, 44, 8, 1920), False), ((182, 20, 4, 2560), False), ((288, 57, 4, 3072), True), ((30, 57, 8, 1024), False), ((2047, 1, 8, 1024), False),
              ((2048, 1, 8, 1024), True), ((3071, 1, 8, 1152), False), ((3072, 1, 8, 1152), True), ((4095, 1, 4, 512), False), ((4096, 1, 1, 512), True)]
     assert tiling([c + (256,) for c, _ in calls], rule=["which", "projections", "of", "a", "fit", "stream"]) == [w for _, w in calls]
+
+
+def test_full_steps_in_two_launches(tiling):
+    """The calls of the GPU test of the two launches take them, at every height of the projection's tiles, and so do 18432 x 3072 float32 at rank 128 (235 us in one
+    launch, 190 in two) and 57 x 4608 x 3072 bf16 (2117 / 1645); not at rank 64 (1174 / 1223) and 32 (871 / 1020), nor in single operands at rank 64."""
+    rule = ["which", "full", "steps", "take", "two", "launches", "instead"]
+    calls = [(B, N, D, k, dtype == "f32", not fast, 256) for dtype, B, N, D, k, fast, _, _ in TWO_LAUNCHES]
+    assert tiling(calls, rule=rule) == [c[7] for c in TWO_LAUNCHES] and {c[7] for c in TWO_LAUNCHES} == {1, 2, 3, 4, 5, 6}
+    calls = [(1, 18432, 3072, 128, 1, 1), (57, 4608, 3072, 128, 0, 1), (57, 4608, 3072, 64, 0, 1), (57, 4608, 3072, 32, 0, 1), (2, 119056, 3072, 64, 0, 0),
+             (1, 300, 256, 128, 1, 1), (4, 2048, 4096, 32, 1, 1)]
+    assert [r > 0 for r in tiling([c + (256,) for c in calls], rule=rule)] == [True, True, False, False, False, False, False]
+
+
+@pytest.mark.parametrize("ntile,B,rows", [(1, 1, 1), (256, 1, 1), (257, 1, 2), (288, 1, 2), (1000, 1, 4), (1152, 1, 5), (288, 20, 6), (288, 4, 5)])
+def test_heights_of_the_streamed_projection(tiling, ntile, B, rows):
+    """Rounds x (rows + 1.25) is least: 1152 tiles are 231 workgroups of 5 (one round); of 6 192, of 4 288, two rounds."""
+    assert tiling([(B, 16 * ntile, 4096, 128, 1, 1, 256)], rule=["which", "full", "steps", "take", "two", "launches", "instead"]) == [rows]

@@ -10,6 +10,14 @@ import torch
 # 1e-4 for float32 storage, 2e-2 for bf16 storage with fp32 accumulation.
 TOL = {"f32": 1e-4, "bf16": 2e-2}
 
+# Full steps that take two launches with a buffer for C (256 compute units): storage, B, N, D, k, single operands, padding of the rows, and the
+# row tiles of 16 that a workgroup of their projection takes.
+TWO_LAUNCHES = [
+    ("f32", 1, 37, 5120, 8, 0, 0, 1), ("f32", 3, 333, 4096, 40, 0, 8, 1), ("f32", 1, 150, 3072, 128, 0, 0, 1), ("bf16", 1, 101, 3072, 100, 0, 64, 1),
+    ("f32", 1, 6131, 1152, 68, 0, 0, 2), ("bf16", 4, 1031, 2560, 96, 0, 0, 2), ("bf16", 1, 4609, 3072, 64, 0, 0, 2), ("f32", 2, 5001, 1920, 128, 0, 0, 3),
+    ("f32", 7, 2299, 2048, 100, 0, 0, 4), ("bf16", 4, 4199, 4096, 68, 0, 0, 5), ("bf16", 3, 6001, 1536, 128, 0, 8, 5), ("f32", 3, 7297, 512, 128, 0, 0, 6),
+    ("bf16", 5, 5003, 2560, 120, 1, 0, 4)]
+
 
 def to_np(t: torch.Tensor) -> np.ndarray:
     """Exact float64 copy of a float32 / bfloat16 tensor."""
