@@ -177,7 +177,7 @@ int32_t svdcache_fit_basis_static(const svdc_shape* shape, const svdc_fit_params
 int32_t svdcache_pack_basis(const svdc_shape* shape, const float* V, void* packed,
                             size_t packed_bytes, void* stream);
 
-/* Full-compute step (Eq. 8-11), one pass over F:
+/* Full-compute step (Eq. 8-11):
  *   C = F V                       coefficients in the cached basis (sigma of Eq. 8-9 cancels)
  *   R = F - C V^T                 residual (Eq. 10)
  *   S = C                         if init != 0 (first full step)
@@ -187,8 +187,15 @@ int32_t svdcache_pack_basis(const svdc_shape* shape, const float* V, void* packe
  *   packed  in      packed copy of the same V, or NULL (general kernel)
  *   R       out     [B,N,D] dtype; may be the same buffer as F (in place)
  *   S       in/out  [B,N,k] float32 (not read when init != 0)
- *   C       out     [B,N,k] float32; may be NULL
- *   alpha   in (0, 1] */
+ *   C       out     [B,N,k] float32; may be NULL; must not overlap F, R, V or packed
+ *   alpha   in (0, 1]
+ * With packed given and C NULL the step is one launch and one pass over F.  With a C it may be two launches on `stream`, where streaming the
+ * basis costs more than a second read of F (above all at ranks 65 to 128, and for float32 rows of 4096 channels and more): one that
+ * forms C and S, and one that reads C back to form R.  C then belongs to the call until it has completed on the stream: calls in
+ * flight on different streams must not share one, not even if nobody reads it (pass NULL for coefficients that are not wanted).  R, S and
+ * C have the same bits either way, except in rows of F that hold an infinity or a NaN: all of R there is not finite (an
+ * infinity in one form may be a NaN in the other); other rows are not affected by them.  The same holds for svdcache_full_step_packed, and for
+ * svdcache_full_step_residual_ema where it does not smooth the residual. */
 int32_t svdcache_full_step(const svdc_shape* shape, const void* F, const float* V,
                            const void* packed, void* R, float* S, float* C,
                            float alpha, int32_t init, void* stream);

@@ -289,6 +289,8 @@ def svdcache_pack_basis(shape: Shape, V, packed):
 
 
 def svdcache_full_step(shape: Shape, F, V, packed, R, S, Cout, alpha: float, init: bool):
+    """C = F V, R = F - C V^T and the update of S.  Cout (or None): the step may form R from it in a second launch, so steps in
+    flight on different streams need one each, even where nobody reads it; it must not overlap the other tensors."""
     if _fast_call("full_step", shape, F, V, packed, R, S, Cout, alpha, init):
         return
     _check_step_args(shape, V, packed, {"S": S, "C": Cout}, {"F": F, "R": R})

@@ -1026,6 +1026,40 @@ def test_full_step_in_two_launches(dtype, B, N, D, k, fast, pad):
     assert_close(to_np(C[b, -40:]), Cr, "bf16" if fast else "f32", f"C[{b}]", fast=bool(fast))
 
 
+@pytest.mark.parametrize("dtype,B,N,D,k,fast", [(torch_dtype(c[0]), *c[1:6]) for c in TWO_LAUNCHES if c[0:4] in
+                                                (("f32", 1, 6131, 1152), ("bf16", 1, 4609, 3072), ("bf16", 5, 5003, 2560))])
+def test_rows_that_are_not_finite_stay_by_themselves_in_both_forms_of_the_full_step(dtype, B, N, D, k, fast):
+    """An infinity or a NaN in a row of F: nothing of R is finite in that row, with a buffer for C (two launches) and without (one), C and S are the
+    same in both, and all other rows keep the bits that they have without it.  C may also be the buffer S."""
+    g = torch.Generator(device=DEV).manual_seed(N + k)
+    F = torch.randn(B, N, D, generator=g, device=DEV).to(dtype)
+    V = torch.linalg.qr(torch.randn(B, D, k, generator=g, device=DEV))[0].contiguous()
+    S0 = torch.randn(B, N, k, generator=g, device=DEV)
+    shape = pkg.make_shape(F, k, pkg.SVDC_FAST if fast else pkg.SVDC_PRECISE)
+    pk = pkg.pack_basis(shape, V)
+
+    def step(F, with_C):
+        R, S, C = torch.empty_like(F), S0.clone(), torch.empty_like(S0) if with_C else None
+        pkg.svdcache_full_step(shape, F, V, pk, R, S, C, 0.3, False)
+        return R, S, C
+    clean, S_clean, C_clean = step(F, True)
+    alone = S0.clone()
+    pkg.svdcache_full_step(shape, F, V, pk, torch.empty_like(F), alone, alone, 0.3, False)
+    assert torch.equal(alone, C_clean)
+    bad = [(0, 0), (0, 17), (B - 1, N // 2), (B - 1, N - 1)]
+    for i, (b, n) in enumerate(bad):
+        F[b, n, (331 * i) % D] = (float("inf"), float("nan"), float("-inf"), float("inf"))[i]
+    R1, S1, _ = step(F, False)
+    R2, S2, C2 = step(F, True)
+    rows = torch.zeros(B, N, dtype=torch.bool, device=DEV)
+    for b, n in bad:
+        rows[b, n] = True
+    for R in (R1, R2):
+        assert not torch.isfinite(R[rows].float()).any() and torch.equal(R[~rows], clean[~rows])
+    assert torch.equal(S1.nan_to_num(7.0), S2.nan_to_num(7.0)) and torch.equal(S2[~rows], S_clean[~rows])
+    assert not torch.isfinite(C2[rows]).any() and torch.equal(C2[~rows], C_clean[~rows])
+
+
 @pytest.mark.parametrize("dtype,B,N,D,k,fast,pad", [
     (torch.float32, 1, 6150, 3072, 32, 0, 0), (torch.float32, 3, 2777, 1920, 20, 0, 8), (torch.float32, 2, 13001, 256, 8, 0, 0),      # slabs of 6, 5, 2
     (torch.float32, 1, 4403, 3072, 64, 0, 0), (torch.float32, 2, 3333, 2048, 40, 0, 64),                                       # 3, 4
