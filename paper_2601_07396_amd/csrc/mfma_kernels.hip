@@ -673,9 +673,10 @@ namespace {
 // rank 112: 12.3 and 13.9 us), one or several states of rank <= 32 in float32 up to 15 % (12 x 691 x 512: 9.5 and 10.9 us), in bf16
 // without an added tensor 3 to 7 %; all others 1 to 40 % faster (370 sampled calls).
 enum class Share { kNever, kLongCalls, kAlways };
-template <typename T, int KT2, bool EXT, bool PS, bool HX>
+template <typename T, int NCW, int KT2, bool EXT, bool PS, bool HX>
 constexpr Share forecast_share() {
   constexpr bool kF32 = sizeof(T) == 4;
+  if (NCW == 12 && KT2 == 1 && HX) return Share::kNever;   // adding_takes_wide_slabs
   if (KT2 == 1 && !EXT) return kF32 ? Share::kLongCalls : Share::kNever;
   if (PS || (KT2 == 1 && (kF32 || !HX))) return Share::kLongCalls;
   return Share::kAlways;
@@ -732,7 +733,7 @@ int32_t forecast_launch(const svdc_shape& s, const CoefStates& cs, const void* p
     constexpr bool HX = decltype(adds)::value;
     // the kind that may take slabs of 12 unshared (forecast_by_width), and the narrow ones chosen in their place
     constexpr bool kWide = PS && !SPLIT && KT2 == 2;
-    constexpr Share share = kWide && NCW == 12 ? Share::kNever : forecast_share<T, KT2, EXT, PS, HX>();
+    constexpr Share share = kWide && NCW == 12 ? Share::kNever : forecast_share<T, NCW, KT2, EXT, PS, HX>();
     auto go = [&](auto shared) {
       constexpr bool SHARED = decltype(shared)::value;
       constexpr ForecastVariant v = forecast_variant<T, KT2, SPLIT, EXT, HX, MSX>(NCW, SHARED, NARROW);
@@ -750,19 +751,13 @@ int32_t forecast_launch(const svdc_shape& s, const CoefStates& cs, const void* p
   using Two = std::integral_constant<int, 2>;
   using Most = std::integral_constant<int, kMaxStates>;
   if constexpr (EXT) {
-    // registers for two or four states, with or without the added tensor (forecast_by_width gives the widest slabs of rank <= 32 no
-    // added tensor)
+    // registers for two or four states, with or without the added tensor
     auto by_states = [&](auto adds) {
       if (cs.m <= 2) launch(Two{}, adds);
       else launch(Most{}, adds);
     };
-    if constexpr (KT2 > 1 || NCW <= 6) {
-      if (X) {
-        by_states(std::true_type{});
-        return launch_status();
-      }
-    }
-    by_states(std::false_type{});
+    if (X) by_states(std::true_type{});
+    else by_states(std::false_type{});
   } else {
     launch(Most{}, std::false_type{});
   }
@@ -799,7 +794,8 @@ int32_t forecast_by_width(const svdc_shape& s, const CoefStates& cs, const void*
     if constexpr (!EXT) {
       return call.template first<12, 10, 9, 8, 6, 5, 4, 3, 2, 1>();
     } else {
-      if (X) return call.template first<6, 4, 3, 2, 1>();
+      const CachedCall tiles{s.D / 128, (s.N + 15) / 16, s.B, KT2, 2, (int)sizeof(T), call.cus};
+      if (X && !adding_takes_wide_slabs(tiles, cs.m)) return call.template first<6, 4, 3, 2, 1>();
       return call.template first<12, 6, 4, 3, 2, 1>();
     }
   } else if constexpr (KT2 == 1) {

@@ -65,6 +65,20 @@ inline CachedTiling cached_tiling(const CachedCall& call, int chunks, int narrow
   return best;
 }
 
+// Whether a cached step that adds a tensor (bf16, rank <= 32) takes slabs of 12 chunks, one workgroup per compute unit whose waves each load all
+// coefficients, instead of slabs of 6 that share them, two workgroups per unit.  Wide ones are 2 to 4 % faster in long calls of well-filled rounds (from 40
+// row tiles of 1536 channels per unit: 57 x 4608 x 3072 rank 32, two states 945 and 969 us), and above two states, where a third or fifth round of the
+// others is a half-empty one (4 x 6865 x 3072, four states: 1.11 of the wide ones' time; 10 blocks of 1607 rows 1.04); elsewhere up to 17 % slower (19 x
+// 4608 x 3072: 327 and 323 us).  Over 475 sampled calls of one and more rounds this takes 0.2 % longer on average than the better of the two, slabs of 6
+// alone 0.8 %, of 12 alone 2.7 %.
+inline bool adding_takes_wide_slabs(const CachedCall& call, int states) {
+  if (call.m % 12 != 0) return false;
+  const CachedTiling wide = cached_tiling(call, 12, 0), half = cached_tiling(call, 6, 0);
+  if (call.m / 12 * call.ntile * call.B >= 40 * (int64_t)call.cus && call.fill(wide) >= 0.96) return true;
+  const int64_t rounds = (call.workgroups(half) + call.cus - 1) / call.cus;
+  return states > 2 && call.fill(wide) >= 0.7 && (rounds == 3 || rounds == 5);
+}
+
 // Whether the full step of a small call takes tiles of 16 rows: where they fit into one round of the machine (a second round
 // costs more than a taller tile: 4608 x 3072 rows, rank 32: 24 us with tall tiles, 30 us), unless most of the machine then
 // streams operands that no L2 (4 MB) holds: each tile reads all basis operands of its block twice.  Against tiles

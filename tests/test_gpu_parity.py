@@ -1118,6 +1118,12 @@ def test_cached_steps_share_their_coefficients(dtype, B, N, D, k, fast, pad):
             assert worst <= 1.0, (w, x, b, worst)
 
 
+@pytest.mark.parametrize("B,N,D,k,pad", [(1, 85001, 3072, 24, 0), (8, 5206, 1536, 8, 8)])
+def test_cached_steps_that_add_a_tensor_in_wide_slabs(B, N, D, k, pad):
+    """Two states in a long call, three in three rounds of the narrower slabs: slabs of 12 chunks whose waves share nothing."""
+    test_cached_steps_share_their_coefficients(torch.bfloat16, B, N, D, k, 0, pad)
+
+
 @pytest.mark.parametrize("B,N,k", [(4, 4090, 32), (4, 3060, 64), (2, 4090, 128)])
 def test_full_step_tiles_with_a_row_tile_in_lds(B, N, k):
     """3072 channels and one round of 256 or more workgroup tiles, each block ending in a partly filled tile.  At

@@ -16,8 +16,16 @@ PROGRAM = r"""
 // whether the full step takes tiles of 16 rows; with three: B N D k f32 smoothing / tensor added cus -> 10 x the row tiles of the
 // general full step in parts + whether the general cached step runs in parts; with four: B N D k f32 states cus -> the latter; with five:
 // rows l tiles most cus -> rows of a slice of the Gram matrices; with six: ntile B kt D cus -> whether a projection is large; with
-// seven: B N D k f32 split cus -> row tiles of the projection of a full step that takes two launches, or 0
+// seven: B N D k f32 split cus -> row tiles of the projection of a full step that takes two launches, or 0; with eight: B N D states cus -> whether a
+// cached step that adds a tensor takes slabs of 12 chunks
 int main(int argc, char**) {
+  if (argc > 8) {
+    long long B;
+    int N, D, states, cus;
+    while (std::scanf("%lld %d %d %d %d", &B, &N, &D, &states, &cus) == 5)
+      std::printf("%d\n", (int)svdc::adding_takes_wide_slabs({D / 128, (N + 15) / 16, B, 1, 2, 2, cus}, states));
+    return 0;
+  }
   if (argc > 7) {
     long long B;
     int N, D, k, f32, split, cus;
@@ -228,3 +236,12 @@ def test_full_steps_in_two_launches(tiling):
 def test_heights_of_the_streamed_projection(tiling, ntile, B, rows):
     """Rounds x (rows + 1.25) is least: 1152 tiles are 231 workgroups of 5 (one round); of 6 192, of 4 288, two rounds."""
     assert tiling([(B, 16 * ntile, 4096, 128, 1, 1, 256)], rule=["which", "full", "steps", "take", "two", "launches", "instead"]) == [rows]
+
+
+def test_cached_steps_that_add_a_tensor_in_wide_slabs(tiling):
+    """Measured (us with slabs of 12 chunks, with 6 shared): 57 x 4608 x 3072 rank 32 two states 945 / 969, 19 x 4608 x 3072 327 / 323,
+    6 x 4608 x 3072 108 / 104, four states in 3 rounds of the narrower slabs 4 x 6865 x 3072 1 / 1.11 of its time.  Not for widths that 12 chunks do not divide."""
+    calls = [((57, 4608, 3072, 2), True), ((57, 4608, 3072, 4), True), ((19, 4608, 3072, 2), False), ((6, 4608, 3072, 2), False),
+             ((4, 6865, 3072, 4), True), ((4, 6865, 3072, 2), False), ((1, 85001, 3072, 2), True), ((8, 5206, 1536, 3), True), ((1, 300, 3072, 4), False), ((57, 4608, 2048, 2), False), ((57, 4608, 5120, 4), False)]
+    rule = ["which", "cached", "steps", "that", "add", "take", "wide", "slabs"]
+    assert tiling([c + (256,) for c, _ in calls], rule=rule) == [w for _, w in calls]
