@@ -673,10 +673,13 @@ namespace {
 // rank 112: 12.3 and 13.9 us), one or several states of rank <= 32 in float32 up to 15 % (12 x 691 x 512: 9.5 and 10.9 us), in bf16
 // without an added tensor 3 to 7 %; all others 1 to 40 % faster (370 sampled calls).
 enum class Share { kNever, kLongCalls, kAlways };
-template <typename T, int NCW, int KT2, bool EXT, bool PS, bool HX>
+template <typename T, int NCW, int KT2, bool EXT, bool PS, bool HX, int MSX>
 constexpr Share forecast_share() {
   constexpr bool kF32 = sizeof(T) == 4;
   if (NCW == 12 && KT2 == 1 && HX) return Share::kNever;   // adding_takes_wide_slabs
+  // three and four states and a tensor in float32, slabs of 6: the barriers cost 2 to 4 % in calls of every length and rank (130 sampled calls;
+  // 10 x 11383 x 3072 rank 8 760 -> 793 us), narrower slabs gain as the other kinds do
+  if (kF32 && NCW == 6 && KT2 == 1 && HX && MSX > 2) return Share::kNever;
   if (KT2 == 1 && !EXT) return kF32 ? Share::kLongCalls : Share::kNever;
   if (PS || (KT2 == 1 && (kF32 || !HX))) return Share::kLongCalls;
   return Share::kAlways;
@@ -733,7 +736,8 @@ int32_t forecast_launch(const svdc_shape& s, const CoefStates& cs, const void* p
     constexpr bool HX = decltype(adds)::value;
     // the kind that may take slabs of 12 unshared (forecast_by_width), and the narrow ones chosen in their place
     constexpr bool kWide = PS && !SPLIT && KT2 == 2;
-    constexpr Share share = kWide && NCW == 12 ? Share::kNever : forecast_share<T, NCW, KT2, EXT, PS, HX>();
+    constexpr Share share = kWide && NCW == 12 ? Share::kNever : forecast_share<T, NCW, KT2, EXT, PS, HX, MSX>();
+    constexpr bool kTwoPlain = EXT && KT2 == 1 && sizeof(T) == 2 && !HX && MSX <= 2;
     auto go = [&](auto shared) {
       constexpr bool SHARED = decltype(shared)::value;
       constexpr ForecastVariant v = forecast_variant<T, KT2, SPLIT, EXT, HX, MSX>(NCW, SHARED, NARROW);
@@ -741,7 +745,8 @@ int32_t forecast_launch(const svdc_shape& s, const CoefStates& cs, const void* p
           cs, (const uint16_t*)packed, (const T*)R, (const T*)X, (T*)Fhat, s.N, s.D, s.k, s.ldf, s.block_stride, NS, gpb, tpg);
     };
     if constexpr (share != Share::kNever) {
-      if (share == Share::kAlways || (grid > cus && !(kWide && NARROW && s.D % 1536 == 0))) {
+      if (share == Share::kAlways ||
+          (grid > cus && !(kWide && NARROW && s.D % 1536 == 0) && !(kTwoPlain && two_states_stay_unshared(ntile, s.B, s.D, s.k, cus)))) {
         go(std::true_type{});
         return;
       }

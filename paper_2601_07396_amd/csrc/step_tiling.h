@@ -79,6 +79,13 @@ inline bool adding_takes_wide_slabs(const CachedCall& call, int states) {
   return states > 2 && call.fill(wide) >= 0.7 && (rounds == 3 || rounds == 5);
 }
 
+// Whether the waves of a cached step of one or two states (bf16, nothing added) each load all coefficients in a long call: up to rank 16 those are one load
+// per state and tile, and with rows of a power of two of channels the waves that a barrier keeps in step lose more than the loads cost (2 to 6 % from 25 row
+// tiles of 1536 channels per unit, 9 sampled calls; 4 x 12079 x 4096 rank 8 165 -> 176 us); shorter calls, other widths and higher ranks gain 2 to 10 %.
+inline bool two_states_stay_unshared(int ntile, int64_t B, int D, int k, int cus) {
+  return k <= 16 && (D & (D - 1)) == 0 && ntile * B * D >= (int64_t)25 * 1536 * cus;
+}
+
 // Whether the full step of a small call takes tiles of 16 rows: where they fit into one round of the machine (a second round
 // costs more than a taller tile: 4608 x 3072 rows, rank 32: 24 us with tall tiles, 30 us), unless most of the machine then
 // streams operands that no L2 (4 MB) holds: each tile reads all basis operands of its block twice.  Against tiles

@@ -1124,6 +1124,12 @@ def test_cached_steps_that_add_a_tensor_in_wide_slabs(B, N, D, k, pad):
     test_cached_steps_share_their_coefficients(torch.bfloat16, B, N, D, k, 0, pad)
 
 
+@pytest.mark.parametrize("B,N,D,k", [(1, 308009, 512, 4), (2, 38407, 2048, 16)])
+def test_long_cached_steps_of_two_states_that_do_not_share(B, N, D, k):
+    """Rows of a power of two of channels, rank <= 16."""
+    test_cached_steps_share_their_coefficients(torch.bfloat16, B, N, D, k, 0, 0)
+
+
 @pytest.mark.parametrize("B,N,k", [(4, 4090, 32), (4, 3060, 64), (2, 4090, 128)])
 def test_full_step_tiles_with_a_row_tile_in_lds(B, N, k):
     """3072 channels and one round of 256 or more workgroup tiles, each block ending in a partly filled tile.  At

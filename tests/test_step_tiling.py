@@ -17,8 +17,14 @@ PROGRAM = r"""
 // general full step in parts + whether the general cached step runs in parts; with four: B N D k f32 states cus -> the latter; with five:
 // rows l tiles most cus -> rows of a slice of the Gram matrices; with six: ntile B kt D cus -> whether a projection is large; with
 // seven: B N D k f32 split cus -> row tiles of the projection of a full step that takes two launches, or 0; with eight: B N D states cus -> whether a
-// cached step that adds a tensor takes slabs of 12 chunks
+// cached step that adds a tensor takes slabs of 12 chunks; with nine: B N D k cus -> whether one of two states does not share its coefficients
 int main(int argc, char**) {
+  if (argc > 9) {
+    long long B;
+    int N, D, k, cus;
+    while (std::scanf("%lld %d %d %d %d", &B, &N, &D, &k, &cus) == 5) std::printf("%d\n", (int)svdc::two_states_stay_unshared((N + 15) / 16, B, D, k, cus));
+    return 0;
+  }
   if (argc > 8) {
     long long B;
     int N, D, states, cus;
@@ -244,4 +250,13 @@ def test_cached_steps_that_add_a_tensor_in_wide_slabs(tiling):
     calls = [((57, 4608, 3072, 2), True), ((57, 4608, 3072, 4), True), ((19, 4608, 3072, 2), False), ((6, 4608, 3072, 2), False),
              ((4, 6865, 3072, 4), True), ((4, 6865, 3072, 2), False), ((1, 85001, 3072, 2), True), ((8, 5206, 1536, 3), True), ((1, 300, 3072, 4), False), ((57, 4608, 2048, 2), False), ((57, 4608, 5120, 4), False)]
     rule = ["which", "cached", "steps", "that", "add", "take", "wide", "slabs"]
+    assert tiling([c + (256,) for c, _ in calls], rule=rule) == [w for _, w in calls]
+
+
+def test_cached_steps_of_two_states_that_do_not_share(tiling):
+    """Measured (us unshared, shared): 4 x 12079 x 4096 rank 8 165 / 176, 6 x 21312 x 2048 rank 16 217 / 230, 41 x 4525 x 1024 rank 8 172 / 181; with a rank above 16,
+    other widths and shorter calls the shared ones are faster."""
+    calls = [((4, 12079, 4096, 8), True), ((6, 21312, 2048, 16), True), ((41, 4525, 1024, 8), True), ((1, 308001, 512, 4), True), ((6, 21312, 2048, 20), False),
+             ((57, 4608, 3072, 8), False), ((57, 4608, 1152, 8), False), ((4, 6000, 4096, 8), False)]
+    rule = ["which", "cached", "steps", "of", "two", "states", "do", "not", "share"]
     assert tiling([c + (256,) for c, _ in calls], rule=rule) == [w for _, w in calls]
