@@ -716,13 +716,13 @@ int32_t forecast_launch(const svdc_shape& s, const CoefStates& cs, const void* p
   const int ntile = (s.N + 15) / 16;
   if (tpg == 0) {
     const int m = s.D / 128;
-    constexpr bool kToOne = NCW == 3 && KT2 == 4 && sizeof(T) == 4;
+    constexpr bool kToOne = narrow_slab(24, NCW, KT2, sizeof(T) == 4, EXT) == 1;
     const CachedCall call{m, ntile, s.B, KT2, SPLIT ? 2 : 1, (int)sizeof(T), cus};
-    const CachedTiling t = cached_tiling(call, NCW, NCW > 3 ? (m % 3 == 0 ? 3 : (m % 2 == 0 ? 2 : 0)) : (kToOne ? 1 : 0));
+    const CachedTiling t = cached_tiling(call, NCW, narrow_slab(m, NCW, KT2, sizeof(T) == 4, EXT));
     if constexpr (kToOne) {
       if (t.chunks == 1) return forecast_launch<T, 1, KT2, SPLIT, EXT, PS, true>(s, cs, packed, R, X, Fhat, st, cus, t.tiles);
     }
-    if constexpr (NCW > 3) {
+    if constexpr (NCW > 3 && !kToOne) {
       if (t.chunks == 3) return forecast_launch<T, 3, KT2, SPLIT, EXT, PS, true>(s, cs, packed, R, X, Fhat, st, cus, t.tiles);
       if (t.chunks == 2) return forecast_launch<T, 2, KT2, SPLIT, EXT, PS, true>(s, cs, packed, R, X, Fhat, st, cus, t.tiles);
     }

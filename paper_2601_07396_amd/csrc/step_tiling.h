@@ -44,10 +44,16 @@ struct CachedCall {
 // 1278 and 828 us).
 // A call for which even the best of these fills less than 0.7 leaves compute units idle (one block of 4608 x 3072 rows:
 // 96 workgroups of 1536 channels).  It may take fewer tiles, and a slab of 3 or 2 chunks (`narrow`, 0 if there is none)
-// instead of the widest one, where that costs less: 23 -> 13 us for that block at rank 32, 23 -> 17 us at rank 64; one chunk instead of
-// 3 for float32 rows at rank 128 of an odd number of chunks (1 x 439 x 1152: 5.1 us with 3, 4.3 with one).  Not
+// instead of the widest one (narrow_slab), where that costs less: 23 -> 13 us for that block at rank 32, 23 -> 17 us at rank 64.  Not
 // where many small workgroups would only load operands (43 x 129 x 2048, rank 128: 29 us wide, 46 us narrow); over 460
 // sampled calls of up to two rounds this is within 4 % of the best of all choices.
+// Float32 rows above rank 32 go down to one chunk with several states, whose loads a short call waits for (us with 2 or 3 chunks and with one: 1 x 273 x 1152
+// rank 48, two states 5.1 and 3.7, 2 x 404 x 512 rank 124 4.6 and 4.0; 700 calls of up to 30 MB), and at rank 128 where 3 chunks are the widest slab (1 x 439 x
+// 1152: 5.1 and 4.3).
+constexpr int narrow_slab(int m, int chunks, int kt2, bool f32, bool several_states) {
+  if (f32 && kt2 > 1 && chunks > 1 && (several_states || (kt2 == 4 && chunks == 3))) return 1;
+  return chunks <= 3 ? 0 : (m % 3 == 0 ? 3 : (m % 2 == 0 ? 2 : 0));
+}
 inline CachedTiling cached_tiling(const CachedCall& call, int chunks, int narrow) {
   CachedTiling best{chunks, 16};
   for (int cand = 15; cand >= 6; --cand)

@@ -1130,6 +1130,12 @@ def test_long_cached_steps_of_two_states_that_do_not_share(B, N, D, k):
     test_cached_steps_share_their_coefficients(torch.bfloat16, B, N, D, k, 0, 0)
 
 
+@pytest.mark.parametrize("B,N,D,k", [(1, 273, 1152, 48), (1, 304, 256, 36), (2, 404, 512, 124), (1, 336, 512, 40), (1, 257, 1920, 128)])
+def test_short_cached_steps_of_several_float32_states(B, N, D, k):
+    """Slabs of one chunk in the place of 2, 3 or 4."""
+    test_cached_steps_share_their_coefficients(torch.float32, B, N, D, k, 0, 0)
+
+
 @pytest.mark.parametrize("B,N,k", [(4, 4090, 32), (4, 3060, 64), (2, 4090, 128)])
 def test_full_step_tiles_with_a_row_tile_in_lds(B, N, k):
     """3072 channels and one round of 256 or more workgroup tiles, each block ending in a partly filled tile.  At

@@ -17,8 +17,19 @@ PROGRAM = r"""
 // general full step in parts + whether the general cached step runs in parts; with four: B N D k f32 states cus -> the latter; with five:
 // rows l tiles most cus -> rows of a slice of the Gram matrices; with six: ntile B kt D cus -> whether a projection is large; with
 // seven: B N D k f32 split cus -> row tiles of the projection of a full step that takes two launches, or 0; with eight: B N D states cus -> whether a
-// cached step that adds a tensor takes slabs of 12 chunks; with nine: B N D k cus -> whether one of two states does not share its coefficients
+// cached step that adds a tensor takes slabs of 12 chunks; with nine: B N D k cus -> whether one of two states does not share its coefficients;
+// with ten: B N D kt2 f32 split states cus and the widest slab -> the narrow slab, and chunks and tiles of what is launched
 int main(int argc, char**) {
+  if (argc > 10) {
+    long long B;
+    int N, D, kt2, f32, split, states, cus, chunks;
+    while (std::scanf("%lld %d %d %d %d %d %d %d %d", &B, &N, &D, &kt2, &f32, &split, &states, &cus, &chunks) == 9) {
+      const int m = D / 128, narrow = svdc::narrow_slab(m, chunks, kt2, f32, states > 1);
+      const svdc::CachedTiling t = svdc::cached_tiling({m, (N + 15) / 16, B, kt2, split ? 2 : 1, f32 ? 4 : 2, cus}, chunks, narrow);
+      std::printf("%d %d %d 0\n", narrow, t.chunks, t.tiles);
+    }
+    return 0;
+  }
   if (argc > 9) {
     long long B;
     int N, D, k, cus;
@@ -112,7 +123,7 @@ def tiling(tmp_path_factory):
             return [int(line) for line in out.split()]
         if len(rule) == 3:
             return [(int(line) // 10, bool(int(line) % 10)) for line in out.split()]
-        if rule:
+        if rule and len(rule) != 10:
             return [bool(int(line)) for line in out.split()]
         return [(int(a), int(b), int(c), float(d)) for a, b, c, d in (line.split() for line in out.splitlines())]
     return run
@@ -260,3 +271,15 @@ def test_cached_steps_of_two_states_that_do_not_share(tiling):
              ((57, 4608, 3072, 8), False), ((57, 4608, 1152, 8), False), ((4, 6000, 4096, 8), False)]
     rule = ["which", "cached", "steps", "of", "two", "states", "do", "not", "share"]
     assert tiling([c + (256,) for c, _ in calls], rule=rule) == [w for _, w in calls]
+
+
+@pytest.mark.parametrize("B,N,D,kt2,f32,split,states,widest,want", [
+    (1, 439, 1152, 4, 1, 1, 1, 3, (1, 1)), (1, 18432, 1152, 4, 1, 1, 1, 3, (1, 3)),       # rank 128, 9 chunks: one chunk in a short call, 3 in a long one
+    (1, 273, 1152, 2, 1, 1, 2, 3, (1, 1)), (1, 304, 256, 2, 1, 1, 2, 2, (1, 1)), (2, 404, 512, 4, 1, 1, 2, 2, (1, 1)), (1, 336, 512, 2, 1, 1, 2, 4, (1, 1)),
+    (1, 18432, 3072, 2, 1, 1, 2, 3, (1, 3)), (28, 1548, 1920, 4, 1, 1, 1, 3, (1, 3)), (1, 273, 1152, 2, 1, 1, 1, 3, (0, 3)),
+    (24, 2000, 3072, 2, 0, 1, 2, 4, (3, 4)), (2, 119056, 3072, 4, 0, 1, 2, 2, (0, 2)), (1, 4608, 3072, 1, 0, 1, 1, 12, (3, 3)), (1, 4608, 2048, 1, 0, 1, 1, 8, (2, 2))])
+def test_slabs_of_the_cached_step(tiling, B, N, D, kt2, f32, split, states, widest, want):
+    """With the widest slab that the launcher starts from: the narrower one that it may take, and the one that it takes.  One chunk in the place of 3 or 2
+    where float32 rows have several states (us: 1 x 273 x 1152 rank 48 5.1 -> 3.7, 2 x 404 x 512 rank 124 4.6 -> 4.0)."""
+    rule = ["which", "slabs", "does", "the", "cached", "step", "take", "in", "the", "end"]
+    assert tiling([(B, N, D, kt2, f32, split, states, 256, widest)], rule=rule)[0][:2] == want
