@@ -771,7 +771,8 @@ int32_t forecast_launch(const svdc_shape& s, const CoefStates& cs, const void* p
 
 // Slab per wave (NCW chunks): the first of the widths that suit the kind of call and divide D / 128.  Plain bf16 calls up to rank 32 take the widest
 // that keeps the basis operands in registers; hidden sizes that 12 does not divide (1152 = 9 x 128, 2560 and 5120 = 20 and 40 x
-// 128, 4096 = 32 x 128, 1920 = 15 x 128) the next.  The kinds that share the coefficients: see forecast_mfma_kernel.
+// 128, 4096 = 32 x 128, 1920 = 15 x 128) the next.  Every width has a divisor of 2 or 3 chunks; the last one of a list is not asked for.  The kinds that
+// share the coefficients: see forecast_mfma_kernel.
 template <typename T, int KT2, bool SPLIT, bool EXT, bool PS>
 struct ForecastCall {
   const svdc_shape& s;
@@ -797,31 +798,31 @@ int32_t forecast_by_width(const svdc_shape& s, const CoefStates& cs, const void*
   const ForecastCall<T, KT2, SPLIT, EXT, PS> call{s, cs, packed, R, X, Fhat, st, num_compute_units()};
   if constexpr (KT2 == 1 && !kF32) {
     if constexpr (!EXT) {
-      return call.template first<12, 10, 9, 8, 6, 5, 4, 3, 2, 1>();
+      return call.template first<12, 10, 9, 8, 6, 5, 4, 3, 2>();
     } else {
       const CachedCall tiles{s.D / 128, (s.N + 15) / 16, s.B, KT2, 2, (int)sizeof(T), call.cus};
-      if (X && !adding_takes_wide_slabs(tiles, cs.m)) return call.template first<6, 4, 3, 2, 1>();
-      return call.template first<12, 6, 4, 3, 2, 1>();
+      if (X && !adding_takes_wide_slabs(tiles, cs.m)) return call.template first<6, 4, 3, 2>();
+      return call.template first<12, 6, 4, 3, 2>();
     }
   } else if constexpr (KT2 == 1) {
-    return call.template first<6, 5, 4, 3, 2, 1>();
+    return call.template first<6, 5, 4, 3, 2>();
   } else if constexpr (KT2 == 2) {
-    if constexpr (kF32) return call.template first<3, 4, 2, 1>();
+    if constexpr (kF32) return call.template first<3, 4, 2>();
     else if constexpr (!SPLIT && PS) {
       // Single operand words that are loaded as they are: 2 KB per tile, and four waves hold 1536 channels.  Slabs of 12 unshared beat
       // 6 shared in long calls, and in short ones, where they make way for narrow ones (57 x 4608 x 3072, 128 pieces of a tile per compute
       // unit: 636 and 649 us; 1 x 4608, 2.25 pieces: 15.9 and 17.4), but not between them (9 and 18 pieces: 1 x 18432 x 3072 50.3 and 49.5 us,
       // 16 x 4608 x 1536 100 and 95; 29: 149.6 and 150.2).
       const int64_t pieces = (int64_t)((s.N + 15) / 16) * s.B * (s.D / 1536);
-      if (pieces <= 4 * (int64_t)call.cus || pieces >= 48 * (int64_t)call.cus) return call.template first<12, 6, 8, 5, 4, 3, 2, 1>();
-      return call.template first<6, 8, 5, 4, 3, 2, 1>();
-    } else if constexpr (!SPLIT) return call.template first<6, 8, 5, 4, 3, 2, 1>();
-    else if constexpr (PS) return call.template first<5, 4, 3, 2, 1>();
-    else return call.template first<4, 3, 2, 1>();
+      if (pieces <= 4 * (int64_t)call.cus || pieces >= 48 * (int64_t)call.cus) return call.template first<12, 6, 8, 5, 4, 3, 2>();
+      return call.template first<6, 8, 5, 4, 3, 2>();
+    } else if constexpr (!SPLIT) return call.template first<6, 8, 5, 4, 3, 2>();
+    else if constexpr (PS) return call.template first<5, 4, 3, 2>();
+    else return call.template first<4, 3, 2>();
   } else {
-    if constexpr (kF32 || (EXT && SPLIT)) return call.template first<2, 3, 1>();
-    else if constexpr (PS && !SPLIT) return call.template first<5, 4, 3, 2, 1>();
-    else return call.template first<4, 3, 2, 1>();
+    if constexpr (kF32 || (EXT && SPLIT)) return call.template first<2, 3>();
+    else if constexpr (PS && !SPLIT) return call.template first<5, 4, 3, 2>();
+    else return call.template first<4, 3, 2>();
   }
 }
 
