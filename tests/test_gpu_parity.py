@@ -998,10 +998,16 @@ def test_fit_basis_partial_gram_matrices_in_several_areas(dtype, B, D, l, N):
     test_fit_basis_at_the_block_edges_of_the_small_matrices(dtype, B, D, l, N - l)
 
 
-@pytest.mark.parametrize("dtype,B,N,D,k,fast,pad", [(torch_dtype(c[0]), *c[1:7]) for c in TWO_LAUNCHES])
+@pytest.mark.parametrize("dtype,B,N,D,k,fast,pad", [
+    (torch.float32, 1, 37, 5120, 8, 0, 0), (torch.float32, 3, 333, 4096, 40, 0, 8), (torch.float32, 1, 150, 3072, 128, 0, 0),    # 1 tile per workgroup
+    (torch.bfloat16, 1, 101, 3072, 100, 0, 64), (torch.float32, 1, 6131, 1152, 68, 0, 0), (torch.bfloat16, 4, 1031, 2560, 96, 0, 0),    # 2
+    (torch.bfloat16, 1, 4609, 3072, 64, 0, 0), (torch.float32, 2, 5001, 1920, 128, 0, 0),                                      # 2, 3
+    (torch.float32, 7, 2299, 2048, 100, 0, 0), (torch.bfloat16, 4, 4199, 4096, 68, 0, 0),                                       # 4, 5
+    (torch.bfloat16, 3, 6001, 1536, 128, 0, 8), (torch.float32, 3, 7297, 512, 128, 0, 0),                                       # 5, 6
+    (torch.bfloat16, 5, 5003, 2560, 120, 1, 0)])
 def test_full_step_in_two_launches(dtype, B, N, D, k, fast, pad):
-    """A full step with a buffer for C may run as a projection and a reconstruction (these do: test_step_tiling.py); without one it is a single
-    launch.  Both add up in the same order: R, S and the packed state have the same bits, also in place, and C is the oracle's."""
+    """A full step with a buffer for C may run as a projection and a reconstruction; without one it is a single launch.  Both add up in the
+    same order: R, S and the packed state have the same bits, also in place, and C is the oracle's."""
     g = torch.Generator(device=DEV).manual_seed(N + D + k)
     wide = torch.randn(B, N, D + pad, generator=g, device=DEV).to(dtype)
     F = wide[:, :, :D]
