@@ -169,12 +169,12 @@ struct RowPiece<float> {
 // MSX, HX (EXT only): registers are held for MSX coefficient states per tile in flight, and for the added tensor only
 // with HX -- a forecaster of two states that adds nothing should not pay for four states and a second row tile.
 // SHARED: each wave loads (and combines, and converts) a quarter of a tile's coefficients and the four pass the operand words to each
-// other through LDS, one barrier per tile; otherwise every wave loads all of them.  What a compute unit loads per time is limited (6 B per clock
-// here, whether it comes from HBM or a cache), and at rank 64 the coefficients were a third of it for bf16 rows, at rank 128 a half.  With the
-// registers that this frees, two workgroups per compute unit where the table (forecast_variant) says so.  us, before and now:
-// 2 x 119056 x 3072 bf16 rank 64 674 -> 597, 16 x 4608 rank 64 223 -> 193, rank 128 312 -> 250, single operands 194 -> 184 and 237 -> 201;
-// 18432 rows of float32, rank 32, 64, 128 93 -> 89, 98 -> 92, 116 -> 103; two states and an added tensor, 19 x 4608 bf16 rank 16 304 -> 266, 16
-// blocks rank 64 326 -> 236, 8 blocks rank 128 306 -> 171.  Not for plain bf16 calls up to rank 32 (57 x 4608: 606 and 610 us).
+// other through LDS, one barrier per tile; otherwise every wave loads all of them, at rank 64 a third of what the workgroup asks for with bf16
+// rows, at rank 128 a half, and holds them in registers.  What those cost most, requests or registers, was not separated; with the registers that sharing
+// frees, two workgroups per compute unit run where the table (forecast_variant) says so.  us, every wave and shared, inputs in turn: 2 x 119056 x
+// 3072 bf16 rank 64 695 -> 611, 16 x 4608 rank 64 218 -> 195, rank 128 299 -> 256, single operands 193 -> 185 and 236 -> 202; 18432 rows of float32,
+// rank 32, 64, 128 95 -> 90, 97 -> 93, 111 -> 103; two states and an added tensor, 19 x 4608 bf16 rank 16 322 -> 318, 16 blocks rank 64 359 -> 281, 8
+// blocks rank 128 515 -> 181.  Not for plain bf16 calls up to rank 32 (57 x 4608, the same buffers again: 606 and 610 us).
 template <typename T, int NCW, int KT2, bool SPLIT, int PD, bool EXT, bool PS, int MSX, bool HX, bool SHARED, int WPE>
 __global__ __launch_bounds__(256, WPE) void forecast_mfma_kernel(const CoefStates cs, const uint16_t* __restrict__ P,
                                                             const T* R, const T* X, T* Fh, int N, int D, int k,
@@ -668,10 +668,10 @@ int32_t launch_pack_basis(const svdc_shape& s, const float* V, void* packed, hip
 namespace {
 
 // Whether a kind of call shares the coefficients among the waves of a workgroup, where they are a fair part of what it loads, and whether only
-// calls of more than one workgroup per compute unit do: one that has only a few row tiles does not win back the barriers.  Against
-// every wave loading all of them in such short calls: packed states (nothing to convert) of rank 64 and 128 4 to 11 % slower (4 x 703 x 1920,
-// rank 112: 12.3 and 13.9 us), one or several states of rank <= 32 in float32 up to 15 % (12 x 691 x 512: 9.5 and 10.9 us), in bf16
-// without an added tensor 3 to 7 %; all others 1 to 40 % faster (370 sampled calls).
+// calls of more than one workgroup per compute unit do: one that has only a few row tiles does not win back the barriers.  Shared
+// against not, in such short calls, inputs in turn: several states of rank <= 32 in float32 5 % slower on average (290 sampled calls, up to 16 %; 12 x 691 x 512:
+// 12.7 and 13.2 us), in bf16 without an added tensor 11 % (113 calls); packed states of rank 64 and 128 the same on average, -7 to +8 % (4 x 703 x 1920, rank 112:
+// 13.6 and 14.4 us); all others 1 to 40 % faster.
 enum class Share { kNever, kLongCalls, kAlways };
 template <typename T, int NCW, int KT2, bool EXT, bool PS, bool HX, int MSX>
 constexpr Share forecast_share() {
@@ -812,7 +812,8 @@ int32_t forecast_by_width(const svdc_shape& s, const CoefStates& cs, const void*
       // Single operand words that are loaded as they are: 2 KB per tile, and four waves hold 1536 channels.  Slabs of 12 unshared beat
       // 6 shared in long calls, and in short ones, where they make way for narrow ones (57 x 4608 x 3072, 128 pieces of a tile per compute
       // unit: 636 and 649 us; 1 x 4608, 2.25 pieces: 15.9 and 17.4), but not between them (9 and 18 pieces: 1 x 18432 x 3072 50.3 and 49.5 us,
-      // 16 x 4608 x 1536 100 and 95; 29: 149.6 and 150.2).
+      // 16 x 4608 x 1536 100 and 95; 29: 149.6 and 150.2).  400 sampled calls of 1536 and 3072 channels: 0.98 of the time of slabs of 12 alone, none
+      // more than 3 % slower.
       const int64_t pieces = (int64_t)((s.N + 15) / 16) * s.B * (s.D / 1536);
       if (pieces <= 4 * (int64_t)call.cus || pieces >= 48 * (int64_t)call.cus) return call.template first<12, 6, 8, 5, 4, 3, 2>();
       return call.template first<6, 8, 5, 4, 3, 2>();

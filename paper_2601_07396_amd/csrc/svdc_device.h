@@ -46,7 +46,8 @@ __device__ __forceinline__ void split_operand(const float (&c)[8], u32x4* hi, u3
               pack_bf16(rem[6], rem[7])};
 }
 
-// (1 - alpha) old + alpha now, rounded in one way wherever it is formed
+// (1 - alpha) old + alpha now, rounded in one way in both forms of the full step on the bf16 matrix cores (the general steps leave the contraction to
+// the compiler)
 __device__ __forceinline__ float ema(float old, float now, float alpha) { return __builtin_fmaf(1.f - alpha, old, alpha * now); }
 
 // ---- wavefront reductions -----------------------------------------------------
