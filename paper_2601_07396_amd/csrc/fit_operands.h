@@ -5,11 +5,6 @@
 namespace svdc {
 namespace {
 
-__device__ __forceinline__ f32x4 mfma16(const u32x4& a, const u32x4& b, const f32x4& c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
-                                                 0, 0, 0);
-}
-
 // Eight consecutive channels of one token as they are loaded, and as matrix-core operands.  bf16 features are the
 // operand; float32 features are split into bf16 high + low parts when used (the products then take the high part
 // against both parts of the other operand and the low part against its high part: about 16 significant bits).

@@ -32,11 +32,6 @@ namespace {
 
 constexpr int kWavesPerGroup = 4;
 
-__device__ __forceinline__ f32x4 mfma16(const u32x4& a, const u32x4& b, const f32x4& c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
-                                                 0, 0, 0);
-}
-
 // Direct global-to-LDS load of 16 bytes per lane: lane l's bytes land at lds_wave_base + 16 l.  Counts in vmcnt
 // like any other vector memory load; lds_wave_base must be the same in all lanes of the wave.
 __device__ __forceinline__ void load_to_lds16(const void* gsrc_lane, void* lds_wave_base) {

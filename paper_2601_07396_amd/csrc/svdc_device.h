@@ -46,6 +46,12 @@ __device__ __forceinline__ void split_operand(const float (&c)[8], u32x4* hi, u3
               pack_bf16(rem[6], rem[7])};
 }
 
+// 16 x 16 products over 32 channels or rows, operands as words of 8 bf16
+__device__ __forceinline__ f32x4 mfma16(const u32x4& a, const u32x4& b, const f32x4& c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
+                                                 0, 0, 0);
+}
+
 // (1 - alpha) old + alpha now, rounded in one way in both forms of the full step on the bf16 matrix cores (the general steps leave the contraction to
 // the compiler)
 __device__ __forceinline__ float ema(float old, float now, float alpha) { return __builtin_fmaf(1.f - alpha, old, alpha * now); }
