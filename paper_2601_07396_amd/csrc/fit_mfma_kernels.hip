@@ -149,7 +149,7 @@ __global__ __launch_bounds__(256) void fit_project_mfma_kernel(const bf16_t* __r
 // buffered, one barrier per slab) and every wave reads them from there.  Per token row the packed sketch is then
 // read from L2 once per 64 RTW rows and from LDS once per 16 RTW rows, against once per 16 to 96 rows when both operands are
 // streamed (project_stream_kernel), at the price of a memory latency and a barrier per slab, which only several workgroups on a
-// compute unit hide.  57 x 4608 x 3072, this and streamed: split operands, width 64 394 and 447 us, width 128 575 and 587; plain
+// compute unit hide.  57 x 4608 x 3072, this and streamed: split operands, width 64 394 and 447 us alone (435 in a traced refit), width 128 575 and 587; plain
 // ones, width 128 431 and 457 us.  20 blocks: 146 and 164, 225 and 216, 166 and 170; 8 blocks: 92 and 72, 118 and 95, 88 and 76.
 //   A operand = F tile   (m = token row, kk = channel)   -- the natural 16-byte row pieces
 //   B operand = Q tile   (kk = channel, n = coefficient)
