@@ -713,7 +713,8 @@ int32_t forecast_launch(const svdc_shape& s, const CoefStates& cs, const void* p
     const int m = s.D / 128;
     constexpr bool kToOne = narrow_slab(24, NCW, KT2, sizeof(T) == 4, EXT) == 1;
     const CachedCall call{m, ntile, s.B, KT2, SPLIT ? 2 : 1, (int)sizeof(T), cus};
-    const CachedTiling t = cached_tiling(call, NCW, narrow_slab(m, NCW, KT2, sizeof(T) == 4, EXT));
+    const bool two_per_unit = EXT && X && KT2 == 1 && sizeof(T) == 2 && NCW < 12;
+    const CachedTiling t = cached_tiling(call, NCW, narrow_slab(m, NCW, KT2, sizeof(T) == 4, EXT), two_per_unit ? kAddingOneRound : 0.7);
     if constexpr (kToOne) {
       if (t.chunks == 1) return forecast_launch<T, 1, KT2, SPLIT, EXT, PS, true>(s, cs, packed, R, X, Fhat, st, cus, t.tiles);
     }

@@ -47,6 +47,9 @@ struct CachedCall {
 // instead of the widest one (narrow_slab), where that costs less: 23 -> 13 us for that block at rank 32, 23 -> 17 us at rank 64.  Not
 // where many small workgroups would only load operands (43 x 129 x 2048, rank 128: 29 us wide, 46 us narrow); over 460
 // sampled calls of up to two rounds this is within 4 % of the best of all choices.
+// one_round: the fill that a call of at most one workgroup per unit needs to keep the widest slab.  0.9 where a unit holds two workgroups and bf16 rows
+// have a tensor added, rank <= 32 (kAddingOneRound): below it half of the places for workgroups are empty (us at 0.7 and like this: 12 x 749 x 1536, four states 25.6 and
+// 23.3, 8 x 534 x 2048, two states 16.5 and 15.2; of 900 calls 13 change, all faster, by 8 %).  Elsewhere it gains nothing (1500 calls of all kinds: as many slower as faster).
 // Float32 rows above rank 32 go down to one chunk with several states, whose loads a short call waits for (us with 2 or 3 chunks and with one: 1 x 273 x 1152
 // rank 48, two states 5.1 and 3.7, 2 x 404 x 512 rank 124 4.6 and 4.0; 700 calls of up to 30 MB), and at rank 128 where 3 chunks are the widest slab (1 x 439 x
 // 1152: 5.1 and 4.3).
@@ -54,11 +57,11 @@ constexpr int narrow_slab(int m, int chunks, int kt2, bool f32, bool several_sta
   if (f32 && kt2 > 1 && chunks > 1 && (several_states || (kt2 == 4 && chunks == 3))) return 1;
   return chunks <= 3 ? 0 : (m % 3 == 0 ? 3 : (m % 2 == 0 ? 2 : 0));
 }
-inline CachedTiling cached_tiling(const CachedCall& call, int chunks, int narrow) {
+inline CachedTiling cached_tiling(const CachedCall& call, int chunks, int narrow, double one_round = 0.7) {
   CachedTiling best{chunks, 16};
   for (int cand = 15; cand >= 6; --cand)
     if (call.fill({chunks, cand}) > call.fill(best) + 1e-9) best.tiles = cand;
-  if (call.fill(best) >= 0.7) return best;
+  if (call.fill(best) >= (call.workgroups(best) <= call.cus ? one_round : 0.7)) return best;
   double least = 0.85 * call.cost(best);
   const int few = chunks > 3 || narrow > 0 ? narrow : chunks;
   for (int cand = std::min(16, call.ntile); few > 0 && cand >= 1; --cand) {
@@ -70,6 +73,8 @@ inline CachedTiling cached_tiling(const CachedCall& call, int chunks, int narrow
   }
   return best;
 }
+
+constexpr double kAddingOneRound = 0.9;
 
 // Whether a cached step that adds a tensor (bf16, rank <= 32) takes slabs of 12 chunks, one workgroup per compute unit whose waves each load all
 // coefficients, instead of slabs of 6 that share them, two workgroups per unit.  Wide ones are 2 to 4 % faster in long calls of well-filled rounds (from 40

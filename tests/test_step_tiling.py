@@ -18,14 +18,14 @@ PROGRAM = r"""
 // rows l tiles most cus -> rows of a slice of the Gram matrices; with six: ntile B kt D cus -> whether a projection is large; with
 // seven: B N D k f32 split cus -> row tiles of the projection of a full step that takes two launches, or 0; with eight: B N D states cus -> whether a
 // cached step that adds a tensor takes slabs of 12 chunks; with nine: B N D k cus -> whether one of two states does not share its coefficients;
-// with ten: B N D kt2 f32 split states cus and the widest slab -> the narrow slab, and chunks and tiles of what is launched
+// with ten: B N D kt2 f32 split states cus, the widest slab and whether a tensor is added -> the narrow slab, and chunks and tiles of what is launched
 int main(int argc, char**) {
   if (argc > 10) {
     long long B;
-    int N, D, kt2, f32, split, states, cus, chunks;
-    while (std::scanf("%lld %d %d %d %d %d %d %d %d", &B, &N, &D, &kt2, &f32, &split, &states, &cus, &chunks) == 9) {
+    int N, D, kt2, f32, split, states, cus, chunks, adds;
+    while (std::scanf("%lld %d %d %d %d %d %d %d %d %d", &B, &N, &D, &kt2, &f32, &split, &states, &cus, &chunks, &adds) == 10) {
       const int m = D / 128, narrow = svdc::narrow_slab(m, chunks, kt2, f32, states > 1);
-      const svdc::CachedTiling t = svdc::cached_tiling({m, (N + 15) / 16, B, kt2, split ? 2 : 1, f32 ? 4 : 2, cus}, chunks, narrow);
+      const svdc::CachedTiling t = svdc::cached_tiling({m, (N + 15) / 16, B, kt2, split ? 2 : 1, f32 ? 4 : 2, cus}, chunks, narrow, adds ? svdc::kAddingOneRound : 0.7);
       std::printf("%d %d %d 0\n", narrow, t.chunks, t.tiles);
     }
     return 0;
@@ -282,4 +282,13 @@ def test_slabs_of_the_cached_step(tiling, B, N, D, kt2, f32, split, states, wide
     """With the widest slab that the launcher starts from: the narrower one that it may take, and the one that it takes.  One chunk in the place of 3 or 2
     where float32 rows have several states (us: 1 x 273 x 1152 rank 48 5.1 -> 3.7, 2 x 404 x 512 rank 124 4.6 -> 4.0)."""
     rule = ["which", "slabs", "does", "the", "cached", "step", "take", "in", "the", "end"]
-    assert tiling([(B, N, D, kt2, f32, split, states, 256, widest)], rule=rule)[0][:2] == want
+    assert tiling([(B, N, D, kt2, f32, split, states, 256, widest, 0)], rule=rule)[0][:2] == want
+
+
+@pytest.mark.parametrize("B,N,D,widest,plain,adding", [(12, 749, 1536, 6, 6, 3), (8, 534, 2048, 4, 4, 2), (1, 4368, 3072, 6, 6, 3), (6, 4608, 3072, 6, 6, 6), (1, 5400, 3072, 6, 6, 6)])
+def test_cached_steps_that_add_a_tensor_fill_one_round(tiling, B, N, D, widest, plain, adding):
+    """Two workgroups of these steps fit on a compute unit: a grid of at most one per unit that fills less than 0.9 of that gives way to narrower slabs.  Measured (us with the
+    slab that others keep, with the narrower one): 12 x 749 x 1536 four states 25.6 / 23.3, 8 x 534 x 2048 two states 16.5 / 15.2, 1 x 4368 x 3072 24.5 / 21.1."""
+    rule = ["which", "slabs", "does", "the", "cached", "step", "take", "in", "the", "end"]
+    got = tiling([(B, N, D, 1, 0, 1, 2, 256, widest, adds) for adds in (0, 1)], rule=rule)
+    assert [g[1] for g in got] == [plain, adding]
