@@ -225,7 +225,8 @@ inline bool full_step_in_two_launches(OneLaunch one, int N, int64_t B, int D, in
 
 // Row tiles of the projection of a full step with a buffer for C that takes two launches, 0 where it takes one.
 inline int full_step_projection_rows(int N, int64_t B, int D, int k, bool f32, bool split, int cus) {
-  if (!full_step_may_take_two_launches(D, k, f32, split)) return 0;
+  // beyond 2^26 row tiles (a terabyte of the narrowest rows that come here) a grid could have more than 2^31 workgroups: the single launch refuses those
+  if (!full_step_may_take_two_launches(D, k, f32, split) || ((int64_t)N + 15) / 16 * B > (int64_t)1 << 26) return 0;
   const int rows = full_step_rows(D / 128, f32 ? 2 : 1, k <= 32 ? 1 : (k <= 64 ? 2 : 4), split, N, B, cus);
   const int64_t tiles = (int64_t)((N + 16 * rows - 1) / (16 * rows)) * B;
   return full_step_in_two_launches({rows, tiles}, N, B, D, k, f32, split, cus) ? stream_rows((N + 15) / 16, B, cus) : 0;

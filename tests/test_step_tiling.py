@@ -292,3 +292,10 @@ def test_cached_steps_that_add_a_tensor_fill_one_round(tiling, B, N, D, widest, 
     rule = ["which", "slabs", "does", "the", "cached", "step", "take", "in", "the", "end"]
     got = tiling([(B, N, D, 1, 0, 1, 2, 256, widest, adds) for adds in (0, 1)], rule=rule)
     assert [g[1] for g in got] == [plain, adding]
+
+
+def test_full_steps_of_more_rows_than_a_grid_has_workgroups_stay_one_launch(tiling):
+    """The single launch refuses those before anything runs; the projection of two launches has no such check of its own."""
+    rule = ["which", "full", "steps", "take", "two", "launches", "instead"]
+    calls = [(170, 2 ** 30 - 1, 1536, 128, 0, 1, 256), (3, 2 ** 30 - 1, 5120, 8, 1, 1, 256), (60, 119056, 3072, 128, 0, 1, 256)]
+    assert [r > 0 for r in tiling(calls, rule=rule)] == [False, False, True]
