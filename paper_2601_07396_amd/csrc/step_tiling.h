@@ -49,7 +49,8 @@ struct CachedCall {
 // sampled calls of up to two rounds this is within 4 % of the best of all choices.
 // one_round: the fill that a call of at most one workgroup per unit needs to keep the widest slab.  0.9 where a unit holds two workgroups and bf16 rows
 // have a tensor added, rank <= 32 (kAddingOneRound): below it half of the places for workgroups are empty (us at 0.7 and like this: 12 x 749 x 1536, four states 25.6 and
-// 23.3, 8 x 534 x 2048, two states 16.5 and 15.2; of 900 calls 13 change, all faster, by 8 %).  Elsewhere it gains nothing (1500 calls of all kinds: as many slower as faster).
+// 23.3, 8 x 534 x 2048, two states 16.5 and 15.2; of 900 calls 13 change, all faster, by 8 %).  Elsewhere
+// it is mixed: of 835 calls of one state above rank 32, 46 change, 32 to less time and 14 to more, 3.5 % less on average.
 // Float32 rows above rank 32 go down to one chunk with several states, whose loads a short call waits for (us with 2 or 3 chunks and with one: 1 x 273 x 1152
 // rank 48, two states 5.1 and 3.7, 2 x 404 x 512 rank 124 4.6 and 4.0; 700 calls of up to 30 MB), and at rank 128 where 3 chunks are the widest slab (1 x 439 x
 // 1152: 5.1 and 4.3).
