@@ -37,6 +37,15 @@ struct CachedCall {
   }
 };
 
+// The slab that a cached step may take in the place of its widest one of `chunks`, 0: none.  3 or 2 chunks; float32 rows above rank 32 go down to one chunk
+// with several states, whose loads a short call waits for (us with 2 or 3 chunks and with one: 1 x 273 x 1152
+// rank 48, two states 5.1 and 3.7, 2 x 404 x 512 rank 124 4.6 and 4.0; 700 calls of up to 30 MB), and at rank 128 where 3 chunks are the widest slab (1 x 439 x
+// 1152: 5.1 and 4.3).
+constexpr int narrow_slab(int m, int chunks, int kt2, bool f32, bool several_states) {
+  if (f32 && kt2 > 1 && chunks > 1 && (several_states || (kt2 == 4 && chunks == 3))) return 1;
+  return chunks <= 3 ? 0 : (m % 3 == 0 ? 3 : (m % 2 == 0 ? 2 : 0));
+}
+
 // Every workgroup loads the operands of its slab once and uses them for each of its row tiles, so a call that fills the
 // machine takes 6 to 16 of them, the number whose grid fills whole rounds best (a grid of e.g. 16.03 x the compute units
 // costs a 17th, nearly empty round): with fewer the operands outweigh the features, and rounding better gains little
@@ -51,13 +60,6 @@ struct CachedCall {
 // have a tensor added, rank <= 32 (kAddingOneRound): below it half of the places for workgroups are empty (us at 0.7 and like this: 12 x 749 x 1536, four states 25.6 and
 // 23.3, 8 x 534 x 2048, two states 16.5 and 15.2; of 900 calls 13 change, all faster, by 8 %).  Elsewhere
 // it is mixed: of 835 calls of one state above rank 32, 46 change, 32 to less time and 14 to more, 3.5 % less on average.
-// Float32 rows above rank 32 go down to one chunk with several states, whose loads a short call waits for (us with 2 or 3 chunks and with one: 1 x 273 x 1152
-// rank 48, two states 5.1 and 3.7, 2 x 404 x 512 rank 124 4.6 and 4.0; 700 calls of up to 30 MB), and at rank 128 where 3 chunks are the widest slab (1 x 439 x
-// 1152: 5.1 and 4.3).
-constexpr int narrow_slab(int m, int chunks, int kt2, bool f32, bool several_states) {
-  if (f32 && kt2 > 1 && chunks > 1 && (several_states || (kt2 == 4 && chunks == 3))) return 1;
-  return chunks <= 3 ? 0 : (m % 3 == 0 ? 3 : (m % 2 == 0 ? 2 : 0));
-}
 inline CachedTiling cached_tiling(const CachedCall& call, int chunks, int narrow, double one_round = 0.7) {
   CachedTiling best{chunks, 16};
   for (int cand = 15; cand >= 6; --cand)
